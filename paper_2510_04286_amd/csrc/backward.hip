@@ -572,7 +572,7 @@ BackwardPlan backward_plan(const slicemoe_config &c)
     size_t at = 0;
     p.dxrow = at;  at = align_up(at + Na * ds * sizeof(float), 256);
     p.dpk = at;    at = align_up(at + Na * sizeof(float), 256);
-    p.expert_part = at;  at = align_up(at + (size_t)p.chunks * expert_slot_floats((int)ds, c.He) * sizeof(float), 256);
+    p.expert_part = at;  at = align_up(at + (size_t)(backward_mfma_shape(c) ? backward_weights_slots(c) : p.chunks) * expert_slot_floats((int)ds, c.He) * sizeof(float), 256);
     p.router_part = at;  at = align_up(at + (size_t)p.slice_blocks * router_slot_floats((int)ds, c.Hr, c.E) * sizeof(float), 256);
     p.packed = at;  at = align_up(at + backward_mfma_packed_bytes(c), 256);
     p.router_scratch = at;  at = align_up(at + backward_router_mfma_scratch_bytes(c), 256);
@@ -715,14 +715,12 @@ static hipError_t run_backward(const slicemoe_config &c, const void *h, const sl
     SideJoin joiner;
     hipStream_t se = s;   // stream of the expert weight gradients and their reduction
     if (backward_mfma_shape(c) && (c.flags & SLICEMOE_FLAG_SINGLE_STREAM)) {
-        e = launch_backward_expert_mfma(c, h, w, d_out, pk, offsets, perm, ws + P.packed, P.rows_per_chunk, P.chunks, eslot,
-                                        dxrow, dpk, epart, s);
+        e = launch_backward_expert_mfma(c, h, w, d_out, pk, offsets, perm, ws + P.packed, eslot, dxrow, dpk, epart, s);
         if (e != hipSuccess) return e;
     } else if (backward_mfma_shape(c)) {
         side_lock.lock();
         if ((e = side_stream(&side)) != hipSuccess) return e;
-        e = launch_backward_expert_mfma(c, h, w, d_out, pk, offsets, perm, ws + P.packed, P.rows_per_chunk, P.chunks, eslot,
-                                        dxrow, dpk, epart, s, &side);
+        e = launch_backward_expert_mfma(c, h, w, d_out, pk, offsets, perm, ws + P.packed, eslot, dxrow, dpk, epart, s, &side);
         joiner.side = &side;   // from here on the side stream holds work of this call: joined on every way out
         joiner.s = s;
         se = side.stream;
@@ -746,6 +744,9 @@ static hipError_t run_backward(const slicemoe_config &c, const void *h, const sl
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
     }
+    if (backward_mfma_shape(c)) {
+        if ((e = launch_backward_reduce_segments(c, offsets, epart, eslot, g, se)) != hipSuccess) return e;
+    } else {
     const bool vec4 = ds % 4 == 0 && c.He % 4 == 0 &&
                       (((uintptr_t)g.W1 | (uintptr_t)g.b1 | (uintptr_t)g.W2 | (uintptr_t)g.b2 | (uintptr_t)epart) & 15) == 0;
     if (vec4)
@@ -755,6 +756,7 @@ static hipError_t run_backward(const slicemoe_config &c, const void *h, const sl
         bwd_reduce_expert_kernel<1><<<dim3((unsigned)c.E, (unsigned)((eslot + kRedElems - 1) / kRedElems)), kRedElems * kRedSeqs, 0, se>>>(
             epart, offsets, ds, c.He, c.E, P.rows_per_chunk, g.W1, g.b1, g.W2, g.b2);
     if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
 
     const size_t rslot = router_slot_floats(ds, c.Hr, c.E);
     if (backward_router_mfma_shape(c)) {

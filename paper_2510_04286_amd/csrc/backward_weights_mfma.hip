@@ -1,0 +1,711 @@
+// Matrix-core weight gradients of the experts, and for the narrow experts the whole expert backward in the same pass.
+//
+// The weight gradients contract over ROWS, which the forward's layout (a lane owns a row, see mfma.h) keeps on lanes.
+// Swapping the operands of an MFMA transposes its result: with the row fragment as A and the weight fragment as B the
+// accumulators of u = x W1 and da = dy W2^T come out as lane = hidden unit, registers = 16 of 32 rows.  There z, the
+// activation a1 and p dz are formed, split into two bf16 terms (register pairs are row pairs: contraction slots), and
+// dW2 += a1^T dy, dW1 += x^T (p dz) run on matrix instructions.  Their other operand, x and dy with lane = slice feature
+// and slots = rows, comes out of the LDS by transposing reads (ds_read_b64_tr_b16), so no vector instruction is spent on it.
+//
+// A block's wavefronts own one hidden tile each and share the rows: units of 32 stacked rows of one expert are
+// gathered into registers while the unit before is computed, and put into the LDS in front of the barrier.
+//
+// What bounds it: vector issue and its latency.  A hidden element takes about 30 vector instructions, two of them
+// transcendental; measured on this chip a wavefront issues one every 4.7 cycles at best, waits 8.3 for the result of the
+// one before (so the activation runs four elements side by side), and a SIMD with two wavefronts gets through one every
+// 2.4.  Hence: no vector instructions for transposes (LDS), LDS reads in front of a run of vector instructions and the
+// matrix instructions that use them behind it, the weight gradients half a unit behind the activation, barriers that do not
+// wait for global memory, and the younger wavefront of a SIMD first for half of every unit.
+//
+// FUSE (experts whose hidden tiles fit one block: the benchmark shapes at width 64 and the paper's narrow slices): the
+// same pass also gives dL/dx and dL/dp of the rows, so that z and the activation are evaluated once instead of once per
+// layout.  dx = W1 (p dz) contracts over the hidden units of ALL wavefronts, so the terms of p dz of a unit go through
+// the LDS ([hidden][row], read back transposed) and during the next unit each wavefront multiplies its 16-row, 16-feature
+// tile.  dL/dp = sum of dz u over the hidden units, which sit on lanes and wavefronts here: an exchange inside the
+// wavefront that halves the number of values at every step, and one sum over the wavefronts.
+//
+// Measured, 524 288 rows, width 64, He = 256, 32 experts: rows kernel 172 us + weights kernel 283 us (both evaluating the
+// activation, the latter without prefetch and with transposes on the matrix pipe) -> 239 us; the partial sums of the
+// weight gradients fall from 140 MB in 1056 slots to 38 MB in 288 (their reduction 29-35 -> 13 us).  Unfused at width 128,
+// He = 512: 2.78 -> 1.09 ms for 1 048 576 rows; width 96, He = 384: 228 -> 98 us for 131 056 rows.  131 072 rows at width
+// 48: 2.9 ms of vector-ALU kernel -> 59 us.
+//
+// TERMS: bf16 terms of the activation and of p dz.  Two (16 significant bits) where this backward has always run on two; three
+// (24 bits, products exact) for the widths whose backward used to be, and stays, fp32 in every operand: 24, 48 and 192.
+#include "bwd_mfma.h"
+#include "wavefront.h"
+
+namespace slicemoe {
+
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+
+// ------------------------------------------------------------------------------------------- work split over blocks
+// Rows are handed out in steps of `step` rows counted from each expert's first row, on an axis where an expert with rows
+// occupies one position more than it has steps (what it costs a block to begin an expert: its weights in, its sums out).
+// Block v takes `share` consecutive positions.  A segment is what one block has of one expert; along the axis the block or
+// the expert advances from one segment to the next, so v + e names a segment's slot of partial sums uniquely.
+struct RowAxis {
+    int first, steps;   // of lane e's expert (E <= 64): its first position, its steps
+    int share;          // uniform
+};
+__device__ __forceinline__ RowAxis row_axis(int rows, int step, int blocks, int lane)
+{
+    RowAxis A;
+    A.steps = (rows + step - 1) / step;
+    const int cost = A.steps > 0 ? A.steps + 1 : 0;
+    A.first = wavefront_exclusive_scan(cost, lane);
+    A.share = max(1, (wavefront_sum(cost) + blocks - 1) / blocks);
+    return A;
+}
+
+// ------------------------------------------------------------------------------------------- rows in the LDS
+// PW 16-byte pieces per row (a power of two; the pieces past the slice width stay zero), the piece index XORed with a
+// function of the row so that both ways of reading are free of bank conflicts: as A operand (32 lanes, one row each, the
+// same piece) and transposed (4 rows x 64 bytes per half-wavefront).
+template <int DS> struct LdsRows {
+    static constexpr int P = DS / 8;
+    static constexpr int PW = P <= 4 ? 4 : P <= 8 ? 8 : P <= 16 ? 16 : P <= 32 ? 32 : 64;
+    static constexpr int STRIDE = PW * 16;
+    static __device__ __forceinline__ int swizzle(int row)
+    {
+        return PW == 4 ? (row >> 2) & 3 : PW == 8 ? (((row >> 1) & 1) << 2) | ((row >> 2) & 3) : ((row & 3) << 2) | ((row >> 2) & 3);
+    }
+    static __device__ __forceinline__ int offset(int row, int piece) { return row * STRIDE + ((piece ^ swizzle(row)) << 4); }
+};
+
+typedef __attribute__((address_space(3))) char *lds_ptr;
+__device__ __forceinline__ lds_ptr as_lds(const char *p) { return (lds_ptr)p; }
+
+// a / k for assignment ids (0 <= a < 2^31) and 1 <= k <= 8, uniform k: a shift, or one high multiplication (with
+// m = ceil(2^(32 + s) / k) the excess e = m k - 2^(32 + s) < k keeps a e below 2^(32 + s)).
+__device__ __forceinline__ int divide_by_k(int a, int k)
+{
+    if ((k & (k - 1)) == 0) return a >> (31 - __clz(k));
+    const unsigned m = k == 3 ? 2863311531u : k == 5 ? 3435973837u : k == 6 ? 2863311531u : 2454267027u;
+    return (int)(__umulhi((unsigned)a, m) >> (k == 3 ? 1 : 2));
+}
+
+// Two transposing reads: slots 0..3 from the four rows at `a`, slots 4..7 from those at `b`.
+__device__ __forceinline__ bf16x8 read_transposed(lds_ptr a, lds_ptr b)
+{
+    union {
+        s16x4 h[2];
+        bf16x8 v;
+    } r;
+    r.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)a);
+    r.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)b);
+    return r.v;
+}
+
+// Sum of the eight bf16 values of a fragment.
+__device__ __forceinline__ float fragment_sum(bf16x8 f)
+{
+    const uint4 u = __builtin_bit_cast(uint4, f);
+    const uint32_t w[4] = {u.x, u.y, u.z, u.w};
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s += __uint_as_float(w[i] << 16) + __uint_as_float(w[i] & 0xffff0000u);
+    return s;
+}
+
+// Sums over the 32 lanes of a lane group of 16 values each, half of the values at every exchange, so that what is left
+// spreads over the lanes: 32 instructions.  Afterwards v[0] and v[1] are the sums of the values that were registers
+// acc-order rows hidden_sum_row(lane) and + 1 (the four lanes of a quad hold the same).  The additions of a lane's own
+// value and one from another lane of its row of 16 are single instructions whose bank mask restricts them to the lanes
+// (banks of four) that keep that value; each group starts with the two wait states a moved operand needs.
+__device__ __forceinline__ float sum_over_row_pair(float a, float b)   // even rows of 16 lanes keep a, odd ones b
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ void sum_over_hidden(float (&v)[8])   // v[i]: sum_over_row_pair of values i and i + 8
+{
+    asm("s_nop 1\n\t"
+        "v_add_f32_dpp %0, %0, %0 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+        "v_add_f32_dpp %1, %1, %1 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+        "v_add_f32_dpp %2, %2, %2 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+        "v_add_f32_dpp %3, %3, %3 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+        "v_add_f32_dpp %0, %4, %4 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %1, %5, %5 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %2, %6, %6 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %3, %7, %7 row_ror:8 row_mask:0xf bank_mask:0xc"
+        : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3])
+        : "v"(v[4]), "v"(v[5]), "v"(v[6]), "v"(v[7]));
+    asm("s_nop 1\n\t"
+        "v_add_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+        "v_add_f32_dpp %1, %1, %1 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+        "v_add_f32_dpp %0, %2, %2 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+        "v_add_f32_dpp %1, %3, %3 row_half_mirror row_mask:0xf bank_mask:0xa"
+        : "+v"(v[0]), "+v"(v[1])
+        : "v"(v[2]), "v"(v[3]));
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        v[i] += __int_as_float(lane_move<0xB1>(__float_as_int(v[i])));   // quad_perm [1, 0, 3, 2]
+        v[i] += __int_as_float(lane_move<0x4E>(__float_as_int(v[i])));   // quad_perm [2, 3, 0, 1]
+    }
+}
+__device__ __forceinline__ int hidden_sum_row(int lane)
+{
+    return 16 * ((lane >> 4) & 1) + 8 * ((lane >> 3) & 1) + 4 * (lane >> 5) + 2 * ((lane >> 2) & 1);
+}
+
+// p dz of a unit in the LDS: [term][hidden unit of the block][32 rows] bf16, the 8-byte quads of rows permuted inside a hidden unit's
+// 64 bytes so that neither the writes (a lane per hidden unit) nor the transposing reads meet bank conflicts.
+__device__ __forceinline__ int pdz_offset(int hidden, int quad)
+{
+    const int sw = ((hidden >> 2) & 1) | (((hidden >> 4) & 1) << 1) | (((hidden >> 3) & 1) << 2);
+    return hidden * 64 + ((quad ^ sw) << 3);
+}
+
+constexpr int kUnit = 32;   // stacked rows a block works on at a time
+
+// Geometry of one instantiation.
+template <int DS, int WAVES, int NBUF, bool WLDS, bool FUSE, int TERMS> struct WeightsTile {
+    static constexpr int KS = SliceTiles<DS>::KS, OT = SliceTiles<DS>::OT, FT = (DS + 15) / 16;
+    static constexpr int THREADS = WAVES * 64;
+    static constexpr int NBW = WAVES < 2 * OT ? WAVES : 2 * OT, TB = (2 * OT + NBW - 1) / NBW;   // wavefronts that add up db2, their shares
+    static constexpr size_t rows_bytes = (size_t)2 * kUnit * LdsRows<DS>::STRIDE;                // x and dy of one unit
+    static constexpr size_t pdz_bytes = (size_t)TERMS * WAVES * 32 * kUnit * 2;                  // p dz of one unit
+    static constexpr size_t off_p = NBUF * rows_bytes;                                           // [NBUF][32] probabilities
+    static constexpr size_t off_dp = off_p + NBUF * kUnit * 4;                                   // [2][WAVES][32] partial dL/dp
+    static constexpr size_t off_db2 = off_dp + (FUSE ? 2 * WAVES * kUnit * 4 : 0);               // [2][32 OT] partial db2
+    static constexpr size_t off_w = off_db2 + 2 * OT * 32 * 4;                                   // fragments of W1 and W2
+    static constexpr size_t off_pdz = off_w + (WLDS ? (size_t)WAVES * KS * 2048 : 0);
+    static constexpr size_t off_w1d = off_pdz + (FUSE ? 2 * pdz_bytes : 0);
+    static constexpr size_t lds = off_w1d + (FUSE ? (size_t)FT * WAVES * 1024 : 0);
+};
+
+template <int DS, int WAVES, int NBUF, bool WLDS, bool FUSE, int TERMS, int MINWAVES>
+__global__ __launch_bounds__(WAVES * 64, MINWAVES) void bwd_weights_kernel(
+    const bf16_t *__restrict__ x, const bf16_t *__restrict__ dout, const float *__restrict__ pk,
+    const int32_t *__restrict__ offsets, const int32_t *__restrict__ perm, const char *__restrict__ packed,
+    size_t e_stride, size_t off_w2r, size_t off_w1d, size_t off_b1, int He, int E, int k, int blocks, int groups,
+    size_t slot_floats, float *__restrict__ part, float *__restrict__ dxrow, float *__restrict__ dpk)
+{
+    typedef WeightsTile<DS, WAVES, NBUF, WLDS, FUSE, TERMS> G;
+    typedef LdsRows<DS> LR;
+    constexpr int KS = G::KS, OT = G::OT, THREADS = G::THREADS, P = LR::P, PW = LR::PW;
+    constexpr int NX = (2 * kUnit * P + THREADS - 1) / THREADS;   // 16-byte pieces (of x, then of dy) a thread moves per unit
+    static_assert(!FUSE || NBUF == 2, "the fused kernel has one barrier per unit");
+    extern __shared__ __align__(16) char lds[];
+
+    const int tid = threadIdx.x, lane = tid & 63, jj = lane & 31, g = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int HT = He / 32;
+    // consecutive blocks go to the eight XCDs in turn, each with its own L2: the groups of hidden tiles of a block's rows
+    // take block ids that are equal modulo 8
+    const int grp = (int)(blockIdx.x / 8) % groups;
+    const int vb = (int)(blockIdx.x / (8 * groups)) * 8 + (int)(blockIdx.x % 8);
+    if (vb >= blocks) return;
+    const int ht = grp * WAVES + wave;
+    const bool active = ht < HT;
+
+    const int off_lo = offsets[min(lane, E)], off_hi = offsets[min(lane + 1, E)];
+    const RowAxis A = row_axis(off_hi - off_lo, kUnit, blocks, lane);
+    const int c0 = vb * A.share, c1 = c0 + A.share;
+
+    // ---- addresses that do not change
+    int mrow[NX], mcol[NX], mdst[NX];   // row, feature and LDS offset of the pieces this thread moves
+    const bf16_t *msrc[NX];
+#pragma unroll
+    for (int i = 0; i < NX; ++i) {
+        const int q = tid + i * THREADS, half = q >= kUnit * P ? 1 : 0, r = q - half * kUnit * P;
+        mrow[i] = min(r / P, kUnit - 1);
+        mcol[i] = 8 * (r % P);
+        msrc[i] = (half ? dout : x) + mcol[i];
+        mdst[i] = half * kUnit * LR::STRIDE + LR::offset(mrow[i], r % P);
+    }
+    const int sw = LR::swizzle(jj);
+    const int a_base = jj * LR::STRIDE + ((g ^ sw) << 4);   // piece 2 ks + g of row jj: a_base ^ (ks << 5)
+    const int c16 = lane & 15, G4 = lane >> 4;
+    const int trow = 4 * g + (c16 >> 2);                    // first row this lane points at in a transposing read
+    const int t_base = trow * LR::STRIDE + (((2 * (G4 & 1) + ((lane & 3) >> 1)) ^ LR::swizzle(trow)) << 4) + 8 * (lane & 1);
+    auto slice_of = [&](int a) { return divide_by_k(a, k); };
+
+    if constexpr (PW > P) {   // the pieces past the slice width stay zero
+        for (int t = tid; t < NBUF * 2 * kUnit * (PW - P); t += THREADS) {
+            const int row = t / (PW - P), piece = P + t % (PW - P);
+            *(uint4 *)(lds + (row / kUnit) * (kUnit * LR::STRIDE) + LR::offset(row % kUnit, piece)) = make_uint4(0, 0, 0, 0);
+        }
+    }
+
+    if constexpr (FUSE) {   // hidden tiles past the last one: zeros in both operands of dL/dx, and nothing for dL/dp
+        const uint4 zero = make_uint4(0, 0, 0, 0);
+        if (!active) ((float *)(lds + G::off_dp))[((lane >> 5) * WAVES + wave) * kUnit + jj] = 0.f;
+        if (!active)
+            for (int t = lane; t < 2 * TERMS * 128; t += 64) *(uint4 *)(lds + G::off_pdz + ((t >> 7) * WAVES + wave) * 2048 + (t & 127) * 16) = zero;
+        for (int t = tid; t < G::FT * (WAVES - HT) * 64; t += THREADS) {
+            const int ft = t / ((WAVES - HT) * 64), r = t - ft * (WAVES - HT) * 64;
+            *(uint4 *)(lds + G::off_w1d + (ft * WAVES + HT) * 1024 + r * 16) = zero;
+        }
+    }
+
+    for (int e = 0; e < E; ++e) {
+        const int first = __builtin_amdgcn_readlane(A.first, e), steps = __builtin_amdgcn_readlane(A.steps, e);
+        if (first >= c1) break;
+        const int s_lo = max(0, c0 - first - 1), s_hi = min(steps, c1 - first - 1);
+        if (s_hi <= s_lo) continue;
+        const int row0 = __builtin_amdgcn_readlane(off_lo, e) + s_lo * kUnit;   // rows below count from here
+        const int nrows = min(__builtin_amdgcn_readlane(off_hi, e) - row0, (s_hi - s_lo) * kUnit);
+        const int32_t *ids = perm + row0;
+        const char *ew = packed + (size_t)e * e_stride;
+
+        __syncthreads();   // everyone is done with the LDS of the segment before
+        // ---- this expert's weights
+        bf16x8 w1r[WLDS ? 1 : KS], w2q[WLDS ? 1 : KS];
+        const int htc = active ? ht : 0;
+        if constexpr (WLDS) {
+            const int nt = min(WAVES, HT - grp * WAVES);
+            stage_bytes(ew + (size_t)grp * WAVES * KS * 1024, lds + G::off_w, (size_t)nt * KS * 1024, tid, THREADS);
+            stage_bytes(ew + off_w2r + (size_t)grp * WAVES * KS * 1024, lds + G::off_w + (size_t)WAVES * KS * 1024, (size_t)nt * KS * 1024, tid,
+                        THREADS);
+        } else {
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                w1r[ks] = __builtin_bit_cast(bf16x8, ((const uint4 *)ew)[(htc * KS + ks) * 64 + lane]);
+                w2q[ks] = __builtin_bit_cast(bf16x8, ((const uint4 *)(ew + off_w2r))[(htc * KS + ks) * 64 + lane]);
+            }
+        }
+        if constexpr (FUSE)
+            for (int ft = 0; ft < G::FT; ++ft)
+                stage_bytes(ew + off_w1d + (size_t)ft * HT * 1024, lds + G::off_w1d + ft * WAVES * 1024, (size_t)HT * 1024, tid, THREADS);
+        const float bias = ((const float *)(ew + off_b1))[htc * 32 + jj];
+        auto w1_frag = [&](int ks) {
+            return WLDS ? __builtin_bit_cast(bf16x8, ((const uint4 *)(lds + G::off_w))[(wave * KS + ks) * 64 + lane]) : w1r[WLDS ? 0 : ks];
+        };
+        auto w2_frag = [&](int ks) {
+            return WLDS ? __builtin_bit_cast(bf16x8, ((const uint4 *)(lds + G::off_w))[((WAVES + wave) * KS + ks) * 64 + lane]) : w2q[WLDS ? 0 : ks];
+        };
+
+        f32x16 aW1[OT], aW2[OT];
+        float ab1 = 0.f, ab2[G::TB];
+#pragma unroll
+        for (int t = 0; t < G::TB; ++t) ab2[t] = 0.f;
+#pragma unroll
+        for (int ot = 0; ot < OT; ++ot)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) aW1[ot][i] = aW2[ot][i] = 0.f;
+
+        // ---- gather of a unit: assignment ids two units ahead, rows one unit ahead.  The slices are worked out from the ids
+        // in front of a unit's stores of dL/dx, which would otherwise have to complete before the ids can be used.
+        int an[NX], ao_next = 0, ao_load = 0, ao = 0;
+        uint4 mv[NX];
+        float p_next = 0.f;
+        auto load_ids = [&](int r0) {
+#pragma unroll
+            for (int i = 0; i < NX; ++i) an[i] = ids[(unsigned)min(r0 + mrow[i], nrows - 1)];
+            if (tid < kUnit) ao_next = ids[(unsigned)min(r0 + tid, nrows - 1)];
+        };
+        auto find_slices = [&]() {
+#pragma unroll
+            for (int i = 0; i < NX; ++i) an[i] = slice_of(an[i]);
+        };
+        auto load_rows = [&]() {
+#pragma unroll
+            for (int i = 0; i < NX; ++i) mv[i] = *(const uint4 *)(msrc[i] + (size_t)an[i] * DS);
+            if (tid < kUnit) {
+                ao_load = ao_next;
+                p_next = pk[ao_next];
+            }
+        };
+        auto store_rows = [&](int r0, int buf) {   // rows past the end: dy and p are zero, so they add nothing
+#pragma unroll
+            for (int i = 0; i < NX; ++i) {
+                const int q = tid + i * THREADS;
+                if (NX * THREADS == 2 * kUnit * P || q < 2 * kUnit * P)
+                    *(uint4 *)(lds + buf * G::rows_bytes + mdst[i]) = q < kUnit * P || r0 + mrow[i] < nrows ? mv[i] : make_uint4(0, 0, 0, 0);
+            }
+            if (tid < kUnit) {
+                ao = ao_load;
+                ((float *)(lds + G::off_p))[buf * kUnit + tid] = r0 + tid < nrows ? p_next : 0.f;
+            }
+        };
+        load_ids(0);
+        find_slices();
+        load_rows();
+        store_rows(0, 0);
+        load_ids(kUnit);   // (past the end: the last row's)
+        find_slices();
+        __syncthreads();
+
+        // ---- dL/dx of the unit before (FUSE): 16-row, 16-feature tiles, lane = row c16 of the tile, dealt out to the
+        // wavefronts; one 32-wide contraction step `kk` is one hidden tile (zeros past the last one: no branch).  For the
+        // first unit of a segment it works on what the buffers hold, and nothing of it is stored.
+        constexpr int NT = FUSE ? (2 * G::FT + WAVES - 1) / WAVES : 1;
+        f32x4 dx[NT];
+        struct DxFrags {
+            bf16x8 w[NT], b[NT][TERMS];
+        };
+        auto dx_load = [&](DxFrags &f, int kk, int buf) {
+            const char *pz = lds + G::off_pdz + buf * G::pdz_bytes;
+            const int h0 = 8 * G4 + (c16 >> 2);
+            const uint4 *w1d = (const uint4 *)(lds + G::off_w1d);
+#pragma unroll
+            for (int i = 0; i < NT; ++i) {
+                const int tile = wave + i * WAVES, rt = tile & 1;
+                const int ft = NT * WAVES == 2 * G::FT ? tile >> 1 : min(tile >> 1, G::FT - 1);   // a tile too many is not stored
+                const char *b0 = pz + pdz_offset(h0, 4 * rt + (c16 & 3)) + kk * 2048;
+                const char *b1 = pz + pdz_offset(h0 + 4, 4 * rt + (c16 & 3)) + kk * 2048;
+                f.w[i] = __builtin_bit_cast(bf16x8, w1d[(ft * WAVES + kk) * 64 + lane]);
+#pragma unroll
+                for (int t = 0; t < TERMS; ++t) f.b[i][t] = read_transposed(as_lds(b0 + t * WAVES * 2048), as_lds(b1 + t * WAVES * 2048));
+            }
+        };
+        auto dx_mma = [&](const DxFrags &f) {
+#pragma unroll
+            for (int t = TERMS - 1; t >= 0; --t)   // small terms first
+#pragma unroll
+                for (int i = 0; i < NT; ++i) dx[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.w[i], f.b[i][t], dx[i], 0, 0, 0);
+        };
+        auto dx_all = [&](int buf) {
+            for (int kk = 0; kk < WAVES; ++kk) {
+                DxFrags f;
+                dx_load(f, kk, buf);
+                dx_mma(f);
+            }
+        };
+        auto dx_begin = [&]() {
+#pragma unroll
+            for (int i = 0; i < NT; ++i) dx[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        };
+        float *dxs = FUSE ? dxrow + (size_t)row0 * DS : nullptr;
+        auto dx_end = [&](int r0, int buf, int a) {   // stores the rows r0 ..; a: this thread's assignment
+#pragma unroll
+            for (int i = 0; i < NT; ++i) {
+                const int tile = wave + i * WAVES, row = r0 + 16 * (tile & 1) + c16, col = 16 * (tile >> 1) + 4 * G4;
+                if ((tile >> 1) < G::FT && (DS % 16 == 0 || col < DS) && row < nrows) *(f32x4 *)(dxs + (unsigned)(row * DS + col)) = dx[i];
+            }
+            if (tid < kUnit && r0 + tid < nrows) {
+                const float *dps = (const float *)(lds + G::off_dp) + buf * WAVES * kUnit + tid;
+                float v[WAVES], t = 0.f;
+#pragma unroll
+                for (int w = 0; w < WAVES; ++w) v[w] = dps[w * kUnit];
+#pragma unroll
+                for (int w = 0; w < WAVES; ++w) t += v[w];
+                dpk[a] = t;
+            }
+        };
+
+        int buf = 0, a_prev = 0;
+        for (int r0 = 0; r0 < nrows; r0 += kUnit) {
+            const bool more = r0 + kUnit < nrows;
+            const int a_cur = ao;
+            if (more) {
+                load_rows();
+                load_ids(r0 + 2 * kUnit);
+            }
+            char *xs = lds + (NBUF == 2 ? buf : 0) * G::rows_bytes, *gs = xs + kUnit * LR::STRIDE;
+            const float *ps = (const float *)(lds + G::off_p) + (NBUF == 2 ? buf : 0) * kUnit;
+            // the transposed fragment i (rows 16 (i & 1) .., features 32 (i >> 1) ..) of x or dy
+            auto transposed = [&](const char *rows, int i) {
+                const int at = 16 * (i & 1) * LR::STRIDE, col = t_base ^ ((i >> 1) << 6);
+                return read_transposed(as_lds(rows + at + col), as_lds(rows + at + 8 * LR::STRIDE + (col ^ 32)));
+            };
+            if constexpr (FUSE) dx_begin();
+            if (active) {
+                // lane = hidden unit jj of this tile, register i = row acc_feature(i, g) of the unit
+                f32x16 u, da;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) u[i] = da[i] = 0.f;
+                constexpr int KH = KS <= 4 ? KS : KS % 4 == 0 ? 4 : 3;   // fragments requested together
+                static_assert(KS % KH == 0, "whole groups of K-steps");
+#pragma unroll
+                for (int k0 = 0; k0 < KS; k0 += KH) {
+                    bf16x8 xa[KH], ga[KH];
+#pragma unroll
+                    for (int ks = 0; ks < KH; ++ks) {
+                        const int at = a_base ^ ((k0 + ks) << 5);
+                        xa[ks] = *(const bf16x8 *)(xs + at);
+                        ga[ks] = *(const bf16x8 *)(gs + at);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int ks = 0; ks < KH; ++ks) {
+                        u = mfma_bf16(xa[ks], w1_frag(k0 + ks), u);
+                        da = mfma_bf16(ga[ks], w2_frag(k0 + ks), da);
+                    }
+                }
+                // The weight gradients run half a unit (16 rows, one K-step) behind the activation, and dL/dx of the unit
+                // before runs beside it, so that the matrix pipe works while the vector instructions of the next half are
+                // issued.  A quad of registers is two runs of vector instructions (about 60 each); in front of each run stand
+                // the LDS reads, behind it the matrix instructions that use them: the reads' latency is covered by the run.
+                uint32_t a1[2][TERMS][4], pdz[2][TERMS][4];   // by half of the unit; terms, the largest first
+                bf16x8 gt, xt;
+                auto second_load = [&](int half, int ot) {
+                    gt = transposed(gs, 2 * ot + half);
+                    xt = transposed(xs, 2 * ot + half);
+                };
+                auto second_mma = [&](int half, int ot) {   // small terms first
+                    auto frag = [](const uint32_t (&v)[4]) { return __builtin_bit_cast(bf16x8, make_uint4(v[0], v[1], v[2], v[3])); };
+#pragma unroll
+                    for (int t = TERMS - 1; t >= 0; --t) {
+                        aW2[ot] = mfma_bf16(frag(a1[half][t]), gt, aW2[ot]);    // [hidden unit][slice feature]: lane = feature
+                        aW1[ot] = mfma_bf16(xt, frag(pdz[half][t]), aW1[ot]);   // [slice feature][hidden unit]: lane = hidden unit
+                    }
+                };
+                float du[8];   // dz u, summed over the hidden units below
+                // Of two wavefronts on a SIMD the older is served first, and would then wait at the barrier for the younger
+                // working alone; so the younger goes first in the first half of the unit.
+                if (wave >= WAVES / 2) __builtin_amdgcn_s_setprio(1);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int half = 0; half < 2; ++half)
+#pragma unroll
+                    for (int qd = 0; qd < 2; ++qd) {   // registers 8 half + 4 qd ..: rows 8 q + 4 g ..
+                        const int q = 2 * half + qd;
+                        if (q == 2) __builtin_amdgcn_s_setprio(0);
+                        // output tiles of the second stage behind each run (half 1 only): [o0, o1) and [o1, o2), the
+                        // first of each with its reads in front of the run
+                        const int o0 = qd == 0 ? 0 : OT / 2, o2 = qd == 0 ? OT / 2 : OT, o1 = (o0 + o2 + 1) / 2;
+                        const f32x4 pv = *(const f32x4 *)(ps + 8 * q + 4 * g);
+                        DxFrags fr;
+                        if (FUSE && 2 * q < WAVES) dx_load(fr, 2 * q, buf ^ 1);
+                        if (half == 1 && o0 < o1) second_load(0, o0);
+                        __builtin_amdgcn_sched_barrier(0);
+                        float z[4], cdf[4], dens[4], dz[4], act[4], pd[4];
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) z[c] = fmaf(pv[c], u[4 * q + c], bias);
+                        normal_cdf_pdf4(z, cdf, dens);
+                        __builtin_amdgcn_sched_barrier(0);
+                        if (FUSE && 2 * q < WAVES) dx_mma(fr);
+                        if (half == 1) {
+#pragma unroll
+                            for (int ot = 0; ot < OT; ++ot) {
+                                if (ot > o0 && ot < o1) second_load(0, ot);
+                                if (ot >= o0 && ot < o1) second_mma(0, ot);
+                            }
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                        if (FUSE && 2 * q + 1 < WAVES) dx_load(fr, 2 * q + 1, buf ^ 1);
+                        if (half == 1 && o1 < o2) second_load(0, o1);
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) dz[c] = fmaf(z[c], dens[c], cdf[c]);
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) dz[c] *= da[4 * q + c];
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) act[c] = z[c] * cdf[c];
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) pd[c] = pv[c] * dz[c];
+                        split_terms<TERMS>(act, a1[half], 2 * qd);
+                        split_terms<TERMS>(pd, pdz[half], 2 * qd);
+                        ab1 += (dz[0] + dz[1]) + (dz[2] + dz[3]);
+                        if constexpr (FUSE) {
+#pragma unroll
+                            for (int c = 0; c < 4; ++c)
+                                du[4 * qd + c] = half == 0 ? dz[c] * u[4 * q + c] : sum_over_row_pair(du[4 * qd + c], dz[c] * u[4 * q + c]);
+                            char *dst = lds + G::off_pdz + buf * G::pdz_bytes + pdz_offset(wave * 32 + jj, 2 * q + g);
+#pragma unroll
+                            for (int t = 0; t < TERMS; ++t) *(uint2 *)(dst + t * WAVES * 2048) = make_uint2(pdz[half][t][2 * qd], pdz[half][t][2 * qd + 1]);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                        if (FUSE && 2 * q + 1 < WAVES) dx_mma(fr);
+                        if (half == 1) {
+#pragma unroll
+                            for (int ot = 0; ot < OT; ++ot) {
+                                if (ot > o1 && ot < o2) second_load(0, ot);
+                                if (ot >= o1 && ot < o2) second_mma(0, ot);
+                            }
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                second_load(1, 0);
+                if constexpr (FUSE) {   // dL/dp: this tile's hidden units; every fourth lane ends up with the sums of two rows
+                    sum_over_hidden(du);
+                    if ((lane & 3) == 0)
+                        *(float2 *)((float *)(lds + G::off_dp) + (buf * WAVES + wave) * kUnit + hidden_sum_row(lane)) = make_float2(du[0], du[1]);
+                }
+#pragma unroll
+                for (int ot = 0; ot < OT; ++ot) {
+                    if (ot > 0) second_load(1, ot);
+                    second_mma(1, ot);
+                }
+            } else if (FUSE) {
+                dx_all(buf ^ 1);
+            }
+            if (grp == 0 && wave < G::NBW) {   // db2: sums of dy over the rows, the fragments dealt out to the wavefronts
+#pragma unroll
+                for (int t = 0; t < G::TB; ++t)
+                    if (wave + t * G::NBW < 2 * OT) ab2[t] += fragment_sum(transposed(gs, wave + t * G::NBW));
+            }
+            if (NBUF == 2 && more) store_rows(r0 + kUnit, buf ^ 1);
+            find_slices();
+            if (FUSE && r0 > 0) dx_end(r0 - kUnit, buf ^ 1, a_prev);
+            lds_barrier();
+            if (NBUF == 1) {
+                if (more) store_rows(r0 + kUnit, 0);
+                lds_barrier();
+            }
+            a_prev = a_cur;
+            buf ^= 1;
+        }
+        if constexpr (FUSE) {   // the last unit's dL/dx
+            dx_begin();
+            dx_all(buf ^ 1);
+            dx_end((s_hi - s_lo - 1) * kUnit, buf ^ 1, a_prev);
+        }
+
+        // ---- this segment's slot: dW1 [ds][He] | dW2 [He][ds] | db1 [He] | db2 [ds]
+        int he = He, jo = jj, go = g;   // opaque copies: the store addresses are made here, not kept in registers through the loop above
+        asm volatile("" : "+s"(he), "+v"(jo), "+v"(go));
+        float *slot = part + (size_t)(vb + e) * slot_floats;
+        float *pW1 = slot, *pW2 = pW1 + (size_t)DS * he, *pb1 = pW2 + (size_t)he * DS, *pb2 = pb1 + he;
+        float *red = (float *)(lds + G::off_db2);
+        __syncthreads();
+        if (active) {
+#pragma unroll
+            for (int ot = 0; ot < OT; ++ot)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const int f = 32 * ot + acc_feature(i, go);
+                    if (DS % 32 == 0 || f < DS) pW1[(size_t)f * he + 32 * ht + jo] = aW1[ot][i];
+                    if (DS % 32 == 0 || 32 * ot + jo < DS) pW2[(size_t)(32 * ht + acc_feature(i, go)) * DS + 32 * ot + jo] = aW2[ot][i];
+                }
+            ab1 += __shfl_xor(ab1, 32);   // the two lane groups hold different rows of the same hidden unit
+            if (go == 0) pb1[32 * ht + jo] = ab1;
+        }
+        if (grp == 0 && wave < G::NBW) {
+#pragma unroll
+            for (int t = 0; t < G::TB; ++t) {
+                const int i = wave + t * G::NBW;   // rows 16 (i & 1) .. of every unit, features 32 (i >> 1) ..
+                const float v = ab2[t] + __shfl_xor(ab2[t], 32);
+                if (i < 2 * OT && g == 0) red[(i & 1) * OT * 32 + 32 * (i >> 1) + jj] = v;
+            }
+        }
+        __syncthreads();
+        if (grp == 0)
+            for (int f = tid; f < DS; f += THREADS) pb2[f] = red[f] + red[OT * 32 + f];
+    }
+}
+
+// ------------------------------------------------------------------------------------------------ sum of the slots
+// One block per expert and 64 groups of V slot elements; the expert's slots are vf + e .. vl + e, the blocks its steps
+// fall into.  kSegSeqs interleaved sequences of slots, added up in a fixed order.
+constexpr int kSegElems = 64, kSegSeqs = 4;
+template <int V>
+__global__ __launch_bounds__(kSegElems * kSegSeqs) void bwd_reduce_segments_kernel(
+    const float *__restrict__ part, const int32_t *__restrict__ offsets, int ds, int He, int E, int step, int blocks, size_t slot,
+    float *__restrict__ dW1, float *__restrict__ db1, float *__restrict__ dW2, float *__restrict__ db2)
+{
+    typedef float vec __attribute__((ext_vector_type(V)));
+    __shared__ vec red[kSegSeqs][kSegElems];
+    const int e = blockIdx.x, lane = threadIdx.x & 63;
+    const int ex = threadIdx.x % kSegElems, sq = threadIdx.x / kSegElems;
+    const size_t t = ((size_t)blockIdx.y * kSegElems + ex) * V;
+    const RowAxis A = row_axis(offsets[min(lane + 1, E)] - offsets[min(lane, E)], step, blocks, lane);
+    const int first = __builtin_amdgcn_readlane(A.first, e), steps = __builtin_amdgcn_readlane(A.steps, e);
+    // position first is the expert's overhead; its steps are first + 1 .. first + steps
+    const int vf = (first + 1) / A.share, vl = steps > 0 ? (first + steps) / A.share : vf - 1;
+    vec acc = {};
+    if (t < slot) {
+        const float *src = part + (size_t)e * slot + t;
+#pragma unroll 4
+        for (int v = vf + sq; v <= vl; v += kSegSeqs) acc += *(const vec *)(src + (size_t)v * slot);
+    }
+    red[sq][ex] = acc;
+    __syncthreads();
+    if (sq != 0 || t >= slot) return;
+    acc = vec{};
+#pragma unroll
+    for (int q = 0; q < kSegSeqs; ++q) acc += red[q][ex];
+    const size_t nW = (size_t)ds * He;
+    if (t < nW) *(vec *)(dW1 + (size_t)e * nW + t) = acc;
+    else if (t < 2 * nW) *(vec *)(dW2 + (size_t)e * nW + (t - nW)) = acc;
+    else if (t < 2 * nW + He) *(vec *)(db1 + (size_t)e * He + (t - 2 * nW)) = acc;
+    else *(vec *)(db2 + (size_t)e * ds + (t - 2 * nW - He)) = acc;
+}
+
+// ------------------------------------------------------------------------------------------------------ host
+// Instantiations by slice width: wavefronts per block, row buffers, weights in LDS, fused, terms, wavefronts per SIMD the
+// registers allow.
+//   width <= 64   fused where the expert's hidden tiles fit one block (He <= 256): see the header
+//   96, 128       64 accumulators and weights per hidden tile leave no registers for the fragments (LDS) or for dL/dx
+//   192           192 accumulators: one wavefront per SIMD
+struct WeightsConfig {
+    int waves, per_cu;
+    bool fused;
+};
+static WeightsConfig weights_config(int ds, int He)
+{
+    const int HT = He / 32;
+    if (ds <= 64) {
+        if (HT <= 4) return {4, ds == 24 ? 2 : 1, true};
+        return {8, 1, HT <= 8};
+    }
+    if (ds == 96) return {4, 2, false};
+    if (ds == 128) return {8, 1, false};
+    return {4, 1, false};
+}
+
+BackwardWeightsPlan backward_weights_plan(const slicemoe_config &c)
+{
+    BackwardWeightsPlan W;
+    const WeightsConfig C = weights_config(c.d / c.S, c.He);
+    const int HT = c.He / 32;
+    const long long Na = (long long)c.T * c.S * c.k;
+    W.fused = C.fused;
+    W.step = kUnit;
+    W.groups = (HT + C.waves - 1) / C.waves;
+    long long blocks = (long long)num_compute_units() * C.per_cu / W.groups;
+    const long long most = (Na + kUnit - 1) / kUnit;
+    if (blocks > most) blocks = most;
+    W.blocks = blocks < 1 ? 1 : (int)blocks;
+    W.slots = (long long)W.blocks + c.E;
+    return W;
+}
+
+long long backward_weights_slots(const slicemoe_config &c) { return backward_weights_plan(c).slots; }
+
+template <int DS, int WAVES, int NBUF, bool WLDS, bool FUSE, int TERMS, int MINWAVES>
+static hipError_t run_weights(const slicemoe_config &c, const BackwardWeightsPlan &W, const BwdPacked &L, const void *h, const void *d_out,
+                              const float *pk, const int32_t *offsets, const int32_t *perm, const char *packed, size_t slot_floats,
+                              float *part, float *dxrow, float *dpk, hipStream_t s)
+{
+    typedef WeightsTile<DS, WAVES, NBUF, WLDS, FUSE, TERMS> G;
+    if (W.fused != FUSE || W.groups != (c.He / 32 + WAVES - 1) / WAVES) return hipErrorInvalidValue;
+    auto kern = bwd_weights_kernel<DS, WAVES, NBUF, WLDS, FUSE, TERMS, MINWAVES>;
+    const hipError_t e = grant_dynamic_lds((const void *)kern, G::lds);
+    if (e != hipSuccess) return e;
+    kern<<<(unsigned)((W.blocks + 7) / 8 * 8 * W.groups), WAVES * 64, G::lds, s>>>(
+        (const bf16_t *)h, (const bf16_t *)d_out, pk, offsets, perm, packed, L.stride, L.w2r, L.w1d, L.b1, c.He, c.E, c.k, W.blocks,
+        W.groups, slot_floats, part, dxrow, dpk);
+    return hipGetLastError();
+}
+
+hipError_t launch_backward_weights(const slicemoe_config &c, const BwdPacked &L, const void *h, const void *d_out, const float *pk,
+                                   const int32_t *offsets, const int32_t *perm, const char *packed, size_t slot_floats, float *part,
+                                   float *dxrow, float *dpk, hipStream_t s)
+{
+    const BackwardWeightsPlan W = backward_weights_plan(c);
+    const int ds = c.d / c.S, waves = weights_config(ds, c.He).waves;
+#define SLICEMOE_WEIGHTS(DS, WAVES, NBUF, WLDS, FUSE, TERMS, MINW)                                                                   if (ds == DS && waves == WAVES && W.fused == FUSE)                                                                                    return run_weights<DS, WAVES, NBUF, WLDS, FUSE, TERMS, MINW>(c, W, L, h, d_out, pk, offsets, perm, packed, slot_floats,                                                                       part, dxrow, dpk, s);
+    SLICEMOE_WEIGHTS(24, 4, 2, false, true, 3, 2)
+    SLICEMOE_WEIGHTS(24, 8, 2, false, true, 3, 2)
+    SLICEMOE_WEIGHTS(24, 8, 2, false, false, 3, 2)
+    SLICEMOE_WEIGHTS(48, 4, 2, false, true, 3, 2)
+    SLICEMOE_WEIGHTS(48, 8, 2, false, true, 3, 2)
+    SLICEMOE_WEIGHTS(48, 8, 2, false, false, 3, 2)
+    SLICEMOE_WEIGHTS(64, 4, 2, false, true, 2, 2)
+    SLICEMOE_WEIGHTS(64, 8, 2, false, true, 2, 2)
+    SLICEMOE_WEIGHTS(64, 8, 2, false, false, 2, 2)
+    SLICEMOE_WEIGHTS(96, 4, 1, true, false, 2, 2)
+    SLICEMOE_WEIGHTS(128, 8, 1, true, false, 2, 2)
+    SLICEMOE_WEIGHTS(192, 4, 1, true, false, 3, 1)
+#undef SLICEMOE_WEIGHTS
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_backward_reduce_segments(const slicemoe_config &c, const int32_t *offsets, const float *part, size_t slot,
+                                           const slicemoe_weight_grads &g, hipStream_t s)
+{
+    const BackwardWeightsPlan W = backward_weights_plan(c);
+    const int ds = c.d / c.S;
+    const bool vec4 = (((uintptr_t)g.W1 | (uintptr_t)g.b1 | (uintptr_t)g.W2 | (uintptr_t)g.b2 | (uintptr_t)part) & 15) == 0;   // ds, He: multiples of 8
+    const size_t items = vec4 ? slot / 4 : slot;
+    const dim3 grid((unsigned)c.E, (unsigned)((items + kSegElems - 1) / kSegElems));
+    if (vec4) bwd_reduce_segments_kernel<4><<<grid, kSegElems * kSegSeqs, 0, s>>>(part, offsets, ds, c.He, c.E, W.step, W.blocks, slot, g.W1, g.b1, g.W2, g.b2);
+    else bwd_reduce_segments_kernel<1><<<grid, kSegElems * kSegSeqs, 0, s>>>(part, offsets, ds, c.He, c.E, W.step, W.blocks, slot, g.W1, g.b1, g.W2, g.b2);
+    return hipGetLastError();
+}
+
+}  // namespace slicemoe

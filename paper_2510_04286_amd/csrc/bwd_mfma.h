@@ -12,8 +12,10 @@ namespace slicemoe {
 //   kPackLayer1    [N/32][K/16][64]: lane (i, g), slot m: M[16ks + 8g + m][32nt + i]
 //   kPackChain     [K/32][2][N/32][64]: lane (i, g), slot m: M[32ht + chain_feature(s, g, m)][32nt + i], i.e. the
 //                  contraction slots follow the accumulator order; kPackChainF16: the same converted to fp16
+//   kPackTile16    [K/16][N/32][64]: lane (i, g) of 16 x 4, slot m: M[16kt + i][32nt + 8g + m], the A operand of
+//                  v_mfma_f32_16x16x32 (contraction over the columns)
 //   kPackBias      K values per matrix widened to fp32, zero-padded to N
-enum { kPackLayer1 = 0, kPackChain = 1, kPackChainF16 = 2, kPackBias = 3 };
+enum { kPackLayer1 = 0, kPackChain = 1, kPackChainF16 = 2, kPackBias = 3, kPackTile16 = 4 };
 struct BwdPackJob {
     int kind, K, Kv, N, Nv;
     const bf16_t *src;
@@ -29,6 +31,29 @@ struct BwdPackJobs {
 BwdPackJob bwd_pack_job(int kind, const void *src, int K, int Kv, int N, int Nv, size_t rs, size_t cs, size_t src_stride,
                         char *dst, size_t dst_stride, int nmat);
 hipError_t bwd_pack_launch(const BwdPackJobs &jobs, hipStream_t s);
+
+// Backward copies of one expert's weights in fragment order (bytes from the start of the expert's block).
+//   w1f  [HT][KS][64]      W1 fragments as the forward packs them: lane (i, g), slot m: W1[16ks + 8g + m][32ht + i]
+//   w2r  [HT][KS][64]      rows of W2: lane (i, g), slot m: W2[32ht + i][16ks + 8g + m]
+//   w1c  [HT][2][OT][64]   W1 with the hidden units as contraction slots in accumulator order:
+//                          lane (i, g), slot m: W1[32ot + i][32ht + chain_feature(s, g, m)]
+//   w1d  [FT][HT][64]      the same for 16-feature tiles: lane (i, g) of 16 x 4, slot m: W1[16ft + i][32ht + 8g + m]
+//                          (only one of w1c and w1d is there: w1d when the fused kernel runs)
+//   b1   [He] fp32
+struct BwdPacked {
+    size_t w1f, w2r, w1c, w1d, b1, stride;
+};
+// Matrix-core expert weight gradients (backward_weights_mfma.hip): the split of the rows and the launches.  fused: the
+// kernel also writes dL/dx and dL/dp of the rows.
+struct BackwardWeightsPlan {
+    bool fused;
+    int step, groups, blocks;
+    long long slots;   // of partial weight gradients
+};
+BackwardWeightsPlan backward_weights_plan(const slicemoe_config &c);
+hipError_t launch_backward_weights(const slicemoe_config &c, const BwdPacked &L, const void *h, const void *d_out, const float *pk,
+                                   const int32_t *offsets, const int32_t *perm, const char *packed, size_t slot_floats, float *part,
+                                   float *dxrow, float *dpk, hipStream_t s);
 
 // Phi(z), and phi(z) through *density: the normal CDF by Abramowitz & Stegun 7.1.26 on |z| / sqrt 2 (|error| < 1.5e-7),
 // whose exponential exp(-z^2 / 2) is the density's.
@@ -47,6 +72,41 @@ __device__ __forceinline__ float normal_cdf_pdf(float z, float *density)
     return z > 0.f ? 1.f - tail : tail;
 }
 
+// The same for four values side by side: a vector instruction that needs the result of the one before waits 8.3 cycles for
+// it, where a wavefront can issue one every 4.7, so the four chains are interleaved step by step.
+__device__ __forceinline__ void normal_cdf_pdf4(const float (&z)[4], float (&cdf)[4], float (&density)[4])
+{
+    float ax[4], ex[4], t[4], q[4];
+#define SLICEMOE_EACH for (int i = 0; i < 4; ++i)
+#pragma unroll
+    SLICEMOE_EACH ax[i] = fmaf(0.3275911f * 0.70710678118654752f, fabsf(z[i]), 1.f);
+#pragma unroll
+    SLICEMOE_EACH ex[i] = z[i] * 0.84932180028801907f;   // exp(-z^2 / 2) = 2^-(z sqrt(log2(e) / 2))^2
+#pragma unroll
+    SLICEMOE_EACH t[i] = __builtin_amdgcn_rcpf(ax[i]);
+#pragma unroll
+    SLICEMOE_EACH ex[i] = -ex[i] * ex[i];
+#pragma unroll
+    SLICEMOE_EACH ex[i] = __builtin_amdgcn_exp2f(ex[i]);
+#pragma unroll
+    SLICEMOE_EACH q[i] = fmaf(0.5f * 1.061405429f, t[i], 0.5f * -1.453152027f);
+#pragma unroll
+    SLICEMOE_EACH q[i] = fmaf(q[i], t[i], 0.5f * 1.421413741f);
+#pragma unroll
+    SLICEMOE_EACH q[i] = fmaf(q[i], t[i], 0.5f * -0.284496736f);
+#pragma unroll
+    SLICEMOE_EACH q[i] = fmaf(q[i], t[i], 0.5f * 0.254829592f);
+#pragma unroll
+    SLICEMOE_EACH q[i] *= t[i];
+#pragma unroll
+    SLICEMOE_EACH q[i] *= ex[i];   // 1 - Phi(|z|)
+#pragma unroll
+    SLICEMOE_EACH density[i] = 0.39894228040143267794f * ex[i];
+#pragma unroll
+    SLICEMOE_EACH cdf[i] = z[i] > 0.f ? 1.f - q[i] : q[i];
+#undef SLICEMOE_EACH
+}
+
 __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b)   // round to nearest even
 {
     typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
@@ -61,6 +121,25 @@ __device__ __forceinline__ void split_bf16x2(float a, float b, uint32_t &hi, uin
 {
     hi = pack_bf16x2(a, b);
     lo = pack_bf16x2(a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xffff0000u));
+}
+
+// TERMS-term bf16 split of four values, the largest term first: 8 significant bits each.
+template <int TERMS>
+__device__ __forceinline__ void split_terms(const float (&v)[4], uint32_t (&out)[TERMS][4], int i)
+{
+    float r[4] = {v[0], v[1], v[2], v[3]};
+#pragma unroll
+    for (int t = 0; t < TERMS; ++t) {
+        const uint32_t h0 = pack_bf16x2(r[0], r[1]), h1 = pack_bf16x2(r[2], r[3]);
+        out[t][i] = h0;
+        out[t][i + 1] = h1;
+        if (t + 1 < TERMS) {
+            r[0] -= __uint_as_float(h0 << 16);
+            r[1] -= __uint_as_float(h0 & 0xffff0000u);
+            r[2] -= __uint_as_float(h1 << 16);
+            r[3] -= __uint_as_float(h1 & 0xffff0000u);
+        }
+    }
 }
 
 // Two fp32 values that are exactly bf16 values (results of an MFMA against an identity): their high halves.

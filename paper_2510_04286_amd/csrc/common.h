@@ -65,6 +65,13 @@ __device__ __forceinline__ void stage_to_lds(const void *__restrict__ src, void 
     }
 }
 
+// Workgroup barrier that orders LDS traffic only.  __syncthreads() also waits for every global load and store a
+// wavefront has in flight, which would expose the latency of loads issued ahead for a later step.
+__device__ __forceinline__ void lds_barrier()
+{
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
 // ---- packed-weight buffer layout (bf16 MFMA path) -------------------------------------
 // All offsets in bytes from the start of the packed buffer; every region 256-byte aligned.
 struct PackedLayout {
@@ -132,7 +139,7 @@ struct BackwardPlan {
 };
 BackwardPlan backward_plan(const slicemoe_config &c);
 // Matrix-core expert backward (backward_mfma.hip): shapes it takes, bytes of its repacked weights, and the launch
-// (same outputs as the vector-ALU expert kernel: row gradients, dL/dp, one slot of partial weight gradients per chunk).
+// (row gradients, dL/dp, and slots of partial weight gradients).
 bool backward_mfma_shape(const slicemoe_config &c);
 size_t backward_mfma_packed_bytes(const slicemoe_config &c);
 // Matrix-core router backward (backward_router_mfma.hip): shapes it takes, bytes of its scratch (repacked router and
@@ -145,16 +152,20 @@ hipError_t launch_backward_router_mfma(const slicemoe_config &c, const void *h, 
                                        const int32_t *inv, const float *dpk, const float *dxrow, void *d_h, void *scratch,
                                        int slices_per_block, long long slice_blocks, size_t slot_floats, float *part,
                                        hipStream_t s);
-// side (optional): a second stream with a fork event.  The weight-gradient kernel is then launched on side->stream, ordered
-// after the repacking on s by the event; the caller joins the stream back before anything reads `part`.
+// side (optional): a second stream with a fork event.  A weight-gradient kernel of its own is launched on side->stream,
+// ordered after the repacking on s by the event; the caller puts the reduction of `part` there too and joins the stream back.
 struct SideStream {
     hipStream_t stream;
     hipEvent_t fork, join;
 };
 hipError_t launch_backward_expert_mfma(const slicemoe_config &c, const void *h, const slicemoe_weights &w, const void *d_out,
                                        const float *pk, const int32_t *offsets, const int32_t *perm, void *packed,
-                                       int rows_per_chunk, long long chunks, size_t slot_floats, float *dxrow, float *dpk,
-                                       float *part, hipStream_t s, const SideStream *side = nullptr);
+                                       size_t slot_floats, float *dxrow, float *dpk, float *part, hipStream_t s,
+                                       const SideStream *side = nullptr);
+// its slots of partial weight gradients, and their sum into the gradients
+long long backward_weights_slots(const slicemoe_config &c);
+hipError_t launch_backward_reduce_segments(const slicemoe_config &c, const int32_t *offsets, const float *part, size_t slot,
+                                           const slicemoe_weight_grads &g, hipStream_t s);
 size_t backward_lds_bytes(const slicemoe_config &c);
 hipError_t launch_backward(const slicemoe_config &c, const void *h, const slicemoe_weights &w, const RouteVariant &v,
                            const float *drop_u, float rate, const int32_t *idx, const float *pk, const int32_t *offsets,
