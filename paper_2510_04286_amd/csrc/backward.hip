@@ -569,11 +569,12 @@ BackwardPlan backward_plan(const slicemoe_config &c)
     size_t spb = ((Ns + 1023) / 1024 + 31) / 32 * 32;
     p.slices_per_block = (int)(spb < (size_t)kBwdSlices ? (size_t)kBwdSlices : spb);
     p.slice_blocks = (long long)((Ns + p.slices_per_block - 1) / p.slices_per_block);
+    p.router_slots = backward_router_mfma_shape(c) ? backward_router_mfma_slots(c) : p.slice_blocks;
     size_t at = 0;
     p.dxrow = at;  at = align_up(at + Na * ds * sizeof(float), 256);
     p.dpk = at;    at = align_up(at + Na * sizeof(float), 256);
     p.expert_part = at;  at = align_up(at + (size_t)(backward_mfma_shape(c) ? backward_weights_slots(c) : p.chunks) * expert_slot_floats((int)ds, c.He) * sizeof(float), 256);
-    p.router_part = at;  at = align_up(at + (size_t)p.slice_blocks * router_slot_floats((int)ds, c.Hr, c.E) * sizeof(float), 256);
+    p.router_part = at;  at = align_up(at + (size_t)p.router_slots * router_slot_floats((int)ds, c.Hr, c.E) * sizeof(float), 256);
     p.packed = at;  at = align_up(at + backward_mfma_packed_bytes(c), 256);
     p.router_scratch = at;  at = align_up(at + backward_router_mfma_scratch_bytes(c), 256);
     p.cap = at;  at = align_up(at + (size_t)c.E * (sizeof(unsigned long long) + sizeof(float)), 256);
@@ -761,7 +762,7 @@ static hipError_t run_backward(const slicemoe_config &c, const void *h, const sl
     const size_t rslot = router_slot_floats(ds, c.Hr, c.E);
     if (backward_router_mfma_shape(c)) {
         e = launch_backward_router_mfma(c, h, w, v, drop_u, rate, idx, inv, dpk, dxrow, d_h, ws + P.router_scratch,
-                                        P.slices_per_block, P.slice_blocks, rslot, rpart, s);
+                                        rslot, rpart, s);
         if (e != hipSuccess) return e;
     } else {
     const size_t lds_r = sizeof(float) * kBwdRB * ((size_t)ds + 2 * (size_t)c.Hr + 2 * (size_t)c.E);
@@ -782,7 +783,7 @@ static hipError_t run_backward(const slicemoe_config &c, const void *h, const sl
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    bwd_reduce_router_kernel<<<(unsigned)((rslot + kRedElems - 1) / kRedElems), kRedElems * kRedSeqs, 0, s>>>(rpart, (int)P.slice_blocks, ds, c.Hr, c.E, g.Wr1,
+    bwd_reduce_router_kernel<<<(unsigned)((rslot + kRedElems - 1) / kRedElems), kRedElems * kRedSeqs, 0, s>>>(rpart, (int)P.router_slots, ds, c.Hr, c.E, g.Wr1,
                                                                            g.br1, g.Wr2, g.br2);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     return joiner.join();

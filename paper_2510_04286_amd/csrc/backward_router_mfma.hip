@@ -1,22 +1,22 @@
-// Matrix-core backward of the router and assembly of dL/dh, for slice widths 64, 96 and 128, Hr = 256 and up to 64
-// experts.  Same mathematics as bwd_router_kernel in backward.hip; three kernels, all without any exchange between
-// wavefronts:
+// Matrix-core backward of the router and assembly of dL/dh, for the forward's matrix-core slice widths except 384,
+// Hr = 256 and up to 64 experts.  Same mathematics as bwd_router_kernel in backward.hip; three kernels:
 //
 //   bwd_route_logits_mfma_kernel   the forward router's layout: a lane owns one slice of a 32-slice tile.  Recomputes the
 //       router exactly as the forward does (hidden layer on bf16 MFMA with the bias preloaded, ReLU, two-term fp16 split,
 //       logits on fp16 MFMA; noise; softmax with the temperature), then per lane: the selected probabilities, back
 //       through the dropout's renormalisation and the softmax to dL/dg (16 experts per lane and expert tile, as the
-//       logits).  Writes dL/dg as two bf16 tables (hi, lo: a two-term split) and the ReLU pattern, one bit per hidden
-//       unit.
+//       logits).  Writes dL/dg as bf16 tables, one per term, and the ReLU pattern, one bit per hidden unit.
 //   bwd_route_inputs_mfma_kernel   same layout: dL/du = Wr2 dL/dg with dL/dg read back in accumulator order, i.e. as
-//       the B operand, masked by the ReLU bits, then dL/dx += Wr1 dL/du chained from registers (two-term bf16).  Writes
+//       the B operand, masked by the ReLU bits, then dL/dx += Wr1 dL/du chained from registers.  Writes
 //       dL/dh = that + the k expert-path rows of the slice (one bf16 rounding).  It is a kernel of its own because the
 //       fragments of the two halves do not fit in LDS together at width 128 or with 64 experts.
-//   bwd_route_weights_mfma_kernel  the transposed layout (see backward_mfma.hip): one wavefront per hidden tile walks
-//       the slices of its block.  u^T by operand swap, dL/du^T = dL/dg Wr2^T straight from the dL/dg tables (their rows
-//       are A operands as stored), x^T and dL/dg^T by identity-MFMA transposes, then dWr1 += x^T dL/du and
-//       dWr2 += u^T dL/dg with two-term operands.  Stores its pieces into the block's slot of partial sums.
+//   bwd_route_weights_mfma_kernel  the transposed layout (see backward_weights_mfma.hip): one wavefront per hidden tile walks
+//       the slices of its block.  Stores its pieces into the block's slot of partial sums.
+//
+// dL/dg, u and dL/du enter matrix instructions as two bf16 terms (16 significant bits) at widths 64, 96 and 128, as three (24
+// bits) at 24, 48 and 192, where they used to be, and stay, fp32 (kRbTerms).
 #include "bwd_mfma.h"
+#include "lds_rows.h"
 
 namespace slicemoe {
 
@@ -26,9 +26,9 @@ typedef _Float16 r_f16x8 __attribute__((ext_vector_type(8)));
 constexpr int kRbHr = 256, kRbHT = 8;
 constexpr int kRbThreads = 512;                 // slice kernels: 8 wavefronts
 constexpr int kRbWaves = kRbThreads / 64;
-constexpr int kRbWgWaves = 4;                   // weights kernel: one wavefront per hidden tile, two groups of four
+template <int DS> constexpr int kRbTerms = DS == 24 || DS == 48 || DS == 192 ? 3 : 2;   // bf16 terms of dL/dg, u and dL/du
 
-// Repacked router (bytes from the start of the buffer); KS = ds / 16, OT = ds / 32, ET = expert tiles of 32 (experts
+// Repacked router (bytes from the start of the buffer); KS = ds / 16 and OT = ds / 32 rounded up (zero-padded), ET = expert tiles of 32 (experts
 // past E are zero).
 //   w1f  [8][KS][64]      Wr1 fragments, lane (i, g), slot m: Wr1[16ks + 8g + m][32ht + i]                   (bf16)
 //   w2f  [8][2][ET][64]   Wr2 for the logits: lane (i, g), slot m: Wr2[32ht + chain(s, g, m)][32et + i]       (fp16)
@@ -42,7 +42,7 @@ struct RouterBwdPacked {
 static RouterBwdPacked router_bwd_layout(int ds, int ET)
 {
     RouterBwdPacked L;
-    const int KS = ds / 16, OT = ds / 32;
+    const int KS = (ds + 15) / 16, OT = (ds + 31) / 32;
     size_t at = 0;
     L.w1f = at;  at += (size_t)kRbHT * KS * 1024;
     L.w2f = at;  at += (size_t)ET * kRbHT * 2 * 1024;
@@ -62,9 +62,9 @@ __global__ __launch_bounds__(kRbThreads) void bwd_route_logits_mfma_kernel(
     const bf16_t *__restrict__ x, long long Ns, int E, int k, const char *__restrict__ packed, RouterBwdPacked L,
     const float *__restrict__ noise, float sigma, float inv_tau, const float *__restrict__ drop_u, float rate,
     const int32_t *__restrict__ idx, const int32_t *__restrict__ inv, const float *__restrict__ dpk,
-    const float *__restrict__ capg, bf16_t *__restrict__ dg_hi, bf16_t *__restrict__ dg_lo, uint32_t *__restrict__ relu_bits)
+    const float *__restrict__ capg, bf16_t *__restrict__ dg_terms /* [terms][Ns][EP] */, uint32_t *__restrict__ relu_bits)
 {
-    constexpr int KS = DS / 16, EP = ET * 32;
+    constexpr int KS = SliceTiles<DS>::KS, EP = ET * 32, TERMS = kRbTerms<DS>;
     extern __shared__ __align__(16) char lds[];
     uint4 *w1f = (uint4 *)lds;                              // [8][KS][64]
     uint4 *w2f = w1f + kRbHT * KS * 64;                     // [8][2][ET][64]
@@ -87,7 +87,7 @@ __global__ __launch_bounds__(kRbThreads) void bwd_route_logits_mfma_kernel(
         const uint4 *xr = (const uint4 *)(x + nn * DS);
         bf16x8 xb[KS];
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) xb[ks] = __builtin_bit_cast(bf16x8, xr[2 * ks + g]);
+        for (int ks = 0; ks < KS; ++ks) xb[ks] = load_row_piece<DS>(xr, ks, g);
 
         // ---- the forward router, remembering which hidden units are active (bit r of half ht & 1 of word ht / 2)
         f32x16 gacc[ET];
@@ -210,7 +210,7 @@ __global__ __launch_bounds__(kRbThreads) void bwd_route_logits_mfma_kernel(
 #pragma unroll
             for (int et = 0; et < ET; ++et)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {   // experts 32 et + 8q + 4g .. + 3 of this slice: four bf16 values per table
+                for (int q = 0; q < 4; ++q) {   // experts 32 et + 8q + 4g .. + 3 of this slice: four bf16 values per term
                     float dg[4];
 #pragma unroll
                     for (int c = 0; c < 4; ++c) {
@@ -220,11 +220,11 @@ __global__ __launch_bounds__(kRbThreads) void bwd_route_logits_mfma_kernel(
                         for (int jj = 0; jj < 8; ++jj) t += e == ej[jj] ? dpf[jj] : 0.f;
                         dg[c] = t * inv_tau;
                     }
-                    uint32_t h0, l0, h1, l1;
-                    split_bf16x2(dg[0], dg[1], h0, l0);
-                    split_bf16x2(dg[2], dg[3], h1, l1);
-                    *(uint2 *)(dg_hi + n * EP + et * 32 + 8 * q + 4 * g) = make_uint2(h0, h1);
-                    *(uint2 *)(dg_lo + n * EP + et * 32 + 8 * q + 4 * g) = make_uint2(l0, l1);
+                    uint32_t dt[TERMS][4];
+                    split_terms<TERMS>(dg, dt, 0);
+#pragma unroll
+                    for (int t = 0; t < TERMS; ++t)
+                        *(uint2 *)(dg_terms + (t * Ns + n) * EP + et * 32 + 8 * q + 4 * g) = make_uint2(dt[t][0], dt[t][1]);
                 }
             *(uint4 *)(relu_bits + (n * 2 + g) * 4) = make_uint4(act0, act1, act2, act3);
         }
@@ -249,10 +249,10 @@ __device__ __forceinline__ void wave_lds_sync()
 template <int DS, int ET>
 __global__ __launch_bounds__(kRbThreads) void bwd_route_inputs_mfma_kernel(
     long long Ns, int k, const char *__restrict__ packed, RouterBwdPacked L, const int32_t *__restrict__ inv,
-    const float *__restrict__ dxrow, const bf16_t *__restrict__ dg_hi, const bf16_t *__restrict__ dg_lo,
-    const uint32_t *__restrict__ relu_bits, bf16_t *__restrict__ dh)
+    const float *__restrict__ dxrow, const bf16_t *__restrict__ dg_terms, const uint32_t *__restrict__ relu_bits,
+    bf16_t *__restrict__ dh)
 {
-    constexpr int OT = DS / 32, EP = ET * 32;
+    constexpr int OT = SliceTiles<DS>::OT, EP = ET * 32, TERMS = kRbTerms<DS>;
     extern __shared__ __align__(16) char lds[];
     const uint4 *w2c = (const uint4 *)lds;                       // [ET][2][8][64]
     const uint4 *w1c = w2c + ET * 2 * kRbHT * 64;                // [8][2][OT][64]
@@ -269,21 +269,19 @@ __global__ __launch_bounds__(kRbThreads) void bwd_route_inputs_mfma_kernel(
         const long long n = tile * 32 + j;
         const bool valid = n < Ns;
         // dL/dg of this lane in accumulator order: register pairs, i.e. B-operand fragments, as they were stored
-        uint32_t dgh[ET][8], dgl[ET][8];
+        uint32_t dgt[ET][TERMS][8];
         uint4 act = make_uint4(0, 0, 0, 0);
 #pragma unroll
         for (int et = 0; et < ET; ++et)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                uint2 h = make_uint2(0, 0), l = make_uint2(0, 0);   // a lane without a slice contributes nothing
-                if (valid) {
-                    h = *(const uint2 *)(dg_hi + n * EP + et * 32 + 8 * q + 4 * g);
-                    l = *(const uint2 *)(dg_lo + n * EP + et * 32 + 8 * q + 4 * g);
+#pragma unroll
+                for (int t = 0; t < TERMS; ++t) {
+                    uint2 v = make_uint2(0, 0);   // a lane without a slice contributes nothing
+                    if (valid) v = *(const uint2 *)(dg_terms + (t * Ns + n) * EP + et * 32 + 8 * q + 4 * g);
+                    dgt[et][t][2 * q] = v.x;
+                    dgt[et][t][2 * q + 1] = v.y;
                 }
-                dgh[et][2 * q] = h.x;
-                dgh[et][2 * q + 1] = h.y;
-                dgl[et][2 * q] = l.x;
-                dgl[et][2 * q + 1] = l.y;
             }
         if (valid) act = *(const uint4 *)(relu_bits + (n * 2 + g) * 4);
 
@@ -303,25 +301,27 @@ __global__ __launch_bounds__(kRbThreads) void bwd_route_inputs_mfma_kernel(
 #pragma unroll
                 for (int s = 0; s < 2; ++s) {
                     const bf16x8 wf = __builtin_bit_cast(bf16x8, w2c[((et * 2 + s) * kRbHT + ht) * 64 + lane]);
-                    du = mfma_bf16(wf, frag_of(dgl[et], s), du);
-                    du = mfma_bf16(wf, frag_of(dgh[et], s), du);
+#pragma unroll
+                    for (int t = TERMS - 1; t >= 0; --t) du = mfma_bf16(wf, frag_of(dgt[et][t], s), du);
                 }
             const uint32_t word = (ht >> 1) == 0 ? act.x : (ht >> 1) == 1 ? act.y : (ht >> 1) == 2 ? act.z : act.w;
             const uint32_t bits = word >> ((ht & 1) * 16);
-            uint32_t duh[8], dul[8];
+            uint32_t dut[2][TERMS][4];   // by K-step
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const float d0 = (bits >> (2 * i)) & 1u ? du[2 * i] : 0.f;
-                const float d1 = (bits >> (2 * i + 1)) & 1u ? du[2 * i + 1] : 0.f;
-                split_bf16x2(d0, d1, duh[i], dul[i]);
+            for (int q = 0; q < 4; ++q) {
+                float d[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) d[c] = (bits >> (4 * q + c)) & 1u ? du[4 * q + c] : 0.f;
+                split_terms<TERMS>(d, dut[q >> 1], 2 * (q & 1));
             }
 #pragma unroll
             for (int s = 0; s < 2; ++s)
 #pragma unroll
                 for (int ot = 0; ot < OT; ++ot) {
                     const bf16x8 wf = __builtin_bit_cast(bf16x8, w1c[((ht * 2 + s) * OT + ot) * 64 + lane]);
-                    dx[ot] = mfma_bf16(wf, frag_of(dul, s), dx[ot]);
-                    dx[ot] = mfma_bf16(wf, frag_of(duh, s), dx[ot]);
+#pragma unroll
+                    for (int t = TERMS - 1; t >= 0; --t)
+                        dx[ot] = mfma_bf16(wf, __builtin_bit_cast(bf16x8, make_uint4(dut[s][t][0], dut[s][t][1], dut[s][t][2], dut[s][t][3])), dx[ot]);
                 }
         }
 
@@ -346,7 +346,8 @@ __global__ __launch_bounds__(kRbThreads) void bwd_route_inputs_mfma_kernel(
                 f32x4 v = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int jj = 0; jj < 8; ++jj)
-                    if (rws[it][jj] >= 0) v += *(const f32x4 *)(dxrow + (size_t)rws[it][jj] * DS + 32 * ot + 4 * piece);
+                    if (rws[it][jj] >= 0 && (DS % 32 == 0 || 32 * ot + 4 * piece < DS))
+                        v += *(const f32x4 *)(dxrow + (size_t)rws[it][jj] * DS + 32 * ot + 4 * piece);
                 *(f32x4 *)(stg + (it * 8 + sl) * kRbStageRow + 4 * piece) = v;
             }
             wave_lds_sync();
@@ -365,7 +366,8 @@ __global__ __launch_bounds__(kRbThreads) void bwd_route_inputs_mfma_kernel(
             for (int half = 0; half < 2; ++half) {
                 const int i = half * 16 + (lane >> 2), pc = lane & 3;
                 const long long ns = n0 + i;
-                if (ns < Ns) *(uint4 *)(dh + ns * DS + 32 * ot + 8 * pc) = *(const uint4 *)((const char *)(stg + i * kRbStageRow) + pc * 16);
+                if (ns < Ns && (DS % 32 == 0 || 32 * ot + 8 * pc < DS))
+                    *(uint4 *)(dh + ns * DS + 32 * ot + 8 * pc) = *(const uint4 *)((const char *)(stg + i * kRbStageRow) + pc * 16);
             }
             wave_lds_sync();   // before the next gather overwrites the tile
         }
@@ -373,35 +375,105 @@ __global__ __launch_bounds__(kRbThreads) void bwd_route_inputs_mfma_kernel(
 }
 
 // ----------------------------------------------------------------------------------------------- weights kernel
-// grid = ranges of slices_per_block slices (each a slot of partial sums; rounded up to eight) x two groups of four hidden tiles, block = one
-// wavefront per hidden tile of the group.
-template <int DS, int ET>
-__global__ __launch_bounds__(kRbWgWaves * 64, (DS * (ET + 1) <= 256) ? 2 : 1) void bwd_route_weights_mfma_kernel(
+// The transposed layout: a block of eight wavefronts, one per hidden tile, walks 32-slice units.  x and the dL/dg terms of a
+// unit (contiguous rows of the tables) are loaded a unit ahead and put into one of two LDS buffers in front of the one barrier
+// per unit; as A operands they give u^T and dL/du^T (lane = hidden unit, registers = slices), and read back transposed they are
+// the other operand of dWr1 += x^T dL/du and dWr2 += u^T dL/dg, whose own operand comes from those registers.
+// Bound: the matrix pipe nominally (22 instructions per tile and unit at width 64, 32 experts).  262 144 slices at that
+// shape, with the transposes in the LDS instead of on the matrix pipe and rows loaded ahead: 95 -> 56 us; 524 288
+// slices at width 128, 64 experts: 405 -> 166 us.  At width 48 (32 768 slices, with the logits and inputs kernels): 4.0 ms of
+// vector-ALU kernel -> 50 us.
+constexpr int kRbUnit = 32;
+template <int DS, int ET, int TERMS> struct RouterWeightsTile {
+    static constexpr int KS = SliceTiles<DS>::KS, OT = SliceTiles<DS>::OT, GS = 2 * ET;   // GS: K-steps of 16 experts
+    static constexpr bool WLDS = DS >= 96;                                                 // fragments of Wr1 in LDS (else registers)
+    static constexpr size_t x_bytes = (size_t)kRbUnit * LdsRows<DS>::STRIDE, g_bytes = (size_t)kRbUnit * LdsRows<32 * ET>::STRIDE;
+    static constexpr size_t buf_bytes = x_bytes + TERMS * g_bytes;
+    static constexpr size_t off_red = 2 * buf_bytes;                        // [2 ET][32] partial dbr2
+    static constexpr size_t off_w = off_red + 2 * ET * 32 * sizeof(float);
+    static constexpr size_t lds = off_w + (WLDS ? (size_t)kRbHT * KS * 1024 : 0);
+};
+
+template <int DS, int ET, int TERMS>
+__global__ __launch_bounds__(kRbThreads, DS <= 128 ? 2 : 1) void bwd_route_weights_mfma_kernel(
     const bf16_t *__restrict__ x, long long Ns, int E, const char *__restrict__ packed, RouterBwdPacked L,
-    const bf16_t *__restrict__ dg_hi, const bf16_t *__restrict__ dg_lo, int slices_per_block, size_t slot_floats,
-    float *__restrict__ part)
+    const bf16_t *__restrict__ dg /* [TERMS][Ns][32 ET] */, int units_per_block, size_t slot_floats, float *__restrict__ part)
 {
-    constexpr int KS = DS / 16, OT = DS / 32, EP = ET * 32, GS = 2 * ET;   // GS: K-steps of 16 experts
+    typedef RouterWeightsTile<DS, ET, TERMS> G;
+    typedef LdsRows<DS> XR;
+    typedef LdsRows<32 * ET> GR;
+    constexpr int KS = G::KS, OT = G::OT, GS = G::GS, EP = 32 * ET, PX = XR::P, PG = GR::P;
+    constexpr int kPieces = kRbUnit * (PX + TERMS * PG), NX = (kPieces + kRbThreads - 1) / kRbThreads;
     extern __shared__ __align__(16) char lds[];
-    // this group's fragments only: [wave][KS][64] of w1f, [wave][GS][64] of w2r, 32 biases per wavefront
-    uint4 *w1f = (uint4 *)lds;
-    uint4 *w2r = w1f + kRbWgWaves * KS * 64;
-    float *b1s = (float *)(w2r + kRbWgWaves * GS * 64);
 
     const int tid = threadIdx.x, lane = tid & 63, jj = lane & 31, g = lane >> 5;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // Consecutive blocks go to the eight XCDs in turn, each with its own L2: the two groups of a slice range, which
-    // read the same rows, take block ids that are equal modulo 8.
-    constexpr int kGroups = kRbHT / kRbWgWaves;   // kRbHT is a multiple of the group size
-    const int ht0 = ((int)(blockIdx.x / 8) % kGroups) * kRbWgWaves, ht = ht0 + wave;
-    const long long range = (long long)(blockIdx.x / (8 * kGroups)) * 8 + (long long)(blockIdx.x % 8);
-    stage_bytes(packed + L.w1f + (size_t)ht0 * KS * 1024, (char *)w1f, (size_t)kRbWgWaves * KS * 1024, tid, kRbWgWaves * 64);
-    stage_bytes(packed + L.w2r + (size_t)ht0 * GS * 1024, (char *)w2r, (size_t)kRbWgWaves * GS * 1024, tid, kRbWgWaves * 64);
-    if (tid < kRbWgWaves * 32) b1s[tid] = ((const float *)(packed + L.b1))[ht0 * 32 + tid];
+    const int ht = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const long long n_begin = (long long)blockIdx.x * units_per_block * kRbUnit;   // < Ns by the launch
+    const int nrows = (int)min((long long)units_per_block * kRbUnit, Ns - n_begin);
+
+    // ---- the pieces this thread moves: source (row 0 of the block), row, step between rows, LDS offset
+    const bf16_t *msrc[NX];
+    int mrow[NX], mstep[NX], mdst[NX];
+    bool mx[NX];
+#pragma unroll
+    for (int i = 0; i < NX; ++i) {
+        const int q = min(tid + i * kRbThreads, kPieces - 1);
+        if (q < kRbUnit * PX) {
+            mrow[i] = q / PX;
+            mstep[i] = DS;
+            msrc[i] = x + n_begin * DS + 8 * (q % PX);
+            mdst[i] = XR::offset(mrow[i], q % PX);
+            mx[i] = true;
+        } else {
+            const int r = q - kRbUnit * PX, t = r / (kRbUnit * PG), rr = r - t * (kRbUnit * PG);
+            mrow[i] = rr / PG;
+            mstep[i] = EP;
+            msrc[i] = dg + ((long long)t * Ns + n_begin) * EP + 8 * (rr % PG);
+            mdst[i] = (int)G::x_bytes + t * (int)G::g_bytes + GR::offset(mrow[i], rr % PG);
+            mx[i] = false;
+        }
+    }
+    uint4 mv[NX];
+    auto load_rows = [&](int r0) {
+#pragma unroll
+        for (int i = 0; i < NX; ++i) mv[i] = *(const uint4 *)(msrc[i] + (unsigned)(min(r0 + mrow[i], nrows - 1) * mstep[i]));
+    };
+    auto store_rows = [&](int r0, int buf) {   // dL/dg of slices past the end is zero, so they add nothing
+#pragma unroll
+        for (int i = 0; i < NX; ++i)
+            if (NX * kRbThreads == kPieces || tid + i * kRbThreads < kPieces)
+                *(uint4 *)(lds + buf * G::buf_bytes + mdst[i]) = mx[i] || r0 + mrow[i] < nrows ? mv[i] : make_uint4(0, 0, 0, 0);
+    };
+    // ---- fragment addresses: rows as A operand, and transposed
+    const int ax = jj * XR::STRIDE + ((g ^ XR::swizzle(jj)) << 4), ag = jj * GR::STRIDE + ((g ^ GR::swizzle(jj)) << 4);
+    const int c16 = lane & 15, G4 = lane >> 4, trow = 4 * g + (c16 >> 2), tpiece = 2 * (G4 & 1) + ((lane & 3) >> 1);
+    const int tx = trow * XR::STRIDE + ((tpiece ^ XR::swizzle(trow)) << 4) + 8 * (lane & 1);
+    const int tg = trow * GR::STRIDE + ((tpiece ^ GR::swizzle(trow)) << 4) + 8 * (lane & 1);
+    auto transposed = [&](const char *rows, int base, int stride, int tile, int s) {   // rows 16 s .., columns 32 tile ..
+        const char *p = rows + 16 * s * stride + (base ^ (tile << 6));
+        return read_transposed(as_lds(p), as_lds(rows + (16 * s + 8) * stride + (base ^ (tile << 6) ^ 32)));
+    };
+
+    load_rows(0);
+    // ---- this wavefront's weights
+    bf16x8 w1r[G::WLDS ? 1 : KS], w2r[GS];
+    if constexpr (G::WLDS) {
+        stage_bytes(packed + L.w1f, lds + G::off_w, (size_t)kRbHT * KS * 1024, tid, kRbThreads);
+    } else {
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) w1r[ks] = __builtin_bit_cast(bf16x8, ((const uint4 *)(packed + L.w1f))[(ht * KS + ks) * 64 + lane]);
+    }
+#pragma unroll
+    for (int s = 0; s < GS; ++s) w2r[s] = __builtin_bit_cast(bf16x8, ((const uint4 *)(packed + L.w2r))[(ht * GS + s) * 64 + lane]);
+    const float bias = ((const float *)(packed + L.b1))[ht * 32 + jj];
+    if constexpr (XR::PW > PX) {   // the pieces past the slice width stay zero
+        for (int t = tid; t < 2 * kRbUnit * (XR::PW - PX); t += kRbThreads) {
+            const int row = t / (XR::PW - PX), piece = PX + t % (XR::PW - PX);
+            *(uint4 *)(lds + (row / kRbUnit) * G::buf_bytes + XR::offset(row % kRbUnit, piece)) = make_uint4(0, 0, 0, 0);
+        }
+    }
+    store_rows(0, 0);
     __syncthreads();
-    bf16x8 id_even, id_odd;
-    identity_fragments(jj, g, id_even, id_odd);
-    const float bias = b1s[wave * 32 + jj];
 
     f32x16 aW1[OT], aW2[ET];
 #pragma unroll
@@ -411,28 +483,13 @@ __global__ __launch_bounds__(kRbWgWaves * 64, (DS * (ET + 1) <= 256) ? 2 : 1) vo
 #pragma unroll
         for (int ot = 0; ot < OT; ++ot) aW1[ot][i] = 0.f;
     }
-    float ab1 = 0.f, ab2[ET];
-#pragma unroll
-    for (int et = 0; et < ET; ++et) ab2[et] = 0.f;
-
-    const long long n_begin = range * slices_per_block;
-    if (n_begin >= Ns) return;   // the grid is rounded up to whole groups of eight ranges (no barrier follows)
-    const long long n_end = min(Ns, n_begin + slices_per_block);
-    for (long long n0 = n_begin; n0 < n_end; n0 += 32) {
-        const long long n = n0 + jj;   // as A operand a lane holds slice jj of the unit, contraction slots 8g..8g+7
-        const bool valid = n < n_end;
-        const long long nn = valid ? n : n_begin;
-        const uint4 *xr = (const uint4 *)(x + nn * DS);
-        bf16x8 xa[KS], gh[GS], gl[GS];
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) xa[ks] = __builtin_bit_cast(bf16x8, xr[2 * ks + g]);
-#pragma unroll
-        for (int s = 0; s < GS; ++s) {   // experts 16s + 8g .. + 7 of the slice; slices past the end add nothing
-            const uint4 z = make_uint4(0, 0, 0, 0);
-            gh[s] = __builtin_bit_cast(bf16x8, valid ? *(const uint4 *)(dg_hi + nn * EP + 16 * s + 8 * g) : z);
-            gl[s] = __builtin_bit_cast(bf16x8, valid ? *(const uint4 *)(dg_lo + nn * EP + 16 * s + 8 * g) : z);
-        }
-        // transposed: lane = hidden unit jj of this tile, register i = slice acc_feature(i, g) of the unit
+    float ab1 = 0.f, ab2 = 0.f;
+    int buf = 0;
+#pragma unroll 1
+    for (int r0 = 0; r0 < nrows; r0 += kRbUnit) {
+        const bool more = r0 + kRbUnit < nrows;
+        if (more) load_rows(r0 + kRbUnit);
+        const char *xs = lds + buf * G::buf_bytes, *gs = xs + G::x_bytes;
         f32x16 u, du;
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
@@ -440,111 +497,107 @@ __global__ __launch_bounds__(kRbWgWaves * 64, (DS * (ET + 1) <= 256) ? 2 : 1) vo
             du[i] = 0.f;
         }
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) u = mfma_bf16(xa[ks], __builtin_bit_cast(bf16x8, w1f[(wave * KS + ks) * 64 + lane]), u);
-#pragma unroll
-        for (int s = 0; s < GS; ++s) {
-            const bf16x8 wf = __builtin_bit_cast(bf16x8, w2r[(wave * GS + s) * 64 + lane]);
-            du = mfma_bf16(gl[s], wf, du);
-            du = mfma_bf16(gh[s], wf, du);
-        }
-        uint32_t uh[8], ul[8], duh[8], dul[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const float u0 = fmaxf(u[2 * i], 0.f), u1 = fmaxf(u[2 * i + 1], 0.f);
-            const float d0 = u[2 * i] > 0.f ? du[2 * i] : 0.f, d1 = u[2 * i + 1] > 0.f ? du[2 * i + 1] : 0.f;
-            ab1 += d0 + d1;
-            split_bf16x2(u0, u1, uh[i], ul[i]);
-            split_bf16x2(d0, d1, duh[i], dul[i]);
+        for (int ks = 0; ks < KS; ++ks) {
+            const bf16x8 wf = G::WLDS ? __builtin_bit_cast(bf16x8, ((const uint4 *)(lds + G::off_w))[(ht * KS + ks) * 64 + lane]) : w1r[G::WLDS ? 0 : ks];
+            u = mfma_bf16(*(const bf16x8 *)(xs + (ax ^ (ks << 5))), wf, u);
         }
 #pragma unroll
-        for (int et = 0; et < ET; ++et) {
-            // dL/dg of the unit with lane = expert 32 et + jj, registers = slices (exact: both tables hold bf16 values)
-            f32x16 gth, gtl;
+        for (int s = 0; s < GS; ++s)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) gth[i] = gtl[i] = 0.f;
-            gth = mfma_bf16(gh[2 * et], id_even, gth);
-            gth = mfma_bf16(gh[2 * et + 1], id_odd, gth);
-            gtl = mfma_bf16(gl[2 * et], id_even, gtl);
-            gtl = mfma_bf16(gl[2 * et + 1], id_odd, gtl);
-            uint32_t gthp[8], gtlp[8];
+            for (int t = TERMS - 1; t >= 0; --t)   // small terms first
+                du = mfma_bf16(*(const bf16x8 *)(gs + t * G::g_bytes + (ag ^ (s << 5))), w2r[s], du);
+        uint32_t up[2][TERMS][4], dup[2][TERMS][4];   // by half of the unit (K-step)
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                gthp[i] = pack_exact_bf16x2(gth[2 * i], gth[2 * i + 1]);
-                gtlp[i] = pack_exact_bf16x2(gtl[2 * i], gtl[2 * i + 1]);
-                if (ht == 0) ab2[et] += (gth[2 * i] + gtl[2 * i]) + (gth[2 * i + 1] + gtl[2 * i + 1]);
+        for (int q = 0; q < 4; ++q) {
+            float uv[4], dv[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                dv[c] = u[4 * q + c] > 0.f ? du[4 * q + c] : 0.f;
+                uv[c] = fmaxf(u[4 * q + c], 0.f);
+            }
+            ab1 += (dv[0] + dv[1]) + (dv[2] + dv[3]);
+            split_terms<TERMS>(uv, up[q >> 1], 2 * (q & 1));
+            split_terms<TERMS>(dv, dup[q >> 1], 2 * (q & 1));
+        }
+        auto frag = [](const uint32_t (&v)[4]) { return __builtin_bit_cast(bf16x8, make_uint4(v[0], v[1], v[2], v[3])); };
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+#pragma unroll
+            for (int et = 0; et < ET; ++et) {   // dWr2 [hidden unit][expert]: lane = expert; products of terms down to the last one's size
+                bf16x8 gt[TERMS];
+#pragma unroll
+                for (int t = 0; t < TERMS; ++t) gt[t] = transposed(gs + t * G::g_bytes, tg, GR::STRIDE, et, s);
+#pragma unroll
+                for (int o = TERMS - 1; o >= 0; --o)
+#pragma unroll
+                    for (int t = 0; t <= o; ++t) aW2[et] = mfma_bf16(frag(up[s][o - t]), gt[t], aW2[et]);
+                if (ht == 2 * et + s) {   // dbr2: the sums of dL/dg over the slices, one fragment per wavefront
+#pragma unroll
+                    for (int t = TERMS - 1; t >= 0; --t) ab2 += fragment_sum(gt[t]);
+                }
             }
 #pragma unroll
-            for (int s = 0; s < 2; ++s) {   // dWr2 [hidden unit][expert]: lane = expert, registers = hidden units
-                aW2[et] = mfma_bf16(frag_of(ul, s), frag_of(gthp, s), aW2[et]);
-                aW2[et] = mfma_bf16(frag_of(uh, s), frag_of(gtlp, s), aW2[et]);
-                aW2[et] = mfma_bf16(frag_of(uh, s), frag_of(gthp, s), aW2[et]);
+            for (int ot = 0; ot < OT; ++ot) {   // dWr1 [slice feature][hidden unit]: lane = hidden unit
+                const bf16x8 xt = transposed(xs, tx, XR::STRIDE, ot, s);
+#pragma unroll
+                for (int t = TERMS - 1; t >= 0; --t) aW1[ot] = mfma_bf16(xt, frag(dup[s][t]), aW1[ot]);
             }
         }
-#pragma unroll
-        for (int ot = 0; ot < OT; ++ot) {
-            f32x16 xt;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) xt[i] = 0.f;
-            xt = mfma_bf16(xa[2 * ot], id_even, xt);
-            xt = mfma_bf16(xa[2 * ot + 1], id_odd, xt);
-            uint32_t xtp[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) xtp[i] = pack_exact_bf16x2(xt[2 * i], xt[2 * i + 1]);
-#pragma unroll
-            for (int s = 0; s < 2; ++s) {   // dWr1 [slice feature][hidden unit]: lane = hidden unit, registers = features
-                aW1[ot] = mfma_bf16(frag_of(xtp, s), frag_of(dul, s), aW1[ot]);
-                aW1[ot] = mfma_bf16(frag_of(xtp, s), frag_of(duh, s), aW1[ot]);
-            }
-        }
+        if (more) store_rows(r0 + kRbUnit, buf ^ 1);
+        lds_barrier();
+        buf ^= 1;
     }
 
-    // this block's slot: dWr1 [ds][Hr] | dWr2 [Hr][E] | dbr1 [Hr] | dbr2 [E]
-    float *slot = part + (size_t)range * slot_floats;
+    // ---- this block's slot: dWr1 [ds][Hr] | dWr2 [Hr][E] | dbr1 [Hr] | dbr2 [E]
+    float *slot = part + (size_t)blockIdx.x * slot_floats;
     float *pWr1 = slot, *pWr2 = pWr1 + (size_t)DS * kRbHr, *pbr1 = pWr2 + (size_t)kRbHr * E, *pbr2 = pbr1 + kRbHr;
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
 #pragma unroll
-        for (int ot = 0; ot < OT; ++ot) pWr1[(size_t)(32 * ot + acc_feature(i, g)) * kRbHr + 32 * ht + jj] = aW1[ot][i];
+        for (int ot = 0; ot < OT; ++ot) {
+            const int f = 32 * ot + acc_feature(i, g);
+            if (DS % 32 == 0 || f < DS) pWr1[(size_t)f * kRbHr + 32 * ht + jj] = aW1[ot][i];
+        }
 #pragma unroll
         for (int et = 0; et < ET; ++et)
             if (32 * et + jj < E) pWr2[(size_t)(32 * ht + acc_feature(i, g)) * E + 32 * et + jj] = aW2[et][i];
     }
     ab1 += __shfl_xor(ab1, 32);   // the two lane groups hold different slices of the same hidden unit
     if (g == 0) pbr1[32 * ht + jj] = ab1;
-#pragma unroll
-    for (int et = 0; et < ET; ++et) {
-        const float t = ab2[et] + __shfl_xor(ab2[et], 32);
-        if (ht == 0 && g == 0 && 32 * et + jj < E) pbr2[32 * et + jj] = t;
-    }
+    float *red = (float *)(lds + G::off_red);
+    ab2 += __shfl_xor(ab2, 32);
+    if (ht < 2 * ET && g == 0) red[ht * 32 + jj] = ab2;   // [et][half of the unit][32]
+    __syncthreads();
+    if (tid < E) pbr2[tid] = red[(tid >> 5) * 64 + (tid & 31)] + red[(tid >> 5) * 64 + 32 + (tid & 31)];
 }
 
 // ------------------------------------------------------------------------------------------------------ host
-static size_t logits_lds(int ds, int ET) { return (size_t)(kRbHT * (ds / 16) + kRbHT * 2 * ET) * 1024 + (kRbHr + 32 * ET) * sizeof(float); }
-static size_t inputs_lds(int ds, int ET)
+static size_t logits_lds(int KS, int ET) { return (size_t)(kRbHT * KS + kRbHT * 2 * ET) * 1024 + (kRbHr + 32 * ET) * sizeof(float); }
+static size_t inputs_lds(int OT, int ET)
 {
-    return (size_t)(ET * 2 * kRbHT + kRbHT * 2 * (ds / 32)) * 1024 + (size_t)kRbWaves * 32 * kRbStageRow * sizeof(float);
+    return (size_t)(ET * 2 * kRbHT + kRbHT * 2 * OT) * 1024 + (size_t)kRbWaves * 32 * kRbStageRow * sizeof(float);
 }
-static size_t weights_lds(int ds, int ET) { return (size_t)kRbWgWaves * (ds / 16 + 2 * ET) * 1024 + kRbWgWaves * 32 * sizeof(float); }
 
 bool backward_router_mfma_shape(const slicemoe_config &c)
 {
-    const int ds = c.d / c.S, ET = (c.E + 31) / 32;
-    return c.dtype == SLICEMOE_BF16 && (ds == 64 || ds == 96 || ds == 128) && c.Hr == kRbHr && c.E <= 64 &&
-           !(c.flags & SLICEMOE_FLAG_FORCE_GENERIC) && logits_lds(ds, ET) <= (size_t)max_lds_per_block() &&
-           inputs_lds(ds, ET) <= (size_t)max_lds_per_block();
+    const int ds = c.d / c.S, ET = (c.E + 31) / 32, KS = (ds + 15) / 16, OT = (ds + 31) / 32;
+    return c.dtype == SLICEMOE_BF16 && (ds == 24 || ds == 48 || ds == 64 || ds == 96 || ds == 128 || ds == 192) && c.Hr == kRbHr &&
+           c.E <= 64 && !(c.flags & SLICEMOE_FLAG_FORCE_GENERIC) && logits_lds(KS, ET) <= (size_t)max_lds_per_block() &&
+           inputs_lds(OT, ET) <= (size_t)max_lds_per_block();
 }
 
-// scratch: the repacked router | dL/dg hi [Ns][32 ET] bf16 | dL/dg lo | ReLU bits [Ns][2][4] words
+static int router_terms(int ds) { return ds == 24 || ds == 48 || ds == 192 ? 3 : 2; }   // kRbTerms
+
+// scratch: the repacked router | dL/dg terms [terms][Ns][32 ET] bf16 | ReLU bits [Ns][2][4] words
 struct RouterBwdScratch {
-    size_t dg_hi, dg_lo, bits, total;
+    size_t dg, bits, total;
 };
 static RouterBwdScratch router_bwd_scratch(const slicemoe_config &c)
 {
     const size_t Ns = (size_t)c.T * c.S, ET = (size_t)(c.E + 31) / 32;
     RouterBwdScratch R;
     size_t at = align_up(router_bwd_layout(c.d / c.S, (int)ET).total, 256);
-    R.dg_hi = at;  at += align_up(Ns * 32 * ET * sizeof(bf16_t), 256);
-    R.dg_lo = at;  at += align_up(Ns * 32 * ET * sizeof(bf16_t), 256);
+    R.dg = at;     at += align_up(router_terms(c.d / c.S) * Ns * 32 * ET * sizeof(bf16_t), 256);
     R.bits = at;   at += align_up(Ns * 8 * sizeof(uint32_t), 256);
     R.total = at;
     return R;
@@ -555,86 +608,100 @@ size_t backward_router_mfma_scratch_bytes(const slicemoe_config &c)
     return backward_router_mfma_shape(c) ? router_bwd_scratch(c).total : 0;
 }
 
+// Units of 32 slices per block of the weights kernel: one block per CU, at least two units each (a block leaves a slot of
+// partial sums behind, as large as the router's weights).
+static int router_units_per_block(const slicemoe_config &c)
+{
+    const long long units = ((long long)c.T * c.S + kRbUnit - 1) / kRbUnit;
+    const long long per = (units + num_compute_units() - 1) / num_compute_units();
+    return per < 2 ? 2 : (int)per;
+}
+
+long long backward_router_mfma_slots(const slicemoe_config &c)
+{
+    const long long units = ((long long)c.T * c.S + kRbUnit - 1) / kRbUnit, per = router_units_per_block(c);
+    return (units + per - 1) / per;
+}
+
 template <int DS, int ET>
 static hipError_t run_router_mfma(const slicemoe_config &c, const RouterBwdPacked &L, const void *h, const RouteVariant &v,
                                   const float *drop_u, float rate, const int32_t *idx, const int32_t *inv, const float *dpk,
-                                  const float *dxrow, void *d_h, const char *pb, bf16_t *dg_hi, bf16_t *dg_lo, uint32_t *bits,
-                                  int slices_per_block, long long slice_blocks, size_t slot_floats, float *part, hipStream_t s)
+                                  const float *dxrow, void *d_h, const char *pb, bf16_t *dg, uint32_t *bits, size_t slot_floats,
+                                  float *part, hipStream_t s)
 {
+    constexpr int KS = SliceTiles<DS>::KS, OT = SliceTiles<DS>::OT;
     const long long Ns = (long long)c.T * c.S;
     const long long ntiles = (Ns + 31) / 32, units = (ntiles + kRbWaves - 1) / kRbWaves;
     auto lk = bwd_route_logits_mfma_kernel<DS, ET>;
-    hipError_t e = grant_dynamic_lds((const void *)lk, logits_lds(DS, ET));
+    hipError_t e = grant_dynamic_lds((const void *)lk, logits_lds(KS, ET));
     if (e != hipSuccess) return e;
     // as many blocks as can be resident at once (registers and LDS allow two per CU for the narrow shapes)
     static int lk_per_cu = 0;   // per instantiation; the same on every device of the machine
     if (lk_per_cu == 0) {
         int n = 1;
-        if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, (const void *)lk, kRbThreads, logits_lds(DS, ET))) != hipSuccess) return e;
+        if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, (const void *)lk, kRbThreads, logits_lds(KS, ET))) != hipSuccess) return e;
         lk_per_cu = n < 1 ? 1 : n;
     }
     long long blocks = (long long)num_compute_units() * lk_per_cu;
     if (blocks > units) blocks = units;
-    lk<<<(int)blocks, kRbThreads, logits_lds(DS, ET), s>>>((const bf16_t *)h, Ns, c.E, c.k, pb, L, v.sigma > 0.f ? v.noise : nullptr,
+    lk<<<(int)blocks, kRbThreads, logits_lds(KS, ET), s>>>((const bf16_t *)h, Ns, c.E, c.k, pb, L, v.sigma > 0.f ? v.noise : nullptr,
                                                            v.sigma, v.inv_tau, rate > 0.f ? drop_u : nullptr, rate, idx, inv, dpk,
-                                                           v.capg, dg_hi, dg_lo, bits);
+                                                           v.capg, dg, bits);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     auto ik = bwd_route_inputs_mfma_kernel<DS, ET>;
-    if ((e = grant_dynamic_lds((const void *)ik, inputs_lds(DS, ET))) != hipSuccess) return e;
+    if ((e = grant_dynamic_lds((const void *)ik, inputs_lds(OT, ET))) != hipSuccess) return e;
     // one block per CU: this kernel waits on its row gathers, and a second resident block measured slower (cache misses)
     blocks = num_compute_units() < units ? num_compute_units() : units;
-    ik<<<(int)blocks, kRbThreads, inputs_lds(DS, ET), s>>>(Ns, c.k, pb, L, inv, dxrow, dg_hi, dg_lo, bits, (bf16_t *)d_h);
+    ik<<<(int)blocks, kRbThreads, inputs_lds(OT, ET), s>>>(Ns, c.k, pb, L, inv, dxrow, dg, bits, (bf16_t *)d_h);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    auto wk = bwd_route_weights_mfma_kernel<DS, ET>;
-    if ((e = grant_dynamic_lds((const void *)wk, weights_lds(DS, ET))) != hipSuccess) return e;
-    wk<<<(unsigned)((slice_blocks + 7) / 8 * 8 * (kRbHT / kRbWgWaves)), kRbWgWaves * 64, weights_lds(DS, ET), s>>>(
-        (const bf16_t *)h, Ns, c.E, pb, L, dg_hi, dg_lo, slices_per_block, slot_floats, part);
+    typedef RouterWeightsTile<DS, ET, kRbTerms<DS>> G;
+    auto wk = bwd_route_weights_mfma_kernel<DS, ET, kRbTerms<DS>>;
+    if ((e = grant_dynamic_lds((const void *)wk, G::lds)) != hipSuccess) return e;
+    wk<<<(unsigned)backward_router_mfma_slots(c), kRbThreads, G::lds, s>>>((const bf16_t *)h, Ns, c.E, pb, L, dg, router_units_per_block(c),
+                                                                          slot_floats, part);
     return hipGetLastError();
 }
 
-// scratch: backward_router_mfma_scratch_bytes; part: slice_blocks = ceil(Ns / slices_per_block) slots of slot_floats
-// floats (the slice ranges of the vector-ALU router kernel; slices_per_block a multiple of 32).  dxrow, dpk: the expert stage's row gradients and dL/dp.
+// scratch: backward_router_mfma_scratch_bytes; part: backward_router_mfma_slots slots of slot_floats floats.  dxrow, dpk:
+// the expert stage's row gradients and dL/dp.
 hipError_t launch_backward_router_mfma(const slicemoe_config &c, const void *h, const slicemoe_weights &w,
                                        const RouteVariant &v, const float *drop_u, float rate, const int32_t *idx,
                                        const int32_t *inv, const float *dpk, const float *dxrow, void *d_h, void *scratch,
-                                       int slices_per_block, long long slice_blocks, size_t slot_floats, float *part,
-                                       hipStream_t s)
+                                       size_t slot_floats, float *part, hipStream_t s)
 {
-    const long long Ns = (long long)c.T * c.S;
-    if (!backward_router_mfma_shape(c) || slices_per_block < 32 || slices_per_block % 32 != 0 ||
-        slice_blocks != (Ns + slices_per_block - 1) / slices_per_block)
-        return hipErrorInvalidValue;
+    if (!backward_router_mfma_shape(c)) return hipErrorInvalidValue;
     const int E = c.E, Hr = kRbHr, ds = c.d / c.S, ET = (E + 31) / 32, EP = 32 * ET;
+    const int dsK = (ds + 15) / 16 * 16, dsN = (ds + 31) / 32 * 32;
     const RouterBwdPacked L = router_bwd_layout(ds, ET);
     const RouterBwdScratch R = router_bwd_scratch(c);
     char *pb = (char *)scratch;
-    bf16_t *dg_hi = (bf16_t *)(pb + R.dg_hi), *dg_lo = (bf16_t *)(pb + R.dg_lo);
+    bf16_t *dg = (bf16_t *)(pb + R.dg);
     uint32_t *bits = (uint32_t *)(pb + R.bits);
     const bf16_t *Wr1 = (const bf16_t *)w.Wr1, *Wr2 = (const bf16_t *)w.Wr2;
     BwdPackJobs jobs;
     jobs.count = 7;
     // w1f: Wr1 [ds, Hr] itself.  w2f: Wr2 [Hr, E] with the hidden units as contraction slots, fp16, experts padded to EP.
-    jobs.job[0] = bwd_pack_job(kPackLayer1, Wr1, ds, ds, Hr, Hr, (size_t)Hr, 1, 0, pb + L.w1f, 0, 1);
+    jobs.job[0] = bwd_pack_job(kPackLayer1, Wr1, dsK, ds, Hr, Hr, (size_t)Hr, 1, 0, pb + L.w1f, 0, 1);
     jobs.job[1] = bwd_pack_job(kPackChainF16, Wr2, Hr, Hr, EP, E, (size_t)E, 1, 0, pb + L.w2f, 0, 1);
     // w2c: M[e][h] = Wr2[h][e] ([EP, Hr], experts as contraction slots).  w1c: M[h][c] = Wr1[c][h] ([Hr, ds]).
     jobs.job[2] = bwd_pack_job(kPackChain, Wr2, EP, E, Hr, Hr, 1, (size_t)E, 0, pb + L.w2c, 0, 1);
-    jobs.job[3] = bwd_pack_job(kPackChain, Wr1, Hr, Hr, ds, ds, 1, (size_t)Hr, 0, pb + L.w1c, 0, 1);
+    jobs.job[3] = bwd_pack_job(kPackChain, Wr1, Hr, Hr, dsN, ds, 1, (size_t)Hr, 0, pb + L.w1c, 0, 1);
     // w2r: M[e][h] = Wr2[h][e] ([EP, Hr]) in plain K-steps of 16 experts
     jobs.job[4] = bwd_pack_job(kPackLayer1, Wr2, EP, E, Hr, Hr, 1, (size_t)E, 0, pb + L.w2r, 0, 1);
     jobs.job[5] = bwd_pack_job(kPackBias, w.br1, Hr, Hr, Hr, Hr, 0, 0, 0, pb + L.b1, 0, 1);
     jobs.job[6] = bwd_pack_job(kPackBias, w.br2, E, E, EP, EP, 0, 0, 0, pb + L.b2, 0, 1);
     const hipError_t e = bwd_pack_launch(jobs, s);
     if (e != hipSuccess) return e;
-#define SLICEMOE_ROUTER_BWD(DSV, ETV)                                                                                            \
-    if (ds == DSV && ET == ETV)                                                                                                  \
-        return run_router_mfma<DSV, ETV>(c, L, h, v, drop_u, rate, idx, inv, dpk, dxrow, d_h, pb, dg_hi, dg_lo, bits, slices_per_block, slice_blocks, \
-                                         slot_floats, part, s);
-    SLICEMOE_ROUTER_BWD(64, 1)
-    SLICEMOE_ROUTER_BWD(64, 2)
-    SLICEMOE_ROUTER_BWD(96, 1)
-    SLICEMOE_ROUTER_BWD(96, 2)
-    SLICEMOE_ROUTER_BWD(128, 1)
-    SLICEMOE_ROUTER_BWD(128, 2)
+#define SLICEMOE_ROUTER_BWD(DSV)                                                                                                   \
+    if (ds == DSV)                                                                                                                 \
+        return ET == 1 ? run_router_mfma<DSV, 1>(c, L, h, v, drop_u, rate, idx, inv, dpk, dxrow, d_h, pb, dg, bits, slot_floats, part, s) \
+                       : run_router_mfma<DSV, 2>(c, L, h, v, drop_u, rate, idx, inv, dpk, dxrow, d_h, pb, dg, bits, slot_floats, part, s);
+    SLICEMOE_ROUTER_BWD(24)
+    SLICEMOE_ROUTER_BWD(48)
+    SLICEMOE_ROUTER_BWD(64)
+    SLICEMOE_ROUTER_BWD(96)
+    SLICEMOE_ROUTER_BWD(128)
+    SLICEMOE_ROUTER_BWD(192)
 #undef SLICEMOE_ROUTER_BWD
     return hipErrorInvalidValue;
 }

@@ -133,8 +133,9 @@ hipError_t launch_route_mfma(const slicemoe_config &c, const void *h, const void
 struct BackwardPlan {
     int rows_per_chunk;            // stacked rows per block of the expert kernel
     long long chunks;              // its grid.x (an upper bound on the chunks in use)
-    int slices_per_block;          // slices per block of the router kernel (its slot of partial weight gradients)
-    long long slice_blocks;        // grid.x of the router kernel
+    int slices_per_block;          // slices per block of the vector-ALU router kernel (its slot of partial weight gradients)
+    long long slice_blocks;        // grid.x of that kernel
+    long long router_slots;        // slots of the router kernel that runs
     size_t dxrow, dpk, expert_part, router_part, packed, router_scratch, cap, total;   // byte offsets into the workspace, total size
 };
 BackwardPlan backward_plan(const slicemoe_config &c);
@@ -143,15 +144,14 @@ BackwardPlan backward_plan(const slicemoe_config &c);
 bool backward_mfma_shape(const slicemoe_config &c);
 size_t backward_mfma_packed_bytes(const slicemoe_config &c);
 // Matrix-core router backward (backward_router_mfma.hip): shapes it takes, bytes of its scratch (repacked router and
-// the dL/dg tables), and the launch (same outputs as the vector-ALU router kernel: dL/dh and one slot of partial
-// weight gradients per range of slices_per_block slices).
+// the dL/dg tables), and the launch (dL/dh and backward_router_mfma_slots slots of partial weight gradients).
 bool backward_router_mfma_shape(const slicemoe_config &c);
 size_t backward_router_mfma_scratch_bytes(const slicemoe_config &c);
 hipError_t launch_backward_router_mfma(const slicemoe_config &c, const void *h, const slicemoe_weights &w,
                                        const RouteVariant &v, const float *drop_u, float rate, const int32_t *idx,
                                        const int32_t *inv, const float *dpk, const float *dxrow, void *d_h, void *scratch,
-                                       int slices_per_block, long long slice_blocks, size_t slot_floats, float *part,
-                                       hipStream_t s);
+                                       size_t slot_floats, float *part, hipStream_t s);
+long long backward_router_mfma_slots(const slicemoe_config &c);
 // side (optional): a second stream with a fork event.  A weight-gradient kernel of its own is launched on side->stream,
 // ordered after the repacking on s by the event; the caller puts the reduction of `part` there too and joins the stream back.
 struct SideStream {

@@ -1,4 +1,4 @@
-"""The matrix-core expert backward at the edges of its split: rows per unit (32), hidden tiles per block (4 or 8, fewer,
+"""The matrix-core backward at the edges of its split: rows per unit (32), hidden tiles per block (4 or 8, fewer,
 or several groups of them), widths with zero-padded pieces, experts with no row, one row, or all of them, and the division
 of assignment ids by k.  Every gradient against the fp64 oracle with the bars of test_gpu_4_backward.py, whose derivation
 (one bf16 rounding of dL/dh, fp32 sums over operands of 16 or more significant bits) covers these kernels; the widths that
@@ -38,6 +38,11 @@ CASES = {
     "w128_hot": shape(128, 64, 4, 2, 1500),
     "w192_2tiles": shape(192, 64, 8, 2, 65),
     "w192_5tiles": shape(192, 160, 3, 3, 22),
+    # two 32-expert tiles in the router's kernels; slices that end inside a 32-slice unit, one unit, several blocks of units
+    "w24_E40": shape(24, 96, 40, 2, 331, S=3),
+    "w48_E64": shape(48, 64, 64, 2, 8),
+    "w64_E33": shape(64, 64, 33, 3, 7, S=3),
+    "w192_E40": shape(192, 64, 40, 2, 30),
 }
 
 
