@@ -1,0 +1,606 @@
+// Backward pass on fp32 arithmetic, for every shape the bf16 matrix-core kernels do not take (fp32 storage, other slice
+// widths, forced generic): gradients by the chain rule as described in backward.hip, any shape within the library limits,
+// either storage type.  The contractions run on the fp32 matrix instruction (32 x 32 x 2: operands, products and sums
+// fp32), in the layout of backward_weights_mfma.hip: a block of eight wavefronts works on 32 rows (slices), a wavefront owns
+// one 32-wide hidden tile, lane = hidden unit, registers = rows.  What is formed there is directly the operand of the weight
+// gradients (contraction over rows); for the gradients of the rows (contraction over the hidden units) it goes through the
+// LDS.  Slice features are taken in chunks of 32 OTC columns, one block per chunk (grid.y), each chunk recomputing the
+// shared quantities; hidden widths above 256 in groups that a block works through in turn, the same thread adding each
+// group's part of dL/dx and dL/dp to what it wrote before.  Nothing is added in an order that changes from run to run.
+//
+// Bound: the matrix instruction (64 cycles; 160 per hidden tile and unit at ds = 64) and, for the small batches these shapes
+// run at, latency: a batch of weights in flight at a time.  8000 rows, ds = 64, He = 256, 8 experts: 4.13 ms -> 51 us;
+// 4000 slices, E = 8: 3.69 ms -> 39 us (one thread per hidden unit over 512 rows per block before).
+#include "bwd_mfma.h"
+
+namespace slicemoe {
+
+constexpr int kGbThreads = 512, kGbWaves = 8, kGbRows = 32, kGbHidden = 256;
+constexpr int kGbT = 33;   // row stride of 32-wide tiles: neighbouring rows in different banks
+
+__device__ __forceinline__ f32x16 mfma_f32(float a, float b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0); }
+
+// Four consecutive values p[0..3], those at or past `n` zero; vec: the address is aligned for one load.
+template <typename T> struct Quad;
+template <> struct Quad<float> {
+    static __device__ __forceinline__ void load(const float *p, float (&v)[4])
+    {
+        const float4 q = *(const float4 *)p;
+        v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
+    }
+};
+template <> struct Quad<bf16_t> {
+    static __device__ __forceinline__ void load(const bf16_t *p, float (&v)[4])
+    {
+        const uint2 q = *(const uint2 *)p;
+        v[0] = __uint_as_float(q.x << 16); v[1] = __uint_as_float(q.x & 0xffff0000u);
+        v[2] = __uint_as_float(q.y << 16); v[3] = __uint_as_float(q.y & 0xffff0000u);
+    }
+};
+template <typename T> __device__ __forceinline__ void load_quad(const T *p, int n, bool vec, float (&v)[4])
+{
+    if (vec && n >= 4) {
+        Quad<T>::load(p, v);
+        return;
+    }
+#pragma unroll
+    for (int s = 0; s < 4; ++s) v[s] = s < n ? Storage<T>::load(p + s) : 0.f;
+}
+
+// d/dz of the exact GELU z Phi(z): Phi(z) + z phi(z)
+__device__ __forceinline__ float gelu_grad(float z, float *act)
+{
+    const float cdf = 0.5f * (1.f + erff(z * 0.70710678118654752f));
+    *act = z * cdf;
+    return cdf + z * expf(-0.5f * z * z) * 0.39894228040143267794f;
+}
+
+// ------------------------------------------------------------------------------------------------ experts
+template <int OTC> struct GenericExpertLds {
+    static constexpr int CC = 32 * OTC, XST = CC + 1;
+    static constexpr size_t xs = 0, gs = xs + (size_t)kGbRows * XST, pz = gs + (size_t)kGbRows * XST;   // floats
+    static constexpr size_t red = pz + (size_t)kGbHidden * kGbT, dps = red + (size_t)kGbWaves * kGbRows * kGbT;
+    static constexpr size_t ps = dps + kGbWaves * kGbRows, ids = ps + kGbRows, total = ids + 2 * kGbRows;
+};
+
+template <typename T, int OTC>
+__global__ __launch_bounds__(kGbThreads) void bwd_expert_generic_kernel(
+    const T *__restrict__ x, const T *__restrict__ dout, const float *__restrict__ pk,
+    const int32_t *__restrict__ offsets, const int32_t *__restrict__ perm, int ds, int He, int E, int k,
+    const T *__restrict__ W1, const T *__restrict__ b1, const T *__restrict__ W2, bool vec_ds, bool vec_he,
+    float *__restrict__ dxrow, float *__restrict__ dpk, size_t slot_floats, float *__restrict__ part)
+{
+    typedef GenericExpertLds<OTC> L;
+    constexpr int CC = L::CC, XST = L::XST, PARTS = kGbWaves / OTC;
+    extern __shared__ __align__(16) float smem[];
+    float *xs = smem + L::xs, *gs = smem + L::gs, *pz = smem + L::pz, *red = smem + L::red, *dps = smem + L::dps, *ps = smem + L::ps;
+    int *as = (int *)(smem + L::ids), *ns = as + kGbRows;
+    const int tid = threadIdx.x, lane = tid & 63, jj = lane & 31, g = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nch = (int)gridDim.y, own = (int)blockIdx.y, own_c0 = own * CC, own_n = min(CC, ds - own_c0);
+    const int off_lo = offsets[min(lane, E)], off_hi = offsets[min(lane + 1, E)];
+    const RowAxis A = row_axis(off_hi - off_lo, kGbRows, (int)gridDim.x, lane);
+    const int p0 = (int)blockIdx.x * A.share, p1 = p0 + A.share;
+
+    for (int e = 0; e < E; ++e) {
+        const int first = __builtin_amdgcn_readlane(A.first, e), steps = __builtin_amdgcn_readlane(A.steps, e);
+        if (first >= p1) break;
+        const int s_lo = max(0, p0 - first - 1), s_hi = min(steps, p1 - first - 1);
+        if (s_hi <= s_lo) continue;
+        const int row0 = __builtin_amdgcn_readlane(off_lo, e) + s_lo * kGbRows;
+        const int nrows = min(__builtin_amdgcn_readlane(off_hi, e) - row0, (s_hi - s_lo) * kGbRows);
+        const T *w1 = W1 + (size_t)e * ds * He, *w2 = W2 + (size_t)e * He * ds;
+        float *slot = part + (size_t)((int)blockIdx.x + e) * slot_floats;
+        float *pW1 = slot, *pW2 = pW1 + (size_t)ds * He, *pb1 = pW2 + (size_t)He * ds, *pb2 = pb1 + He;
+
+        for (int h0 = 0; h0 < He; h0 += kGbHidden) {
+            const int hid = h0 + wave * 32 + jj, hidc = min(hid, He - 1);
+            const bool hok = hid < He;
+            const float bias = Storage<T>::load(b1 + (size_t)e * He + hidc);
+            f32x16 aW1[OTC], aW2[OTC];
+#pragma unroll
+            for (int ot = 0; ot < OTC; ++ot)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) aW1[ot][i] = aW2[ot][i] = 0.f;
+            float ab1 = 0.f, ab2 = 0.f;
+
+            for (int r0 = 0; r0 < nrows; r0 += kGbRows) {
+                const int rows = min(kGbRows, nrows - r0);
+                __syncthreads();   // everyone is done with the unit before
+                if (tid < kGbRows) {
+                    const int a = perm[row0 + r0 + min(tid, rows - 1)];
+                    as[tid] = a;
+                    ns[tid] = a / k;
+                    ps[tid] = tid < rows ? pk[a] : 0.f;
+                }
+                f32x16 u, da;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) u[i] = da[i] = 0.f;
+                for (int i = 1; i <= nch; ++i) {   // the block's own columns last: they stay for the weight gradients
+                    const int c0 = (own + i) % nch * CC, nf = min(CC, ds - c0);
+                    __syncthreads();
+                    for (int t = tid; t < kGbRows * CC; t += kGbThreads) {
+                        const int r = t / CC, c = t % CC;
+                        const bool in = c < nf;
+                        const size_t at = (size_t)ns[r] * ds + c0 + c;
+                        xs[r * XST + c] = in ? Storage<T>::load(x + at) : 0.f;
+                        gs[r * XST + c] = in && r < rows ? Storage<T>::load(dout + at) : 0.f;   // rows past the end add nothing
+                    }
+                    __syncthreads();
+                    // 32 features at a time: sixteen weights of each product in flight, then sixteen matrix instructions of each
+                    for (int kb = 0; kb < nf; kb += 32) {
+                        float bu[16], bd[16];
+#pragma unroll
+                        for (int s = 0; s < 16; ++s) {
+                            const int f = kb + 2 * s + g;
+                            bu[s] = f < nf ? Storage<T>::load(w1 + (size_t)(c0 + f) * He + hidc) : 0.f;
+                        }
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {   // K-step s of quad q: features kb + 8 q + 4 g + s
+                            float v[4];
+                            const int f = kb + 8 * q + 4 * g;
+                            load_quad(w2 + (size_t)hidc * ds + c0 + f, nf - f, vec_ds, v);
+#pragma unroll
+                            for (int s = 0; s < 4; ++s) bd[4 * q + s] = v[s];
+                        }
+#pragma unroll
+                        for (int s = 0; s < 16; ++s) {
+                            u = mfma_f32(xs[jj * XST + kb + 2 * s + g], bu[s], u);
+                            da = mfma_f32(gs[jj * XST + kb + 8 * (s >> 2) + 4 * g + (s & 3)], bd[s], da);
+                        }
+                    }
+                }
+                float du[8];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const int r = acc_feature(i, g);
+                    const float p = ps[r], z = fmaf(p, u[i], bias);
+                    float act;
+                    const float gg = gelu_grad(z, &act), dz = hok ? da[i] * gg : 0.f, pdz = p * dz;
+                    du[i & 7] = i < 8 ? dz * u[i] : sum_over_row_pair(du[i & 7], dz * u[i]);
+                    ab1 += dz;
+                    pz[(wave * 32 + jj) * kGbT + r] = pdz;
+#pragma unroll
+                    for (int ot = 0; ot < OTC; ++ot) {
+                        aW1[ot] = mfma_f32(xs[r * XST + 32 * ot + jj], pdz, aW1[ot]);   // [feature][hidden unit]: lane = hidden unit
+                        aW2[ot] = mfma_f32(act, gs[r * XST + 32 * ot + jj], aW2[ot]);   // [hidden unit][feature]: lane = feature
+                    }
+                    if (i & 1) __builtin_amdgcn_sched_barrier(0);   // two elements at a time: more would not fit the registers
+                }
+                sum_over_hidden(du);
+                if ((lane & 3) == 0) *(float2 *)(dps + wave * kGbRows + hidden_sum_row(lane)) = make_float2(du[0], du[1]);
+                if (h0 == 0 && tid < own_n)
+                    for (int r = 0; r < rows; ++r) ab2 += gs[r * XST + tid];
+                __syncthreads();
+                {   // dL/dx, own columns: lane = feature, registers = rows; the hidden units of a tile over PARTS wavefronts
+                    const int ot = wave % OTC, k0 = wave / OTC * (kGbHidden / PARTS), f = 32 * ot + jj;
+                    f32x16 dx;
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) dx[i] = 0.f;
+                    const T *wf = w1 + (size_t)(own_c0 + min(f, own_n - 1)) * He + h0;
+                    for (int kb = k0; kb < min(k0 + kGbHidden / PARTS, He - h0); kb += 32) {
+                        float b[16];
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            float v[4];
+                            load_quad(wf + kb + 8 * q + 4 * g, He - h0 - (kb + 8 * q + 4 * g), vec_he, v);
+#pragma unroll
+                            for (int s = 0; s < 4; ++s) b[4 * q + s] = v[s];
+                        }
+#pragma unroll
+                        for (int s = 0; s < 16; ++s) dx = mfma_f32(pz[(kb + 8 * (s >> 2) + 4 * g + (s & 3)) * kGbT + jj], b[s], dx);
+                    }
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) red[(wave * kGbRows + acc_feature(i, g)) * kGbT + jj] = dx[i];
+                }
+                __syncthreads();
+                for (int t = tid; t < rows * own_n; t += kGbThreads) {
+                    const int r = t / own_n, f = t - r * own_n;
+                    float v = 0.f;
+#pragma unroll
+                    for (int q = 0; q < PARTS; ++q) v += red[((q * OTC + (f >> 5)) * kGbRows + r) * kGbT + (f & 31)];
+                    float *dst = dxrow + (size_t)(row0 + r0 + r) * ds + own_c0 + f;   // the same thread wrote it for the group before
+                    *dst = h0 > 0 ? *dst + v : v;
+                }
+                if (own == 0 && tid < rows) {
+                    float v = 0.f;
+#pragma unroll
+                    for (int w = 0; w < kGbWaves; ++w) v += dps[w * kGbRows + tid];
+                    dpk[as[tid]] = h0 > 0 ? dpk[as[tid]] + v : v;
+                }
+            }
+            // ---- this segment's slot: dW1 [ds][He] | dW2 [He][ds] | db1 [He] | db2 [ds]; every element is written once
+            int jo = jj, go = g;   // opaque copies: the addresses are made here, not kept in registers through the loop above
+            asm volatile("" : "+v"(jo), "+v"(go));
+#pragma unroll
+            for (int ot = 0; ot < OTC; ++ot)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const int f = 32 * ot + acc_feature(i, go), ho = h0 + wave * 32 + jo, hr = h0 + wave * 32 + acc_feature(i, go);
+                    if (hok && f < own_n) pW1[(size_t)(own_c0 + f) * He + ho] = aW1[ot][i];
+                    if (hr < He && 32 * ot + jo < own_n) pW2[(size_t)hr * ds + own_c0 + 32 * ot + jo] = aW2[ot][i];
+                }
+            ab1 += __shfl_xor(ab1, 32);
+            if (own == 0 && g == 0 && hok) pb1[hid] = ab1;
+            if (h0 == 0 && tid < own_n) pb2[own_c0 + tid] = ab2;
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------------------------ router
+// Hr <= 256 and E <= 64.  The hidden layer is recomputed by plain multiply-add chains in a fixed order over the features (its
+// sign decides what the ReLU lets through): four hidden units and four slices per thread, weights and slices from LDS.
+constexpr int kGrFeat = 64;   // features at a time, and columns of a block
+struct GenericRouterLds {   // floats
+    static constexpr size_t xT = 0, w = xT + (size_t)kGrFeat * 36, us = w + (size_t)kGrFeat * kGbHidden;   // us: [32][257] u, then [256][33] dL/du
+    static constexpr size_t dgs = us + (size_t)kGbHidden * kGbT, red = dgs + (size_t)kGbRows * 65;
+    static constexpr size_t total = red + (size_t)kGbWaves * kGbRows * kGbT;
+};
+
+template <typename T>
+__global__ __launch_bounds__(kGbThreads) void bwd_router_generic_kernel(
+    const T *__restrict__ x, long long Ns, int ds, int Hr, int E, int k,
+    const T *__restrict__ Wr1, const T *__restrict__ br1, const T *__restrict__ Wr2, const T *__restrict__ br2,
+    const float *__restrict__ noise, float sigma, float inv_tau, const float *__restrict__ drop_u, float rate,
+    const int32_t *__restrict__ idx, const int32_t *__restrict__ inv, const float *__restrict__ dpk,
+    const float *__restrict__ capg, const float *__restrict__ dxrow, T *__restrict__ dh, int units_per_block, bool vec_hr, bool vec_e,
+    float *__restrict__ part, size_t slot_floats)
+{
+    typedef GenericRouterLds L;
+    constexpr int OTC = kGrFeat / 32, PARTS = kGbWaves / OTC, UST = kGbHidden + 1, GST = 65;
+    extern __shared__ __align__(16) float smem[];
+    float *xT = smem + L::xT, *ws = smem + L::w, *us = smem + L::us, *dgs = smem + L::dgs, *red = smem + L::red;
+    const int tid = threadIdx.x, lane = tid & 63, jj = lane & 31, g = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nch = (int)gridDim.y, own = (int)blockIdx.y, own_c0 = own * kGrFeat, own_n = min(kGrFeat, ds - own_c0);
+    const long long n_begin = (long long)blockIdx.x * units_per_block * kGbRows;
+    const long long n_end = min(Ns, n_begin + (long long)units_per_block * kGbRows);
+    const int ET = (E + 31) / 32, hid = wave * 32 + jj, hidc = min(hid, Hr - 1);
+    const bool hok = hid < Hr, quads = (ds & 3) == 0;
+
+    f32x16 aW1[OTC], aW2[2];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        aW1[0][i] = aW1[1][i] = 0.f;
+        aW2[0][i] = aW2[1][i] = 0.f;
+    }
+    float ab1 = 0.f, ab2 = 0.f;
+    auto stage_x = [&](long long n0, int rows, int c0, int nf) {
+        for (int t = tid; t < kGbRows * kGrFeat; t += kGbThreads) {
+            const int r = t / kGrFeat, c = t % kGrFeat;
+            xT[c * 36 + r] = r < rows && c < nf ? Storage<T>::load(x + (n0 + r) * ds + c0 + c) : 0.f;
+        }
+    };
+
+    for (long long n0 = n_begin; n0 < n_end; n0 += kGbRows) {
+        const int rows = (int)min((long long)kGbRows, n_end - n0);
+        // ---- hidden layer: hidden units 4 lane .., slices 4 wave ..
+        float acc[4][4];   // [slice][hidden unit]
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const float b = 4 * lane + c < Hr ? Storage<T>::load(br1 + 4 * lane + c) : 0.f;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[r][c] = b;
+        }
+        for (int ch = 0; ch < nch; ++ch) {
+            const int c0 = ch * kGrFeat, nf = min(kGrFeat, ds - c0);
+            __syncthreads();   // everyone is done with the features before
+            stage_x(n0, rows, c0, nf);
+            if (nch > 1 || n0 == n_begin)
+                for (int t = tid; t < nf * kGbHidden; t += kGbThreads) {
+                    const int f = t / kGbHidden, j = t % kGbHidden;
+                    ws[t] = j < Hr ? Storage<T>::load(Wr1 + (size_t)(c0 + f) * Hr + j) : 0.f;
+                }
+            __syncthreads();
+            if (quads) {
+                for (int f = 0; f < nf; f += 4) {
+                    float4 xq[4], wq[4];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        xq[q] = *(const float4 *)(xT + (f + q) * 36 + 4 * wave);
+                        wq[q] = *(const float4 *)(ws + (f + q) * kGbHidden + 4 * lane);
+                    }
+#pragma unroll
+                    for (int q = 3; q >= 0; --q) {   // (the last of four features first)
+                        const float xr[4] = {xq[q].x, xq[q].y, xq[q].z, xq[q].w}, wc[4] = {wq[q].x, wq[q].y, wq[q].z, wq[q].w};
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+#pragma unroll
+                            for (int c = 0; c < 4; ++c) acc[r][c] = fmaf(xr[r], wc[c], acc[r][c]);
+                    }
+                }
+            } else {
+                for (int f = 0; f < nf; ++f) {
+                    const float4 xq = *(const float4 *)(xT + f * 36 + 4 * wave), wq = *(const float4 *)(ws + f * kGbHidden + 4 * lane);
+                    const float xr[4] = {xq.x, xq.y, xq.z, xq.w}, wc[4] = {wq.x, wq.y, wq.z, wq.w};
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) acc[r][c] = fmaf(xr[r], wc[c], acc[r][c]);
+                }
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) us[(4 * wave + r) * UST + 4 * lane + c] = fmaxf(acc[r][c], 0.f);
+        __syncthreads();
+        if (nch > 1) stage_x(n0, rows, own_c0, own_n);   // the block's own columns, for dWr1
+        {   // ---- logits: lane = expert, registers = slices; the hidden units of a 32-expert tile over 8 / ET wavefronts
+            const int et = wave % ET, parts = kGbWaves / ET, per = kGbHidden / parts, k0 = wave / ET * per, e = min(32 * et + jj, E - 1);
+            f32x16 lg;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) lg[i] = 0.f;
+            for (int kb = k0; kb < k0 + per; kb += 32) {
+                float b[16];
+#pragma unroll
+                for (int s = 0; s < 16; ++s) b[s] = kb + 2 * s + g < Hr ? Storage<T>::load(Wr2 + (size_t)(kb + 2 * s + g) * E + e) : 0.f;
+#pragma unroll
+                for (int s = 0; s < 16; ++s) lg = mfma_f32(us[jj * UST + kb + 2 * s + g], b[s], lg);
+            }
+#pragma unroll
+            for (int i = 0; i < 16; ++i) red[(wave * kGbRows + acc_feature(i, g)) * kGbT + jj] = lg[i];
+        }
+        __syncthreads();
+        {   // ---- softmax, back through the dropout's renormalisation, dL/dg: 16 lanes per slice, experts l, l + 16, ..
+            const int r = tid >> 4, l = tid & 15;
+            const long long n = n0 + min(r, rows - 1);
+            float v[4], m = -INFINITY, den = 0.f;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int e = l + 16 * i;
+                v[i] = -INFINITY;
+                if (e < E) {
+                    float t = Storage<T>::load(br2 + e);
+                    for (int q = 0; q < kGbWaves / ET; ++q) t += red[((q * ET + (e >> 5)) * kGbRows + r) * kGbT + (e & 31)];
+                    if (noise != nullptr) t = fmaf(sigma, noise[n * E + e], t);
+                    v[i] = t;
+                }
+                m = fmaxf(m, v[i]);
+            }
+            for (int o = 8; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                v[i] = l + 16 * i < E ? expf((v[i] - m) * inv_tau) : 0.f;
+                den += v[i];
+            }
+            for (int o = 8; o > 0; o >>= 1) den += __shfl_xor(den, o);
+            const float rden = 1.f / den;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] *= rden;   // softmax probability of every expert
+            float psel[8], dpf[8];
+            bool keep[8];
+            int ej[8], kept = 0;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                psel[j] = dpf[j] = 0.f;
+                keep[j] = false;
+                ej[j] = 0;
+                if (j < k) {
+                    const long long a = n * k + j;
+                    ej[j] = min(max(idx[a], 0), E - 1);
+                    float mine = 0.f;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) mine = ej[j] == l + 16 * i ? v[i] : mine;
+                    for (int o = 8; o > 0; o >>= 1) mine += __shfl_xor(mine, o);
+                    psel[j] = mine;
+                    dpf[j] = inv[a] >= 0 ? dpk[a] : 0.f;   // a capacity-dropped assignment carries no gradient from h'
+                    if (capg != nullptr) dpf[j] += capg[ej[j]];   // but it counts as assigned (capacity loss)
+                    keep[j] = rate > 0.f ? !(drop_u[a] < rate) : true;
+                    kept += keep[j] ? 1 : 0;
+                }
+            }
+            if (rate > 0.f) {
+                if (kept == 0) keep[0] = true;
+                float ssum = 0.f, dot = 0.f;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) ssum += keep[j] ? psel[j] : 0.f;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) dot += keep[j] ? dpf[j] * (psel[j] / ssum) : 0.f;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) dpf[j] = keep[j] ? (dpf[j] - dot) / ssum : 0.f;
+            }
+            float csum = 0.f;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                dpf[j] = j < k ? dpf[j] * psel[j] * inv_tau : 0.f;
+                csum += dpf[j];
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int e = l + 16 * i;
+                float t = -v[i] * csum;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) t += j < k && e == ej[j] ? dpf[j] : 0.f;
+                dgs[r * GST + e] = r < rows && e < E ? t : 0.f;   // slices past the end contribute nothing
+            }
+        }
+        __syncthreads();
+        // ---- dL/du of this wavefront's hidden tile (ReLU applied), and the weight gradients
+        f32x16 du;
+        float uv[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            du[i] = 0.f;
+            uv[i] = us[acc_feature(i, g) * UST + hid];
+        }
+        for (int kb = 0; kb < E; kb += 8) {
+            float v[4];
+            load_quad(Wr2 + (size_t)hidc * E + kb + 4 * g, E - kb - 4 * g, vec_e, v);
+#pragma unroll
+            for (int s = 0; s < 4; ++s) du = mfma_f32(dgs[jj * GST + kb + 4 * g + s], v[s], du);
+        }
+        __syncthreads();   // everyone has taken its u: the region now takes dL/du
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int r = acc_feature(i, g);
+            const float d = hok && uv[i] > 0.f ? du[i] : 0.f;
+            ab1 += d;
+            us[hid * kGbT + r] = d;
+#pragma unroll
+            for (int ot = 0; ot < OTC; ++ot) aW1[ot] = mfma_f32(xT[(32 * ot + jj) * 36 + r], d, aW1[ot]);   // [feature][hidden unit]
+            if (own == 0) {
+                aW2[0] = mfma_f32(uv[i], dgs[r * GST + jj], aW2[0]);                                        // [hidden unit][expert]
+                if (ET > 1) aW2[1] = mfma_f32(uv[i], dgs[r * GST + 32 + jj], aW2[1]);
+            }
+        }
+        if (own == 0 && tid < E)
+            for (int r = 0; r < rows; ++r) ab2 += dgs[r * GST + tid];
+        __syncthreads();
+        {   // ---- dL/dh of the slices, own columns: router path ...
+            const int ot = wave % OTC, k0 = wave / OTC * (kGbHidden / PARTS), f = min(32 * ot + jj, own_n - 1);
+            f32x16 dx;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) dx[i] = 0.f;
+            const T *wf = Wr1 + (size_t)(own_c0 + f) * Hr;
+            for (int kb = k0; kb < min(k0 + kGbHidden / PARTS, Hr); kb += 32) {
+                float b[16];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    float v[4];
+                    load_quad(wf + kb + 8 * q + 4 * g, Hr - (kb + 8 * q + 4 * g), vec_hr, v);
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) b[4 * q + s] = v[s];
+                }
+#pragma unroll
+                for (int s = 0; s < 16; ++s) dx = mfma_f32(us[(kb + 8 * (s >> 2) + 4 * g + (s & 3)) * kGbT + jj], b[s], dx);
+            }
+#pragma unroll
+            for (int i = 0; i < 16; ++i) red[(wave * kGbRows + acc_feature(i, g)) * kGbT + jj] = dx[i];
+        }
+        __syncthreads();
+        for (int t = tid; t < rows * own_n; t += kGbThreads) {   // ... plus the expert-path rows of the k assignments
+            const int r = t / own_n, f = t - r * own_n;
+            const long long n = n0 + r;
+            float v = 0.f;
+#pragma unroll
+            for (int q = 0; q < PARTS; ++q) v += red[((q * OTC + (f >> 5)) * kGbRows + r) * kGbT + (f & 31)];
+            for (int j = 0; j < k; ++j) {
+                const int row = inv[n * k + j];
+                if (row >= 0) v += dxrow[(size_t)row * ds + own_c0 + f];
+            }
+            Storage<T>::store(dh + n * ds + own_c0 + f, v);
+        }
+    }
+
+    // ---- this block's slot: dWr1 [ds][Hr] | dWr2 [Hr][E] | dbr1 [Hr] | dbr2 [E]; the feature chunks write disjoint parts
+    float *slot = part + (size_t)blockIdx.x * slot_floats;
+    float *pWr1 = slot, *pWr2 = pWr1 + (size_t)ds * Hr, *pbr1 = pWr2 + (size_t)Hr * E, *pbr2 = pbr1 + Hr;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+#pragma unroll
+        for (int ot = 0; ot < OTC; ++ot) {
+            const int f = 32 * ot + acc_feature(i, g);
+            if (hok && f < own_n) pWr1[(size_t)(own_c0 + f) * Hr + hid] = aW1[ot][i];
+        }
+        const int hr = wave * 32 + acc_feature(i, g);
+        if (own == 0 && hr < Hr) {
+            if (jj < E) pWr2[(size_t)hr * E + jj] = aW2[0][i];
+            if (32 + jj < E) pWr2[(size_t)hr * E + 32 + jj] = aW2[1][i];
+        }
+    }
+    ab1 += __shfl_xor(ab1, 32);
+    if (own == 0 && g == 0 && hok) pbr1[hid] = ab1;
+    if (own == 0 && tid < E) pbr2[tid] = ab2;
+}
+
+// ------------------------------------------------------------------------------------------------------ host
+static int generic_col_tiles(int ds) { return ds <= 32 ? 1 : ds <= 64 ? 2 : 4; }   // columns per block of the expert kernel, in tiles
+
+BackwardWeightsPlan backward_generic_plan(const slicemoe_config &c)
+{
+    BackwardWeightsPlan W;
+    const long long Na = (long long)c.T * c.S * c.k;
+    const int ds = c.d / c.S, cc = 32 * generic_col_tiles(ds);
+    W.fused = true;
+    W.groups = 1;
+    W.step = kGbRows;
+    long long blocks = num_compute_units() / ((ds + cc - 1) / cc);
+    const long long most = (Na + kGbRows - 1) / kGbRows;
+    if (blocks > most) blocks = most;
+    W.blocks = blocks < 1 ? 1 : (int)blocks;
+    W.slots = (long long)W.blocks + c.E;
+    return W;
+}
+
+long long backward_generic_expert_slots(const slicemoe_config &c) { return backward_generic_plan(c).slots; }
+
+static int generic_router_units_per_block(const slicemoe_config &c)
+{
+    const long long units = ((long long)c.T * c.S + kGbRows - 1) / kGbRows;
+    const int ds = c.d / c.S, nch = (ds + kGrFeat - 1) / kGrFeat;
+    long long blocks = num_compute_units() / nch;
+    if (blocks < 1) blocks = 1;
+    const long long per = (units + blocks - 1) / blocks;
+    return per < 1 ? 1 : (int)per;
+}
+
+long long backward_generic_router_slots(const slicemoe_config &c)
+{
+    const long long units = ((long long)c.T * c.S + kGbRows - 1) / kGbRows, per = generic_router_units_per_block(c);
+    return (units + per - 1) / per;
+}
+
+template <typename T> static bool quad_aligned(const void *p, int stride) { return stride % 4 == 0 && (uintptr_t)p % (4 * sizeof(T)) == 0; }
+
+template <typename T, int OTC>
+static hipError_t run_expert(const slicemoe_config &c, const void *h, const slicemoe_weights &w, const void *d_out, const float *pk,
+                             const int32_t *offsets, const int32_t *perm, size_t slot_floats, float *dxrow, float *dpk, float *part, hipStream_t s)
+{
+    const int ds = c.d / c.S, cc = 32 * OTC;
+    const size_t lds = GenericExpertLds<OTC>::total * sizeof(float);
+    auto kern = bwd_expert_generic_kernel<T, OTC>;
+    const hipError_t e = grant_dynamic_lds((const void *)kern, lds);
+    if (e != hipSuccess) return e;
+    kern<<<dim3((unsigned)backward_generic_plan(c).blocks, (unsigned)((ds + cc - 1) / cc)), kGbThreads, lds, s>>>(
+        (const T *)h, (const T *)d_out, pk, offsets, perm, ds, c.He, c.E, c.k, (const T *)w.W1, (const T *)w.b1, (const T *)w.W2,
+        quad_aligned<T>(w.W2, ds), quad_aligned<T>(w.W1, c.He), dxrow, dpk, slot_floats, part);
+    return hipGetLastError();
+}
+
+template <typename T>
+static hipError_t run_generic(const slicemoe_config &c, const void *h, const slicemoe_weights &w, const void *d_out, const float *pk,
+                              const int32_t *offsets, const int32_t *perm, size_t slot_floats, float *dxrow, float *dpk, float *part, hipStream_t s)
+{
+    switch (generic_col_tiles(c.d / c.S)) {
+        case 1: return run_expert<T, 1>(c, h, w, d_out, pk, offsets, perm, slot_floats, dxrow, dpk, part, s);
+        case 2: return run_expert<T, 2>(c, h, w, d_out, pk, offsets, perm, slot_floats, dxrow, dpk, part, s);
+        default: return run_expert<T, 4>(c, h, w, d_out, pk, offsets, perm, slot_floats, dxrow, dpk, part, s);
+    }
+}
+
+hipError_t launch_backward_expert_generic(const slicemoe_config &c, const void *h, const slicemoe_weights &w, const void *d_out,
+                                          const float *pk, const int32_t *offsets, const int32_t *perm, size_t slot_floats, float *dxrow,
+                                          float *dpk, float *part, hipStream_t s)
+{
+    return c.dtype == SLICEMOE_BF16 ? run_generic<bf16_t>(c, h, w, d_out, pk, offsets, perm, slot_floats, dxrow, dpk, part, s)
+                                    : run_generic<float>(c, h, w, d_out, pk, offsets, perm, slot_floats, dxrow, dpk, part, s);
+}
+
+template <typename T>
+static hipError_t run_router(const slicemoe_config &c, const void *h, const slicemoe_weights &w, const RouteVariant &v, const float *drop_u,
+                             float rate, const int32_t *idx, const int32_t *inv, const float *dpk, const float *dxrow, void *d_h,
+                             size_t slot_floats, float *part, hipStream_t s)
+{
+    const long long Ns = (long long)c.T * c.S;
+    const int ds = c.d / c.S;
+    const size_t lds = GenericRouterLds::total * sizeof(float);
+    auto kern = bwd_router_generic_kernel<T>;
+    const hipError_t e = grant_dynamic_lds((const void *)kern, lds);
+    if (e != hipSuccess) return e;
+    kern<<<dim3((unsigned)backward_generic_router_slots(c), (unsigned)((ds + kGrFeat - 1) / kGrFeat)), kGbThreads, lds, s>>>(
+        (const T *)h, Ns, ds, c.Hr, c.E, c.k, (const T *)w.Wr1, (const T *)w.br1, (const T *)w.Wr2, (const T *)w.br2,
+        v.sigma > 0.f ? v.noise : nullptr, v.sigma, v.inv_tau, rate > 0.f ? drop_u : nullptr, rate, idx, inv, dpk, v.capg, dxrow, (T *)d_h,
+        generic_router_units_per_block(c), quad_aligned<T>(w.Wr1, c.Hr), quad_aligned<T>(w.Wr2, c.E), part, slot_floats);
+    return hipGetLastError();
+}
+
+hipError_t launch_backward_router_generic(const slicemoe_config &c, const void *h, const slicemoe_weights &w, const RouteVariant &v,
+                                          const float *drop_u, float rate, const int32_t *idx, const int32_t *inv, const float *dpk,
+                                          const float *dxrow, void *d_h, size_t slot_floats, float *part, hipStream_t s)
+{
+    return c.dtype == SLICEMOE_BF16 ? run_router<bf16_t>(c, h, w, v, drop_u, rate, idx, inv, dpk, dxrow, d_h, slot_floats, part, s)
+                                    : run_router<float>(c, h, w, v, drop_u, rate, idx, inv, dpk, dxrow, d_h, slot_floats, part, s);
+}
+
+}  // namespace slicemoe

@@ -38,66 +38,6 @@
 
 namespace slicemoe {
 
-// ------------------------------------------------------------------------------------------- work split over blocks
-// Rows are handed out in steps of `step` rows counted from each expert's first row, on an axis where an expert with rows
-// occupies one position more than it has steps (what it costs a block to begin an expert: its weights in, its sums out).
-// Block v takes `share` consecutive positions.  A segment is what one block has of one expert; along the axis the block or
-// the expert advances from one segment to the next, so v + e names a segment's slot of partial sums uniquely.
-struct RowAxis {
-    int first, steps;   // of lane e's expert (E <= 64): its first position, its steps
-    int share;          // uniform
-};
-__device__ __forceinline__ RowAxis row_axis(int rows, int step, int blocks, int lane)
-{
-    RowAxis A;
-    A.steps = (rows + step - 1) / step;
-    const int cost = A.steps > 0 ? A.steps + 1 : 0;
-    A.first = wavefront_exclusive_scan(cost, lane);
-    A.share = max(1, (wavefront_sum(cost) + blocks - 1) / blocks);
-    return A;
-}
-
-// Sums over the 32 lanes of a lane group of 16 values each, half of the values at every exchange, so that what is left
-// spreads over the lanes: 32 instructions.  Afterwards v[0] and v[1] are the sums of the values that were registers
-// acc-order rows hidden_sum_row(lane) and + 1 (the four lanes of a quad hold the same).  The additions of a lane's own
-// value and one from another lane of its row of 16 are single instructions whose bank mask restricts them to the lanes
-// (banks of four) that keep that value; each group starts with the two wait states a moved operand needs.
-__device__ __forceinline__ float sum_over_row_pair(float a, float b)   // even rows of 16 lanes keep a, odd ones b
-{
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-__device__ __forceinline__ void sum_over_hidden(float (&v)[8])   // v[i]: sum_over_row_pair of values i and i + 8
-{
-    asm("s_nop 1\n\t"
-        "v_add_f32_dpp %0, %0, %0 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
-        "v_add_f32_dpp %1, %1, %1 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
-        "v_add_f32_dpp %2, %2, %2 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
-        "v_add_f32_dpp %3, %3, %3 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
-        "v_add_f32_dpp %0, %4, %4 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
-        "v_add_f32_dpp %1, %5, %5 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
-        "v_add_f32_dpp %2, %6, %6 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
-        "v_add_f32_dpp %3, %7, %7 row_ror:8 row_mask:0xf bank_mask:0xc"
-        : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3])
-        : "v"(v[4]), "v"(v[5]), "v"(v[6]), "v"(v[7]));
-    asm("s_nop 1\n\t"
-        "v_add_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
-        "v_add_f32_dpp %1, %1, %1 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
-        "v_add_f32_dpp %0, %2, %2 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
-        "v_add_f32_dpp %1, %3, %3 row_half_mirror row_mask:0xf bank_mask:0xa"
-        : "+v"(v[0]), "+v"(v[1])
-        : "v"(v[2]), "v"(v[3]));
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        v[i] += __int_as_float(lane_move<0xB1>(__float_as_int(v[i])));   // quad_perm [1, 0, 3, 2]
-        v[i] += __int_as_float(lane_move<0x4E>(__float_as_int(v[i])));   // quad_perm [2, 3, 0, 1]
-    }
-}
-__device__ __forceinline__ int hidden_sum_row(int lane)
-{
-    return 16 * ((lane >> 4) & 1) + 8 * ((lane >> 3) & 1) + 4 * (lane >> 5) + 2 * ((lane >> 2) & 1);
-}
-
 // p dz of a unit in the LDS: [term][hidden unit of the block][32 rows] bf16, the 8-byte quads of rows permuted inside a hidden unit's
 // 64 bytes so that neither the writes (a lane per hidden unit) nor the transposing reads meet bank conflicts.
 __device__ __forceinline__ int pdz_offset(int hidden, int quad)
@@ -647,9 +587,10 @@ hipError_t launch_backward_weights(const slicemoe_config &c, const BwdPacked &L,
 hipError_t launch_backward_reduce_segments(const slicemoe_config &c, const int32_t *offsets, const float *part, size_t slot,
                                            const slicemoe_weight_grads &g, hipStream_t s)
 {
-    const BackwardWeightsPlan W = backward_weights_plan(c);
+    const BackwardWeightsPlan W = backward_mfma_shape(c) ? backward_weights_plan(c) : backward_generic_plan(c);
     const int ds = c.d / c.S;
-    const bool vec4 = (((uintptr_t)g.W1 | (uintptr_t)g.b1 | (uintptr_t)g.W2 | (uintptr_t)g.b2 | (uintptr_t)part) & 15) == 0;   // ds, He: multiples of 8
+    const bool vec4 = ds % 4 == 0 && c.He % 4 == 0 &&
+                      (((uintptr_t)g.W1 | (uintptr_t)g.b1 | (uintptr_t)g.W2 | (uintptr_t)g.b2 | (uintptr_t)part) & 15) == 0;
     const size_t items = vec4 ? slot / 4 : slot;
     const dim3 grid((unsigned)c.E, (unsigned)((items + kSegElems - 1) / kSegElems));
     if (vec4) bwd_reduce_segments_kernel<4><<<grid, kSegElems * kSegSeqs, 0, s>>>(part, offsets, ds, c.He, c.E, W.step, W.blocks, slot, g.W1, g.b1, g.W2, g.b2);

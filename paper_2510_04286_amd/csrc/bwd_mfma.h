@@ -2,8 +2,28 @@
 // the normal CDF and density, bf16 pair conversions.  See mfma.h for the operand layouts.
 #pragma once
 #include "mfma.h"
+#include "wavefront.h"
 
 namespace slicemoe {
+
+// ------------------------------------------------------------------------------------------- work split over blocks
+// Rows are handed out in steps of `step` rows counted from each expert's first row, on an axis where an expert with rows
+// occupies one position more than it has steps (what it costs a block to begin an expert: its weights in, its sums out).
+// Block v takes `share` consecutive positions.  A segment is what one block has of one expert; along the axis the block or
+// the expert advances from one segment to the next, so v + e names a segment's slot of partial sums uniquely.
+struct RowAxis {
+    int first, steps;   // of lane e's expert (E <= 64): its first position, its steps
+    int share;          // uniform
+};
+__device__ __forceinline__ RowAxis row_axis(int rows, int step, int blocks, int lane)
+{
+    RowAxis A;
+    A.steps = (rows + step - 1) / step;
+    const int cost = A.steps > 0 ? A.steps + 1 : 0;
+    A.first = wavefront_exclusive_scan(cost, lane);
+    A.share = max(1, (wavefront_sum(cost) + blocks - 1) / blocks);
+    return A;
+}
 
 // Weight repacking for the backward kernels: a few jobs per launch, one thread per 16-byte fragment (or bias value).
 // Generic strided source so that the same code packs a matrix or its transpose: element (kk, col) of the [K, N] matrix
@@ -51,28 +71,14 @@ struct BackwardWeightsPlan {
     long long slots;   // of partial weight gradients
 };
 BackwardWeightsPlan backward_weights_plan(const slicemoe_config &c);
+BackwardWeightsPlan backward_generic_plan(const slicemoe_config &c);   // of the fp32 expert kernel (backward_generic.hip)
 hipError_t launch_backward_weights(const slicemoe_config &c, const BwdPacked &L, const void *h, const void *d_out, const float *pk,
                                    const int32_t *offsets, const int32_t *perm, const char *packed, size_t slot_floats, float *part,
                                    float *dxrow, float *dpk, hipStream_t s);
 
 // Phi(z), and phi(z) through *density: the normal CDF by Abramowitz & Stegun 7.1.26 on |z| / sqrt 2 (|error| < 1.5e-7),
 // whose exponential exp(-z^2 / 2) is the density's.
-__device__ __forceinline__ float normal_cdf_pdf(float z, float *density)
-{
-    const float ax = fabsf(z) * 0.70710678118654752f;
-    const float ex = __builtin_amdgcn_exp2f(-0.72134752044448170f * z * z);   // exp(-z^2 / 2)
-    const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f, ax, 1.f));
-    // half the published coefficients: the factor 1/2 of 1 - Phi = erfc / 2 costs nothing and changes no bit
-    float q = fmaf(0.5f * 1.061405429f, t, 0.5f * -1.453152027f);
-    q = fmaf(q, t, 0.5f * 1.421413741f);
-    q = fmaf(q, t, 0.5f * -0.284496736f);
-    q = fmaf(q, t, 0.5f * 0.254829592f);
-    const float tail = q * t * ex;   // 1 - Phi(|z|)
-    *density = 0.39894228040143267794f * ex;
-    return z > 0.f ? 1.f - tail : tail;
-}
-
-// The same for four values side by side: a vector instruction that needs the result of the one before waits 8.3 cycles for
+// For four values side by side: a vector instruction that needs the result of the one before waits 8.3 cycles for
 // it, where a wavefront can issue one every 4.7, so the four chains are interleaved step by step.
 __device__ __forceinline__ void normal_cdf_pdf4(const float (&z)[4], float (&cdf)[4], float (&density)[4])
 {
@@ -115,14 +121,6 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b)   // round to 
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
 }
 
-// Two-term bf16 split of a pair: hi = bf16(v), lo = bf16(v - hi); hi + lo carries 16 significant bits, so a matrix
-// instruction run once per term is as good as an fp32 operand (the other operand being exact bf16 data).
-__device__ __forceinline__ void split_bf16x2(float a, float b, uint32_t &hi, uint32_t &lo)
-{
-    hi = pack_bf16x2(a, b);
-    lo = pack_bf16x2(a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xffff0000u));
-}
-
 // TERMS-term bf16 split of four values, the largest term first: 8 significant bits each.
 template <int TERMS>
 __device__ __forceinline__ void split_terms(const float (&v)[4], uint32_t (&out)[TERMS][4], int i)
@@ -142,30 +140,9 @@ __device__ __forceinline__ void split_terms(const float (&v)[4], uint32_t (&out)
     }
 }
 
-// Two fp32 values that are exactly bf16 values (results of an MFMA against an identity): their high halves.
-__device__ __forceinline__ uint32_t pack_exact_bf16x2(float a, float b)
-{
-    return (__float_as_uint(a) >> 16) | (__float_as_uint(b) & 0xffff0000u);
-}
-
 __device__ __forceinline__ bf16x8 frag_of(const uint32_t (&p)[8], int s)   // K-step s of eight register pairs
 {
     return __builtin_bit_cast(bf16x8, make_uint4(p[4 * s], p[4 * s + 1], p[4 * s + 2], p[4 * s + 3]));
-}
-
-// Identity fragments for transposing a row fragment with an MFMA: as B operand of K-step ks against output tile ot,
-// slot m of lane (jj, g) is 1 where 16 ks + 8 g + m == 32 ot + jj; only the parity of ks matters.
-__device__ __forceinline__ void identity_fragments(int jj, int g, bf16x8 &id_even, bf16x8 &id_odd)
-{
-    uint32_t ide[4] = {0, 0, 0, 0}, ido[4] = {0, 0, 0, 0};
-    const int me = jj - 8 * g, mo = jj - 16 - 8 * g;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {   // static indices: the arrays stay in registers
-        if (me >= 0 && me < 8 && (me >> 1) == t) ide[t] = (me & 1) ? 0x3f800000u : 0x00003f80u;
-        if (mo >= 0 && mo < 8 && (mo >> 1) == t) ido[t] = (mo & 1) ? 0x3f800000u : 0x00003f80u;
-    }
-    id_even = __builtin_bit_cast(bf16x8, make_uint4(ide[0], ide[1], ide[2], ide[3]));
-    id_odd = __builtin_bit_cast(bf16x8, make_uint4(ido[0], ido[1], ido[2], ido[3]));
 }
 
 // Block-wide copy of `bytes` (a multiple of 16) from memory to LDS; callers synchronise.

@@ -127,15 +127,10 @@ hipError_t launch_route_generic(const slicemoe_config &c, const void *h, const s
 hipError_t launch_route_mfma(const slicemoe_config &c, const void *h, const void *packed,
                              int32_t *idx, float *p, hipStream_t s, const RouteVariant &v = RouteVariant(),
                              int32_t *hist_table = nullptr /* see route_mfma_hist_chunk */);
-// Backward pass (backward.hip): weight gradients into g, dL/dh into d_h.  backward_plan: geometry and layout of its
-// scratch (row gradients, dL/dp, one slot of partial weight gradients per block); backward_lds_bytes: dynamic LDS its
-// kernels ask for at least.
+// Backward pass (backward.hip): weight gradients into g, dL/dh into d_h.  backward_plan: layout of its scratch (row
+// gradients, dL/dp, slots of partial weight gradients); backward_lds_bytes: the measure that bounds the shapes it takes.
 struct BackwardPlan {
-    int rows_per_chunk;            // stacked rows per block of the expert kernel
-    long long chunks;              // its grid.x (an upper bound on the chunks in use)
-    int slices_per_block;          // slices per block of the vector-ALU router kernel (its slot of partial weight gradients)
-    long long slice_blocks;        // grid.x of that kernel
-    long long router_slots;        // slots of the router kernel that runs
+    long long expert_slots, router_slots;   // slots of partial weight gradients
     size_t dxrow, dpk, expert_part, router_part, packed, router_scratch, cap, total;   // byte offsets into the workspace, total size
 };
 BackwardPlan backward_plan(const slicemoe_config &c);
@@ -166,6 +161,15 @@ hipError_t launch_backward_expert_mfma(const slicemoe_config &c, const void *h, 
 long long backward_weights_slots(const slicemoe_config &c);
 hipError_t launch_backward_reduce_segments(const slicemoe_config &c, const int32_t *offsets, const float *part, size_t slot,
                                            const slicemoe_weight_grads &g, hipStream_t s);
+// The fp32 backward of every other shape (backward_generic.hip): same outputs.
+long long backward_generic_expert_slots(const slicemoe_config &c);
+long long backward_generic_router_slots(const slicemoe_config &c);
+hipError_t launch_backward_expert_generic(const slicemoe_config &c, const void *h, const slicemoe_weights &w, const void *d_out,
+                                          const float *pk, const int32_t *offsets, const int32_t *perm, size_t slot_floats, float *dxrow,
+                                          float *dpk, float *part, hipStream_t s);
+hipError_t launch_backward_router_generic(const slicemoe_config &c, const void *h, const slicemoe_weights &w, const RouteVariant &v,
+                                          const float *drop_u, float rate, const int32_t *idx, const int32_t *inv, const float *dpk,
+                                          const float *dxrow, void *d_h, size_t slot_floats, float *part, hipStream_t s);
 size_t backward_lds_bytes(const slicemoe_config &c);
 hipError_t launch_backward(const slicemoe_config &c, const void *h, const slicemoe_weights &w, const RouteVariant &v,
                            const float *drop_u, float rate, const int32_t *idx, const float *pk, const int32_t *offsets,

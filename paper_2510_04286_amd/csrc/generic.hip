@@ -1,155 +1,265 @@
-// Generic (vector-ALU, fp32 arithmetic) router and expert kernels.  They take any shape within
-// the library limits and either storage type, and serve the fp32 configuration and every
-// shape the matrix-core kernels do not cover.  Straightforward by design: a block stages RB
-// slices in LDS, one thread per hidden unit accumulates with fmaf in ascending input order.
-#include "common.h"
+// Generic router and expert kernels, fp32 arithmetic.  They take any shape within the library limits and either storage
+// type, and serve the fp32 configuration and every shape the bf16 matrix-core kernels do not cover.
+#include "mfma.h"
+#include "wavefront.h"
 
 namespace slicemoe {
 
-constexpr int kRB = 8;          // slices (rows) per block
+constexpr int kRB = 8;          // slices per block of the router
 constexpr int kGenThreads = 256;
+constexpr int kW2LdsBytes = 40 * 1024;   // Wr2 goes to LDS up to this size (fp32)
 
-// Router of paper Section 3.1: g = ReLU(x Wr1 + br1) Wr2 + br2, softmax over E, top-k on the
-// fp32 logits with ties to the lower expert index.
-template <typename T>
+// Router of paper Section 3.1: g = ReLU(x Wr1 + br1) Wr2 + br2, softmax over E, top-k on the fp32 logits with ties to the
+// lower expert index.  Every pre-activation and logit is one chain of fused multiply-adds in ascending input order (which
+// experts win, and which hidden units are active, depends on no split of the sums), so the chains are what bounds it: one
+// thread per hidden unit with eight slices side by side; one thread per logit, fed from LDS; 32 lanes per slice for the
+// softmax and the selection.  2048 slices, ds = 64, Hr = 256, E = 8: 15.3 -> 11.5 us (logits from memory, softmax
+// by one thread per slice before).
+template <typename T, bool W2LDS>
 __global__ __launch_bounds__(kGenThreads) void route_generic_kernel(
     const T *__restrict__ x, long long Ns, int ds, int Hr, int E, int k,
     const T *__restrict__ Wr1, const T *__restrict__ br1, const T *__restrict__ Wr2, const T *__restrict__ br2,
     const float *__restrict__ noise, float sigma, float inv_tau, int32_t *__restrict__ idx, float *__restrict__ pk)
 {
-    extern __shared__ float smem[];
-    float *xs = smem;                 // [kRB][ds]
-    float *us = xs + kRB * ds;        // [kRB][Hr]
-    float *gs = us + kRB * Hr;        // [kRB][E]
+    extern __shared__ __align__(16) float smem[];
+    const int dsp = (ds + 3) & ~3, ust = Hr + 1;   // row strides: whole quads of features; hidden units of neighbouring slices in different banks
+    float *xs = smem;                 // [kRB][dsp]
+    float *us = xs + kRB * dsp;       // [kRB][ust]
+    float *gs = us + kRB * ust;       // [kRB][E]
+    float *w2s = gs + kRB * E;        // [Hr][E] (W2LDS only)
     const int tid = threadIdx.x;
     const long long n0 = (long long)blockIdx.x * kRB;
     const int rows = (int)min((long long)kRB, Ns - n0);
 
-    for (int i = tid; i < kRB * ds; i += kGenThreads) {
-        const int r = i / ds;
-        xs[i] = r < rows ? Storage<T>::load(x + n0 * ds + i) : 0.f;
+    for (int i = tid; i < kRB * dsp; i += kGenThreads) {
+        const int r = i / dsp, c = i - r * dsp;
+        xs[i] = r < rows && c < ds ? Storage<T>::load(x + (n0 + r) * ds + c) : 0.f;
     }
+    if (W2LDS)
+        for (int i = tid; i < Hr * E; i += kGenThreads) w2s[i] = Storage<T>::load(Wr2 + i);
     __syncthreads();
     for (int j = tid; j < Hr; j += kGenThreads) {
         float acc[kRB];
         const float b = Storage<T>::load(br1 + j);
 #pragma unroll
         for (int r = 0; r < kRB; ++r) acc[r] = b;
-        for (int i = 0; i < ds; ++i) {
+        const int ds4 = ds & ~3;
+#pragma unroll 4
+        for (int i = 0; i < ds4; i += 4) {
+            float wv[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) wv[q] = Storage<T>::load(Wr1 + (size_t)(i + q) * Hr + j);
+#pragma unroll
+            for (int r = 0; r < kRB; ++r) {
+                const float4 xq = *(const float4 *)(xs + r * dsp + i);
+                acc[r] = fmaf(xq.x, wv[0], acc[r]);
+                acc[r] = fmaf(xq.y, wv[1], acc[r]);
+                acc[r] = fmaf(xq.z, wv[2], acc[r]);
+                acc[r] = fmaf(xq.w, wv[3], acc[r]);
+            }
+        }
+        for (int i = ds4; i < ds; ++i) {
             const float wv = Storage<T>::load(Wr1 + (size_t)i * Hr + j);
 #pragma unroll
-            for (int r = 0; r < kRB; ++r) acc[r] = fmaf(xs[r * ds + i], wv, acc[r]);
+            for (int r = 0; r < kRB; ++r) acc[r] = fmaf(xs[r * dsp + i], wv, acc[r]);
         }
 #pragma unroll
-        for (int r = 0; r < kRB; ++r) us[r * Hr + j] = fmaxf(acc[r], 0.f);
+        for (int r = 0; r < kRB; ++r) us[r * ust + j] = fmaxf(acc[r], 0.f);
     }
     __syncthreads();
     for (int t = tid; t < kRB * E; t += kGenThreads) {
         const int r = t / E, e = t - r * E;
         float acc = Storage<T>::load(br2 + e);
-        for (int j = 0; j < Hr; ++j) acc = fmaf(us[r * Hr + j], Storage<T>::load(Wr2 + (size_t)j * E + e), acc);
+#pragma unroll 8
+        for (int j = 0; j < Hr; ++j) acc = fmaf(us[r * ust + j], W2LDS ? w2s[j * E + e] : Storage<T>::load(Wr2 + (size_t)j * E + e), acc);
         // training-time logit noise (Section 5): before the selection and the softmax
         if (noise != nullptr && r < rows) acc = fmaf(sigma, noise[(n0 + r) * E + e], acc);
         gs[t] = acc;
     }
     __syncthreads();
-    if (tid < rows) {
-        float *g = gs + tid * E;
-        float m = g[0];
-        for (int e = 1; e < E; ++e) m = fmaxf(m, g[e]);
-        float den = 0.f;
-        for (int e = 0; e < E; ++e) den += expf((g[e] - m) * inv_tau);   // softmax of g / tau (Appendix B)
-        const long long n = n0 + tid;
-        for (int j = 0; j < k; ++j) {
-            int best = 0;
-            float bv = g[0];
-            for (int e = 1; e < E; ++e)
-                if (g[e] > bv) {
-                    bv = g[e];
-                    best = e;
-                }
+    // 32 lanes per slice, experts l and l + 32
+    const int r = tid >> 5, l = tid & 31;
+    static_assert(kGenThreads == 32 * kRB, "32 lanes per slice");
+    float v0 = l < E ? gs[r * E + l] : -INFINITY, v1 = l + 32 < E ? gs[r * E + l + 32] : -INFINITY;
+    float m = fmaxf(v0, v1);
+    for (int o = 16; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+    float den = (l < E ? expf((v0 - m) * inv_tau) : 0.f) + (l + 32 < E ? expf((v1 - m) * inv_tau) : 0.f);   // softmax of g / tau (Appendix B)
+    for (int o = 16; o > 0; o >>= 1) den += __shfl_xor(den, o);
+    const long long n = n0 + r;
+    for (int j = 0; j < k; ++j) {
+        float bv = v0;
+        int best = l;
+        if (v1 > bv) {
+            bv = v1;
+            best = l + 32;
+        }
+        for (int o = 16; o > 0; o >>= 1) {
+            const float ov = __shfl_xor(bv, o);
+            const int oe = __shfl_xor(best, o);
+            if (ov > bv || (ov == bv && oe < best)) {
+                bv = ov;
+                best = oe;
+            }
+        }
+        best = min(best, E - 1);   // only matters for logits that are not numbers
+        if (l == 0 && r < rows) {
             idx[n * k + j] = best;
             pk[n * k + j] = expf((bv - m) * inv_tau) / den;
-            g[best] = -INFINITY;
         }
+        if (best == l) v0 = -INFINITY;
+        if (best == l + 32) v1 = -INFINITY;
     }
 }
 
 // Expert FFN of Section 3.1 on stacked rows with the Eq. 1 input weighting and the gather fused:
 // y[r] = GELU((p x) W1[e] + b1[e]) W2[e] + b2[e], exact (erf) GELU.  y is fp32 for fp32 storage and
-// fp16 for bf16 storage (same convention as the matrix-core kernel).
-template <typename T, typename YT>
-__global__ __launch_bounds__(kGenThreads) void ffn_generic_kernel(
+// fp16 for bf16 storage (same convention as the bf16 matrix-core kernels).
+// A block of eight wavefronts takes 32 rows of one expert and runs both products on the fp32 matrix instruction
+// (32 x 32 x 2, operands and sums fp32).  First product: a wavefront per 32-wide hidden tile, lane = hidden unit (its weights
+// are coalesced rows of W1), registers = rows; the activations go to LDS; second product: lane = output feature, the
+// hidden units of a tile split over several wavefronts when there are fewer output tiles than wavefronts.  Bound by the
+// matrix instruction (64 cycles each) and the latency of the first weights; 4096 rows, ds = 64, He = 256: 75 ->
+// 16 us (one thread per hidden unit reading its weights once per row before).
+constexpr int kF32Threads = 512, kF32Waves = 8, kF32Rows = 32;
+constexpr int kF32Feat = 128;              // features of the rows staged at a time
+constexpr int kF32Hidden = 32 * kF32Waves;  // hidden units at a time
+constexpr int kF32Batch = 16;               // weight loads in flight per lane
+
+template <typename T, typename YT, int NO>
+__global__ __launch_bounds__(kF32Threads) void ffn_generic_kernel(
     const T *__restrict__ x, const float *__restrict__ pk, const int32_t *__restrict__ offsets,
     const int32_t *__restrict__ perm, int ds, int He, int E, int k,
     const T *__restrict__ W1, const T *__restrict__ b1, const T *__restrict__ W2, const T *__restrict__ b2,
     YT *__restrict__ y)
 {
-    extern __shared__ float smem[];
-    float *xs = smem;             // [kRB][ds]  (already multiplied by p)
-    float *zs = xs + kRB * ds;    // [kRB][He]
-    __shared__ int ex[kRB];
-    const int tid = threadIdx.x;
-    const long long r0 = (long long)blockIdx.x * kRB;
-    const int n_kept = offsets[E];
-    if (r0 >= n_kept) return;
-    const int rows = (int)min((long long)kRB, n_kept - r0);
-    if (tid < kRB) {
-        int e = 0;
-        if (tid < rows) {
-            const int row = (int)r0 + tid;
-            while (e + 1 < E && offsets[e + 1] <= row) ++e;
-        }
-        ex[tid] = e;
-    }
-    for (int i = tid; i < kRB * ds; i += kGenThreads) {
-        const int r = i / ds, c = i - r * ds;
-        float v = 0.f;
-        if (r < rows) {
-            const int a = perm[r0 + r];
-            const long long n = a / k;
-            v = pk[a] * Storage<T>::load(x + n * ds + c);
-        }
-        xs[i] = v;
+    constexpr int XST = kF32Feat + 1, HST = kF32Hidden + 1;
+    __shared__ float xs[kF32Rows * XST];                     // p x, features c0 .. of the rows
+    __shared__ float hs[kF32Waves * kF32Rows * 33];          // activations [row][HST]; then partial outputs [wavefront][row][33]
+    __shared__ int ns[kF32Rows];
+    __shared__ float ps[kF32Rows];
+    static_assert(kF32Rows * HST <= kF32Waves * kF32Rows * 33, "the activations fit");
+    const int tid = threadIdx.x, lane = tid & 63, jj = lane & 31, g = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // the block's expert and rows: units of 32 counted from each expert's first row
+    const int off_lo = offsets[min(lane, E)], off_hi = offsets[min(lane + 1, E)];
+    const int units = (off_hi - off_lo + kF32Rows - 1) / kF32Rows, first = wavefront_exclusive_scan(units, lane);
+    const unsigned long long mine = __ballot((int)blockIdx.x >= first && (int)blockIdx.x < first + units);
+    if (mine == 0) return;   // the grid is an upper bound; uniform
+    const int e = __builtin_ctzll(mine);
+    const int row0 = __builtin_amdgcn_readlane(off_lo, e) + ((int)blockIdx.x - __builtin_amdgcn_readlane(first, e)) * kF32Rows;
+    const int nrows = min(kF32Rows, __builtin_amdgcn_readlane(off_hi, e) - row0);
+    const T *w1 = W1 + (size_t)e * ds * He, *w2 = W2 + (size_t)e * He * ds;
+    if (tid < kF32Rows) {
+        const int a = perm[row0 + min(tid, nrows - 1)];
+        ns[tid] = a / k;
+        ps[tid] = tid < nrows ? pk[a] : 0.f;
     }
     __syncthreads();
-    for (int j = tid; j < He; j += kGenThreads) {
-        for (int r = 0; r < rows; ++r) {
-            const int e = ex[r];
-            const T *w = W1 + (size_t)e * ds * He + j;
-            float acc = Storage<T>::load(b1 + (size_t)e * He + j);
-            for (int i = 0; i < ds; ++i) acc = fmaf(xs[r * ds + i], Storage<T>::load(w + (size_t)i * He), acc);
-            zs[r * He + j] = 0.5f * acc * (1.f + erff(acc * 0.70710678118654752f));
+
+    const int OT = (ds + 31) / 32, parts = OT >= kF32Waves ? 1 : kF32Waves / OT;
+    const int part = OT >= kF32Waves ? 0 : wave / OT, ot0 = OT >= kF32Waves ? wave : wave % OT;
+    f32x16 yacc[NO];
+#pragma unroll
+    for (int o = 0; o < NO; ++o)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) yacc[o][i] = 0.f;
+    for (int h0 = 0; h0 < He; h0 += kF32Hidden) {
+        const int hid = h0 + wave * 32 + jj, hidc = min(hid, He - 1);
+        f32x16 z;
+        const float bias = Storage<T>::load(b1 + (size_t)e * He + hidc);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) z[i] = bias;
+        for (int c0 = 0; c0 < ds; c0 += kF32Feat) {
+            const int nf = min(kF32Feat, ds - c0), nf2 = (nf + 1) & ~1;
+            if (h0 == 0 || ds > kF32Feat) {
+                __syncthreads();   // everyone is done with the features before
+                for (int i = tid; i < kF32Rows * kF32Feat; i += kF32Threads) {
+                    const int r = i / kF32Feat, c = i % kF32Feat;
+                    if (c < nf2) xs[r * XST + c] = c < nf ? ps[r] * Storage<T>::load(x + (size_t)ns[r] * ds + c0 + c) : 0.f;
+                }
+                __syncthreads();
+            }
+            const T *wp = w1 + (size_t)c0 * He + hidc;
+            for (int k0 = 0; k0 < nf2; k0 += 2 * kF32Batch) {
+                float b[kF32Batch];   // a batch of weights in flight at a time
+#pragma unroll
+                for (int s = 0; s < kF32Batch; ++s) b[s] = k0 + 2 * s + g < nf ? Storage<T>::load(wp + (size_t)(k0 + 2 * s + g) * He) : 0.f;
+#pragma unroll
+                for (int s = 0; s < kF32Batch; ++s)
+                    if (k0 + 2 * s < nf2) z = __builtin_amdgcn_mfma_f32_32x32x2f32(xs[jj * XST + k0 + 2 * s + g], b[s], z, 0, 0, 0);
+            }
+        }
+        __syncthreads();   // everyone is done with the activations before
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            hs[acc_feature(i, g) * HST + wave * 32 + jj] = hid < He ? 0.5f * z[i] * (1.f + erff(z[i] * 0.70710678118654752f)) : 0.f;
+        __syncthreads();
+        if (part < parts) {
+            const int per = (kF32Hidden / parts + 1) & ~1, k0 = part * per, k1 = min(min(k0 + per, kF32Hidden), (He - h0 + 1) & ~1);
+#pragma unroll
+            for (int o = 0; o < NO; ++o) {
+                const int f = 32 * (ot0 + kF32Waves * o) + jj, fc = min(f, ds - 1);
+                if (32 * (ot0 + kF32Waves * o) < ds) {
+                    for (int kb = k0; kb < k1; kb += 2 * kF32Batch) {
+                        float b[kF32Batch];
+#pragma unroll
+                        for (int s = 0; s < kF32Batch; ++s)
+                            b[s] = h0 + kb + 2 * s + g < He && kb + 2 * s < k1 ? Storage<T>::load(w2 + (size_t)(h0 + kb + 2 * s + g) * ds + fc) : 0.f;
+#pragma unroll
+                        for (int s = 0; s < kF32Batch; ++s)
+                            if (kb + 2 * s < k1) yacc[o] = __builtin_amdgcn_mfma_f32_32x32x2f32(hs[jj * HST + kb + 2 * s + g], b[s], yacc[o], 0, 0, 0);
+                    }
+                }
+            }
         }
     }
-    __syncthreads();
-    for (int t = tid; t < rows * ds; t += kGenThreads) {
-        const int r = t / ds, c = t - r * ds;
-        const int e = ex[r];
-        const T *w = W2 + (size_t)e * He * ds + c;
-        float acc = Storage<T>::load(b2 + (size_t)e * ds + c);
-        for (int j = 0; j < He; ++j) acc = fmaf(zs[r * He + j], Storage<T>::load(w + (size_t)j * ds), acc);
-        y[(r0 + r) * ds + c] = (YT)acc;
+    if (parts == 1) {   // lane = feature, registers = rows
+#pragma unroll
+        for (int o = 0; o < NO; ++o) {
+            const int f = 32 * (ot0 + kF32Waves * o) + jj;
+            if (f < ds) {
+                const float bias = Storage<T>::load(b2 + (size_t)e * ds + f);
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    if (acc_feature(i, g) < nrows) y[(size_t)(row0 + acc_feature(i, g)) * ds + f] = (YT)(yacc[o][i] + bias);
+            }
+        }
+        return;
     }
+    __syncthreads();
+    if (part < parts)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) hs[(wave * kF32Rows + acc_feature(i, g)) * 33 + jj] = yacc[0][i];
+    __syncthreads();
+    for (int t = tid; t < nrows * ds; t += kF32Threads) {
+        const int r = t / ds, f = t - r * ds;
+        float v = Storage<T>::load(b2 + (size_t)e * ds + f);
+        for (int q = 0; q < parts; ++q) v += hs[((q * OT + (f >> 5)) * kF32Rows + r) * 33 + (f & 31)];
+        y[(size_t)(row0 + r) * ds + f] = (YT)v;
+    }
+}
+
+template <typename T>
+static void run_route_generic(const slicemoe_config &c, const void *h, const slicemoe_weights &w, int32_t *idx, float *p, hipStream_t s,
+                              const RouteVariant &v)
+{
+    const long long Ns = (long long)c.T * c.S;
+    const int ds = c.d / c.S;
+    const int blocks = (int)((Ns + kRB - 1) / kRB);
+    const float *noise = v.sigma > 0.f ? v.noise : nullptr;
+    const size_t smem = sizeof(float) * (size_t)kRB * (((ds + 3) & ~3) + c.Hr + 1 + c.E), w2 = sizeof(float) * (size_t)c.Hr * c.E;
+    const bool w2lds = w2 <= kW2LdsBytes && smem + w2 <= 64 * 1024;
+    auto kern = w2lds ? route_generic_kernel<T, true> : route_generic_kernel<T, false>;
+    kern<<<blocks, kGenThreads, smem + (w2lds ? w2 : 0), s>>>((const T *)h, Ns, ds, c.Hr, c.E, c.k, (const T *)w.Wr1, (const T *)w.br1,
+                                                              (const T *)w.Wr2, (const T *)w.br2, noise, v.sigma, v.inv_tau, idx, p);
 }
 
 hipError_t launch_route_generic(const slicemoe_config &c, const void *h, const slicemoe_weights &w,
                                 int32_t *idx, float *p, hipStream_t s, const RouteVariant &v)
 {
-    const long long Ns = (long long)c.T * c.S;
-    if (Ns == 0) return hipSuccess;
-    const int ds = c.d / c.S;
-    const int blocks = (int)((Ns + kRB - 1) / kRB);
-    const float *noise = v.sigma > 0.f ? v.noise : nullptr;
-    const size_t smem = sizeof(float) * (size_t)kRB * (ds + c.Hr + c.E);
-    if (c.dtype == SLICEMOE_BF16)
-        route_generic_kernel<bf16_t><<<blocks, kGenThreads, smem, s>>>(
-            (const bf16_t *)h, Ns, ds, c.Hr, c.E, c.k, (const bf16_t *)w.Wr1, (const bf16_t *)w.br1,
-            (const bf16_t *)w.Wr2, (const bf16_t *)w.br2, noise, v.sigma, v.inv_tau, idx, p);
-    else
-        route_generic_kernel<float><<<blocks, kGenThreads, smem, s>>>(
-            (const float *)h, Ns, ds, c.Hr, c.E, c.k, (const float *)w.Wr1, (const float *)w.br1,
-            (const float *)w.Wr2, (const float *)w.br2, noise, v.sigma, v.inv_tau, idx, p);
+    if ((long long)c.T * c.S == 0) return hipSuccess;
+    if (c.dtype == SLICEMOE_BF16) run_route_generic<bf16_t>(c, h, w, idx, p, s, v);
+    else run_route_generic<float>(c, h, w, idx, p, s, v);
     return hipGetLastError();
 }
 
@@ -191,23 +301,26 @@ hipError_t launch_route_dropout(const slicemoe_config &c, float *p, const float 
     return hipGetLastError();
 }
 
+template <typename T, typename YT>
+static void run_ffn_generic(const slicemoe_config &c, const void *h, const float *p, const int32_t *offsets, const int32_t *perm,
+                            const slicemoe_weights &w, void *y, hipStream_t s)
+{
+    const long long Na = (long long)c.T * c.S * c.k;
+    const int ds = c.d / c.S, no = ((ds + 31) / 32 + kF32Waves - 1) / kF32Waves;   // output tiles per wavefront: ds < 2048
+    const long long blocks = Na / kF32Rows + (Na < c.E ? Na : c.E);                 // at most one partial unit per expert
+    auto kern = no <= 1 ? ffn_generic_kernel<T, YT, 1> : no <= 2 ? ffn_generic_kernel<T, YT, 2> : no <= 4 ? ffn_generic_kernel<T, YT, 4>
+                                                                                               : ffn_generic_kernel<T, YT, 8>;
+    kern<<<(unsigned)blocks, kF32Threads, 0, s>>>((const T *)h, p, offsets, perm, ds, c.He, c.E, c.k, (const T *)w.W1, (const T *)w.b1,
+                                                  (const T *)w.W2, (const T *)w.b2, (YT *)y);
+}
+
 hipError_t launch_ffn_generic(const slicemoe_config &c, const void *h, const float *p,
                               const int32_t *offsets, const int32_t *perm, const slicemoe_weights &w,
                               void *y, hipStream_t s)
 {
-    const long long Na = (long long)c.T * c.S * c.k;
-    if (Na == 0) return hipSuccess;
-    const int ds = c.d / c.S;
-    const int blocks = (int)((Na + kRB - 1) / kRB);
-    const size_t smem = sizeof(float) * (size_t)kRB * (ds + c.He);
-    if (c.dtype == SLICEMOE_BF16)
-        ffn_generic_kernel<bf16_t, _Float16><<<blocks, kGenThreads, smem, s>>>(
-            (const bf16_t *)h, p, offsets, perm, ds, c.He, c.E, c.k, (const bf16_t *)w.W1,
-            (const bf16_t *)w.b1, (const bf16_t *)w.W2, (const bf16_t *)w.b2, (_Float16 *)y);
-    else
-        ffn_generic_kernel<float, float><<<blocks, kGenThreads, smem, s>>>(
-            (const float *)h, p, offsets, perm, ds, c.He, c.E, c.k, (const float *)w.W1,
-            (const float *)w.b1, (const float *)w.W2, (const float *)w.b2, (float *)y);
+    if ((long long)c.T * c.S * c.k == 0) return hipSuccess;
+    if (c.dtype == SLICEMOE_BF16) run_ffn_generic<bf16_t, _Float16>(c, h, p, offsets, perm, w, y, s);
+    else run_ffn_generic<float, float>(c, h, p, offsets, perm, w, y, s);
     return hipGetLastError();
 }
 
