@@ -62,6 +62,139 @@ __device__ __forceinline__ f32x16 load_bias_tile(const float *__restrict__ b, in
     return r;
 }
 
+// What follows the second layer, for one slice per lane pair (j, j + 32) and v[16 et + r] the logit of expert
+// 32 et + acc_feature(r, g): logit noise, softmax, top-k, and the selections added to the LDS table counts[64].
+template <int ET>
+__device__ __forceinline__ void select_experts(float (&v)[ET * 16], long long n, bool valid, int g, int E, int k,
+                                               const float *__restrict__ noise, float sigma, float exp_scale,
+                                               int32_t *__restrict__ idx, float *__restrict__ pk, bool count, int *counts)
+{
+    if (noise != nullptr) {   // training-time logit noise: g += sigma * draw, before the selection and the softmax
+        const float *nr = noise + (valid ? n : 0) * E;
+        if ((E & 3) == 0) {   // rows of the table are 16-byte aligned: this lane's four consecutive experts at once
+#pragma unroll
+            for (int et = 0; et < ET; ++et)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int e0 = et * 32 + 8 * q + 4 * g;
+                    if (e0 < E) {
+                        const f32x4 z = *(const f32x4 *)(nr + e0);
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) v[et * 16 + 4 * q + c] = fmaf(sigma, z[c], v[et * 16 + 4 * q + c]);
+                    }
+                }
+        } else {
+#pragma unroll
+            for (int et = 0; et < ET; ++et)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int e = et * 32 + acc_feature(r, g);
+                    if (e < E) v[et * 16 + r] = fmaf(sigma, nr[e], v[et * 16 + r]);
+                }
+        }
+    }
+    if (E != ET * 32) {   // padded experts never win
+#pragma unroll
+        for (int et = 0; et < ET; ++et)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                if (et * 32 + acc_feature(r, g) >= E) v[et * 16 + r] = -INFINITY;
+    }
+    // Largest and second-largest logit of the lane (the median of the running pair and a new value is the new
+    // second), then of the slice: lanes j and j + 32 trade values with one swap instruction whose two results are
+    // {own, other} in an order that max / min / + do not care about.
+    // (the maximum as a median with +infinity: the median instruction takes its operands as they are, while a
+    // floating-point maximum would first spend an instruction on quieting each of them)
+    float kInf;   // (opaque to the compiler, which would otherwise turn the medians back into maxima)
+    asm("v_mov_b32 %0, 0x7f800000" : "=v"(kInf));
+    float m = v[0], second = -INFINITY;
+#pragma unroll
+    for (int i = 1; i < ET * 16; ++i) {
+        second = __builtin_amdgcn_fmed3f(m, second, v[i]);
+        m = __builtin_amdgcn_fmed3f(m, v[i], kInf);
+    }
+    {
+        const auto sm = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
+        const auto ss = __builtin_amdgcn_permlane32_swap(__float_as_uint(second), __float_as_uint(second), false, false);
+        const float m0 = __uint_as_float(sm[0]), m1 = __uint_as_float(sm[1]);
+        m = __builtin_amdgcn_fmed3f(m0, m1, kInf);
+        const float lower = __builtin_amdgcn_fmed3f(m0, m1, -kInf);   // the smaller of the two maxima (the negation is an operand modifier)
+        second = __builtin_amdgcn_fmed3f(__builtin_amdgcn_fmed3f(__uint_as_float(ss[0]), __uint_as_float(ss[1]), kInf), lower, kInf);
+    }
+    // softmax denominator: exp((v - m) / tau) = exp2(v * c - m * c) with c = log2(e) / tau, one multiply-add and
+    // one exp2 per logit
+    const float kLog2e = exp_scale;
+    const float nm = -m * kLog2e;
+    float den = 0.f;
+#pragma unroll
+    for (int i = 0; i < ET * 16; ++i) den += __builtin_amdgcn_exp2f(fmaf(v[i], kLog2e, nm));
+    {
+        const auto sd = __builtin_amdgcn_permlane32_swap(__float_as_uint(den), __float_as_uint(den), false, false);
+        den = __uint_as_float(sd[0]) + __uint_as_float(sd[1]);
+    }
+    const float rden = __builtin_amdgcn_rcpf(den);   // within one unit in the last place, like the exp2 above
+
+    // k = 2 with distinct top values (wavefront-wide; anything else takes the general selection below): the two
+    // experts are where the two values sit, the lowest index among equals of the second value
+    bool picked = false;
+    if (k == 2 && __builtin_amdgcn_ballot_w64(!(m > second)) == 0) {
+        constexpr int kNone = 1 << 20;
+        int ia = kNone, ib = kNone;
+#pragma unroll
+        for (int i = ET * 16 - 1; i >= 0; --i) {
+            const int e0 = (i >> 4) * 32 + acc_feature(i & 15, 0);   // + 4 g below: constants here
+            ia = v[i] == m ? e0 : ia;
+            ib = v[i] == second ? e0 : ib;
+        }
+        ia += 4 * g;
+        ib += 4 * g;
+        const auto sa = __builtin_amdgcn_permlane32_swap((uint32_t)ia, (uint32_t)ia, false, false);
+        const auto sb = __builtin_amdgcn_permlane32_swap((uint32_t)ib, (uint32_t)ib, false, false);
+        ia = min(min((int)sa[0], (int)sa[1]), E - 1);   // the bound only matters for logits that are not numbers
+        ib = min(min((int)sb[0], (int)sb[1]), E - 1);
+        if (valid && g == 0) {
+            idx[n * 2] = ia;
+            idx[n * 2 + 1] = ib;
+            pk[n * 2] = __builtin_amdgcn_exp2f(fmaf(m, kLog2e, nm)) * rden;
+            pk[n * 2 + 1] = __builtin_amdgcn_exp2f(fmaf(second, kLog2e, nm)) * rden;
+            if (count) {
+                atomicAdd(&counts[ia], 1);
+                atomicAdd(&counts[ib], 1);
+            }
+        }
+        picked = true;
+    }
+
+    for (int jj = 0; jj < (picked ? 0 : k); ++jj) {
+        float bv = v[0];
+        int be = acc_feature(0, g);
+#pragma unroll
+        for (int i = 1; i < ET * 16; ++i) {
+            const int e = (i >> 4) * 32 + acc_feature(i & 15, g);
+            if (v[i] > bv) {
+                bv = v[i];
+                be = e;
+            }
+        }
+        const float ov = __shfl_xor(bv, 32);
+        const int oe = __shfl_xor(be, 32);
+        if (ov > bv || (ov == bv && oe < be)) {
+            bv = ov;
+            be = oe;
+        }
+#pragma unroll
+        for (int i = 0; i < ET * 16; ++i) {
+            const int e = (i >> 4) * 32 + acc_feature(i & 15, g);
+            if (e == be) v[i] = -INFINITY;
+        }
+        if (valid && g == 0) {
+            idx[n * k + jj] = be;
+            pk[n * k + jj] = __builtin_amdgcn_exp2f(fmaf(bv, kLog2e, nm)) * rden;
+            if (count) atomicAdd(&counts[be], 1);
+        }
+    }
+}
+
 // One block per CU shares one LDS copy of the router, with as many wavefronts as the registers allow: a wavefront's
 // chain  GEMM1 -> ReLU/split -> GEMM2  is serial, so only other wavefronts fill the matrix pipe while it does vector work or
 // waits for the LDS.  THREADS = 1024 (16 wavefronts, <= 128 VGPRs) for the small shapes, 768 (<= 168) where two expert
@@ -178,130 +311,7 @@ __global__ __launch_bounds__(THREADS) void route_mfma_kernel(
         for (int et = 0; et < ET; ++et)
 #pragma unroll
             for (int r = 0; r < 16; ++r) v[et * 16 + r] = gacc[et][r];
-        if (noise != nullptr) {   // training-time logit noise: g += sigma * draw, before the selection and the softmax
-            const float *nr = noise + (valid ? n : 0) * E;
-            if ((E & 3) == 0) {   // rows of the table are 16-byte aligned: this lane's four consecutive experts at once
-#pragma unroll
-                for (int et = 0; et < ET; ++et)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int e0 = et * 32 + 8 * q + 4 * g;
-                        if (e0 < E) {
-                            const f32x4 z = *(const f32x4 *)(nr + e0);
-#pragma unroll
-                            for (int c = 0; c < 4; ++c) v[et * 16 + 4 * q + c] = fmaf(sigma, z[c], v[et * 16 + 4 * q + c]);
-                        }
-                    }
-            } else {
-#pragma unroll
-                for (int et = 0; et < ET; ++et)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const int e = et * 32 + acc_feature(r, g);
-                        if (e < E) v[et * 16 + r] = fmaf(sigma, nr[e], v[et * 16 + r]);
-                    }
-            }
-        }
-        if (E != ET * 32) {   // padded experts never win
-#pragma unroll
-            for (int et = 0; et < ET; ++et)
-#pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    if (et * 32 + acc_feature(r, g) >= E) v[et * 16 + r] = -INFINITY;
-        }
-        // Largest and second-largest logit of the lane (the median of the running pair and a new value is the new
-        // second), then of the slice: lanes j and j + 32 trade values with one swap instruction whose two results are
-        // {own, other} in an order that max / min / + do not care about.
-        // (the maximum as a median with +infinity: the median instruction takes its operands as they are, while a
-        // floating-point maximum would first spend an instruction on quieting each of them)
-        float kInf;   // (opaque to the compiler, which would otherwise turn the medians back into maxima)
-        asm("v_mov_b32 %0, 0x7f800000" : "=v"(kInf));
-        float m = v[0], second = -INFINITY;
-#pragma unroll
-        for (int i = 1; i < ET * 16; ++i) {
-            second = __builtin_amdgcn_fmed3f(m, second, v[i]);
-            m = __builtin_amdgcn_fmed3f(m, v[i], kInf);
-        }
-        {
-            const auto sm = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
-            const auto ss = __builtin_amdgcn_permlane32_swap(__float_as_uint(second), __float_as_uint(second), false, false);
-            const float m0 = __uint_as_float(sm[0]), m1 = __uint_as_float(sm[1]);
-            m = __builtin_amdgcn_fmed3f(m0, m1, kInf);
-            const float lower = __builtin_amdgcn_fmed3f(m0, m1, -kInf);   // the smaller of the two maxima (the negation is an operand modifier)
-            second = __builtin_amdgcn_fmed3f(__builtin_amdgcn_fmed3f(__uint_as_float(ss[0]), __uint_as_float(ss[1]), kInf), lower, kInf);
-        }
-        // softmax denominator: exp((v - m) / tau) = exp2(v * c - m * c) with c = log2(e) / tau, one multiply-add and
-        // one exp2 per logit
-        const float kLog2e = exp_scale;
-        const float nm = -m * kLog2e;
-        float den = 0.f;
-#pragma unroll
-        for (int i = 0; i < ET * 16; ++i) den += __builtin_amdgcn_exp2f(fmaf(v[i], kLog2e, nm));
-        {
-            const auto sd = __builtin_amdgcn_permlane32_swap(__float_as_uint(den), __float_as_uint(den), false, false);
-            den = __uint_as_float(sd[0]) + __uint_as_float(sd[1]);
-        }
-        const float rden = __builtin_amdgcn_rcpf(den);   // within one unit in the last place, like the exp2 above
-
-        // k = 2 with distinct top values (wavefront-wide; anything else takes the general selection below): the two
-        // experts are where the two values sit, the lowest index among equals of the second value
-        bool picked = false;
-        if (k == 2 && __builtin_amdgcn_ballot_w64(!(m > second)) == 0) {
-            constexpr int kNone = 1 << 20;
-            int ia = kNone, ib = kNone;
-#pragma unroll
-            for (int i = ET * 16 - 1; i >= 0; --i) {
-                const int e0 = (i >> 4) * 32 + acc_feature(i & 15, 0);   // + 4 g below: constants here
-                ia = v[i] == m ? e0 : ia;
-                ib = v[i] == second ? e0 : ib;
-            }
-            ia += 4 * g;
-            ib += 4 * g;
-            const auto sa = __builtin_amdgcn_permlane32_swap((uint32_t)ia, (uint32_t)ia, false, false);
-            const auto sb = __builtin_amdgcn_permlane32_swap((uint32_t)ib, (uint32_t)ib, false, false);
-            ia = min(min((int)sa[0], (int)sa[1]), E - 1);   // the bound only matters for logits that are not numbers
-            ib = min(min((int)sb[0], (int)sb[1]), E - 1);
-            if (valid && g == 0) {
-                idx[n * 2] = ia;
-                idx[n * 2 + 1] = ib;
-                pk[n * 2] = __builtin_amdgcn_exp2f(fmaf(m, kLog2e, nm)) * rden;
-                pk[n * 2 + 1] = __builtin_amdgcn_exp2f(fmaf(second, kLog2e, nm)) * rden;
-                if (hist != nullptr) {
-                    atomicAdd(&hcnt[round * 64 + ia], 1);
-                    atomicAdd(&hcnt[round * 64 + ib], 1);
-                }
-            }
-            picked = true;
-        }
-
-        for (int jj = 0; jj < (picked ? 0 : k); ++jj) {
-            float bv = v[0];
-            int be = acc_feature(0, g);
-#pragma unroll
-            for (int i = 1; i < ET * 16; ++i) {
-                const int e = (i >> 4) * 32 + acc_feature(i & 15, g);
-                if (v[i] > bv) {
-                    bv = v[i];
-                    be = e;
-                }
-            }
-            const float ov = __shfl_xor(bv, 32);
-            const int oe = __shfl_xor(be, 32);
-            if (ov > bv || (ov == bv && oe < be)) {
-                bv = ov;
-                be = oe;
-            }
-#pragma unroll
-            for (int i = 0; i < ET * 16; ++i) {
-                const int e = (i >> 4) * 32 + acc_feature(i & 15, g);
-                if (e == be) v[i] = -INFINITY;
-            }
-            if (valid && g == 0) {
-                idx[n * k + jj] = be;
-                pk[n * k + jj] = __builtin_amdgcn_exp2f(fmaf(bv, kLog2e, nm)) * rden;
-                if (hist != nullptr) atomicAdd(&hcnt[round * 64 + be], 1);
-            }
-        }
+        select_experts<ET>(v, n, valid, g, E, k, noise, sigma, exp_scale, idx, pk, hist != nullptr, hcnt + round * 64);
         if (hist != nullptr) {
             // The LDS executes a wavefront's operations in order, so this wavefront's additions above are in the table
             // before its ticket; the wavefront that draws the last ticket of the chunk therefore sees everybody's.
@@ -326,6 +336,122 @@ __global__ __launch_bounds__(THREADS) void route_mfma_kernel(
     }
 }
 
+// Small batches, whose tiles would leave most CUs without a block of the kernel above (512 slices are 16 tiles, one
+// block of sixteen wavefronts).  What bounds them is latency: the router's 48 KiB (width 64) to the LDS, then one
+// wavefront's serial chain over eight hidden tiles.  Here the eight wavefronts of a block share a tile, each with one
+// of the eight hidden tiles, whose fragments it keeps in registers (read straight from memory: nobody else in the block
+// needs them), and leave their parts of the logits in the LDS; one wavefront per tile adds them up in order and selects.
+// A block takes up to NB consecutive tiles.
+// Measured, whole forward: 32 tokens of d = 1024, S = 16: 28.7 -> 23.4 us; 4095 tokens of d = 512, S = 8: 36.6 -> 33.1 us;
+// 5001 tokens of d = 768, S = 4: 78 -> 70 us.
+constexpr int kSplitThreads = kRouteHT * 64, kSplitTiles = 4;
+template <int DS, int ET> struct SplitTile {
+    static constexpr int NB = kSplitTiles / ET;                     // 128 KiB of partial logits
+    static constexpr bool HOLD = SliceTiles<DS>::KS <= (ET == 1 ? 12 : 8);          // first-layer fragments and a tile's rows ahead in registers
+    static constexpr size_t lds = (size_t)kRouteHT * NB * ET * 4096 + 64 * 4;
+};
+template <int DS, int ET>
+__global__ __launch_bounds__(kSplitThreads) void route_split_kernel(
+    const bf16_t *__restrict__ x, long long Ns, int E, int k, const char *__restrict__ packed, size_t off_w1, size_t off_w2,
+    size_t off_b1, size_t off_b2, const float *__restrict__ noise, float sigma, float exp_scale, int tiles,
+    int32_t *__restrict__ idx, float *__restrict__ pk, uint16_t *__restrict__ hist /* may be null */, int hist_stride)
+{
+    constexpr int KS = SliceTiles<DS>::KS, NB = SplitTile<DS, ET>::NB;
+    constexpr bool HOLD = SplitTile<DS, ET>::HOLD;
+    extern __shared__ __align__(16) char lds[];
+    f32x4 *part = (f32x4 *)lds;                                         // [wavefront][NB][ET][4][64]
+    int *hcnt = (int *)(lds + (size_t)kRouteHT * NB * ET * 4096);       // [64]
+    const int tid = threadIdx.x, lane = tid & 63, j = lane & 31, g = lane >> 5;
+    const int ht = __builtin_amdgcn_readfirstlane(tid >> 6);            // this wavefront's hidden tile
+    const int ntiles = (int)((Ns + 31) / 32);
+    const int tile0 = (int)blockIdx.x * tiles, tile_end = min(ntiles, tile0 + tiles);
+
+    auto load_x = [&](int tile, bf16x8 (&xb)[KS]) {
+        const long long n = (long long)tile * 32 + j;
+        const uint4 *xr = (const uint4 *)(x + (tile < tile_end && n < Ns ? n : 0) * DS);   // a lane without a slice reads slice 0
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) xb[ks] = load_row_piece<DS>(xr, ks, g);
+    };
+    bf16x8 xb[KS];
+    load_x(tile0, xb);
+    const uint4 *w1 = (const uint4 *)(packed + off_w1) + ht * KS * 64 + lane;
+    uint4 w1r[HOLD ? KS : 1], w2r[ET][2];
+    if constexpr (HOLD) {
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) w1r[ks] = w1[ks * 64];
+    }
+#pragma unroll
+    for (int et = 0; et < ET; ++et)
+#pragma unroll
+        for (int s = 0; s < 2; ++s) w2r[et][s] = ((const uint4 *)(packed + off_w2))[((et * kRouteHT + ht) * 2 + s) * 64 + lane];
+    const f32x16 bias1 = load_bias_tile((const float *)(packed + off_b1), ht, g);
+    f32x16 bias2[ET];
+#pragma unroll
+    for (int et = 0; et < ET; ++et) bias2[et] = load_bias_tile((const float *)(packed + off_b2), et, g);
+    if (tid < 64) hcnt[tid] = 0;
+
+#pragma unroll
+    for (int t = 0; t < NB; ++t) {
+        if (tile0 + t >= tile_end) break;
+        bf16x8 xn[HOLD ? KS : 1];
+        if constexpr (HOLD) load_x(tile0 + t + 1, xn);
+        else if (t > 0) load_x(tile0 + t, xb);
+        f32x16 acc = bias1;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) acc = mfma_bf16(__builtin_bit_cast(bf16x8, HOLD ? w1r[HOLD ? ks : 0] : w1[ks * 64]), xb[ks], acc);
+        uint32_t t0[8], t1[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) relu_split_pair(acc[2 * i], acc[2 * i + 1], t0[i], t1[i]);
+#pragma unroll
+        for (int et = 0; et < ET; ++et) {
+            f32x16 lg;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) lg[r] = 0.f;
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {   // small term first
+                const f16x8 a2 = __builtin_bit_cast(f16x8, w2r[et][s]);
+                const f16x8 u0 = __builtin_bit_cast(f16x8, make_uint4(t0[4 * s], t0[4 * s + 1], t0[4 * s + 2], t0[4 * s + 3]));
+                const f16x8 u1 = __builtin_bit_cast(f16x8, make_uint4(t1[4 * s], t1[4 * s + 1], t1[4 * s + 2], t1[4 * s + 3]));
+                lg = __builtin_amdgcn_mfma_f32_32x32x16_f16(a2, u1, lg, 0, 0, 0);
+                lg = __builtin_amdgcn_mfma_f32_32x32x16_f16(a2, u0, lg, 0, 0, 0);
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                part[(((ht * NB + t) * ET + et) * 4 + q) * 64 + lane] = f32x4{lg[4 * q], lg[4 * q + 1], lg[4 * q + 2], lg[4 * q + 3]};
+        }
+        if constexpr (HOLD) {
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) xb[ks] = xn[ks];
+        }
+    }
+    __syncthreads();
+    if (ht < NB && tile0 + ht < tile_end) {   // this wavefront's tile
+        float v[ET * 16];
+#pragma unroll
+        for (int et = 0; et < ET; ++et)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) v[et * 16 + r] = bias2[et][r];
+        for (int w = 0; w < kRouteHT; ++w)
+#pragma unroll
+            for (int i = 0; i < ET * 4; ++i) {
+                const f32x4 p = part[((w * NB + ht) * ET * 4 + i) * 64 + lane];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) v[4 * i + c] += p[c];
+            }
+        const long long n = (long long)(tile0 + ht) * 32 + j;
+        select_experts<ET>(v, n, n < Ns, g, E, k, noise, sigma, exp_scale, idx, pk, hist != nullptr, hcnt);
+    }
+    if (hist != nullptr) {
+        __syncthreads();
+        if (tid < E) {
+            uint16_t *row = hist + (size_t)tid * hist_stride;
+            row[blockIdx.x] = (uint16_t)hcnt[tid];
+            if (blockIdx.x == gridDim.x - 1)   // the padding of a row reads as zero
+                for (int c = (int)gridDim.x; c < hist_stride; ++c) row[c] = 0;
+        }
+    }
+}
+
 // Threads per block of the instantiation that serves a slice width and a number of 32-expert tiles (see the kernel).
 static int route_threads(int ds, int et)
 {
@@ -346,13 +472,28 @@ static long long route_blocks(long long Ns, int chunk_tiles)
     return nchunks < cap ? nchunks : cap;
 }
 
-// Assignments per chunk of the histogram this router can leave behind, or 0: the chunk must be worth a dispatch block
+// Tiles per block of the kernel for small batches, or 0: the batch is for the other kernel.  As many tiles per CU as a block
+// holds at once: measured at width 64 with 32 experts (whole forward, other kernel / this one) 28.3 / 23.3 us with a tile on
+// every fourth CU, 29.6 / 23.6 with one per CU, 36.8 / 33.6 with four, 40.5 / 39.9 with six, 42.6 / 44.1 with eight; at width
+// 128 with 64 experts 64.4 / 58.0 with one, 66.5 / 61.6 with two, 68.4 / 68.1 with three, 68.7 / 70.2 with four; at width 192
+// 74.2 / 70.3 with three, 113.4 / 113.0 with four.  Width 384: a tile's rows and first-layer fragments exceed the registers.
+static int split_tiles(int ds, int et, long long Ns)
+{
+    const long long ntiles = (Ns + 31) / 32, cus = num_compute_units();
+    return ds != 384 && ntiles <= cus * (kSplitTiles / et) ? (int)((ntiles + cus - 1) / cus) : 0;
+}
+
+// Assignments per chunk of the histogram this router can leave behind, or 0.  Outside the small batches the chunk must be worth a dispatch block
 // (at least 512 assignments, at most kDispMaxItems rounds of it) and a block's rounds must fit the LDS slots.
 int route_mfma_hist_chunk(const slicemoe_config &c)
 {
     const long long Ns = (long long)c.T * c.S;
     if (Ns == 0) return 0;
     const int ds = c.d / c.S, et = (c.E + 31) / 32;
+    if (const int tiles = split_tiles(ds, et, Ns)) {   // a block is a chunk; its table is 16-bit counts
+        const int chunk = tiles * 32 * c.k;
+        return chunk <= kDispThreads * kDispMaxItems && dispatch_geometry(Ns * c.k, c.E, chunk).fused ? chunk : 0;
+    }
     const int chunk_tiles = route_threads(ds, et) / 64;
     const int chunk = chunk_tiles * 32 * c.k;
     if (chunk < 512 || chunk > kDispThreads * kDispMaxItems) return 0;
@@ -360,6 +501,27 @@ int route_mfma_hist_chunk(const slicemoe_config &c)
     const long long nchunks = (ntiles + chunk_tiles - 1) / chunk_tiles, blocks = route_blocks(Ns, chunk_tiles);
     if ((nchunks + blocks - 1) / blocks > kRouteHistMaxRounds) return 0;
     return chunk;
+}
+
+template <int DS, int ET>
+static hipError_t run_split(const slicemoe_config &c, const PackedLayout &L, const void *h, const void *packed, int32_t *idx, float *p,
+                            hipStream_t s, const RouteVariant &v, int32_t *hist, int tiles)
+{
+    const long long Ns = (long long)c.T * c.S, ntiles = (Ns + 31) / 32;
+    const int blocks = (int)((ntiles + tiles - 1) / tiles);
+    int hist_stride = 0;
+    if (hist != nullptr) {
+        const DispatchGeom g = dispatch_geometry(Ns * c.k, c.E, tiles * 32 * c.k);
+        if (g.nchunks != blocks || !g.fused || route_mfma_hist_chunk(c) != g.chunk) return hipErrorInvalidValue;
+        hist_stride = g.stride;
+    }
+    auto kern = route_split_kernel<DS, ET>;
+    const hipError_t err = grant_dynamic_lds((const void *)kern, SplitTile<DS, ET>::lds);
+    if (err != hipSuccess) return err;
+    kern<<<blocks, kSplitThreads, SplitTile<DS, ET>::lds, s>>>((const bf16_t *)h, Ns, c.E, c.k, (const char *)packed, L.r_w1, L.r_w2, L.r_b1,
+                                                               L.r_b2, v.sigma > 0.f ? v.noise : nullptr, v.sigma,
+                                                               1.4426950408889634f * v.inv_tau, tiles, idx, p, (uint16_t *)hist, hist_stride);
+    return hipGetLastError();
 }
 
 template <int DS, int ET, int THREADS, bool W1_LDS = true>
@@ -371,6 +533,9 @@ static hipError_t run_route(const slicemoe_config &c, const void *h, const void 
     constexpr int KS = SliceTiles<DS>::KS;
     constexpr int kChunkTiles = THREADS / 64;
     if (route_threads(DS, ET) != THREADS) return hipErrorInvalidValue;
+    if constexpr (DS != 384) {
+        if (const int tiles = split_tiles(DS, ET, Ns)) return run_split<DS, ET>(c, L, h, packed, idx, p, s, v, hist, tiles);
+    }
     const long long blocks = route_blocks(Ns, kChunkTiles);
     const long long nchunks = ((Ns + 31) / 32 + kChunkTiles - 1) / kChunkTiles;
     int hist_rounds = 0, hist_stride = 0;
