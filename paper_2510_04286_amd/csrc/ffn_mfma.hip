@@ -28,7 +28,8 @@
 // roundings are replayed on the CPU in tests/test_gelu_poly.py).
 // Range: |x W1| beyond 65504 / kappa saturates the conversion, |z| beyond that overflows fp16.
 //
-// Three variants:
+// Four variants:
+//   split     small batches, any shape: a block is one 32-row unit and its wavefronts share the hidden tiles (see the kernel).
 //   pipelined a whole expert fits in LDS twice over (ds = 64, He <= 256: the benchmark shapes).  One block of
 //             eight wavefronts per CU holds the images of up to two experts; stacked rows are split evenly over
 //             the blocks regardless of expert boundaries; inside a wavefront the stages of consecutive hidden
@@ -792,6 +793,123 @@ __global__ __launch_bounds__(THREADS) void ffn_streamed_kernel(
     }
 }
 
+// ------------------------------------------------------------------------------ split
+// Small batches (a decoding step: a few units of 32 rows per expert).  What bounds them is the latency of a block that
+// brings an expert's 64 KiB and more into the LDS for one wavefront's serial walk over the hidden tiles.  Here the eight
+// wavefronts of a block share ONE unit of 32 rows, each with every eighth hidden tile, whose fragments go straight from
+// memory into its registers (nobody else in the block needs them, and they are requested before the row indices have
+// arrived), and the parts of y are added up in the LDS, in a fixed order.  SLOTS of them fit there; where that is half
+// of the wavefronts (width 192), the other half hands its parts over first.
+// Measured: see ffn_is_small.
+constexpr int kSplitWaves = 8;
+template <int DS> struct SplitFfn {
+    static constexpr int OT = SliceTiles<DS>::OT;
+    static constexpr int SLOTS = OT <= 4 ? kSplitWaves : kSplitWaves / 2;
+    static constexpr size_t lds = (size_t)SLOTS * OT * 4096;
+};
+template <int DS>
+__global__ __launch_bounds__(kSplitWaves * 64) void ffn_split_kernel(
+    const bf16_t *__restrict__ x, const float *__restrict__ pk, const int32_t *__restrict__ offsets,
+    const int32_t *__restrict__ perm, const char *__restrict__ experts, size_t e_stride, size_t off_w1, size_t off_w2,
+    size_t off_b1, size_t off_b2, int HT, int E, int k, EpiConst K, half_t *__restrict__ y)
+{
+    constexpr int KS = SliceTiles<DS>::KS, OT = SliceTiles<DS>::OT, SLOTS = SplitFfn<DS>::SLOTS;
+    extern __shared__ __align__(16) char lds[];
+    f32x4 *part = (f32x4 *)lds;   // [SLOTS][OT][4][64]
+    const int tid = threadIdx.x, lane = tid & 63, j = lane & 31, g = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+    // the unit of this block: units are counted from each expert's first row; lane e holds expert e (E <= 64)
+    const int off_lo = offsets[min(lane, E)], off_hi = offsets[min(lane + 1, E)];
+    const int units = (off_hi - off_lo + kResU - 1) / kResU, first = wavefront_exclusive_scan(units, lane);
+    const unsigned long long own = __ballot((int)blockIdx.x >= first && (int)blockIdx.x < first + units);
+    if (own == 0) return;   // the grid holds the most units there can be
+    const int e = __builtin_ctzll(own);
+    const int row0 = __builtin_amdgcn_readlane(off_lo, e) + kResU * ((int)blockIdx.x - __builtin_amdgcn_readlane(first, e));
+    const int row_end = __builtin_amdgcn_readlane(off_hi, e);
+    int row[1], a[1];
+    unit_rows<1>(row0, row_end, true, j, perm, row, a);
+
+    const char *ew = experts + (size_t)e * e_stride;
+    uint4 w1[KS], w2[2 * OT];
+    auto load_w1 = [&](int ht) {
+#pragma unroll
+        for (int i = 0; i < KS; ++i) w1[i] = ((const uint4 *)(ew + off_w1))[(ht * KS + i) * 64 + lane];
+    };
+    auto load_w2 = [&](int ht) {
+#pragma unroll
+        for (int i = 0; i < 2 * OT; ++i) w2[i] = ((const uint4 *)(ew + off_w2))[(ht * 2 * OT + i) * 64 + lane];
+    };
+    const int ht0 = min(wave, HT - 1);
+    load_w1(ht0);
+    load_w2(ht0);
+    RowUnit<DS, 1> cur;
+    float p[1];
+    load_rows<DS, 1>(cur, a, row, x, pk, k, g, p);
+    set_p<DS, 1>(cur, p);
+
+    f32x16 yacc[1][OT];
+    zero_acc<DS, 1>(yacc);
+    for (int ht = wave; ht < HT; ht += kSplitWaves) {
+        const int next = min(ht + kSplitWaves, HT - 1);
+        h2 bias[8];
+        load_bias_tile((const uint4 *)(ew + off_b1), ht, g, bias);
+        f32x16 acc;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) acc = mfma_bf16(__builtin_bit_cast(bf16x8, w1[ks]), cur.xb[0][ks], acc);
+        if (HT > kSplitWaves) load_w1(next);
+        uint4 hb[2];
+        activation_tile(acc, cur.p2[0], bias, K, hb);
+#pragma unroll
+        for (int i = 0; i < 2 * OT; ++i)   // i = s * OT + ot
+            yacc[0][i % OT] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, w2[i]), __builtin_bit_cast(f16x8, hb[i / OT]),
+                                                                     yacc[0][i % OT], 0, 0, 0);
+        if (HT > kSplitWaves) load_w2(next);
+    }
+
+    auto put = [&](int slot) {
+#pragma unroll
+        for (int ot = 0; ot < OT; ++ot)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const f32x16 &v = yacc[0][ot];
+                part[((slot * OT + ot) * 4 + q) * 64 + lane] = f32x4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
+            }
+    };
+    if constexpr (SLOTS < kSplitWaves) {
+        if (wave >= SLOTS) put(wave - SLOTS);
+        __syncthreads();
+        if (wave < SLOTS) {
+#pragma unroll
+            for (int ot = 0; ot < OT; ++ot)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const f32x4 v = part[((wave * OT + ot) * 4 + q) * 64 + lane];
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) yacc[0][ot][4 * q + c] += v[c];
+                }
+        }
+    }
+    if (wave < SLOTS) put(wave);   // (into the slot this wavefront has just read)
+    __syncthreads();
+    const float *b2 = (const float *)(ew + off_b2);   // padded with zeros by the packer
+    for (int i = wave; i < 2 * OT; i += kSplitWaves) {   // the halves of the output tiles are dealt out to the wavefronts
+        const int ot = i >> 1, qp = i & 1;
+        f32x4 s[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+        for (int w = 0; w < SLOTS; ++w)
+#pragma unroll
+            for (int t = 0; t < 2; ++t) s[t] += part[((w * OT + ot) * 4 + 2 * qp + t) * 64 + lane];
+        f32x16 acc;   // the eight values stand where the store looks for them
+#pragma unroll
+        for (int c = 0; c < 8; ++c) acc[c] = acc[8 + c] = s[c >> 2][c & 3];
+        if (qp == 0) store_row_pieces<DS, true>(row[0], acc, ot, 0, b2, y, g);
+        else store_row_pieces<DS, true>(row[0], acc, ot, 1, b2, y, g);
+    }
+}
+
 struct FfnPlan {
     bool resident;
     int hc;
@@ -890,6 +1008,35 @@ static hipError_t run_streamed(const slicemoe_config &c, const PackedLayout &L, 
     return hipGetLastError();
 }
 
+template <int DS>
+static hipError_t run_split(const slicemoe_config &c, const PackedLayout &L, const void *h, const float *p, const int32_t *offsets,
+                            const int32_t *perm, const char *experts, void *y, hipStream_t s)
+{
+    const long long Na = (long long)c.T * c.S * c.k;
+    const long long blocks = Na / kResU + c.E;   // sum over the experts of ceil(rows / 32) is no larger
+    auto kern = ffn_split_kernel<DS>;
+    const hipError_t err = grant_dynamic_lds((const void *)kern, SplitFfn<DS>::lds);
+    if (err != hipSuccess) return err;
+    kern<<<(int)blocks, kSplitWaves * 64, SplitFfn<DS>::lds, s>>>((const bf16_t *)h, p, offsets, perm, experts, L.e_stride, L.e_w1, L.e_w2,
+                                                                   L.e_b1, L.e_b2, c.He / 32, c.E, c.k, make_epi_const(), (half_t *)y);
+    return hipGetLastError();
+}
+
+// Whether the batch is for the split kernel: units (of 32 rows, two experts per slice) per CU up to which it was measured
+// to be the faster one.  Whole forward in us, other kernel / split (21.3 us is what four launches in a row take):
+//   width 24   0.1: 22.7 / 21.6   4: 23.0 / 21.6   6: 24.7 / 22.4   8: 25.5 / 25.3
+//         48   0.1: 24.8 / 21.9   2: 22.9 / 21.5   3: 23.8 / 22.6   4: 24.3 / 24.9
+//         64   0.1: 23.7 / 21.1   1: 22.2 / 21.3   1.5: 23.0 / 21.5   2: 23.2 / 23.9
+//         96   0.1: 37.9 / 21.6   1: 38.8 / 24.8   3: 41.6 / 37.1   4: 42.5 / 42.3   6: 40.5 / 53.2
+//         128  0.1: 48.9 / 24.1   1: 54.4 / 35.7   3: 59.5 / 52.6   4: 60.3 / 60.2   6: 67.5 / 81.4
+//         192  0.1: 51.4 / 34.4   0.5: 54.0 / 41.4   1: 58.6 / 62.4
+// Width 384 has no instantiation: its rows and accumulators take a SIMD's whole register file.
+static bool ffn_is_small(int ds, long long Na)
+{
+    const double units_per_cu = ds == 24 ? 6 : ds == 48 ? 3 : ds == 64 ? 1.5 : ds == 96 || ds == 128 ? 3 : ds == 192 ? 0.5 : 0;
+    return (double)Na <= units_per_cu * kResU * num_compute_units();
+}
+
 hipError_t launch_ffn_mfma(const slicemoe_config &c, const void *h, const float *p,
                            const int32_t *offsets, const int32_t *perm, const void *packed,
                            void *y, hipStream_t s)
@@ -899,6 +1046,14 @@ hipError_t launch_ffn_mfma(const slicemoe_config &c, const void *h, const float 
     const PackedLayout L = packed_layout(c);
     const FfnPlan pl = plan_ffn(L);
     const char *experts = (const char *)packed + L.experts;
+    if (ffn_is_small(L.ds, Na)) {
+        if (L.ds == 24) return run_split<24>(c, L, h, p, offsets, perm, experts, y, s);
+        if (L.ds == 48) return run_split<48>(c, L, h, p, offsets, perm, experts, y, s);
+        if (L.ds == 64) return run_split<64>(c, L, h, p, offsets, perm, experts, y, s);
+        if (L.ds == 96) return run_split<96>(c, L, h, p, offsets, perm, experts, y, s);
+        if (L.ds == 128) return run_split<128>(c, L, h, p, offsets, perm, experts, y, s);
+        return run_split<192>(c, L, h, p, offsets, perm, experts, y, s);
+    }
     if (pl.resident) {
         if (L.ds == 24) return run_resident<24, 3, 1024>(c, L, pl, h, p, offsets, perm, experts, y, s);
         if (L.ds == 48) return run_resident<48, 6, 1024>(c, L, pl, h, p, offsets, perm, experts, y, s);
