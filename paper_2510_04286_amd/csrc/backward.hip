@@ -13,6 +13,7 @@
 // varies from run to run; this way the result is reproducible bit for bit).
 #include <mutex>
 
+#include "bwd_mfma.h"
 #include "common.h"
 
 namespace slicemoe {
@@ -72,6 +73,14 @@ size_t backward_lds_bytes(const slicemoe_config &c)
     return expert > router ? expert : router;
 }
 
+// Blocks of the capacity sums: two assignments per thread and up, at most one block per CU of the chip.
+constexpr int kCapThreads = 1024;
+static int cap_blocks(long long Na)
+{
+    const long long want = (Na + 2 * kCapThreads - 1) / (2 * kCapThreads);
+    return (int)(want < 256 ? want : 256);
+}
+
 BackwardPlan backward_plan(const slicemoe_config &c)
 {
     BackwardPlan p;
@@ -86,7 +95,7 @@ BackwardPlan backward_plan(const slicemoe_config &c)
     p.router_part = at;  at = align_up(at + (size_t)p.router_slots * router_slot_floats((int)ds, c.Hr, c.E) * sizeof(float), 256);
     p.packed = at;  at = align_up(at + backward_mfma_packed_bytes(c), 256);
     p.router_scratch = at;  at = align_up(at + backward_router_mfma_scratch_bytes(c), 256);
-    p.cap = at;  at = align_up(at + (size_t)c.E * (sizeof(unsigned long long) + sizeof(float)), 256);
+    p.cap = at;  at = align_up(at + (size_t)c.E * (cap_blocks((long long)Na) * sizeof(unsigned long long) + sizeof(float)), 256);
     p.total = at + 256;
     return p;
 }
@@ -97,10 +106,13 @@ BackwardPlan backward_plan(const slicemoe_config &c)
 // alpha CV^2(c) with the population variance, and dL_cap/dp_a = alpha (2E / S^2) (c_e(a) - Q / S), S = sum c, Q = sum c^2.
 // The sums are exact and the same on every run: each probability, a float in [0, 1], is added as the integer
 // p * 2^38 (at most 2^22 * k assignments: no overflow in 64 bits; bits below 2^-38 of a tiny p are rounded off).
+// Bound by launches and latency (a few hundred KiB to read): every block stores its sums in a slot of its own, which the
+// one-block kernel behind it adds up, so nothing has to be cleared first; and only the router's kernels need the result,
+// so the two run behind the expert rows, beside the weight gradients (or their reduction) on the other stream.
 constexpr float kCapScale = 274877906944.f;   // 2^38
 
-__global__ __launch_bounds__(256) void bwd_cap_sums_kernel(const int32_t *__restrict__ idx, const float *__restrict__ pk,
-                                                           long long Na, int E, unsigned long long *__restrict__ sums)
+__global__ __launch_bounds__(kCapThreads) void bwd_cap_sums_kernel(const int32_t *__restrict__ idx, const float *__restrict__ pk,
+                                                           long long Na, int E, unsigned long long *__restrict__ slots /* [gridDim.x][E] */)
 {
     extern __shared__ unsigned long long cap_s[];
     for (int e = threadIdx.x; e < E; e += blockDim.x) cap_s[e] = 0ull;
@@ -112,14 +124,19 @@ __global__ __launch_bounds__(256) void bwd_cap_sums_kernel(const int32_t *__rest
         atomicAdd(&cap_s[e], (unsigned long long)__float2ll_rn(p * kCapScale));
     }
     __syncthreads();
-    for (int e = threadIdx.x; e < E; e += blockDim.x)
-        if (cap_s[e] != 0ull) atomicAdd(&sums[e], cap_s[e]);
+    for (int e = threadIdx.x; e < E; e += blockDim.x) slots[(size_t)blockIdx.x * E + e] = cap_s[e];
 }
 
-// One block.  Every thread adds up all E sums in the same order, then writes its experts' derivatives.
-__global__ __launch_bounds__(256) void bwd_cap_coeff_kernel(const unsigned long long *__restrict__ sums, int E, float alpha,
-                                                            float *__restrict__ capg)
+// One block.  The slots' integers are added in the LDS, then every thread adds up all E sums in the same order and writes
+// its experts' derivatives.
+__global__ __launch_bounds__(kCapThreads) void bwd_cap_coeff_kernel(const unsigned long long *__restrict__ slots, int nslots, int E,
+                                                                    float alpha, float *__restrict__ capg)
 {
+    extern __shared__ unsigned long long sums[];
+    for (int e = threadIdx.x; e < E; e += blockDim.x) sums[e] = 0ull;
+    __syncthreads();
+    for (int i = threadIdx.x; i < nslots * E; i += blockDim.x) atomicAdd(&sums[i % E], slots[i]);
+    __syncthreads();
     double S = 0.0, Q = 0.0;
     for (int e = 0; e < E; ++e) {
         const double c = (double)sums[e] / (double)kCapScale;
@@ -202,20 +219,16 @@ static hipError_t run_backward(const slicemoe_config &c, const void *h, const sl
     char *ws = (char *)workspace;
     RouteVariant v = v_in;
     v.capg = nullptr;
-    if (v.cap_alpha != 0.f) {
-        unsigned long long *sums = (unsigned long long *)(ws + P.cap);
-        float *capg = (float *)(sums + c.E);
-        if ((e = zero_fill((float *)sums, 2 * (size_t)c.E, s)) != hipSuccess) return e;
-        long long blocks = (Na + 256 * 16 - 1) / (256 * 16);
-        if (blocks > 1024) blocks = 1024;
-        bwd_cap_sums_kernel<<<(unsigned)blocks, 256, (size_t)c.E * sizeof(unsigned long long), s>>>(idx, pk, Na, c.E, sums);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        bwd_cap_coeff_kernel<<<1, 256, 0, s>>>(sums, c.E, v.cap_alpha, capg);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        v.capg = capg;
-    }
     float *dxrow = (float *)(ws + P.dxrow), *dpk = (float *)(ws + P.dpk);
     float *epart = (float *)(ws + P.expert_part), *rpart = (float *)(ws + P.router_part);
+
+    // Both parts' repacked weights in one launch: a second one is 5-7 us of an otherwise idle stream (or waits for a free
+    // CU beside the weight gradients), whatever it moves.
+    BwdPackJobs jobs;
+    jobs.count = 0;
+    if (backward_mfma_shape(c)) backward_expert_pack_jobs(c, w, ws + P.packed, jobs);
+    if (backward_router_mfma_shape(c)) backward_router_pack_jobs(c, w, ws + P.router_scratch, jobs);
+    if ((e = bwd_pack_launch(jobs, s)) != hipSuccess) return e;
 
     const size_t eslot = expert_slot_floats(ds, c.He);
     std::unique_lock<std::mutex> side_lock(g_side_mutex, std::defer_lock);
@@ -223,12 +236,12 @@ static hipError_t run_backward(const slicemoe_config &c, const void *h, const sl
     SideJoin joiner;
     hipStream_t se = s;   // stream of the expert weight gradients and their reduction
     if (backward_mfma_shape(c) && (c.flags & SLICEMOE_FLAG_SINGLE_STREAM)) {
-        e = launch_backward_expert_mfma(c, h, w, d_out, pk, offsets, perm, ws + P.packed, eslot, dxrow, dpk, epart, s);
+        e = launch_backward_expert_mfma(c, h, d_out, pk, offsets, perm, ws + P.packed, eslot, dxrow, dpk, epart, s);
         if (e != hipSuccess) return e;
     } else if (backward_mfma_shape(c)) {
         side_lock.lock();
         if ((e = side_stream(&side)) != hipSuccess) return e;
-        e = launch_backward_expert_mfma(c, h, w, d_out, pk, offsets, perm, ws + P.packed, eslot, dxrow, dpk, epart, s, &side);
+        e = launch_backward_expert_mfma(c, h, d_out, pk, offsets, perm, ws + P.packed, eslot, dxrow, dpk, epart, s, &side);
         joiner.side = &side;   // from here on the side stream holds work of this call: joined on every way out
         joiner.s = s;
         se = side.stream;
@@ -239,9 +252,21 @@ static hipError_t run_backward(const slicemoe_config &c, const void *h, const sl
     }
     if ((e = launch_backward_reduce_segments(c, offsets, epart, eslot, g, se)) != hipSuccess) return e;
 
+    if (v.cap_alpha != 0.f) {
+        const int blocks = cap_blocks(Na);
+        const size_t lds = (size_t)c.E * sizeof(unsigned long long);
+        unsigned long long *slots = (unsigned long long *)(ws + P.cap);
+        float *capg = (float *)(slots + (size_t)blocks * c.E);
+        bwd_cap_sums_kernel<<<blocks, kCapThreads, lds, s>>>(idx, pk, Na, c.E, slots);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        bwd_cap_coeff_kernel<<<1, kCapThreads, lds, s>>>(slots, blocks, c.E, v.cap_alpha, capg);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        v.capg = capg;
+    }
+
     const size_t rslot = router_slot_floats(ds, c.Hr, c.E);
     if (backward_router_mfma_shape(c)) {
-        e = launch_backward_router_mfma(c, h, w, v, drop_u, rate, idx, inv, dpk, dxrow, d_h, ws + P.router_scratch,
+        e = launch_backward_router_mfma(c, h, v, drop_u, rate, idx, inv, dpk, dxrow, d_h, ws + P.router_scratch,
                                         rslot, rpart, s);
         if (e != hipSuccess) return e;
     } else {

@@ -338,33 +338,40 @@ static hipError_t run_rows_mfma(const slicemoe_config &c, const BwdPacked &L, co
     return hipGetLastError();
 }
 
-// Packs the backward copies of the expert weights into `packed` (backward_mfma_packed_bytes), then runs the kernels.
+void backward_expert_pack_jobs(const slicemoe_config &c, const slicemoe_weights &w, void *packed, BwdPackJobs &jobs)
+{
+    const int He = c.He, E = c.E, ds = c.d / c.S, dsK = (ds + 15) / 16 * 16, dsN = (ds + 31) / 32 * 32;
+    const BwdPacked L = bwd_packed_layout(c);
+    char *pb = (char *)packed;
+    const size_t wstride = (size_t)ds * He;
+    BwdPackJob *J = jobs.job + jobs.count;
+    jobs.count += 4;
+    // w1f: the [ds, He] matrix W1 itself; w2r: the [ds, He] matrix M[c][hidden] = W2[hidden][c]
+    J[0] = bwd_pack_job(kPackLayer1, w.W1, dsK, ds, He, He, (size_t)He, 1, wstride, pb + L.w1f, L.stride, E);
+    J[1] = bwd_pack_job(kPackLayer1, w.W2, dsK, ds, He, He, 1, (size_t)ds, wstride, pb + L.w2r, L.stride, E);
+    // w1d: W1 in 16-feature tiles.  w1c: the [He, ds] matrix M[hidden][c] = W1[c][hidden], contraction over the hidden units
+    // in accumulator order
+    if (backward_weights_plan(c).fused)
+        J[2] = bwd_pack_job(kPackTile16, w.W1, dsK, ds, He, He, (size_t)He, 1, wstride, pb + L.w1d, L.stride, E);
+    else J[2] = bwd_pack_job(kPackChain, w.W1, He, He, dsN, ds, 1, (size_t)He, wstride, pb + L.w1c, L.stride, E);
+    J[3] = bwd_pack_job(kPackBias, w.b1, He, He, He, He, 0, 0, (size_t)He, pb + L.b1, L.stride, E);
+}
+
+// Runs the kernels on the backward copies of the expert weights in `packed` (backward_expert_pack_jobs, launched on s before).
 // part holds backward_weights_plan(c).slots slots of slot_floats floats.  When the weight gradients come from a kernel of
 // their own it runs on the side stream, from the moment the repacked weights are there; otherwise that stream only waits
 // for the fused kernel (for the reduction that the caller puts on it).
-hipError_t launch_backward_expert_mfma(const slicemoe_config &c, const void *h, const slicemoe_weights &w, const void *d_out,
+hipError_t launch_backward_expert_mfma(const slicemoe_config &c, const void *h, const void *d_out,
                                        const float *pk, const int32_t *offsets, const int32_t *perm, void *packed,
                                        size_t slot_floats, float *dxrow, float *dpk, float *part, hipStream_t s,
                                        const SideStream *side)
 {
     if (!backward_mfma_shape(c)) return hipErrorInvalidValue;
-    const int He = c.He, E = c.E, ds = c.d / c.S, dsK = (ds + 15) / 16 * 16, dsN = (ds + 31) / 32 * 32;
+    const int ds = c.d / c.S;
     const BackwardWeightsPlan W = backward_weights_plan(c);
     const BwdPacked L = bwd_packed_layout(c);
-    char *pb = (char *)packed;
-    const size_t wstride = (size_t)ds * He;
-    BwdPackJobs jobs;
-    jobs.count = 4;
-    // w1f: the [ds, He] matrix W1 itself; w2r: the [ds, He] matrix M[c][hidden] = W2[hidden][c]
-    jobs.job[0] = bwd_pack_job(kPackLayer1, w.W1, dsK, ds, He, He, (size_t)He, 1, wstride, pb + L.w1f, L.stride, E);
-    jobs.job[1] = bwd_pack_job(kPackLayer1, w.W2, dsK, ds, He, He, 1, (size_t)ds, wstride, pb + L.w2r, L.stride, E);
-    // w1d: W1 in 16-feature tiles.  w1c: the [He, ds] matrix M[hidden][c] = W1[c][hidden], contraction over the hidden units
-    // in accumulator order
-    if (W.fused) jobs.job[2] = bwd_pack_job(kPackTile16, w.W1, dsK, ds, He, He, (size_t)He, 1, wstride, pb + L.w1d, L.stride, E);
-    else jobs.job[2] = bwd_pack_job(kPackChain, w.W1, He, He, dsN, ds, 1, (size_t)He, wstride, pb + L.w1c, L.stride, E);
-    jobs.job[3] = bwd_pack_job(kPackBias, w.b1, He, He, He, He, 0, 0, (size_t)He, pb + L.b1, L.stride, E);
-    hipError_t e = bwd_pack_launch(jobs, s);
-    if (e != hipSuccess) return e;
+    const char *pb = (const char *)packed;
+    hipError_t e;
     auto fork = [&]() -> hipError_t {
         if (side == nullptr) return hipSuccess;
         const hipError_t f = hipEventRecord(side->fork, s);

@@ -662,36 +662,41 @@ static hipError_t run_router_mfma(const slicemoe_config &c, const RouterBwdPacke
     return hipGetLastError();
 }
 
-// scratch: backward_router_mfma_scratch_bytes; part: backward_router_mfma_slots slots of slot_floats floats.  dxrow, dpk:
-// the expert stage's row gradients and dL/dp.
-hipError_t launch_backward_router_mfma(const slicemoe_config &c, const void *h, const slicemoe_weights &w,
+void backward_router_pack_jobs(const slicemoe_config &c, const slicemoe_weights &w, void *scratch, BwdPackJobs &jobs)
+{
+    const int E = c.E, Hr = kRbHr, ds = c.d / c.S, ET = (E + 31) / 32, EP = 32 * ET;
+    const int dsK = (ds + 15) / 16 * 16, dsN = (ds + 31) / 32 * 32;
+    const RouterBwdPacked L = router_bwd_layout(ds, ET);
+    char *pb = (char *)scratch;
+    const bf16_t *Wr1 = (const bf16_t *)w.Wr1, *Wr2 = (const bf16_t *)w.Wr2;
+    BwdPackJob *J = jobs.job + jobs.count;
+    jobs.count += 7;
+    // w1f: Wr1 [ds, Hr] itself.  w2f: Wr2 [Hr, E] with the hidden units as contraction slots, fp16, experts padded to EP.
+    J[0] = bwd_pack_job(kPackLayer1, Wr1, dsK, ds, Hr, Hr, (size_t)Hr, 1, 0, pb + L.w1f, 0, 1);
+    J[1] = bwd_pack_job(kPackChainF16, Wr2, Hr, Hr, EP, E, (size_t)E, 1, 0, pb + L.w2f, 0, 1);
+    // w2c: M[e][h] = Wr2[h][e] ([EP, Hr], experts as contraction slots).  w1c: M[h][c] = Wr1[c][h] ([Hr, ds]).
+    J[2] = bwd_pack_job(kPackChain, Wr2, EP, E, Hr, Hr, 1, (size_t)E, 0, pb + L.w2c, 0, 1);
+    J[3] = bwd_pack_job(kPackChain, Wr1, Hr, Hr, dsN, ds, 1, (size_t)Hr, 0, pb + L.w1c, 0, 1);
+    // w2r: M[e][h] = Wr2[h][e] ([EP, Hr]) in plain K-steps of 16 experts
+    J[4] = bwd_pack_job(kPackLayer1, Wr2, EP, E, Hr, Hr, 1, (size_t)E, 0, pb + L.w2r, 0, 1);
+    J[5] = bwd_pack_job(kPackBias, w.br1, Hr, Hr, Hr, Hr, 0, 0, 0, pb + L.b1, 0, 1);
+    J[6] = bwd_pack_job(kPackBias, w.br2, E, E, EP, EP, 0, 0, 0, pb + L.b2, 0, 1);
+}
+
+// scratch: backward_router_mfma_scratch_bytes, holding the repacked weights (backward_router_pack_jobs); part:
+// backward_router_mfma_slots slots of slot_floats floats.  dxrow, dpk: the expert stage's row gradients and dL/dp.
+hipError_t launch_backward_router_mfma(const slicemoe_config &c, const void *h,
                                        const RouteVariant &v, const float *drop_u, float rate, const int32_t *idx,
                                        const int32_t *inv, const float *dpk, const float *dxrow, void *d_h, void *scratch,
                                        size_t slot_floats, float *part, hipStream_t s)
 {
     if (!backward_router_mfma_shape(c)) return hipErrorInvalidValue;
-    const int E = c.E, Hr = kRbHr, ds = c.d / c.S, ET = (E + 31) / 32, EP = 32 * ET;
-    const int dsK = (ds + 15) / 16 * 16, dsN = (ds + 31) / 32 * 32;
+    const int ds = c.d / c.S, ET = (c.E + 31) / 32;
     const RouterBwdPacked L = router_bwd_layout(ds, ET);
     const RouterBwdScratch R = router_bwd_scratch(c);
     char *pb = (char *)scratch;
     bf16_t *dg = (bf16_t *)(pb + R.dg);
     uint32_t *bits = (uint32_t *)(pb + R.bits);
-    const bf16_t *Wr1 = (const bf16_t *)w.Wr1, *Wr2 = (const bf16_t *)w.Wr2;
-    BwdPackJobs jobs;
-    jobs.count = 7;
-    // w1f: Wr1 [ds, Hr] itself.  w2f: Wr2 [Hr, E] with the hidden units as contraction slots, fp16, experts padded to EP.
-    jobs.job[0] = bwd_pack_job(kPackLayer1, Wr1, dsK, ds, Hr, Hr, (size_t)Hr, 1, 0, pb + L.w1f, 0, 1);
-    jobs.job[1] = bwd_pack_job(kPackChainF16, Wr2, Hr, Hr, EP, E, (size_t)E, 1, 0, pb + L.w2f, 0, 1);
-    // w2c: M[e][h] = Wr2[h][e] ([EP, Hr], experts as contraction slots).  w1c: M[h][c] = Wr1[c][h] ([Hr, ds]).
-    jobs.job[2] = bwd_pack_job(kPackChain, Wr2, EP, E, Hr, Hr, 1, (size_t)E, 0, pb + L.w2c, 0, 1);
-    jobs.job[3] = bwd_pack_job(kPackChain, Wr1, Hr, Hr, dsN, ds, 1, (size_t)Hr, 0, pb + L.w1c, 0, 1);
-    // w2r: M[e][h] = Wr2[h][e] ([EP, Hr]) in plain K-steps of 16 experts
-    jobs.job[4] = bwd_pack_job(kPackLayer1, Wr2, EP, E, Hr, Hr, 1, (size_t)E, 0, pb + L.w2r, 0, 1);
-    jobs.job[5] = bwd_pack_job(kPackBias, w.br1, Hr, Hr, Hr, Hr, 0, 0, 0, pb + L.b1, 0, 1);
-    jobs.job[6] = bwd_pack_job(kPackBias, w.br2, E, E, EP, EP, 0, 0, 0, pb + L.b2, 0, 1);
-    const hipError_t e = bwd_pack_launch(jobs, s);
-    if (e != hipSuccess) return e;
 #define SLICEMOE_ROUTER_BWD(DSV)                                                                                                   \
     if (ds == DSV)                                                                                                                 \
         return ET == 1 ? run_router_mfma<DSV, 1>(c, L, h, v, drop_u, rate, idx, inv, dpk, dxrow, d_h, pb, dg, bits, slot_floats, part, s) \

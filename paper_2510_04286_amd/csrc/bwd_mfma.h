@@ -46,11 +46,14 @@ struct BwdPackJob {
 };
 struct BwdPackJobs {
     int count;
-    BwdPackJob job[8];
+    BwdPackJob job[12];
 };
 BwdPackJob bwd_pack_job(int kind, const void *src, int K, int Kv, int N, int Nv, size_t rs, size_t cs, size_t src_stride,
                         char *dst, size_t dst_stride, int nmat);
 hipError_t bwd_pack_launch(const BwdPackJobs &jobs, hipStream_t s);
+// Append what the expert part and the router part need (four and seven jobs); `packed` and `scratch` are their regions.
+void backward_expert_pack_jobs(const slicemoe_config &c, const slicemoe_weights &w, void *packed, BwdPackJobs &jobs);
+void backward_router_pack_jobs(const slicemoe_config &c, const slicemoe_weights &w, void *scratch, BwdPackJobs &jobs);
 
 // Backward copies of one expert's weights in fragment order (bytes from the start of the expert's block).
 //   w1f  [HT][KS][64]      W1 fragments as the forward packs them: lane (i, g), slot m: W1[16ks + 8g + m][32ht + i]

@@ -142,7 +142,7 @@ size_t backward_mfma_packed_bytes(const slicemoe_config &c);
 // the dL/dg tables), and the launch (dL/dh and backward_router_mfma_slots slots of partial weight gradients).
 bool backward_router_mfma_shape(const slicemoe_config &c);
 size_t backward_router_mfma_scratch_bytes(const slicemoe_config &c);
-hipError_t launch_backward_router_mfma(const slicemoe_config &c, const void *h, const slicemoe_weights &w,
+hipError_t launch_backward_router_mfma(const slicemoe_config &c, const void *h,
                                        const RouteVariant &v, const float *drop_u, float rate, const int32_t *idx,
                                        const int32_t *inv, const float *dpk, const float *dxrow, void *d_h, void *scratch,
                                        size_t slot_floats, float *part, hipStream_t s);
@@ -153,7 +153,7 @@ struct SideStream {
     hipStream_t stream;
     hipEvent_t fork, join;
 };
-hipError_t launch_backward_expert_mfma(const slicemoe_config &c, const void *h, const slicemoe_weights &w, const void *d_out,
+hipError_t launch_backward_expert_mfma(const slicemoe_config &c, const void *h, const void *d_out,
                                        const float *pk, const int32_t *offsets, const int32_t *perm, void *packed,
                                        size_t slot_floats, float *dxrow, float *dpk, float *part, hipStream_t s,
                                        const SideStream *side = nullptr);
