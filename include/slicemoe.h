@@ -305,8 +305,8 @@ slicemoe_status slicemoe_forward_train(const slicemoe_config *cfg, const void *h
  * For bf16 storage with d/S in {24, 48, 64, 96, 128, 192} and He % 32 == 0 (slicemoe_backward_uses_mfma: 1, 0, or -1
  * for an invalid config) the expert part (row gradients, dL/dp, expert weight gradients) runs on the matrix cores, and
  * with Hr = 256 the router part too: fp32 pre-activations and derivatives, two-term bf16 operands
- * (three-term at 24, 48 and 192) for the second matrix instructions, fp32-grade results.  Everything else runs on vector-ALU kernels in fp32.
- * SLICEMOE_FLAG_FORCE_GENERIC selects those throughout.  UNSUPPORTED for Hr > 256.
+ * (three-term at 24, 48 and 192) for the second matrix instructions, fp32-grade results.  Everything else runs in fp32 throughout.
+ * SLICEMOE_FLAG_FORCE_GENERIC selects that throughout.  UNSUPPORTED for Hr > 256.
  */
 typedef struct {
     float *Wr1, *br1, *Wr2, *br2, *W1, *b1, *W2, *b2;

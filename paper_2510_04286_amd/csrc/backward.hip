@@ -1,4 +1,4 @@
-// Backward pass of the layer (vector-ALU, fp32 arithmetic): gradients of a loss that depends on h and on the
+// Backward pass of the layer: gradients of a loss that depends on h and on the
 // weights only through h', by the chain rule through the k-sum, the expert FFN and the Eq. 1 input weighting
 // (Section 3.1), and the router (Section 3.1; temperature of Appendix B, logit noise of Section 5 and cross-slice
 // dropout of Section 3.3 as in the forward).  The routing decisions -- selected experts, capacity drops, dropout

@@ -1,5 +1,5 @@
 // Matrix-core backward of the router and assembly of dL/dh, for the forward's matrix-core slice widths except 384,
-// Hr = 256 and up to 64 experts.  Same mathematics as bwd_router_kernel in backward.hip; three kernels:
+// Hr = 256 and up to 64 experts.  Same mathematics as bwd_router_generic_kernel in backward_generic.hip; three kernels:
 //
 //   bwd_route_logits_mfma_kernel   the forward router's layout: a lane owns one slice of a 32-slice tile.  Recomputes the
 //       router exactly as the forward does (hidden layer on bf16 MFMA with the bias preloaded, ReLU, two-term fp16 split,
