@@ -303,8 +303,8 @@ def main():
         # gradients) plus the router's three passes forward-size each way
         bflops = 10 * ds * He * n_kept_rows(B, cfg, ws) + 6 * Ns * (ds * Hr + Hr * E)
         backward = {"ms": round(bms, 4), "calls": nb, "flops": bflops, "tflops": round(bflops / (bms * 1e-3) / 1e12, 2),
-                    "expert_kernels": "matrix-core" if B.slicemoe_backward_uses_mfma(cfg) == 1 else "vector-ALU fp32",
-                    "router_kernels": "matrix-core" if B.slicemoe_backward_uses_mfma(cfg) == 1 and shape.Hr == 256 and shape.E <= 64 else "vector-ALU fp32"}
+                    "expert_kernels": "matrix-core" if B.slicemoe_backward_uses_mfma(cfg) == 1 else "matrix-core fp32",
+                    "router_kernels": "matrix-core" if B.slicemoe_backward_uses_mfma(cfg) == 1 and shape.Hr == 256 and shape.E <= 64 else "matrix-core fp32"}
 
     cpu = parity = None
     if not args.no_cpu_baseline:
