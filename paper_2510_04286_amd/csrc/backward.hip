@@ -151,7 +151,7 @@ __global__ __launch_bounds__(kCapThreads) void bwd_cap_coeff_kernel(const unsign
 
 // ---- A stream of the library's own, beside the caller's.  The expert weight gradients (their kernel and the
 // reduction after it) depend on nothing that the rest of the backward produces, and nothing but the caller depends on
-// them, so they run on this stream while the row gradients and the router's kernels run on the caller's: the two
+// them, so they run on this stream (where they are a kernel of their own) while the row gradients and the router's kernels run on the caller's: the two
 // chains fill each other's launch gaps and tails.  One stream and two events per device, made at the first backward on
 // that device and kept until the process ends; default priority, no implicit synchronisation with the null stream.
 // The events are shared by all calls on a device, so the enqueueing of one call (fork .. join) holds a lock.
@@ -235,7 +235,10 @@ static hipError_t run_backward(const slicemoe_config &c, const void *h, const sl
     SideStream side = {};
     SideJoin joiner;
     hipStream_t se = s;   // stream of the expert weight gradients and their reduction
-    if (backward_mfma_shape(c) && (c.flags & SLICEMOE_FLAG_SINGLE_STREAM)) {
+    // Where one kernel gives dL/dx and the weight gradients only their reduction could run beside the router's kernels,
+    // and it takes more from the first of them than it hides (d=1024 S=16 E=32 T=16384: 13 us + 45 us in turn, 67 us
+    // together, and 6 us for the fork; the whole backward 469 us on one stream, 482 us on two).
+    if (backward_mfma_shape(c) && ((c.flags & SLICEMOE_FLAG_SINGLE_STREAM) || backward_weights_plan(c).fused)) {
         e = launch_backward_expert_mfma(c, h, d_out, pk, offsets, perm, ws + P.packed, eslot, dxrow, dpk, epart, s);
         if (e != hipSuccess) return e;
     } else if (backward_mfma_shape(c)) {

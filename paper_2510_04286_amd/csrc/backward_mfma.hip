@@ -359,8 +359,7 @@ void backward_expert_pack_jobs(const slicemoe_config &c, const slicemoe_weights 
 
 // Runs the kernels on the backward copies of the expert weights in `packed` (backward_expert_pack_jobs, launched on s before).
 // part holds backward_weights_plan(c).slots slots of slot_floats floats.  When the weight gradients come from a kernel of
-// their own it runs on the side stream, from the moment the repacked weights are there; otherwise that stream only waits
-// for the fused kernel (for the reduction that the caller puts on it).
+// their own it runs on the side stream (if there is one), from the moment the repacked weights are there.
 hipError_t launch_backward_expert_mfma(const slicemoe_config &c, const void *h, const void *d_out,
                                        const float *pk, const int32_t *offsets, const int32_t *perm, void *packed,
                                        size_t slot_floats, float *dxrow, float *dpk, float *part, hipStream_t s,
@@ -372,13 +371,11 @@ hipError_t launch_backward_expert_mfma(const slicemoe_config &c, const void *h, 
     const BwdPacked L = bwd_packed_layout(c);
     const char *pb = (const char *)packed;
     hipError_t e;
-    auto fork = [&]() -> hipError_t {
-        if (side == nullptr) return hipSuccess;
-        const hipError_t f = hipEventRecord(side->fork, s);
-        return f == hipSuccess ? hipStreamWaitEvent(side->stream, side->fork, 0) : f;
-    };
     if (!W.fused) {
-        if ((e = fork()) != hipSuccess) return e;
+        if (side != nullptr) {
+            if ((e = hipEventRecord(side->fork, s)) != hipSuccess) return e;
+            if ((e = hipStreamWaitEvent(side->stream, side->fork, 0)) != hipSuccess) return e;
+        }
         e = ds == 24 ? run_rows_mfma<24>(c, L, h, d_out, pk, offsets, perm, pb, dxrow, dpk, s)
           : ds == 48 ? run_rows_mfma<48>(c, L, h, d_out, pk, offsets, perm, pb, dxrow, dpk, s)
           : ds == 64 ? run_rows_mfma<64>(c, L, h, d_out, pk, offsets, perm, pb, dxrow, dpk, s)
@@ -387,9 +384,8 @@ hipError_t launch_backward_expert_mfma(const slicemoe_config &c, const void *h, 
                       : run_rows_mfma<192>(c, L, h, d_out, pk, offsets, perm, pb, dxrow, dpk, s);
         if (e != hipSuccess) return e;
     }
-    e = launch_backward_weights(c, L, h, d_out, pk, offsets, perm, pb, slot_floats, part, dxrow, dpk,
-                                !W.fused && side != nullptr ? side->stream : s);
-    return e == hipSuccess && W.fused ? fork() : e;
+    return launch_backward_weights(c, L, h, d_out, pk, offsets, perm, pb, slot_floats, part, dxrow, dpk,
+                                   !W.fused && side != nullptr ? side->stream : s);
 }
 
 }  // namespace slicemoe
