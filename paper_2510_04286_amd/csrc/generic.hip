@@ -1,6 +1,7 @@
 // Generic router and expert kernels, fp32 arithmetic.  They take any shape within the library limits and either storage
 // type, and serve the fp32 configuration and every shape the bf16 matrix-core kernels do not cover.
 #include "mfma.h"
+#include "output_role.h"
 #include "wavefront.h"
 
 namespace slicemoe {
@@ -156,8 +157,9 @@ __global__ __launch_bounds__(kF32Threads) void ffn_generic_kernel(
     }
     __syncthreads();
 
-    const int OT = (ds + 31) / 32, parts = OT >= kF32Waves ? 1 : kF32Waves / OT;
-    const int part = OT >= kF32Waves ? 0 : wave / OT, ot0 = OT >= kF32Waves ? wave : wave % OT;
+    const int OT = (ds + 31) / 32;
+    const OutputRole role = output_role(OT, kF32Waves, wave);
+    const int parts = role.parts;
     f32x16 yacc[NO];
 #pragma unroll
     for (int o = 0; o < NO; ++o)
@@ -194,12 +196,12 @@ __global__ __launch_bounds__(kF32Threads) void ffn_generic_kernel(
         for (int i = 0; i < 16; ++i)
             hs[acc_feature(i, g) * HST + wave * 32 + jj] = hid < He ? 0.5f * z[i] * (1.f + erff(z[i] * 0.70710678118654752f)) : 0.f;
         __syncthreads();
-        if (part < parts) {
-            const int per = (kF32Hidden / parts + 1) & ~1, k0 = part * per, k1 = min(min(k0 + per, kF32Hidden), (He - h0 + 1) & ~1);
+        if (role.part < parts) {
+            const int per = (kF32Hidden / parts + 1) & ~1, k0 = role.part * per, k1 = min(min(k0 + per, kF32Hidden), (He - h0 + 1) & ~1);
 #pragma unroll
             for (int o = 0; o < NO; ++o) {
-                const int f = 32 * (ot0 + kF32Waves * o) + jj, fc = min(f, ds - 1);
-                if (32 * (ot0 + kF32Waves * o) < ds) {
+                const int f = 32 * (role.tile + kF32Waves * o) + jj, fc = min(f, ds - 1);
+                if (role.has_tile(o)) {
                     for (int kb = k0; kb < k1; kb += 2 * kF32Batch) {
                         float b[kF32Batch];
 #pragma unroll
@@ -216,8 +218,8 @@ __global__ __launch_bounds__(kF32Threads) void ffn_generic_kernel(
     if (parts == 1) {   // lane = feature, registers = rows
 #pragma unroll
         for (int o = 0; o < NO; ++o) {
-            const int f = 32 * (ot0 + kF32Waves * o) + jj;
-            if (f < ds) {
+            const int f = 32 * (role.tile + kF32Waves * o) + jj;
+            if (role.has_tile(o) && f < ds) {   // a wavefront without a tile has sums of nothing
                 const float bias = Storage<T>::load(b2 + (size_t)e * ds + f);
 #pragma unroll
                 for (int i = 0; i < 16; ++i)
@@ -227,7 +229,7 @@ __global__ __launch_bounds__(kF32Threads) void ffn_generic_kernel(
         return;
     }
     __syncthreads();
-    if (part < parts)
+    if (role.part < parts)
 #pragma unroll
         for (int i = 0; i < 16; ++i) hs[(wave * kF32Rows + acc_feature(i, g)) * 33 + jj] = yacc[0][i];
     __syncthreads();

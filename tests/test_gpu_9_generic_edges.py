@@ -30,6 +30,11 @@ CASES = {
     "ds65_two_groups": shape(65, 300, 9, 2, 37, 256),
     "ds128": shape(128, 33, 4, 2, 50, 64),
     "ds132_k8": shape(132, 40, 33, 8, 21, 64),
+    # five to seven output tiles on eight wavefronts: some have none.  A hidden width of a few units makes the product short
+    "ds160_five_tiles": shape(160, 2, 3, 2, 41, 64),
+    "ds192_six_tiles": shape(192, 4, 3, 2, 41, 64),
+    "ds224_seven_tiles": shape(224, 2, 3, 2, 41, 64),
+    "bf16_ds192_six_tiles": shape(192, 8, 4, 2, 70, 64, "bf16"),
     "ds257_wide": shape(257, 270, 3, 2, 21, 130, S=2),
     "hot": shape(48, 72, 4, 1, 900, 128),
     "capacity": shape(64, 128, 8, 2, 200, 256, cf=0.6),
