@@ -302,8 +302,8 @@ slicemoe_status slicemoe_forward_train(const slicemoe_config *cfg, const void *h
  *                        events, which a HIP graph capture of `stream` takes along (after one eager call has created
  *                        the stream).  Calls from several host threads on one device are enqueued one after the other.
  *                        SLICEMOE_FLAG_SINGLE_STREAM keeps every kernel on `stream` (same results, a few percent slower).
- * For bf16 storage with d/S in {24, 48, 64, 96, 128, 192} and He % 32 == 0 (slicemoe_backward_uses_mfma: 1, 0, or -1
- * for an invalid config) the expert part (row gradients, dL/dp, expert weight gradients) runs on the matrix cores, and
+ * For bf16 storage with d/S in {24, 48, 64, 96, 128, 192}, He % 32 == 0 and He up to what the LDS holds of an expert's
+ * biases (about 30 000; slicemoe_backward_uses_mfma: 1, 0, or -1 for an invalid config) the expert part (row gradients, dL/dp, expert weight gradients) runs on the matrix cores, and
  * with Hr = 256 the router part too: fp32 pre-activations and derivatives, two-term bf16 operands
  * (three-term at 24, 48 and 192) for the second matrix instructions, fp32-grade results.  Everything else runs in fp32 throughout.
  * SLICEMOE_FLAG_FORCE_GENERIC selects that throughout.  UNSUPPORTED for Hr > 256.

@@ -291,18 +291,6 @@ __global__ __launch_bounds__(kBmTileWaves<DS> * 64) void bwd_rows_streamed_mfma_
 }
 
 // ------------------------------------------------------------------------------------------------------ host
-bool backward_mfma_shape(const slicemoe_config &c)
-{
-    const int ds = c.d / c.S;
-    return c.dtype == SLICEMOE_BF16 && (ds == 24 || ds == 48 || ds == 64 || ds == 96 || ds == 128 || ds == 192) && c.He % 32 == 0 &&
-           !(c.flags & SLICEMOE_FLAG_FORCE_GENERIC);
-}
-
-size_t backward_mfma_packed_bytes(const slicemoe_config &c)
-{
-    return backward_mfma_shape(c) ? bwd_packed_layout(c).stride * (size_t)c.E : 0;
-}
-
 // Hidden tiles per chunk of the streamed rows kernel: the largest divisor of HT whose fragments fit, and its LDS bytes.
 static int streamed_chunk(int KS, int OT, int He, int E, size_t *lds)
 {
@@ -318,6 +306,24 @@ static int streamed_chunk(int KS, int OT, int He, int E, size_t *lds)
         }
     *lds = per_ht * hc + fixed;
     return hc;
+}
+
+bool backward_mfma_shape(const slicemoe_config &c)
+{
+    const int ds = c.d / c.S;
+    const bool width = ds == 24 || ds == 48 || ds == 64 || ds == 96 || ds == 128 || ds == 192;
+    if (c.dtype != SLICEMOE_BF16 || !width || c.He % 32 != 0 || (c.flags & SLICEMOE_FLAG_FORCE_GENERIC)) return false;
+    if (backward_weights_plan(c).fused) return true;
+    // the rows kernel keeps an expert's biases in the LDS, beside at least one hidden tile's fragments: hidden widths up to about
+    // 31 000 (slice width 192) to 39 000 (24); the fp32 kernels take any
+    size_t lds = 0;
+    streamed_chunk((ds + 15) / 16, (ds + 31) / 32, c.He, c.E, &lds);
+    return lds <= (size_t)max_lds_per_block();
+}
+
+size_t backward_mfma_packed_bytes(const slicemoe_config &c)
+{
+    return backward_mfma_shape(c) ? bwd_packed_layout(c).stride * (size_t)c.E : 0;
 }
 
 template <int DS>

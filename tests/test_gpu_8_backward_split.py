@@ -38,6 +38,9 @@ CASES = {
     "w128_hot": shape(128, 64, 4, 2, 1500),
     "w192_2tiles": shape(192, 64, 8, 2, 65),
     "w192_5tiles": shape(192, 160, 3, 3, 22),
+    # an expert's biases beyond the LDS of the rows kernel: the fp32 kernels (the router's part stays on the matrix cores)
+    "w24_biases_beyond_lds": shape(24, 40000, 2, 1, 10, S=2),
+    "w192_biases_beyond_lds": shape(192, 32000, 2, 1, 5, S=2),
     # two 32-expert tiles in the router's kernels; slices that end inside a 32-slice unit, one unit, several blocks of units
     "w24_E40": shape(24, 96, 40, 2, 331, S=3),
     "w48_E64": shape(48, 64, 64, 2, 8),
@@ -54,7 +57,7 @@ def test_backward_at_the_edges_of_the_split(name):
     if name.endswith("hot"):
         w["br2"] = wl.to_storage(np.where(np.arange(s.E) == s.E - 1, 8.0, w["br2"]), s.dtype)
     cfg = B.config_of(s)
-    assert B.slicemoe_backward_uses_mfma(cfg) == 1
+    assert B.slicemoe_backward_uses_mfma(cfg) == (0 if name.endswith("beyond_lds") else 1)
     dout = wl.make_dout(s)
     ref_f = oracle.forward_train(h, s.S, s.k, w, noise=None, drop_u=None, capacity=s.capacity(), tau=1.0, sigma=0.0, rate=0.0)
     ref = oracle.backward(h, s.S, s.k, w, dout, ref_f["idx"], ref_f["inv"])
