@@ -11,12 +11,11 @@
 //   bwd_weights_kernel       (backward_weights_mfma.hip) the transposed layout, for the weight gradients; for experts
 //                            whose hidden tiles fit one block it gives dL/dx and dL/dp too, and this kernel does not run.
 //
-// Precision: u, da, z, the activation and its derivative in fp32 (erf by the five-term rational approximation of
-// Abramowitz & Stegun 7.1.26, absolute error 1.5e-7, sharing its exponential with the density); the operands of the
+// Precision: u, da, z, the activation and its derivative in fp32 (normal_cdf_pdf4); the operands of the
 // second-stage matrix instructions (p dz, a1) enter as two-term bf16 splits (hi + lo, 16 significant bits, one
-// matrix matrix instruction per term against exact bf16 data), so the results are of fp32 grade; three terms (24 significant
-// bits) at widths 24, 48 and 192, whose operands used to be, and stay, fp32.  The kernels are bound by
-// vector instructions, not by the matrix pipe, so a further term costs little.
+// matrix instruction per term against exact bf16 data), so the results are of fp32 grade; three terms (24 significant
+// bits) at widths 24, 48 and 192 (backward_terms), which are as close to 64-bit arithmetic as the fp32 kernels.  The kernels are
+// bound by vector instructions, not by the matrix pipe, so a further term costs little.
 #include "bwd_mfma.h"
 
 namespace slicemoe {
@@ -168,7 +167,6 @@ hipError_t bwd_pack_launch(const BwdPackJobs &jobs, hipStream_t s)
 // chunks.  Eight wavefronts (two per SIMD); four at width 192, whose rows and accumulators take more than half a SIMD's
 // registers.
 template <int DS> constexpr int kBmTileWaves = DS <= 128 ? 8 : 4;
-template <int DS> constexpr int kBmTerms = DS == 24 || DS == 48 || DS == 192 ? 3 : 2;   // bf16 terms of p dz
 template <int DS>
 __global__ __launch_bounds__(kBmTileWaves<DS> * 64) void bwd_rows_streamed_mfma_kernel(
     const bf16_t *__restrict__ x, const bf16_t *__restrict__ dout, const float *__restrict__ pk,
@@ -224,7 +222,9 @@ __global__ __launch_bounds__(kBmTileWaves<DS> * 64) void bwd_rows_streamed_mfma_
         for (int ot = 0; ot < OT; ++ot)
 #pragma unroll
             for (int i = 0; i < 16; ++i) dx[ot][i] = 0.f;
-        float dp = 0.f;
+        float dps[8];   // dL/dp: eight sums side by side, a single chain over the hidden units would round more than a tree
+#pragma unroll
+        for (int i = 0; i < 8; ++i) dps[i] = 0.f;
         for (int ch = 0; ch < nchunks; ++ch) {
             __syncthreads();   // everyone is done with the previous contents
             stage_bytes(ew + (size_t)ch * hc * KS * 1024, (char *)w1f, (size_t)hc * KS * 1024, tid, THREADS);
@@ -246,7 +246,7 @@ __global__ __launch_bounds__(kBmTileWaves<DS> * 64) void bwd_rows_streamed_mfma_
                     u = mfma_bf16(__builtin_bit_cast(bf16x8, w1f[(hl * KS + ks) * 64 + lane]), xb[ks], u);
                     da = mfma_bf16(__builtin_bit_cast(bf16x8, w2r[(hl * KS + ks) * 64 + lane]), gb[ks], da);
                 }
-                constexpr int TERMS = kBmTerms<DS>;
+                constexpr int TERMS = backward_terms(DS);   // of p dz
                 uint32_t pd[2][TERMS][4];   // p dz by K-step of the second product; terms, the largest first
 #pragma unroll
                 for (int qq = 0; qq < 4; ++qq) {
@@ -254,11 +254,11 @@ __global__ __launch_bounds__(kBmTileWaves<DS> * 64) void bwd_rows_streamed_mfma_
                     float z[4], cdf[4], dens[4], pdz[4];
 #pragma unroll
                     for (int c = 0; c < 4; ++c) z[c] = fmaf(p, u[4 * qq + c], bb[c]);
-                    normal_cdf_pdf4(z, cdf, dens);
+                    normal_cdf_pdf4<TERMS == 3>(z, cdf, dens);
 #pragma unroll
                     for (int c = 0; c < 4; ++c) {
                         const float dz = da[4 * qq + c] * fmaf(z[c], dens[c], cdf[c]);
-                        dp = fmaf(dz, u[4 * qq + c], dp);
+                        dps[4 * (qq & 1) + c] = fmaf(dz, u[4 * qq + c], dps[4 * (qq & 1) + c]);
                         pdz[c] = p * dz;
                     }
                     split_terms<TERMS>(pdz, pd[qq >> 1], 2 * (qq & 1));
@@ -275,6 +275,7 @@ __global__ __launch_bounds__(kBmTileWaves<DS> * 64) void bwd_rows_streamed_mfma_
             }
         }
         cur_e = e;
+        float dp = ((dps[0] + dps[1]) + (dps[2] + dps[3])) + ((dps[4] + dps[5]) + (dps[6] + dps[7]));
         dp += __shfl_xor(dp, 32);
         if (valid) {
             if (g == 0) dpk[a] = dp;

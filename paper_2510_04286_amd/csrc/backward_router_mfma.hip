@@ -2,8 +2,9 @@
 // Hr = 256 and up to 64 experts.  Same mathematics as bwd_router_generic_kernel in backward_generic.hip; three kernels:
 //
 //   bwd_route_logits_mfma_kernel   the forward router's layout: a lane owns one slice of a 32-slice tile.  Recomputes the
-//       router exactly as the forward does (hidden layer on bf16 MFMA with the bias preloaded, ReLU, two-term fp16 split,
-//       logits on fp16 MFMA; noise; softmax with the temperature), then per lane: the selected probabilities, back
+//       router: the hidden layer exactly as the forward does (bf16 MFMA with the bias preloaded: the same ReLU pattern), the
+//       logits to fp32 rounding (ReLU and two-term fp16 split on fp16 MFMA like the forward's, or three bf16 terms on bf16
+//       MFMA, see below); noise; softmax with the temperature; then per lane: the selected probabilities, back
 //       through the dropout's renormalisation and the softmax to dL/dg (16 experts per lane and expert tile, as the
 //       logits).  Writes dL/dg as bf16 tables, one per term, and the ReLU pattern, one bit per hidden unit.
 //   bwd_route_inputs_mfma_kernel   same layout: dL/du = Wr2 dL/dg with dL/dg read back in accumulator order, i.e. as
@@ -14,7 +15,9 @@
 //       the slices of its block.  Stores its pieces into the block's slot of partial sums.
 //
 // dL/dg, u and dL/du enter matrix instructions as two bf16 terms (16 significant bits) at widths 64, 96 and 128, as three (24
-// bits) at 24, 48 and 192, where they used to be, and stay, fp32 (kRbTerms).
+// bits: the fp32 values themselves) at 24, 48 and 192 (kRbTerms).  At the latter the logits too are formed from all of u and from
+// Wr2 as it is stored, the softmax uses expf, and dWr2 takes the products of all terms: the gradients are as close to 64-bit
+// arithmetic as those of the fp32 kernels (relative errors at width 48, 16 384 slices: 1.5e-7 to 2.8e-7).
 #include "bwd_mfma.h"
 #include "lds_rows.h"
 
@@ -26,12 +29,12 @@ typedef _Float16 r_f16x8 __attribute__((ext_vector_type(8)));
 constexpr int kRbHr = 256, kRbHT = 8;
 constexpr int kRbThreads = 512;                 // slice kernels: 8 wavefronts
 constexpr int kRbWaves = kRbThreads / 64;
-template <int DS> constexpr int kRbTerms = DS == 24 || DS == 48 || DS == 192 ? 3 : 2;   // bf16 terms of dL/dg, u and dL/du
+template <int DS> constexpr int kRbTerms = backward_terms(DS);   // bf16 terms of dL/dg, u and dL/du
 
 // Repacked router (bytes from the start of the buffer); KS = ds / 16 and OT = ds / 32 rounded up (zero-padded), ET = expert tiles of 32 (experts
 // past E are zero).
 //   w1f  [8][KS][64]      Wr1 fragments, lane (i, g), slot m: Wr1[16ks + 8g + m][32ht + i]                   (bf16)
-//   w2f  [8][2][ET][64]   Wr2 for the logits: lane (i, g), slot m: Wr2[32ht + chain(s, g, m)][32et + i]       (fp16)
+//   w2f  [8][2][ET][64]   Wr2 for the logits: lane (i, g), slot m: Wr2[32ht + chain(s, g, m)][32et + i]       (fp16; bf16 with three terms)
 //   w2c  [ET][2][8][64]   Wr2 for dL/du:      lane (i, g), slot m: Wr2[32ht + i][32et + chain(s, g, m)]       (bf16)
 //   w1c  [8][2][OT][64]   Wr1 for dL/dx:      lane (i, g), slot m: Wr1[32ot + i][32ht + chain(s, g, m)]       (bf16)
 //   w2r  [8][2 ET][64]    rows of Wr2:        lane (i, g), slot m: Wr2[32ht + i][16s + 8g + m]                (bf16)
@@ -112,31 +115,50 @@ __global__ __launch_bounds__(kRbThreads) void bwd_route_logits_mfma_kernel(
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks)
                 acc = mfma_bf16(__builtin_bit_cast(bf16x8, w1f[(ht * KS + ks) * 64 + lane]), xb[ks], acc);
-            uint32_t t0[8], t1[8], bits = 0;
+            uint32_t bits = 0;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const float u0 = fmaxf(acc[2 * i], 0.f), u1 = fmaxf(acc[2 * i + 1], 0.f);
-                bits |= (acc[2 * i] > 0.f ? 1u : 0u) << (2 * i);
-                bits |= (acc[2 * i + 1] > 0.f ? 1u : 0u) << (2 * i + 1);
-                const r_h2 hi = __builtin_bit_cast(r_h2, __builtin_amdgcn_cvt_pkrtz(u0, u1));
-                const float r0 = u0 - (float)hi[0], r1 = u1 - (float)hi[1];   // exact remainders
-                t0[i] = __builtin_bit_cast(uint32_t, hi);
-                t1[i] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(r0, r1));
-            }
+            for (int i = 0; i < 16; ++i) bits |= (acc[i] > 0.f ? 1u : 0u) << i;
             bits <<= (ht & 1) * 16;
             act0 |= (ht >> 1) == 0 ? bits : 0u;
             act1 |= (ht >> 1) == 1 ? bits : 0u;
             act2 |= (ht >> 1) == 2 ? bits : 0u;
             act3 |= (ht >> 1) == 3 ? bits : 0u;
+            if constexpr (TERMS == 3) {   // the hidden layer whole, against the bf16 weights as they are
+                uint32_t ut[2][TERMS][4];
 #pragma unroll
-            for (int s = 0; s < 2; ++s) {
-                const r_f16x8 u0 = __builtin_bit_cast(r_f16x8, make_uint4(t0[4 * s], t0[4 * s + 1], t0[4 * s + 2], t0[4 * s + 3]));
-                const r_f16x8 u1 = __builtin_bit_cast(r_f16x8, make_uint4(t1[4 * s], t1[4 * s + 1], t1[4 * s + 2], t1[4 * s + 3]));
+                for (int q = 0; q < 4; ++q) {
+                    const float u[4] = {fmaxf(acc[4 * q], 0.f), fmaxf(acc[4 * q + 1], 0.f), fmaxf(acc[4 * q + 2], 0.f), fmaxf(acc[4 * q + 3], 0.f)};
+                    split_terms<TERMS>(u, ut[q >> 1], 2 * (q & 1));
+                }
 #pragma unroll
-                for (int et = 0; et < ET; ++et) {
-                    const r_f16x8 a2 = __builtin_bit_cast(r_f16x8, w2f[((ht * 2 + s) * ET + et) * 64 + lane]);
-                    gacc[et] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a2, u1, gacc[et], 0, 0, 0);   // small term first
-                    gacc[et] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a2, u0, gacc[et], 0, 0, 0);
+                for (int s = 0; s < 2; ++s)
+#pragma unroll
+                    for (int et = 0; et < ET; ++et) {
+                        const bf16x8 a2 = __builtin_bit_cast(bf16x8, w2f[((ht * 2 + s) * ET + et) * 64 + lane]);
+#pragma unroll
+                        for (int t = TERMS - 1; t >= 0; --t)   // small terms first
+                            gacc[et] = mfma_bf16(a2, __builtin_bit_cast(bf16x8, make_uint4(ut[s][t][0], ut[s][t][1], ut[s][t][2], ut[s][t][3])), gacc[et]);
+                    }
+            } else {
+                uint32_t t0[8], t1[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const float u0 = fmaxf(acc[2 * i], 0.f), u1 = fmaxf(acc[2 * i + 1], 0.f);
+                    const r_h2 hi = __builtin_bit_cast(r_h2, __builtin_amdgcn_cvt_pkrtz(u0, u1));
+                    const float r0 = u0 - (float)hi[0], r1 = u1 - (float)hi[1];   // exact remainders
+                    t0[i] = __builtin_bit_cast(uint32_t, hi);
+                    t1[i] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(r0, r1));
+                }
+#pragma unroll
+                for (int s = 0; s < 2; ++s) {
+                    const r_f16x8 u0 = __builtin_bit_cast(r_f16x8, make_uint4(t0[4 * s], t0[4 * s + 1], t0[4 * s + 2], t0[4 * s + 3]));
+                    const r_f16x8 u1 = __builtin_bit_cast(r_f16x8, make_uint4(t1[4 * s], t1[4 * s + 1], t1[4 * s + 2], t1[4 * s + 3]));
+#pragma unroll
+                    for (int et = 0; et < ET; ++et) {
+                        const r_f16x8 a2 = __builtin_bit_cast(r_f16x8, w2f[((ht * 2 + s) * ET + et) * 64 + lane]);
+                        gacc[et] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a2, u1, gacc[et], 0, 0, 0);   // small term first
+                        gacc[et] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a2, u0, gacc[et], 0, 0, 0);
+                    }
                 }
             }
         }
@@ -158,7 +180,7 @@ __global__ __launch_bounds__(kRbThreads) void bwd_route_logits_mfma_kernel(
         float den = 0.f;
 #pragma unroll
         for (int i = 0; i < ET * 16; ++i) {
-            v[i] = __builtin_amdgcn_exp2f(fmaf(v[i], sc, nm));
+            v[i] = TERMS == 3 ? expf((v[i] - m) * inv_tau) : __builtin_amdgcn_exp2f(fmaf(v[i], sc, nm));
             den += v[i];
         }
         den += __shfl_xor(den, 32);
@@ -302,7 +324,7 @@ __global__ __launch_bounds__(kRbThreads) void bwd_route_inputs_mfma_kernel(
                 for (int s = 0; s < 2; ++s) {
                     const bf16x8 wf = __builtin_bit_cast(bf16x8, w2c[((et * 2 + s) * kRbHT + ht) * 64 + lane]);
 #pragma unroll
-                    for (int t = TERMS - 1; t >= 0; --t) du = mfma_bf16(wf, frag_of(dgt[et][t], s), du);
+                    for (int t = 0; t < TERMS; ++t) du = mfma_bf16(wf, frag_of(dgt[et][t], s), du);   // large terms first, see the weights kernel
                 }
             const uint32_t word = (ht >> 1) == 0 ? act.x : (ht >> 1) == 1 ? act.y : (ht >> 1) == 2 ? act.z : act.w;
             const uint32_t bits = word >> ((ht & 1) * 16);
@@ -475,15 +497,17 @@ __global__ __launch_bounds__(kRbThreads, DS <= 128 ? 2 : 1) void bwd_route_weigh
     store_rows(0, 0);
     __syncthreads();
 
-    f32x16 aW1[OT], aW2[ET];
+    // dWr2 and dbr2 with three terms: the products of small terms are summed on their own, so that the large ones are rounded as
+    // seldom as there are K-steps
+    f32x16 aW1[OT], aW2[ET], aW2s[ET];
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
 #pragma unroll
-        for (int et = 0; et < ET; ++et) aW2[et][i] = 0.f;
+        for (int et = 0; et < ET; ++et) aW2[et][i] = aW2s[et][i] = 0.f;
 #pragma unroll
         for (int ot = 0; ot < OT; ++ot) aW1[ot][i] = 0.f;
     }
-    float ab1 = 0.f, ab2 = 0.f;
+    float ab1 = 0.f, ab2 = 0.f, ab2s = 0.f;
     int buf = 0;
 #pragma unroll 1
     for (int r0 = 0; r0 < nrows; r0 += kRbUnit) {
@@ -501,11 +525,19 @@ __global__ __launch_bounds__(kRbThreads, DS <= 128 ? 2 : 1) void bwd_route_weigh
             const bf16x8 wf = G::WLDS ? __builtin_bit_cast(bf16x8, ((const uint4 *)(lds + G::off_w))[(ht * KS + ks) * 64 + lane]) : w1r[G::WLDS ? 0 : ks];
             u = mfma_bf16(*(const bf16x8 *)(xs + (ax ^ (ks << 5))), wf, u);
         }
+        // A matrix instruction whose products outweigh its accumulator input cuts the latter off toward minus infinity, which adds
+        // up in dbr1: so the large term comes first, and with three terms every K-step starts from zero.
 #pragma unroll
-        for (int s = 0; s < GS; ++s)
+        for (int s = 0; s < GS; ++s) {
+            const bool fresh = TERMS == 3 && s > 0;
+            f32x16 d;
 #pragma unroll
-            for (int t = TERMS - 1; t >= 0; --t)   // small terms first
-                du = mfma_bf16(*(const bf16x8 *)(gs + t * G::g_bytes + (ag ^ (s << 5))), w2r[s], du);
+            for (int i = 0; i < 16; ++i) d[i] = fresh ? 0.f : du[i];
+#pragma unroll
+            for (int t = 0; t < TERMS; ++t) d = mfma_bf16(*(const bf16x8 *)(gs + t * G::g_bytes + (ag ^ (s << 5))), w2r[s], d);
+#pragma unroll
+            for (int i = 0; i < 16; ++i) du[i] = fresh ? du[i] + d[i] : d[i];
+        }
         uint32_t up[2][TERMS][4], dup[2][TERMS][4];   // by half of the unit (K-step)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -523,17 +555,22 @@ __global__ __launch_bounds__(kRbThreads, DS <= 128 ? 2 : 1) void bwd_route_weigh
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
 #pragma unroll
-            for (int et = 0; et < ET; ++et) {   // dWr2 [hidden unit][expert]: lane = expert; products of terms down to the last one's size
+            for (int et = 0; et < ET; ++et) {   // dWr2 [hidden unit][expert]: lane = expert; small products first
                 bf16x8 gt[TERMS];
 #pragma unroll
                 for (int t = 0; t < TERMS; ++t) gt[t] = transposed(gs + t * G::g_bytes, tg, GR::STRIDE, et, s);
 #pragma unroll
-                for (int o = TERMS - 1; o >= 0; --o)
+                for (int o = TERMS == 3 ? 4 : 1; o >= 0; --o)   // two terms: products down to the second's size
 #pragma unroll
-                    for (int t = 0; t <= o; ++t) aW2[et] = mfma_bf16(frag(up[s][o - t]), gt[t], aW2[et]);
+                    for (int t = 0; t < TERMS; ++t)
+                        if (o - t >= 0 && o - t < TERMS) {
+                            if (TERMS == 3 && o > 0) aW2s[et] = mfma_bf16(frag(up[s][o - t]), gt[t], aW2s[et]);
+                            else aW2[et] = mfma_bf16(frag(up[s][o - t]), gt[t], aW2[et]);
+                        }
                 if (ht == 2 * et + s) {   // dbr2: the sums of dL/dg over the slices, one fragment per wavefront
 #pragma unroll
-                    for (int t = TERMS - 1; t >= 0; --t) ab2 += fragment_sum(gt[t]);
+                    for (int t = TERMS - 1; t > 0; --t) ab2s += fragment_sum(gt[t]);
+                    ab2 += fragment_sum(gt[0]);
                 }
             }
 #pragma unroll
@@ -549,6 +586,11 @@ __global__ __launch_bounds__(kRbThreads, DS <= 128 ? 2 : 1) void bwd_route_weigh
     }
 
     // ---- this block's slot: dWr1 [ds][Hr] | dWr2 [Hr][E] | dbr1 [Hr] | dbr2 [E]
+    if constexpr (TERMS == 3) {
+#pragma unroll
+        for (int et = 0; et < ET; ++et) aW2[et] += aW2s[et];
+    }
+    ab2 += ab2s;
     float *slot = part + (size_t)blockIdx.x * slot_floats;
     float *pWr1 = slot, *pWr2 = pWr1 + (size_t)DS * kRbHr, *pbr1 = pWr2 + (size_t)kRbHr * E, *pbr2 = pbr1 + kRbHr;
 #pragma unroll
@@ -586,8 +628,6 @@ bool backward_router_mfma_shape(const slicemoe_config &c)
            inputs_lds(OT, ET) <= (size_t)max_lds_per_block();
 }
 
-static int router_terms(int ds) { return ds == 24 || ds == 48 || ds == 192 ? 3 : 2; }   // kRbTerms
-
 // scratch: the repacked router | dL/dg terms [terms][Ns][32 ET] bf16 | ReLU bits [Ns][2][4] words
 struct RouterBwdScratch {
     size_t dg, bits, total;
@@ -597,7 +637,7 @@ static RouterBwdScratch router_bwd_scratch(const slicemoe_config &c)
     const size_t Ns = (size_t)c.T * c.S, ET = (size_t)(c.E + 31) / 32;
     RouterBwdScratch R;
     size_t at = align_up(router_bwd_layout(c.d / c.S, (int)ET).total, 256);
-    R.dg = at;     at += align_up(router_terms(c.d / c.S) * Ns * 32 * ET * sizeof(bf16_t), 256);
+    R.dg = at;     at += align_up(backward_terms(c.d / c.S) * Ns * 32 * ET * sizeof(bf16_t), 256);
     R.bits = at;   at += align_up(Ns * 8 * sizeof(uint32_t), 256);
     R.total = at;
     return R;
@@ -671,9 +711,9 @@ void backward_router_pack_jobs(const slicemoe_config &c, const slicemoe_weights 
     const bf16_t *Wr1 = (const bf16_t *)w.Wr1, *Wr2 = (const bf16_t *)w.Wr2;
     BwdPackJob *J = jobs.job + jobs.count;
     jobs.count += 7;
-    // w1f: Wr1 [ds, Hr] itself.  w2f: Wr2 [Hr, E] with the hidden units as contraction slots, fp16, experts padded to EP.
+    // w1f: Wr1 [ds, Hr] itself.  w2f: Wr2 [Hr, E] with the hidden units as contraction slots, experts padded to EP.
     J[0] = bwd_pack_job(kPackLayer1, Wr1, dsK, ds, Hr, Hr, (size_t)Hr, 1, 0, pb + L.w1f, 0, 1);
-    J[1] = bwd_pack_job(kPackChainF16, Wr2, Hr, Hr, EP, E, (size_t)E, 1, 0, pb + L.w2f, 0, 1);
+    J[1] = bwd_pack_job(backward_terms(ds) == 3 ? kPackChain : kPackChainF16, Wr2, Hr, Hr, EP, E, (size_t)E, 1, 0, pb + L.w2f, 0, 1);
     // w2c: M[e][h] = Wr2[h][e] ([EP, Hr], experts as contraction slots).  w1c: M[h][c] = Wr1[c][h] ([Hr, ds]).
     J[2] = bwd_pack_job(kPackChain, Wr2, EP, E, Hr, Hr, 1, (size_t)E, 0, pb + L.w2c, 0, 1);
     J[3] = bwd_pack_job(kPackChain, Wr1, Hr, Hr, dsN, ds, 1, (size_t)Hr, 0, pb + L.w1c, 0, 1);

@@ -30,8 +30,7 @@
 // He = 512: 2.78 -> 1.09 ms for 1 048 576 rows; width 96, He = 384: 228 -> 98 us for 131 056 rows.  131 072 rows at width
 // 48: 2.9 ms of vector-ALU kernel -> 59 us.
 //
-// TERMS: bf16 terms of the activation and of p dz.  Two (16 significant bits) where this backward has always run on two; three
-// (24 bits, products exact) for the widths whose backward used to be, and stays, fp32 in every operand: 24, 48 and 192.
+// TERMS: bf16 terms of the activation and of p dz, backward_terms(DS).
 #include "bwd_mfma.h"
 #include "lds_rows.h"
 #include "wavefront.h"
@@ -354,7 +353,7 @@ __global__ __launch_bounds__(WAVES * 64, MINWAVES) void bwd_weights_kernel(
                         float z[4], cdf[4], dens[4], dz[4], act[4], pd[4];
 #pragma unroll
                         for (int c = 0; c < 4; ++c) z[c] = fmaf(pv[c], u[4 * q + c], bias);
-                        normal_cdf_pdf4(z, cdf, dens);
+                        normal_cdf_pdf4<TERMS == 3>(z, cdf, dens);
                         __builtin_amdgcn_sched_barrier(0);
                         if (FUSE && 2 * q < WAVES) dx_mma(fr);
                         if (half == 1) {
@@ -567,19 +566,22 @@ hipError_t launch_backward_weights(const slicemoe_config &c, const BwdPacked &L,
 {
     const BackwardWeightsPlan W = backward_weights_plan(c);
     const int ds = c.d / c.S, waves = weights_config(ds, c.He).waves;
-#define SLICEMOE_WEIGHTS(DS, WAVES, NBUF, WLDS, FUSE, TERMS, MINW)                                                                   if (ds == DS && waves == WAVES && W.fused == FUSE)                                                                                    return run_weights<DS, WAVES, NBUF, WLDS, FUSE, TERMS, MINW>(c, W, L, h, d_out, pk, offsets, perm, packed, slot_floats,                                                                       part, dxrow, dpk, s);
-    SLICEMOE_WEIGHTS(24, 4, 2, false, true, 3, 2)
-    SLICEMOE_WEIGHTS(24, 8, 2, false, true, 3, 2)
-    SLICEMOE_WEIGHTS(24, 8, 2, false, false, 3, 2)
-    SLICEMOE_WEIGHTS(48, 4, 2, false, true, 3, 2)
-    SLICEMOE_WEIGHTS(48, 8, 2, false, true, 3, 2)
-    SLICEMOE_WEIGHTS(48, 8, 2, false, false, 3, 2)
-    SLICEMOE_WEIGHTS(64, 4, 2, false, true, 2, 2)
-    SLICEMOE_WEIGHTS(64, 8, 2, false, true, 2, 2)
-    SLICEMOE_WEIGHTS(64, 8, 2, false, false, 2, 2)
-    SLICEMOE_WEIGHTS(96, 4, 1, true, false, 2, 2)
-    SLICEMOE_WEIGHTS(128, 8, 1, true, false, 2, 2)
-    SLICEMOE_WEIGHTS(192, 4, 1, true, false, 3, 1)
+#define SLICEMOE_WEIGHTS(DS, WAVES, NBUF, WLDS, FUSE, MINW)                                                                        \
+    if (ds == DS && waves == WAVES && W.fused == FUSE)                                                                              \
+        return run_weights<DS, WAVES, NBUF, WLDS, FUSE, backward_terms(DS), MINW>(c, W, L, h, d_out, pk, offsets, perm, packed,      \
+                                                                                  slot_floats, part, dxrow, dpk, s);
+    SLICEMOE_WEIGHTS(24, 4, 2, false, true, 2)
+    SLICEMOE_WEIGHTS(24, 8, 2, false, true, 2)
+    SLICEMOE_WEIGHTS(24, 8, 2, false, false, 2)
+    SLICEMOE_WEIGHTS(48, 4, 2, false, true, 2)
+    SLICEMOE_WEIGHTS(48, 8, 2, false, true, 2)
+    SLICEMOE_WEIGHTS(48, 8, 2, false, false, 2)
+    SLICEMOE_WEIGHTS(64, 4, 2, false, true, 2)
+    SLICEMOE_WEIGHTS(64, 8, 2, false, true, 2)
+    SLICEMOE_WEIGHTS(64, 8, 2, false, false, 2)
+    SLICEMOE_WEIGHTS(96, 4, 1, true, false, 2)
+    SLICEMOE_WEIGHTS(128, 8, 1, true, false, 2)
+    SLICEMOE_WEIGHTS(192, 4, 1, true, false, 1)
 #undef SLICEMOE_WEIGHTS
     return hipErrorInvalidValue;
 }

@@ -25,6 +25,11 @@ __device__ __forceinline__ RowAxis row_axis(int rows, int step, int blocks, int 
     return A;
 }
 
+// bf16 terms that an fp32 operand of the second-stage matrix instructions is split into.  Two (16 significant bits) where this
+// backward has always run on two: 64, 96 and 128.  Three (24 bits: the operand itself) at the widths whose backward used to be
+// the fp32 kernels' and stays of that precision: 24, 48 and 192.
+constexpr int backward_terms(int ds) { return ds == 24 || ds == 48 || ds == 192 ? 3 : 2; }
+
 // Weight repacking for the backward kernels: a few jobs per launch, one thread per 16-byte fragment (or bias value).
 // Generic strided source so that the same code packs a matrix or its transpose: element (kk, col) of the [K, N] matrix
 // being packed is src[kk * rs + col * cs] for kk < Kv and col < Nv, and zero in the padding up to K and N (multiples of
@@ -79,12 +84,23 @@ hipError_t launch_backward_weights(const slicemoe_config &c, const BwdPacked &L,
                                    const int32_t *offsets, const int32_t *perm, const char *packed, size_t slot_floats, float *part,
                                    float *dxrow, float *dpk, hipStream_t s);
 
-// Phi(z), and phi(z) through *density: the normal CDF by Abramowitz & Stegun 7.1.26 on |z| / sqrt 2 (|error| < 1.5e-7),
-// whose exponential exp(-z^2 / 2) is the density's.
-// For four values side by side: a vector instruction that needs the result of the one before waits 8.3 cycles for
+// Phi(z) and the density phi(z) of four values.  EXACT (the widths with three-term operands): by erff and expf.  Otherwise Phi by
+// Abramowitz & Stegun 7.1.26 on |z| / sqrt 2 (|error| < 1.5e-7), whose exponential exp(-z^2 / 2) is the density's.
+// Four side by side: a vector instruction that needs the result of the one before waits 8.3 cycles for
 // it, where a wavefront can issue one every 4.7, so the four chains are interleaved step by step.
+// (65 536 rows at width 48, one training step: 169 us with the approximation everywhere, 176 us with erff and expf; the
+// gradients of the router are then at most as far from 64-bit arithmetic as those of the fp32 kernels, without up to 1.2 times.)
+template <bool EXACT>
 __device__ __forceinline__ void normal_cdf_pdf4(const float (&z)[4], float (&cdf)[4], float (&density)[4])
 {
+    if constexpr (EXACT) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            cdf[i] = 0.5f * (1.f + erff(z[i] * 0.70710678118654752f));
+            density[i] = expf(-0.5f * z[i] * z[i]) * 0.39894228040143267794f;
+        }
+        return;
+    }
     float ax[4], ex[4], t[4], q[4];
 #define SLICEMOE_EACH for (int i = 0; i < 4; ++i)
 #pragma unroll

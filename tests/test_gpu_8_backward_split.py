@@ -83,3 +83,34 @@ def test_backward_at_the_edges_of_the_split(name):
     assert max(err.values()) <= 5e-4, err
     if s.ds in (24, 48, 192):
         assert max(err[n] for n in ("W1", "b1", "W2", "b2")) <= 5e-5, err
+
+
+@pytest.mark.parametrize("ds,He,T,E,draws", [(24, 96, 512, 16, False), (48, 192, 1024, 16, False), (192, 768, 512, 16, False),
+                                              (48, 192, 600, 40, True), (192, 768, 400, 40, True)])
+def test_gradients_of_the_three_term_widths_are_fp32_exact(ds, He, T, E, draws):
+    """Widths 24, 48 and 192 keep every operand at 24 bits: the relative 2-norm error of each weight gradient against the fp64
+    oracle stays below 2^-21 = 4.8e-7, four roundings to fp32 of every summand (probability, dL/dp, dL/dg, dL/du) and of the
+    sums over them.  Operands of 22 bits, or an order of the matrix instructions' sums that is biased, do not meet it (8.5e-7)."""
+    import torch
+    from paper_2510_04286_amd import binding as B
+    s, h, w = make_inputs(shape(ds, He, E, 2, T, S=768 // ds))
+    cfg = B.config_of(s)
+    dout = wl.make_dout(s)
+    noise, drop_u = wl.make_router_draws(s) if draws else (None, None)
+    tau, sigma, rate = (0.8, 0.1, 0.2) if draws else (1.0, 0.0, 0.0)
+    wd, ws, hd = B.pack(cfg, B.weights_to_device(w, s.dtype)), B.alloc_workspace(cfg), B.to_device(h, s.dtype)
+    train = {"temperature": tau, "noise_std": sigma, "dropout_rate": rate, "capacity_alpha": 0.0,
+             "noise": torch.from_numpy(noise).to("cuda:0") if draws else None,
+             "drop_u": torch.from_numpy(drop_u).to("cuda:0") if draws else None}
+    out = torch.empty_like(hd)
+    B.slicemoe_forward_train(cfg, hd, wd, out, ws, **train)
+    grads, d_h = B.alloc_weight_grads(cfg), torch.empty_like(hd)
+    bws = torch.empty(B.slicemoe_backward_workspace_bytes(cfg), dtype=torch.uint8, device="cuda:0")
+    B.slicemoe_backward(cfg, hd, wd, ws, B.to_device(dout, s.dtype), d_h, grads, bws, train=train)
+    torch.cuda.synchronize()
+    views = B.workspace_views(cfg, ws)
+    kw = {"tau": tau, "noise": noise, "sigma": sigma, "drop_u": drop_u, "rate": rate}
+    ref = oracle.backward(h, s.S, s.k, w, dout, views["topk_idx"].cpu().numpy(), views["inv"].cpu().numpy(), **kw)
+    err = {n: np.linalg.norm(grads[n].cpu().numpy().astype(np.float64) - ref[n]) / np.linalg.norm(ref[n]) for n in NAMES}
+    print("\n" + " ".join(f"{n} {e:.2e}" for n, e in err.items()))
+    assert max(err.values()) <= 2.0 ** -21, err
