@@ -642,7 +642,8 @@ __global__ __launch_bounds__(THREADS) void ffn_pipelined_kernel(
             PipeSlots slots;
             slots.prev = slots.cur = unit_image(wave);
             slots.next = unit_image(wave + kWaves);
-            load_b2acc<DS, HT>(S, lds, slots.cur, off_b2, g);
+            int b2_image = slots.cur;
+            load_b2acc<DS, HT>(S, lds, b2_image, off_b2, g);
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) S.xb[ks] = cur.xb[0][ks];
 #pragma unroll
@@ -696,7 +697,13 @@ __global__ __launch_bounds__(THREADS) void ffn_pipelined_kernel(
                 slots.prev = slots.cur;
                 slots.cur = slots.next;
                 slots.next = unit_image(wave + (ui + 2) * kWaves);
-                if (slots.cur != slots.prev) load_b2acc<DS, HT>(S, lds, slots.cur, off_b2, g);   // the next unit is another expert's
+                // the bias of the unit whose GEMM2 starts next: the next unit's own, two steps into it; with two hidden tiles that
+                // of the unit just finished, whose whole GEMM2 runs in the next unit's steps (after the last unit: in the drain)
+                const int b2_next = HT > 2 ? slots.cur : slots.prev;
+                if (b2_next != b2_image) {
+                    b2_image = b2_next;
+                    load_b2acc<DS, HT>(S, lds, b2_image, off_b2, g);
+                }
             }
         }
         r = end1;

@@ -24,6 +24,12 @@ CASES = {
     "w64_9tiles": shape(64, 288, 64, 2, 777),
     "w64_last_split_ffn": shape(64, 256, 32, 2, 6144, S=16),     # 1.5 units per CU
     "w64_first_other_ffn": shape(64, 256, 32, 2, 6160, S=16),
+    # an expert of two hidden tiles in the pipelined kernel, whose second layer lags by a whole unit: blocks with one unit per
+    # wavefront, with several, and with the rows of two experts
+    "w64_2tiles_other_ffn": shape(64, 64, 16, 2, 6400, S=4),
+    "w64_2tiles_E64": shape(64, 64, 64, 3, 20000, S=4),
+    "w64_2tiles_E5": shape(64, 64, 5, 2, 9000, S=4),
+    "w64_4tiles_E64": shape(64, 128, 64, 3, 20000, S=4),
     "w64_two_tiles_a_block": shape(64, 128, 16, 3, 8193),
     "w64_last_split_router": shape(64, 128, 16, 2, 32768, S=16),  # four tiles per CU
     "w64_first_other_router": shape(64, 128, 16, 2, 32784, S=16),
