@@ -15,7 +15,8 @@
  *   - Every call only enqueues kernels on `stream` and returns (slicemoe_backward forks one of
  *     its kernels onto a stream of the library's own and joins it back, see there); there is
  *     no host-side synchronisation and no device->host copy.  Same inputs give bit-identical
- *     outputs.
+ *     outputs, and without a capacity limit a slice's routing, probabilities and output do not
+ *     depend on the batch it comes in (sums have one order, whichever kernel a batch size takes).
  *   - Slice id n = t*S + s; because slices are contiguous, h[T, d] row-major IS the slice
  *     matrix x[Ns = T*S, ds].  Assignment id a = n*k + j for the j-th selected expert.
  *   - Linear layers are y = x W + b with W stored [in, out] row-major; expert tensors carry

@@ -803,26 +803,22 @@ __global__ __launch_bounds__(THREADS) void ffn_streamed_kernel(
 // ------------------------------------------------------------------------------ split
 // Small batches (a decoding step: a few units of 32 rows per expert).  What bounds them is the latency of a block that
 // brings an expert's 64 KiB and more into the LDS for one wavefront's serial walk over the hidden tiles.  Here the eight
-// wavefronts of a block share ONE unit of 32 rows, each with every eighth hidden tile, whose fragments go straight from
-// memory into its registers (nobody else in the block needs them, and they are requested before the row indices have
-// arrived), and the parts of y are added up in the LDS, in a fixed order.  SLOTS of them fit there; where that is half
-// of the wavefronts (width 192), the other half hands its parts over first.
+// wavefronts of a block share ONE unit of 32 rows: eight hidden tiles at a time, one per wavefront, whose first-layer fragments
+// go straight from memory into its registers (nobody else in the block needs them, and they are requested before the row
+// indices have arrived); the activations go to the LDS, and the second layer is one wavefront per output tile.
+// The sums of an output tile run over the hidden tiles in the order of the other kernels, from the same start (b2_first: the
+// second-layer bias, as the pipelined kernel; else zero), so a row's y does not depend on which kernel its batch takes.
 // Measured: see ffn_is_small.
 constexpr int kSplitWaves = 8;
-template <int DS> struct SplitFfn {
-    static constexpr int OT = SliceTiles<DS>::OT;
-    static constexpr int SLOTS = OT <= 4 ? kSplitWaves : kSplitWaves / 2;
-    static constexpr size_t lds = (size_t)SLOTS * OT * 4096;
-};
 template <int DS>
 __global__ __launch_bounds__(kSplitWaves * 64) void ffn_split_kernel(
     const bf16_t *__restrict__ x, const float *__restrict__ pk, const int32_t *__restrict__ offsets,
     const int32_t *__restrict__ perm, const char *__restrict__ experts, size_t e_stride, size_t off_w1, size_t off_w2,
-    size_t off_b1, size_t off_b2, int HT, int E, int k, EpiConst K, half_t *__restrict__ y)
+    size_t off_b1, size_t off_b2, int HT, int E, int k, bool b2_first, EpiConst K, half_t *__restrict__ y)
 {
-    constexpr int KS = SliceTiles<DS>::KS, OT = SliceTiles<DS>::OT, SLOTS = SplitFfn<DS>::SLOTS;
-    extern __shared__ __align__(16) char lds[];
-    f32x4 *part = (f32x4 *)lds;   // [SLOTS][OT][4][64]
+    constexpr int KS = SliceTiles<DS>::KS, OT = SliceTiles<DS>::OT;
+    static_assert(OT <= kSplitWaves, "one wavefront per output tile");
+    __shared__ uint4 hs[2][kSplitWaves][2][64];   // activations of eight hidden tiles, as operands of the second layer
     const int tid = threadIdx.x, lane = tid & 63, j = lane & 31, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
@@ -838,82 +834,69 @@ __global__ __launch_bounds__(kSplitWaves * 64) void ffn_split_kernel(
     unit_rows<1>(row0, row_end, true, j, perm, row, a);
 
     const char *ew = experts + (size_t)e * e_stride;
-    uint4 w1[KS], w2[2 * OT];
+    uint4 w1[KS], w2[kSplitWaves][2];
     auto load_w1 = [&](int ht) {
 #pragma unroll
-        for (int i = 0; i < KS; ++i) w1[i] = ((const uint4 *)(ew + off_w1))[(ht * KS + i) * 64 + lane];
+        for (int i = 0; i < KS; ++i) w1[i] = ((const uint4 *)(ew + off_w1))[(min(ht, HT - 1) * KS + i) * 64 + lane];
     };
-    auto load_w2 = [&](int ht) {
+    auto load_w2 = [&](int ht0) {   // this wavefront's output tile, eight hidden tiles
 #pragma unroll
-        for (int i = 0; i < 2 * OT; ++i) w2[i] = ((const uint4 *)(ew + off_w2))[(ht * 2 * OT + i) * 64 + lane];
+        for (int i = 0; i < kSplitWaves; ++i)
+#pragma unroll
+            for (int s = 0; s < 2; ++s) w2[i][s] = ((const uint4 *)(ew + off_w2))[((min(ht0 + i, HT - 1) * 2 + s) * OT + wave) * 64 + lane];
     };
-    const int ht0 = min(wave, HT - 1);
-    load_w1(ht0);
-    load_w2(ht0);
+    load_w1(wave);
+    if (wave < OT) load_w2(0);
     RowUnit<DS, 1> cur;
     float p[1];
     load_rows<DS, 1>(cur, a, row, x, pk, k, g, p);
     set_p<DS, 1>(cur, p);
 
-    f32x16 yacc[1][OT];
-    zero_acc<DS, 1>(yacc);
-    for (int ht = wave; ht < HT; ht += kSplitWaves) {
-        const int next = min(ht + kSplitWaves, HT - 1);
-        h2 bias[8];
-        load_bias_tile((const uint4 *)(ew + off_b1), ht, g, bias);
-        f32x16 acc;
+    const float *b2 = (const float *)(ew + off_b2);   // padded with zeros by the packer
+    f32x16 yacc;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+    for (int q = 0; q < 4; ++q) {
+        f32x4 bb = {0.f, 0.f, 0.f, 0.f};
+        if (b2_first && wave < OT) bb = *(const f32x4 *)(b2 + wave * 32 + 8 * q + 4 * g);
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) acc = mfma_bf16(__builtin_bit_cast(bf16x8, w1[ks]), cur.xb[0][ks], acc);
-        if (HT > kSplitWaves) load_w1(next);
-        uint4 hb[2];
-        activation_tile(acc, cur.p2[0], bias, K, hb);
-#pragma unroll
-        for (int i = 0; i < 2 * OT; ++i)   // i = s * OT + ot
-            yacc[0][i % OT] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, w2[i]), __builtin_bit_cast(f16x8, hb[i / OT]),
-                                                                     yacc[0][i % OT], 0, 0, 0);
-        if (HT > kSplitWaves) load_w2(next);
+        for (int c = 0; c < 4; ++c) yacc[4 * q + c] = bb[c];
     }
-
-    auto put = [&](int slot) {
+    int buf = 0;
+    for (int ht0 = 0; ht0 < HT; ht0 += kSplitWaves, buf ^= 1) {
+        const int ht = ht0 + wave;
+        if (ht < HT) {
+            h2 bias[8];
+            load_bias_tile((const uint4 *)(ew + off_b1), ht, g, bias);
+            f32x16 acc;
 #pragma unroll
-        for (int ot = 0; ot < OT; ++ot)
+            for (int r = 0; r < 16; ++r) acc[r] = 0.f;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const f32x16 &v = yacc[0][ot];
-                part[((slot * OT + ot) * 4 + q) * 64 + lane] = f32x4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
+            for (int ks = 0; ks < KS; ++ks) acc = mfma_bf16(__builtin_bit_cast(bf16x8, w1[ks]), cur.xb[0][ks], acc);
+            if (HT > kSplitWaves) load_w1(ht + kSplitWaves);
+            uint4 hb[2];
+            activation_tile(acc, cur.p2[0], bias, K, hb);
+#pragma unroll
+            for (int s = 0; s < 2; ++s) hs[buf][wave][s][lane] = hb[s];
+        }
+        lds_barrier();   // (the other buffer is free: everyone has read it before arriving here)
+        if (wave < OT) {
+#pragma unroll
+            for (int i = 0; i < kSplitWaves; ++i) {
+                if (ht0 + i >= HT) break;
+#pragma unroll
+                for (int s = 0; s < 2; ++s)
+                    yacc = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, w2[i][s]), __builtin_bit_cast(f16x8, hs[buf][i][s][lane]),
+                                                                  yacc, 0, 0, 0);
             }
-    };
-    if constexpr (SLOTS < kSplitWaves) {
-        if (wave >= SLOTS) put(wave - SLOTS);
-        __syncthreads();
-        if (wave < SLOTS) {
-#pragma unroll
-            for (int ot = 0; ot < OT; ++ot)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const f32x4 v = part[((wave * OT + ot) * 4 + q) * 64 + lane];
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) yacc[0][ot][4 * q + c] += v[c];
-                }
+            if (ht0 + kSplitWaves < HT) load_w2(ht0 + kSplitWaves);
         }
     }
-    if (wave < SLOTS) put(wave);   // (into the slot this wavefront has just read)
-    __syncthreads();
-    const float *b2 = (const float *)(ew + off_b2);   // padded with zeros by the packer
-    for (int i = wave; i < 2 * OT; i += kSplitWaves) {   // the halves of the output tiles are dealt out to the wavefronts
-        const int ot = i >> 1, qp = i & 1;
-        f32x4 s[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+    if (wave < OT) {
 #pragma unroll
-        for (int w = 0; w < SLOTS; ++w)
-#pragma unroll
-            for (int t = 0; t < 2; ++t) s[t] += part[((w * OT + ot) * 4 + 2 * qp + t) * 64 + lane];
-        f32x16 acc;   // the eight values stand where the store looks for them
-#pragma unroll
-        for (int c = 0; c < 8; ++c) acc[c] = acc[8 + c] = s[c >> 2][c & 3];
-        if (qp == 0) store_row_pieces<DS, true>(row[0], acc, ot, 0, b2, y, g);
-        else store_row_pieces<DS, true>(row[0], acc, ot, 1, b2, y, g);
+        for (int qp = 0; qp < 2; ++qp) {
+            if (b2_first) store_row_pieces<DS, false>(row[0], yacc, wave, qp, b2, y, g);
+            else store_row_pieces<DS, true>(row[0], yacc, wave, qp, b2, y, g);
+        }
     }
 }
 
@@ -1017,30 +1000,27 @@ static hipError_t run_streamed(const slicemoe_config &c, const PackedLayout &L, 
 
 template <int DS>
 static hipError_t run_split(const slicemoe_config &c, const PackedLayout &L, const void *h, const float *p, const int32_t *offsets,
-                            const int32_t *perm, const char *experts, void *y, hipStream_t s)
+                            const int32_t *perm, const char *experts, bool b2_first, void *y, hipStream_t s)
 {
     const long long Na = (long long)c.T * c.S * c.k;
     const long long blocks = Na / kResU + c.E;   // sum over the experts of ceil(rows / 32) is no larger
-    auto kern = ffn_split_kernel<DS>;
-    const hipError_t err = grant_dynamic_lds((const void *)kern, SplitFfn<DS>::lds);
-    if (err != hipSuccess) return err;
-    kern<<<(int)blocks, kSplitWaves * 64, SplitFfn<DS>::lds, s>>>((const bf16_t *)h, p, offsets, perm, experts, L.e_stride, L.e_w1, L.e_w2,
-                                                                   L.e_b1, L.e_b2, c.He / 32, c.E, c.k, make_epi_const(), (half_t *)y);
+    ffn_split_kernel<DS><<<(int)blocks, kSplitWaves * 64, 0, s>>>((const bf16_t *)h, p, offsets, perm, experts, L.e_stride, L.e_w1, L.e_w2,
+                                                                  L.e_b1, L.e_b2, c.He / 32, c.E, c.k, b2_first, make_epi_const(), (half_t *)y);
     return hipGetLastError();
 }
 
 // Whether the batch is for the split kernel: units (of 32 rows, two experts per slice) per CU up to which it was measured
-// to be the faster one.  Whole forward in us, other kernel / split (21.3 us is what four launches in a row take):
-//   width 24   0.1: 22.7 / 21.6   4: 23.0 / 21.6   6: 24.7 / 22.4   8: 25.5 / 25.3
-//         48   0.1: 24.8 / 21.9   2: 22.9 / 21.5   3: 23.8 / 22.6   4: 24.3 / 24.9
-//         64   0.1: 23.7 / 21.1   1: 22.2 / 21.3   1.5: 23.0 / 21.5   2: 23.2 / 23.9
-//         96   0.1: 37.9 / 21.6   1: 38.8 / 24.8   3: 41.6 / 37.1   4: 42.5 / 42.3   6: 40.5 / 53.2
-//         128  0.1: 48.9 / 24.1   1: 54.4 / 35.7   3: 59.5 / 52.6   4: 60.3 / 60.2   6: 67.5 / 81.4
-//         192  0.1: 51.4 / 34.4   0.5: 54.0 / 41.4   1: 58.6 / 62.4
+// to be the faster one.  Whole forward in us, other kernel / split (21 to 23 us is what four launches in a row take):
+//   width 24   0.1: 23.4 / 21.5   2: 22.9 / 21.5   3: 22.1 / 22.3   4: 23.3 / 23.8   6: 23.4 / 27.8
+//         48   0.1: 25.0 / 23.2   2: 23.3 / 23.1   2.5: 24.0 / 23.1   3: 24.1 / 25.1   4: 24.7 / 27.3
+//         64   0.1: 24.1 / 22.8   1: 22.6 / 22.6   1.5: 23.4 / 22.9   2: 23.9 / 25.2   3: 25.6 / 29.7
+//         96   0.1: 38.1 / 22.9   1: 32.0 / 25.8   2: 33.3 / 32.1   2.5: 34.8 / 34.4   3: 35.4 / 38.5   4: 36.6 / 44.3
+//         128  0.1: 49.1 / 24.4   1: 53.7 / 36.6   3: 59.9 / 54.1   3.5: 59.9 / 55.5   4: 60.1 / 61.2
+//         192  0.1: 50.8 / 28.9   1: 58.9 / 45.6   1.5: 60.0 / 46.7   2: 60.6 / 58.2   3: 64.2 / 73.9
 // Width 384 has no instantiation: its rows and accumulators take a SIMD's whole register file.
 static bool ffn_is_small(int ds, long long Na)
 {
-    const double units_per_cu = ds == 24 ? 6 : ds == 48 ? 3 : ds == 64 ? 1.5 : ds == 96 || ds == 128 ? 3 : ds == 192 ? 0.5 : 0;
+    const double units_per_cu = ds == 24 ? 2 : ds == 48 || ds == 96 ? 2.5 : ds == 64 ? 1.5 : ds == 128 ? 3.5 : ds == 192 ? 2 : 0;
     return (double)Na <= units_per_cu * kResU * num_compute_units();
 }
 
@@ -1054,12 +1034,13 @@ hipError_t launch_ffn_mfma(const slicemoe_config &c, const void *h, const float 
     const FfnPlan pl = plan_ffn(L);
     const char *experts = (const char *)packed + L.experts;
     if (ffn_is_small(L.ds, Na)) {
-        if (L.ds == 24) return run_split<24>(c, L, h, p, offsets, perm, experts, y, s);
-        if (L.ds == 48) return run_split<48>(c, L, h, p, offsets, perm, experts, y, s);
-        if (L.ds == 64) return run_split<64>(c, L, h, p, offsets, perm, experts, y, s);
-        if (L.ds == 96) return run_split<96>(c, L, h, p, offsets, perm, experts, y, s);
-        if (L.ds == 128) return run_split<128>(c, L, h, p, offsets, perm, experts, y, s);
-        return run_split<192>(c, L, h, p, offsets, perm, experts, y, s);
+        const bool b2_first = pl.resident && L.ds == 64;   // the start of the sums in the kernel that larger batches take
+        if (L.ds == 24) return run_split<24>(c, L, h, p, offsets, perm, experts, b2_first, y, s);
+        if (L.ds == 48) return run_split<48>(c, L, h, p, offsets, perm, experts, b2_first, y, s);
+        if (L.ds == 64) return run_split<64>(c, L, h, p, offsets, perm, experts, b2_first, y, s);
+        if (L.ds == 96) return run_split<96>(c, L, h, p, offsets, perm, experts, b2_first, y, s);
+        if (L.ds == 128) return run_split<128>(c, L, h, p, offsets, perm, experts, b2_first, y, s);
+        return run_split<192>(c, L, h, p, offsets, perm, experts, b2_first, y, s);
     }
     if (pl.resident) {
         if (L.ds == 24) return run_resident<24, 3, 1024>(c, L, pl, h, p, offsets, perm, experts, y, s);

@@ -338,17 +338,20 @@ __global__ __launch_bounds__(THREADS) void route_mfma_kernel(
 
 // Small batches, whose tiles would leave most CUs without a block of the kernel above (512 slices are 16 tiles, one
 // block of sixteen wavefronts).  What bounds them is latency: the router's 48 KiB (width 64) to the LDS, then one
-// wavefront's serial chain over eight hidden tiles.  Here the eight wavefronts of a block share a tile, each with one
-// of the eight hidden tiles, whose fragments it keeps in registers (read straight from memory: nobody else in the block
-// needs them), and leave their parts of the logits in the LDS; one wavefront per tile adds them up in order and selects.
-// A block takes up to NB consecutive tiles.
-// Measured, whole forward: 32 tokens of d = 1024, S = 16: 28.7 -> 23.4 us; 4095 tokens of d = 512, S = 8: 36.6 -> 33.1 us;
-// 5001 tokens of d = 768, S = 4: 78 -> 70 us.
+// wavefront's serial chain over eight hidden tiles.  Here the eight wavefronts of a block share a tile in the first layer, each
+// with one of the eight hidden tiles, whose fragments it keeps in registers (read straight from memory: nobody else in the block
+// needs them), and leave the two terms of the hidden layer in the LDS; then one wavefront
+// per tile runs the second layer in the order of the kernel above and selects.  Every logit is therefore the same sum in the
+// same order in both kernels: a slice is routed the same way whatever batch it comes in.
+// A block takes up to NB consecutive tiles.  Measured: see split_tiles.
 constexpr int kSplitThreads = kRouteHT * 64, kSplitTiles = 4;
 template <int DS, int ET> struct SplitTile {
-    static constexpr int NB = kSplitTiles / ET;                     // 128 KiB of partial logits
+    static constexpr int NB = kSplitTiles / ET;
     static constexpr bool HOLD = SliceTiles<DS>::KS <= (ET == 1 ? 12 : 8);          // first-layer fragments and a tile's rows ahead in registers
-    static constexpr size_t lds = (size_t)kRouteHT * NB * ET * 4096 + 64 * 4;
+    static constexpr size_t off_w2 = (size_t)NB * kRouteHT * 4096;                  // behind the terms of u: [NB][HT][2 K-steps][2 terms][64]
+    static constexpr bool W2_LDS = ET == 2;                                         // else in the registers of the wavefronts that select
+    static constexpr size_t off_cnt = off_w2 + (W2_LDS ? (size_t)ET * kRouteHT * 2048 : 0);
+    static constexpr size_t lds = off_cnt + 64 * 4;
 };
 template <int DS, int ET>
 __global__ __launch_bounds__(kSplitThreads) void route_split_kernel(
@@ -356,11 +359,13 @@ __global__ __launch_bounds__(kSplitThreads) void route_split_kernel(
     size_t off_b1, size_t off_b2, const float *__restrict__ noise, float sigma, float exp_scale, int tiles,
     int32_t *__restrict__ idx, float *__restrict__ pk, uint16_t *__restrict__ hist /* may be null */, int hist_stride)
 {
-    constexpr int KS = SliceTiles<DS>::KS, NB = SplitTile<DS, ET>::NB;
-    constexpr bool HOLD = SplitTile<DS, ET>::HOLD;
+    typedef SplitTile<DS, ET> G;
+    constexpr int KS = SliceTiles<DS>::KS, NB = G::NB;
+    constexpr bool HOLD = G::HOLD;
     extern __shared__ __align__(16) char lds[];
-    f32x4 *part = (f32x4 *)lds;                                         // [wavefront][NB][ET][4][64]
-    int *hcnt = (int *)(lds + (size_t)kRouteHT * NB * ET * 4096);       // [64]
+    uint4 *us = (uint4 *)lds;                    // [NB][HT][2][2][64]
+    uint4 *w2s = (uint4 *)(lds + G::off_w2);     // [ET][HT][2][64]
+    int *hcnt = (int *)(lds + G::off_cnt);       // [64]
     const int tid = threadIdx.x, lane = tid & 63, j = lane & 31, g = lane >> 5;
     const int ht = __builtin_amdgcn_readfirstlane(tid >> 6);            // this wavefront's hidden tile
     const int ntiles = (int)((Ns + 31) / 32);
@@ -375,19 +380,27 @@ __global__ __launch_bounds__(kSplitThreads) void route_split_kernel(
     bf16x8 xb[KS];
     load_x(tile0, xb);
     const uint4 *w1 = (const uint4 *)(packed + off_w1) + ht * KS * 64 + lane;
-    uint4 w1r[HOLD ? KS : 1], w2r[ET][2];
+    uint4 w1r[HOLD ? KS : 1], w2r[G::W2_LDS ? ET : kRouteHT][2];
     if constexpr (HOLD) {
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) w1r[ks] = w1[ks * 64];
     }
+    const uint4 *w2 = (const uint4 *)(packed + off_w2) + lane;   // [ET][HT][2][64]
+    if constexpr (G::W2_LDS) {
 #pragma unroll
-    for (int et = 0; et < ET; ++et)
+        for (int et = 0; et < ET; ++et)
 #pragma unroll
-        for (int s = 0; s < 2; ++s) w2r[et][s] = ((const uint4 *)(packed + off_w2))[((et * kRouteHT + ht) * 2 + s) * 64 + lane];
+            for (int s = 0; s < 2; ++s) w2r[et][s] = w2[((et * kRouteHT + ht) * 2 + s) * 64];
+    } else if (ht < NB) {
+#pragma unroll
+        for (int h = 0; h < kRouteHT; ++h)
+#pragma unroll
+            for (int s = 0; s < 2; ++s) w2r[h][s] = w2[(h * 2 + s) * 64];
+    }
     const f32x16 bias1 = load_bias_tile((const float *)(packed + off_b1), ht, g);
-    f32x16 bias2[ET];
+    f32x16 gacc[ET];   // logit accumulators start from the second-layer bias
 #pragma unroll
-    for (int et = 0; et < ET; ++et) bias2[et] = load_bias_tile((const float *)(packed + off_b2), et, g);
+    for (int et = 0; et < ET; ++et) gacc[et] = load_bias_tile((const float *)(packed + off_b2), et, g);
     if (tid < 64) hcnt[tid] = 0;
 
 #pragma unroll
@@ -403,41 +416,41 @@ __global__ __launch_bounds__(kSplitThreads) void route_split_kernel(
 #pragma unroll
         for (int i = 0; i < 8; ++i) relu_split_pair(acc[2 * i], acc[2 * i + 1], t0[i], t1[i]);
 #pragma unroll
-        for (int et = 0; et < ET; ++et) {
-            f32x16 lg;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) lg[r] = 0.f;
-#pragma unroll
-            for (int s = 0; s < 2; ++s) {   // small term first
-                const f16x8 a2 = __builtin_bit_cast(f16x8, w2r[et][s]);
-                const f16x8 u0 = __builtin_bit_cast(f16x8, make_uint4(t0[4 * s], t0[4 * s + 1], t0[4 * s + 2], t0[4 * s + 3]));
-                const f16x8 u1 = __builtin_bit_cast(f16x8, make_uint4(t1[4 * s], t1[4 * s + 1], t1[4 * s + 2], t1[4 * s + 3]));
-                lg = __builtin_amdgcn_mfma_f32_32x32x16_f16(a2, u1, lg, 0, 0, 0);
-                lg = __builtin_amdgcn_mfma_f32_32x32x16_f16(a2, u0, lg, 0, 0, 0);
-            }
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                part[(((ht * NB + t) * ET + et) * 4 + q) * 64 + lane] = f32x4{lg[4 * q], lg[4 * q + 1], lg[4 * q + 2], lg[4 * q + 3]};
+        for (int s = 0; s < 2; ++s) {
+            us[(((t * kRouteHT + ht) * 2 + s) * 2 + 0) * 64 + lane] = make_uint4(t0[4 * s], t0[4 * s + 1], t0[4 * s + 2], t0[4 * s + 3]);
+            us[(((t * kRouteHT + ht) * 2 + s) * 2 + 1) * 64 + lane] = make_uint4(t1[4 * s], t1[4 * s + 1], t1[4 * s + 2], t1[4 * s + 3]);
         }
         if constexpr (HOLD) {
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) xb[ks] = xn[ks];
         }
     }
+    if constexpr (G::W2_LDS) {
+#pragma unroll
+        for (int et = 0; et < ET; ++et)
+#pragma unroll
+            for (int s = 0; s < 2; ++s) w2s[((et * kRouteHT + ht) * 2 + s) * 64 + lane] = w2r[et][s];
+    }
     __syncthreads();
     if (ht < NB && tile0 + ht < tile_end) {   // this wavefront's tile
+#pragma unroll
+        for (int h = 0; h < kRouteHT; ++h)
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                const f16x8 u0 = __builtin_bit_cast(f16x8, us[(((ht * kRouteHT + h) * 2 + s) * 2 + 0) * 64 + lane]);
+                const f16x8 u1 = __builtin_bit_cast(f16x8, us[(((ht * kRouteHT + h) * 2 + s) * 2 + 1) * 64 + lane]);
+#pragma unroll
+                for (int et = 0; et < ET; ++et) {   // small term first
+                    const f16x8 a2 = __builtin_bit_cast(f16x8, G::W2_LDS ? w2s[((et * kRouteHT + h) * 2 + s) * 64 + lane] : w2r[G::W2_LDS ? 0 : h][s]);
+                    gacc[et] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a2, u1, gacc[et], 0, 0, 0);
+                    gacc[et] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a2, u0, gacc[et], 0, 0, 0);
+                }
+            }
         float v[ET * 16];
 #pragma unroll
         for (int et = 0; et < ET; ++et)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) v[et * 16 + r] = bias2[et][r];
-        for (int w = 0; w < kRouteHT; ++w)
-#pragma unroll
-            for (int i = 0; i < ET * 4; ++i) {
-                const f32x4 p = part[((w * NB + ht) * ET * 4 + i) * 64 + lane];
-#pragma unroll
-                for (int c = 0; c < 4; ++c) v[4 * i + c] += p[c];
-            }
+            for (int r = 0; r < 16; ++r) v[et * 16 + r] = gacc[et][r];
         const long long n = (long long)(tile0 + ht) * 32 + j;
         select_experts<ET>(v, n, n < Ns, g, E, k, noise, sigma, exp_scale, idx, pk, hist != nullptr, hcnt);
     }
@@ -473,10 +486,10 @@ static long long route_blocks(long long Ns, int chunk_tiles)
 }
 
 // Tiles per block of the kernel for small batches, or 0: the batch is for the other kernel.  As many tiles per CU as a block
-// holds at once: measured at width 64 with 32 experts (whole forward, other kernel / this one) 28.3 / 23.3 us with a tile on
-// every fourth CU, 29.6 / 23.6 with one per CU, 36.8 / 33.6 with four, 40.5 / 39.9 with six, 42.6 / 44.1 with eight; at width
-// 128 with 64 experts 64.4 / 58.0 with one, 66.5 / 61.6 with two, 68.4 / 68.1 with three, 68.7 / 70.2 with four; at width 192
-// 74.2 / 70.3 with three, 113.4 / 113.0 with four.  Width 384: a tile's rows and first-layer fragments exceed the registers.
+// holds at once.  Whole forward in us, other kernel / this one: width 64, 32 experts 29.2 / 23.8 with a tile on every sixteenth
+// CU, 29.2 / 23.8 with one per CU, 31.7 / 27.2 with two, 36.5 / 33.8 with four; width 128, 64 experts 63.9 / 56.5 with one,
+// 66.2 / 60.2 with two; width 192, 16 experts 76.5 / 72.6 with three.  Width 384: a tile's rows and first-layer fragments exceed
+// the registers.
 static int split_tiles(int ds, int et, long long Ns)
 {
     const long long ntiles = (Ns + 31) / 32, cus = num_compute_units();

@@ -26,6 +26,9 @@ CASES = {
     "w64_first_other_ffn": shape(64, 256, 32, 2, 6160, S=16),
     # an expert of two hidden tiles in the pipelined kernel, whose second layer lags by a whole unit: blocks with one unit per
     # wavefront, with several, and with the rows of two experts
+    "w24_first_other_ffn": shape(24, 96, 16, 2, 8208, S=16),       # 2 units per CU
+    "w192_last_split_ffn": shape(192, 768, 16, 2, 8192, S=4),
+    "w192_first_other_ffn": shape(192, 768, 16, 2, 8196, S=4),
     "w64_2tiles_other_ffn": shape(64, 64, 16, 2, 6400, S=4),
     "w64_2tiles_E64": shape(64, 64, 64, 3, 20000, S=4),
     "w64_2tiles_E5": shape(64, 64, 5, 2, 9000, S=4),
@@ -83,3 +86,32 @@ def test_small_batches(name):
     print(f"\n[{name}] near-ties {n_tie}, masked {int(bad.sum())}, max|err|/rms {err:.2e}")
     assert n_tie <= 1 and bad.sum() <= 4
     assert err <= TOL_BF16
+
+
+@pytest.mark.parametrize("ds,He,E,k", [(24, 96, 16, 2), (48, 192, 40, 2), (64, 256, 32, 2), (64, 64, 64, 3), (64, 288, 16, 1),
+                                       (96, 384, 16, 2), (96, 160, 33, 2), (128, 512, 64, 2), (192, 768, 16, 3), (192, 96, 40, 2)])
+def test_a_slice_does_not_depend_on_its_batch(ds, He, E, k):
+    """Dropless, a slice's selected experts, probabilities and output are the same bits whether it comes alone, in a batch small
+    enough for the split kernels of the router, the experts or both, or in a large one: every sum has one order."""
+    import torch
+    from paper_2510_04286_amd import binding as B
+    full = shape(ds, He, E, k, 40000, S=4)   # beyond both kernels' small batches
+    s, _, w = make_inputs(shape(ds, He, E, k, 4, S=4))
+    wd = B.pack(B.config_of(s), B.weights_to_device(w, s.dtype))
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(3)
+    h = torch.randn((full.T, full.d), generator=gen, device="cuda:0").to(torch.bfloat16)
+
+    def layer(T):
+        cfg = B.config_of(shape(ds, He, E, k, 4 * T, S=4))
+        ws, out = B.alloc_workspace(cfg), torch.empty((T, full.d), dtype=torch.bfloat16, device="cuda:0")
+        B.slicemoe_forward(cfg, h[:T], wd, out, ws)
+        torch.cuda.synchronize()
+        v = B.workspace_views(cfg, ws)
+        return out, v["topk_idx"].reshape(-1, k).clone(), v["topk_p"].reshape(-1, k).clone()
+
+    want = layer(full.T)
+    for T in (1, 9, 250, 1500, 5000):
+        got = layer(T)
+        for name, a, b in zip(("h'", "topk_idx", "topk_p"), got, want):
+            assert torch.equal(a, b[:a.shape[0]]), f"{name}, {T} tokens"
