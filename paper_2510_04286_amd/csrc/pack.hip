@@ -142,9 +142,9 @@ hipError_t launch_pack(const slicemoe_config &c, const slicemoe_weights &w, void
     const PackedLayout L = packed_layout(c);
     char *base = (char *)packed, *eb = base + L.experts;
     const int ds = L.ds, Hr = L.Hr, He = L.He, E = L.E;
-    // fragments of all experts of one matrix; the items are counted in 32 bits (the LDS of the kernels that use the
-    // buffer bounds He long before)
-    if ((long long)E * (L.dsK > L.dsN ? L.dsK : L.dsN) * He / 8 > (1ll << 28)) return hipErrorInvalidValue;
+    // items are counted in 32 bits, as threads of a launch are: a launch per piece where all pieces together exceed that
+    const unsigned long long most = 0xffffff00ull, frags = (unsigned long long)E * (L.dsK > L.dsN ? L.dsK : L.dsN) * He / 8;
+    if (frags > most) return hipErrorInvalidValue;
     PackJobs P;
     P.job[0] = pack_job(kLayer1, w.W1, ds, L.dsK, He, He, 0, kGeluKappa, (size_t)ds * He, eb + L.e_w1, L.e_stride, E);
     P.job[1] = pack_job(kLayer2, w.W2, He, He, ds, L.dsN, 0, 1.f / kGeluKappa, (size_t)He * ds, eb + L.e_w2, L.e_stride, E);
@@ -154,10 +154,21 @@ hipError_t launch_pack(const slicemoe_config &c, const slicemoe_weights &w, void
     P.job[5] = pack_job(kLayer2, w.Wr2, Hr, Hr, E, L.Epad, 1, 1.f, 0, base + L.r_w2, 0, 1);
     P.job[6] = pack_job(kBias, w.br1, 1, 1, Hr, Hr, 0, 1.f, 0, base + L.r_b1, 0, 1);
     P.job[7] = pack_job(kBias, w.br2, 1, 1, E, L.Epad, 0, 1.f, 0, base + L.r_b2, 0, 1);
-    unsigned total = 0;
+    unsigned long long total = 0;
     for (const PackJob &J : P.job) total += J.items;
-    pack_kernel<<<(total + 255) / 256, 256, 0, s>>>(P);
-    return hipGetLastError();
+    if (total <= most) {
+        pack_kernel<<<(unsigned)((total + 255) / 256), 256, 0, s>>>(P);
+        return hipGetLastError();
+    }
+    for (int q = 0; q < kPackJobs; ++q) {
+        PackJobs one = P;
+        for (int r = 0; r < kPackJobs; ++r)
+            if (r != q) one.job[r].items = 0;
+        pack_kernel<<<(P.job[q].items + 255) / 256, 256, 0, s>>>(one);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace slicemoe

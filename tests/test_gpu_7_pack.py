@@ -57,3 +57,27 @@ def test_packed_buffer_is_the_documented_layout(ds, E, He):
         assert np.array_equal(got[at:at + want.size], want), f"region {n}"
         at = (at + want.size + 255) // 256 * 256
     assert at == got.size
+
+
+def test_matrices_of_more_than_two_gib():
+    """2^28 fragments and more per matrix (64 experts of 2^20 + 32 hidden units): the last tiles of the last expert."""
+    import torch
+    from paper_2510_04286_amd import binding as B
+    ds, E, He = 24, 64, 2 ** 20 + 32
+    cfg = B.config_of(wl.SliceMoEShape("wide", T=1, d=2 * ds, S=2, E=E, k=1, He=He))
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(5)
+
+    def normal(*size):
+        return torch.empty(size, dtype=torch.bfloat16, device="cuda:0").normal_(generator=gen)
+
+    w = {"Wr1": normal(ds, 256), "br1": normal(256), "Wr2": normal(256, E), "br2": normal(E), "W1": normal(E, ds, He),
+         "b1": normal(E, He), "W2": normal(E, He, ds), "b2": normal(E, ds)}
+    got = B.pack(cfg, w)["packed"]
+    n1, n2 = 32 * He * 2, 32 * He * 2   # bytes of an expert's W1 and W2 (both padded to 32)
+    base = got.numel() - ((n1 + 255) // 256 * 256 + (n2 + 255) // 256 * 256 + (He * 2 + 255) // 256 * 256 + 256)
+    tail = 2 * 64 * 16                  # two fragments of 64 lanes: the last hidden tile
+    f1 = got[base + n1 - tail:base + n1].cpu().numpy()
+    f2 = got[base + n1 + n2 - tail:base + n1 + n2].cpu().numpy()
+    np.testing.assert_array_equal(f1, frags_layer1(w["W1"][-1, :, -32:].float().cpu().numpy(), 0.25).view(np.uint8))
+    np.testing.assert_array_equal(f2, frags_layer2(w["W2"][-1, -32:].float().cpu().numpy(), 4.0, False).view(np.uint8))
