@@ -258,13 +258,15 @@ def test_forward_is_deterministic(B):
         np.testing.assert_array_equal(wa[name], wb[name])
 
 
-def test_forward_and_backward_captured_in_a_hip_graph_replay_identically(B):
+@pytest.mark.parametrize("layer,T", [("headline", 1024), ("paper", 1024)])
+def test_forward_and_backward_captured_in_a_hip_graph_replay_identically(B, layer, T):
     """The entry points only launch kernels on the caller's stream (no allocation, no memset, no host wait), so after one
-    eager call (which sets the kernels' LDS attributes) a caller may capture them in a HIP graph.  Every replay is checked
+    eager call (which sets the kernels' LDS attributes) a caller may capture them in a HIP graph, with the fork and join of the
+    expert weight gradients where they are a kernel of their own (the paper's layer).  Every replay is checked
     against the eager result for the inputs then in the captured buffers, with the program's own eager work and
     synchronisations between the replays."""
     import torch
-    shape, h, w = make_inputs(wl.CONFIGS["headline"], 1024)
+    shape, h, w = make_inputs(wl.CONFIGS[layer], T)
     cfg = B.config_of(shape)
     wd = B.pack(cfg, B.weights_to_device(w, shape.dtype))
     hs = [B.to_device(wl.make_h(shape, seed=s), shape.dtype) for s in (1, 5, 9, 13)]
