@@ -12,8 +12,8 @@
  * Conventions common to every entry point
  *   - Every pointer is caller-allocated DEVICE memory unless it is the config / weights
  *     struct itself (HOST).  The library never allocates, frees or keeps a pointer.
- *   - Every call only enqueues kernels on `stream` and returns (slicemoe_backward forks one of
- *     its kernels onto a stream of the library's own and joins it back, see there); there is
+ *   - Every call only enqueues kernels on `stream` and returns (slicemoe_backward may fork
+ *     one of its kernels onto a stream of the library's own and joins it back, see there); there is
  *     no host-side synchronisation and no device->host copy.  Same inputs give bit-identical
  *     outputs, and without a capacity limit a slice's routing, probabilities and output do not
  *     depend on the batch it comes in (sums have one order, whichever kernel a batch size takes).
@@ -294,19 +294,23 @@ slicemoe_status slicemoe_forward_train(const slicemoe_config *cfg, const void *h
  *                        path (no floating-point atomics anywhere in the backward).
  *   workspace            >= slicemoe_backward_workspace_bytes(cfg), 256-byte aligned
  *   stream               the call's place in this stream orders it against the caller's other work, as for every entry
- *                        point.  On the matrix-core path the expert weight gradients (one kernel and its reduction,
- *                        which the rest of the backward neither feeds nor needs) run on a second stream that the library
- *                        owns (one per device, default priority, created at the first backward on the device and kept
- *                        until the process ends): it is forked from `stream` after the weights are repacked and joined
- *                        back into `stream` before the call returns, so everything the call writes is complete when the
- *                        work the caller enqueues next on `stream` runs.  The pattern is a plain fork and join with two
- *                        events, which a HIP graph capture of `stream` takes along (after one eager call has created
- *                        the stream).  Calls from several host threads on one device are enqueued one after the other.
- *                        SLICEMOE_FLAG_SINGLE_STREAM keeps every kernel on `stream` (same results, a few percent slower).
+ *                        point.  Experts that one pass of the matrix cores takes whole (d/S <= 64 and He <= 256) and the fp32
+ *                        kernels stay on `stream`.  For the other experts on the matrix-core path the weight gradients (one
+ *                        kernel and its reduction, which the rest of the backward neither feeds nor needs) run on a second
+ *                        stream that the library owns (one per device, default priority, created at the first such backward
+ *                        on the device and kept until the process ends): it is forked from `stream` after the weights are
+ *                        repacked and joined back into `stream` before the call returns, so everything the call writes is
+ *                        complete when the work the caller enqueues next on `stream` runs.  The pattern is a plain fork and
+ *                        join with two events, which a HIP graph capture of `stream` takes along (after one eager call has
+ *                        created the stream).  Calls from several host threads on one device are enqueued one after the
+ *                        other.  SLICEMOE_FLAG_SINGLE_STREAM keeps every kernel on `stream` (same results; 2% slower at the
+ *                        largest batches of such layers to half as slow again at d/S = 192, no difference elsewhere).
  * For bf16 storage with d/S in {24, 48, 64, 96, 128, 192}, He % 32 == 0 and He up to what the LDS holds of an expert's
- * biases (about 30 000; slicemoe_backward_uses_mfma: 1, 0, or -1 for an invalid config) the expert part (row gradients, dL/dp, expert weight gradients) runs on the matrix cores, and
- * with Hr = 256 the router part too: fp32 pre-activations and derivatives, two-term bf16 operands
- * (three-term at 24, 48 and 192) for the second matrix instructions, fp32-grade results.  Everything else runs in fp32 throughout.
+ * biases (about 30 000; slicemoe_backward_uses_mfma: 1, 0, or -1 for an invalid config) the expert part (row gradients,
+ * dL/dp, expert weight gradients) runs on the bf16 matrix cores, and with Hr = 256 (at d/S = 192 also E <= 32) the router
+ * part too: fp32 pre-activations and derivatives, operands of the second matrix instructions as two bf16 terms (16 bits)
+ * at 64, 96 and 128, as three (24 bits, the fp32 values) at 24, 48 and 192; results of fp32 grade.  At 64, 96 and 128 the
+ * router is recomputed within the numeric range of the forward's (above).  Everything else runs in fp32 throughout.
  * SLICEMOE_FLAG_FORCE_GENERIC selects that throughout.  UNSUPPORTED for Hr > 256.
  */
 typedef struct {

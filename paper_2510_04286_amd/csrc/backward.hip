@@ -108,7 +108,8 @@ BackwardPlan backward_plan(const slicemoe_config &c)
 // p * 2^38 (at most 2^22 * k assignments: no overflow in 64 bits; bits below 2^-38 of a tiny p are rounded off).
 // Bound by launches and latency (a few hundred KiB to read): every block stores its sums in a slot of its own, which the
 // one-block kernel behind it adds up, so nothing has to be cleared first; and only the router's kernels need the result,
-// so the two run behind the expert rows, beside the weight gradients (or their reduction) on the other stream.
+// so the two run behind the expert rows: beside the weight gradients where those are on the other stream, else behind their
+// reduction.
 constexpr float kCapScale = 274877906944.f;   // 2^38
 
 __global__ __launch_bounds__(kCapThreads) void bwd_cap_sums_kernel(const int32_t *__restrict__ idx, const float *__restrict__ pk,
@@ -149,10 +150,13 @@ __global__ __launch_bounds__(kCapThreads) void bwd_cap_coeff_kernel(const unsign
     }
 }
 
-// ---- A stream of the library's own, beside the caller's.  The expert weight gradients (their kernel and the
-// reduction after it) depend on nothing that the rest of the backward produces, and nothing but the caller depends on
-// them, so they run on this stream (where they are a kernel of their own) while the row gradients and the router's kernels run on the caller's: the two
-// chains fill each other's launch gaps and tails.  One stream and two events per device, made at the first backward on
+// ---- A stream of the library's own, beside the caller's, for experts whose weight gradients are a kernel of their own (more
+// hidden tiles than a block, or a width above 64).  That kernel and the reduction after it depend on nothing that the rest of
+// the backward produces, and nothing but the caller depends on them, so they run on this stream while the row gradients and
+// the router's kernels run on the caller's: the two chains fill each other's launch gaps and tails.  Whole backward, one
+// stream / two: width 96, He 384: T = 1024 130 / 105 us, T = 8191 278 / 250; width 128, He 512: T = 1024 349 / 283,
+// T = 16384 2538 / 2483; width 192, He 768: T = 1000 325 / 248, T = 4096 730 / 487; width 64, He 288: T = 16384 692 / 694.
+// One stream and two events per device, made at the first such backward on
 // that device and kept until the process ends; default priority, no implicit synchronisation with the null stream.
 // The events are shared by all calls on a device, so the enqueueing of one call (fork .. join) holds a lock.
 static std::mutex g_side_mutex;
@@ -195,11 +199,10 @@ struct SideJoin {
     }
 };
 
-template <typename T>
-static hipError_t run_backward(const slicemoe_config &c, const void *h, const slicemoe_weights &w, const RouteVariant &v_in,
-                               const float *drop_u, float rate, const int32_t *idx, const float *pk,
-                               const int32_t *offsets, const int32_t *perm, const int32_t *inv, const void *d_out,
-                               void *d_h, const slicemoe_weight_grads &g, void *workspace, hipStream_t s)
+hipError_t launch_backward(const slicemoe_config &c, const void *h, const slicemoe_weights &w, const RouteVariant &v_in,
+                           const float *drop_u, float rate, const int32_t *idx, const float *pk, const int32_t *offsets,
+                           const int32_t *perm, const int32_t *inv, const void *d_out, void *d_h,
+                           const slicemoe_weight_grads &g, void *workspace, hipStream_t s)
 {
     const long long Ns = (long long)c.T * c.S, Na = Ns * c.k;
     const int ds = c.d / c.S;
@@ -280,16 +283,6 @@ static hipError_t run_backward(const slicemoe_config &c, const void *h, const sl
                                                                            g.br1, g.Wr2, g.br2);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     return joiner.join();
-}
-
-hipError_t launch_backward(const slicemoe_config &c, const void *h, const slicemoe_weights &w, const RouteVariant &v,
-                           const float *drop_u, float rate, const int32_t *idx, const float *pk, const int32_t *offsets,
-                           const int32_t *perm, const int32_t *inv, const void *d_out, void *d_h,
-                           const slicemoe_weight_grads &g, void *workspace, hipStream_t s)
-{
-    if (c.dtype == SLICEMOE_BF16)
-        return run_backward<bf16_t>(c, h, w, v, drop_u, rate, idx, pk, offsets, perm, inv, d_out, d_h, g, workspace, s);
-    return run_backward<float>(c, h, w, v, drop_u, rate, idx, pk, offsets, perm, inv, d_out, d_h, g, workspace, s);
 }
 
 }  // namespace slicemoe
