@@ -402,9 +402,9 @@ __global__ __launch_bounds__(kRbThreads) void bwd_route_inputs_mfma_kernel(
 // per unit; as A operands they give u^T and dL/du^T (lane = hidden unit, registers = slices), and read back transposed they are
 // the other operand of dWr1 += x^T dL/du and dWr2 += u^T dL/dg, whose own operand comes from those registers.
 // Bound: the matrix pipe nominally (22 instructions per tile and unit at width 64, 32 experts).  262 144 slices at that
-// shape, with the transposes in the LDS instead of on the matrix pipe and rows loaded ahead: 95 -> 56 us; 524 288
+// shape, with the transposes in the LDS instead of on the matrix pipe and rows loaded ahead: 95 -> 60 us; 524 288
 // slices at width 128, 64 experts: 405 -> 166 us.  At width 48 (32 768 slices, with the logits and inputs kernels): 4.0 ms of
-// vector-ALU kernel -> 50 us.
+// vector-ALU kernel -> 52 us.
 constexpr int kRbUnit = 32;
 template <int DS, int ET, int TERMS> struct RouterWeightsTile {
     static constexpr int KS = SliceTiles<DS>::KS, OT = SliceTiles<DS>::OT, GS = 2 * ET;   // GS: K-steps of 16 experts

@@ -25,10 +25,10 @@
 // wavefront that halves the number of values at every step, and one sum over the wavefronts.
 //
 // Measured, 524 288 rows, width 64, He = 256, 32 experts: rows kernel 172 us + weights kernel 283 us (both evaluating the
-// activation, the latter without prefetch and with transposes on the matrix pipe) -> 239 us; the partial sums of the
-// weight gradients fall from 140 MB in 1056 slots to 38 MB in 288 (their reduction 29-35 -> 13 us).  Unfused at width 128,
-// He = 512: 2.78 -> 1.09 ms for 1 048 576 rows; width 96, He = 384: 228 -> 98 us for 131 056 rows.  131 072 rows at width
-// 48: 2.9 ms of vector-ALU kernel -> 59 us.
+// activation, the latter without prefetch and with transposes on the matrix pipe) -> 254 us (236 at the least); the partial sums of
+// the weight gradients fall from 140 MB in 1056 slots to 38 MB in 288 (their reduction 29-35 -> 12 us).  Unfused, alone on the
+// chip, at width 128, He = 512: 2.78 -> 1.09 ms for 1 048 576 rows; width 96, He = 384: 228 -> 98 us for 131 056 rows.  65 536 rows at
+// width 48: 2.9 ms of vector-ALU kernel -> 60 us, 69 us with erff and expf (see normal_cdf_pdf4).
 //
 // TERMS: bf16 terms of the activation and of p dz, backward_terms(DS).
 #include "bwd_mfma.h"

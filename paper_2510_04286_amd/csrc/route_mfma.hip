@@ -487,8 +487,9 @@ static long long route_blocks(long long Ns, int chunk_tiles)
 
 // Tiles per block of the kernel for small batches, or 0: the batch is for the other kernel.  As many tiles per CU as a block
 // holds at once.  Whole forward in us, other kernel / this one: width 64, 32 experts 29.2 / 23.8 with a tile on every sixteenth
-// CU, 29.2 / 23.8 with one per CU, 31.7 / 27.2 with two, 36.5 / 33.8 with four; width 128, 64 experts 63.9 / 56.5 with one,
-// 66.2 / 60.2 with two; width 192, 16 experts 76.5 / 72.6 with three.  Width 384: a tile's rows and first-layer fragments exceed
+// CU, 29.2 / 23.7 with one per CU, 31.8 / 27.3 with two, 36.6 / 33.8 with four; with 16 experts at width 24 24.8 / 22.1 with one,
+// 27.4 / 24.0 with four, width 48 26.7 / 22.9 and 32.3 / 29.0, width 96 38.9 / 32.1 and 48.4 / 44.2, width 192 66.2 / 58.1 and
+// 113.8 / 112.7; width 128, 64 experts 63.9 / 56.5 with one, 66.3 / 60.3 with two.  Width 384: a tile's rows and first-layer fragments exceed
 // the registers.
 static int split_tiles(int ds, int et, long long Ns)
 {
