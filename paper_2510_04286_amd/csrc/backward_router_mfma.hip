@@ -258,15 +258,6 @@ __global__ __launch_bounds__(kRbThreads) void bwd_route_logits_mfma_kernel(
 // distinct banks.
 constexpr int kRbStageRow = 36;
 
-// Orders LDS traffic between the lanes of one wavefront (the hardware keeps a wavefront's LDS operations in order; this
-// keeps the compiler from moving them across).
-__device__ __forceinline__ void wave_lds_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // LDS: w2c | w1c (the third and fourth pieces of the packed buffer, adjacent) | staging tiles.
 template <int DS, int ET>
 __global__ __launch_bounds__(kRbThreads) void bwd_route_inputs_mfma_kernel(

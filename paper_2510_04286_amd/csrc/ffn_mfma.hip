@@ -28,7 +28,7 @@
 // roundings are replayed on the CPU in tests/test_gelu_poly.py).
 // Range: |x W1| beyond 65504 / kappa saturates the conversion, |z| beyond that overflows fp16.
 //
-// Four variants:
+// Five variants:
 //   split     small batches, any shape: a block is one 32-row unit and its wavefronts share the hidden tiles (see the kernel).
 //   pipelined a whole expert fits in LDS twice over (ds = 64, He <= 256: the benchmark shapes).  One block of
 //             eight wavefronts per CU holds the images of up to two experts; stacked rows are split evenly over
@@ -39,9 +39,12 @@
 //             wavefronts, one wavefront's matrix work overlapping another's vector work; a block re-stages
 //             weights when its range crosses into another expert; wavefront priority follows the number of units
 //             a wavefront still has to do, which keeps them finishing together.
-//   streamed  larger experts (ds = 128, He = 512: 256 KiB; ds = 96, He = 384 of the paper's own shape:
-//             144 KiB): a block walks tiles of one expert and streams the weights through LDS in chunks
-//             of hidden tiles, per row tile.
+//   streamed  larger experts (ds = 128, He = 512: 256 KiB): a block walks row tiles and streams the weights of their expert through the
+//             LDS; software-pipelined with one wavefront per SIMD at the wide slices (128, 192, 384), in chunks of hidden tiles with two
+//             at the others.
+#include <type_traits>
+#include <utility>
+
 #include "mfma.h"
 #include "wavefront.h"
 
@@ -800,6 +803,291 @@ __global__ __launch_bounds__(THREADS) void ffn_streamed_kernel(
     }
 }
 
+// Instruction o of the activation of two pairs of hidden units, the two chains in turn.
+constexpr int kPairOps = 18;
+template <int O>
+__device__ __forceinline__ void activation_op(PairChains &c, const float (&a)[4], h2 p2, h2 bias0, h2 bias1, const EpiConst &K, uint32_t &out0, uint32_t &out1)
+{
+    constexpr int i = O & 1, stage = O >> 1;
+    const h2 bias = i == 0 ? bias0 : bias1;
+    if constexpr (stage == 0) c.s[i] = __builtin_bit_cast(h2, __builtin_amdgcn_cvt_pkrtz(a[2 * i], a[2 * i + 1]));
+    else if constexpr (stage == 1) c.s[i] = pk_fma(c.s[i], p2, bias);
+    else if constexpr (stage == 2) c.v[i] = pk_fma(c.s[i], c.s[i], as_h2(K.neg_w0));
+    else if constexpr (stage == 3) c.Q[i] = pk_fma(c.v[i], as_h2(K.q[4]), as_h2(K.q[3]));
+    else if constexpr (stage < 7) c.Q[i] = pk_fma(c.Q[i], c.v[i], as_h2(K.q[6 - stage]));
+    else if constexpr (stage == 7) c.Q[i] = pk_fma_clamp01(c.s[i], c.Q[i], as_h2(K.half));
+    else (i == 0 ? out0 : out1) = __builtin_bit_cast(uint32_t, c.s[i] * c.Q[i]);
+}
+
+// ------------------------------------------------------------------------------ streamed, software-pipelined
+// One wavefront per SIMD with the whole register file: SUBS row groups of 32 per wavefront, their output accumulators in the
+// accumulation registers.  In step ht a wavefront issues, for all its row groups, GEMM2 of tile ht - 2 and GEMM1 of tile ht, and between
+// these matrix instructions the activation of tile ht - 1: nothing in a step waits for anything else in it.  Two steps after the last
+// tile finish a row tile.  A weight fragment is read from the LDS once for SUBS matrix instructions, through a ring of four.
+// Weights come from memory through registers into two LDS slots, each with W1 of the tile that a step's GEMM1 takes and W2 of the
+// one that its GEMM2 takes: requested two steps ahead, stored one step ahead.  One barrier per step, where the last fragment of the
+// step has been requested and before the first of the next is.
+// Bound: a SIMD with one wavefront issues an instruction every 4.7 cycles at best, whatever its kind, and 12 for a matrix instruction:
+// 1.9 thousand cycles for a step of 48 matrix instructions and 280 others at width 128, measured 2.4 with the arrival of the weights (a
+// CU draws 16 to 20 bytes per cycle from the L2).  Rows go straight to and from registers; through the LDS, spread over the steps, was
+// no faster, and neither was a wavefront of each kind per SIMD (first layer and activation, second layer).
+// Measured against ffn_streamed_kernel, whose two wavefronts per SIMD each wait for their own stages: width 128, He 512,
+// 4 194 304 rows 1421 -> 1315 us; width 192, He 768, 60 012 rows 51.9 -> 41.1 us, 262 144 rows 238 -> 180 us; width 384, He 1536,
+// 65 536 rows 416 -> 231 us.
+template <int DS, int SUBS> struct StreamPipe {
+    static constexpr int KS = SliceTiles<DS>::KS, OT = SliceTiles<DS>::OT;
+    static constexpr int kWaves = 4, kThreads = kWaves * 64, ROWS = SUBS * 32, TM = kWaves * ROWS;   // rows of a wavefront, of a block
+    static constexpr int kT1 = KS * 64, kT2 = 2 * OT * 64, kSlot = kT1 + kT2;   // 16-byte pieces of a tile of W1, W2
+    static constexpr int NP = (KS + 2 * OT) / kWaves;                            // pieces of a slot per thread
+    static_assert(KS % 4 == 0 && (2 * OT) % 4 == 0 && NP <= KS - 4 && NP <= 2 * OT - 4, "whole rounds of the fragment ring; staging before the barrier");
+    bf16x8 xb[SUBS][KS];
+    f32x16 yacc[SUBS][OT];
+    f32x16 acc[SUBS];          // GEMM1 of the tile before
+    uint32_t hb[2][SUBS][4];   // activations of the tile before that, by K-step of GEMM2
+    uint4 ring[4];
+    uint4 bias[2];             // first-layer biases of the tile before
+    h2 p2[SUBS];
+    u32x4 st[NP];              // weights on their way to the LDS
+};
+
+template <int... I, typename F> __device__ __forceinline__ void static_for_impl(std::integer_sequence<int, I...>, F &&f) { (f(std::integral_constant<int, I>{}), ...); }
+template <int N, typename F> __device__ __forceinline__ void static_for(F &&f) { static_for_impl(std::make_integer_sequence<int, N>{}, f); }
+
+// Where a step's weights are in the LDS (this lane's fragments), where those of the steps to come are in memory and go to (this
+// thread's pieces: lane offset in 16-byte pieces from uniform bases).
+struct StreamStep {
+    const uint4 *w, *wn;          // the slots of this step and the next
+    const uint4 *b1;              // this lane group's biases of GEMM1's tile
+    const u32x4 *src1, *src2;     // memory: W1 of the tile two steps ahead, W2 of this step's tile
+    u32x4 *dst;
+};
+
+// One step.  G2, ACT, G1: the stages that it has; FIRST: GEMM2 starts the sums; NEXT2: the next step begins with GEMM2.
+template <int DS, int SUBS, bool G2, bool ACT, bool G1, bool FIRST, bool NEXT2>
+__device__ __forceinline__ void stream_step(StreamPipe<DS, SUBS> &S, const StreamStep &W, const EpiConst &K)
+{
+    typedef StreamPipe<DS, SUBS> P;
+    constexpr int KS = P::KS, OT = P::OT, N2 = G2 ? 2 * OT : 0, NF = N2 + (G1 ? KS : 0), M = SUBS * NF, OPS = 4 * SUBS * kPairOps;
+    static_assert(P::NP + 1 <= NF - 3, "the barrier comes behind the staging");
+    uint32_t out[2][SUBS][4];
+    f32x16 nacc[SUBS];
+    PairChains c;
+    const uint32_t bw[8] = {S.bias[0].x, S.bias[0].y, S.bias[0].z, S.bias[0].w, S.bias[1].x, S.bias[1].y, S.bias[1].z, S.bias[1].w};
+    static_for<M>([&](auto mc) __attribute__((always_inline)) {
+        constexpr int m = decltype(mc)::value, f = m / SUBS, sub = m % SUBS;
+        if constexpr (sub == 0 && f >= 1 && f <= P::NP) {   // a piece requested a step ago to the LDS, the next one requested
+            constexpr int i = f - 1;
+            W.dst[i * P::kThreads] = S.st[i];
+            S.st[i] = i < KS / 4 ? W.src1[i * P::kThreads] : W.src2[(i - KS / 4) * P::kThreads];
+        }
+        const uint4 frag = S.ring[f & 3];
+        if constexpr (f < N2) {
+            constexpr int s = f / OT, ot = f % OT;
+            const f16x8 b = __builtin_bit_cast(f16x8, make_uint4(S.hb[s][sub][0], S.hb[s][sub][1], S.hb[s][sub][2], S.hb[s][sub][3]));
+            f32x16 z = S.yacc[sub][ot];
+            if constexpr (FIRST && s == 0) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) z[r] = 0.f;
+            }
+            S.yacc[sub][ot] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, frag), b, z, 0, 0, 0);
+        } else {
+            constexpr int ks = f - N2;
+            f32x16 z = nacc[sub];
+            if constexpr (ks == 0) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) z[r] = 0.f;
+            }
+            nacc[sub] = mfma_bf16(__builtin_bit_cast(bf16x8, frag), S.xb[sub][ks], z);
+        }
+        if constexpr (sub == SUBS - 1) {   // refill with the fragment four ahead; at the fourth from the end that is the next step's
+            constexpr int fn = f + 4;
+            if constexpr (fn == NF) lds_barrier();
+            if constexpr (fn < N2) S.ring[f & 3] = W.w[P::kT1 + fn * 64];
+            else if constexpr (fn < NF) S.ring[f & 3] = W.w[(fn - N2) * 64];
+            else S.ring[f & 3] = W.wn[(NEXT2 ? P::kT1 : 0) + (fn - NF) * 64];
+        }
+        if constexpr (ACT) {   // the step's activation instructions, spread evenly behind its first two matrix instructions
+            constexpr int o0 = m < 2 ? 0 : ((m - 2) * OPS + M - 3) / (M - 2), o1 = m < 2 ? 0 : ((m - 1) * OPS + M - 3) / (M - 2);
+            static_for<(o1 < OPS ? o1 : OPS) - o0>([&](auto oc) __attribute__((always_inline)) {
+                constexpr int o = o0 + decltype(oc)::value, q = o / kPairOps, sb = q % SUBS, pp = 2 * (q / SUBS);   // row groups in turn
+                const float a[4] = {S.acc[sb][2 * pp], S.acc[sb][2 * pp + 1], S.acc[sb][2 * pp + 2], S.acc[sb][2 * pp + 3]};
+                activation_op<o % kPairOps>(c, a, S.p2[sb], as_h2(bw[pp]), as_h2(bw[pp + 1]), K, out[pp >> 2][sb][pp & 3], out[pp >> 2][sb][(pp & 3) + 1]);
+            });
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    });
+    if constexpr (ACT) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int sub = 0; sub < SUBS; ++sub)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) S.hb[s][sub][i] = out[s][sub][i];
+    }
+    if constexpr (G1) {
+#pragma unroll
+        for (int sub = 0; sub < SUBS; ++sub) S.acc[sub] = nacc[sub];
+        S.bias[0] = W.b1[0];   // of the tile whose GEMM1 this was, for the next step
+        S.bias[1] = W.b1[1];
+    }
+}
+
+template <int DS, int SUBS>
+__global__ __launch_bounds__(256, 1) void ffn_streampipe_kernel(
+    const bf16_t *__restrict__ x, const float *__restrict__ pk, const int32_t *__restrict__ offsets,
+    const int32_t *__restrict__ perm, const char *__restrict__ experts, size_t e_stride, size_t off_w1,
+    size_t off_w2, size_t off_b1, size_t off_b2, int He, int E, int k, EpiConst K, half_t *__restrict__ y)
+{
+    typedef StreamPipe<DS, SUBS> P;
+    constexpr int KS = P::KS, OT = P::OT, TM = P::TM, kT1 = P::kT1, kT2 = P::kT2;
+    const int HT = He / 32;   // at least 3
+    extern __shared__ __align__(16) char lds[];
+    uint4 *slots = (uint4 *)lds;                                   // [2] of W1 [KS][64] | W2 [2][OT][64] fragments
+    const int bias_bytes = He * 2 + OT * 32 * 4;
+    char *bias_lds = lds + 2 * P::kSlot * 16;                      // two images of b1 [HT][2][16] fp16 | b2 [32 OT]
+    int *ids_all = (int *)(bias_lds + 2 * bias_bytes);             // [4][ROWS] slices of the next row tile
+
+    const int tid = threadIdx.x, lane = tid & 63, j = lane & 31, g = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int kshift = (k & (k - 1)) == 0 ? __ffs(k) - 1 : -1;
+    int *ids = ids_all + wave * P::ROWS;
+
+    // row tiles, counted from each expert's first row; lane e holds expert e (E <= 64).  A block takes consecutive ones, blocks that
+    // share an XCD (blockIdx % 8) neighbouring runs, so that few experts are streamed through its L2.
+    const int off_lo = offsets[min(lane, E)], off_hi = offsets[min(lane + 1, E)];
+    const int tiles = (off_hi - off_lo + TM - 1) / TM, first = wavefront_exclusive_scan(tiles, lane);
+    const int total = wavefront_sum(tiles);
+    const int vblock = gridDim.x % 8 == 0 ? (int)(blockIdx.x % 8) * (int)(gridDim.x / 8) + (int)(blockIdx.x / 8) : (int)blockIdx.x;
+    const int t_begin = (int)((long long)vblock * total / gridDim.x), t_end = (int)((long long)(vblock + 1) * total / gridDim.x);
+    if (t_begin >= t_end) return;
+    auto expert_of = [&](int t) { return __builtin_ctzll(__ballot(t >= first && t < first + tiles)); };
+
+    // ---- a wavefront's rows of a row tile
+    struct Rows {
+        int row0, left;   // the first, and how many there are from it to the expert's end (can be less than one)
+    };
+    auto rows_of = [&](int t, int e) {
+        Rows R;
+        R.row0 = __builtin_amdgcn_readlane(off_lo, e) + (t - __builtin_amdgcn_readlane(first, e)) * TM + wave * P::ROWS;
+        R.left = __builtin_amdgcn_readlane(off_hi, e) - R.row0;
+        return R;
+    };
+    auto request_ids = [&](const Rows &R, int (&a)[SUBS]) {   // a lane without a row takes perm[0]
+#pragma unroll
+        for (int sub = 0; sub < SUBS; ++sub) a[sub] = perm[sub * 32 + j < R.left ? R.row0 + sub * 32 + j : 0];
+    };
+    auto store_ids = [&](const int (&a)[SUBS]) {
+#pragma unroll
+        for (int sub = 0; sub < SUBS; ++sub) ids[sub * 32 + j] = kshift >= 0 ? a[sub] >> kshift : a[sub] / k;
+    };
+    auto request_p = [&](const int (&a)[SUBS], float (&p)[SUBS]) {
+#pragma unroll
+        for (int sub = 0; sub < SUBS; ++sub) p[sub] = pk[a[sub]];
+    };
+    auto weights_p = [&](const Rows &R, const float (&p)[SUBS], h2 (&p2)[SUBS]) {
+#pragma unroll
+        for (int sub = 0; sub < SUBS; ++sub) {
+            const float pv = sub * 32 + j < R.left ? p[sub] : 0.f;
+            p2[sub] = __builtin_bit_cast(h2, __builtin_amdgcn_cvt_pkrtz(pv, pv));
+        }
+    };
+    // addresses formed where they are used, not kept in registers through the steps
+    auto opaque_lane = [&]() {
+        int l = lane;
+        asm volatile("" : "+v"(l));
+        return l;
+    };
+    auto take_x = [&](P &S) __attribute__((always_inline)) {   // the rows, as operands
+        const int ln = opaque_lane();
+#pragma unroll
+        for (int sub = 0; sub < SUBS; ++sub)
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks)
+                S.xb[sub][ks] = load_row_piece<DS>((const uint4 *)(x + (size_t)(unsigned)ids[sub * 32 + (ln & 31)] * DS), ks, ln >> 5);
+    };
+    auto leave_y = [&](P &S, const float *b2s, const Rows &R) __attribute__((always_inline)) {   // the output rows, rounded to fp16
+        const int ln = opaque_lane();
+        __builtin_amdgcn_sched_barrier(0);
+        RowUnit<DS, SUBS> u;
+#pragma unroll
+        for (int sub = 0; sub < SUBS; ++sub) u.row[sub] = sub * 32 + (ln & 31) < R.left ? R.row0 + sub * 32 + (ln & 31) : -1;
+        store_rows<DS, SUBS>(u, S.yacc, b2s, y, ln >> 5);
+    };
+    auto stage_bias = [&](int e, int image) {
+        const uint4 *gb1 = (const uint4 *)(experts + (size_t)e * e_stride + off_b1), *gb2 = (const uint4 *)(experts + (size_t)e * e_stride + off_b2);
+        uint4 *d = (uint4 *)(bias_lds + image * bias_bytes);
+        for (int i = tid; i < He / 8; i += P::kThreads) d[i] = gb1[i];
+        if (tid < OT * 8) d[He / 8 + tid] = gb2[tid];   // padded with zeros by the packer
+    };
+
+    // ---- the block's first row tile
+    P S;
+    int e = expert_of(t_begin), image = 0, cur = 0;
+    Rows R = rows_of(t_begin, e);
+    const char *ew = experts + (size_t)e * e_stride, *ewn = ew;
+    {
+        const u32x4 *g1 = (const u32x4 *)(ew + off_w1), *g2 = (const u32x4 *)(ew + off_w2);
+        stage_to_lds<P::kThreads>(g1, slots, kT1, tid);
+#pragma unroll
+        for (int i = 0; i < P::NP; ++i) S.st[i] = i < KS / 4 ? g1[kT1 + i * P::kThreads + tid] : g2[(i - KS / 4) * P::kThreads + tid];
+        stage_bias(e, 0);
+        int a[SUBS];
+        float p[SUBS];
+        request_ids(R, a);
+        request_p(a, p);
+        store_ids(a);
+        wave_lds_sync();
+        take_x(S);
+        weights_p(R, p, S.p2);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < 4; ++m) S.ring[m] = slots[m * 64 + lane];
+
+    auto step = [&](int ht) __attribute__((always_inline)) {
+        StreamStep W;
+        const int h1 = ht + 2;
+        W.w = slots + cur * P::kSlot + lane;
+        W.wn = slots + (cur ^ 1) * P::kSlot + lane;
+        W.dst = (u32x4 *)slots + (cur ^ 1) * P::kSlot + tid;
+        W.b1 = (const uint4 *)(bias_lds + image * bias_bytes) + (ht * 2 + g) * 2;
+        W.src1 = (const u32x4 *)((h1 < HT ? ew : ewn) + off_w1 + (size_t)(h1 < HT ? h1 : max(0, h1 - HT - 2)) * (kT1 * 16)) + tid;
+        W.src2 = (const u32x4 *)(ew + off_w2 + (size_t)min(ht, HT - 1) * (kT2 * 16)) + tid;   // (steps HT, HT + 1: not used)
+        cur ^= 1;
+        return W;
+    };
+    int a[SUBS];
+    float p[SUBS];
+    for (int t = t_begin;; ++t) {
+        const bool more = t + 1 < t_end;
+        const int e_next = more ? expert_of(t + 1) : e;
+        const Rows Rn = rows_of(more ? t + 1 : t, e_next);
+        ewn = experts + (size_t)e_next * e_stride;
+        request_ids(Rn, a);
+        stream_step<DS, SUBS, false, false, true, false, false>(S, step(0), K);
+        stream_step<DS, SUBS, false, true, true, false, true>(S, step(1), K);
+        store_ids(a);
+        request_p(a, p);
+        wave_lds_sync();
+        stream_step<DS, SUBS, true, true, true, true, true>(S, step(2), K);
+        if (e_next != e) stage_bias(e_next, image ^ 1);   // (its last readers have been through the barrier of a step since)
+#pragma unroll 1
+        for (int ht = 3; ht < HT; ++ht) stream_step<DS, SUBS, true, true, true, false, true>(S, step(ht), K);
+        // the rows of the next row tile take the registers that GEMM1 no longer reads, and arrive behind the last two steps
+        if (more) take_x(S);
+        __builtin_amdgcn_sched_barrier(0);
+        stream_step<DS, SUBS, true, true, false, false, true>(S, step(HT), K);
+        stream_step<DS, SUBS, true, false, false, false, false>(S, step(HT + 1), K);
+        leave_y(S, (const float *)(bias_lds + image * bias_bytes + He * 2), R);
+        if (!more) break;
+        R = Rn;
+        weights_p(R, p, S.p2);
+        if (e_next != e) image ^= 1;
+        e = e_next;
+        ew = ewn;
+    }
+}
+
 // ------------------------------------------------------------------------------ split
 // Small batches (a decoding step: a few units of 32 rows per expert).  What bounds them is the latency of a block that
 // brings an expert's 64 KiB and more into the LDS for one wavefront's serial walk over the hidden tiles.  Here the eight
@@ -900,6 +1188,12 @@ __global__ __launch_bounds__(kSplitWaves * 64) void ffn_split_kernel(
     }
 }
 
+template <int DS, int SUBS> static size_t streampipe_lds(int He)
+{
+    typedef StreamPipe<DS, SUBS> P;
+    return (size_t)2 * P::kSlot * 16 + 2 * ((size_t)He * 2 + SliceTiles<DS>::OT * 32 * 4) + (size_t)P::TM * 4;
+}
+
 struct FfnPlan {
     bool resident;
     int hc;
@@ -998,6 +1292,23 @@ static hipError_t run_streamed(const slicemoe_config &c, const PackedLayout &L, 
     return hipGetLastError();
 }
 
+template <int DS, int SUBS>
+static hipError_t run_streampipe(const slicemoe_config &c, const PackedLayout &L, const void *h, const float *p, const int32_t *offsets,
+                                 const int32_t *perm, const char *experts, void *y, hipStream_t s)
+{
+    typedef StreamPipe<DS, SUBS> P;
+    const long long Na = (long long)c.T * c.S * c.k;
+    const long long max_tiles = Na / P::TM + c.E;   // sum over the experts of ceil(rows / TM) is no larger
+    const long long blocks = max_tiles < num_compute_units() ? max_tiles : num_compute_units();
+    auto kern = ffn_streampipe_kernel<DS, SUBS>;
+    const size_t lds = streampipe_lds<DS, SUBS>(c.He);
+    hipError_t err = grant_dynamic_lds((const void *)kern, lds);
+    if (err != hipSuccess) return err;
+    kern<<<(int)blocks, P::kThreads, lds, s>>>((const bf16_t *)h, p, offsets, perm, experts, L.e_stride, L.e_w1, L.e_w2, L.e_b1, L.e_b2, c.He,
+                                               c.E, c.k, make_epi_const(), (half_t *)y);
+    return hipGetLastError();
+}
+
 template <int DS>
 static hipError_t run_split(const slicemoe_config &c, const PackedLayout &L, const void *h, const float *p, const int32_t *offsets,
                             const int32_t *perm, const char *experts, bool b2_first, void *y, hipStream_t s)
@@ -1050,6 +1361,12 @@ hipError_t launch_ffn_mfma(const slicemoe_config &c, const void *h, const float 
         if (L.He == 128) return run_pipelined<64, 4, kPipeThreads>(c, L, pl, h, p, offsets, perm, experts, y, s);
         return run_pipelined<64, 2, kPipeThreads>(c, L, pl, h, p, offsets, perm, experts, y, s);
     }
+    // the pipelined streamed kernel wherever it can run: at least three hidden tiles, biases (twice) beside the weights in the LDS
+    const int HT = c.He / 32;
+    const size_t lds_max = (size_t)max_lds_per_block();
+    if (L.ds == 128 && HT >= 3 && streampipe_lds<128, 3>(c.He) <= lds_max) return run_streampipe<128, 3>(c, L, h, p, offsets, perm, experts, y, s);
+    if (L.ds == 192 && HT >= 3 && streampipe_lds<192, 2>(c.He) <= lds_max) return run_streampipe<192, 2>(c, L, h, p, offsets, perm, experts, y, s);
+    if (L.ds == 384 && HT >= 3 && streampipe_lds<384, 1>(c.He) <= lds_max) return run_streampipe<384, 1>(c, L, h, p, offsets, perm, experts, y, s);
     if (L.ds == 24) return run_streamed<24, 2>(c, L, pl, h, p, offsets, perm, experts, y, s);
     if (L.ds == 48) return run_streamed<48, 2>(c, L, pl, h, p, offsets, perm, experts, y, s);
     if (L.ds == 64) return run_streamed<64, 2>(c, L, pl, h, p, offsets, perm, experts, y, s);

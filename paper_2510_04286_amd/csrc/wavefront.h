@@ -69,4 +69,13 @@ __device__ __forceinline__ int hidden_sum_row(int lane)
     return 16 * ((lane >> 4) & 1) + 8 * ((lane >> 3) & 1) + 4 * (lane >> 5) + 2 * ((lane >> 2) & 1);
 }
 
+// Orders LDS traffic between the lanes of one wavefront (the hardware keeps a wavefront's LDS operations in order; this
+// keeps the compiler from moving them across).
+__device__ __forceinline__ void wave_lds_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 }  // namespace slicemoe

@@ -1,0 +1,48 @@
+"""The streamed expert kernel at its edges: row tiles (of 384, 256 and 128 rows at widths 128, 192 and 384) that are full, one
+row short or one row over, experts without a row and with one, blocks with several row tiles and several experts, the fewest
+hidden tiles it takes, and k that is and is not a power of two."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2510_04286_amd import workload as wl
+from tests.common import TOL_BF16, rms
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("ds,He,k,Ns,tile", [(128, 96, 2, 20000, 384), (128, 128, 3, 120000, 384), (192, 96, 3, 9001, 256), (192, 160, 2, 70000, 256),
+                                             (384, 96, 2, 3000, 128), (384, 128, 1, 40000, 128)])
+def test_row_tiles(ds, He, k, Ns, tile):
+    import torch
+    from paper_2510_04286_amd import binding as B
+    E = 12
+    s = wl.SliceMoEShape("tiles", T=Ns, d=ds, S=1, E=E, k=k, He=He)
+    # slot 0 of a slice: experts 0, 2, 3, ... with 0, 1, tile - 1, tile, tile + 1, ... rows, the rest on expert 11; other slots: 8, 9
+    idx = np.empty((Ns, k), np.int32)
+    idx[:, 0] = 11
+    at = 0
+    for e, rows in zip((2, 3, 4, 5, 6, 7), (1, tile - 1, tile, tile + 1, 2 * tile + 33, 31)):
+        idx[at:at + rows, 0] = e
+        at += rows
+    for j in range(1, k):
+        idx[:, j] = 7 + j
+    order = np.argsort(wl.uniform01(5, 0, 0, Ns))   # scattered over the batch
+    idx = idx[order]
+    pk = (0.25 + 0.5 * wl.uniform01(4, 0, 0, idx.size)).reshape(idx.shape)
+    w = wl.make_weights(s)
+    h = wl.make_h(s)
+    d = oracle.dispatch(idx, E, -1)
+    ref = oracle.expert_rows(h.reshape(-1, ds), idx, pk, d["perm"], s.Na, w["W1"], w["b1"], w["W2"], w["b2"])
+    cfg = B.config_of(s)
+    wd = B.pack(cfg, B.weights_to_device(w, s.dtype))
+
+    def dev(a):
+        return torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+    y = torch.full((s.Na + 1, ds), 123.0, dtype=B.y_dtype(cfg), device="cuda:0")
+    B.slicemoe_expert_ffn(cfg, B.to_device(h, s.dtype), dev(pk.astype(np.float32).reshape(-1)), dev(d["offsets"]), dev(d["perm"]), wd, y[:-1])
+    got = y.float().cpu().numpy()
+    assert np.all(got[-1] == 123.0)   # nothing past the last row
+    err = np.abs(got[:-1] - ref).max() / rms(ref)
+    print(f"\n[width {ds} He {He}] max|err|/rms={err:.3e}")
+    assert err <= TOL_BF16
