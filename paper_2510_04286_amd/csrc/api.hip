@@ -272,13 +272,15 @@ static slicemoe_status make_route_variant(const slicemoe_route_train_params *tp,
     v->inv_tau = 1.f / tp->temperature;
     v->sigma = tp->noise_std;
     v->noise = noise;
+    v->rate = tp->dropout_rate;
+    v->drop_u = drop_u;
     v->cap_alpha = tp->capacity_alpha;
     return SLICEMOE_OK;
 }
 
 static slicemoe_status route_common(const slicemoe_config *cfg, const void *h, const slicemoe_weights *w,
-                                    const RouteVariant &v, const float *drop_u, float rate, int32_t *topk_idx,
-                                    float *topk_p, void *workspace, size_t workspace_bytes, hipStream_t s)
+                                    const RouteVariant &v, int32_t *topk_idx, float *topk_p, void *workspace,
+                                    size_t workspace_bytes, hipStream_t s)
 {
     if (!w || !topk_idx || !topk_p || (!h && cfg->T > 0)) return SLICEMOE_ERR_INVALID_ARG;
     if (misaligned(h, 16)) return SLICEMOE_ERR_INVALID_ARG;
@@ -292,7 +294,6 @@ static slicemoe_status route_common(const slicemoe_config *cfg, const void *h, c
         if (!logical_weights_ok(*w, true, false)) return SLICEMOE_ERR_INVALID_ARG;
         e = launch_route_generic(*cfg, h, *w, topk_idx, topk_p, s, v);
     }
-    if (e == hipSuccess && rate > 0.f) e = launch_route_dropout(*cfg, topk_p, drop_u, rate, s);
     return e == hipSuccess ? SLICEMOE_OK : SLICEMOE_ERR_HIP;
 }
 
@@ -302,8 +303,7 @@ slicemoe_status slicemoe_route(const slicemoe_config *cfg, const void *h, const 
 {
     const slicemoe_status st = validate(cfg);
     if (st != SLICEMOE_OK) return st;
-    return route_common(cfg, h, w, RouteVariant(), nullptr, 0.f, topk_idx, topk_p, workspace, workspace_bytes,
-                        (hipStream_t)stream);
+    return route_common(cfg, h, w, RouteVariant(), topk_idx, topk_p, workspace, workspace_bytes, (hipStream_t)stream);
 }
 
 slicemoe_status slicemoe_route_train(const slicemoe_config *cfg, const void *h, const slicemoe_weights *w,
@@ -316,8 +316,7 @@ slicemoe_status slicemoe_route_train(const slicemoe_config *cfg, const void *h, 
     RouteVariant v;
     const slicemoe_status vs = make_route_variant(params, noise, drop_u, &v);
     if (vs != SLICEMOE_OK) return vs;
-    return route_common(cfg, h, w, v, drop_u, params->dropout_rate, topk_idx, topk_p, workspace, workspace_bytes,
-                        (hipStream_t)stream);
+    return route_common(cfg, h, w, v, topk_idx, topk_p, workspace, workspace_bytes, (hipStream_t)stream);
 }
 
 slicemoe_status slicemoe_dispatch(const slicemoe_config *cfg, const int32_t *topk_idx, int32_t *counts_raw,
@@ -389,8 +388,8 @@ slicemoe_status slicemoe_load_stats(const slicemoe_config *cfg, const int32_t *c
 }
 
 static slicemoe_status forward_common(const slicemoe_config *cfg, const void *h, const slicemoe_weights *w,
-                                      const RouteVariant &v, const float *drop_u, float rate, void *h_out,
-                                      void *workspace, size_t workspace_bytes, slicemoe_stream_t stream)
+                                      const RouteVariant &v, void *h_out, void *workspace, size_t workspace_bytes,
+                                      slicemoe_stream_t stream)
 {
     if (!w || ((!h || !h_out) && cfg->T > 0)) return SLICEMOE_ERR_INVALID_ARG;
     if (misaligned(h, 16) || misaligned(h_out, 16)) return SLICEMOE_ERR_INVALID_ARG;
@@ -423,10 +422,6 @@ static slicemoe_status forward_common(const slicemoe_config *cfg, const void *h,
     hipError_t e = mfma ? launch_route_mfma(*cfg, h, packed, idx, p, s, v, hist_chunk > 0 ? table : nullptr)
                         : launch_route_generic(*cfg, h, *w, idx, p, s, v);
     if (e != hipSuccess) return SLICEMOE_ERR_HIP;
-    if (rate > 0.f) {
-        e = launch_route_dropout(*cfg, p, drop_u, rate, s);
-        if (e != hipSuccess) return SLICEMOE_ERR_HIP;
-    }
     // the load statistics ride along in the scan kernel of the dispatch
     e = launch_dispatch(*cfg, idx, counts_raw, counts, offsets, perm, inv, table, stats, s, hist_chunk);
     if (e != hipSuccess) return SLICEMOE_ERR_HIP;
@@ -442,7 +437,7 @@ slicemoe_status slicemoe_forward(const slicemoe_config *cfg, const void *h, cons
 {
     const slicemoe_status st = validate(cfg);
     if (st != SLICEMOE_OK) return st;
-    return forward_common(cfg, h, w, RouteVariant(), nullptr, 0.f, h_out, workspace, workspace_bytes, stream);
+    return forward_common(cfg, h, w, RouteVariant(), h_out, workspace, workspace_bytes, stream);
 }
 
 slicemoe_status slicemoe_forward_train(const slicemoe_config *cfg, const void *h, const slicemoe_weights *w,
@@ -455,7 +450,7 @@ slicemoe_status slicemoe_forward_train(const slicemoe_config *cfg, const void *h
     RouteVariant v;
     const slicemoe_status vs = make_route_variant(params, noise, drop_u, &v);
     if (vs != SLICEMOE_OK) return vs;
-    return forward_common(cfg, h, w, v, drop_u, params->dropout_rate, h_out, workspace, workspace_bytes, stream);
+    return forward_common(cfg, h, w, v, h_out, workspace, workspace_bytes, stream);
 }
 
 int slicemoe_backward_uses_mfma(const slicemoe_config *cfg)

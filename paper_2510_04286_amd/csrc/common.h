@@ -36,6 +36,27 @@ template <> struct Storage<bf16_t> {
 
 __host__ __device__ __forceinline__ size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
+// Cross-slice dropout (Section 3.3) of a slice's k selected probabilities, in place: assignment j is dropped when its uniform draw
+// is below the rate; the probabilities that remain are divided by their sum; a slice that would lose all of them keeps its first.
+__device__ __forceinline__ void drop_assignments(float *p, const float *u, int k, float rate)
+{
+    float v[8];
+    bool keep[8], any = false;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        v[j] = j < k ? p[j] : 0.f;
+        keep[j] = j < k && !(u[j < k ? j : 0] < rate);
+        any = any || keep[j];
+    }
+    if (!any) keep[0] = true;
+    float sum = 0.f;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) sum += keep[j] ? v[j] : 0.f;
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+        if (j < k) p[j] = keep[j] ? v[j] / sum : 0.f;
+}
+
 // Block-wide copy of n_pieces 16-byte pieces from global memory to LDS through registers, in rounds of
 // ROUND (4 or 8) pieces per thread: the loads of a round are all in flight before its first LDS write, so
 // a round costs one memory round trip.  (The direct global->LDS path moves only 16 bytes per cycle and CU.)
@@ -117,6 +138,9 @@ struct RouteVariant {
     float inv_tau = 1.f;             // softmax of g / tau
     float sigma = 0.f;               // g += sigma * noise[n, e] before the selection and the softmax
     const float *noise = nullptr;    // [Ns, E] standard-normal draws; read only when sigma > 0
+    float rate = 0.f;                // forward only: cross-slice dropout (Section 3.3) of the selected probabilities
+    const float *drop_u = nullptr;   // [Ns, k] its uniform draws; read only when rate > 0
+    bool train() const { return sigma > 0.f || rate > 0.f; }
     // backward only: weight of the capacity loss's differentiable reading (0: none), and, once the backward has
     // computed it, the device table [E] of its derivatives with respect to each expert's probability sum
     float cap_alpha = 0.f;
@@ -175,8 +199,6 @@ hipError_t launch_backward(const slicemoe_config &c, const void *h, const slicem
                            const float *drop_u, float rate, const int32_t *idx, const float *pk, const int32_t *offsets,
                            const int32_t *perm, const int32_t *inv, const void *d_out, void *d_h,
                            const slicemoe_weight_grads &g, void *workspace, hipStream_t s);
-// Cross-slice dropout (Section 3.3) on the selected probabilities p[Ns, k], in place.
-hipError_t launch_route_dropout(const slicemoe_config &c, float *p, const float *drop_u, float rate, hipStream_t s);
 hipError_t launch_dispatch(const slicemoe_config &c, const int32_t *idx, int32_t *counts_raw,
                            int32_t *counts, int32_t *offsets, int32_t *perm, int32_t *inv,
                            int32_t *table, float *stats /* nullable */, hipStream_t s,

@@ -20,7 +20,8 @@ template <typename T, bool W2LDS>
 __global__ __launch_bounds__(kGenThreads) void route_generic_kernel(
     const T *__restrict__ x, long long Ns, int ds, int Hr, int E, int k,
     const T *__restrict__ Wr1, const T *__restrict__ br1, const T *__restrict__ Wr2, const T *__restrict__ br2,
-    const float *__restrict__ noise, float sigma, float inv_tau, int32_t *__restrict__ idx, float *__restrict__ pk)
+    const float *__restrict__ noise, float sigma, float inv_tau, const float *__restrict__ drop_u /* may be null */, float rate,
+    int32_t *__restrict__ idx, float *pk)
 {
     extern __shared__ __align__(16) float smem[];
     const int dsp = (ds + 3) & ~3, ust = Hr + 1;   // row strides: whole quads of features; hidden units of neighbouring slices in different banks
@@ -110,6 +111,7 @@ __global__ __launch_bounds__(kGenThreads) void route_generic_kernel(
         if (best == l) v0 = -INFINITY;
         if (best == l + 32) v1 = -INFINITY;
     }
+    if (drop_u != nullptr && l == 0 && r < rows) drop_assignments(pk + n * k, drop_u + n * k, k, rate);   // (this lane has written them)
 }
 
 // Expert FFN of Section 3.1 on stacked rows with the Eq. 1 input weighting and the gather fused:
@@ -253,7 +255,8 @@ static void run_route_generic(const slicemoe_config &c, const void *h, const sli
     const bool w2lds = w2 <= kW2LdsBytes && smem + w2 <= 64 * 1024;
     auto kern = w2lds ? route_generic_kernel<T, true> : route_generic_kernel<T, false>;
     kern<<<blocks, kGenThreads, smem + (w2lds ? w2 : 0), s>>>((const T *)h, Ns, ds, c.Hr, c.E, c.k, (const T *)w.Wr1, (const T *)w.br1,
-                                                              (const T *)w.Wr2, (const T *)w.br2, noise, v.sigma, v.inv_tau, idx, p);
+                                                              (const T *)w.Wr2, (const T *)w.br2, noise, v.sigma, v.inv_tau,
+                                                              v.rate > 0.f ? v.drop_u : nullptr, v.rate, idx, p);
 }
 
 hipError_t launch_route_generic(const slicemoe_config &c, const void *h, const slicemoe_weights &w,
@@ -262,44 +265,6 @@ hipError_t launch_route_generic(const slicemoe_config &c, const void *h, const s
     if ((long long)c.T * c.S == 0) return hipSuccess;
     if (c.dtype == SLICEMOE_BF16) run_route_generic<bf16_t>(c, h, w, idx, p, s, v);
     else run_route_generic<float>(c, h, w, idx, p, s, v);
-    return hipGetLastError();
-}
-
-// Cross-slice dropout (Section 3.3): assignment j of a slice is dropped when its uniform draw is below the rate; the
-// remaining probabilities are renormalised to sum to 1, the dropped ones are 0.  A slice whose draws would drop all k
-// keeps slot 0.  One thread per slice; k <= 8.
-__global__ __launch_bounds__(256) void route_dropout_kernel(float *__restrict__ pk, const float *__restrict__ drop_u,
-                                                            long long Ns, int k, float rate)
-{
-    const long long n = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= Ns) return;
-    float p[8];
-    bool keep[8];
-    int kept = 0;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        p[j] = 0.f;
-        keep[j] = false;
-        if (j < k) {
-            p[j] = pk[n * k + j];
-            keep[j] = !(drop_u[n * k + j] < rate);
-            kept += keep[j] ? 1 : 0;
-        }
-    }
-    if (kept == 0) keep[0] = true;
-    float sum = 0.f;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) sum += keep[j] ? p[j] : 0.f;
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-        if (j < k) pk[n * k + j] = keep[j] ? p[j] / sum : 0.f;
-}
-
-hipError_t launch_route_dropout(const slicemoe_config &c, float *p, const float *drop_u, float rate, hipStream_t s)
-{
-    const long long Ns = (long long)c.T * c.S;
-    if (Ns == 0 || !(rate > 0.f)) return hipSuccess;
-    route_dropout_kernel<<<(int)((Ns + 255) / 256), 256, 0, s>>>(p, drop_u, Ns, c.k, rate);
     return hipGetLastError();
 }
 

@@ -63,12 +63,21 @@ __device__ __forceinline__ f32x16 load_bias_tile(const float *__restrict__ b, in
 }
 
 // What follows the second layer, for one slice per lane pair (j, j + 32) and v[16 et + r] the logit of expert
-// 32 et + acc_feature(r, g): logit noise, softmax, top-k, and the selections added to the LDS table counts[64].
-template <int ET>
+// 32 et + acc_feature(r, g): logit noise, softmax, top-k, and the selections added to the LDS table counts[64].  TRAIN: with the
+// noise, and the cross-slice dropout of the selected probabilities (a launch of its own took 2 to 4 us of every training step);
+// instances without them, because the unused branches and arguments cost the inference router 0.6 us of 22.
+template <int ET, bool TRAIN>
 __device__ __forceinline__ void select_experts(float (&v)[ET * 16], long long n, bool valid, int g, int E, int k,
-                                               const float *__restrict__ noise, float sigma, float exp_scale,
-                                               int32_t *__restrict__ idx, float *__restrict__ pk, bool count, int *counts)
+                                               const float *__restrict__ noise_, float sigma, float exp_scale,
+                                               const float *__restrict__ drop_u_, float rate, int32_t *__restrict__ idx,
+                                               float *pk, bool count, int *counts)
 {
+    const float *noise = TRAIN ? noise_ : nullptr, *drop_u = TRAIN ? drop_u_ : nullptr;
+    float u2[2] = {1.f, 1.f};   // the dropout's draws of a slice with two experts: requested ahead of the softmax
+    if (drop_u != nullptr && k == 2 && valid && g == 0) {
+        u2[0] = drop_u[n * 2];
+        u2[1] = drop_u[n * 2 + 1];
+    }
     if (noise != nullptr) {   // training-time logit noise: g += sigma * draw, before the selection and the softmax
         const float *nr = noise + (valid ? n : 0) * E;
         if ((E & 3) == 0) {   // rows of the table are 16-byte aligned: this lane's four consecutive experts at once
@@ -155,8 +164,10 @@ __device__ __forceinline__ void select_experts(float (&v)[ET * 16], long long n,
         if (valid && g == 0) {
             idx[n * 2] = ia;
             idx[n * 2 + 1] = ib;
-            pk[n * 2] = __builtin_amdgcn_exp2f(fmaf(m, kLog2e, nm)) * rden;
-            pk[n * 2 + 1] = __builtin_amdgcn_exp2f(fmaf(second, kLog2e, nm)) * rden;
+            float p2[2] = {__builtin_amdgcn_exp2f(fmaf(m, kLog2e, nm)) * rden, __builtin_amdgcn_exp2f(fmaf(second, kLog2e, nm)) * rden};
+            if (drop_u != nullptr) drop_assignments(p2, u2, 2, rate);
+            pk[n * 2] = p2[0];
+            pk[n * 2 + 1] = p2[1];
             if (count) {
                 atomicAdd(&counts[ia], 1);
                 atomicAdd(&counts[ib], 1);
@@ -193,6 +204,7 @@ __device__ __forceinline__ void select_experts(float (&v)[ET * 16], long long n,
             if (count) atomicAdd(&counts[be], 1);
         }
     }
+    if (drop_u != nullptr && !picked && valid && g == 0) drop_assignments(pk + n * k, drop_u + n * k, k, rate);   // (this lane has written them)
 }
 
 // One block per CU shares one LDS copy of the router, with as many wavefronts as the registers allow: a wavefront's
@@ -203,11 +215,11 @@ __device__ __forceinline__ void select_experts(float (&v)[ET * 16], long long n,
 // matrix instruction is followed by one pair's vector work of another stage -- 28.4 and 29.0 us against 27.8.)
 // W1_LDS = false (slice width 384, whose first layer of 192 KiB exceeds the LDS): the first-layer fragments are read
 // from memory as they are used; only the second layer and the biases are staged.
-template <int DS, int ET, int THREADS, bool W1_LDS>
+template <int DS, int ET, int THREADS, bool W1_LDS, bool TRAIN>
 __global__ __launch_bounds__(THREADS) void route_mfma_kernel(
     const bf16_t *__restrict__ x, long long Ns, int E, int k, const char *__restrict__ packed,
     size_t off_w1, size_t off_b1, size_t off_b2, const float *__restrict__ noise, float sigma, float exp_scale,
-    int32_t *__restrict__ idx, float *__restrict__ pk, void *__restrict__ hist /* may be null */, int hist_stride,
+    const float *__restrict__ drop_u, float rate, int32_t *__restrict__ idx, float *__restrict__ pk, void *__restrict__ hist /* may be null */, int hist_stride,
     int hist_rounds, bool hist_narrow)
 {
     constexpr int KS = SliceTiles<DS>::KS;
@@ -311,7 +323,7 @@ __global__ __launch_bounds__(THREADS) void route_mfma_kernel(
         for (int et = 0; et < ET; ++et)
 #pragma unroll
             for (int r = 0; r < 16; ++r) v[et * 16 + r] = gacc[et][r];
-        select_experts<ET>(v, n, valid, g, E, k, noise, sigma, exp_scale, idx, pk, hist != nullptr, hcnt + round * 64);
+        select_experts<ET, TRAIN>(v, n, valid, g, E, k, noise, sigma, exp_scale, drop_u, rate, idx, pk, hist != nullptr, hcnt + round * 64);
         if (hist != nullptr) {
             // The LDS executes a wavefront's operations in order, so this wavefront's additions above are in the table
             // before its ticket; the wavefront that draws the last ticket of the chunk therefore sees everybody's.
@@ -353,11 +365,11 @@ template <int DS, int ET> struct SplitTile {
     static constexpr size_t off_cnt = off_w2 + (W2_LDS ? (size_t)ET * kRouteHT * 2048 : 0);
     static constexpr size_t lds = off_cnt + 64 * 4;
 };
-template <int DS, int ET>
+template <int DS, int ET, bool TRAIN>
 __global__ __launch_bounds__(kSplitThreads) void route_split_kernel(
     const bf16_t *__restrict__ x, long long Ns, int E, int k, const char *__restrict__ packed, size_t off_w1, size_t off_w2,
-    size_t off_b1, size_t off_b2, const float *__restrict__ noise, float sigma, float exp_scale, int tiles,
-    int32_t *__restrict__ idx, float *__restrict__ pk, uint16_t *__restrict__ hist /* may be null */, int hist_stride)
+    size_t off_b1, size_t off_b2, const float *__restrict__ noise, float sigma, float exp_scale,
+    const float *__restrict__ drop_u, float rate, int tiles, int32_t *__restrict__ idx, float *__restrict__ pk, uint16_t *__restrict__ hist /* may be null */, int hist_stride)
 {
     typedef SplitTile<DS, ET> G;
     constexpr int KS = SliceTiles<DS>::KS, NB = G::NB;
@@ -452,7 +464,7 @@ __global__ __launch_bounds__(kSplitThreads) void route_split_kernel(
 #pragma unroll
             for (int r = 0; r < 16; ++r) v[et * 16 + r] = gacc[et][r];
         const long long n = (long long)(tile0 + ht) * 32 + j;
-        select_experts<ET>(v, n, n < Ns, g, E, k, noise, sigma, exp_scale, idx, pk, hist != nullptr, hcnt);
+        select_experts<ET, TRAIN>(v, n, n < Ns, g, E, k, noise, sigma, exp_scale, drop_u, rate, idx, pk, hist != nullptr, hcnt);
     }
     if (hist != nullptr) {
         __syncthreads();
@@ -529,12 +541,13 @@ static hipError_t run_split(const slicemoe_config &c, const PackedLayout &L, con
         if (g.nchunks != blocks || !g.fused || route_mfma_hist_chunk(c) != g.chunk) return hipErrorInvalidValue;
         hist_stride = g.stride;
     }
-    auto kern = route_split_kernel<DS, ET>;
+    auto kern = v.train() ? route_split_kernel<DS, ET, true> : route_split_kernel<DS, ET, false>;
     const hipError_t err = grant_dynamic_lds((const void *)kern, SplitTile<DS, ET>::lds);
     if (err != hipSuccess) return err;
     kern<<<blocks, kSplitThreads, SplitTile<DS, ET>::lds, s>>>((const bf16_t *)h, Ns, c.E, c.k, (const char *)packed, L.r_w1, L.r_w2, L.r_b1,
                                                                L.r_b2, v.sigma > 0.f ? v.noise : nullptr, v.sigma,
-                                                               1.4426950408889634f * v.inv_tau, tiles, idx, p, (uint16_t *)hist, hist_stride);
+                                                               1.4426950408889634f * v.inv_tau, v.rate > 0.f ? v.drop_u : nullptr, v.rate, tiles,
+                                                               idx, p, (uint16_t *)hist, hist_stride);
     return hipGetLastError();
 }
 
@@ -565,13 +578,13 @@ static hipError_t run_route(const slicemoe_config &c, const void *h, const void 
     }
     const size_t lds = (size_t)((W1_LDS ? kRouteHT * KS * 64 : 0) + ET * kRouteHT * 2 * 64) * 16 + (kRouteHr + ET * 32) * 4 +
                        (size_t)hist_rounds * 65 * 4;
-    auto kern = route_mfma_kernel<DS, ET, THREADS, W1_LDS>;
+    auto kern = v.train() ? route_mfma_kernel<DS, ET, THREADS, W1_LDS, true> : route_mfma_kernel<DS, ET, THREADS, W1_LDS, false>;
     hipError_t err = grant_dynamic_lds((const void *)kern, lds);
     if (err != hipSuccess) return err;
     if (L.r_w2 != L.r_w1 + (size_t)kRouteHT * KS * 64 * 16) return hipErrorInvalidValue;   // the kernel copies W1 | W2 as one run
     kern<<<(int)blocks, THREADS, lds, s>>>((const bf16_t *)h, Ns, c.E, c.k, (const char *)packed, L.r_w1, L.r_b1, L.r_b2,
-                                           v.sigma > 0.f ? v.noise : nullptr, v.sigma, 1.4426950408889634f * v.inv_tau, idx, p,
-                                           hist, hist_stride, hist_rounds, hist_narrow);
+                                           v.sigma > 0.f ? v.noise : nullptr, v.sigma, 1.4426950408889634f * v.inv_tau,
+                                           v.rate > 0.f ? v.drop_u : nullptr, v.rate, idx, p, hist, hist_stride, hist_rounds, hist_narrow);
     return hipGetLastError();
 }
 
