@@ -1,5 +1,6 @@
 // Matrix-core backward of the router and assembly of dL/dh, for the forward's matrix-core slice widths except 384,
-// Hr = 256 and up to 64 experts.  Same mathematics as bwd_router_generic_kernel in backward_generic.hip; three kernels:
+// Hr = 256 and up to 64 experts.  Same mathematics as bwd_router_generic_kernel in backward_generic.hip; three kernels, the first two in one
+// (bwd_route_slices_mfma_kernel) where the LDS holds the fragments of both: widths 24, 48 and 64, and 96 with up to 32 experts:
 //
 //   bwd_route_logits_mfma_kernel   the forward router's layout: a lane owns one slice of a 32-slice tile.  Recomputes the
 //       router: the hidden layer exactly as the forward does (bf16 MFMA with the bias preloaded: the same ReLU pattern), the
@@ -9,8 +10,7 @@
 //       logits).  Writes dL/dg as bf16 tables, one per term, and the ReLU pattern, one bit per hidden unit.
 //   bwd_route_inputs_mfma_kernel   same layout: dL/du = Wr2 dL/dg with dL/dg read back in accumulator order, i.e. as
 //       the B operand, masked by the ReLU bits, then dL/dx += Wr1 dL/du chained from registers.  Writes
-//       dL/dh = that + the k expert-path rows of the slice (one bf16 rounding).  It is a kernel of its own because the
-//       fragments of the two halves do not fit in LDS together at width 128 or with 64 experts.
+//       dL/dh = that + the k expert-path rows of the slice (one bf16 rounding).
 //   bwd_route_weights_mfma_kernel  the transposed layout (see backward_weights_mfma.hip): one wavefront per hidden tile walks
 //       the slices of its block.  Stores its pieces into the block's slot of partial sums.
 //
@@ -58,6 +58,396 @@ static RouterBwdPacked router_bwd_layout(int ds, int ET)
     return L;
 }
 
+// ------------------------------------------------------------------------------------------ stages of the slice kernels
+// ReLU of a hidden pre-activation, at most twice the largest fp16 value (what the two fp16 terms of the hidden layer can hold): a median
+// takes its operands as they are, where a maximum would first spend an instruction on quieting one.  0 for NaN.
+__device__ __forceinline__ float relu_capped(float a) { return __builtin_amdgcn_fmed3f(a, 0.f, 131008.f); }
+// The ReLU pattern of 32 hidden units in one word, the first unit in the top bit: shifted up by one with the bit of a unit below
+// (r >= 0 is above zero exactly if adding 2^31 - 1 to its bit pattern reaches the sign bit).
+__device__ __forceinline__ uint32_t push_active(uint32_t bits, float r)
+{
+    return __builtin_amdgcn_alignbit(bits, (uint32_t)__float_as_int(r) + 0x7fffffffu, 31);
+}
+// Two-term fp16 split of a pair of hidden activations: the round-toward-zero conversion of the pair, and per activation one
+// mixed-precision multiply-add r - u0 rounded to fp16.
+__device__ __forceinline__ void split_pair_f16(float r0, float r1, uint32_t &u0, uint32_t &u1)
+{
+    u0 = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(r0, r1));
+    asm("v_fma_mixlo_f16 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(u1) : "v"(u0), "v"(r0));
+    asm("v_fma_mixhi_f16 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "+v"(u1) : "v"(u0), "v"(r1));
+}
+
+// The forward router for one slice per lane pair: logits in accumulator order, and which hidden units are active (word w: hidden tiles
+// 2w and 2w + 1, accumulator order).  w1f [8][KS][64], w2f [8][2][ET][64], b1s [256], b2s [32 ET].
+template <int DS, int ET>
+__device__ __forceinline__ void router_logits(const bf16x8 (&xb)[SliceTiles<DS>::KS], const uint4 *w1f, const uint4 *w2f, const float *b1s,
+                                              const float *b2s, int lane, int g, f32x16 (&gacc)[ET], uint32_t (&act)[4])
+{
+    constexpr int KS = SliceTiles<DS>::KS, TERMS = kRbTerms<DS>;
+#pragma unroll
+    for (int et = 0; et < ET; ++et)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const f32x4 b = *(const f32x4 *)(b2s + et * 32 + 8 * q + 4 * g);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) gacc[et][4 * q + c] = b[c];
+        }
+    act[0] = act[1] = act[2] = act[3] = 0;
+#pragma unroll 1
+    for (int hp = 0; hp < kRbHT; hp += 2) {
+        uint32_t bits = 0;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int ht = hp + h;
+            f32x16 acc;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const f32x4 b = *(const f32x4 *)(b1s + ht * 32 + 8 * q + 4 * g);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) acc[4 * q + c] = b[c];
+            }
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) acc = mfma_bf16(__builtin_bit_cast(bf16x8, w1f[(ht * KS + ks) * 64 + lane]), xb[ks], acc);
+            if constexpr (TERMS == 3) {   // the hidden layer whole, against the bf16 weights as they are
+                uint32_t ut[2][TERMS][4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float u[4] = {fmaxf(acc[4 * q], 0.f), fmaxf(acc[4 * q + 1], 0.f), fmaxf(acc[4 * q + 2], 0.f), fmaxf(acc[4 * q + 3], 0.f)};
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) bits = push_active(bits, u[c]);
+                    split_terms<TERMS>(u, ut[q >> 1], 2 * (q & 1));
+                }
+#pragma unroll
+                for (int s = 0; s < 2; ++s)
+#pragma unroll
+                    for (int et = 0; et < ET; ++et) {
+                        const bf16x8 a2 = __builtin_bit_cast(bf16x8, w2f[((ht * 2 + s) * ET + et) * 64 + lane]);
+#pragma unroll
+                        for (int t = TERMS - 1; t >= 0; --t)   // small terms first
+                            gacc[et] = mfma_bf16(a2, __builtin_bit_cast(bf16x8, make_uint4(ut[s][t][0], ut[s][t][1], ut[s][t][2], ut[s][t][3])), gacc[et]);
+                    }
+            } else {
+                uint32_t t0[8], t1[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const float r0 = relu_capped(acc[2 * i]), r1 = relu_capped(acc[2 * i + 1]);
+                    bits = push_active(push_active(bits, r0), r1);
+                    split_pair_f16(r0, r1, t0[i], t1[i]);
+                }
+#pragma unroll
+                for (int s = 0; s < 2; ++s) {
+                    const r_f16x8 u0 = __builtin_bit_cast(r_f16x8, make_uint4(t0[4 * s], t0[4 * s + 1], t0[4 * s + 2], t0[4 * s + 3]));
+                    const r_f16x8 u1 = __builtin_bit_cast(r_f16x8, make_uint4(t1[4 * s], t1[4 * s + 1], t1[4 * s + 2], t1[4 * s + 3]));
+#pragma unroll
+                    for (int et = 0; et < ET; ++et) {
+                        const r_f16x8 a2 = __builtin_bit_cast(r_f16x8, w2f[((ht * 2 + s) * ET + et) * 64 + lane]);
+                        gacc[et] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a2, u1, gacc[et], 0, 0, 0);   // small term first
+                        gacc[et] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a2, u0, gacc[et], 0, 0, 0);
+                    }
+                }
+            }
+        }
+        act[0] = act[1];   // (the words move up: after four pairs the first is in front)
+        act[1] = act[2];
+        act[2] = act[3];
+        act[3] = bits;
+    }
+}
+
+// What a slice's gradient needs from memory beside its row (both lanes of a slice hold the same selections), requested ahead: of its first
+// two assignments (further ones are fetched where they are used).
+constexpr int kRbAhead = 2;
+template <int ET> struct SliceDraws {
+    float noise[ET * 16];                 // of this lane's experts
+    int e[kRbAhead], row[kRbAhead];       // the selected experts, their stacked rows (negative: dropped by the capacity limit)
+    float dp[kRbAhead], u[kRbAhead];      // dL/dp, the dropout's draws
+};
+template <int ET>
+__device__ __forceinline__ void load_draws(SliceDraws<ET> &D, long long n, int g, int E, int k, const float *__restrict__ noise,
+                                           const float *__restrict__ drop_u, const int32_t *__restrict__ idx, const int32_t *__restrict__ inv,
+                                           const float *__restrict__ dpk)
+{
+    asm volatile("" : "+v"(g));   // the addresses are formed here, not kept in registers from tile to tile
+    if (noise != nullptr) {
+        const float *nr = noise + n * E;
+        if ((E & 3) == 0) {   // rows of the table are 16-byte aligned: this lane's four consecutive experts at once
+#pragma unroll
+            for (int q = 0; q < ET * 4; ++q) {
+                const int e0 = (q >> 2) * 32 + 8 * (q & 3) + 4 * g;
+                const f32x4 z = *(const f32x4 *)(nr + (e0 < E ? e0 : 0));
+#pragma unroll
+                for (int c = 0; c < 4; ++c) D.noise[4 * q + c] = z[c];
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < ET * 16; ++i) D.noise[i] = nr[min((i >> 4) * 32 + acc_feature(i & 15, g), E - 1)];
+        }
+    }
+#pragma unroll
+    for (int jj = 0; jj < kRbAhead; ++jj)
+        if (jj < k) {
+            const long long a = n * k + jj;
+            D.e[jj] = idx[a];
+            D.row[jj] = inv[a];
+            D.dp[jj] = dpk[a];
+            if (drop_u != nullptr) D.u[jj] = drop_u[a];
+        }
+}
+
+// dL/dg of one slice per lane pair from its logits gacc: noise; softmax with the temperature; the selected probabilities, back through
+// the dropout's renormalisation and the softmax.  As bf16 pairs in accumulator order, by term.
+template <int ET, int TERMS>
+__device__ __forceinline__ void logit_gradients(const f32x16 (&gacc)[ET], const SliceDraws<ET> &D, long long n, int g, int E, int k, bool noisy,
+                                                float sigma, float inv_tau, const float *__restrict__ drop_u, float rate,
+                                                const int32_t *__restrict__ idx, const int32_t *__restrict__ inv, const float *__restrict__ dpk,
+                                                const float *__restrict__ capg, uint32_t (&dgt)[ET][TERMS][8])
+{
+    // ---- this lane's 16 ET logits: expert 32 et + acc_feature(r, g); noise; softmax of g / tau over the E experts
+    float v[ET * 16];
+#pragma unroll
+    for (int i = 0; i < ET * 16; ++i) {
+        const int e = (i >> 4) * 32 + acc_feature(i & 15, g);
+        float t = gacc[i >> 4][i & 15];
+        if (noisy) t = fmaf(sigma, D.noise[i], t);
+        v[i] = e < E ? t : -INFINITY;
+    }
+    float m = v[0];
+#pragma unroll
+    for (int i = 1; i < ET * 16; ++i) m = fmaxf(m, v[i]);
+    m = fmaxf(m, __shfl_xor(m, 32));
+    const float sc = 1.4426950408889634f * inv_tau, nm = -m * sc;
+    float den = 0.f;
+#pragma unroll
+    for (int i = 0; i < ET * 16; ++i) {
+        v[i] = TERMS == 3 ? expf((v[i] - m) * inv_tau) : __builtin_amdgcn_exp2f(fmaf(v[i], sc, nm));
+        den += v[i];
+    }
+    den += __shfl_xor(den, 32);
+    const float rden = 1.f / den;
+#pragma unroll
+    for (int i = 0; i < ET * 16; ++i) v[i] *= rden;   // probability of every expert of this lane's half
+
+    // ---- the k selections: probability, upstream gradient, dropout flag (both lanes of a slice do the same)
+    float psel[8], dpf[8];
+    bool keep[8];
+    int ej[8];
+    int kept = 0;
+#pragma unroll
+    for (int jj = 0; jj < 8; ++jj) {
+        psel[jj] = dpf[jj] = 0.f;
+        keep[jj] = false;
+        ej[jj] = -1;
+        if (jj < k) {
+            const long long a = n * k + jj;
+            ej[jj] = jj < kRbAhead ? D.e[jj < kRbAhead ? jj : 0] : idx[a];
+            float mine = 0.f;
+#pragma unroll
+            for (int i = 0; i < ET * 16; ++i) mine = (i >> 4) * 32 + acc_feature(i & 15, g) == ej[jj] ? v[i] : mine;
+            psel[jj] = mine + __shfl_xor(mine, 32);     // the expert sits in one of the two halves
+            if (jj < kRbAhead) dpf[jj] = D.row[jj < kRbAhead ? jj : 0] >= 0 ? D.dp[jj < kRbAhead ? jj : 0] : 0.f;
+            else dpf[jj] = inv[a] >= 0 ? dpk[a] : 0.f;  // a capacity-dropped assignment carries no gradient from h'
+            if (capg != nullptr) dpf[jj] += capg[min(max(ej[jj], 0), E - 1)];   // but it counts as assigned (capacity loss)
+            keep[jj] = drop_u != nullptr ? !((jj < kRbAhead ? D.u[jj < kRbAhead ? jj : 0] : drop_u[a]) < rate) : true;
+            kept += keep[jj] ? 1 : 0;
+        }
+    }
+    if (drop_u != nullptr) {
+        if (kept == 0) keep[0] = true;
+        float ssum = 0.f, dot = 0.f;
+#pragma unroll
+        for (int jj = 0; jj < 8; ++jj) ssum += keep[jj] ? psel[jj] : 0.f;
+#pragma unroll
+        for (int jj = 0; jj < 8; ++jj) dot += keep[jj] ? dpf[jj] * (psel[jj] / ssum) : 0.f;
+#pragma unroll
+        for (int jj = 0; jj < 8; ++jj) dpf[jj] = keep[jj] ? (dpf[jj] - dot) / ssum : 0.f;
+    }
+    // dL/dg_e = (1/tau) (sum_j c_j [e = e_j] - p_e sum_j c_j),  c_j = dL/dp_j p_j
+    float csum = 0.f;
+#pragma unroll
+    for (int jj = 0; jj < 8; ++jj) {
+        dpf[jj] = jj < k ? dpf[jj] * psel[jj] : 0.f;
+        csum += dpf[jj];
+    }
+#pragma unroll
+    for (int i = 0; i < ET * 16; ++i) v[i] = -v[i] * csum;
+#pragma unroll
+    for (int jj = 0; jj < 8; ++jj)
+        if (jj < k) {
+#pragma unroll
+            for (int i = 0; i < ET * 16; ++i) v[i] += (i >> 4) * 32 + acc_feature(i & 15, g) == ej[jj] ? dpf[jj] : 0.f;
+        }
+#pragma unroll
+    for (int et = 0; et < ET; ++et)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {   // experts 32 et + 8q + 4g .. + 3 of this slice: four bf16 values per term
+            float dg[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) dg[c] = v[et * 16 + 4 * q + c] * inv_tau;
+            uint32_t dt[TERMS][4];
+            split_terms<TERMS>(dg, dt, 0);
+#pragma unroll
+            for (int t = 0; t < TERMS; ++t) {
+                dgt[et][t][2 * q] = dt[t][0];
+                dgt[et][t][2 * q + 1] = dt[t][1];
+            }
+        }
+}
+
+// dL/dg of a slice in its rows of the tables.
+template <int ET, int TERMS>
+__device__ __forceinline__ void store_logit_gradients(const uint32_t (&dgt)[ET][TERMS][8], bf16_t *__restrict__ dg_terms, long long Ns, long long n, int g)
+{
+    constexpr int EP = ET * 32;
+#pragma unroll
+    for (int et = 0; et < ET; ++et)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int t = 0; t < TERMS; ++t)
+                *(uint2 *)(dg_terms + (t * Ns + n) * EP + et * 32 + 8 * q + 4 * g) = make_uint2(dgt[et][t][2 * q], dgt[et][t][2 * q + 1]);
+}
+
+// dL/du = Wr2 dL/dg (ReLU pattern applied), dL/dx += Wr1 dL/du, both from registers.  w2c [ET][2][8][64], w1c [8][2][OT][64].
+template <int DS, int ET>
+__device__ __forceinline__ void input_gradients(const uint32_t (&dgt)[ET][kRbTerms<DS>][8], const uint32_t (&act)[4], const uint4 *w2c, const uint4 *w1c,
+                                                int lane, f32x16 (&dx)[SliceTiles<DS>::OT])
+{
+    constexpr int OT = SliceTiles<DS>::OT, TERMS = kRbTerms<DS>;
+#pragma unroll
+    for (int ot = 0; ot < OT; ++ot)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) dx[ot][i] = 0.f;
+    uint32_t a0 = act[0], a1 = act[1], a2 = act[2], a3 = act[3];
+#pragma unroll 1
+    for (int hp = 0; hp < kRbHT; hp += 2) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int ht = hp + h;
+            f32x16 du;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) du[i] = 0.f;
+#pragma unroll
+            for (int et = 0; et < ET; ++et)
+#pragma unroll
+                for (int s = 0; s < 2; ++s) {
+                    const bf16x8 wf = __builtin_bit_cast(bf16x8, w2c[((et * 2 + s) * kRbHT + ht) * 64 + lane]);
+#pragma unroll
+                    for (int t = 0; t < TERMS; ++t) du = mfma_bf16(wf, frag_of(dgt[et][t], s), du);   // large terms first, see the weights kernel
+                }
+            uint32_t dut[2][TERMS][4];   // by K-step
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                float d[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c)   // the unit's bit, spread over the word, as a mask
+                    d[c] = __int_as_float(__float_as_int(du[4 * q + c]) & __builtin_amdgcn_sbfe((int)a0, 31 - 16 * h - 4 * q - c, 1));
+                split_terms<TERMS>(d, dut[q >> 1], 2 * (q & 1));
+            }
+#pragma unroll
+            for (int s = 0; s < 2; ++s)
+#pragma unroll
+                for (int ot = 0; ot < OT; ++ot) {
+                    const bf16x8 wf = __builtin_bit_cast(bf16x8, w1c[((ht * 2 + s) * OT + ot) * 64 + lane]);
+#pragma unroll
+                    for (int t = TERMS - 1; t >= 0; --t)
+                        dx[ot] = mfma_bf16(wf, __builtin_bit_cast(bf16x8, make_uint4(dut[s][t][0], dut[s][t][1], dut[s][t][2], dut[s][t][3])), dx[ot]);
+                }
+        }
+        a0 = a1;
+        a1 = a2;
+        a2 = a3;
+    }
+}
+
+// Rows of the per-wavefront staging tile are 36 floats apart: 16-byte reads at a stride of one row then fall into
+// distinct banks.
+constexpr int kRbStageRow = 36;
+
+// dL/dh of a tile's slices: router path dx plus the expert-path rows of their k assignments, one rounding.  The rows are
+// gathered and the result is stored through a tile of LDS private to the wavefront (stg), one 32-feature tile at a
+// time, so that every memory instruction covers whole 128-byte (gather) or 64-byte (store) runs: eight lanes per
+// slice fetch and add the k row pieces, lane (j, g) picks up its accumulator order from the tile, adds the router
+// path, rounds, and puts the packed row back for four lanes per slice to store.
+// A lane's part: pieces lane % 8 of the slices 8 it + lane / 8.  rows[it][jj]: their first stacked rows (negative: none), which have been
+// requested (`ahead`) unless AHEAD is 0.
+template <int DS, int AHEAD> struct RowsAhead {
+    f32x4 v[SliceTiles<DS>::OT][4][AHEAD > 0 ? AHEAD : 1];
+};
+// Without a condition, which would be a branch with a wait behind it: the caller adds it only if the row is there.
+template <int DS>
+__device__ __forceinline__ f32x4 gradient_row_piece(const float *__restrict__ dxrow, int row, int ot, int piece)
+{
+    const int c = DS % 32 == 0 || 32 * ot + 4 * piece < DS ? 32 * ot + 4 * piece : 0;
+    return *(const f32x4 *)(dxrow + (size_t)max(row, 0) * DS + c);
+}
+// The stacked rows of the first assignments of the slices whose pieces a lane handles (of others where there are none: see assemble_rows).
+__device__ __forceinline__ void slice_rows(int (&rows)[4][kRbAhead], const int32_t *__restrict__ inv, long long n0, long long Ns, int k, int lane)
+{
+#pragma unroll
+    for (int it = 0; it < 4; ++it) {
+        const long long ns = n0 + it * 8 + (lane >> 3);
+#pragma unroll
+        for (int jj = 0; jj < kRbAhead; ++jj) rows[it][jj] = inv[min(ns, Ns - 1) * k + min(jj, k - 1)];
+    }
+}
+template <int DS, int AHEAD, int SROWS = 32>
+__device__ __forceinline__ void assemble_rows(const f32x16 (&dx)[SliceTiles<DS>::OT], const int (&rows)[4][kRbAhead], const RowsAhead<DS, AHEAD> &ahead,
+                                              const float *__restrict__ dxrow, const int32_t *__restrict__ inv, int k, bf16_t *__restrict__ dh,
+                                              long long n0, long long Ns, int lane, float *stg)
+{
+    const int j = lane & 31, g = lane >> 5, piece = lane & 7, sl = lane >> 3;
+#pragma unroll
+    for (int ot = 0; ot < SliceTiles<DS>::OT; ++ot)
+#pragma unroll
+        for (int s0 = 0; s0 < 32; s0 += SROWS) {
+#pragma unroll
+            for (int it = s0 / 8; it < (s0 + SROWS) / 8; ++it) {
+                f32x4 v = {0.f, 0.f, 0.f, 0.f};
+                const long long ns = n0 + it * 8 + sl;
+#pragma unroll
+                for (int jj = 0; jj < kRbAhead; ++jj) {
+                    f32x4 t;
+                    if constexpr (AHEAD > 0) t = ahead.v[ot][it][jj];
+                    else t = gradient_row_piece<DS>(dxrow, rows[it][jj], ot, piece);
+                    const bool there = jj < k && ns < Ns && rows[it][jj] >= 0;
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) v[c] += there ? t[c] : 0.f;
+                }
+                for (int jj = kRbAhead; jj < k; ++jj) {
+                    const int row = ns < Ns ? inv[ns * k + jj] : -1;
+                    const f32x4 t = gradient_row_piece<DS>(dxrow, row, ot, piece);
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) v[c] += row >= 0 ? t[c] : 0.f;
+                }
+                *(f32x4 *)(stg + (it * 8 + sl - s0) * kRbStageRow + 4 * piece) = v;
+            }
+            wave_lds_sync();
+            uint2 o[4];
+            if (SROWS == 32 || (j & ~(SROWS - 1)) == s0) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const f32x4 t = *(const f32x4 *)(stg + (j - s0) * kRbStageRow + 8 * q + 4 * g);
+                    o[q] = make_uint2(pack_bf16x2(dx[ot][4 * q] + t[0], dx[ot][4 * q + 1] + t[1]),
+                                      pack_bf16x2(dx[ot][4 * q + 2] + t[2], dx[ot][4 * q + 3] + t[3]));
+                }
+            }
+            wave_lds_sync();   // every lane has read its sums: the tile now takes the packed rows (64 bytes per slice)
+            if (SROWS == 32 || (j & ~(SROWS - 1)) == s0) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) *(uint2 *)((char *)(stg + (j - s0) * kRbStageRow) + (8 * q + 4 * g) * 2) = o[q];
+            }
+            wave_lds_sync();
+#pragma unroll
+            for (int half = 0; half < SROWS / 16; ++half) {
+                const int i = half * 16 + (lane >> 2), pc = lane & 3;
+                const long long ns = n0 + s0 + i;
+                if (ns < Ns && (DS % 32 == 0 || 32 * ot + 8 * pc < DS))
+                    *(uint4 *)(dh + ns * DS + 32 * ot + 8 * pc) = *(const uint4 *)((const char *)(stg + i * kRbStageRow) + pc * 16);
+            }
+            wave_lds_sync();   // before the next gather overwrites the tile
+        }
+}
+
 // ------------------------------------------------------------------------------------------------ logits kernel
 // LDS: w1f | w2f | b1 | b2 (the first, second, sixth and seventh pieces of the packed buffer).
 template <int DS, int ET>
@@ -91,173 +481,20 @@ __global__ __launch_bounds__(kRbThreads) void bwd_route_logits_mfma_kernel(
         bf16x8 xb[KS];
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) xb[ks] = load_row_piece<DS>(xr, ks, g);
-
-        // ---- the forward router, remembering which hidden units are active (bit r of half ht & 1 of word ht / 2)
         f32x16 gacc[ET];
-#pragma unroll
-        for (int et = 0; et < ET; ++et)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const f32x4 b = *(const f32x4 *)(b2s + et * 32 + 8 * q + 4 * g);
-#pragma unroll
-                for (int c = 0; c < 4; ++c) gacc[et][4 * q + c] = b[c];
-            }
-        uint32_t act0 = 0, act1 = 0, act2 = 0, act3 = 0;
-#pragma unroll 1
-        for (int ht = 0; ht < kRbHT; ++ht) {
-            f32x16 acc;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const f32x4 b = *(const f32x4 *)(b1s + ht * 32 + 8 * q + 4 * g);
-#pragma unroll
-                for (int c = 0; c < 4; ++c) acc[4 * q + c] = b[c];
-            }
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks)
-                acc = mfma_bf16(__builtin_bit_cast(bf16x8, w1f[(ht * KS + ks) * 64 + lane]), xb[ks], acc);
-            uint32_t bits = 0;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) bits |= (acc[i] > 0.f ? 1u : 0u) << i;
-            bits <<= (ht & 1) * 16;
-            act0 |= (ht >> 1) == 0 ? bits : 0u;
-            act1 |= (ht >> 1) == 1 ? bits : 0u;
-            act2 |= (ht >> 1) == 2 ? bits : 0u;
-            act3 |= (ht >> 1) == 3 ? bits : 0u;
-            if constexpr (TERMS == 3) {   // the hidden layer whole, against the bf16 weights as they are
-                uint32_t ut[2][TERMS][4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const float u[4] = {fmaxf(acc[4 * q], 0.f), fmaxf(acc[4 * q + 1], 0.f), fmaxf(acc[4 * q + 2], 0.f), fmaxf(acc[4 * q + 3], 0.f)};
-                    split_terms<TERMS>(u, ut[q >> 1], 2 * (q & 1));
-                }
-#pragma unroll
-                for (int s = 0; s < 2; ++s)
-#pragma unroll
-                    for (int et = 0; et < ET; ++et) {
-                        const bf16x8 a2 = __builtin_bit_cast(bf16x8, w2f[((ht * 2 + s) * ET + et) * 64 + lane]);
-#pragma unroll
-                        for (int t = TERMS - 1; t >= 0; --t)   // small terms first
-                            gacc[et] = mfma_bf16(a2, __builtin_bit_cast(bf16x8, make_uint4(ut[s][t][0], ut[s][t][1], ut[s][t][2], ut[s][t][3])), gacc[et]);
-                    }
-            } else {
-                uint32_t t0[8], t1[8];
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const float u0 = fmaxf(acc[2 * i], 0.f), u1 = fmaxf(acc[2 * i + 1], 0.f);
-                    const r_h2 hi = __builtin_bit_cast(r_h2, __builtin_amdgcn_cvt_pkrtz(u0, u1));
-                    const float r0 = u0 - (float)hi[0], r1 = u1 - (float)hi[1];   // exact remainders
-                    t0[i] = __builtin_bit_cast(uint32_t, hi);
-                    t1[i] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(r0, r1));
-                }
-#pragma unroll
-                for (int s = 0; s < 2; ++s) {
-                    const r_f16x8 u0 = __builtin_bit_cast(r_f16x8, make_uint4(t0[4 * s], t0[4 * s + 1], t0[4 * s + 2], t0[4 * s + 3]));
-                    const r_f16x8 u1 = __builtin_bit_cast(r_f16x8, make_uint4(t1[4 * s], t1[4 * s + 1], t1[4 * s + 2], t1[4 * s + 3]));
-#pragma unroll
-                    for (int et = 0; et < ET; ++et) {
-                        const r_f16x8 a2 = __builtin_bit_cast(r_f16x8, w2f[((ht * 2 + s) * ET + et) * 64 + lane]);
-                        gacc[et] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a2, u1, gacc[et], 0, 0, 0);   // small term first
-                        gacc[et] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a2, u0, gacc[et], 0, 0, 0);
-                    }
-                }
-            }
-        }
-
-        // ---- this lane's 16 ET logits: expert 32 et + acc_feature(r, g); noise; softmax of g / tau over the E experts
-        float v[ET * 16];
-#pragma unroll
-        for (int i = 0; i < ET * 16; ++i) {
-            const int e = (i >> 4) * 32 + acc_feature(i & 15, g);
-            float t = gacc[i >> 4][i & 15];
-            if (noise != nullptr && e < E) t = fmaf(sigma, noise[nn * E + e], t);
-            v[i] = e < E ? t : -INFINITY;
-        }
-        float m = v[0];
-#pragma unroll
-        for (int i = 1; i < ET * 16; ++i) m = fmaxf(m, v[i]);
-        m = fmaxf(m, __shfl_xor(m, 32));
-        const float sc = 1.4426950408889634f * inv_tau, nm = -m * sc;
-        float den = 0.f;
-#pragma unroll
-        for (int i = 0; i < ET * 16; ++i) {
-            v[i] = TERMS == 3 ? expf((v[i] - m) * inv_tau) : __builtin_amdgcn_exp2f(fmaf(v[i], sc, nm));
-            den += v[i];
-        }
-        den += __shfl_xor(den, 32);
-        const float rden = 1.f / den;
-#pragma unroll
-        for (int i = 0; i < ET * 16; ++i) v[i] *= rden;   // probability of every expert of this lane's half
-
-        // ---- the k selections: probability, upstream gradient, dropout flag (both lanes of a slice do the same)
-        float psel[8], dpf[8];
-        bool keep[8];
-        int ej[8];
-        int kept = 0;
-#pragma unroll
-        for (int jj = 0; jj < 8; ++jj) {
-            psel[jj] = dpf[jj] = 0.f;
-            keep[jj] = false;
-            ej[jj] = -1;
-            if (jj < k) {
-                const long long a = nn * k + jj;
-                ej[jj] = idx[a];
-                float mine = 0.f;
-#pragma unroll
-                for (int i = 0; i < ET * 16; ++i) mine = (i >> 4) * 32 + acc_feature(i & 15, g) == ej[jj] ? v[i] : mine;
-                psel[jj] = mine + __shfl_xor(mine, 32);   // the expert sits in one of the two halves
-                dpf[jj] = inv[a] >= 0 ? dpk[a] : 0.f;     // a capacity-dropped assignment carries no gradient from h'
-                if (capg != nullptr) dpf[jj] += capg[min(max(ej[jj], 0), E - 1)];   // but it counts as assigned (capacity loss)
-                keep[jj] = rate > 0.f ? !(drop_u[a] < rate) : true;
-                kept += keep[jj] ? 1 : 0;
-            }
-        }
-        if (rate > 0.f) {
-            if (kept == 0) keep[0] = true;
-            float ssum = 0.f, dot = 0.f;
-#pragma unroll
-            for (int jj = 0; jj < 8; ++jj) ssum += keep[jj] ? psel[jj] : 0.f;
-#pragma unroll
-            for (int jj = 0; jj < 8; ++jj) dot += keep[jj] ? dpf[jj] * (psel[jj] / ssum) : 0.f;
-#pragma unroll
-            for (int jj = 0; jj < 8; ++jj) dpf[jj] = keep[jj] ? (dpf[jj] - dot) / ssum : 0.f;
-        }
-        // dL/dg_e = (1/tau) (sum_j c_j [e = e_j] - p_e sum_j c_j),  c_j = dL/dp_j p_j
-        float csum = 0.f;
-#pragma unroll
-        for (int jj = 0; jj < 8; ++jj) {
-            dpf[jj] = jj < k ? dpf[jj] * psel[jj] : 0.f;
-            csum += dpf[jj];
-        }
+        uint32_t act[4], dgt[ET][TERMS][8];
+        router_logits<DS, ET>(xb, w1f, w2f, b1s, b2s, lane, g, gacc, act);
+        SliceDraws<ET> D;
+        load_draws<ET>(D, nn, g, E, k, noise, drop_u, idx, inv, dpk);
+        logit_gradients<ET, TERMS>(gacc, D, nn, g, E, k, noise != nullptr, sigma, inv_tau, drop_u, rate, idx, inv, dpk, capg, dgt);
         if (valid) {
-#pragma unroll
-            for (int et = 0; et < ET; ++et)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {   // experts 32 et + 8q + 4g .. + 3 of this slice: four bf16 values per term
-                    float dg[4];
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        const int i = et * 16 + 4 * q + c, e = et * 32 + 8 * q + 4 * g + c;
-                        float t = -v[i] * csum;
-#pragma unroll
-                        for (int jj = 0; jj < 8; ++jj) t += e == ej[jj] ? dpf[jj] : 0.f;
-                        dg[c] = t * inv_tau;
-                    }
-                    uint32_t dt[TERMS][4];
-                    split_terms<TERMS>(dg, dt, 0);
-#pragma unroll
-                    for (int t = 0; t < TERMS; ++t)
-                        *(uint2 *)(dg_terms + (t * Ns + n) * EP + et * 32 + 8 * q + 4 * g) = make_uint2(dt[t][0], dt[t][1]);
-                }
-            *(uint4 *)(relu_bits + (n * 2 + g) * 4) = make_uint4(act0, act1, act2, act3);
+            store_logit_gradients<ET, TERMS>(dgt, dg_terms, Ns, n, g);
+            *(uint4 *)(relu_bits + (n * 2 + g) * 4) = make_uint4(act[0], act[1], act[2], act[3]);
         }
     }
 }
 
 // ------------------------------------------------------------------------------------------------ inputs kernel
-// Rows of the per-wavefront staging tile are 36 floats apart: 16-byte reads at a stride of one row then fall into
-// distinct banks.
-constexpr int kRbStageRow = 36;
-
 // LDS: w2c | w1c (the third and fourth pieces of the packed buffer, adjacent) | staging tiles.
 template <int DS, int ET>
 __global__ __launch_bounds__(kRbThreads) void bwd_route_inputs_mfma_kernel(
@@ -282,8 +519,7 @@ __global__ __launch_bounds__(kRbThreads) void bwd_route_inputs_mfma_kernel(
         const long long n = tile * 32 + j;
         const bool valid = n < Ns;
         // dL/dg of this lane in accumulator order: register pairs, i.e. B-operand fragments, as they were stored
-        uint32_t dgt[ET][TERMS][8];
-        uint4 act = make_uint4(0, 0, 0, 0);
+        uint32_t dgt[ET][TERMS][8], act[4] = {0, 0, 0, 0};
 #pragma unroll
         for (int et = 0; et < ET; ++et)
 #pragma unroll
@@ -296,94 +532,93 @@ __global__ __launch_bounds__(kRbThreads) void bwd_route_inputs_mfma_kernel(
                     dgt[et][t][2 * q + 1] = v.y;
                 }
             }
-        if (valid) act = *(const uint4 *)(relu_bits + (n * 2 + g) * 4);
-
-        // dL/du = Wr2 dL/dg (ReLU pattern applied), dL/dx += Wr1 dL/du, both from registers
+        if (valid) {
+            const uint4 b = *(const uint4 *)(relu_bits + (n * 2 + g) * 4);
+            act[0] = b.x; act[1] = b.y; act[2] = b.z; act[3] = b.w;
+        }
         f32x16 dx[OT];
-#pragma unroll
-        for (int ot = 0; ot < OT; ++ot)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) dx[ot][i] = 0.f;
-#pragma unroll 1
-        for (int ht = 0; ht < kRbHT; ++ht) {
-            f32x16 du;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) du[i] = 0.f;
-#pragma unroll
-            for (int et = 0; et < ET; ++et)
-#pragma unroll
-                for (int s = 0; s < 2; ++s) {
-                    const bf16x8 wf = __builtin_bit_cast(bf16x8, w2c[((et * 2 + s) * kRbHT + ht) * 64 + lane]);
-#pragma unroll
-                    for (int t = 0; t < TERMS; ++t) du = mfma_bf16(wf, frag_of(dgt[et][t], s), du);   // large terms first, see the weights kernel
-                }
-            const uint32_t word = (ht >> 1) == 0 ? act.x : (ht >> 1) == 1 ? act.y : (ht >> 1) == 2 ? act.z : act.w;
-            const uint32_t bits = word >> ((ht & 1) * 16);
-            uint32_t dut[2][TERMS][4];   // by K-step
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                float d[4];
-#pragma unroll
-                for (int c = 0; c < 4; ++c) d[c] = (bits >> (4 * q + c)) & 1u ? du[4 * q + c] : 0.f;
-                split_terms<TERMS>(d, dut[q >> 1], 2 * (q & 1));
-            }
-#pragma unroll
-            for (int s = 0; s < 2; ++s)
-#pragma unroll
-                for (int ot = 0; ot < OT; ++ot) {
-                    const bf16x8 wf = __builtin_bit_cast(bf16x8, w1c[((ht * 2 + s) * OT + ot) * 64 + lane]);
-#pragma unroll
-                    for (int t = TERMS - 1; t >= 0; --t)
-                        dx[ot] = mfma_bf16(wf, __builtin_bit_cast(bf16x8, make_uint4(dut[s][t][0], dut[s][t][1], dut[s][t][2], dut[s][t][3])), dx[ot]);
-                }
-        }
+        input_gradients<DS, ET>(dgt, act, w2c, w1c, lane, dx);
+        int rows[4][kRbAhead];
+        slice_rows(rows, inv, tile * 32, Ns, k, lane);
+        RowsAhead<DS, 0> none;
+        assemble_rows<DS, 0>(dx, rows, none, dxrow, inv, k, dh, tile * 32, Ns, lane, stg);
+    }
+}
 
-        // dL/dh of the slices: router path plus the expert-path rows of their k assignments, one rounding.  The rows are
-        // gathered and the result is stored through a tile of LDS private to the wavefront, one 32-feature tile at a
-        // time, so that every memory instruction covers whole 128-byte (gather) or 64-byte (store) runs: eight lanes per
-        // slice fetch and add the k row pieces, lane (j, g) picks up its accumulator order from the tile, adds the router
-        // path, rounds, and puts the packed row back for four lanes per slice to store.
-        const long long n0 = tile * 32;
-        const int piece = lane & 7, sl = lane >> 3;
-        int rws[4][8];
+// ------------------------------------------------------------------------------------------------ both in one
+// Where the fragments of both halves fit the LDS together: dL/dg and the ReLU pattern stay in registers, x of the next tile and the
+// first two gradient rows of every slice are requested ahead of the matrix instructions that they wait behind.
+// Bound: the latency of two wavefronts per SIMD (33 thousand cycles per tile, of which 2000 vector and 160 matrix instructions issue in
+// 12 thousand); four would not hold the gradient rows (128 registers: spills, 187 us).
+// 262 144 slices at width 64, 32 experts: logits 60 + inputs 83 us -> 93 us, of which the gradient rows' loads without a branch and a
+// wait behind each are 25, the ReLU pattern in two instructions per unit, the capped median and the mixed-precision split 14.  32 768 slices
+// at width 48: 17 + 20 -> 24 us.
+template <int DS, int ET, int THREADS, int AHEAD, int SROWS>
+__global__ __launch_bounds__(THREADS) void bwd_route_slices_mfma_kernel(
+    const bf16_t *__restrict__ x, long long Ns, int E, int k, const char *__restrict__ packed, RouterBwdPacked L,
+    const float *__restrict__ noise, float sigma, float inv_tau, const float *__restrict__ drop_u, float rate,
+    const int32_t *__restrict__ idx, const int32_t *__restrict__ inv, const float *__restrict__ dpk,
+    const float *__restrict__ capg, const float *__restrict__ dxrow, bf16_t *__restrict__ dg_terms /* [terms][Ns][EP] */, bf16_t *__restrict__ dh)
+{
+    constexpr int KS = SliceTiles<DS>::KS, OT = SliceTiles<DS>::OT, EP = ET * 32, TERMS = kRbTerms<DS>, kWaves = THREADS / 64;
+    extern __shared__ __align__(16) char lds[];
+    uint4 *w1f = (uint4 *)lds;                              // [8][KS][64]
+    uint4 *w2f = w1f + kRbHT * KS * 64;                     // [8][2][ET][64]
+    uint4 *w2c = w2f + ET * kRbHT * 2 * 64;                 // [ET][2][8][64]
+    uint4 *w1c = w2c + ET * 2 * kRbHT * 64;                 // [8][2][OT][64]
+    float *b1s = (float *)(w1c + kRbHT * 2 * OT * 64);      // [256]
+    float *b2s = b1s + kRbHr;                               // [EP]
+    float *stg_all = b2s + EP;                              // [wavefronts][SROWS][kRbStageRow]
+
+    const int tid = threadIdx.x, lane = tid & 63, j = lane & 31, g = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    float *stg = stg_all + wave * SROWS * kRbStageRow;
+    // A block takes consecutive tiles: the gradient rows of a run of slices are runs of rows in every expert, on few memory pages.
+    const long long all = (Ns + 31) / 32, per = (all + gridDim.x - 1) / gridDim.x, ntiles = min(all, (blockIdx.x + 1) * per), step = kWaves;
+    long long tile = blockIdx.x * per + wave;
+
+    auto load_x = [&](long long t, bf16x8 (&xb)[KS]) {   // a lane without a slice reads slice 0 and writes nothing
+        const long long n = t * 32 + j;
+        const uint4 *xr = (const uint4 *)(x + (n < Ns ? n : 0) * DS);
 #pragma unroll
-        for (int it = 0; it < 4; ++it) {
-            const long long ns = n0 + it * 8 + sl;
+        for (int ks = 0; ks < KS; ++ks) xb[ks] = load_row_piece<DS>(xr, ks, g);
+    };
+    bf16x8 xb[KS];
+    int rows[4][kRbAhead];
+    load_x(tile, xb);
+    slice_rows(rows, inv, tile * 32, Ns, k, lane);
+    stage_bytes(packed + L.w1f, (char *)w1f, (size_t)(kRbHT * KS + ET * kRbHT * 2 + ET * 2 * kRbHT + kRbHT * 2 * OT) * 1024, tid, THREADS);   // (adjacent)
+    if (tid < kRbHr) b1s[tid] = ((const float *)(packed + L.b1))[tid];
+    if (tid < EP) b2s[tid] = ((const float *)(packed + L.b2))[tid];
+    __syncthreads();
+
+    for (; tile < ntiles; tile += step) {
+        const long long n = tile * 32 + j, nn = n < Ns ? n : 0;
+        SliceDraws<ET> D;
+        RowsAhead<DS, AHEAD> ahead;
+        if constexpr (AHEAD > 0) {
 #pragma unroll
-            for (int jj = 0; jj < 8; ++jj) rws[it][jj] = (jj < k && ns < Ns) ? inv[ns * k + jj] : -1;
+            for (int ot = 0; ot < OT; ++ot)
+#pragma unroll
+                for (int it = 0; it < 4; ++it)
+#pragma unroll
+                    for (int jj = 0; jj < AHEAD; ++jj) ahead.v[ot][it][jj] = gradient_row_piece<DS>(dxrow, rows[it][jj], ot, lane & 7);
         }
+        load_draws<ET>(D, nn, g, E, k, noise, drop_u, idx, inv, dpk);
+        f32x16 gacc[ET], dx[OT];
+        uint32_t act[4], dgt[ET][TERMS][8];
+        router_logits<DS, ET>(xb, w1f, w2f, b1s, b2s, lane, g, gacc, act);
+        load_x(tile + step, xb);
+        logit_gradients<ET, TERMS>(gacc, D, nn, g, E, k, noise != nullptr, sigma, inv_tau, drop_u, rate, idx, inv, dpk, capg, dgt);
+        if (n < Ns) store_logit_gradients<ET, TERMS>(dgt, dg_terms, Ns, n, g);
+        input_gradients<DS, ET>(dgt, act, w2c, w1c, lane, dx);
+        int next[4][kRbAhead];
+        slice_rows(next, inv, (tile + step) * 32, Ns, k, lane);
+        assemble_rows<DS, AHEAD, SROWS>(dx, rows, ahead, dxrow, inv, k, dh, tile * 32, Ns, lane, stg);
 #pragma unroll
-        for (int ot = 0; ot < OT; ++ot) {
+        for (int it = 0; it < 4; ++it)
 #pragma unroll
-            for (int it = 0; it < 4; ++it) {
-                f32x4 v = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int jj = 0; jj < 8; ++jj)
-                    if (rws[it][jj] >= 0 && (DS % 32 == 0 || 32 * ot + 4 * piece < DS))
-                        v += *(const f32x4 *)(dxrow + (size_t)rws[it][jj] * DS + 32 * ot + 4 * piece);
-                *(f32x4 *)(stg + (it * 8 + sl) * kRbStageRow + 4 * piece) = v;
-            }
-            wave_lds_sync();
-            uint2 o[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const f32x4 t = *(const f32x4 *)(stg + j * kRbStageRow + 8 * q + 4 * g);
-                o[q] = make_uint2(pack_bf16x2(dx[ot][4 * q] + t[0], dx[ot][4 * q + 1] + t[1]),
-                                  pack_bf16x2(dx[ot][4 * q + 2] + t[2], dx[ot][4 * q + 3] + t[3]));
-            }
-            wave_lds_sync();   // every lane has read its sums: the tile now takes the packed rows (64 bytes per slice)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) *(uint2 *)((char *)(stg + j * kRbStageRow) + (8 * q + 4 * g) * 2) = o[q];
-            wave_lds_sync();
-#pragma unroll
-            for (int half = 0; half < 2; ++half) {
-                const int i = half * 16 + (lane >> 2), pc = lane & 3;
-                const long long ns = n0 + i;
-                if (ns < Ns && (DS % 32 == 0 || 32 * ot + 8 * pc < DS))
-                    *(uint4 *)(dh + ns * DS + 32 * ot + 8 * pc) = *(const uint4 *)((const char *)(stg + i * kRbStageRow) + pc * 16);
-            }
-            wave_lds_sync();   // before the next gather overwrites the tile
-        }
+            for (int jj = 0; jj < kRbAhead; ++jj) rows[it][jj] = next[it][jj];
     }
 }
 
@@ -611,6 +846,16 @@ static size_t inputs_lds(int OT, int ET)
     return (size_t)(ET * 2 * kRbHT + kRbHT * 2 * OT) * 1024 + (size_t)kRbWaves * 32 * kRbStageRow * sizeof(float);
 }
 
+// One kernel for the logits and the inputs: wavefronts per block (0: the fragments of both do not fit the LDS), gradient rows
+// requested ahead, staging rows.
+template <int DS, int ET> struct RouterFused {
+    static constexpr size_t weights = (size_t)(kRbHT * SliceTiles<DS>::KS + 4 * ET * kRbHT + kRbHT * 2 * SliceTiles<DS>::OT) * 1024 + (kRbHr + 32 * ET) * 4;
+    static constexpr size_t row = (size_t)kRbStageRow * 4;
+    static constexpr int SROWS = weights + 8 * 32 * row <= 160 * 1024 ? 32 : 16, AHEAD = SROWS == 32 ? kRbAhead : 0;   // (no registers for them at the wider shapes)
+    static constexpr int waves = weights + 8 * SROWS * row <= 160 * 1024 ? 8 : 0;
+    static constexpr size_t lds = weights + waves * SROWS * row;
+};
+
 bool backward_router_mfma_shape(const slicemoe_config &c)
 {
     const int ds = c.d / c.S, ET = (c.E + 31) / 32, KS = (ds + 15) / 16, OT = (ds + 31) / 32;
@@ -663,28 +908,39 @@ static hipError_t run_router_mfma(const slicemoe_config &c, const RouterBwdPacke
     constexpr int KS = SliceTiles<DS>::KS, OT = SliceTiles<DS>::OT;
     const long long Ns = (long long)c.T * c.S;
     const long long ntiles = (Ns + 31) / 32, units = (ntiles + kRbWaves - 1) / kRbWaves;
-    auto lk = bwd_route_logits_mfma_kernel<DS, ET>;
-    hipError_t e = grant_dynamic_lds((const void *)lk, logits_lds(KS, ET));
-    if (e != hipSuccess) return e;
-    // as many blocks as can be resident at once (registers and LDS allow two per CU for the narrow shapes)
-    static int lk_per_cu = 0;   // per instantiation; the same on every device of the machine
-    if (lk_per_cu == 0) {
-        int n = 1;
-        if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, (const void *)lk, kRbThreads, logits_lds(KS, ET))) != hipSuccess) return e;
-        lk_per_cu = n < 1 ? 1 : n;
+    hipError_t e;
+    typedef RouterFused<DS, ET> F;
+    if constexpr (F::waves > 0) {
+        auto fk = bwd_route_slices_mfma_kernel<DS, ET, F::waves * 64, F::AHEAD, F::SROWS>;
+        if ((e = grant_dynamic_lds((const void *)fk, F::lds)) != hipSuccess) return e;
+        const long long blocks = num_compute_units() < ntiles ? num_compute_units() : ntiles;   // (a small batch spreads over all CUs)
+        fk<<<(int)blocks, F::waves * 64, F::lds, s>>>((const bf16_t *)h, Ns, c.E, c.k, pb, L, v.sigma > 0.f ? v.noise : nullptr, v.sigma, v.inv_tau,
+                                                      rate > 0.f ? drop_u : nullptr, rate, idx, inv, dpk, v.capg, dxrow, dg, (bf16_t *)d_h);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    } else {
+        auto lk = bwd_route_logits_mfma_kernel<DS, ET>;
+        e = grant_dynamic_lds((const void *)lk, logits_lds(KS, ET));
+        if (e != hipSuccess) return e;
+        // as many blocks as can be resident at once (registers and LDS allow two per CU for the narrow shapes)
+        static int lk_per_cu = 0;   // per instantiation; the same on every device of the machine
+        if (lk_per_cu == 0) {
+            int n = 1;
+            if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, (const void *)lk, kRbThreads, logits_lds(KS, ET))) != hipSuccess) return e;
+            lk_per_cu = n < 1 ? 1 : n;
+        }
+        long long blocks = (long long)num_compute_units() * lk_per_cu;
+        if (blocks > units) blocks = units;
+        lk<<<(int)blocks, kRbThreads, logits_lds(KS, ET), s>>>((const bf16_t *)h, Ns, c.E, c.k, pb, L, v.sigma > 0.f ? v.noise : nullptr,
+                                                               v.sigma, v.inv_tau, rate > 0.f ? drop_u : nullptr, rate, idx, inv, dpk,
+                                                               v.capg, dg, bits);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        auto ik = bwd_route_inputs_mfma_kernel<DS, ET>;
+        if ((e = grant_dynamic_lds((const void *)ik, inputs_lds(OT, ET))) != hipSuccess) return e;
+        // one block per CU: this kernel waits on its row gathers, and a second resident block measured slower (cache misses)
+        blocks = num_compute_units() < units ? num_compute_units() : units;
+        ik<<<(int)blocks, kRbThreads, inputs_lds(OT, ET), s>>>(Ns, c.k, pb, L, inv, dxrow, dg, bits, (bf16_t *)d_h);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    long long blocks = (long long)num_compute_units() * lk_per_cu;
-    if (blocks > units) blocks = units;
-    lk<<<(int)blocks, kRbThreads, logits_lds(KS, ET), s>>>((const bf16_t *)h, Ns, c.E, c.k, pb, L, v.sigma > 0.f ? v.noise : nullptr,
-                                                           v.sigma, v.inv_tau, rate > 0.f ? drop_u : nullptr, rate, idx, inv, dpk,
-                                                           v.capg, dg, bits);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    auto ik = bwd_route_inputs_mfma_kernel<DS, ET>;
-    if ((e = grant_dynamic_lds((const void *)ik, inputs_lds(OT, ET))) != hipSuccess) return e;
-    // one block per CU: this kernel waits on its row gathers, and a second resident block measured slower (cache misses)
-    blocks = num_compute_units() < units ? num_compute_units() : units;
-    ik<<<(int)blocks, kRbThreads, inputs_lds(OT, ET), s>>>(Ns, c.k, pb, L, inv, dxrow, dg, bits, (bf16_t *)d_h);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
     typedef RouterWeightsTile<DS, ET, kRbTerms<DS>> G;
     auto wk = bwd_route_weights_mfma_kernel<DS, ET, kRbTerms<DS>>;
     if ((e = grant_dynamic_lds((const void *)wk, G::lds)) != hipSuccess) return e;
