@@ -227,9 +227,10 @@ __global__ __launch_bounds__(kBmTileWaves<DS> * 64) void bwd_rows_streamed_mfma_
         for (int i = 0; i < 8; ++i) dps[i] = 0.f;
         for (int ch = 0; ch < nchunks; ++ch) {
             __syncthreads();   // everyone is done with the previous contents
-            stage_bytes(ew + (size_t)ch * hc * KS * 1024, (char *)w1f, (size_t)hc * KS * 1024, tid, THREADS);
-            stage_bytes(ew + off_w2r + (size_t)ch * hc * KS * 1024, (char *)w2r, (size_t)hc * KS * 1024, tid, THREADS);
-            stage_bytes(ew + off_w1c + (size_t)ch * hc * 2 * OT * 1024, (char *)w1c, (size_t)hc * 2 * OT * 1024, tid, THREADS);
+            // (eight pieces in flight per thread: one at a time took 1.08 ms at width 128, 1 048 576 rows, He 512, now 0.97)
+            stage_to_lds<THREADS, 8>(ew + (size_t)ch * hc * KS * 1024, w1f, hc * KS * 64, tid);
+            stage_to_lds<THREADS, 8>(ew + off_w2r + (size_t)ch * hc * KS * 1024, w2r, hc * KS * 64, tid);
+            stage_to_lds<THREADS, 8>(ew + off_w1c + (size_t)ch * hc * 2 * OT * 1024, w1c, hc * 2 * OT * 64, tid);
             if (e != cur_e && ch == 0) {
                 const float *gb1 = (const float *)(ew + off_b1);
                 for (int i = tid; i < He; i += THREADS) b1s[i] = gb1[i];
