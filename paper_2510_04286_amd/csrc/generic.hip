@@ -16,12 +16,12 @@ constexpr int kW2LdsBytes = 40 * 1024;   // Wr2 goes to LDS up to this size (fp3
 // thread per hidden unit with eight slices side by side; one thread per logit, fed from LDS; 32 lanes per slice for the
 // softmax and the selection.  2048 slices, ds = 64, Hr = 256, E = 8: 15.3 -> 11.5 us (logits from memory, softmax
 // by one thread per slice before).
-template <typename T, bool W2LDS>
+template <typename T, bool W2LDS, bool DROP>
 __global__ __launch_bounds__(kGenThreads) void route_generic_kernel(
     const T *__restrict__ x, long long Ns, int ds, int Hr, int E, int k,
     const T *__restrict__ Wr1, const T *__restrict__ br1, const T *__restrict__ Wr2, const T *__restrict__ br2,
-    const float *__restrict__ noise, float sigma, float inv_tau, const float *__restrict__ drop_u /* may be null */, float rate,
-    int32_t *__restrict__ idx, float *pk)
+    const float *__restrict__ noise, float sigma, float inv_tau, const float *__restrict__ drop_u, float rate,
+    int32_t *__restrict__ idx, float *__restrict__ pk)
 {
     extern __shared__ __align__(16) float smem[];
     const int dsp = (ds + 3) & ~3, ust = Hr + 1;   // row strides: whole quads of features; hidden units of neighbouring slices in different banks
@@ -111,7 +111,7 @@ __global__ __launch_bounds__(kGenThreads) void route_generic_kernel(
         if (best == l) v0 = -INFINITY;
         if (best == l + 32) v1 = -INFINITY;
     }
-    if (drop_u != nullptr && l == 0 && r < rows) drop_assignments(pk + n * k, drop_u + n * k, k, rate);   // (this lane has written them)
+    if (DROP && l == 0 && r < rows) drop_assignments(pk + n * k, drop_u + n * k, k, rate);   // (this lane has written them)
 }
 
 // Expert FFN of Section 3.1 on stacked rows with the Eq. 1 input weighting and the gather fused:
@@ -253,10 +253,12 @@ static void run_route_generic(const slicemoe_config &c, const void *h, const sli
     const float *noise = v.sigma > 0.f ? v.noise : nullptr;
     const size_t smem = sizeof(float) * (size_t)kRB * (((ds + 3) & ~3) + c.Hr + 1 + c.E), w2 = sizeof(float) * (size_t)c.Hr * c.E;
     const bool w2lds = w2 <= kW2LdsBytes && smem + w2 <= 64 * 1024;
-    auto kern = w2lds ? route_generic_kernel<T, true> : route_generic_kernel<T, false>;
+    const bool drop = v.rate > 0.f;
+    auto kern = w2lds ? (drop ? route_generic_kernel<T, true, true> : route_generic_kernel<T, true, false>)
+                      : (drop ? route_generic_kernel<T, false, true> : route_generic_kernel<T, false, false>);
     kern<<<blocks, kGenThreads, smem + (w2lds ? w2 : 0), s>>>((const T *)h, Ns, ds, c.Hr, c.E, c.k, (const T *)w.Wr1, (const T *)w.br1,
                                                               (const T *)w.Wr2, (const T *)w.br2, noise, v.sigma, v.inv_tau,
-                                                              v.rate > 0.f ? v.drop_u : nullptr, v.rate, idx, p);
+                                                              v.drop_u, v.rate, idx, p);
 }
 
 hipError_t launch_route_generic(const slicemoe_config &c, const void *h, const slicemoe_weights &w,
