@@ -122,7 +122,7 @@ PackedLayout packed_layout(const slicemoe_config &c)
 }
 
 // Whether slicemoe_forward lets the router write the dispatch histogram, and in chunks of how many assignments.
-static int forward_hist_chunk(const slicemoe_config &c) { return use_mfma(c) ? route_mfma_hist_chunk(c) : 0; }
+static int forward_hist_chunk(const slicemoe_config &c) { return use_mfma(c) ? route_mfma_hist_chunk(c) : route_generic_hist_chunk(c); }
 
 // The per-chunk histogram table of the dispatch: large enough for the stage entry point's chunks and for the router's.
 static size_t dispatch_scratch_bytes(const slicemoe_config &c)
@@ -416,11 +416,11 @@ static slicemoe_status forward_common(const slicemoe_config *cfg, const void *h,
         const slicemoe_status ps = resolve_packed(*cfg, *w, workspace, workspace_bytes, s, &packed);
         if (ps != SLICEMOE_OK) return ps;
     }
-    // the matrix-core router leaves the per-chunk histogram of its selections in the dispatch table
+    // the router leaves the per-chunk histogram of its selections in the dispatch table
     const int hist_chunk = forward_hist_chunk(*cfg);
     int32_t *table = (int32_t *)(ws + L.scratch);
     hipError_t e = mfma ? launch_route_mfma(*cfg, h, packed, idx, p, s, v, hist_chunk > 0 ? table : nullptr)
-                        : launch_route_generic(*cfg, h, *w, idx, p, s, v);
+                        : launch_route_generic(*cfg, h, *w, idx, p, s, v, hist_chunk > 0 ? table : nullptr);
     if (e != hipSuccess) return SLICEMOE_ERR_HIP;
     // the load statistics ride along in the scan kernel of the dispatch
     e = launch_dispatch(*cfg, idx, counts_raw, counts, offsets, perm, inv, table, stats, s, hist_chunk);

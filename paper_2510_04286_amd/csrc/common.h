@@ -130,6 +130,7 @@ size_t dispatch_table_bytes(const DispatchGeom &g, int E);
 // (layout and entry width as dispatch_geometry(Na, E, chunk) says, chunks of route_mfma_hist_chunk(c) assignments); 0
 // when it cannot for this shape.
 int route_mfma_hist_chunk(const slicemoe_config &c);
+int route_generic_hist_chunk(const slicemoe_config &c);   // the same of the generic router
 
 // ---- kernel launchers (each only enqueues; returns hipGetLastError) --------------------
 // Training-time variations of the router (softmax temperature: Appendix B; Gaussian logit noise: Section 5); the
@@ -147,7 +148,8 @@ struct RouteVariant {
     const float *capg = nullptr;
 };
 hipError_t launch_route_generic(const slicemoe_config &c, const void *h, const slicemoe_weights &w,
-                                int32_t *idx, float *p, hipStream_t s, const RouteVariant &v = RouteVariant());
+                                int32_t *idx, float *p, hipStream_t s, const RouteVariant &v = RouteVariant(),
+                                int32_t *hist_table = nullptr /* see route_generic_hist_chunk */);
 hipError_t launch_route_mfma(const slicemoe_config &c, const void *h, const void *packed,
                              int32_t *idx, float *p, hipStream_t s, const RouteVariant &v = RouteVariant(),
                              int32_t *hist_table = nullptr /* see route_mfma_hist_chunk */);

@@ -21,8 +21,9 @@ __global__ __launch_bounds__(kGenThreads) void route_generic_kernel(
     const T *__restrict__ x, long long Ns, int ds, int Hr, int E, int k,
     const T *__restrict__ Wr1, const T *__restrict__ br1, const T *__restrict__ Wr2, const T *__restrict__ br2,
     const float *__restrict__ noise, float sigma, float inv_tau, const float *__restrict__ drop_u, float rate,
-    int32_t *__restrict__ idx, float *__restrict__ pk)
+    int32_t *__restrict__ idx, float *__restrict__ pk, uint16_t *__restrict__ hist /* may be null */, int hist_stride)
 {
+    __shared__ int counts[64];   // selections of this block per expert
     extern __shared__ __align__(16) float smem[];
     const int dsp = (ds + 3) & ~3, ust = Hr + 1;   // row strides: whole quads of features; hidden units of neighbouring slices in different banks
     float *xs = smem;                 // [kRB][dsp]
@@ -30,6 +31,7 @@ __global__ __launch_bounds__(kGenThreads) void route_generic_kernel(
     float *gs = us + kRB * ust;       // [kRB][E]
     float *w2s = gs + kRB * E;        // [Hr][E] (W2LDS only)
     const int tid = threadIdx.x;
+    if (tid < 64) counts[tid] = 0;
     const long long n0 = (long long)blockIdx.x * kRB;
     const int rows = (int)min((long long)kRB, Ns - n0);
 
@@ -107,11 +109,21 @@ __global__ __launch_bounds__(kGenThreads) void route_generic_kernel(
         if (l == 0 && r < rows) {
             idx[n * k + j] = best;
             pk[n * k + j] = expf((bv - m) * inv_tau) / den;
+            if (hist != nullptr) atomicAdd(&counts[best], 1);
         }
         if (best == l) v0 = -INFINITY;
         if (best == l + 32) v1 = -INFINITY;
     }
     if (DROP && l == 0 && r < rows) drop_assignments(pk + n * k, drop_u + n * k, k, rate);   // (this lane has written them)
+    if (hist != nullptr) {   // the block's chunk of the dispatch histogram
+        __syncthreads();
+        if (tid < E) {
+            uint16_t *row = hist + (size_t)tid * hist_stride;
+            row[blockIdx.x] = (uint16_t)counts[tid];
+            if (blockIdx.x == gridDim.x - 1)   // the padding of a row reads as zero
+                for (int c = (int)gridDim.x; c < hist_stride; ++c) row[c] = 0;
+        }
+    }
 }
 
 // Expert FFN of Section 3.1 on stacked rows with the Eq. 1 input weighting and the gather fused:
@@ -245,28 +257,43 @@ __global__ __launch_bounds__(kF32Threads) void ffn_generic_kernel(
 
 template <typename T>
 static void run_route_generic(const slicemoe_config &c, const void *h, const slicemoe_weights &w, int32_t *idx, float *p, hipStream_t s,
-                              const RouteVariant &v)
+                              const RouteVariant &v, uint16_t *hist, int hist_stride)
 {
     const long long Ns = (long long)c.T * c.S;
     const int ds = c.d / c.S;
     const int blocks = (int)((Ns + kRB - 1) / kRB);
     const float *noise = v.sigma > 0.f ? v.noise : nullptr;
     const size_t smem = sizeof(float) * (size_t)kRB * (((ds + 3) & ~3) + c.Hr + 1 + c.E), w2 = sizeof(float) * (size_t)c.Hr * c.E;
-    const bool w2lds = w2 <= kW2LdsBytes && smem + w2 <= 64 * 1024;
+    const bool w2lds = w2 <= kW2LdsBytes && smem + w2 <= 64 * 1024 - 256;   // (256 bytes: the counts)
     const bool drop = v.rate > 0.f;
     auto kern = w2lds ? (drop ? route_generic_kernel<T, true, true> : route_generic_kernel<T, true, false>)
                       : (drop ? route_generic_kernel<T, false, true> : route_generic_kernel<T, false, false>);
     kern<<<blocks, kGenThreads, smem + (w2lds ? w2 : 0), s>>>((const T *)h, Ns, ds, c.Hr, c.E, c.k, (const T *)w.Wr1, (const T *)w.br1,
                                                               (const T *)w.Wr2, (const T *)w.br2, noise, v.sigma, v.inv_tau,
-                                                              v.drop_u, v.rate, idx, p);
+                                                              v.drop_u, v.rate, idx, p, hist, hist_stride);
+}
+
+// A block's slices are a chunk of the dispatch histogram, in batches whose table is small enough for the scatter blocks to sum it: up to
+// 16 384 slices with 16 experts, 4096 with 64; beyond, chunks of eight slices would make the scan longer than the histogram kernel that they
+// save.  2048 slices, E = 8: forward 40.9 -> 38.5 us, the histogram's launch between router and scatter.
+int route_generic_hist_chunk(const slicemoe_config &c)
+{
+    const long long Ns = (long long)c.T * c.S;
+    return Ns > 0 && dispatch_geometry(Ns * c.k, c.E, kRB * c.k).fused ? kRB * c.k : 0;
 }
 
 hipError_t launch_route_generic(const slicemoe_config &c, const void *h, const slicemoe_weights &w,
-                                int32_t *idx, float *p, hipStream_t s, const RouteVariant &v)
+                                int32_t *idx, float *p, hipStream_t s, const RouteVariant &v, int32_t *hist)
 {
-    if ((long long)c.T * c.S == 0) return hipSuccess;
-    if (c.dtype == SLICEMOE_BF16) run_route_generic<bf16_t>(c, h, w, idx, p, s, v);
-    else run_route_generic<float>(c, h, w, idx, p, s, v);
+    const long long Ns = (long long)c.T * c.S;
+    if (Ns == 0) return hipSuccess;
+    int stride = 0;
+    if (hist != nullptr) {
+        if (route_generic_hist_chunk(c) == 0) return hipErrorInvalidValue;
+        stride = dispatch_geometry(Ns * c.k, c.E, kRB * c.k).stride;
+    }
+    if (c.dtype == SLICEMOE_BF16) run_route_generic<bf16_t>(c, h, w, idx, p, s, v, (uint16_t *)hist, stride);
+    else run_route_generic<float>(c, h, w, idx, p, s, v, (uint16_t *)hist, stride);
     return hipGetLastError();
 }
 
