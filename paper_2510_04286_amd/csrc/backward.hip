@@ -34,33 +34,112 @@ static hipError_t zero_fill(float *p, size_t n, hipStream_t s)
     return hipGetLastError();
 }
 
-constexpr int kRedElems = 64, kRedSeqs = 8;
-// Sum of the router slots of all blocks in a fixed order: a block is 64 slot elements x 8 interleaved sequences of slots, whose
-// eight partial sums are added in order at the end.
-__global__ __launch_bounds__(kRedElems * kRedSeqs) void bwd_reduce_router_kernel(
-    const float *__restrict__ part, int nslots, int ds, int Hr, int E,
-    float *__restrict__ dWr1, float *__restrict__ dbr1, float *__restrict__ dWr2, float *__restrict__ dbr2)
+// ---- Sum of the slots, each element in a fixed order.
+// Up to kReduceApartBytes of partial sums there is one launch for the router's slots and the experts' (where those are not on a
+// stream of their own): a launch more costs 3-5 us of a single stream, whatever it sums.  The router's blocks come first in the
+// grid: their chains are the longer ones.  Beyond, the experts' are summed at once, while they are still in a cache.  Forward and
+// backward, two launches / one: width 48, He 192, E 16, T = 2048 (41 MB): 163.9 / 160.9 us; width 64 fp32, He 256, E 8, T = 1000
+// (43 MB): 142.1 / 139.0; width 64, He 256, E 16 (57 MB): T = 2013 180.4 / 181.2, T = 6312 214.3 / 217.4, T = 16384 526.5 / 529.9.
+struct ReduceArgs {
+    // experts: blocks of THREADS / 4 groups of V slot elements, one expert each
+    const float *epart;
+    const int32_t *offsets;
+    int step, blocks;
+    size_t eslot;
+    // router: blocks of THREADS / 8 slot elements
+    const float *rpart;
+    int nslots;
+    size_t rslot;
+    unsigned router_blocks;
+    int ds, He, Hr, E;
+    slicemoe_weight_grads g;
+};
+constexpr size_t kReduceApartBytes = (size_t)48 << 20;
+
+// The expert's slots are vf + e .. vl + e, the blocks its steps fall into; four interleaved sequences of slots.
+template <int V, int THREADS>
+__device__ __forceinline__ void reduce_expert(const ReduceArgs &A, unsigned block, float *smem)
 {
-    __shared__ float red[kRedSeqs][kRedElems];
-    const int ex = threadIdx.x % kRedElems, sq = threadIdx.x / kRedElems;
-    const size_t slot = router_slot_floats(ds, Hr, E);
-    const size_t t = (size_t)blockIdx.x * kRedElems + ex;
-    float acc = 0.f;
-    if (t < slot) {
+    typedef float vec __attribute__((ext_vector_type(V)));
+    constexpr int SEQS = 4, ELEMS = THREADS / SEQS;
+    vec *red = (vec *)smem;   // [SEQS][ELEMS]
+    const int e = (int)(block % (unsigned)A.E), lane = threadIdx.x & 63;
+    const int ex = threadIdx.x % ELEMS, sq = threadIdx.x / ELEMS;
+    const size_t t = ((size_t)(block / (unsigned)A.E) * ELEMS + ex) * V;
+    const RowAxis X = row_axis(A.offsets[min(lane + 1, A.E)] - A.offsets[min(lane, A.E)], A.step, A.blocks, lane);
+    const int first = __builtin_amdgcn_readlane(X.first, e), steps = __builtin_amdgcn_readlane(X.steps, e);
+    // position first is the expert's overhead; its steps are first + 1 .. first + steps
+    const int vf = (first + 1) / X.share, vl = steps > 0 ? (first + steps) / X.share : vf - 1;
+    vec acc = {};
+    if (t < A.eslot) {
+        const float *src = A.epart + (size_t)e * A.eslot + t;
 #pragma unroll 4
-        for (int b = sq; b < nslots; b += kRedSeqs) acc += part[(size_t)b * slot + t];
+        for (int v = vf + sq; v <= vl; v += SEQS) acc += *(const vec *)(src + (size_t)v * A.eslot);
     }
-    red[sq][ex] = acc;
+    red[sq * ELEMS + ex] = acc;
     __syncthreads();
-    if (sq != 0 || t >= slot) return;
+    if (sq != 0 || t >= A.eslot) return;
+    acc = vec{};
+#pragma unroll
+    for (int q = 0; q < SEQS; ++q) acc += red[q * ELEMS + ex];
+    const size_t nW = (size_t)A.ds * A.He;
+    if (t < nW) *(vec *)(A.g.W1 + (size_t)e * nW + t) = acc;
+    else if (t < 2 * nW) *(vec *)(A.g.W2 + (size_t)e * nW + (t - nW)) = acc;
+    else if (t < 2 * nW + A.He) *(vec *)(A.g.b1 + (size_t)e * A.He + (t - 2 * nW)) = acc;
+    else *(vec *)(A.g.b2 + (size_t)e * A.ds + (t - 2 * nW - A.He)) = acc;
+}
+
+// Eight interleaved sequences of slots.
+template <int THREADS>
+__device__ __forceinline__ void reduce_router(const ReduceArgs &A, unsigned block, float *red /* [SEQS][ELEMS] */)
+{
+    constexpr int SEQS = 8, ELEMS = THREADS / SEQS;
+    const int ex = threadIdx.x % ELEMS, sq = threadIdx.x / ELEMS;
+    const size_t t = (size_t)block * ELEMS + ex;
+    float acc = 0.f;
+    if (t < A.rslot) {
+#pragma unroll 4
+        for (int b = sq; b < A.nslots; b += SEQS) acc += A.rpart[(size_t)b * A.rslot + t];
+    }
+    red[sq * ELEMS + ex] = acc;
+    __syncthreads();
+    if (sq != 0 || t >= A.rslot) return;
     acc = 0.f;
 #pragma unroll
-    for (int q = 0; q < kRedSeqs; ++q) acc += red[q][ex];   // fixed order
-    const size_t n1 = (size_t)ds * Hr, n2 = (size_t)Hr * E;
-    if (t < n1) dWr1[t] = acc;
-    else if (t < n1 + n2) dWr2[t - n1] = acc;
-    else if (t < n1 + n2 + Hr) dbr1[t - n1 - n2] = acc;
-    else dbr2[t - n1 - n2 - Hr] = acc;
+    for (int q = 0; q < SEQS; ++q) acc += red[q * ELEMS + ex];
+    const size_t n1 = (size_t)A.ds * A.Hr, n2 = (size_t)A.Hr * A.E;
+    if (t < n1) A.g.Wr1[t] = acc;
+    else if (t < n1 + n2) A.g.Wr2[t - n1] = acc;
+    else if (t < n1 + n2 + A.Hr) A.g.br1[t - n1 - n2] = acc;
+    else A.g.br2[t - n1 - n2 - A.Hr] = acc;
+}
+
+template <int V, int THREADS, bool EXPERTS, bool ROUTER>
+__global__ __launch_bounds__(THREADS) void bwd_reduce_kernel(ReduceArgs A)
+{
+    __shared__ __align__(16) float smem[THREADS * (EXPERTS ? V : 1)];
+    if (ROUTER && (!EXPERTS || blockIdx.x < A.router_blocks)) reduce_router<THREADS>(A, blockIdx.x, smem);
+    else if (EXPERTS) reduce_expert<V, THREADS>(A, blockIdx.x - A.router_blocks, smem);
+}
+
+template <int V, int THREADS, bool EXPERTS, bool ROUTER>
+static hipError_t run_reduce(ReduceArgs A, hipStream_t s)
+{
+    const size_t per_expert = (size_t)V * THREADS / 4, per_router = THREADS / 8;
+    A.router_blocks = ROUTER ? (unsigned)((A.rslot + per_router - 1) / per_router) : 0;
+    const unsigned blocks = A.router_blocks + (EXPERTS ? (unsigned)((A.eslot + per_expert - 1) / per_expert * A.E) : 0);
+    bwd_reduce_kernel<V, THREADS, EXPERTS, ROUTER><<<blocks, THREADS, 0, s>>>(A);
+    return hipGetLastError();
+}
+
+static hipError_t launch_reduce(const ReduceArgs &A, bool experts, bool router, hipStream_t s)
+{
+    const slicemoe_weight_grads &g = A.g;
+    const bool vec4 = A.ds % 4 == 0 && A.He % 4 == 0 &&
+                      (((uintptr_t)g.W1 | (uintptr_t)g.b1 | (uintptr_t)g.W2 | (uintptr_t)g.b2 | (uintptr_t)A.epart) & 15) == 0;
+    if (!experts) return run_reduce<1, 512, false, true>(A, s);
+    if (!router) return vec4 ? run_reduce<4, 256, true, false>(A, s) : run_reduce<1, 256, true, false>(A, s);
+    return vec4 ? run_reduce<4, 512, true, true>(A, s) : run_reduce<1, 512, true, true>(A, s);
 }
 
 // What bounds the slice width and the router of a backward pass (the caller compares it with 60 KiB): eight rows of x and
@@ -108,8 +187,7 @@ BackwardPlan backward_plan(const slicemoe_config &c)
 // p * 2^38 (at most 2^22 * k assignments: no overflow in 64 bits; bits below 2^-38 of a tiny p are rounded off).
 // Bound by launches and latency (a few hundred KiB to read): every block stores its sums in a slot of its own, which the
 // one-block kernel behind it adds up, so nothing has to be cleared first; and only the router's kernels need the result,
-// so the two run behind the expert rows: beside the weight gradients where those are on the other stream, else behind their
-// reduction.
+// so the two run behind the expert rows: beside the weight gradients where those are on the other stream.
 constexpr float kCapScale = 274877906944.f;   // 2^38
 
 __global__ __launch_bounds__(kCapThreads) void bwd_cap_sums_kernel(const int32_t *__restrict__ idx, const float *__restrict__ pk,
@@ -256,7 +334,12 @@ hipError_t launch_backward(const slicemoe_config &c, const void *h, const slicem
         e = launch_backward_expert_generic(c, h, w, d_out, pk, offsets, perm, eslot, dxrow, dpk, epart, s);
         if (e != hipSuccess) return e;
     }
-    if ((e = launch_backward_reduce_segments(c, offsets, epart, eslot, g, se)) != hipSuccess) return e;
+    const size_t rslot = router_slot_floats(ds, c.Hr, c.E);
+    const BackwardWeightsPlan W = backward_mfma_shape(c) ? backward_weights_plan(c) : backward_generic_plan(c);
+    const ReduceArgs sums = {epart, offsets, W.step, W.blocks, eslot, rpart, (int)P.router_slots, rslot, 0, ds, c.He, c.Hr, c.E, g};
+    // the experts' slots: at once, on the stream that fills them, or together with the router's (see kReduceApartBytes)
+    const bool apart = se != s || ((size_t)P.expert_slots * eslot + (size_t)P.router_slots * rslot) * sizeof(float) > kReduceApartBytes;
+    if (apart && (e = launch_reduce(sums, true, false, se)) != hipSuccess) return e;
 
     if (v.cap_alpha != 0.f) {
         const int blocks = cap_blocks(Na);
@@ -270,7 +353,6 @@ hipError_t launch_backward(const slicemoe_config &c, const void *h, const slicem
         v.capg = capg;
     }
 
-    const size_t rslot = router_slot_floats(ds, c.Hr, c.E);
     if (backward_router_mfma_shape(c)) {
         e = launch_backward_router_mfma(c, h, v, drop_u, rate, idx, inv, dpk, dxrow, d_h, ws + P.router_scratch,
                                         rslot, rpart, s);
@@ -279,9 +361,7 @@ hipError_t launch_backward(const slicemoe_config &c, const void *h, const slicem
         e = launch_backward_router_generic(c, h, w, v, drop_u, rate, idx, inv, dpk, dxrow, d_h, rslot, rpart, s);
         if (e != hipSuccess) return e;
     }
-    bwd_reduce_router_kernel<<<(unsigned)((rslot + kRedElems - 1) / kRedElems), kRedElems * kRedSeqs, 0, s>>>(rpart, (int)P.router_slots, ds, c.Hr, c.E, g.Wr1,
-                                                                           g.br1, g.Wr2, g.br2);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if ((e = launch_reduce(sums, !apart, true, s)) != hipSuccess) return e;
     return joiner.join();
 }
 

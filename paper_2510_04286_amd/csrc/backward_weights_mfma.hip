@@ -466,43 +466,6 @@ __global__ __launch_bounds__(WAVES * 64, MINWAVES) void bwd_weights_kernel(
     }
 }
 
-// ------------------------------------------------------------------------------------------------ sum of the slots
-// One block per expert and 64 groups of V slot elements; the expert's slots are vf + e .. vl + e, the blocks its steps
-// fall into.  kSegSeqs interleaved sequences of slots, added up in a fixed order.
-constexpr int kSegElems = 64, kSegSeqs = 4;
-template <int V>
-__global__ __launch_bounds__(kSegElems * kSegSeqs) void bwd_reduce_segments_kernel(
-    const float *__restrict__ part, const int32_t *__restrict__ offsets, int ds, int He, int E, int step, int blocks, size_t slot,
-    float *__restrict__ dW1, float *__restrict__ db1, float *__restrict__ dW2, float *__restrict__ db2)
-{
-    typedef float vec __attribute__((ext_vector_type(V)));
-    __shared__ vec red[kSegSeqs][kSegElems];
-    const int e = blockIdx.x, lane = threadIdx.x & 63;
-    const int ex = threadIdx.x % kSegElems, sq = threadIdx.x / kSegElems;
-    const size_t t = ((size_t)blockIdx.y * kSegElems + ex) * V;
-    const RowAxis A = row_axis(offsets[min(lane + 1, E)] - offsets[min(lane, E)], step, blocks, lane);
-    const int first = __builtin_amdgcn_readlane(A.first, e), steps = __builtin_amdgcn_readlane(A.steps, e);
-    // position first is the expert's overhead; its steps are first + 1 .. first + steps
-    const int vf = (first + 1) / A.share, vl = steps > 0 ? (first + steps) / A.share : vf - 1;
-    vec acc = {};
-    if (t < slot) {
-        const float *src = part + (size_t)e * slot + t;
-#pragma unroll 4
-        for (int v = vf + sq; v <= vl; v += kSegSeqs) acc += *(const vec *)(src + (size_t)v * slot);
-    }
-    red[sq][ex] = acc;
-    __syncthreads();
-    if (sq != 0 || t >= slot) return;
-    acc = vec{};
-#pragma unroll
-    for (int q = 0; q < kSegSeqs; ++q) acc += red[q][ex];
-    const size_t nW = (size_t)ds * He;
-    if (t < nW) *(vec *)(dW1 + (size_t)e * nW + t) = acc;
-    else if (t < 2 * nW) *(vec *)(dW2 + (size_t)e * nW + (t - nW)) = acc;
-    else if (t < 2 * nW + He) *(vec *)(db1 + (size_t)e * He + (t - 2 * nW)) = acc;
-    else *(vec *)(db2 + (size_t)e * ds + (t - 2 * nW - He)) = acc;
-}
-
 // ------------------------------------------------------------------------------------------------------ host
 // Instantiations by slice width: wavefronts per block, row buffers, weights in LDS, fused, terms, wavefronts per SIMD the
 // registers allow.
@@ -584,20 +547,6 @@ hipError_t launch_backward_weights(const slicemoe_config &c, const BwdPacked &L,
     SLICEMOE_WEIGHTS(192, 4, 1, true, false, 1)
 #undef SLICEMOE_WEIGHTS
     return hipErrorInvalidValue;
-}
-
-hipError_t launch_backward_reduce_segments(const slicemoe_config &c, const int32_t *offsets, const float *part, size_t slot,
-                                           const slicemoe_weight_grads &g, hipStream_t s)
-{
-    const BackwardWeightsPlan W = backward_mfma_shape(c) ? backward_weights_plan(c) : backward_generic_plan(c);
-    const int ds = c.d / c.S;
-    const bool vec4 = ds % 4 == 0 && c.He % 4 == 0 &&
-                      (((uintptr_t)g.W1 | (uintptr_t)g.b1 | (uintptr_t)g.W2 | (uintptr_t)g.b2 | (uintptr_t)part) & 15) == 0;
-    const size_t items = vec4 ? slot / 4 : slot;
-    const dim3 grid((unsigned)c.E, (unsigned)((items + kSegElems - 1) / kSegElems));
-    if (vec4) bwd_reduce_segments_kernel<4><<<grid, kSegElems * kSegSeqs, 0, s>>>(part, offsets, ds, c.He, c.E, W.step, W.blocks, slot, g.W1, g.b1, g.W2, g.b2);
-    else bwd_reduce_segments_kernel<1><<<grid, kSegElems * kSegSeqs, 0, s>>>(part, offsets, ds, c.He, c.E, W.step, W.blocks, slot, g.W1, g.b1, g.W2, g.b2);
-    return hipGetLastError();
 }
 
 }  // namespace slicemoe

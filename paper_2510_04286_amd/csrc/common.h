@@ -183,10 +183,7 @@ hipError_t launch_backward_expert_mfma(const slicemoe_config &c, const void *h, 
                                        const float *pk, const int32_t *offsets, const int32_t *perm, void *packed,
                                        size_t slot_floats, float *dxrow, float *dpk, float *part, hipStream_t s,
                                        const SideStream *side = nullptr);
-// its slots of partial weight gradients, and their sum into the gradients
-long long backward_weights_slots(const slicemoe_config &c);
-hipError_t launch_backward_reduce_segments(const slicemoe_config &c, const int32_t *offsets, const float *part, size_t slot,
-                                           const slicemoe_weight_grads &g, hipStream_t s);
+long long backward_weights_slots(const slicemoe_config &c);   // its slots of partial weight gradients
 // The fp32 backward of every other shape (backward_generic.hip): same outputs.
 long long backward_generic_expert_slots(const slicemoe_config &c);
 long long backward_generic_router_slots(const slicemoe_config &c);
