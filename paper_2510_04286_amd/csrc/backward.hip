@@ -152,12 +152,11 @@ size_t backward_lds_bytes(const slicemoe_config &c)
     return expert > router ? expert : router;
 }
 
-// Blocks of the capacity sums: two assignments per thread and up, at most one block per CU of the chip.
-constexpr int kCapThreads = 1024;
+// Blocks of the capacity sums: eight assignments per thread and up.
 static int cap_blocks(long long Na)
 {
-    const long long want = (Na + 2 * kCapThreads - 1) / (2 * kCapThreads);
-    return (int)(want < 256 ? want : 256);
+    const long long want = (Na + 2047) / 2048;
+    return (int)(want < kCapBlocks ? want : kCapBlocks);
 }
 
 BackwardPlan backward_plan(const slicemoe_config &c)
@@ -174,58 +173,9 @@ BackwardPlan backward_plan(const slicemoe_config &c)
     p.router_part = at;  at = align_up(at + (size_t)p.router_slots * router_slot_floats((int)ds, c.Hr, c.E) * sizeof(float), 256);
     p.packed = at;  at = align_up(at + backward_mfma_packed_bytes(c), 256);
     p.router_scratch = at;  at = align_up(at + backward_router_mfma_scratch_bytes(c), 256);
-    p.cap = at;  at = align_up(at + (size_t)c.E * (cap_blocks((long long)Na) * sizeof(unsigned long long) + sizeof(float)), 256);
+    p.cap = at;  at = align_up(at + (size_t)c.E * cap_blocks((long long)Na) * sizeof(unsigned long long), 256);
     p.total = at + 256;
     return p;
-}
-
-// ---- The capacity loss (Section 3.2, Eq. 2) in its differentiable reading.  Eq. 2 is a function of integer counts;
-// the router can only be trained with it (Section 3.1) through a stand-in, and the one taken here is the usual one: the
-// count of expert e becomes the sum c_e of the final probabilities of the assignments routed to e, the loss
-// alpha CV^2(c) with the population variance, and dL_cap/dp_a = alpha (2E / S^2) (c_e(a) - Q / S), S = sum c, Q = sum c^2.
-// The sums are exact and the same on every run: each probability, a float in [0, 1], is added as the integer
-// p * 2^38 (at most 2^22 * k assignments: no overflow in 64 bits; bits below 2^-38 of a tiny p are rounded off).
-// Bound by launches and latency (a few hundred KiB to read): every block stores its sums in a slot of its own, which the
-// one-block kernel behind it adds up, so nothing has to be cleared first; and only the router's kernels need the result,
-// so the two run behind the expert rows: beside the weight gradients where those are on the other stream.
-constexpr float kCapScale = 274877906944.f;   // 2^38
-
-__global__ __launch_bounds__(kCapThreads) void bwd_cap_sums_kernel(const int32_t *__restrict__ idx, const float *__restrict__ pk,
-                                                           long long Na, int E, unsigned long long *__restrict__ slots /* [gridDim.x][E] */)
-{
-    extern __shared__ unsigned long long cap_s[];
-    for (int e = threadIdx.x; e < E; e += blockDim.x) cap_s[e] = 0ull;
-    __syncthreads();
-    for (long long a = (long long)blockIdx.x * blockDim.x + threadIdx.x; a < Na; a += (long long)gridDim.x * blockDim.x) {
-        const int ee = idx[a];
-        const int e = ee < 0 ? 0 : (ee >= E ? E - 1 : ee);
-        const float p = fminf(fmaxf(pk[a], 0.f), 1.f);
-        atomicAdd(&cap_s[e], (unsigned long long)__float2ll_rn(p * kCapScale));
-    }
-    __syncthreads();
-    for (int e = threadIdx.x; e < E; e += blockDim.x) slots[(size_t)blockIdx.x * E + e] = cap_s[e];
-}
-
-// One block.  The slots' integers are added in the LDS, then every thread adds up all E sums in the same order and writes
-// its experts' derivatives.
-__global__ __launch_bounds__(kCapThreads) void bwd_cap_coeff_kernel(const unsigned long long *__restrict__ slots, int nslots, int E,
-                                                                    float alpha, float *__restrict__ capg)
-{
-    extern __shared__ unsigned long long sums[];
-    for (int e = threadIdx.x; e < E; e += blockDim.x) sums[e] = 0ull;
-    __syncthreads();
-    for (int i = threadIdx.x; i < nslots * E; i += blockDim.x) atomicAdd(&sums[i % E], slots[i]);
-    __syncthreads();
-    double S = 0.0, Q = 0.0;
-    for (int e = 0; e < E; ++e) {
-        const double c = (double)sums[e] / (double)kCapScale;
-        S += c;
-        Q += c * c;
-    }
-    for (int e = threadIdx.x; e < E; e += blockDim.x) {
-        const double c = (double)sums[e] / (double)kCapScale;
-        capg[e] = S > 0.0 ? (float)((double)alpha * (2.0 * E / (S * S)) * (c - Q / S)) : 0.f;
-    }
 }
 
 // ---- A stream of the library's own, beside the caller's, for experts whose weight gradients are a kernel of their own (more
@@ -299,7 +249,6 @@ hipError_t launch_backward(const slicemoe_config &c, const void *h, const slicem
     const BackwardPlan P = backward_plan(c);
     char *ws = (char *)workspace;
     RouteVariant v = v_in;
-    v.capg = nullptr;
     float *dxrow = (float *)(ws + P.dxrow), *dpk = (float *)(ws + P.dpk);
     float *epart = (float *)(ws + P.expert_part), *rpart = (float *)(ws + P.router_part);
 
@@ -309,7 +258,13 @@ hipError_t launch_backward(const slicemoe_config &c, const void *h, const slicem
     jobs.count = 0;
     if (backward_mfma_shape(c)) backward_expert_pack_jobs(c, w, ws + P.packed, jobs);
     if (backward_router_mfma_shape(c)) backward_router_pack_jobs(c, w, ws + P.router_scratch, jobs);
-    if ((e = bwd_pack_launch(jobs, s)) != hipSuccess) return e;
+    CapSums cap = {0, idx, pk, Na, c.E, (unsigned long long *)(ws + P.cap)};
+    if (v.cap_alpha != 0.f) {
+        cap.blocks = cap_blocks(Na);
+        v.cap_slots = cap.slots;
+        v.cap_nslots = cap.blocks;
+    }
+    if ((e = bwd_pack_launch(jobs, cap, s)) != hipSuccess) return e;
 
     const size_t eslot = expert_slot_floats(ds, c.He);
     std::unique_lock<std::mutex> side_lock(g_side_mutex, std::defer_lock);
@@ -340,18 +295,6 @@ hipError_t launch_backward(const slicemoe_config &c, const void *h, const slicem
     // the experts' slots: at once, on the stream that fills them, or together with the router's (see kReduceApartBytes)
     const bool apart = se != s || ((size_t)P.expert_slots * eslot + (size_t)P.router_slots * rslot) * sizeof(float) > kReduceApartBytes;
     if (apart && (e = launch_reduce(sums, true, false, se)) != hipSuccess) return e;
-
-    if (v.cap_alpha != 0.f) {
-        const int blocks = cap_blocks(Na);
-        const size_t lds = (size_t)c.E * sizeof(unsigned long long);
-        unsigned long long *slots = (unsigned long long *)(ws + P.cap);
-        float *capg = (float *)(slots + (size_t)blocks * c.E);
-        bwd_cap_sums_kernel<<<blocks, kCapThreads, lds, s>>>(idx, pk, Na, c.E, slots);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        bwd_cap_coeff_kernel<<<1, kCapThreads, lds, s>>>(slots, blocks, c.E, v.cap_alpha, capg);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        v.capg = capg;
-    }
 
     if (backward_router_mfma_shape(c)) {
         e = launch_backward_router_mfma(c, h, v, drop_u, rate, idx, inv, dpk, dxrow, d_h, ws + P.router_scratch,

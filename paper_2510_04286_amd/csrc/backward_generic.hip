@@ -243,7 +243,7 @@ __global__ __launch_bounds__(kGbThreads) void bwd_router_generic_kernel(
     const T *__restrict__ Wr1, const T *__restrict__ br1, const T *__restrict__ Wr2, const T *__restrict__ br2,
     const float *__restrict__ noise, float sigma, float inv_tau, const float *__restrict__ drop_u, float rate,
     const int32_t *__restrict__ idx, const int32_t *__restrict__ inv, const float *__restrict__ dpk,
-    const float *__restrict__ capg, const float *__restrict__ dxrow, T *__restrict__ dh, int units_per_block, bool vec_hr, bool vec_e,
+    CapLoss cap, const float *__restrict__ dxrow, T *__restrict__ dh, int units_per_block, bool vec_hr, bool vec_e,
     float *__restrict__ part, size_t slot_floats)
 {
     typedef GenericRouterLds L;
@@ -255,6 +255,13 @@ __global__ __launch_bounds__(kGbThreads) void bwd_router_generic_kernel(
     const int nch = (int)gridDim.y, own = (int)blockIdx.y, own_c0 = own * kGrFeat, own_n = min(kGrFeat, ds - own_c0);
     const long long n_begin = (long long)blockIdx.x * units_per_block * kGbRows;
     const long long n_end = min(Ns, n_begin + (long long)units_per_block * kGbRows);
+    __shared__ float capg_s[64];
+    if (cap.slots != nullptr) {
+        capacity_part<kGbWaves>(cap, E, tid, (unsigned long long *)us);
+        __syncthreads();
+        capacity_derivatives<kGbWaves>(cap, E, tid, (const unsigned long long *)us, capg_s);
+        __syncthreads();
+    }
     const int ET = (E + 31) / 32, hid = wave * 32 + jj, hidc = min(hid, Hr - 1);
     const bool hok = hid < Hr, quads = (ds & 3) == 0;
 
@@ -385,7 +392,7 @@ __global__ __launch_bounds__(kGbThreads) void bwd_router_generic_kernel(
                     for (int o = 8; o > 0; o >>= 1) mine += __shfl_xor(mine, o);
                     psel[j] = mine;
                     dpf[j] = inv[a] >= 0 ? dpk[a] : 0.f;   // a capacity-dropped assignment carries no gradient from h'
-                    if (capg != nullptr) dpf[j] += capg[ej[j]];   // but it counts as assigned (capacity loss)
+                    if (cap.slots != nullptr) dpf[j] += capg_s[ej[j]];   // but it counts as assigned (capacity loss)
                     keep[j] = rate > 0.f ? !(drop_u[a] < rate) : true;
                     kept += keep[j] ? 1 : 0;
                 }
@@ -590,7 +597,8 @@ static hipError_t run_router(const slicemoe_config &c, const void *h, const slic
     if (e != hipSuccess) return e;
     kern<<<dim3((unsigned)backward_generic_router_slots(c), (unsigned)((ds + kGrFeat - 1) / kGrFeat)), kGbThreads, lds, s>>>(
         (const T *)h, Ns, ds, c.Hr, c.E, c.k, (const T *)w.Wr1, (const T *)w.br1, (const T *)w.Wr2, (const T *)w.br2,
-        v.sigma > 0.f ? v.noise : nullptr, v.sigma, v.inv_tau, rate > 0.f ? drop_u : nullptr, rate, idx, inv, dpk, v.capg, dxrow, (T *)d_h,
+        v.sigma > 0.f ? v.noise : nullptr, v.sigma, v.inv_tau, rate > 0.f ? drop_u : nullptr, rate, idx, inv, dpk,
+        CapLoss{v.cap_slots, v.cap_nslots, v.cap_alpha}, dxrow, (T *)d_h,
         generic_router_units_per_block(c), quad_aligned<T>(w.Wr1, c.Hr), quad_aligned<T>(w.Wr2, c.E), part, slot_floats);
     return hipGetLastError();
 }

@@ -120,9 +120,29 @@ __device__ __forceinline__ void pack_bias_item(const BwdPackJob &J, long long t)
     ((float *)(J.dst + (size_t)mat * J.dst_stride))[i] = i < J.K ? bf16_to_f32(J.src[(size_t)mat * J.src_stride + i]) : 0.f;
 }
 
-__global__ void bwd_pack_jobs_kernel(BwdPackJobs jobs)
+constexpr int kPackThreads = 256;
+__device__ __forceinline__ void capacity_sums(const CapSums &C)
 {
-    long long f = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    __shared__ unsigned long long sums[64];
+    if (threadIdx.x < 64) sums[threadIdx.x] = 0ull;
+    __syncthreads();
+#pragma unroll 4
+    for (long long a = (long long)blockIdx.x * kPackThreads + threadIdx.x; a < C.Na; a += (long long)C.blocks * kPackThreads) {
+        const int e = min(max(C.idx[a], 0), C.E - 1);
+        const float p = fminf(fmaxf(C.pk[a], 0.f), 1.f);
+        atomicAdd(&sums[e], (unsigned long long)__float2ll_rn(p * kCapScale));
+    }
+    __syncthreads();
+    if (threadIdx.x < C.E) C.slots[(size_t)blockIdx.x * C.E + threadIdx.x] = sums[threadIdx.x];
+}
+
+__global__ __launch_bounds__(kPackThreads) void bwd_pack_jobs_kernel(BwdPackJobs jobs, CapSums cap)
+{
+    if ((int)blockIdx.x < cap.blocks) {
+        capacity_sums(cap);
+        return;
+    }
+    long long f = (long long)(blockIdx.x - cap.blocks) * kPackThreads + threadIdx.x;
     for (int q = 0; q < jobs.count; ++q) {   // the jobs' items are numbered one job after the other
         const BwdPackJob &J = jobs.job[q];
         if (f < J.items) {
@@ -152,12 +172,13 @@ BwdPackJob bwd_pack_job(int kind, const void *src, int K, int Kv, int N, int Nv,
     return J;
 }
 
-hipError_t bwd_pack_launch(const BwdPackJobs &jobs, hipStream_t s)
+hipError_t bwd_pack_launch(const BwdPackJobs &jobs, const CapSums &cap, hipStream_t s)
 {
     long long total = 0;
     for (int q = 0; q < jobs.count; ++q) total += jobs.job[q].items;
-    if (total == 0) return hipSuccess;
-    bwd_pack_jobs_kernel<<<(unsigned)((total + 255) / 256), 256, 0, s>>>(jobs);
+    const long long blocks = (total + kPackThreads - 1) / kPackThreads + cap.blocks;
+    if (blocks == 0) return hipSuccess;
+    bwd_pack_jobs_kernel<<<(unsigned)blocks, kPackThreads, 0, s>>>(jobs, cap);
     return hipGetLastError();
 }
 

@@ -200,7 +200,7 @@ template <int ET, int TERMS>
 __device__ __forceinline__ void logit_gradients(const f32x16 (&gacc)[ET], const SliceDraws<ET> &D, long long n, int g, int E, int k, bool noisy,
                                                 float sigma, float inv_tau, const float *__restrict__ drop_u, float rate,
                                                 const int32_t *__restrict__ idx, const int32_t *__restrict__ inv, const float *__restrict__ dpk,
-                                                const float *__restrict__ capg, uint32_t (&dgt)[ET][TERMS][8])
+                                                bool capped, const float *capg /* [64], LDS */, uint32_t (&dgt)[ET][TERMS][8])
 {
     // ---- this lane's 16 ET logits: expert 32 et + acc_feature(r, g); noise; softmax of g / tau over the E experts
     float v[ET * 16];
@@ -246,7 +246,7 @@ __device__ __forceinline__ void logit_gradients(const f32x16 (&gacc)[ET], const 
             psel[jj] = mine + __shfl_xor(mine, 32);     // the expert sits in one of the two halves
             if (jj < kRbAhead) dpf[jj] = D.row[jj < kRbAhead ? jj : 0] >= 0 ? D.dp[jj < kRbAhead ? jj : 0] : 0.f;
             else dpf[jj] = inv[a] >= 0 ? dpk[a] : 0.f;  // a capacity-dropped assignment carries no gradient from h'
-            if (capg != nullptr) dpf[jj] += capg[min(max(ej[jj], 0), E - 1)];   // but it counts as assigned (capacity loss)
+            if (capped) dpf[jj] += capg[min(max(ej[jj], 0), E - 1)];   // but it counts as assigned (capacity loss)
             keep[jj] = drop_u != nullptr ? !((jj < kRbAhead ? D.u[jj < kRbAhead ? jj : 0] : drop_u[a]) < rate) : true;
             kept += keep[jj] ? 1 : 0;
         }
@@ -455,7 +455,7 @@ __global__ __launch_bounds__(kRbThreads) void bwd_route_logits_mfma_kernel(
     const bf16_t *__restrict__ x, long long Ns, int E, int k, const char *__restrict__ packed, RouterBwdPacked L,
     const float *__restrict__ noise, float sigma, float inv_tau, const float *__restrict__ drop_u, float rate,
     const int32_t *__restrict__ idx, const int32_t *__restrict__ inv, const float *__restrict__ dpk,
-    const float *__restrict__ capg, bf16_t *__restrict__ dg_terms /* [terms][Ns][EP] */, uint32_t *__restrict__ relu_bits)
+    CapLoss cap, bf16_t *__restrict__ dg_terms /* [terms][Ns][EP] */, uint32_t *__restrict__ relu_bits)
 {
     constexpr int KS = SliceTiles<DS>::KS, EP = ET * 32, TERMS = kRbTerms<DS>;
     extern __shared__ __align__(16) char lds[];
@@ -463,14 +463,21 @@ __global__ __launch_bounds__(kRbThreads) void bwd_route_logits_mfma_kernel(
     uint4 *w2f = w1f + kRbHT * KS * 64;                     // [8][2][ET][64]
     float *b1s = (float *)(w2f + ET * kRbHT * 2 * 64);      // [256]
     float *b2s = b1s + kRbHr;                               // [EP]
+    __shared__ unsigned long long cap_part[kRbWaves * 64];
+    __shared__ float capg_s[64];
 
     const int tid = threadIdx.x, lane = tid & 63, j = lane & 31, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (cap.slots != nullptr) capacity_part<kRbWaves>(cap, E, tid, cap_part);
     stage_bytes(packed + L.w1f, (char *)w1f, (size_t)kRbHT * KS * 1024, tid, kRbThreads);
     stage_bytes(packed + L.w2f, (char *)w2f, (size_t)ET * kRbHT * 2 * 1024, tid, kRbThreads);
     if (tid < kRbHr) b1s[tid] = ((const float *)(packed + L.b1))[tid];
     if (tid < EP) b2s[tid] = ((const float *)(packed + L.b2))[tid];
     __syncthreads();
+    if (cap.slots != nullptr) {
+        capacity_derivatives<kRbWaves>(cap, E, tid, cap_part, capg_s);
+        __syncthreads();
+    }
 
     const long long ntiles = (Ns + 31) / 32;
     for (long long tile = (long long)wave * gridDim.x + blockIdx.x; tile < ntiles; tile += (long long)gridDim.x * kRbWaves) {
@@ -486,7 +493,7 @@ __global__ __launch_bounds__(kRbThreads) void bwd_route_logits_mfma_kernel(
         router_logits<DS, ET>(xb, w1f, w2f, b1s, b2s, lane, g, gacc, act);
         SliceDraws<ET> D;
         load_draws<ET>(D, nn, g, E, k, noise, drop_u, idx, inv, dpk);
-        logit_gradients<ET, TERMS>(gacc, D, nn, g, E, k, noise != nullptr, sigma, inv_tau, drop_u, rate, idx, inv, dpk, capg, dgt);
+        logit_gradients<ET, TERMS>(gacc, D, nn, g, E, k, noise != nullptr, sigma, inv_tau, drop_u, rate, idx, inv, dpk, cap.slots != nullptr, capg_s, dgt);
         if (valid) {
             store_logit_gradients<ET, TERMS>(dgt, dg_terms, Ns, n, g);
             *(uint4 *)(relu_bits + (n * 2 + g) * 4) = make_uint4(act[0], act[1], act[2], act[3]);
@@ -558,7 +565,7 @@ __global__ __launch_bounds__(THREADS) void bwd_route_slices_mfma_kernel(
     const bf16_t *__restrict__ x, long long Ns, int E, int k, const char *__restrict__ packed, RouterBwdPacked L,
     const float *__restrict__ noise, float sigma, float inv_tau, const float *__restrict__ drop_u, float rate,
     const int32_t *__restrict__ idx, const int32_t *__restrict__ inv, const float *__restrict__ dpk,
-    const float *__restrict__ capg, const float *__restrict__ dxrow, bf16_t *__restrict__ dg_terms /* [terms][Ns][EP] */, bf16_t *__restrict__ dh)
+    CapLoss cap, const float *__restrict__ dxrow, bf16_t *__restrict__ dg_terms /* [terms][Ns][EP] */, bf16_t *__restrict__ dh)
 {
     constexpr int KS = SliceTiles<DS>::KS, OT = SliceTiles<DS>::OT, EP = ET * 32, TERMS = kRbTerms<DS>, kWaves = THREADS / 64;
     extern __shared__ __align__(16) char lds[];
@@ -568,7 +575,8 @@ __global__ __launch_bounds__(THREADS) void bwd_route_slices_mfma_kernel(
     uint4 *w1c = w2c + ET * 2 * kRbHT * 64;                 // [8][2][OT][64]
     float *b1s = (float *)(w1c + kRbHT * 2 * OT * 64);      // [256]
     float *b2s = b1s + kRbHr;                               // [EP]
-    float *stg_all = b2s + EP;                              // [wavefronts][SROWS][kRbStageRow]
+    float *capg_s = b2s + EP;                               // [64]
+    float *stg_all = capg_s + 64;                           // [wavefronts][SROWS][kRbStageRow]; first the capacity sums' parts [wavefronts][64]
 
     const int tid = threadIdx.x, lane = tid & 63, j = lane & 31, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -587,10 +595,15 @@ __global__ __launch_bounds__(THREADS) void bwd_route_slices_mfma_kernel(
     int rows[4][kRbAhead];
     load_x(tile, xb);
     slice_rows(rows, inv, tile * 32, Ns, k, lane);
+    if (cap.slots != nullptr) capacity_part<kWaves>(cap, E, tid, (unsigned long long *)stg_all);
     stage_bytes(packed + L.w1f, (char *)w1f, (size_t)(kRbHT * KS + ET * kRbHT * 2 + ET * 2 * kRbHT + kRbHT * 2 * OT) * 1024, tid, THREADS);   // (adjacent)
     if (tid < kRbHr) b1s[tid] = ((const float *)(packed + L.b1))[tid];
     if (tid < EP) b2s[tid] = ((const float *)(packed + L.b2))[tid];
     __syncthreads();
+    if (cap.slots != nullptr) {
+        capacity_derivatives<kWaves>(cap, E, tid, (const unsigned long long *)stg_all, capg_s);
+        __syncthreads();
+    }
 
     for (; tile < ntiles; tile += step) {
         const long long n = tile * 32 + j, nn = n < Ns ? n : 0;
@@ -609,7 +622,7 @@ __global__ __launch_bounds__(THREADS) void bwd_route_slices_mfma_kernel(
         uint32_t act[4], dgt[ET][TERMS][8];
         router_logits<DS, ET>(xb, w1f, w2f, b1s, b2s, lane, g, gacc, act);
         load_x(tile + step, xb);
-        logit_gradients<ET, TERMS>(gacc, D, nn, g, E, k, noise != nullptr, sigma, inv_tau, drop_u, rate, idx, inv, dpk, capg, dgt);
+        logit_gradients<ET, TERMS>(gacc, D, nn, g, E, k, noise != nullptr, sigma, inv_tau, drop_u, rate, idx, inv, dpk, cap.slots != nullptr, capg_s, dgt);
         if (n < Ns) store_logit_gradients<ET, TERMS>(dgt, dg_terms, Ns, n, g);
         input_gradients<DS, ET>(dgt, act, w2c, w1c, lane, dx);
         int next[4][kRbAhead];
@@ -849,7 +862,7 @@ static size_t inputs_lds(int OT, int ET)
 // One kernel for the logits and the inputs: wavefronts per block (0: the fragments of both do not fit the LDS), gradient rows
 // requested ahead, staging rows.
 template <int DS, int ET> struct RouterFused {
-    static constexpr size_t weights = (size_t)(kRbHT * SliceTiles<DS>::KS + 4 * ET * kRbHT + kRbHT * 2 * SliceTiles<DS>::OT) * 1024 + (kRbHr + 32 * ET) * 4;
+    static constexpr size_t weights = (size_t)(kRbHT * SliceTiles<DS>::KS + 4 * ET * kRbHT + kRbHT * 2 * SliceTiles<DS>::OT) * 1024 + (kRbHr + 32 * ET + 64) * 4;
     static constexpr size_t row = (size_t)kRbStageRow * 4;
     static constexpr int SROWS = weights + 8 * 32 * row <= 160 * 1024 ? 32 : 16, AHEAD = SROWS == 32 ? kRbAhead : 0;   // (no registers for them at the wider shapes)
     static constexpr int waves = weights + 8 * SROWS * row <= 160 * 1024 ? 8 : 0;
@@ -909,13 +922,14 @@ static hipError_t run_router_mfma(const slicemoe_config &c, const RouterBwdPacke
     const long long Ns = (long long)c.T * c.S;
     const long long ntiles = (Ns + 31) / 32, units = (ntiles + kRbWaves - 1) / kRbWaves;
     hipError_t e;
+    const CapLoss cap = {v.cap_slots, v.cap_nslots, v.cap_alpha};
     typedef RouterFused<DS, ET> F;
     if constexpr (F::waves > 0) {
         auto fk = bwd_route_slices_mfma_kernel<DS, ET, F::waves * 64, F::AHEAD, F::SROWS>;
         if ((e = grant_dynamic_lds((const void *)fk, F::lds)) != hipSuccess) return e;
         const long long blocks = num_compute_units() < ntiles ? num_compute_units() : ntiles;   // (a small batch spreads over all CUs)
         fk<<<(int)blocks, F::waves * 64, F::lds, s>>>((const bf16_t *)h, Ns, c.E, c.k, pb, L, v.sigma > 0.f ? v.noise : nullptr, v.sigma, v.inv_tau,
-                                                      rate > 0.f ? drop_u : nullptr, rate, idx, inv, dpk, v.capg, dxrow, dg, (bf16_t *)d_h);
+                                                      rate > 0.f ? drop_u : nullptr, rate, idx, inv, dpk, cap, dxrow, dg, (bf16_t *)d_h);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     } else {
         auto lk = bwd_route_logits_mfma_kernel<DS, ET>;
@@ -932,7 +946,7 @@ static hipError_t run_router_mfma(const slicemoe_config &c, const RouterBwdPacke
         if (blocks > units) blocks = units;
         lk<<<(int)blocks, kRbThreads, logits_lds(KS, ET), s>>>((const bf16_t *)h, Ns, c.E, c.k, pb, L, v.sigma > 0.f ? v.noise : nullptr,
                                                                v.sigma, v.inv_tau, rate > 0.f ? drop_u : nullptr, rate, idx, inv, dpk,
-                                                               v.capg, dg, bits);
+                                                               cap, dg, bits);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         auto ik = bwd_route_inputs_mfma_kernel<DS, ET>;
         if ((e = grant_dynamic_lds((const void *)ik, inputs_lds(OT, ET))) != hipSuccess) return e;

@@ -55,7 +55,69 @@ struct BwdPackJobs {
 };
 BwdPackJob bwd_pack_job(int kind, const void *src, int K, int Kv, int N, int Nv, size_t rs, size_t cs, size_t src_stride,
                         char *dst, size_t dst_stride, int nmat);
-hipError_t bwd_pack_launch(const BwdPackJobs &jobs, hipStream_t s);
+// In the same launch, in front: the probability sums of the capacity loss (blocks 0: none).
+struct CapSums {
+    int blocks;
+    const int32_t *idx;
+    const float *pk;
+    long long Na;
+    int E;
+    unsigned long long *slots;   // [blocks][E]
+};
+hipError_t bwd_pack_launch(const BwdPackJobs &jobs, const CapSums &cap, hipStream_t s);
+
+// ---- The capacity loss (Section 3.2, Eq. 2) in its differentiable reading.  Eq. 2 is a function of integer counts;
+// the router can only be trained with it (Section 3.1) through a stand-in, and the one taken here is the usual one: the
+// count of expert e becomes the sum c_e of the final probabilities of the assignments routed to e, the loss
+// alpha CV^2(c) with the population variance, and dL_cap/dp_a = alpha (2E / S^2) (c_e(a) - Q / S), S = sum c, Q = sum c^2.
+// The sums are exact and the same on every run: each probability, a float in [0, 1], is added as the integer
+// p * 2^38 (at most 2^22 * k assignments: no overflow in 64 bits; bits below 2^-38 of a tiny p are rounded off).
+// Bound by launches and latency (a few hundred KiB to read), so it has none of its own: up to kCapBlocks blocks in front of the weight
+// repacking store their sums in a slot each, and every block of the router's kernels adds the slots up for itself beside the
+// staging of its weights.  Forward and backward with the two kernels for it of
+// before / now: width 64, E 16, T = 2013 179.3 / 174.2 us; width 96, T = 1496 144.5 / 139.1; T = 8191 342.9 / 342.3 (they ran
+// beside the weight gradients).
+constexpr float kCapScale = 274877906944.f;   // 2^38
+constexpr int kCapBlocks = 64;
+struct CapLoss {
+    const unsigned long long *slots;   // null: no capacity loss
+    int nslots;
+    float alpha;
+};
+// Thread tid of a block of WAVES wavefronts: its part of the sums into part [WAVES][64]; then, behind a barrier, the first wavefront's
+// sums of those and the derivatives [64] (another barrier in front of their use).  E <= 64.
+template <int WAVES>
+__device__ __forceinline__ void capacity_part(const CapLoss &C, int E, int tid, unsigned long long *part)
+{
+    const int e = tid & 63, q = tid >> 6;
+    unsigned long long sum = 0ull;
+    if (e < E) {
+#pragma unroll
+        for (int i = 0; i < kCapBlocks / WAVES; ++i) {   // (unconditional: past the end the last slot is read and not added)
+            const int b = q + i * WAVES;
+            const unsigned long long v = C.slots[(size_t)min(b, C.nslots - 1) * E + e];
+            sum += b < C.nslots ? v : 0ull;
+        }
+    }
+    part[q * 64 + e] = sum;
+}
+template <int WAVES>
+__device__ __forceinline__ void capacity_derivatives(const CapLoss &C, int E, int tid, const unsigned long long *part, float *capg)
+{
+    if (tid >= 64) return;
+    unsigned long long sum = 0ull;
+#pragma unroll
+    for (int q = 0; q < WAVES; ++q) sum += part[q * 64 + tid];
+    const double c = (double)sum / (double)kCapScale;   // (zero for a lane without an expert)
+    double S = c, Q = c * c;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        S += __shfl_xor(S, o);
+        Q += __shfl_xor(Q, o);
+    }
+    capg[tid] = S > 0.0 ? (float)((double)C.alpha * (2.0 * E / (S * S)) * (c - Q / S)) : 0.f;
+}
+
 // Append what the expert part and the router part need (four and seven jobs); `packed` and `scratch` are their regions.
 void backward_expert_pack_jobs(const slicemoe_config &c, const slicemoe_weights &w, void *packed, BwdPackJobs &jobs);
 void backward_router_pack_jobs(const slicemoe_config &c, const slicemoe_weights &w, void *scratch, BwdPackJobs &jobs);

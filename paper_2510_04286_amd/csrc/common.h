@@ -142,10 +142,11 @@ struct RouteVariant {
     float rate = 0.f;                // forward only: cross-slice dropout (Section 3.3) of the selected probabilities
     const float *drop_u = nullptr;   // [Ns, k] its uniform draws; read only when rate > 0
     bool train() const { return sigma > 0.f || rate > 0.f; }
-    // backward only: weight of the capacity loss's differentiable reading (0: none), and, once the backward has
-    // computed it, the device table [E] of its derivatives with respect to each expert's probability sum
+    // backward only: weight of the capacity loss's differentiable reading (0: none), and the probability sums that
+    // the backward leaves for its router kernels (see backward.hip)
     float cap_alpha = 0.f;
-    const float *capg = nullptr;
+    const unsigned long long *cap_slots = nullptr;   // [cap_nslots][E]
+    int cap_nslots = 0;
 };
 hipError_t launch_route_generic(const slicemoe_config &c, const void *h, const slicemoe_weights &w,
                                 int32_t *idx, float *p, hipStream_t s, const RouteVariant &v = RouteVariant(),
