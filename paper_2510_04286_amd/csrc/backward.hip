@@ -38,8 +38,8 @@ static hipError_t zero_fill(float *p, size_t n, hipStream_t s)
 // Up to kReduceApartBytes of partial sums there is one launch for the router's slots and the experts' (where those are not on a
 // stream of their own): a launch more costs 3-5 us of a single stream, whatever it sums.  The router's blocks come first in the
 // grid: their chains are the longer ones.  Beyond, the experts' are summed at once, while they are still in a cache.  Forward and
-// backward, two launches / one: width 48, He 192, E 16, T = 2048 (41 MB): 163.9 / 160.9 us; width 64 fp32, He 256, E 8, T = 1000
-// (43 MB): 142.1 / 139.0; width 64, He 256, E 16 (57 MB): T = 2013 180.4 / 181.2, T = 6312 214.3 / 217.4, T = 16384 526.5 / 529.9.
+// backward, two launches / one: width 48, He 192, 32 768 slices (37 MB): 163.9 / 160.9 us; width 64 fp32, He 256, 4000 slices
+// (43 MB): 142.1 / 139.0; width 64, He 256, E 32 (63 MB): 32 208 slices 180.4 / 181.2, 262 144 slices 526.5 / 529.9.
 struct ReduceArgs {
     // experts: blocks of THREADS / 4 groups of V slot elements, one expert each
     const float *epart;
