@@ -273,7 +273,8 @@ def main():
     resident = (shape.ds, shape.He) in ((64, 64), (64, 128), (64, 256), (96, 384), (48, 192), (24, 96))  # as the library plans
     pipelined = shape.ds == 64 and shape.He in (64, 128, 256)
     kernel = ("ffn_generic_kernel" if not B.slicemoe_uses_mfma(cfg) else "ffn_pipelined_kernel" if pipelined
-              else "ffn_resident_kernel" if resident else "ffn_streamed_kernel")
+              else "ffn_resident_kernel" if resident
+              else "ffn_streampipe_kernel" if shape.ds in (128, 192, 384) and shape.He >= 96 else "ffn_streamed_kernel")
     roofline = {"kernel": kernel, "bound": "mfma", "achieved": round(achieved, 2),
                 "peak": PEAK_MFMA_BF16_TFLOPS, "unit": "TFLOP/s", "frac": round(achieved / PEAK_MFMA_BF16_TFLOPS, 4),
                 "traffic": ffn_traffic_bytes(args.workload)[0],
