@@ -9,7 +9,7 @@
 // kernels (backward_mfma.hip, backward_weights_mfma.hip, backward_router_mfma.hip) or, for every other shape and for fp32
 // storage, on fp32 kernels (backward_generic.hip).
 // Weight gradients: every block stores its partial sums in its own slot of a scratch buffer, and reduction
-// kernels adds the slots up in a fixed order (device-wide atomic adds cost more than the arithmetic, and their order
+// kernels add the slots up in a fixed order (device-wide atomic adds cost more than the arithmetic, and their order
 // varies from run to run; this way the result is reproducible bit for bit).
 #include <mutex>
 
