@@ -60,7 +60,8 @@ static RouterBwdPacked router_bwd_layout(int ds, int ET)
 
 // ------------------------------------------------------------------------------------------ stages of the slice kernels
 // ReLU of a hidden pre-activation, at most twice the largest fp16 value (what the two fp16 terms of the hidden layer can hold): a median
-// takes its operands as they are, where a maximum would first spend an instruction on quieting one.  0 for NaN.
+// takes its operands as they are, where a maximum would first spend an instruction on quieting one.  0 for NaN; +Inf is capped too, see
+// split_pair_f16.
 __device__ __forceinline__ float relu_capped(float a) { return __builtin_amdgcn_fmed3f(a, 0.f, 131008.f); }
 // The ReLU pattern of 32 hidden units in one word, the first unit in the top bit: shifted up by one with the bit of a unit below
 // (r >= 0 is above zero exactly if adding 2^31 - 1 to its bit pattern reaches the sign bit).
@@ -68,11 +69,14 @@ __device__ __forceinline__ uint32_t push_active(uint32_t bits, float r)
 {
     return __builtin_amdgcn_alignbit(bits, (uint32_t)__float_as_int(r) + 0x7fffffffu, 31);
 }
-// Two-term fp16 split of a pair of hidden activations: the round-toward-zero conversion of the pair, and per activation one
-// mixed-precision multiply-add r - u0 rounded to fp16.
-__device__ __forceinline__ void split_pair_f16(float r0, float r1, uint32_t &u0, uint32_t &u1)
+// Two-term fp16 split of the ReLU of a pair of pre-activations a0, a1, whose capped ReLU is r0, r1: the round-toward-zero conversion of the
+// pair, negative halves (and NaN) to zero, and per activation one mixed-precision multiply-add r - u0 rounded to fp16.  An infinite
+// pre-activation stays one in the first term, as in the forward's router, and its second is -Inf: NaN in the logits of the slice, and so in its
+// gradients.  (The first term from r0, r1 would be 65504: finite gradients of a slice whose output is not.)
+__device__ __forceinline__ void split_pair_f16(float a0, float a1, float r0, float r1, uint32_t &u0, uint32_t &u1)
 {
-    u0 = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(r0, r1));
+    const r_h2 hi = __builtin_elementwise_max(__builtin_bit_cast(r_h2, __builtin_amdgcn_cvt_pkrtz(a0, a1)), r_h2{0, 0});
+    u0 = __builtin_bit_cast(uint32_t, hi);
     asm("v_fma_mixlo_f16 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(u1) : "v"(u0), "v"(r0));
     asm("v_fma_mixhi_f16 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "+v"(u1) : "v"(u0), "v"(r1));
 }
@@ -132,7 +136,7 @@ __device__ __forceinline__ void router_logits(const bf16x8 (&xb)[SliceTiles<DS>:
                 for (int i = 0; i < 8; ++i) {
                     const float r0 = relu_capped(acc[2 * i]), r1 = relu_capped(acc[2 * i + 1]);
                     bits = push_active(push_active(bits, r0), r1);
-                    split_pair_f16(r0, r1, t0[i], t1[i]);
+                    split_pair_f16(acc[2 * i], acc[2 * i + 1], r0, r1, t0[i], t1[i]);
                 }
 #pragma unroll
                 for (int s = 0; s < 2; ++s) {
