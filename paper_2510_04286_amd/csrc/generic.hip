@@ -16,14 +16,16 @@ constexpr int kW2LdsBytes = 40 * 1024;   // Wr2 goes to LDS up to this size (fp3
 // thread per hidden unit with eight slices side by side; one thread per logit, fed from LDS; 32 lanes per slice for the
 // softmax and the selection.  2048 slices, ds = 64, Hr = 256, E = 8: 15.3 -> 11.5 us (logits from memory, softmax
 // by one thread per slice before).
-template <typename T, bool W2LDS, bool DROP>
+// HIST: leaves the block's chunk of the dispatch histogram behind.  An instance of its own: with a test of the table's address instead, the
+// large batches that have no use for it took 5% longer (the router alone, E = 8, k = 2, 131 072 slices: 142 us against 133).
+template <typename T, bool W2LDS, bool DROP, bool HIST>
 __global__ __launch_bounds__(kGenThreads) void route_generic_kernel(
     const T *__restrict__ x, long long Ns, int ds, int Hr, int E, int k,
     const T *__restrict__ Wr1, const T *__restrict__ br1, const T *__restrict__ Wr2, const T *__restrict__ br2,
     const float *__restrict__ noise, float sigma, float inv_tau, const float *__restrict__ drop_u, float rate,
-    int32_t *__restrict__ idx, float *__restrict__ pk, uint16_t *__restrict__ hist /* may be null */, int hist_stride)
+    int32_t *__restrict__ idx, float *__restrict__ pk, uint16_t *__restrict__ hist /* read only if HIST */, int hist_stride)
 {
-    __shared__ int counts[64];   // selections of this block per expert
+    __shared__ int counts[HIST ? 64 : 1];   // selections of this block per expert
     extern __shared__ __align__(16) float smem[];
     const int dsp = (ds + 3) & ~3, ust = Hr + 1;   // row strides: whole quads of features; hidden units of neighbouring slices in different banks
     float *xs = smem;                 // [kRB][dsp]
@@ -31,7 +33,7 @@ __global__ __launch_bounds__(kGenThreads) void route_generic_kernel(
     float *gs = us + kRB * ust;       // [kRB][E]
     float *w2s = gs + kRB * E;        // [Hr][E] (W2LDS only)
     const int tid = threadIdx.x;
-    if (tid < 64) counts[tid] = 0;
+    if (HIST && tid < 64) counts[tid] = 0;
     const long long n0 = (long long)blockIdx.x * kRB;
     const int rows = (int)min((long long)kRB, Ns - n0);
 
@@ -109,13 +111,13 @@ __global__ __launch_bounds__(kGenThreads) void route_generic_kernel(
         if (l == 0 && r < rows) {
             idx[n * k + j] = best;
             pk[n * k + j] = expf((bv - m) * inv_tau) / den;
-            if (hist != nullptr) atomicAdd(&counts[best], 1);
+            if (HIST) atomicAdd(&counts[best], 1);
         }
         if (best == l) v0 = -INFINITY;
         if (best == l + 32) v1 = -INFINITY;
     }
     if (DROP && l == 0 && r < rows) drop_assignments(pk + n * k, drop_u + n * k, k, rate);   // (this lane has written them)
-    if (hist != nullptr) {   // the block's chunk of the dispatch histogram
+    if (HIST) {   // the block's chunk of the dispatch histogram
         __syncthreads();
         if (tid < E) {
             uint16_t *row = hist + (size_t)tid * hist_stride;
@@ -264,10 +266,12 @@ static void run_route_generic(const slicemoe_config &c, const void *h, const sli
     const int blocks = (int)((Ns + kRB - 1) / kRB);
     const float *noise = v.sigma > 0.f ? v.noise : nullptr;
     const size_t smem = sizeof(float) * (size_t)kRB * (((ds + 3) & ~3) + c.Hr + 1 + c.E), w2 = sizeof(float) * (size_t)c.Hr * c.E;
-    const bool w2lds = w2 <= kW2LdsBytes && smem + w2 <= 64 * 1024 - 256;   // (256 bytes: the counts)
+    const bool w2lds = w2 <= kW2LdsBytes && smem + w2 <= 64 * 1024 - (hist != nullptr ? 256 : 0);   // (256 bytes: the counts)
     const bool drop = v.rate > 0.f;
-    auto kern = w2lds ? (drop ? route_generic_kernel<T, true, true> : route_generic_kernel<T, true, false>)
-                      : (drop ? route_generic_kernel<T, false, true> : route_generic_kernel<T, false, false>);
+    auto kern = hist != nullptr ? (w2lds ? (drop ? route_generic_kernel<T, true, true, true> : route_generic_kernel<T, true, false, true>)
+                                         : (drop ? route_generic_kernel<T, false, true, true> : route_generic_kernel<T, false, false, true>))
+                                : (w2lds ? (drop ? route_generic_kernel<T, true, true, false> : route_generic_kernel<T, true, false, false>)
+                                         : (drop ? route_generic_kernel<T, false, true, false> : route_generic_kernel<T, false, false, false>));
     kern<<<blocks, kGenThreads, smem + (w2lds ? w2 : 0), s>>>((const T *)h, Ns, ds, c.Hr, c.E, c.k, (const T *)w.Wr1, (const T *)w.br1,
                                                               (const T *)w.Wr2, (const T *)w.br2, noise, v.sigma, v.inv_tau,
                                                               v.drop_u, v.rate, idx, p, hist, hist_stride);
