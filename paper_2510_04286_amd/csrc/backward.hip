@@ -11,9 +11,12 @@
 // Weight gradients: every block stores its partial sums in its own slot of a scratch buffer, and reduction
 // kernels add the slots up in a fixed order (device-wide atomic adds cost more than the arithmetic, and their order
 // varies from run to run; this way the result is reproducible bit for bit).
+#include <math.h>
+
 #include <mutex>
 
 #include "bwd_mfma.h"
+#include "capacity_scale.h"
 #include "common.h"
 
 namespace slicemoe {
@@ -258,11 +261,12 @@ hipError_t launch_backward(const slicemoe_config &c, const void *h, const slicem
     jobs.count = 0;
     if (backward_mfma_shape(c)) backward_expert_pack_jobs(c, w, ws + P.packed, jobs);
     if (backward_router_mfma_shape(c)) backward_router_pack_jobs(c, w, ws + P.router_scratch, jobs);
-    CapSums cap = {0, idx, pk, Na, c.E, (unsigned long long *)(ws + P.cap)};
+    CapSums cap = {0, idx, pk, Na, c.E, ldexpf(1.f, capacity_fraction_bits(Na)), (unsigned long long *)(ws + P.cap)};
     if (v.cap_alpha != 0.f) {
         cap.blocks = cap_blocks(Na);
         v.cap_slots = cap.slots;
         v.cap_nslots = cap.blocks;
+        v.cap_scale = cap.scale;
     }
     if ((e = bwd_pack_launch(jobs, cap, s)) != hipSuccess) return e;
 

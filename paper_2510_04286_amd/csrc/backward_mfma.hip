@@ -130,7 +130,7 @@ __device__ __forceinline__ void capacity_sums(const CapSums &C)
     for (long long a = (long long)blockIdx.x * kPackThreads + threadIdx.x; a < C.Na; a += (long long)C.blocks * kPackThreads) {
         const int e = min(max(C.idx[a], 0), C.E - 1);
         const float p = fminf(fmaxf(C.pk[a], 0.f), 1.f);
-        atomicAdd(&sums[e], (unsigned long long)__float2ll_rn(p * kCapScale));
+        atomicAdd(&sums[e], (unsigned long long)__float2ll_rn(p * C.scale));
     }
     __syncthreads();
     if (threadIdx.x < C.E) C.slots[(size_t)blockIdx.x * C.E + threadIdx.x] = sums[threadIdx.x];

@@ -62,6 +62,7 @@ struct CapSums {
     const float *pk;
     long long Na;
     int E;
+    float scale;                 // a power of two
     unsigned long long *slots;   // [blocks][E]
 };
 hipError_t bwd_pack_launch(const BwdPackJobs &jobs, const CapSums &cap, hipStream_t s);
@@ -71,18 +72,17 @@ hipError_t bwd_pack_launch(const BwdPackJobs &jobs, const CapSums &cap, hipStrea
 // count of expert e becomes the sum c_e of the final probabilities of the assignments routed to e, the loss
 // alpha CV^2(c) with the population variance, and dL_cap/dp_a = alpha (2E / S^2) (c_e(a) - Q / S), S = sum c, Q = sum c^2.
 // The sums are exact and the same on every run: each probability, a float in [0, 1], is added as the integer
-// p * 2^38 (at most 2^22 * k assignments: no overflow in 64 bits; bits below 2^-38 of a tiny p are rounded off).
+// p * scale, 2^38 up to 2^26 assignments (capacity_scale.h; bits of a tiny p below that are rounded off).
 // Bound by launches and latency (a few hundred KiB to read), so it has none of its own: up to kCapBlocks blocks in front of the weight
 // repacking store their sums in a slot each, and every block of the router's kernels adds the slots up for itself beside the
 // staging of its weights.  Forward and backward with the two kernels for it of
 // before / now: 32 208 slices at width 64 179.3 / 174.2 us; at width 96
 // 11 968 slices 144.5 / 139.1, 65 528 342.9 / 342.3 (they ran beside the weight gradients).
-constexpr float kCapScale = 274877906944.f;   // 2^38
 constexpr int kCapBlocks = 64;
 struct CapLoss {
     const unsigned long long *slots;   // null: no capacity loss
     int nslots;
-    float alpha;
+    float scale, alpha;
 };
 // Thread tid of a block of WAVES wavefronts: its part of the sums into part [WAVES][64]; then, behind a barrier, the first wavefront's
 // sums of those and the derivatives [64] (another barrier in front of their use).  E <= 64.
@@ -108,7 +108,7 @@ __device__ __forceinline__ void capacity_derivatives(const CapLoss &C, int E, in
     unsigned long long sum = 0ull;
 #pragma unroll
     for (int q = 0; q < WAVES; ++q) sum += part[q * 64 + tid];
-    const double c = (double)sum / (double)kCapScale;   // (zero for a lane without an expert)
+    const double c = (double)sum / (double)C.scale;   // (zero for a lane without an expert)
     double S = c, Q = c * c;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
