@@ -126,12 +126,24 @@ __device__ __forceinline__ void capacity_sums(const CapSums &C)
     __shared__ unsigned long long sums[64];
     if (threadIdx.x < 64) sums[threadIdx.x] = 0ull;
     __syncthreads();
-#pragma unroll 4
-    for (long long a = (long long)blockIdx.x * kPackThreads + threadIdx.x; a < C.Na; a += (long long)C.blocks * kPackThreads) {
-        const int e = min(max(C.idx[a], 0), C.E - 1);
-        const float p = fminf(fmaxf(C.pk[a], 0.f), 1.f);
+    auto add = [&](int expert, float prob) {
+        const int e = min(max(expert, 0), C.E - 1);
+        const float p = fminf(fmaxf(prob, 0.f), 1.f);
         atomicAdd(&sums[e], (unsigned long long)__float2ll_rn(p * C.scale));
+    };
+    // Four assignments a load, sixteen in flight: a block is a chain of loads, and there are at most kCapBlocks of them.  (idx and pk are regions
+    // of the forward's workspace, 256-byte aligned.)
+    const long long quads = C.Na / 4, first = (long long)blockIdx.x * kPackThreads + threadIdx.x;
+#pragma unroll 4
+    for (long long q = first; q < quads; q += (long long)C.blocks * kPackThreads) {
+        const int4 e = ((const int4 *)C.idx)[q];
+        const float4 p = ((const float4 *)C.pk)[q];
+        add(e.x, p.x);
+        add(e.y, p.y);
+        add(e.z, p.z);
+        add(e.w, p.w);
     }
+    if (first < C.Na - quads * 4) add(C.idx[quads * 4 + first], C.pk[quads * 4 + first]);
     __syncthreads();
     if (threadIdx.x < C.E) C.slots[(size_t)blockIdx.x * C.E + threadIdx.x] = sums[threadIdx.x];
 }

@@ -73,11 +73,13 @@ hipError_t bwd_pack_launch(const BwdPackJobs &jobs, const CapSums &cap, hipStrea
 // alpha CV^2(c) with the population variance, and dL_cap/dp_a = alpha (2E / S^2) (c_e(a) - Q / S), S = sum c, Q = sum c^2.
 // The sums are exact and the same on every run: each probability, a float in [0, 1], is added as the integer
 // p * scale, 2^38 up to 2^26 assignments (capacity_scale.h; bits of a tiny p below that are rounded off).
-// Bound by launches and latency (a few hundred KiB to read), so it has none of its own: up to kCapBlocks blocks in front of the weight
+// Bound by launches and latency, so it has no launch of its own: up to kCapBlocks blocks in front of the weight
 // repacking store their sums in a slot each, and every block of the router's kernels adds the slots up for itself beside the
 // staging of its weights.  Forward and backward with the two kernels for it of
 // before / now: 32 208 slices at width 64 179.3 / 174.2 us; at width 96
 // 11 968 slices 144.5 / 139.1, 65 528 342.9 / 342.3 (they ran beside the weight gradients).
+// Large batches: what the loss adds to a backward, one assignment a load / four: width 64, 1 048 576 slices 29 / 10 us, width 24 60 / 18;
+// 128 slots instead of 64 save another 5 there and cost the router's kernels 1.5 us in every batch.
 constexpr int kCapBlocks = 64;
 struct CapLoss {
     const unsigned long long *slots;   // null: no capacity loss

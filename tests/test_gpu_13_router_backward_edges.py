@@ -24,6 +24,11 @@ CASES = {   # width, E, k, T, S, capacity factor, tau, sigma, rate, alpha
     "64_many_tiles": (64, 6, 3, 8231, 1, 0.9, 1.0, 0.1, 0.2, 0.0),
     "96_E30_k3": (96, 30, 3, 61, 2, 0.0, 0.8, 0.1, 0.4, 40.0),
     "96_E34_k2": (96, 34, 2, 95, 1, 0.8, 1.0, 0.1, 0.2, 40.0),
+    # the capacity loss's sums take four assignments a load: fewer than that, one left over, and more than its blocks take in one round
+    "64_cap_1": (64, 5, 1, 1, 1, 0.0, 1.0, 0.2, 0.0, 40.0),
+    "64_cap_3": (64, 2, 1, 3, 1, 0.0, 1.0, 0.2, 0.0, 40.0),
+    "64_cap_2049": (64, 7, 1, 683, 3, 0.0, 1.0, 0.2, 0.2, 400.0),
+    "24_cap_131073": (24, 9, 3, 43691, 1, 0.0, 1.0, 0.0, 0.2, 4000.0),
 }
 
 
