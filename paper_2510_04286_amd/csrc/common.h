@@ -141,7 +141,6 @@ struct RouteVariant {
     const float *noise = nullptr;    // [Ns, E] standard-normal draws; read only when sigma > 0
     float rate = 0.f;                // forward only: cross-slice dropout (Section 3.3) of the selected probabilities
     const float *drop_u = nullptr;   // [Ns, k] its uniform draws; read only when rate > 0
-    bool train() const { return sigma > 0.f || rate > 0.f; }
     // backward only: weight of the capacity loss's differentiable reading (0: none), and the probability sums that
     // the backward leaves for its router kernels (see backward.hip)
     float cap_alpha = 0.f;

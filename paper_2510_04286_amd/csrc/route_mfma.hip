@@ -63,16 +63,18 @@ __device__ __forceinline__ f32x16 load_bias_tile(const float *__restrict__ b, in
 }
 
 // What follows the second layer, for one slice per lane pair (j, j + 32) and v[16 et + r] the logit of expert
-// 32 et + acc_feature(r, g): logit noise, softmax, top-k, and the selections added to the LDS table counts[64].  TRAIN: with the
-// noise, and the cross-slice dropout of the selected probabilities (a launch of its own took 2 to 4 us of every training step);
-// instances without them, because the unused branches and arguments cost the inference router 0.6 us of 22.
-template <int ET, bool TRAIN>
+// 32 et + acc_feature(r, g): logit noise, softmax, top-k, and the selections added to the LDS table counts[64].  MODE:
+// inference; with the noise; and with the cross-slice dropout of the selected probabilities (a launch of its own took 2 to 4 us of every
+// training step).  Instances of their own, because the unused branches and arguments cost the inference router 0.6 us of 22, and those of
+// the dropout the router with the noise 0.6 of a forward's 58 (width 64, 125 000 slices, E = 32).
+enum { kRouteInference, kRouteNoise, kRouteDropout };
+template <int ET, int MODE>
 __device__ __forceinline__ void select_experts(float (&v)[ET * 16], long long n, bool valid, int g, int E, int k,
                                                const float *__restrict__ noise_, float sigma, float exp_scale,
                                                const float *__restrict__ drop_u_, float rate, int32_t *__restrict__ idx,
                                                float *pk, bool count, int *counts)
 {
-    const float *noise = TRAIN ? noise_ : nullptr, *drop_u = TRAIN ? drop_u_ : nullptr;
+    const float *noise = MODE != kRouteInference ? noise_ : nullptr, *drop_u = MODE == kRouteDropout ? drop_u_ : nullptr;
     float u2[2] = {1.f, 1.f};   // the dropout's draws of a slice with two experts: requested ahead of the softmax
     if (drop_u != nullptr && k == 2 && valid && g == 0) {
         u2[0] = drop_u[n * 2];
@@ -215,7 +217,7 @@ __device__ __forceinline__ void select_experts(float (&v)[ET * 16], long long n,
 // matrix instruction is followed by one pair's vector work of another stage -- 28.4 and 29.0 us against 27.8.)
 // W1_LDS = false (slice width 384, whose first layer of 192 KiB exceeds the LDS): the first-layer fragments are read
 // from memory as they are used; only the second layer and the biases are staged.
-template <int DS, int ET, int THREADS, bool W1_LDS, bool TRAIN>
+template <int DS, int ET, int THREADS, bool W1_LDS, int MODE>
 __global__ __launch_bounds__(THREADS) void route_mfma_kernel(
     const bf16_t *__restrict__ x, long long Ns, int E, int k, const char *__restrict__ packed,
     size_t off_w1, size_t off_b1, size_t off_b2, const float *__restrict__ noise, float sigma, float exp_scale,
@@ -323,7 +325,7 @@ __global__ __launch_bounds__(THREADS) void route_mfma_kernel(
         for (int et = 0; et < ET; ++et)
 #pragma unroll
             for (int r = 0; r < 16; ++r) v[et * 16 + r] = gacc[et][r];
-        select_experts<ET, TRAIN>(v, n, valid, g, E, k, noise, sigma, exp_scale, drop_u, rate, idx, pk, hist != nullptr, hcnt + round * 64);
+        select_experts<ET, MODE>(v, n, valid, g, E, k, noise, sigma, exp_scale, drop_u, rate, idx, pk, hist != nullptr, hcnt + round * 64);
         if (hist != nullptr) {
             // The LDS executes a wavefront's operations in order, so this wavefront's additions above are in the table
             // before its ticket; the wavefront that draws the last ticket of the chunk therefore sees everybody's.
@@ -365,7 +367,7 @@ template <int DS, int ET> struct SplitTile {
     static constexpr size_t off_cnt = off_w2 + (W2_LDS ? (size_t)ET * kRouteHT * 2048 : 0);
     static constexpr size_t lds = off_cnt + 64 * 4;
 };
-template <int DS, int ET, bool TRAIN>
+template <int DS, int ET, int MODE>
 __global__ __launch_bounds__(kSplitThreads) void route_split_kernel(
     const bf16_t *__restrict__ x, long long Ns, int E, int k, const char *__restrict__ packed, size_t off_w1, size_t off_w2,
     size_t off_b1, size_t off_b2, const float *__restrict__ noise, float sigma, float exp_scale,
@@ -464,7 +466,7 @@ __global__ __launch_bounds__(kSplitThreads) void route_split_kernel(
 #pragma unroll
             for (int r = 0; r < 16; ++r) v[et * 16 + r] = gacc[et][r];
         const long long n = (long long)(tile0 + ht) * 32 + j;
-        select_experts<ET, TRAIN>(v, n, n < Ns, g, E, k, noise, sigma, exp_scale, drop_u, rate, idx, pk, hist != nullptr, hcnt);
+        select_experts<ET, MODE>(v, n, n < Ns, g, E, k, noise, sigma, exp_scale, drop_u, rate, idx, pk, hist != nullptr, hcnt);
     }
     if (hist != nullptr) {
         __syncthreads();
@@ -541,7 +543,8 @@ static hipError_t run_split(const slicemoe_config &c, const PackedLayout &L, con
         if (g.nchunks != blocks || !g.fused || route_mfma_hist_chunk(c) != g.chunk) return hipErrorInvalidValue;
         hist_stride = g.stride;
     }
-    auto kern = v.train() ? route_split_kernel<DS, ET, true> : route_split_kernel<DS, ET, false>;
+    auto kern = v.rate > 0.f ? route_split_kernel<DS, ET, kRouteDropout>
+                             : v.sigma > 0.f ? route_split_kernel<DS, ET, kRouteNoise> : route_split_kernel<DS, ET, kRouteInference>;
     const hipError_t err = grant_dynamic_lds((const void *)kern, SplitTile<DS, ET>::lds);
     if (err != hipSuccess) return err;
     kern<<<blocks, kSplitThreads, SplitTile<DS, ET>::lds, s>>>((const bf16_t *)h, Ns, c.E, c.k, (const char *)packed, L.r_w1, L.r_w2, L.r_b1,
@@ -578,7 +581,9 @@ static hipError_t run_route(const slicemoe_config &c, const void *h, const void 
     }
     const size_t lds = (size_t)((W1_LDS ? kRouteHT * KS * 64 : 0) + ET * kRouteHT * 2 * 64) * 16 + (kRouteHr + ET * 32) * 4 +
                        (size_t)hist_rounds * 65 * 4;
-    auto kern = v.train() ? route_mfma_kernel<DS, ET, THREADS, W1_LDS, true> : route_mfma_kernel<DS, ET, THREADS, W1_LDS, false>;
+    auto kern = v.rate > 0.f ? route_mfma_kernel<DS, ET, THREADS, W1_LDS, kRouteDropout>
+                             : v.sigma > 0.f ? route_mfma_kernel<DS, ET, THREADS, W1_LDS, kRouteNoise>
+                                             : route_mfma_kernel<DS, ET, THREADS, W1_LDS, kRouteInference>;
     hipError_t err = grant_dynamic_lds((const void *)kern, lds);
     if (err != hipSuccess) return err;
     if (L.r_w2 != L.r_w1 + (size_t)kRouteHT * KS * 64 * 16) return hipErrorInvalidValue;   // the kernel copies W1 | W2 as one run
