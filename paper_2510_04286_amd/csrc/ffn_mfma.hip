@@ -1335,6 +1335,26 @@ static bool ffn_is_small(int ds, long long Na)
     return (double)Na <= units_per_cu * kResU * num_compute_units();
 }
 
+// Width 128: the pipelined streamed kernel's row tiles are 384 rows, those of ffn_streamed_kernel 512; a block per CU takes them one after
+// the other, and a round costs the latter 1.2 to 1.4 times as much.  So it is the faster one where it needs one round instead of two; and two
+// instead of three, with 256 hidden units and more and few experts (the pipelined kernel keeps an XCD's blocks on few of them), up to a quarter
+// of the third round.  An expert's last tile is half full on average.  Whole forward in us, ffn_streamed_kernel / pipelined:
+//   He  512, E  8   96 446 rows  73.5 / 67.1   102 233:  80.1 /  94.4   129 067:  87.2 /  98.3   136 811: 115.7 /  99.8
+//            E  8  193 698      103.6 / 89.4   197 572: 110.1 / 116.2   219 648: 114   / 118.5   231 488: 116.8 / 118.4
+//            E 64   80 978       79.4 / 68.5    85 837:  81.5 /  90.0   108 367:  96.0 / 102.5   114 869: 124.8 / 103.4
+//            E 48  182 526      111.0 / 93.1   186 178: 111.8 / 116.3   201 524: 123.8 / 127.6   213 860: 126.2 / 125.1
+//            E 64  182 526      112.6 / 93.8   186 178: 113.4 / 114.1   205 554: 126.0 / 124.1
+//   He   96, E 16   90 987       54.0 / 50.7    96 446:  54.6 /  59.1   121 762:  65.3 /  68.5   194 070:  90.1 /  87.6
+// Under a capacity limit the host does not know how many rows there are.
+static bool streamed_saves_a_round(const slicemoe_config &c)
+{
+    if (c.capacity_factor > 0.f) return false;
+    const double Na = (double)c.T * c.S * c.k, cus = num_compute_units();
+    const double tall = (Na / 512 + c.E / 2.) / cus, low = (Na / 384 + c.E / 2.) / cus;   // rounds, not rounded up
+    // (a hundredth of a round: how many last tiles there are depends on the selections, by two or three either way)
+    return (tall < 0.99 && low > 1.01) || (tall < 1.99 && low > 2.01 && low <= 2.25 && c.He >= 256 && c.E <= 48);
+}
+
 hipError_t launch_ffn_mfma(const slicemoe_config &c, const void *h, const float *p,
                            const int32_t *offsets, const int32_t *perm, const void *packed,
                            void *y, hipStream_t s)
@@ -1361,10 +1381,11 @@ hipError_t launch_ffn_mfma(const slicemoe_config &c, const void *h, const float 
         if (L.He == 128) return run_pipelined<64, 4, kPipeThreads>(c, L, pl, h, p, offsets, perm, experts, y, s);
         return run_pipelined<64, 2, kPipeThreads>(c, L, pl, h, p, offsets, perm, experts, y, s);
     }
-    // the pipelined streamed kernel wherever it can run: at least three hidden tiles, biases (twice) beside the weights in the LDS
+    // the pipelined streamed kernel wherever it can run (at least three hidden tiles, biases twice beside the weights in the LDS) but for the
+    // batches of width 128 that fill the other's row tiles better
     const int HT = c.He / 32;
     const size_t lds_max = (size_t)max_lds_per_block();
-    if (L.ds == 128 && HT >= 3 && streampipe_lds<128, 3>(c.He) <= lds_max) return run_streampipe<128, 3>(c, L, h, p, offsets, perm, experts, y, s);
+    if (L.ds == 128 && HT >= 3 && streampipe_lds<128, 3>(c.He) <= lds_max && !streamed_saves_a_round(c)) return run_streampipe<128, 3>(c, L, h, p, offsets, perm, experts, y, s);
     if (L.ds == 192 && HT >= 3 && streampipe_lds<192, 2>(c.He) <= lds_max) return run_streampipe<192, 2>(c, L, h, p, offsets, perm, experts, y, s);
     if (L.ds == 384 && HT >= 3 && streampipe_lds<384, 1>(c.He) <= lds_max) return run_streampipe<384, 1>(c, L, h, p, offsets, perm, experts, y, s);
     if (L.ds == 24) return run_streamed<24, 2>(c, L, pl, h, p, offsets, perm, experts, y, s);

@@ -1,18 +1,19 @@
-"""The streamed expert kernel at its edges: row tiles (of 384, 256 and 128 rows at widths 128, 192 and 384) that are full, one
-row short or one row over, experts without a row and with one, blocks with several row tiles and several experts, the fewest
+"""The streamed expert kernels at their edges: row tiles (of 384, 256 and 128 rows at widths 128, 192 and 384, of 512 where a batch of width
+128 fills those better) that are full, one row short or one row over, experts without a row and with one, blocks with several row tiles and several experts, the fewest
 hidden tiles it takes, and k that is and is not a power of two."""
 import numpy as np
 import pytest
 
 import oracle
 from paper_2510_04286_amd import workload as wl
-from tests.common import TOL_BF16, rms
+from tests.common import TOL_BF16, make_inputs, rms
 
 pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("ds,He,k,Ns,tile", [(128, 96, 2, 20000, 384), (128, 128, 3, 120000, 384), (192, 96, 3, 9001, 256), (192, 160, 2, 70000, 256),
-                                             (384, 96, 2, 3000, 128), (384, 128, 1, 40000, 128)])
+                                             (384, 96, 2, 3000, 128), (384, 128, 1, 40000, 128),
+                                             (128, 96, 1, 110000, 512), (128, 256, 2, 100000, 512)])
 def test_row_tiles(ds, He, k, Ns, tile):
     import torch
     from paper_2510_04286_amd import binding as B
@@ -46,3 +47,25 @@ def test_row_tiles(ds, He, k, Ns, tile):
     err = np.abs(got[:-1] - ref).max() / rms(ref)
     print(f"\n[width {ds} He {He}] max|err|/rms={err:.3e}")
     assert err <= TOL_BF16
+
+
+@pytest.mark.parametrize("He,E,k,Ns", [(96, 12, 1, 110000), (256, 12, 2, 100000), (512, 64, 2, 50000)])
+def test_width_128_the_other_kernel_gives_the_same_bits(He, E, k, Ns):
+    """Batches that fill the 512-row tiles of ffn_streamed_kernel better than the pipelined kernel's 384 (one round of the chip instead of
+    two, two instead of three): the first slices of such a batch have the bits that they have in one that the pipelined kernel takes."""
+    import torch
+    from paper_2510_04286_amd import binding as B
+    s, _, w = make_inputs(wl.SliceMoEShape("rounds", T=4, d=128, S=1, E=E, k=k, He=He))
+    wd = B.pack(B.config_of(s), B.weights_to_device(w, s.dtype))
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(5)
+    h = torch.randn((Ns, 128), generator=gen, device="cuda:0").to(torch.bfloat16)
+
+    def layer(n):
+        cfg = B.config_of(wl.SliceMoEShape("rounds", T=n, d=128, S=1, E=E, k=k, He=He))
+        out, ws = torch.empty((n, 128), dtype=torch.bfloat16, device="cuda:0"), B.alloc_workspace(cfg)
+        B.slicemoe_forward(cfg, h[:n], wd, out, ws)
+        torch.cuda.synchronize()
+        return out
+    n = 70000 // k
+    assert torch.equal(layer(Ns)[:n], layer(n))
