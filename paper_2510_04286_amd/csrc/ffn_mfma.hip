@@ -1321,18 +1321,30 @@ static hipError_t run_split(const slicemoe_config &c, const PackedLayout &L, con
 }
 
 // Whether the batch is for the split kernel: units (of 32 rows, two experts per slice) per CU up to which it was measured
-// to be the faster one.  Whole forward in us, other kernel / split (21 to 23 us is what four launches in a row take):
+// to be the faster one.  Whole forward in us, other kernel / split (18 to 20 us is what four launches in a row take, 21 to 23 with the host's
+// part when the rows of widths 24 to 96 were measured):
 //   width 24   0.1: 23.4 / 21.5   2: 22.9 / 21.5   3: 22.1 / 22.3   4: 23.3 / 23.8   6: 23.4 / 27.8
 //         48   0.1: 25.0 / 23.2   2: 23.3 / 23.1   2.5: 24.0 / 23.1   3: 24.1 / 25.1   4: 24.7 / 27.3
 //         64   0.1: 24.1 / 22.8   1: 22.6 / 22.6   1.5: 23.4 / 22.9   2: 23.9 / 25.2   3: 25.6 / 29.7
 //         96   0.1: 38.1 / 22.9   1: 32.0 / 25.8   2: 33.3 / 32.1   2.5: 34.8 / 34.4   3: 35.4 / 38.5   4: 36.6 / 44.3
-//         128  0.1: 49.1 / 24.4   1: 53.7 / 36.6   3: 59.9 / 54.1   3.5: 59.9 / 55.5   4: 60.1 / 61.2
-//         192  0.1: 50.8 / 28.9   1: 58.9 / 45.6   1.5: 60.0 / 46.7   2: 60.6 / 58.2   3: 64.2 / 73.9
+// The wide slices against the pipelined streamed kernel (with fewer than three hidden tiles: ffn_streamed_kernel).  The split kernel's time
+// goes up in steps, a round of a block per CU each (a block is a unit, an expert's last one counts half), so the limit is whole rounds: three and
+// two.  With many experts, which it draws into every XCD's L2, or few hidden tiles the last of them is 3 to 8% too many.
+//   128  He 512  E 16   0.1: 36.7 / 24.0   1: 40.3 / 32.6   2: 42.1 / 40.2   2.8: 44.9 / 44.0   3.2: 45.1 / 50.1   4: 45.1 / 56.8
+//                E 64   0.1: 38.5 / 25.8   1: 41.7 / 37.0   2: 43.8 / 45.5   2.8: 45.9 / 48.1   3.2: 46.2 / 54.8
+//        He  96  E 16   0.1: 25.3 / 21.8   1: 28.6 / 26.0   2: 30.3 / 31.3   2.8: 35.6 / 37.4   3.2: 37.5 / 43.2
+//        He  64  E 16   0.1: 25.8 / 21.8   1: 30.6 / 25.9   2: 32.7 / 31.3   2.8: 35.5 / 35.3   3.2: 36.0 / 39.3
+//   192  He 768  E 16   0.1: 44.4 / 29.7   1: 47.8 / 45.4   1.95: 50.4 / 48.5   2: 50.2 / 57.7   3: 53.6 / 74.1
+//                E 64   0.1: 47.6 / 35.3   1: 51.4 / 55.0   1.75: 53.0 / 57.4   1.95: 53.2 / 67.9
+//        He  96  E 16   0.1: 26.2 / 23.6   1: 29.7 / 29.9   1.95: 31.9 / 32.9   2: 32.1 / 37.1   3: 36.4 / 45.9
+//        He  64  E 16   0.1: 25.4 / 23.4   1: 29.4 / 29.9   1.75: 31.2 / 32.7   2: 31.6 / 36.9
 // Width 384 has no instantiation: its rows and accumulators take a SIMD's whole register file.
-static bool ffn_is_small(int ds, long long Na)
+static bool ffn_is_small(int ds, int E, long long Na)
 {
-    const double units_per_cu = ds == 24 ? 2 : ds == 48 || ds == 96 ? 2.5 : ds == 64 ? 1.5 : ds == 128 ? 3.5 : ds == 192 ? 2 : 0;
-    return (double)Na <= units_per_cu * kResU * num_compute_units();
+    const double units = (double)Na / kResU, cus = num_compute_units();
+    if (ds == 128 || ds == 192) return units + E / 2. <= (ds == 128 ? 3 : 2) * cus;
+    const double units_per_cu = ds == 24 ? 2 : ds == 48 || ds == 96 ? 2.5 : ds == 64 ? 1.5 : 0;
+    return units <= units_per_cu * cus;
 }
 
 // Width 128: the pipelined streamed kernel's row tiles are 384 rows, those of ffn_streamed_kernel 512; a block per CU takes them one after
@@ -1364,7 +1376,7 @@ hipError_t launch_ffn_mfma(const slicemoe_config &c, const void *h, const float 
     const PackedLayout L = packed_layout(c);
     const FfnPlan pl = plan_ffn(L);
     const char *experts = (const char *)packed + L.experts;
-    if (ffn_is_small(L.ds, Na)) {
+    if (ffn_is_small(L.ds, L.E, Na)) {
         const bool b2_first = pl.resident && L.ds == 64;   // the start of the sums in the kernel that larger batches take
         if (L.ds == 24) return run_split<24>(c, L, h, p, offsets, perm, experts, b2_first, y, s);
         if (L.ds == 48) return run_split<48>(c, L, h, p, offsets, perm, experts, b2_first, y, s);

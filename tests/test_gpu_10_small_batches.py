@@ -27,8 +27,12 @@ CASES = {
     # an expert of two hidden tiles in the pipelined kernel, whose second layer lags by a whole unit: blocks with one unit per
     # wavefront, with several, and with the rows of two experts
     "w24_first_other_ffn": shape(24, 96, 16, 2, 8208, S=16),       # 2 units per CU
-    "w192_last_split_ffn": shape(192, 768, 16, 2, 8192, S=4),
-    "w192_first_other_ffn": shape(192, 768, 16, 2, 8196, S=4),
+    "w192_last_split_ffn": shape(192, 768, 16, 2, 8064, S=4),      # two rounds: 504 units and half a unit of each expert
+    "w192_first_other_ffn": shape(192, 768, 16, 2, 8068, S=4),
+    "w192_8192": shape(192, 768, 16, 2, 8192, S=4),
+    "w192_8196": shape(192, 768, 16, 2, 8196, S=4),
+    "w128_last_split_ffn": shape(128, 96, 16, 2, 12160, S=4),      # three rounds
+    "w128_first_other_ffn": shape(128, 96, 16, 2, 12164, S=4),
     "w64_2tiles_other_ffn": shape(64, 64, 16, 2, 6400, S=4),
     "w64_2tiles_E64": shape(64, 64, 64, 3, 20000, S=4),
     "w64_2tiles_E5": shape(64, 64, 5, 2, 9000, S=4),
