@@ -93,7 +93,8 @@ def test_small_batches(name):
 
 
 @pytest.mark.parametrize("ds,He,E,k", [(24, 96, 16, 2), (48, 192, 40, 2), (64, 256, 32, 2), (64, 64, 64, 3), (64, 288, 16, 1),
-                                       (96, 384, 16, 2), (96, 160, 33, 2), (128, 512, 64, 2), (192, 768, 16, 3), (192, 96, 40, 2)])
+                                       (96, 384, 16, 2), (96, 160, 33, 2), (128, 512, 64, 2), (192, 768, 16, 3), (192, 96, 40, 2),
+                                       (128, 64, 12, 2), (192, 32, 40, 2)])
 def test_a_slice_does_not_depend_on_its_batch(ds, He, E, k):
     """Dropless, a slice's selected experts, probabilities and output are the same bits whether it comes alone, in a batch small
     enough for the split kernels of the router, the experts or both, or in a large one: every sum has one order."""

@@ -1,6 +1,7 @@
-"""The streamed expert kernels at their edges: row tiles (of 384, 256 and 128 rows at widths 128, 192 and 384, of 512 where a batch of width
-128 fills those better) that are full, one row short or one row over, experts without a row and with one, blocks with several row tiles and several experts, the fewest
-hidden tiles it takes, and k that is and is not a power of two."""
+"""The streamed expert kernels at their edges: row tiles (of 384, 256 and 128 rows at widths 128, 192 and 384, of 512 where a batch
+of width 128 fills those better) that are full, one row short or one row over, experts without a row and with one, blocks with several row tiles
+and several experts, the fewest hidden tiles that the pipelined kernel takes and the fewer that stay with the other, and k that is and is not a
+power of two."""
 import numpy as np
 import pytest
 
@@ -13,7 +14,9 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("ds,He,k,Ns,tile", [(128, 96, 2, 20000, 384), (128, 128, 3, 120000, 384), (192, 96, 3, 9001, 256), (192, 160, 2, 70000, 256),
                                              (384, 96, 2, 3000, 128), (384, 128, 1, 40000, 128),
-                                             (128, 96, 1, 110000, 512), (128, 256, 2, 100000, 512)])
+                                             (128, 96, 1, 110000, 512), (128, 256, 2, 100000, 512),
+                                             (128, 32, 2, 30000, 512), (128, 64, 3, 20000, 512), (192, 32, 2, 9001, 256), (192, 64, 3, 20000, 256),
+                                             (384, 32, 2, 3000, 128), (384, 64, 1, 40000, 128)])
 def test_row_tiles(ds, He, k, Ns, tile):
     import torch
     from paper_2510_04286_amd import binding as B

@@ -147,9 +147,9 @@ def test_combine_matches_oracle(B, name, T):
 # ------------------------------------------------------------------ expert FFN
 FFN_CASES = [("tiny", 512, 0), ("lm", 1024, 0), ("headline", 2048, 0), ("skewed", 2048, 0), ("large", 512, 0),
              ("paper", 1024, 0),       # slice width 96: three output tiles, six K-steps
-             ("paper_S4_k2", 700, 0),  # slice width 192: six output tiles, weights streamed in chunks, ragged row tiles
+             ("paper_S4_k2", 700, 0),  # slice width 192: six output tiles, ragged units of the small-batch kernel
              ("paper_S16_k2", 300, 0), ("paper_S32_k2", 150, 0),  # slice widths 48 and 24: padded K-steps and output tiles
-             ("paper_S2_k2", 1100, 0),  # slice width 384: four wavefronts per block, 24 weight chunks per row tile
+             ("paper_S2_k2", 1100, 0),  # slice width 384: four wavefronts per block, 48 hidden tiles streamed per row tile
              ("headline", 1024, 1)]  # last: generic kernels on bf16 storage
 
 
