@@ -873,6 +873,19 @@ template <int DS, int ET> struct RouterFused {
     static constexpr size_t lds = weights + waves * SROWS * row;
 };
 
+template <int DS> static bool router_fused_width(int ET) { return ET == 1 ? RouterFused<DS, 1>::waves > 0 : RouterFused<DS, 2>::waves > 0; }
+static bool router_fused(int ds, int ET)
+{
+    switch (ds) {
+    case 24: return router_fused_width<24>(ET);
+    case 48: return router_fused_width<48>(ET);
+    case 64: return router_fused_width<64>(ET);
+    case 96: return router_fused_width<96>(ET);
+    case 128: return router_fused_width<128>(ET);
+    default: return router_fused_width<192>(ET);
+    }
+}
+
 bool backward_router_mfma_shape(const slicemoe_config &c)
 {
     const int ds = c.d / c.S, ET = (c.E + 31) / 32, KS = (ds + 15) / 16, OT = (ds + 31) / 32;
@@ -881,7 +894,7 @@ bool backward_router_mfma_shape(const slicemoe_config &c)
            inputs_lds(OT, ET) <= (size_t)max_lds_per_block();
 }
 
-// scratch: the repacked router | dL/dg terms [terms][Ns][32 ET] bf16 | ReLU bits [Ns][2][4] words
+// scratch: the repacked router | dL/dg terms [terms][Ns][32 ET] bf16 | ReLU bits [Ns][2][4] words (between two kernels only)
 struct RouterBwdScratch {
     size_t dg, bits, total;
 };
@@ -891,7 +904,7 @@ static RouterBwdScratch router_bwd_scratch(const slicemoe_config &c)
     RouterBwdScratch R;
     size_t at = align_up(router_bwd_layout(c.d / c.S, (int)ET).total, 256);
     R.dg = at;     at += align_up(backward_terms(c.d / c.S) * Ns * 32 * ET * sizeof(bf16_t), 256);
-    R.bits = at;   at += align_up(Ns * 8 * sizeof(uint32_t), 256);
+    R.bits = at;   at += router_fused(c.d / c.S, (int)ET) ? 0 : align_up(Ns * 8 * sizeof(uint32_t), 256);
     R.total = at;
     return R;
 }
