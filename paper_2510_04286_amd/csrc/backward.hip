@@ -266,7 +266,7 @@ hipError_t launch_backward(const slicemoe_config &c, const void *h, const slicem
         cap.blocks = cap_blocks(Na);
         v.cap_slots = cap.slots;
         v.cap_nslots = cap.blocks;
-        v.cap_scale = cap.scale;
+        v.cap_bits = capacity_fraction_bits(Na);
     }
     if ((e = bwd_pack_launch(jobs, cap, s)) != hipSuccess) return e;
 

@@ -598,7 +598,7 @@ static hipError_t run_router(const slicemoe_config &c, const void *h, const slic
     kern<<<dim3((unsigned)backward_generic_router_slots(c), (unsigned)((ds + kGrFeat - 1) / kGrFeat)), kGbThreads, lds, s>>>(
         (const T *)h, Ns, ds, c.Hr, c.E, c.k, (const T *)w.Wr1, (const T *)w.br1, (const T *)w.Wr2, (const T *)w.br2,
         v.sigma > 0.f ? v.noise : nullptr, v.sigma, v.inv_tau, rate > 0.f ? drop_u : nullptr, rate, idx, inv, dpk,
-        CapLoss{v.cap_slots, v.cap_nslots, v.cap_scale, v.cap_alpha}, dxrow, (T *)d_h,
+        CapLoss{v.cap_slots, (short)v.cap_nslots, (short)v.cap_bits, v.cap_alpha}, dxrow, (T *)d_h,
         generic_router_units_per_block(c), quad_aligned<T>(w.Wr1, c.Hr), quad_aligned<T>(w.Wr2, c.E), part, slot_floats);
     return hipGetLastError();
 }

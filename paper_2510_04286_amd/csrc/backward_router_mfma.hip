@@ -939,7 +939,7 @@ static hipError_t run_router_mfma(const slicemoe_config &c, const RouterBwdPacke
     const long long Ns = (long long)c.T * c.S;
     const long long ntiles = (Ns + 31) / 32, units = (ntiles + kRbWaves - 1) / kRbWaves;
     hipError_t e;
-    const CapLoss cap = {v.cap_slots, v.cap_nslots, v.cap_scale, v.cap_alpha};
+    const CapLoss cap = {v.cap_slots, (short)v.cap_nslots, (short)v.cap_bits, v.cap_alpha};
     typedef RouterFused<DS, ET> F;
     if constexpr (F::waves > 0) {
         auto fk = bwd_route_slices_mfma_kernel<DS, ET, F::waves * 64, F::AHEAD, F::SROWS>;

@@ -83,8 +83,8 @@ hipError_t bwd_pack_launch(const BwdPackJobs &jobs, const CapSums &cap, hipStrea
 constexpr int kCapBlocks = 64;
 struct CapLoss {
     const unsigned long long *slots;   // null: no capacity loss
-    int nslots;
-    float scale, alpha;
+    short nslots, bits;                // bits: the sums are in units of 2^-bits
+    float alpha;
 };
 // Thread tid of a block of WAVES wavefronts: its part of the sums into part [WAVES][64]; then, behind a barrier, the first wavefront's
 // sums of those and the derivatives [64] (another barrier in front of their use).  E <= 64.
@@ -110,14 +110,15 @@ __device__ __forceinline__ void capacity_derivatives(const CapLoss &C, int E, in
     unsigned long long sum = 0ull;
 #pragma unroll
     for (int q = 0; q < WAVES; ++q) sum += part[q * 64 + tid];
-    const double c = (double)sum / (double)C.scale;   // (zero for a lane without an expert)
+    const double c = (double)sum;   // (zero for a lane without an expert)
     double S = c, Q = c * c;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
         S += __shfl_xor(S, o);
         Q += __shfl_xor(Q, o);
     }
-    capg[tid] = S > 0.0 ? (float)((double)C.alpha * (2.0 * E / (S * S)) * (c - Q / S)) : 0.f;
+    // (S, Q and c in units of the sums: what is left of the unit goes to alpha)
+    capg[tid] = S > 0.0 ? (float)(ldexp((double)C.alpha, C.bits) * (2.0 * E / (S * S)) * (c - Q / S)) : 0.f;
 }
 
 // Append what the expert part and the router part need (four and seven jobs); `packed` and `scratch` are their regions.
