@@ -864,11 +864,14 @@ static size_t inputs_lds(int OT, int ET)
 }
 
 // One kernel for the logits and the inputs: wavefronts per block (0: the fragments of both do not fit the LDS), gradient rows
-// requested ahead, staging rows.
+// requested ahead, staging rows.  The rows are requested ahead where the registers hold them: 32 per output tile beside 8 per term and expert tile
+// of dL/dg, in 256.  Backward in us, ahead / where they are added, k = 2, 262 144 slices: width 64, E = 32 359 / 380; width 24, E = 16 277 / 279, E = 64
+// 364 / 371; width 48, E = 16 541 / 553, but E = 64 (56 registers spilled) 712 / 694, 2000 slices 89.0 / 87.3.
 template <int DS, int ET> struct RouterFused {
     static constexpr size_t weights = (size_t)(kRbHT * SliceTiles<DS>::KS + 4 * ET * kRbHT + kRbHT * 2 * SliceTiles<DS>::OT) * 1024 + (kRbHr + 32 * ET + 64) * 4;
     static constexpr size_t row = (size_t)kRbStageRow * 4;
-    static constexpr int SROWS = weights + 8 * 32 * row <= 160 * 1024 ? 32 : 16, AHEAD = SROWS == 32 ? kRbAhead : 0;   // (no registers for them at the wider shapes)
+    static constexpr int SROWS = weights + 8 * 32 * row <= 160 * 1024 ? 32 : 16;
+    static constexpr int AHEAD = SROWS == 32 && 32 * SliceTiles<DS>::OT + 8 * ET * kRbTerms<DS> <= 96 ? kRbAhead : 0;   // (no registers for them at the wider shapes)
     static constexpr int waves = weights + 8 * SROWS * row <= 160 * 1024 ? 8 : 0;
     static constexpr size_t lds = weights + waves * SROWS * row;
 };
