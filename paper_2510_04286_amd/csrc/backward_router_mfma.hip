@@ -559,11 +559,11 @@ __global__ __launch_bounds__(kRbThreads) void bwd_route_inputs_mfma_kernel(
 // ------------------------------------------------------------------------------------------------ both in one
 // Where the fragments of both halves fit the LDS together: dL/dg and the ReLU pattern stay in registers, x of the next tile and the
 // first two gradient rows of every slice are requested ahead of the matrix instructions that they wait behind.
-// Bound: the latency of two wavefronts per SIMD (33 thousand cycles per tile, of which 2000 vector and 160 matrix instructions issue in
-// 12 thousand); four would not hold the gradient rows (128 registers: spills, 187 us).
+// Bound: the latency of two wavefronts per SIMD (33 thousand cycles per tile, of which 2340 vector and 160 matrix instructions issue in
+// 11 thousand); four would not hold the gradient rows (128 registers: spills, 187 us).
 // 262 144 slices at width 64, 32 experts: logits 60 + inputs 83 us -> 93 us, of which the gradient rows' loads without a branch and a
-// wait behind each are 25, the ReLU pattern in two instructions per unit, the capped median and the mixed-precision split 14.  32 768 slices
-// at width 48: 17 + 20 -> 24 us.
+// wait behind each are 25, the ReLU pattern in two instructions per unit, the capped median and the mixed-precision split 14 (the packed
+// maximum that keeps an infinity costs 1 to 3 of them).  32 768 slices at width 48: 17 + 20 -> 24 us.
 template <int DS, int ET, int THREADS, int AHEAD, int SROWS>
 __global__ __launch_bounds__(THREADS) void bwd_route_slices_mfma_kernel(
     const bf16_t *__restrict__ x, long long Ns, int E, int k, const char *__restrict__ packed, RouterBwdPacked L,

@@ -146,7 +146,7 @@ struct RouteVariant {
     float cap_alpha = 0.f;
     const unsigned long long *cap_slots = nullptr;   // [cap_nslots][E]
     int cap_nslots = 0;
-    int cap_bits = 0;
+    int cap_bits = 0;                // the sums are in units of 2^-cap_bits
 };
 hipError_t launch_route_generic(const slicemoe_config &c, const void *h, const slicemoe_weights &w,
                                 int32_t *idx, float *p, hipStream_t s, const RouteVariant &v = RouteVariant(),

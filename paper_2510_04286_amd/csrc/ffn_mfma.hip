@@ -41,7 +41,7 @@
 //             a wavefront still has to do, which keeps them finishing together.
 //   streamed  larger experts (ds = 128, He = 512: 256 KiB): a block walks row tiles and streams the weights of their expert through the
 //             LDS; software-pipelined with one wavefront per SIMD at the wide slices (128, 192, 384), in chunks of hidden tiles with two
-//             at the others.
+//             at the others, for one or two hidden tiles, and for the batches of width 128 whose rows fill its taller row tiles better.
 #include <type_traits>
 #include <utility>
 
@@ -834,6 +834,7 @@ __device__ __forceinline__ void activation_op(PairChains &c, const float (&a)[4]
 // Measured against ffn_streamed_kernel, whose two wavefronts per SIMD each wait for their own stages: width 128, He 512,
 // 4 194 304 rows 1421 -> 1315 us; width 192, He 768, 60 012 rows 51.9 -> 41.1 us, 262 144 rows 238 -> 180 us; width 384, He 1536,
 // 65 536 rows 416 -> 231 us.
+// Widths 128 and 384 spill 8 and 6 registers: addresses, fetched again once per row tile; none in the loop over the steps.
 template <int DS, int SUBS> struct StreamPipe {
     static constexpr int KS = SliceTiles<DS>::KS, OT = SliceTiles<DS>::OT;
     static constexpr int kWaves = 4, kThreads = kWaves * 64, ROWS = SUBS * 32, TM = kWaves * ROWS;   // rows of a wavefront, of a block
