@@ -8,10 +8,11 @@
 //                            p dz fed from the accumulator registers as the B operand, exactly like the forward's
 //                            second GEMM.  dL/dp = sum over the hidden units of dz u is a per-lane sum plus one
 //                            exchange with lane ^ 32.  Writes dL/dx of the rows (fp32) and dL/dp.
-//   bwd_weights_kernel       (backward_weights_mfma.hip) the transposed layout, for the weight gradients; for experts
-//                            whose hidden tiles fit one block it gives dL/dx and dL/dp too, and this kernel does not run.
+//   bwd_weights_kernel       (backward_weights_mfma.hip) the transposed layout, for the weight gradients; at width 64, for experts
+//                            whose hidden tiles fit one block, it gives dL/dx and dL/dp too, and this kernel does not run.
+//   bwd_expert_kernel        (backward_expert_mfma.hip) all of it in one pass, 16 hidden units per wavefront: widths 24, 48, 96.
 //
-// Precision: u, da, z, the activation and its derivative in fp32 (normal_cdf_pdf4); the operands of the
+// Precision: u, da, z, the activation and its derivative in fp32 (twice_gelu4); the operands of the
 // second-stage matrix instructions (p dz, a1) enter as two-term bf16 splits (hi + lo, 16 significant bits, one
 // matrix instruction per term against exact bf16 data), so the results are of fp32 grade; three terms (24 significant
 // bits) at widths 24, 48 and 192 (backward_terms), which are as close to 64-bit arithmetic as the fp32 kernels.  The kernels are
@@ -24,12 +25,12 @@ static BwdPacked bwd_packed_layout(const slicemoe_config &c)
 {
     BwdPacked L;
     const int ds = c.d / c.S, He = c.He;
-    const bool fused = backward_weights_plan(c).fused;
+    const bool onepass = backward_onepass(c), fused = backward_weights_plan(c).fused;
     const size_t dsK = (size_t)(ds + 15) / 16 * 16, dsN = (size_t)(ds + 31) / 32 * 32;
     L.w1f = 0;
     L.w2r = dsK * He * 2;
     L.w1c = L.w1d = 2 * L.w2r;
-    L.b1 = L.w1c + (fused ? dsK : dsN) * He * 2;
+    L.b1 = L.w1c + (onepass ? 0 : fused ? dsK : dsN) * He * 2;
     L.stride = align_up(L.b1 + (size_t)He * 4, 256);
     return L;
 }
@@ -242,7 +243,7 @@ __global__ __launch_bounds__(kBmTileWaves<DS> * 64) void bwd_rows_streamed_mfma_
         const bool valid = row < row_end;
         const int a = perm[valid ? row : row_begin];
         const long long n = a / k;
-        const float p = valid ? pk[a] : 0.f;
+        const float p = valid ? pk[a] : 0.f, half_p = 0.5f * p;
         const uint4 *xr = (const uint4 *)(x + n * DS), *gr = (const uint4 *)(dout + n * DS);
         bf16x8 xb[KS], gb[KS];
 #pragma unroll
@@ -285,15 +286,15 @@ __global__ __launch_bounds__(kBmTileWaves<DS> * 64) void bwd_rows_streamed_mfma_
 #pragma unroll
                 for (int qq = 0; qq < 4; ++qq) {
                     const f32x4 bb = *(const f32x4 *)(b1s + ht * 32 + 8 * qq + 4 * g);
-                    float z[4], cdf[4], dens[4], pdz[4];
+                    float z[4], act[4], slope[4], pdz[4];
 #pragma unroll
                     for (int c = 0; c < 4; ++c) z[c] = fmaf(p, u[4 * qq + c], bb[c]);
-                    normal_cdf_pdf4<TERMS == 3>(z, cdf, dens);
+                    twice_gelu4(z, act, slope);
 #pragma unroll
                     for (int c = 0; c < 4; ++c) {
-                        const float dz = da[4 * qq + c] * fmaf(z[c], dens[c], cdf[c]);
+                        const float dz = fmaf(da[4 * qq + c], slope[c], da[4 * qq + c]);   // twice dL/dz
                         dps[4 * (qq & 1) + c] = fmaf(dz, u[4 * qq + c], dps[4 * (qq & 1) + c]);
-                        pdz[c] = p * dz;
+                        pdz[c] = half_p * dz;
                     }
                     split_terms<TERMS>(pdz, pd[qq >> 1], 2 * (qq & 1));
                 }
@@ -312,7 +313,7 @@ __global__ __launch_bounds__(kBmTileWaves<DS> * 64) void bwd_rows_streamed_mfma_
         float dp = ((dps[0] + dps[1]) + (dps[2] + dps[3])) + ((dps[4] + dps[5]) + (dps[6] + dps[7]));
         dp += __shfl_xor(dp, 32);
         if (valid) {
-            if (g == 0) dpk[a] = dp;
+            if (g == 0) dpk[a] = 0.5f * dp;
             float *dst = dxrow + (size_t)row * DS;
 #pragma unroll
             for (int ot = 0; ot < OT; ++ot)
@@ -348,7 +349,6 @@ bool backward_mfma_shape(const slicemoe_config &c)
     const int ds = c.d / c.S;
     const bool width = ds == 24 || ds == 48 || ds == 64 || ds == 96 || ds == 128 || ds == 192;
     if (c.dtype != SLICEMOE_BF16 || !width || c.He % 32 != 0 || (c.flags & SLICEMOE_FLAG_FORCE_GENERIC)) return false;
-    if (backward_weights_plan(c).fused) return true;
     // the rows kernel keeps an expert's biases in the LDS, beside at least one hidden tile's fragments: hidden widths up to about
     // 31 000 (slice width 192) to 39 000 (24); the fp32 kernels take any
     size_t lds = 0;
@@ -385,17 +385,19 @@ void backward_expert_pack_jobs(const slicemoe_config &c, const slicemoe_weights 
     const BwdPacked L = bwd_packed_layout(c);
     char *pb = (char *)packed;
     const size_t wstride = (size_t)ds * He;
+    const bool onepass = backward_onepass(c);
     BwdPackJob *J = jobs.job + jobs.count;
-    jobs.count += 4;
+    jobs.count += onepass ? 3 : 4;
     // w1f: the [ds, He] matrix W1 itself; w2r: the [ds, He] matrix M[c][hidden] = W2[hidden][c]
     J[0] = bwd_pack_job(kPackLayer1, w.W1, dsK, ds, He, He, (size_t)He, 1, wstride, pb + L.w1f, L.stride, E);
     J[1] = bwd_pack_job(kPackLayer1, w.W2, dsK, ds, He, He, 1, (size_t)ds, wstride, pb + L.w2r, L.stride, E);
+    J[2] = bwd_pack_job(kPackBias, w.b1, He, He, He, He, 0, 0, (size_t)He, pb + L.b1, L.stride, E);
+    if (onepass) return;
     // w1d: W1 in 16-feature tiles.  w1c: the [He, ds] matrix M[hidden][c] = W1[c][hidden], contraction over the hidden units
     // in accumulator order
     if (backward_weights_plan(c).fused)
-        J[2] = bwd_pack_job(kPackTile16, w.W1, dsK, ds, He, He, (size_t)He, 1, wstride, pb + L.w1d, L.stride, E);
-    else J[2] = bwd_pack_job(kPackChain, w.W1, He, He, dsN, ds, 1, (size_t)He, wstride, pb + L.w1c, L.stride, E);
-    J[3] = bwd_pack_job(kPackBias, w.b1, He, He, He, He, 0, 0, (size_t)He, pb + L.b1, L.stride, E);
+        J[3] = bwd_pack_job(kPackTile16, w.W1, dsK, ds, He, He, (size_t)He, 1, wstride, pb + L.w1d, L.stride, E);
+    else J[3] = bwd_pack_job(kPackChain, w.W1, He, He, dsN, ds, 1, (size_t)He, wstride, pb + L.w1c, L.stride, E);
 }
 
 // Runs the kernels on the backward copies of the expert weights in `packed` (backward_expert_pack_jobs, launched on s before).
@@ -412,14 +414,13 @@ hipError_t launch_backward_expert_mfma(const slicemoe_config &c, const void *h, 
     const BwdPacked L = bwd_packed_layout(c);
     const char *pb = (const char *)packed;
     hipError_t e;
+    if (backward_onepass(c)) return launch_backward_expert_onepass(c, L, h, d_out, pk, offsets, perm, pb, slot_floats, part, dxrow, dpk, s);
     if (!W.fused) {
         if (side != nullptr) {
             if ((e = hipEventRecord(side->fork, s)) != hipSuccess) return e;
             if ((e = hipStreamWaitEvent(side->stream, side->fork, 0)) != hipSuccess) return e;
         }
-        e = ds == 24 ? run_rows_mfma<24>(c, L, h, d_out, pk, offsets, perm, pb, dxrow, dpk, s)
-          : ds == 48 ? run_rows_mfma<48>(c, L, h, d_out, pk, offsets, perm, pb, dxrow, dpk, s)
-          : ds == 64 ? run_rows_mfma<64>(c, L, h, d_out, pk, offsets, perm, pb, dxrow, dpk, s)
+        e = ds == 64 ? run_rows_mfma<64>(c, L, h, d_out, pk, offsets, perm, pb, dxrow, dpk, s)
           : ds == 96 ? run_rows_mfma<96>(c, L, h, d_out, pk, offsets, perm, pb, dxrow, dpk, s)
           : ds == 128 ? run_rows_mfma<128>(c, L, h, d_out, pk, offsets, perm, pb, dxrow, dpk, s)
                       : run_rows_mfma<192>(c, L, h, d_out, pk, offsets, perm, pb, dxrow, dpk, s);

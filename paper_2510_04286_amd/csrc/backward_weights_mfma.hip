@@ -17,7 +17,7 @@
 // matrix instructions that use them behind it, the weight gradients half a unit behind the activation, barriers that do not
 // wait for global memory, and the younger wavefront of a SIMD first for half of every unit.
 //
-// FUSE (experts whose hidden tiles fit one block: the benchmark shapes at width 64 and the paper's narrow slices): the
+// FUSE (experts whose hidden tiles fit one block: the benchmark shapes at width 64): the
 // same pass also gives dL/dx and dL/dp of the rows, so that z and the activation are evaluated once instead of once per
 // layout.  dx = W1 (p dz) contracts over the hidden units of ALL wavefronts, so the terms of p dz of a unit go through
 // the LDS ([hidden][row], read back transposed) and during the next unit each wavefront multiplies its 16-row, 16-feature
@@ -27,8 +27,8 @@
 // Measured, 524 288 rows, width 64, He = 256, 32 experts: rows kernel 172 us + weights kernel 283 us (both evaluating the
 // activation, the latter without prefetch and with transposes on the matrix pipe) -> 254 us (236 at the least); the partial sums of
 // the weight gradients fall from 140 MB in 1056 slots to 38 MB in 288 (their reduction 29-35 -> 12 us).  Unfused, alone on the
-// chip, at width 128, He = 512: 2.78 -> 1.09 ms for 1 048 576 rows; width 96, He = 384: 228 -> 98 us for 131 056 rows.  65 536 rows at
-// width 48: 2.9 ms of vector-ALU kernel -> 60 us, 69 us with erff and expf (see normal_cdf_pdf4).
+// chip, at width 128, He = 512: 2.78 -> 1.09 ms for 1 048 576 rows; width 96, He = 384: 228 -> 98 us for 131 056 rows.  (Widths 24
+// and 48, and 96 where backward_onepass says so: backward_expert_mfma.hip.)
 //
 // TERMS: bf16 terms of the activation and of p dz, backward_terms(DS).
 #include "bwd_mfma.h"
@@ -185,6 +185,10 @@ __global__ __launch_bounds__(WAVES * 64, MINWAVES) void bwd_weights_kernel(
             if (tid < kUnit) ao_next = ids[(unsigned)min(r0 + tid, nrows - 1)];
         };
         auto find_slices = [&]() {
+            // (Both waited for here on every path: left to their uses, the first wavefront waits for them behind the unit's stores.)
+#pragma unroll
+            for (int i = 0; i < NX; ++i) asm volatile("" : "+v"(an[i]));
+            asm volatile("" : "+v"(ao_next));
 #pragma unroll
             for (int i = 0; i < NX; ++i) an[i] = slice_of(an[i]);
         };
@@ -258,10 +262,15 @@ __global__ __launch_bounds__(WAVES * 64, MINWAVES) void bwd_weights_kernel(
         };
         float *dxs = FUSE ? dxrow + (size_t)row0 * DS : nullptr;
         auto dx_end = [&](int r0, int buf, int a) {   // stores the rows r0 ..; a: this thread's assignment
+            // (Opaque copies: an address stepped from unit to unit would be a register reloaded from scratch in front of the loop, and a wait for
+            // that reload at the end of every unit is one for the unit's stores.)
+            int jo = c16, go = G4;
+            asm volatile("" : "+v"(jo), "+v"(go));
 #pragma unroll
             for (int i = 0; i < NT; ++i) {
-                const int tile = wave + i * WAVES, row = r0 + 16 * (tile & 1) + c16, col = 16 * (tile >> 1) + 4 * G4;
-                if ((tile >> 1) < G::FT && (DS % 16 == 0 || col < DS) && row < nrows) *(f32x4 *)(dxs + (unsigned)(row * DS + col)) = dx[i];
+                const int tile = wave + i * WAVES, row = r0 + 16 * (tile & 1) + jo, col = 16 * (tile >> 1) + 4 * go;
+                if ((tile >> 1) < G::FT && (DS % 16 == 0 || col < DS) && row < nrows)   // (bytes: a segment's dL/dx is below 4 GB)
+                    *(f32x4 *)((char *)dxs + (unsigned)(row * (4 * DS) + 4 * col)) = 0.5f * dx[i];
             }
             if (tid < kUnit && r0 + tid < nrows) {
                 const float *dps = (const float *)(lds + G::off_dp) + buf * WAVES * kUnit + tid;
@@ -270,7 +279,7 @@ __global__ __launch_bounds__(WAVES * 64, MINWAVES) void bwd_weights_kernel(
                 for (int w = 0; w < WAVES; ++w) v[w] = dps[w * kUnit];
 #pragma unroll
                 for (int w = 0; w < WAVES; ++w) t += v[w];
-                dpk[a] = t;
+                dpk[a] = 0.5f * t;
             }
         };
 
@@ -350,10 +359,10 @@ __global__ __launch_bounds__(WAVES * 64, MINWAVES) void bwd_weights_kernel(
                         if (FUSE && 2 * q < WAVES) dx_load(fr, 2 * q, buf ^ 1);
                         if (half == 1 && o0 < o1) second_load(0, o0);
                         __builtin_amdgcn_sched_barrier(0);
-                        float z[4], cdf[4], dens[4], dz[4], act[4], pd[4];
+                        float z[4], dz[4], act[4], slope[4], pd[4];
 #pragma unroll
                         for (int c = 0; c < 4; ++c) z[c] = fmaf(pv[c], u[4 * q + c], bias);
-                        normal_cdf_pdf4<TERMS == 3>(z, cdf, dens);
+                        twice_gelu4(z, act, slope);
                         __builtin_amdgcn_sched_barrier(0);
                         if (FUSE && 2 * q < WAVES) dx_mma(fr);
                         if (half == 1) {
@@ -368,11 +377,7 @@ __global__ __launch_bounds__(WAVES * 64, MINWAVES) void bwd_weights_kernel(
                         if (half == 1 && o1 < o2) second_load(0, o1);
                         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                        for (int c = 0; c < 4; ++c) dz[c] = fmaf(z[c], dens[c], cdf[c]);
-#pragma unroll
-                        for (int c = 0; c < 4; ++c) dz[c] *= da[4 * q + c];
-#pragma unroll
-                        for (int c = 0; c < 4; ++c) act[c] = z[c] * cdf[c];
+                        for (int c = 0; c < 4; ++c) dz[c] = fmaf(da[4 * q + c], slope[c], da[4 * q + c]);   // twice dL/dz
 #pragma unroll
                         for (int c = 0; c < 4; ++c) pd[c] = pv[c] * dz[c];
                         split_terms<TERMS>(act, a1[half], 2 * qd);
@@ -446,11 +451,11 @@ __global__ __launch_bounds__(WAVES * 64, MINWAVES) void bwd_weights_kernel(
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
                     const int f = 32 * ot + acc_feature(i, go);
-                    if (DS % 32 == 0 || f < DS) pW1[(size_t)f * he + 32 * ht + jo] = aW1[ot][i];
-                    if (DS % 32 == 0 || 32 * ot + jo < DS) pW2[(size_t)(32 * ht + acc_feature(i, go)) * DS + 32 * ot + jo] = aW2[ot][i];
+                    if (DS % 32 == 0 || f < DS) pW1[(size_t)f * he + 32 * ht + jo] = 0.5f * aW1[ot][i];
+                    if (DS % 32 == 0 || 32 * ot + jo < DS) pW2[(size_t)(32 * ht + acc_feature(i, go)) * DS + 32 * ot + jo] = 0.5f * aW2[ot][i];
                 }
             ab1 += __shfl_xor(ab1, 32);   // the two lane groups hold different rows of the same hidden unit
-            if (go == 0) pb1[32 * ht + jo] = ab1;
+            if (go == 0) pb1[32 * ht + jo] = 0.5f * ab1;
         }
         if (grp == 0 && wave < G::NBW) {
 #pragma unroll
@@ -469,7 +474,7 @@ __global__ __launch_bounds__(WAVES * 64, MINWAVES) void bwd_weights_kernel(
 // ------------------------------------------------------------------------------------------------------ host
 // Instantiations by slice width: wavefronts per block, row buffers, weights in LDS, fused, terms, wavefronts per SIMD the
 // registers allow.
-//   width <= 64   fused where the expert's hidden tiles fit one block (He <= 256): see the header
+//   64            fused where the expert's hidden tiles fit one block (He <= 256): see the header
 //   96, 128       64 accumulators and weights per hidden tile leave no registers for the fragments (LDS) or for dL/dx
 //   192           192 accumulators: one wavefront per SIMD
 struct WeightsConfig {
@@ -479,8 +484,8 @@ struct WeightsConfig {
 static WeightsConfig weights_config(int ds, int He)
 {
     const int HT = He / 32;
-    if (ds <= 64) {
-        if (HT <= 4) return {4, ds == 24 ? 2 : 1, true};
+    if (ds == 64) {
+        if (HT <= 4) return {4, 1, true};
         return {8, 1, HT <= 8};
     }
     if (ds == 96) return {4, 2, false};
@@ -490,6 +495,7 @@ static WeightsConfig weights_config(int ds, int He)
 
 BackwardWeightsPlan backward_weights_plan(const slicemoe_config &c)
 {
+    if (backward_onepass(c)) return backward_expert_plan(c);
     BackwardWeightsPlan W;
     const WeightsConfig C = weights_config(c.d / c.S, c.He);
     const int HT = c.He / 32;
@@ -533,12 +539,6 @@ hipError_t launch_backward_weights(const slicemoe_config &c, const BwdPacked &L,
     if (ds == DS && waves == WAVES && W.fused == FUSE)                                                                              \
         return run_weights<DS, WAVES, NBUF, WLDS, FUSE, backward_terms(DS), MINW>(c, W, L, h, d_out, pk, offsets, perm, packed,      \
                                                                                   slot_floats, part, dxrow, dpk, s);
-    SLICEMOE_WEIGHTS(24, 4, 2, false, true, 2)
-    SLICEMOE_WEIGHTS(24, 8, 2, false, true, 2)
-    SLICEMOE_WEIGHTS(24, 8, 2, false, false, 2)
-    SLICEMOE_WEIGHTS(48, 4, 2, false, true, 2)
-    SLICEMOE_WEIGHTS(48, 8, 2, false, true, 2)
-    SLICEMOE_WEIGHTS(48, 8, 2, false, false, 2)
     SLICEMOE_WEIGHTS(64, 4, 2, false, true, 2)
     SLICEMOE_WEIGHTS(64, 8, 2, false, true, 2)
     SLICEMOE_WEIGHTS(64, 8, 2, false, false, 2)

@@ -1,0 +1,73 @@
+"""The one-pass expert backward (slice widths 24, 48 and 96) where its split can go wrong: hidden tiles that fill a pass of the block's
+wavefronts exactly, leave some idle, or need several passes (dL/dx and dL/dp of the passes before are read back and added to),
+one row, a ragged last unit, several units per block, every k, a capacity limit, an expert that takes all rows.  Against the fp32
+kernels, which every shape has (SLICEMOE_FLAG_FORCE_GENERIC), on the same routing.
+
+Bars.  Both sides sum in fp32; the operands of the one-pass kernel's second products have 24 significant bits at 24 and 48, 16 at 96 (two
+bf16 terms), so a summand differs by at most 2^-17 of itself at 96 and by fp32 rounding at the others, and a gradient, a sum
+of them that does not cancel below its RMS, by 2e-4 (96) or 5e-5 of that RMS; dL/dh is rounded to bf16 on both sides: one unit in the
+last place, 2^-7 relative, plus the same share of the RMS."""
+import numpy as np
+import pytest
+
+from paper_2510_04286_amd import workload as wl
+from tests.common import make_inputs, rms
+
+pytestmark = pytest.mark.gpu
+
+NAMES = ("Wr1", "br1", "Wr2", "br2", "W1", "b1", "W2", "b2")
+
+
+def shape(ds, He, E, k, T, S=4, cf=0.0):
+    return wl.SliceMoEShape("onepass", T=T, d=S * ds, S=S, E=E, k=k, He=He, capacity_factor=cf)
+
+
+CASES = {
+    "w24_1_pass_full": shape(24, 128, 4, 2, 65),      # eight tiles of 16 on eight wavefronts
+    "w24_2_passes": shape(24, 160, 3, 3, 41),         # ten: six and four
+    "w24_one_row": shape(24, 32, 1, 1, 1, S=1),
+    "w24_k8": shape(24, 96, 9, 8, 30),
+    "w48_1_pass_full": shape(48, 192, 5, 2, 100),     # twelve tiles on twelve wavefronts
+    "w48_2_passes": shape(48, 224, 7, 5, 33),         # fourteen: eight and six
+    "w48_5_passes": shape(48, 832, 2, 2, 40),         # fifty-two: twelve, twelve, twelve, twelve, four
+    "w48_capacity": shape(48, 192, 8, 2, 64, cf=0.4),
+    "w48_units_per_block": shape(48, 64, 2, 2, 3000, S=8),
+    "w96_1_pass_full": shape(96, 192, 9, 7, 29),
+    "w96_2_passes_one_unit": shape(96, 384, 16, 2, 200, S=8),
+    "w96_4_passes_one_unit": shape(96, 768, 3, 1, 77),
+    "w96_2_passes_many_units": shape(96, 224, 5, 4, 2700, S=8),   # 2700 units: ten and more per block
+    "w96_hot": shape(96, 160, 4, 1, 3000, S=4),
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_one_pass_backward_equals_the_fp32_kernels(name):
+    import torch
+    from paper_2510_04286_amd import binding as B
+    s, h, w = make_inputs(CASES[name])
+    if name.endswith("hot"):
+        w["br2"] = wl.to_storage(np.where(np.arange(s.E) == s.E - 1, 8.0, w["br2"]), s.dtype)
+    dout = B.to_device(wl.make_dout(s), s.dtype)
+    hd = B.to_device(h, s.dtype)
+    cfg = B.config_of(s)
+    wd, ws, out = B.pack(cfg, B.weights_to_device(w, s.dtype)), B.alloc_workspace(cfg), torch.empty_like(hd)
+    B.slicemoe_forward(cfg, hd, wd, out, ws)
+    got = []
+    for flags in (0, B.SLICEMOE_FLAG_FORCE_GENERIC):
+        c = B.config_of(s, flags=flags)
+        assert B.slicemoe_backward_uses_mfma(c) == (0 if flags else 1)
+        grads, d_h = B.alloc_weight_grads(c), torch.full_like(hd, 5.0)
+        for t in grads.values():
+            t.fill_(7.0)   # the call overwrites
+        bws = torch.full((B.slicemoe_backward_workspace_bytes(c),), 0xFF, dtype=torch.uint8, device="cuda:0")   # NaNs: nothing is read unwritten
+        for _ in range(2):   # the second call finds the first one's values in the workspace
+            B.slicemoe_backward(c, hd, wd, ws, dout, d_h, grads, bws)
+        torch.cuda.synchronize()
+        got.append({n: t.cpu().numpy().astype(np.float64) for n, t in grads.items()} | {"d_h": d_h.float().cpu().numpy().astype(np.float64)})
+    bar = 2e-4 if s.ds == 96 else 5e-5
+    err = {n: np.abs(got[0][n] - got[1][n]).max() / max(rms(got[1][n]), 1e-30) for n in NAMES}
+    excess = (np.abs(got[0]["d_h"] - got[1]["d_h"]) / (2.0 ** -7 * np.abs(got[1]["d_h"]) + bar * rms(got[1]["d_h"]))).max()
+    print(f"\n[{name}] dL/dh at {excess:.2f} of its bound; " + " ".join(f"{n} {e:.1e}" for n, e in err.items()))
+    assert excess <= 1.0
+    assert max(err[n] for n in ("W1", "b1", "W2", "b2")) <= bar, err
+    assert max(err.values()) <= 5e-4, err
