@@ -242,16 +242,25 @@ __device__ __forceinline__ void logit_gradients(const f32x16 (&gacc)[ET], const 
         keep[jj] = false;
         ej[jj] = -1;
         if (jj < k) {
-            const long long a = n * k + jj;
-            ej[jj] = jj < kRbAhead ? D.e[jj < kRbAhead ? jj : 0] : idx[a];
+            constexpr int LAST = kRbAhead - 1;
+            int e = D.e[min(jj, LAST)], row = D.row[min(jj, LAST)];
+            float dp = D.dp[min(jj, LAST)], u = D.u[min(jj, LAST)];
+            if (jj > LAST) {
+                const long long a = n * k + jj;
+                e = idx[a];
+                row = inv[a];
+                dp = dpk[a];
+                if (drop_u != nullptr) u = drop_u[a];
+                asm volatile("" : "+v"(e), "+v"(row), "+v"(dp), "+v"(u));   // (waited for in this branch, see arrived)
+            }
+            ej[jj] = e;
             float mine = 0.f;
 #pragma unroll
             for (int i = 0; i < ET * 16; ++i) mine = (i >> 4) * 32 + acc_feature(i & 15, g) == ej[jj] ? v[i] : mine;
             psel[jj] = mine + __shfl_xor(mine, 32);     // the expert sits in one of the two halves
-            if (jj < kRbAhead) dpf[jj] = D.row[jj < kRbAhead ? jj : 0] >= 0 ? D.dp[jj < kRbAhead ? jj : 0] : 0.f;
-            else dpf[jj] = inv[a] >= 0 ? dpk[a] : 0.f;  // a capacity-dropped assignment carries no gradient from h'
+            dpf[jj] = row >= 0 ? dp : 0.f;              // a capacity-dropped assignment carries no gradient from h'
             if (capped) dpf[jj] += capg[min(max(ej[jj], 0), E - 1)];   // but it counts as assigned (capacity loss)
-            keep[jj] = drop_u != nullptr ? !((jj < kRbAhead ? D.u[jj < kRbAhead ? jj : 0] : drop_u[a]) < rate) : true;
+            keep[jj] = drop_u != nullptr ? !(u < rate) : true;
             kept += keep[jj] ? 1 : 0;
         }
     }
@@ -363,6 +372,22 @@ __device__ __forceinline__ void input_gradients(const uint32_t (&dgt)[ET][kRbTer
     }
 }
 
+// Waits for a load here, on every path.  (The compiler waits where a value is used, for as many requests as can be in flight there on the path
+// with the fewest: behind a conditional load or store that is for all of them, the next tile's data or this tile's stores among them.)
+template <typename T, int N> __device__ __forceinline__ void arrived(T (&v)[N])
+{
+#pragma unroll
+    for (int i = 0; i < N; ++i) asm volatile("" : "+v"(v[i]));
+}
+template <int ET> __device__ __forceinline__ void arrived(SliceDraws<ET> &D)
+{
+    arrived(D.noise);
+    arrived(D.e);
+    arrived(D.row);
+    arrived(D.dp);
+    arrived(D.u);
+}
+
 // Rows of the per-wavefront staging tile are 36 floats apart: 16-byte reads at a stride of one row then fall into
 // distinct banks.
 constexpr int kRbStageRow = 36;
@@ -394,14 +419,24 @@ __device__ __forceinline__ void slice_rows(int (&rows)[4][kRbAhead], const int32
         for (int jj = 0; jj < kRbAhead; ++jj) rows[it][jj] = inv[min(ns, Ns - 1) * k + min(jj, k - 1)];
     }
 }
-template <int DS, int AHEAD, int SROWS = 32>
-__device__ __forceinline__ void assemble_rows(const f32x16 (&dx)[SliceTiles<DS>::OT], const int (&rows)[4][kRbAhead], const RowsAhead<DS, AHEAD> &ahead,
+// FULL: every slice of the tile exists (stores without a condition: their number in flight is known, and a wait for later loads
+// is not one for them).  TOGETHER: the eight pieces of a feature tile are requested together, not two by two.
+template <int DS, int AHEAD, int SROWS, bool TOGETHER, bool FULL>
+__device__ __forceinline__ void assemble_rows_of(const f32x16 (&dx)[SliceTiles<DS>::OT], const int (&rows)[4][kRbAhead], const RowsAhead<DS, AHEAD> &ahead,
                                               const float *__restrict__ dxrow, const int32_t *__restrict__ inv, int k, bf16_t *__restrict__ dh,
                                               long long n0, long long Ns, int lane, float *stg)
 {
+    constexpr int OT = SliceTiles<DS>::OT;
     const int j = lane & 31, g = lane >> 5, piece = lane & 7, sl = lane >> 3;
 #pragma unroll
-    for (int ot = 0; ot < SliceTiles<DS>::OT; ++ot)
+    for (int ot = 0; ot < OT; ++ot) {
+        f32x4 got[4][kRbAhead];
+        if constexpr (TOGETHER) {
+#pragma unroll
+            for (int it = 0; it < 4; ++it)
+#pragma unroll
+                for (int jj = 0; jj < kRbAhead; ++jj) got[it][jj] = gradient_row_piece<DS>(dxrow, rows[it][jj], ot, piece);
+        }
 #pragma unroll
         for (int s0 = 0; s0 < 32; s0 += SROWS) {
 #pragma unroll
@@ -412,13 +447,14 @@ __device__ __forceinline__ void assemble_rows(const f32x16 (&dx)[SliceTiles<DS>:
                 for (int jj = 0; jj < kRbAhead; ++jj) {
                     f32x4 t;
                     if constexpr (AHEAD > 0) t = ahead.v[ot][it][jj];
+                    else if constexpr (TOGETHER) t = got[it][jj];
                     else t = gradient_row_piece<DS>(dxrow, rows[it][jj], ot, piece);
-                    const bool there = jj < k && ns < Ns && rows[it][jj] >= 0;
+                    const bool there = jj < k && (FULL || ns < Ns) && rows[it][jj] >= 0;
 #pragma unroll
                     for (int c = 0; c < 4; ++c) v[c] += there ? t[c] : 0.f;
                 }
                 for (int jj = kRbAhead; jj < k; ++jj) {
-                    const int row = ns < Ns ? inv[ns * k + jj] : -1;
+                    const int row = FULL || ns < Ns ? inv[ns * k + jj] : -1;
                     const f32x4 t = gradient_row_piece<DS>(dxrow, row, ot, piece);
 #pragma unroll
                     for (int c = 0; c < 4; ++c) v[c] += row >= 0 ? t[c] : 0.f;
@@ -445,12 +481,22 @@ __device__ __forceinline__ void assemble_rows(const f32x16 (&dx)[SliceTiles<DS>:
             for (int half = 0; half < SROWS / 16; ++half) {
                 const int i = half * 16 + (lane >> 2), pc = lane & 3;
                 const long long ns = n0 + s0 + i;
-                if (ns < Ns && (DS % 32 == 0 || 32 * ot + 8 * pc < DS))
+                if ((FULL || ns < Ns) && (DS % 32 == 0 || 32 * ot + 8 * pc < DS))
                     *(uint4 *)(dh + ns * DS + 32 * ot + 8 * pc) = *(const uint4 *)((const char *)(stg + i * kRbStageRow) + pc * 16);
             }
             wave_lds_sync();   // before the next gather overwrites the tile
         }
+    }
 }
+template <int DS, int AHEAD, int SROWS, bool TOGETHER>
+__device__ __forceinline__ void assemble_rows(const f32x16 (&dx)[SliceTiles<DS>::OT], const int (&rows)[4][kRbAhead], const RowsAhead<DS, AHEAD> &ahead,
+                                              const float *__restrict__ dxrow, const int32_t *__restrict__ inv, int k, bf16_t *__restrict__ dh,
+                                              long long n0, long long Ns, int lane, float *stg)
+{
+    if (TOGETHER && n0 + 32 <= Ns) assemble_rows_of<DS, AHEAD, SROWS, TOGETHER, true>(dx, rows, ahead, dxrow, inv, k, dh, n0, Ns, lane, stg);
+    else assemble_rows_of<DS, AHEAD, SROWS, TOGETHER, false>(dx, rows, ahead, dxrow, inv, k, dh, n0, Ns, lane, stg);
+}
+
 
 // ------------------------------------------------------------------------------------------------ logits kernel
 // LDS: w1f | w2f | b1 | b2 (the first, second, sixth and seventh pieces of the packed buffer).
@@ -507,6 +553,8 @@ __global__ __launch_bounds__(kRbThreads) void bwd_route_logits_mfma_kernel(
 
 // ------------------------------------------------------------------------------------------------ inputs kernel
 // LDS: w2c | w1c (the third and fourth pieces of the packed buffer, adjacent) | staging tiles.
+// Bound: memory, 0.8 GB at width 128, 64 experts, 524 288 slices: 208 us.  With the gradient rows of a feature tile requested together
+// it takes 181 alone, but runs beside the expert weight gradients, and the whole backward is slower by 3% (2.50 / 2.60 ms).
 template <int DS, int ET>
 __global__ __launch_bounds__(kRbThreads) void bwd_route_inputs_mfma_kernel(
     long long Ns, int k, const char *__restrict__ packed, RouterBwdPacked L, const int32_t *__restrict__ inv,
@@ -552,7 +600,7 @@ __global__ __launch_bounds__(kRbThreads) void bwd_route_inputs_mfma_kernel(
         int rows[4][kRbAhead];
         slice_rows(rows, inv, tile * 32, Ns, k, lane);
         RowsAhead<DS, 0> none;
-        assemble_rows<DS, 0>(dx, rows, none, dxrow, inv, k, dh, tile * 32, Ns, lane, stg);
+        assemble_rows<DS, 0, 32, false>(dx, rows, none, dxrow, inv, k, dh, tile * 32, Ns, lane, stg);
     }
 }
 
@@ -563,7 +611,9 @@ __global__ __launch_bounds__(kRbThreads) void bwd_route_inputs_mfma_kernel(
 // 11 thousand); four would not hold the gradient rows (128 registers: spills, 187 us).
 // 262 144 slices at width 64, 32 experts: logits 60 + inputs 83 us -> 93 us, of which the gradient rows' loads without a branch and a
 // wait behind each are 25, the ReLU pattern in two instructions per unit, the capped median and the mixed-precision split 14 (the packed
-// maximum that keeps an infinity costs 1 to 3 of them).  32 768 slices at width 48: 17 + 20 -> 24 us.
+// maximum that keeps an infinity costs 1 to 3 of them).  32 768 slices at width 48: 17 + 20 -> 24 us.  Width 96, 65 528 slices: 40.8 -> 37.6
+// us with the gradient rows of a feature tile requested together (assemble_rows) and no wait for the next tile's data or this one's stores;
+// where they are requested ahead anyway (AHEAD) the same order of requests changes nothing.
 template <int DS, int ET, int THREADS, int AHEAD, int SROWS>
 __global__ __launch_bounds__(THREADS) void bwd_route_slices_mfma_kernel(
     const bf16_t *__restrict__ x, long long Ns, int E, int k, const char *__restrict__ packed, RouterBwdPacked L,
@@ -572,6 +622,7 @@ __global__ __launch_bounds__(THREADS) void bwd_route_slices_mfma_kernel(
     CapLoss cap, const float *__restrict__ dxrow, bf16_t *__restrict__ dg_terms /* [terms][Ns][EP] */, bf16_t *__restrict__ dh)
 {
     constexpr int KS = SliceTiles<DS>::KS, OT = SliceTiles<DS>::OT, EP = ET * 32, TERMS = kRbTerms<DS>, kWaves = THREADS / 64;
+    constexpr bool EARLY = AHEAD == 0;   // the next tile's stacked rows with its x, both waited for in front of this tile's stores
     extern __shared__ __align__(16) char lds[];
     uint4 *w1f = (uint4 *)lds;                              // [8][KS][64]
     uint4 *w2f = w1f + kRbHT * KS * 64;                     // [8][2][ET][64]
@@ -625,13 +676,20 @@ __global__ __launch_bounds__(THREADS) void bwd_route_slices_mfma_kernel(
         f32x16 gacc[ET], dx[OT];
         uint32_t act[4], dgt[ET][TERMS][8];
         router_logits<DS, ET>(xb, w1f, w2f, b1s, b2s, lane, g, gacc, act);
+        if constexpr (EARLY) arrived(D);
+        int next[4][kRbAhead];
         load_x(tile + step, xb);
+        if (EARLY) slice_rows(next, inv, (tile + step) * 32, Ns, k, lane);
         logit_gradients<ET, TERMS>(gacc, D, nn, g, E, k, noise != nullptr, sigma, inv_tau, drop_u, rate, idx, inv, dpk, cap.slots != nullptr, capg_s, dgt);
+        if constexpr (EARLY) {
+            arrived(xb);
+#pragma unroll
+            for (int it = 0; it < 4; ++it) arrived(next[it]);
+        }
         if (n < Ns) store_logit_gradients<ET, TERMS>(dgt, dg_terms, Ns, n, g);
         input_gradients<DS, ET>(dgt, act, w2c, w1c, lane, dx);
-        int next[4][kRbAhead];
-        slice_rows(next, inv, (tile + step) * 32, Ns, k, lane);
-        assemble_rows<DS, AHEAD, SROWS>(dx, rows, ahead, dxrow, inv, k, dh, tile * 32, Ns, lane, stg);
+        if (!EARLY) slice_rows(next, inv, (tile + step) * 32, Ns, k, lane);
+        assemble_rows<DS, AHEAD, SROWS, EARLY>(dx, rows, ahead, dxrow, inv, k, dh, tile * 32, Ns, lane, stg);
 #pragma unroll
         for (int it = 0; it < 4; ++it)
 #pragma unroll
