@@ -47,7 +47,7 @@ struct ReduceArgs {
     // experts: blocks of THREADS / 4 groups of V slot elements, one expert each
     const float *epart;
     const int32_t *offsets;
-    int step, blocks;
+    int step, overhead, blocks;
     size_t eslot;
     // router: blocks of THREADS / 8 slot elements
     const float *rpart;
@@ -69,10 +69,10 @@ __device__ __forceinline__ void reduce_expert(const ReduceArgs &A, unsigned bloc
     const int e = (int)(block % (unsigned)A.E), lane = threadIdx.x & 63;
     const int ex = threadIdx.x % ELEMS, sq = threadIdx.x / ELEMS;
     const size_t t = ((size_t)(block / (unsigned)A.E) * ELEMS + ex) * V;
-    const RowAxis X = row_axis(A.offsets[min(lane + 1, A.E)] - A.offsets[min(lane, A.E)], A.step, A.blocks, lane);
+    const RowAxis X = row_axis(A.offsets[min(lane + 1, A.E)] - A.offsets[min(lane, A.E)], A.step, A.overhead, A.blocks, lane);
     const int first = __builtin_amdgcn_readlane(X.first, e), steps = __builtin_amdgcn_readlane(X.steps, e);
-    // position first is the expert's overhead; its steps are first + 1 .. first + steps
-    const int vf = (first + 1) / X.share, vl = steps > 0 ? (first + steps) / X.share : vf - 1;
+    // its steps follow its overhead
+    const int s0 = first + A.overhead, vf = s0 / X.share, vl = steps > 0 ? (s0 + steps - 1) / X.share : vf - 1;
     vec acc = {};
     if (t < A.eslot) {
         const float *src = A.epart + (size_t)e * A.eslot + t;
@@ -295,7 +295,7 @@ hipError_t launch_backward(const slicemoe_config &c, const void *h, const slicem
     }
     const size_t rslot = router_slot_floats(ds, c.Hr, c.E);
     const BackwardWeightsPlan W = backward_mfma_shape(c) ? backward_weights_plan(c) : backward_generic_plan(c);
-    const ReduceArgs sums = {epart, offsets, W.step, W.blocks, eslot, rpart, (int)P.router_slots, rslot, 0, ds, c.He, c.Hr, c.E, g};
+    const ReduceArgs sums = {epart, offsets, W.step, W.overhead, W.blocks, eslot, rpart, (int)P.router_slots, rslot, 0, ds, c.He, c.Hr, c.E, g};
     // the experts' slots: at once, on the stream that fills them, or together with the router's (see kReduceApartBytes)
     const bool apart = se != s || ((size_t)P.expert_slots * eslot + (size_t)P.router_slots * rslot) * sizeof(float) > kReduceApartBytes;
     if (apart && (e = launch_reduce(sums, true, false, se)) != hipSuccess) return e;

@@ -98,7 +98,7 @@ __global__ __launch_bounds__(WAVES * 64, MINWAVES) void bwd_expert_kernel(
     const int vb = blocks % 8 == 0 ? (int)(blockIdx.x % 8) * (blocks / 8) + (int)(blockIdx.x / 8) : (int)blockIdx.x;
 
     const int off_lo = offsets[min(lane, E)], off_hi = offsets[min(lane + 1, E)];
-    const RowAxis A = row_axis(off_hi - off_lo, kUnit, blocks, lane);
+    const RowAxis A = row_axis(off_hi - off_lo, kUnit, 1, blocks, lane);
     const int c0 = vb * A.share, c1 = c0 + A.share;
 
     // ---- the piece this thread moves
@@ -432,6 +432,7 @@ BackwardWeightsPlan backward_expert_plan(const slicemoe_config &c)
     const long long Na = (long long)c.T * c.S * c.k, most = (Na + kUnit - 1) / kUnit;
     W.fused = true;
     W.step = kUnit;
+    W.overhead = 1;
     W.groups = 1;
     long long blocks = (long long)num_compute_units() * (c.d / c.S == 24 ? 2 : 1);
     if (blocks > most) blocks = most;

@@ -9,7 +9,7 @@
 // group's part of dL/dx and dL/dp to what it wrote before.  Nothing is added in an order that changes from run to run.
 //
 // Bound: the matrix instruction (64 cycles; 160 per hidden tile and unit at ds = 64) and, for the small batches these shapes
-// run at, latency: a batch of weights in flight at a time.  8000 rows, ds = 64, He = 256, 8 experts: 4.13 ms -> 51 us;
+// run at, latency: a batch of weights in flight at a time.  8000 rows, ds = 64, He = 256, 8 experts: 4.13 ms -> 33 us;
 // 4000 slices, E = 8: 3.69 ms -> 39 us (one thread per hidden unit over 512 rows per block before).
 #include "bwd_mfma.h"
 
@@ -79,13 +79,13 @@ __global__ __launch_bounds__(kGbThreads) void bwd_expert_generic_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nch = (int)gridDim.y, own = (int)blockIdx.y, own_c0 = own * CC, own_n = min(CC, ds - own_c0);
     const int off_lo = offsets[min(lane, E)], off_hi = offsets[min(lane + 1, E)];
-    const RowAxis A = row_axis(off_hi - off_lo, kGbRows, (int)gridDim.x, lane);
+    const RowAxis A = row_axis(off_hi - off_lo, kGbRows, 0, (int)gridDim.x, lane);
     const int p0 = (int)blockIdx.x * A.share, p1 = p0 + A.share;
 
     for (int e = 0; e < E; ++e) {
         const int first = __builtin_amdgcn_readlane(A.first, e), steps = __builtin_amdgcn_readlane(A.steps, e);
         if (first >= p1) break;
-        const int s_lo = max(0, p0 - first - 1), s_hi = min(steps, p1 - first - 1);
+        const int s_lo = max(0, p0 - first), s_hi = min(steps, p1 - first);
         if (s_hi <= s_lo) continue;
         const int row0 = __builtin_amdgcn_readlane(off_lo, e) + s_lo * kGbRows;
         const int nrows = min(__builtin_amdgcn_readlane(off_hi, e) - row0, (s_hi - s_lo) * kGbRows);
@@ -522,8 +522,12 @@ BackwardWeightsPlan backward_generic_plan(const slicemoe_config &c)
     W.fused = true;
     W.groups = 1;
     W.step = kGbRows;
+    // No position for beginning an expert: a slot costs a block a tenth of a unit, but whole units are handed out, and at the batches
+    // this kernel runs at the extra positions often doubled a block's share.  8000 rows, 8 experts, 256 blocks: 254 units + 8
+    // positions were two to a block (129 blocks at work, 53 us); one to a block 33 us, and 3 us more for twice the slots.
+    W.overhead = 0;
     long long blocks = num_compute_units() / ((ds + cc - 1) / cc);
-    const long long most = (Na + kGbRows - 1) / kGbRows;
+    const long long most = (Na + kGbRows - 1) / kGbRows + c.E - 1;   // units: an expert's rows begin one
     if (blocks > most) blocks = most;
     W.blocks = blocks < 1 ? 1 : (int)blocks;
     W.slots = (long long)W.blocks + c.E;

@@ -89,7 +89,7 @@ __global__ __launch_bounds__(WAVES * 64, MINWAVES) void bwd_weights_kernel(
     const bool active = ht < HT;
 
     const int off_lo = offsets[min(lane, E)], off_hi = offsets[min(lane + 1, E)];
-    const RowAxis A = row_axis(off_hi - off_lo, kUnit, blocks, lane);
+    const RowAxis A = row_axis(off_hi - off_lo, kUnit, 1, blocks, lane);
     const int c0 = vb * A.share, c1 = c0 + A.share;
 
     // ---- addresses that do not change
@@ -502,6 +502,7 @@ BackwardWeightsPlan backward_weights_plan(const slicemoe_config &c)
     const long long Na = (long long)c.T * c.S * c.k;
     W.fused = C.fused;
     W.step = kUnit;
+    W.overhead = 1;
     W.groups = (HT + C.waves - 1) / C.waves;
     long long blocks = (long long)num_compute_units() * C.per_cu / W.groups;
     const long long most = (Na + kUnit - 1) / kUnit;

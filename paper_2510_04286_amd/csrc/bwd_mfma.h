@@ -8,18 +8,18 @@ namespace slicemoe {
 
 // ------------------------------------------------------------------------------------------- work split over blocks
 // Rows are handed out in steps of `step` rows counted from each expert's first row, on an axis where an expert with rows
-// occupies one position more than it has steps (what it costs a block to begin an expert: its weights in, its sums out).
+// occupies `overhead` positions, 0 or 1, more than it has steps (what it costs a block to begin an expert: its weights in, its sums out).
 // Block v takes `share` consecutive positions.  A segment is what one block has of one expert; along the axis the block or
 // the expert advances from one segment to the next, so v + e names a segment's slot of partial sums uniquely.
 struct RowAxis {
     int first, steps;   // of lane e's expert (E <= 64): its first position, its steps
     int share;          // uniform
 };
-__device__ __forceinline__ RowAxis row_axis(int rows, int step, int blocks, int lane)
+__device__ __forceinline__ RowAxis row_axis(int rows, int step, int overhead, int blocks, int lane)
 {
     RowAxis A;
     A.steps = (rows + step - 1) / step;
-    const int cost = A.steps > 0 ? A.steps + 1 : 0;
+    const int cost = A.steps > 0 ? A.steps + overhead : 0;
     A.first = wavefront_exclusive_scan(cost, lane);
     A.share = max(1, (wavefront_sum(cost) + blocks - 1) / blocks);
     return A;
@@ -141,6 +141,7 @@ struct BwdPacked {
 struct BackwardWeightsPlan {
     bool fused;
     int step, groups, blocks;
+    int overhead;      // of an expert, on the axis of the work split: 0 or 1
     long long slots;   // of partial weight gradients
 };
 BackwardWeightsPlan backward_weights_plan(const slicemoe_config &c);

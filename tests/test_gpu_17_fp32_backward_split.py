@@ -1,0 +1,59 @@
+"""How the fp32 expert backward hands its units of 32 rows to the blocks: one unit per block up to as many units as there are
+compute units, two from the next one on (the blocks of the second half then have none), experts without rows, a single row, and
+one expert with every row.  Every gradient against the fp64 oracle on the routing that the forward call left behind.  Bars: those of the fp32 edge
+tests (1e-4 of the RMS for dL/dh; 5e-4 of the RMS for the weight gradients): only the order of fp32 sums of at most 9000 terms differs."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2510_04286_amd import workload as wl
+from tests.common import TOL_F32, make_inputs, rms
+
+pytestmark = pytest.mark.gpu
+
+NAMES = ("Wr1", "br1", "Wr2", "br2", "W1", "b1", "W2", "b2")
+
+
+def shape(T, E, k, S=4, ds=16, He=32):
+    return wl.SliceMoEShape("split", T=T, d=S * ds, S=S, E=E, k=k, He=He, dtype="f32", Hr=32)
+
+
+CASES = {   # the expert that the router's bias prefers, if any: then units are as many as its rows need
+    "one_row": (shape(1, 3, 1, S=1), None),
+    "one_unit_each": (shape(12, 8, 2), None),
+    "units_255": (shape(2040, 2, 1), 1),
+    "units_256": (shape(2048, 2, 1), 1),
+    "units_257": (shape(2049, 2, 1), 0),
+    "two_groups_of_hidden_units": (shape(70, 5, 2, He=290), None),
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_gradients_at_the_edges_of_the_split(name):
+    import torch
+    from paper_2510_04286_amd import binding as B
+    case, hot = CASES[name]
+    s, h, w = make_inputs(case)
+    if hot is not None:
+        w["br2"] = wl.to_storage(np.where(np.arange(s.E) == hot, 50.0, w["br2"]), s.dtype)
+    cfg = B.config_of(s)
+    dout = wl.make_dout(s)
+    wd, ws, hd = B.weights_to_device(w, s.dtype), B.alloc_workspace(cfg), B.to_device(h, s.dtype)
+    B.slicemoe_forward(cfg, hd, wd, torch.empty_like(hd), ws)
+    views = B.workspace_views(cfg, ws)
+    idx, inv = views["topk_idx"].cpu().numpy(), views["inv"].cpu().numpy()
+    if hot is not None:
+        assert (idx == hot).all()
+    ref = oracle.backward(h, s.S, s.k, w, dout, idx, inv)
+    grads, d_h = B.alloc_weight_grads(cfg), torch.full_like(hd, 5.0)
+    for t in grads.values():
+        t.fill_(7.0)   # the call overwrites
+    bws = torch.full((B.slicemoe_backward_workspace_bytes(cfg),), 0xFF, dtype=torch.uint8, device="cuda:0")   # NaNs: nothing is read unwritten
+    for _ in range(2):   # the second call finds the first one's values in the workspace
+        B.slicemoe_backward(cfg, hd, wd, ws, B.to_device(dout, s.dtype), d_h, grads, bws)
+    torch.cuda.synchronize()
+    err = {n: np.abs(grads[n].cpu().numpy() - ref[n]).max() / (rms(ref[n]) or 1.0) for n in NAMES}
+    err_h = np.abs(d_h.cpu().numpy() - ref["d_h"]).max() / rms(ref["d_h"])
+    print(f"\n[{name}] dL/dh {err_h:.1e}; " + " ".join(f"{n} {e:.1e}" for n, e in err.items()))
+    assert err_h <= TOL_F32
+    assert max(err.values()) <= 5e-4, err
