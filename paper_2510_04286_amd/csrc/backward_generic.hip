@@ -8,8 +8,12 @@
 // shared quantities; hidden widths above 256 in groups that a block works through in turn, the same thread adding each
 // group's part of dL/dx and dL/dp to what it wrote before.  Nothing is added in an order that changes from run to run.
 //
-// Bound: the matrix instruction (64 cycles; 160 per hidden tile and unit at ds = 64) and, for the small batches these shapes
-// run at, latency: a batch of weights in flight at a time.  8000 rows, ds = 64, He = 256, 8 experts: 4.13 ms -> 33 us;
+// Bound: the matrix instruction (64 cycles; 160 per hidden tile and unit at ds = 64, 8.5 us for the two wavefronts of a SIMD) and,
+// for the small batches these shapes run at, latency.  Where a block has the whole width and whole quads (AHEAD: 32 or 64 columns,
+// He a multiple of 32), the weights are requested ahead without conditions: the first batch with the rows, the next one and dL/dx's
+// while matrix instructions run.  Elsewhere, with a test per load, a batch at its use.  8000 rows, ds = 64, He = 256, 8 experts: 33 ->
+// 27 us; 32 768 rows (a step's backward): 188 -> 156; ragged widths, ds = 40, He = 100, 8000 rows: 123 -> 83 (bases of the LDS
+// accesses in registers instead of an address per access, spilled, and the rows gathered without a barrier between their index and their load);
 // 4000 slices, E = 8: 3.69 ms -> 39 us (one thread per hidden unit over 512 rows per block before).
 #include "bwd_mfma.h"
 
@@ -60,10 +64,10 @@ template <int OTC> struct GenericExpertLds {
     static constexpr int CC = 32 * OTC, XST = CC + 1;
     static constexpr size_t xs = 0, gs = xs + (size_t)kGbRows * XST, pz = gs + (size_t)kGbRows * XST;   // floats
     static constexpr size_t red = pz + (size_t)kGbHidden * kGbT, dps = red + (size_t)kGbWaves * kGbRows * kGbT;
-    static constexpr size_t ps = dps + kGbWaves * kGbRows, ids = ps + kGbRows, total = ids + 2 * kGbRows;
+    static constexpr size_t ps = dps + kGbWaves * kGbRows, total = ps + kGbWaves * kGbRows;
 };
 
-template <typename T, int OTC>
+template <typename T, int OTC, bool AHEAD>
 __global__ __launch_bounds__(kGbThreads) void bwd_expert_generic_kernel(
     const T *__restrict__ x, const T *__restrict__ dout, const float *__restrict__ pk,
     const int32_t *__restrict__ offsets, const int32_t *__restrict__ perm, int ds, int He, int E, int k,
@@ -74,13 +78,30 @@ __global__ __launch_bounds__(kGbThreads) void bwd_expert_generic_kernel(
     constexpr int CC = L::CC, XST = L::XST, PARTS = kGbWaves / OTC;
     extern __shared__ __align__(16) float smem[];
     float *xs = smem + L::xs, *gs = smem + L::gs, *pz = smem + L::pz, *red = smem + L::red, *dps = smem + L::dps, *ps = smem + L::ps;
-    int *as = (int *)(smem + L::ids), *ns = as + kGbRows;
     const int tid = threadIdx.x, lane = tid & 63, jj = lane & 31, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int nch = (int)gridDim.y, own = (int)blockIdx.y, own_c0 = own * CC, own_n = min(CC, ds - own_c0);
+    const int nch = AHEAD ? 1 : (int)gridDim.y, own = AHEAD ? 0 : (int)blockIdx.y, own_c0 = own * CC, own_n = AHEAD ? CC : min(CC, ds - own_c0);
     const int off_lo = offsets[min(lane, E)], off_hi = offsets[min(lane + 1, E)];
     const RowAxis A = row_axis(off_hi - off_lo, kGbRows, 0, (int)gridDim.x, lane);
     const int p0 = (int)blockIdx.x * A.share, p1 = p0 + A.share;
+    constexpr int ROWS = kGbThreads / CC, STAGED = kGbRows / ROWS;   // staging: a thread has one column of every ROWS-th row
+    const int st_c = tid % CC, st_r = tid / CC;
+    // LDS bases of a lane: what is added to them in the loops is known to the compiler and takes no register
+    const float *xs_b = xs + jj * XST + g, *gs_b = gs + jj * XST + 4 * g, *xs_r = xs + 4 * g * XST + jj, *gs_r = gs + 4 * g * XST + jj, *ps_r = ps + wave * kGbRows + 4 * g;
+    float *pz_w = pz + (wave * 32 + jj) * kGbT + 4 * g, *red_w = red + (wave * kGbRows + 4 * g) * kGbT + jj;
+    // Values kb + 8 q + 4 g .. of a row of n, zero past it: `row` elements from the uniform p, so that an address is one register.
+    auto quads_of = [&](const T *p, unsigned row, int kb, int n, bool vec, float (&b)[16]) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            float v[4];
+            const int f = kb + 8 * q + 4 * g;
+            const T *at = (const T *)((const char *)(p + kb + 8 * q) + (row + 4u * (unsigned)g) * (unsigned)sizeof(T));
+            if (AHEAD) Quad<T>::load(at, v);
+            else load_quad(at, n - f, vec, v);
+#pragma unroll
+            for (int s = 0; s < 4; ++s) b[4 * q + s] = v[s];
+        }
+    };
 
     for (int e = 0; e < E; ++e) {
         const int first = __builtin_amdgcn_readlane(A.first, e), steps = __builtin_amdgcn_readlane(A.steps, e);
@@ -103,67 +124,89 @@ __global__ __launch_bounds__(kGbThreads) void bwd_expert_generic_kernel(
 #pragma unroll
                 for (int i = 0; i < 16; ++i) aW1[ot][i] = aW2[ot][i] = 0.f;
             float ab1 = 0.f, ab2 = 0.f;
-
-            for (int r0 = 0; r0 < nrows; r0 += kGbRows) {
-                const int rows = min(kGbRows, nrows - r0);
-                __syncthreads();   // everyone is done with the unit before
-                if (tid < kGbRows) {
-                    const int a = perm[row0 + r0 + min(tid, rows - 1)];
-                    as[tid] = a;
-                    ns[tid] = a / k;
-                    ps[tid] = tid < rows ? pk[a] : 0.f;
+            // operands of 32 of a chunk's features: column hid of W1, row hid of W2 (K-step s of quad q: features kb + 8 q + 4 g + s)
+            auto first_layer = [&](int c0, int nf, int kb, float (&bu)[16], float (&bd)[16]) {
+                unsigned col = (unsigned)(g * He + hidc), row = (unsigned)(hidc * ds);
+                asm volatile("" : "+v"(col), "+v"(row));   // opaque: addresses are not kept in registers from one unit to the next
+#pragma unroll
+                for (int s = 0; s < 16; ++s) {
+                    const T *at = (const T *)((const char *)(w1 + (size_t)(c0 + kb + 2 * s) * He) + col * (unsigned)sizeof(T));
+                    if (AHEAD) bu[s] = Storage<T>::load(at);
+                    else bu[s] = kb + 2 * s + g < nf ? Storage<T>::load(at) : 0.f;
                 }
+                quads_of(w2 + c0, row, kb, nf, vec_ds, bd);
+            };
+            int assigned = perm[row0 + min(jj, nrows - 1)];   // of row jj of the unit, in every wavefront
+            for (int r0 = 0; r0 < nrows; r0 += kGbRows) {
+                const int rows = min(kGbRows, nrows - r0), mine = assigned;
                 f32x16 u, da;
 #pragma unroll
                 for (int i = 0; i < 16; ++i) u[i] = da[i] = 0.f;
                 for (int i = 1; i <= nch; ++i) {   // the block's own columns last: they stay for the weight gradients
-                    const int c0 = (own + i) % nch * CC, nf = min(CC, ds - c0);
-                    __syncthreads();
-                    for (int t = tid; t < kGbRows * CC; t += kGbThreads) {
-                        const int r = t / CC, c = t % CC;
-                        const bool in = c < nf;
-                        const size_t at = (size_t)ns[r] * ds + c0 + c;
-                        xs[r * XST + c] = in ? Storage<T>::load(x + at) : 0.f;
-                        gs[r * XST + c] = in && r < rows ? Storage<T>::load(dout + at) : 0.f;   // rows past the end add nothing
+                    const int c0 = AHEAD ? 0 : (own + i) % nch * CC, nf = AHEAD ? CC : min(CC, ds - c0);
+                    float bu[AHEAD ? 2 : 1][16], bd[AHEAD ? 2 : 1][16];
+                    if (AHEAD) first_layer(c0, nf, 0, bu[0], bd[0]);
+                    float xv[STAGED], gv[STAGED], pv = 0.f;
+                    {
+                        const int n = mine / k;
+                        if (i == 1) pv = pk[mine];
+#pragma unroll
+                        for (int q = 0; q < STAGED; ++q) {
+                            const size_t at = (size_t)__shfl(n, st_r + q * ROWS) * ds + c0 + min(st_c, nf - 1);
+                            xv[q] = Storage<T>::load(x + at);
+                            gv[q] = Storage<T>::load(dout + at);
+                        }
                     }
+                    if (i == 1) assigned = perm[row0 + min(r0 + kGbRows + jj, nrows - 1)];
+                    __syncthreads();   // everyone is done with what was there
+#pragma unroll
+                    for (int q = 0; q < STAGED; ++q) {
+                        const int r = st_r + q * ROWS;
+                        xs[r * XST + st_c] = st_c < nf ? xv[q] : 0.f;
+                        gs[r * XST + st_c] = st_c < nf && r < rows ? gv[q] : 0.f;   // rows past the end add nothing
+                    }
+                    if (i == 1) ps[wave * kGbRows + jj] = jj < rows ? pv : 0.f;   // a wavefront's own copy
                     __syncthreads();
                     // 32 features at a time: sixteen weights of each product in flight, then sixteen matrix instructions of each
-                    for (int kb = 0; kb < nf; kb += 32) {
-                        float bu[16], bd[16];
+#pragma unroll
+                    for (int t = 0; t < OTC; ++t) {
+                        const int kb = 32 * t, at = AHEAD ? t & 1 : 0;
+                        if (kb >= nf) break;
+                        if (!AHEAD) first_layer(c0, nf, kb, bu[0], bd[0]);
+                        else if (t + 1 < OTC) first_layer(c0, nf, kb + 32, bu[(t + 1) & 1], bd[(t + 1) & 1]);
+                        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                         for (int s = 0; s < 16; ++s) {
-                            const int f = kb + 2 * s + g;
-                            bu[s] = f < nf ? Storage<T>::load(w1 + (size_t)(c0 + f) * He + hidc) : 0.f;
-                        }
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {   // K-step s of quad q: features kb + 8 q + 4 g + s
-                            float v[4];
-                            const int f = kb + 8 * q + 4 * g;
-                            load_quad(w2 + (size_t)hidc * ds + c0 + f, nf - f, vec_ds, v);
-#pragma unroll
-                            for (int s = 0; s < 4; ++s) bd[4 * q + s] = v[s];
-                        }
-#pragma unroll
-                        for (int s = 0; s < 16; ++s) {
-                            u = mfma_f32(xs[jj * XST + kb + 2 * s + g], bu[s], u);
-                            da = mfma_f32(gs[jj * XST + kb + 8 * (s >> 2) + 4 * g + (s & 3)], bd[s], da);
+                            u = mfma_f32(xs_b[kb + 2 * s], bu[at][s], u);
+                            da = mfma_f32(gs_b[kb + 8 * (s >> 2) + (s & 3)], bd[at][s], da);
                         }
                     }
                 }
+                __builtin_amdgcn_sched_barrier(0);
+                float bx[AHEAD ? OTC : 1][16];   // of dL/dx, requested ahead of the activations
+                const int dx_t = wave % OTC, dx_k0 = wave / OTC * (kGbHidden / PARTS), dx_k1 = min(dx_k0 + kGbHidden / PARTS, He - h0);
+                const T *wf = w1 + (size_t)own_c0 * He + h0;
+                unsigned dx_row = (unsigned)(min(32 * dx_t + jj, own_n - 1) * He);
+                asm volatile("" : "+v"(dx_row));
+                if (AHEAD) {
+#pragma unroll
+                    for (int q = 0; q < OTC; ++q) quads_of(wf, dx_row, min(dx_k0 + 32 * q, He - h0 - 32), He - h0, vec_he, bx[q]);   // (those past the end are not used)
+                }
+                __builtin_amdgcn_sched_barrier(0);
                 float du[8];
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
-                    const int r = acc_feature(i, g);
-                    const float p = ps[r], z = fmaf(p, u[i], bias);
+                    const int row = acc_feature(i, 0);   // and 4 g more, in the bases
+                    const float p = ps_r[row], z = fmaf(p, u[i], bias);
                     float act;
                     const float gg = gelu_grad(z, &act), dz = hok ? da[i] * gg : 0.f, pdz = p * dz;
                     du[i & 7] = i < 8 ? dz * u[i] : sum_over_row_pair(du[i & 7], dz * u[i]);
                     ab1 += dz;
-                    pz[(wave * 32 + jj) * kGbT + r] = pdz;
+                    pz_w[row] = pdz;
 #pragma unroll
                     for (int ot = 0; ot < OTC; ++ot) {
-                        aW1[ot] = mfma_f32(xs[r * XST + 32 * ot + jj], pdz, aW1[ot]);   // [feature][hidden unit]: lane = hidden unit
-                        aW2[ot] = mfma_f32(act, gs[r * XST + 32 * ot + jj], aW2[ot]);   // [hidden unit][feature]: lane = feature
+                        aW1[ot] = mfma_f32(xs_r[row * XST + 32 * ot], pdz, aW1[ot]);   // [feature][hidden unit]: lane = hidden unit
+                        aW2[ot] = mfma_f32(act, gs_r[row * XST + 32 * ot], aW2[ot]);   // [hidden unit][feature]: lane = feature
                     }
                     if (i & 1) __builtin_amdgcn_sched_barrier(0);   // two elements at a time: more would not fit the registers
                 }
@@ -173,25 +216,21 @@ __global__ __launch_bounds__(kGbThreads) void bwd_expert_generic_kernel(
                     for (int r = 0; r < rows; ++r) ab2 += gs[r * XST + tid];
                 __syncthreads();
                 {   // dL/dx, own columns: lane = feature, registers = rows; the hidden units of a tile over PARTS wavefronts
-                    const int ot = wave % OTC, k0 = wave / OTC * (kGbHidden / PARTS), f = 32 * ot + jj;
                     f32x16 dx;
 #pragma unroll
                     for (int i = 0; i < 16; ++i) dx[i] = 0.f;
-                    const T *wf = w1 + (size_t)(own_c0 + min(f, own_n - 1)) * He + h0;
-                    for (int kb = k0; kb < min(k0 + kGbHidden / PARTS, He - h0); kb += 32) {
-                        float b[16];
 #pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            float v[4];
-                            load_quad(wf + kb + 8 * q + 4 * g, He - h0 - (kb + 8 * q + 4 * g), vec_he, v);
+                    for (int q = 0; q < OTC; ++q) {
+                        const int kb = dx_k0 + 32 * q;
+                        if (kb >= dx_k1) break;
+                        __builtin_amdgcn_sched_barrier(0);
+                        const float *pz_b = pz + (kb + 4 * g) * kGbT + jj;
+                        if (!AHEAD) quads_of(wf, dx_row, kb, He - h0, vec_he, bx[0]);
 #pragma unroll
-                            for (int s = 0; s < 4; ++s) b[4 * q + s] = v[s];
-                        }
-#pragma unroll
-                        for (int s = 0; s < 16; ++s) dx = mfma_f32(pz[(kb + 8 * (s >> 2) + 4 * g + (s & 3)) * kGbT + jj], b[s], dx);
+                        for (int s = 0; s < 16; ++s) dx = mfma_f32(pz_b[(8 * (s >> 2) + (s & 3)) * kGbT], bx[AHEAD ? q : 0][s], dx);
                     }
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) red[(wave * kGbRows + acc_feature(i, g)) * kGbT + jj] = dx[i];
+                    for (int i = 0; i < 16; ++i) red_w[acc_feature(i, 0) * kGbT] = dx[i];
                 }
                 __syncthreads();
                 for (int t = tid; t < rows * own_n; t += kGbThreads) {
@@ -206,7 +245,7 @@ __global__ __launch_bounds__(kGbThreads) void bwd_expert_generic_kernel(
                     float v = 0.f;
 #pragma unroll
                     for (int w = 0; w < kGbWaves; ++w) v += dps[w * kGbRows + tid];
-                    dpk[as[tid]] = h0 > 0 ? dpk[as[tid]] + v : v;
+                    dpk[mine] = h0 > 0 ? dpk[mine] + v : v;
                 }
             }
             // ---- this segment's slot: dW1 [ds][He] | dW2 [He][ds] | db1 [He] | db2 [ds]; every element is written once
@@ -554,18 +593,21 @@ long long backward_generic_router_slots(const slicemoe_config &c)
 
 template <typename T> static bool quad_aligned(const void *p, int stride) { return stride % 4 == 0 && (uintptr_t)p % (4 * sizeof(T)) == 0; }
 
-template <typename T, int OTC>
+template <typename T, int OTC, bool AHEAD = false>
 static hipError_t run_expert(const slicemoe_config &c, const void *h, const slicemoe_weights &w, const void *d_out, const float *pk,
                              const int32_t *offsets, const int32_t *perm, size_t slot_floats, float *dxrow, float *dpk, float *part, hipStream_t s)
 {
     const int ds = c.d / c.S, cc = 32 * OTC;
+    const bool vec_ds = quad_aligned<T>(w.W2, ds), vec_he = quad_aligned<T>(w.W1, c.He);
+    if constexpr (OTC < 4 && !AHEAD)
+        if (ds == cc && c.He % 32 == 0 && vec_ds && vec_he) return run_expert<T, OTC, true>(c, h, w, d_out, pk, offsets, perm, slot_floats, dxrow, dpk, part, s);
     const size_t lds = GenericExpertLds<OTC>::total * sizeof(float);
-    auto kern = bwd_expert_generic_kernel<T, OTC>;
+    auto kern = bwd_expert_generic_kernel<T, OTC, AHEAD>;
     const hipError_t e = grant_dynamic_lds((const void *)kern, lds);
     if (e != hipSuccess) return e;
     kern<<<dim3((unsigned)backward_generic_plan(c).blocks, (unsigned)((ds + cc - 1) / cc)), kGbThreads, lds, s>>>(
         (const T *)h, (const T *)d_out, pk, offsets, perm, ds, c.He, c.E, c.k, (const T *)w.W1, (const T *)w.b1, (const T *)w.W2,
-        quad_aligned<T>(w.W2, ds), quad_aligned<T>(w.W1, c.He), dxrow, dpk, slot_floats, part);
+        vec_ds, vec_he, dxrow, dpk, slot_floats, part);
     return hipGetLastError();
 }
 

@@ -1,6 +1,7 @@
-"""How the fp32 expert backward hands its units of 32 rows to the blocks: one unit per block up to as many units as there are
+"""The fp32 expert backward.  How it hands its units of 32 rows to the blocks: one unit per block up to as many units as there are
 compute units, two from the next one on (the blocks of the second half then have none), experts without rows, a single row, and
-one expert with every row.  Every gradient against the fp64 oracle on the routing that the forward call left behind.  Bars: those of the fp32 edge
+one expert with every row.  And the instances that request weights a batch ahead (32 and 64 columns, whole quads): hidden widths that
+leave wavefronts without hidden units, without a part of dL/dx, or with a second group of 256.  Every gradient against the fp64 oracle on the routing that the forward call left behind.  Bars: those of the fp32 edge
 tests (1e-4 of the RMS for dL/dh; 5e-4 of the RMS for the weight gradients): only the order of fp32 sums of at most 9000 terms differs."""
 import numpy as np
 import pytest
@@ -25,6 +26,11 @@ CASES = {   # the expert that the router's bias prefers, if any: then units are 
     "units_256": (shape(2048, 2, 1), 1),
     "units_257": (shape(2049, 2, 1), 0),
     "two_groups_of_hidden_units": (shape(70, 5, 2, He=290), None),
+    "w32_one_tile": (shape(50, 3, 2, ds=32, He=32), None),
+    "w32_seven_tiles": (shape(50, 3, 2, ds=32, He=224), None),
+    "w64_three_tiles": (shape(50, 3, 2, ds=64, He=96), None),
+    "w64_two_groups": (shape(50, 3, 2, ds=64, He=288), None),
+    "w64_units_per_block": (shape(2100, 2, 1, ds=64, He=64), 1),
 }
 
 
