@@ -14,7 +14,7 @@
 // while matrix instructions run.  Elsewhere, with a test per load, a batch at its use.  8000 rows, ds = 64, He = 256, 8 experts: 33 ->
 // 27 us; 32 768 rows (a step's backward): 188 -> 156; ragged widths, ds = 40, He = 100, 8000 rows: 123 -> 83 (bases of the LDS
 // accesses in registers instead of an address per access, spilled, and the rows gathered without a barrier between their index and their load);
-// 4000 slices, E = 8: 3.69 ms -> 39 us (one thread per hidden unit over 512 rows per block before).
+// router, 4000 slices, E = 8: 3.69 ms -> 26 us (one thread per hidden unit over 512 rows per block before).
 #include "bwd_mfma.h"
 
 namespace slicemoe {
@@ -41,6 +41,12 @@ template <> struct Quad<bf16_t> {
         v[2] = __uint_as_float(q.y << 16); v[3] = __uint_as_float(q.y & 0xffff0000u);
     }
 };
+__device__ __forceinline__ void store_quad(float *p, const float (&v)[4]) { *(float4 *)p = make_float4(v[0], v[1], v[2], v[3]); }
+__device__ __forceinline__ void store_quad(bf16_t *p, const float (&v)[4])
+{
+#pragma unroll
+    for (int c = 0; c < 4; ++c) Storage<bf16_t>::store(p + c, v[c]);
+}
 template <typename T> __device__ __forceinline__ void load_quad(const T *p, int n, bool vec, float (&v)[4])
 {
     if (vec && n >= 4) {
@@ -269,6 +275,11 @@ __global__ __launch_bounds__(kGbThreads) void bwd_expert_generic_kernel(
 // ------------------------------------------------------------------------------------------------ router
 // Hr <= 256 and E <= 64.  The hidden layer is recomputed by plain multiply-add chains in a fixed order over the features (its
 // sign decides what the ReLU lets through): four hidden units and four slices per thread, weights and slices from LDS.
+// AHEAD (256 hidden units, whole chunks of columns, whole octets of experts, everything aligned for quads): each phase's
+// operands are requested, without conditions, before the phase in front of it -- the softmax's and the logits' with the slices, the
+// expert path's rows and dL/dh's weights before the weight gradients -- and dL/dh leaves as one quad per thread.  A unit of 32
+// slices is a chain of eight phases with a barrier between them, and half of its time was the latency of their loads: 4000
+// slices, ds = 64, E = 8: 39 -> 26 us; 16 384 slices (a step's backward): 156 -> 137.
 constexpr int kGrFeat = 64;   // features at a time, and columns of a block
 struct GenericRouterLds {   // floats
     static constexpr size_t xT = 0, w = xT + (size_t)kGrFeat * 36, us = w + (size_t)kGrFeat * kGbHidden;   // us: [32][257] u, then [256][33] dL/du
@@ -276,7 +287,7 @@ struct GenericRouterLds {   // floats
     static constexpr size_t total = red + (size_t)kGbWaves * kGbRows * kGbT;
 };
 
-template <typename T>
+template <typename T, bool AHEAD>
 __global__ __launch_bounds__(kGbThreads) void bwd_router_generic_kernel(
     const T *__restrict__ x, long long Ns, int ds, int Hr, int E, int k,
     const T *__restrict__ Wr1, const T *__restrict__ br1, const T *__restrict__ Wr2, const T *__restrict__ br2,
@@ -311,33 +322,83 @@ __global__ __launch_bounds__(kGbThreads) void bwd_router_generic_kernel(
         aW2[0][i] = aW2[1][i] = 0.f;
     }
     float ab1 = 0.f, ab2 = 0.f;
-    auto stage_x = [&](long long n0, int rows, int c0, int nf) {
-        for (int t = tid; t < kGbRows * kGrFeat; t += kGbThreads) {
-            const int r = t / kGrFeat, c = t % kGrFeat;
-            xT[c * 36 + r] = r < rows && c < nf ? Storage<T>::load(x + (n0 + r) * ds + c0 + c) : 0.f;
+    constexpr int STAGED = kGbRows * kGrFeat / kGbThreads, ROWS = kGbThreads / kGrFeat;   // a thread has one column of every ROWS-th slice
+    const int st_c = tid % kGrFeat, st_r = tid / kGrFeat;
+    // LDS bases of a lane (see the expert kernel)
+    const float *u_r = us + 4 * g * UST + hid, *dg_b = dgs + jj * GST + 4 * g, *dg_r = dgs + 4 * g * GST + jj, *xT_r = xT + jj * 36 + 4 * g;
+    float *du_w = us + hid * kGbT + 4 * g, *red_w = red + (wave * kGbRows + 4 * g) * kGbT + jj;
+    auto request_x = [&](long long n0, int rows, int c0, int nf, float (&v)[STAGED]) {
+#pragma unroll
+        for (int q = 0; q < STAGED; ++q) v[q] = Storage<T>::load(x + (n0 + min(st_r + q * ROWS, rows - 1)) * ds + c0 + min(st_c, nf - 1));
+    };
+    auto stage_x = [&](int rows, int nf, const float (&v)[STAGED]) {
+#pragma unroll
+        for (int q = 0; q < STAGED; ++q) {
+            const int r = st_r + q * ROWS;
+            xT[st_c * 36 + r] = r < rows && st_c < nf ? v[q] : 0.f;
         }
     };
 
     for (long long n0 = n_begin; n0 < n_end; n0 += kGbRows) {
         const int rows = (int)min((long long)kGbRows, n_end - n0);
+        unsigned here = 0;   // opaque: what is the same for every unit is requested in each, not kept in registers through all of them
+        asm volatile("" : "+v"(here));
+        // the slice and the experts of this thread in the softmax: everything that it reads there is requested here
+        const int sm_r = tid >> 4, sm_l = tid & 15;
+        const long long sm_n = n0 + min(sm_r, rows - 1);
+        const long long sm_a = sm_n * k + min(sm_l, k - 1);   // lane l has assignment l
+        const int sm_idx = idx[sm_a], sm_inv = inv[sm_a];
+        const float sm_d = dpk[sm_a], sm_u = rate > 0.f ? drop_u[sm_a] : 0.f;
+        float sm_noise[4], sm_b[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sm_b[i] = Storage<T>::load(br2 + (min(sm_l + 16 * i, E - 1) + here));
+        if (noise != nullptr)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) sm_noise[i] = noise[sm_n * E + min(sm_l + 16 * i, E - 1)];
         // ---- hidden layer: hidden units 4 lane .., slices 4 wave ..
+        float lw[16];      // of the logits: 32 hidden units of Wr2's column e
+        auto second_layer = [&](int kb, float (&b)[16]) {
+            const int e = min(32 * (wave % ET) + jj, E - 1);
+#pragma unroll
+            for (int s = 0; s < 16; ++s) {
+                const T *at = (const T *)((const char *)(Wr2 + (size_t)(kb + 2 * s) * E) + ((unsigned)(g * E + e) + here) * (unsigned)sizeof(T));
+                if (AHEAD) b[s] = Storage<T>::load(at);
+                else b[s] = kb + 2 * s + g < Hr ? Storage<T>::load(at) : 0.f;
+            }
+        };
         float acc[4][4];   // [slice][hidden unit]
+        float bias[4];
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const float b = 4 * lane + c < Hr ? Storage<T>::load(br1 + 4 * lane + c) : 0.f;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) acc[r][c] = b;
-        }
+        for (int c = 0; c < 4; ++c) bias[c] = AHEAD || 4 * lane + c < Hr ? Storage<T>::load(br1 + (4 * lane + here) + c) : 0.f;
         for (int ch = 0; ch < nch; ++ch) {
             const int c0 = ch * kGrFeat, nf = min(kGrFeat, ds - c0);
-            __syncthreads();   // everyone is done with the features before
-            stage_x(n0, rows, c0, nf);
-            if (nch > 1 || n0 == n_begin)
-                for (int t = tid; t < nf * kGbHidden; t += kGbThreads) {
-                    const int f = t / kGbHidden, j = t % kGbHidden;
-                    ws[t] = j < Hr ? Storage<T>::load(Wr1 + (size_t)(c0 + f) * Hr + j) : 0.f;
-                }
+            if (AHEAD && ch == nch - 1) second_layer(wave / ET * (kGbHidden / (kGbWaves / ET)), lw);
+            float xv[STAGED];
+            request_x(n0, rows, c0, nf, xv);
+            const bool weights = nch > 1 || n0 == n_begin;
+            if (AHEAD && weights) {   // every wavefront whole rows: a quad per lane, eight rows in flight
+                constexpr int QUADS = kGrFeat / kGbWaves;
+                float wv[QUADS][4];
+#pragma unroll
+                for (int q = 0; q < QUADS; ++q) Quad<T>::load(Wr1 + (size_t)(c0 + min(wave + q * kGbWaves, nf - 1)) * Hr + 4 * lane, wv[q]);
+                __syncthreads();   // everyone is done with the features before
+#pragma unroll
+                for (int q = 0; q < QUADS; ++q) *(float4 *)(ws + (wave + q * kGbWaves) * kGbHidden + 4 * lane) = make_float4(wv[q][0], wv[q][1], wv[q][2], wv[q][3]);
+            } else {
+                __syncthreads();
+                if (weights)
+                    for (int t = tid; t < nf * kGbHidden; t += kGbThreads) {
+                        const int f = t / kGbHidden, j = t % kGbHidden;
+                        ws[t] = j < Hr ? Storage<T>::load(Wr1 + (size_t)(c0 + f) * Hr + j) : 0.f;
+                    }
+            }
+            stage_x(rows, nf, xv);
             __syncthreads();
+            if (ch == 0)
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) acc[r][c] = bias[c];
             if (quads) {
                 for (int f = 0; f < nf; f += 4) {
                     float4 xq[4], wq[4];
@@ -371,35 +432,46 @@ __global__ __launch_bounds__(kGbThreads) void bwd_router_generic_kernel(
 #pragma unroll
             for (int c = 0; c < 4; ++c) us[(4 * wave + r) * UST + 4 * lane + c] = fmaxf(acc[r][c], 0.f);
         __syncthreads();
-        if (nch > 1) stage_x(n0, rows, own_c0, own_n);   // the block's own columns, for dWr1
+        if (nch > 1) {   // the block's own columns, for dWr1
+            float xv[STAGED];
+            request_x(n0, rows, own_c0, own_n, xv);
+            stage_x(rows, own_n, xv);
+        }
         {   // ---- logits: lane = expert, registers = slices; the hidden units of a 32-expert tile over 8 / ET wavefronts
-            const int et = wave % ET, parts = kGbWaves / ET, per = kGbHidden / parts, k0 = wave / ET * per, e = min(32 * et + jj, E - 1);
+            const int per = kGbHidden / (kGbWaves / ET), k0 = wave / ET * per;
             f32x16 lg;
 #pragma unroll
             for (int i = 0; i < 16; ++i) lg[i] = 0.f;
             for (int kb = k0; kb < k0 + per; kb += 32) {
-                float b[16];
+                if (!AHEAD || kb != k0) second_layer(kb, lw);
+                const float *u_b = us + jj * UST + kb + g;
 #pragma unroll
-                for (int s = 0; s < 16; ++s) b[s] = kb + 2 * s + g < Hr ? Storage<T>::load(Wr2 + (size_t)(kb + 2 * s + g) * E + e) : 0.f;
-#pragma unroll
-                for (int s = 0; s < 16; ++s) lg = mfma_f32(us[jj * UST + kb + 2 * s + g], b[s], lg);
+                for (int s = 0; s < 16; ++s) lg = mfma_f32(u_b[2 * s], lw[s], lg);
             }
 #pragma unroll
-            for (int i = 0; i < 16; ++i) red[(wave * kGbRows + acc_feature(i, g)) * kGbT + jj] = lg[i];
+            for (int i = 0; i < 16; ++i) red_w[acc_feature(i, 0) * kGbT] = lg[i];
         }
         __syncthreads();
+        float dw[AHEAD ? 4 : 1][4];   // of dL/du: the first 32 experts of Wr2's row hid
+        if (AHEAD)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) Quad<T>::load((const T *)((const char *)(Wr2 + min(8 * q, E - 8)) + ((unsigned)(hidc * E + 4 * g) + here) * (unsigned)sizeof(T)), dw[q]);
         {   // ---- softmax, back through the dropout's renormalisation, dL/dg: 16 lanes per slice, experts l, l + 16, ..
-            const int r = tid >> 4, l = tid & 15;
-            const long long n = n0 + min(r, rows - 1);
+            const int r = sm_r, l = sm_l;
             float v[4], m = -INFINITY, den = 0.f;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int e = l + 16 * i;
                 v[i] = -INFINITY;
                 if (e < E) {
-                    float t = Storage<T>::load(br2 + e);
-                    for (int q = 0; q < kGbWaves / ET; ++q) t += red[((q * ET + (e >> 5)) * kGbRows + r) * kGbT + (e & 31)];
-                    if (noise != nullptr) t = fmaf(sigma, noise[n * E + e], t);
+                    float t = sm_b[i];
+                    const float *at = red + ((e >> 5) * kGbRows + r) * kGbT + (e & 31);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) t += at[q * ET * kGbRows * kGbT];
+                    if (ET == 1)
+#pragma unroll
+                        for (int q = 4; q < kGbWaves; ++q) t += at[q * kGbRows * kGbT];
+                    if (noise != nullptr) t = fmaf(sigma, sm_noise[i], t);
                     v[i] = t;
                 }
                 m = fmaxf(m, v[i]);
@@ -423,16 +495,16 @@ __global__ __launch_bounds__(kGbThreads) void bwd_router_generic_kernel(
                 keep[j] = false;
                 ej[j] = 0;
                 if (j < k) {
-                    const long long a = n * k + j;
-                    ej[j] = min(max(idx[a], 0), E - 1);
+                    ej[j] = min(max(__shfl(sm_idx, j, 16), 0), E - 1);
                     float mine = 0.f;
 #pragma unroll
                     for (int i = 0; i < 4; ++i) mine = ej[j] == l + 16 * i ? v[i] : mine;
                     for (int o = 8; o > 0; o >>= 1) mine += __shfl_xor(mine, o);
                     psel[j] = mine;
-                    dpf[j] = inv[a] >= 0 ? dpk[a] : 0.f;   // a capacity-dropped assignment carries no gradient from h'
+                    const float dj = __shfl(sm_d, j, 16), uj = __shfl(sm_u, j, 16);
+                    dpf[j] = __shfl(sm_inv, j, 16) >= 0 ? dj : 0.f;   // a capacity-dropped assignment carries no gradient from h'
                     if (cap.slots != nullptr) dpf[j] += capg_s[ej[j]];   // but it counts as assigned (capacity loss)
-                    keep[j] = rate > 0.f ? !(drop_u[a] < rate) : true;
+                    keep[j] = rate > 0.f ? !(uj < rate) : true;
                     kept += keep[j] ? 1 : 0;
                 }
             }
@@ -468,54 +540,102 @@ __global__ __launch_bounds__(kGbThreads) void bwd_router_generic_kernel(
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             du[i] = 0.f;
-            uv[i] = us[acc_feature(i, g) * UST + hid];
+            uv[i] = u_r[acc_feature(i, 0) * UST];
         }
-        for (int kb = 0; kb < E; kb += 8) {
+        if (AHEAD)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (8 * q >= E) break;
+#pragma unroll
+                for (int s = 0; s < 4; ++s) du = mfma_f32(dg_b[8 * q + s], dw[q][s], du);
+            }
+        for (int kb = AHEAD ? 32 : 0; kb < E; kb += 8) {
             float v[4];
             load_quad(Wr2 + (size_t)hidc * E + kb + 4 * g, E - kb - 4 * g, vec_e, v);
 #pragma unroll
-            for (int s = 0; s < 4; ++s) du = mfma_f32(dgs[jj * GST + kb + 4 * g + s], v[s], du);
+            for (int s = 0; s < 4; ++s) du = mfma_f32(dg_b[kb + s], v[s], du);
+        }
+        const int dx_t = wave % OTC, dx_k0 = wave / OTC * (kGbHidden / PARTS), dx_f = min(32 * dx_t + jj, own_n - 1);
+        float bx[AHEAD ? 2 : 1][16];   // of dL/dh: the wavefront's 64 hidden units of Wr1's row dx_f
+        static_assert(kGbHidden / PARTS == 64, "two batches");
+        auto first_layer = [&](int kb, float (&b)[16]) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                float v[4];
+                const T *at = (const T *)((const char *)(Wr1 + (size_t)own_c0 * Hr + kb + 8 * q) + ((unsigned)(dx_f * Hr + 4 * g) + here) * (unsigned)sizeof(T));
+                if (AHEAD) Quad<T>::load(at, v);
+                else load_quad(at, Hr - (kb + 8 * q + 4 * g), vec_hr, v);
+#pragma unroll
+                for (int s = 0; s < 4; ++s) b[4 * q + s] = v[s];
+            }
+        };
+        // the expert path's rows of this thread's quad of dL/dh
+        float4 xr[AHEAD ? 2 : 1];
+        if (AHEAD) {
+#pragma unroll
+            for (int q = 0; q < 2; ++q) first_layer(dx_k0 + 32 * q, bx[q]);
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int row = __shfl(sm_inv, min(j, k - 1), 16);
+                xr[j] = *(const float4 *)(dxrow + (size_t)max(row, 0) * ds + own_c0 + 4 * sm_l);
+            }
         }
         __syncthreads();   // everyone has taken its u: the region now takes dL/du
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-            const int r = acc_feature(i, g);
+            const int row = acc_feature(i, 0);   // and 4 g more, in the bases
             const float d = hok && uv[i] > 0.f ? du[i] : 0.f;
             ab1 += d;
-            us[hid * kGbT + r] = d;
+            du_w[row] = d;
 #pragma unroll
-            for (int ot = 0; ot < OTC; ++ot) aW1[ot] = mfma_f32(xT[(32 * ot + jj) * 36 + r], d, aW1[ot]);   // [feature][hidden unit]
+            for (int ot = 0; ot < OTC; ++ot) aW1[ot] = mfma_f32(xT_r[32 * ot * 36 + row], d, aW1[ot]);   // [feature][hidden unit]
             if (own == 0) {
-                aW2[0] = mfma_f32(uv[i], dgs[r * GST + jj], aW2[0]);                                        // [hidden unit][expert]
-                if (ET > 1) aW2[1] = mfma_f32(uv[i], dgs[r * GST + 32 + jj], aW2[1]);
+                aW2[0] = mfma_f32(uv[i], dg_r[row * GST], aW2[0]);                                        // [hidden unit][expert]
+                if (ET > 1) aW2[1] = mfma_f32(uv[i], dg_r[row * GST + 32], aW2[1]);
             }
         }
         if (own == 0 && tid < E)
             for (int r = 0; r < rows; ++r) ab2 += dgs[r * GST + tid];
         __syncthreads();
         {   // ---- dL/dh of the slices, own columns: router path ...
-            const int ot = wave % OTC, k0 = wave / OTC * (kGbHidden / PARTS), f = min(32 * ot + jj, own_n - 1);
             f32x16 dx;
 #pragma unroll
             for (int i = 0; i < 16; ++i) dx[i] = 0.f;
-            const T *wf = Wr1 + (size_t)(own_c0 + f) * Hr;
-            for (int kb = k0; kb < min(k0 + kGbHidden / PARTS, Hr); kb += 32) {
-                float b[16];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    float v[4];
-                    load_quad(wf + kb + 8 * q + 4 * g, Hr - (kb + 8 * q + 4 * g), vec_hr, v);
+            for (int q = 0; q < 2; ++q) {
+                const int kb = dx_k0 + 32 * q;
+                if (kb >= Hr) break;
+                if (!AHEAD) first_layer(kb, bx[0]);
+                const float *du_b = us + (kb + 4 * g) * kGbT + jj;
 #pragma unroll
-                    for (int s = 0; s < 4; ++s) b[4 * q + s] = v[s];
-                }
-#pragma unroll
-                for (int s = 0; s < 16; ++s) dx = mfma_f32(us[(kb + 8 * (s >> 2) + 4 * g + (s & 3)) * kGbT + jj], b[s], dx);
+                for (int s = 0; s < 16; ++s) dx = mfma_f32(du_b[(8 * (s >> 2) + (s & 3)) * kGbT], bx[AHEAD ? q : 0][s], dx);
             }
 #pragma unroll
-            for (int i = 0; i < 16; ++i) red[(wave * kGbRows + acc_feature(i, g)) * kGbT + jj] = dx[i];
+            for (int i = 0; i < 16; ++i) red_w[acc_feature(i, 0) * kGbT] = dx[i];
         }
         __syncthreads();
-        for (int t = tid; t < rows * own_n; t += kGbThreads) {   // ... plus the expert-path rows of the k assignments
+        // ... plus the expert-path rows of the k assignments
+        if (AHEAD) {   // a quad per thread
+            float v[4];
+            const float *at = red + ((sm_l >> 3) * kGbRows + sm_r) * kGbT + (4 * sm_l & 31);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                v[c] = 0.f;
+#pragma unroll
+                for (int q = 0; q < PARTS; ++q) v[c] += at[q * OTC * kGbRows * kGbT + c];
+            }
+            auto add = [&](int j, float4 w) {
+                const float wc[4] = {w.x, w.y, w.z, w.w};
+                const bool has = j < k && __shfl(sm_inv, min(j, k - 1), 16) >= 0;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) v[c] = has ? v[c] + wc[c] : v[c];
+            };
+            add(0, xr[0]);
+            add(1, xr[1]);
+            for (int j = 2; j < k; ++j) add(j, *(const float4 *)(dxrow + (size_t)max(__shfl(sm_inv, j, 16), 0) * ds + own_c0 + 4 * sm_l));
+            if (sm_r < rows) store_quad(dh + sm_n * ds + own_c0 + 4 * sm_l, v);
+        } else
+        for (int t = tid; t < rows * own_n; t += kGbThreads) {
             const int r = t / own_n, f = t - r * own_n;
             const long long n = n0 + r;
             float v = 0.f;
@@ -638,7 +758,9 @@ static hipError_t run_router(const slicemoe_config &c, const void *h, const slic
     const long long Ns = (long long)c.T * c.S;
     const int ds = c.d / c.S;
     const size_t lds = GenericRouterLds::total * sizeof(float);
-    auto kern = bwd_router_generic_kernel<T>;
+    const bool ahead = c.Hr == kGbHidden && ds % kGrFeat == 0 && c.E % 8 == 0 && quad_aligned<T>(w.Wr1, c.Hr) && quad_aligned<T>(w.Wr2, c.E) &&
+                       quad_aligned<T>(d_h, ds) && quad_aligned<float>(dxrow, ds);
+    auto kern = ahead ? bwd_router_generic_kernel<T, true> : bwd_router_generic_kernel<T, false>;
     const hipError_t e = grant_dynamic_lds((const void *)kern, lds);
     if (e != hipSuccess) return e;
     kern<<<dim3((unsigned)backward_generic_router_slots(c), (unsigned)((ds + kGrFeat - 1) / kGrFeat)), kGbThreads, lds, s>>>(

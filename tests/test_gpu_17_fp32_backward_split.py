@@ -1,7 +1,9 @@
 """The fp32 expert backward.  How it hands its units of 32 rows to the blocks: one unit per block up to as many units as there are
 compute units, two from the next one on (the blocks of the second half then have none), experts without rows, a single row, and
 one expert with every row.  And the instances that request weights a batch ahead (32 and 64 columns, whole quads): hidden widths that
-leave wavefronts without hidden units, without a part of dL/dx, or with a second group of 256.  Every gradient against the fp64 oracle on the routing that the forward call left behind.  Bars: those of the fp32 edge
+leave wavefronts without hidden units, without a part of dL/dx, or with a second group of 256.  And the router instance that does so
+(256 hidden units, whole chunks of 64 columns, whole octets of experts): one chunk and two, one and two tiles of experts, one to four
+assignments of which a capacity limit drops some, several units per block.  Every gradient against the fp64 oracle on the routing that the forward call left behind.  Bars: those of the fp32 edge
 tests (1e-4 of the RMS for dL/dh; 5e-4 of the RMS for the weight gradients): only the order of fp32 sums of at most 9000 terms differs."""
 import numpy as np
 import pytest
@@ -15,8 +17,8 @@ pytestmark = pytest.mark.gpu
 NAMES = ("Wr1", "br1", "Wr2", "br2", "W1", "b1", "W2", "b2")
 
 
-def shape(T, E, k, S=4, ds=16, He=32):
-    return wl.SliceMoEShape("split", T=T, d=S * ds, S=S, E=E, k=k, He=He, dtype="f32", Hr=32)
+def shape(T, E, k, S=4, ds=16, He=32, Hr=32, cf=0.0):
+    return wl.SliceMoEShape("split", T=T, d=S * ds, S=S, E=E, k=k, He=He, dtype="f32", Hr=Hr, capacity_factor=cf)
 
 
 CASES = {   # the expert that the router's bias prefers, if any: then units are as many as its rows need
@@ -31,11 +33,14 @@ CASES = {   # the expert that the router's bias prefers, if any: then units are 
     "w64_three_tiles": (shape(50, 3, 2, ds=64, He=96), None),
     "w64_two_groups": (shape(50, 3, 2, ds=64, He=288), None),
     "w64_units_per_block": (shape(2100, 2, 1, ds=64, He=64), 1),
+    "router_one_expert_tile": (shape(11, 8, 1, ds=64, Hr=256), None),
+    "router_two_expert_tiles": (shape(40, 40, 4, ds=128, Hr=256, cf=0.7), None),
+    "router_units_per_block": (shape(2100, 16, 3, ds=64, Hr=256), None),
 }
 
 
 @pytest.mark.parametrize("name", list(CASES))
-def test_gradients_at_the_edges_of_the_split(name):
+def test_gradients_at_the_edges(name):
     import torch
     from paper_2510_04286_amd import binding as B
     case, hot = CASES[name]
