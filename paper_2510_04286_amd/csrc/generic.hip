@@ -136,7 +136,7 @@ __global__ __launch_bounds__(kGenThreads) void route_generic_kernel(
 // are coalesced rows of W1), registers = rows; the activations go to LDS; second product: lane = output feature, the
 // hidden units of a tile split over several wavefronts when there are fewer output tiles than wavefronts.  Bound by the
 // matrix instruction (64 cycles each) and the latency of the first weights; 4096 rows, ds = 64, He = 256: 75 ->
-// 16 us (one thread per hidden unit reading its weights once per row before).
+// 16 us (one thread per hidden unit reading its weights once per row before).  Takes what ffn_generic_ahead_kernel does not.
 constexpr int kF32Threads = 512, kF32Waves = 8, kF32Rows = 32;
 constexpr int kF32Feat = 128;              // features of the rows staged at a time
 constexpr int kF32Hidden = 32 * kF32Waves;  // hidden units at a time
@@ -257,6 +257,111 @@ __global__ __launch_bounds__(kF32Threads) void ffn_generic_kernel(
     }
 }
 
+// The same for slices of exactly 32 OT columns and hidden widths of whole tiles, sums in the same order.  Such a layer's batches are
+// mostly smaller than the chip, and then a block's time is the latency of its loads, one behind the other; without conditions they can
+// all be requested ahead: the first product's weights with the rows, the second's before the activations, the output's bias with
+// those.  Every wavefront reads the unit's indexes itself, so that there is no barrier between an index and its row.
+// 8000 rows, ds = 64, He = 256: 18 -> 13 us; 32 768 rows (a forward pass): 108 -> 73 us, two blocks per compute unit instead of one
+// (128 registers, 144 before); ds = 32, He = 128, 131 072 rows: 289 -> 140.
+template <typename T, typename YT, int OT>
+__global__ __launch_bounds__(kF32Threads, 4) void ffn_generic_ahead_kernel(
+    const T *__restrict__ x, const float *__restrict__ pk, const int32_t *__restrict__ offsets,
+    const int32_t *__restrict__ perm, int He, int E, int k,
+    const T *__restrict__ W1, const T *__restrict__ b1, const T *__restrict__ W2, const T *__restrict__ b2,
+    YT *__restrict__ y)
+{
+    constexpr int DS = 32 * OT, XST = DS + 1, HST = kF32Hidden + 1, PARTS = kF32Waves / OT;
+    constexpr int ROWS = kF32Threads / DS, STAGED = kF32Rows / ROWS;   // staging: a thread has one column of every ROWS-th row
+    __shared__ float xs[kF32Rows * XST];                     // p x
+    __shared__ float hs[kF32Waves * kF32Rows * 33];          // activations [row][HST]; then partial outputs [wavefront][row][33]
+    const int tid = threadIdx.x, lane = tid & 63, jj = lane & 31, g = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int off_lo = offsets[min(lane, E)], off_hi = offsets[min(lane + 1, E)];
+    const int units = (off_hi - off_lo + kF32Rows - 1) / kF32Rows, first = wavefront_exclusive_scan(units, lane);
+    const unsigned long long mine = __ballot((int)blockIdx.x >= first && (int)blockIdx.x < first + units);
+    if (mine == 0) return;   // the grid is an upper bound; uniform
+    const int e = __builtin_ctzll(mine);
+    const int row0 = __builtin_amdgcn_readlane(off_lo, e) + ((int)blockIdx.x - __builtin_amdgcn_readlane(first, e)) * kF32Rows;
+    const int nrows = min(kF32Rows, __builtin_amdgcn_readlane(off_hi, e) - row0);
+    const T *w1 = W1 + (size_t)e * DS * He, *w2 = W2 + (size_t)e * He * DS;
+    const int a = perm[row0 + min(jj, nrows - 1)];
+    const int st_c = tid % DS, st_r = tid / DS, tile = wave % OT, part = wave / OT;
+    const float *xs_b = xs + jj * XST + g;
+    float *hs_w = hs + 4 * g * HST + wave * 32 + jj;
+
+    f32x16 yacc;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) yacc[i] = 0.f;
+    float ybias = 0.f;
+    for (int h0 = 0; h0 < He; h0 += kF32Hidden) {
+        const int hid = h0 + wave * 32 + jj, hidc = min(hid, He - 1);
+        const float bias = Storage<T>::load(b1 + (size_t)e * He + hidc);
+        float b[OT][16];
+#pragma unroll
+        for (int t = 0; t < OT; ++t)
+#pragma unroll
+            for (int s = 0; s < 16; ++s) b[t][s] = Storage<T>::load(w1 + (size_t)(32 * t + 2 * s) * He + (unsigned)(g * He + hidc));
+        if (h0 == 0) {
+            const int n = a / k;
+            const float p = pk[a];
+            float xv[STAGED];
+#pragma unroll
+            for (int q = 0; q < STAGED; ++q) xv[q] = Storage<T>::load(x + (size_t)__shfl(n, st_r + q * ROWS) * DS + st_c);
+#pragma unroll
+            for (int q = 0; q < STAGED; ++q) {
+                const int r = st_r + q * ROWS;
+                const float pr = __shfl(p, r);
+                xs[r * XST + st_c] = r < nrows ? pr * xv[q] : 0.f;
+            }
+            __syncthreads();
+        }
+        f32x16 z;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) z[i] = bias;
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int t = 0; t < OT; ++t)
+#pragma unroll
+            for (int s = 0; s < 16; ++s) z = __builtin_amdgcn_mfma_f32_32x32x2f32(xs_b[32 * t + 2 * s], b[t][s], z, 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int t = 0; t < OT; ++t) {
+            const int kb = min(part * DS + 32 * t, He - h0 - 32);   // (those past the end are not used)
+#pragma unroll
+            for (int s = 0; s < 16; ++s) b[t][s] = Storage<T>::load(w2 + (size_t)(h0 + kb + 2 * s) * DS + (unsigned)(g * DS + 32 * tile + jj));
+        }
+        if (h0 == 0) ybias = Storage<T>::load(b2 + (size_t)e * DS + st_c);
+        __builtin_amdgcn_sched_barrier(0);
+        if (h0 > 0) __syncthreads();   // everyone is done with the activations before
+        if (h0 + 32 * wave < He)   // what lies past the end is not read
+#pragma unroll
+            for (int i = 0; i < 16; ++i) hs_w[acc_feature(i, 0) * HST] = 0.5f * z[i] * (1.f + erff(z[i] * 0.70710678118654752f));
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < OT; ++t) {
+            const int kb = part * DS + 32 * t;
+            if (kb >= He - h0) break;
+            const float *hs_b = hs + jj * HST + kb + g;
+#pragma unroll
+            for (int s = 0; s < 16; ++s) yacc = __builtin_amdgcn_mfma_f32_32x32x2f32(hs_b[2 * s], b[t][s], yacc, 0, 0, 0);
+        }
+    }
+    __syncthreads();
+    float *out_w = hs + (wave * kF32Rows + 4 * g) * 33 + jj;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) out_w[acc_feature(i, 0) * 33] = yacc[i];
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < STAGED; ++q) {
+        const int r = st_r + q * ROWS;
+        const float *at = hs + ((st_c >> 5) * kF32Rows + r) * 33 + (st_c & 31);
+        float v = ybias;
+#pragma unroll
+        for (int u = 0; u < PARTS; ++u) v += at[u * OT * kF32Rows * 33];
+        if (r < nrows) y[(size_t)(row0 + r) * DS + st_c] = (YT)v;
+    }
+}
+
 template <typename T>
 static void run_route_generic(const slicemoe_config &c, const void *h, const slicemoe_weights &w, int32_t *idx, float *p, hipStream_t s,
                               const RouteVariant &v, uint16_t *hist, int hist_stride)
@@ -310,6 +415,12 @@ static void run_ffn_generic(const slicemoe_config &c, const void *h, const float
     const long long blocks = Na / kF32Rows + (Na < c.E ? Na : c.E);                 // at most one partial unit per expert
     auto kern = no <= 1 ? ffn_generic_kernel<T, YT, 1> : no <= 2 ? ffn_generic_kernel<T, YT, 2> : no <= 4 ? ffn_generic_kernel<T, YT, 4>
                                                                                                : ffn_generic_kernel<T, YT, 8>;
+    if ((ds == 32 || ds == 64) && c.He % 32 == 0) {   // faster at every batch measured, one row to 131 072: 1.14 to 2.1 times (a forward pass)
+        auto ahead = ds == 32 ? ffn_generic_ahead_kernel<T, YT, 1> : ffn_generic_ahead_kernel<T, YT, 2>;
+        ahead<<<(unsigned)blocks, kF32Threads, 0, s>>>((const T *)h, p, offsets, perm, c.He, c.E, c.k, (const T *)w.W1, (const T *)w.b1,
+                                                       (const T *)w.W2, (const T *)w.b2, (YT *)y);
+        return;
+    }
     kern<<<(unsigned)blocks, kF32Threads, 0, s>>>((const T *)h, p, offsets, perm, ds, c.He, c.E, c.k, (const T *)w.W1, (const T *)w.b1,
                                                   (const T *)w.W2, (const T *)w.b2, (YT *)y);
 }

@@ -1,4 +1,4 @@
-"""The fp32 expert backward.  How it hands its units of 32 rows to the blocks: one unit per block up to as many units as there are
+"""The fp32 kernels' split and the instances that request weights ahead.  How the expert backward hands its units of 32 rows to the blocks: one unit per block up to as many units as there are
 compute units, two from the next one on (the blocks of the second half then have none), experts without rows, a single row, and
 one expert with every row.  And the instances that request weights a batch ahead (32 and 64 columns, whole quads): hidden widths that
 leave wavefronts without hidden units, without a part of dL/dx, or with a second group of 256.  And the router instance that does so
@@ -10,7 +10,7 @@ import pytest
 
 import oracle
 from paper_2510_04286_amd import workload as wl
-from tests.common import TOL_F32, make_inputs, rms
+from tests.common import TOL_F32, make_inputs, rms, routing_agreement
 
 pytestmark = pytest.mark.gpu
 
@@ -68,3 +68,30 @@ def test_gradients_at_the_edges(name):
     print(f"\n[{name}] dL/dh {err_h:.1e}; " + " ".join(f"{n} {e:.1e}" for n, e in err.items()))
     assert err_h <= TOL_F32
     assert max(err.values()) <= 5e-4, err
+
+
+FORWARD = {   # the expert kernel that requests ahead: 32 and 64 columns, hidden widths of one tile, some, all wavefronts' and two groups
+    "w32_one_tile": shape(50, 3, 2, ds=32, He=32),
+    "w32_seven_tiles": shape(21, 5, 3, ds=32, He=224, cf=0.6),
+    "w64_three_tiles": shape(50, 3, 2, ds=64, He=96),
+    "w64_two_groups": shape(50, 3, 2, ds=64, He=288),
+    "w64_one_row": shape(1, 2, 1, S=1, ds=64, He=256),
+}
+
+
+@pytest.mark.parametrize("name", list(FORWARD))
+def test_forward_at_the_edges(name):
+    import torch
+    from paper_2510_04286_amd import binding as B
+    s, h, w = make_inputs(FORWARD[name])
+    cfg = B.config_of(s)
+    ref = oracle.forward_train(h, s.S, s.k, w, noise=None, drop_u=None, capacity=s.capacity(), tau=1.0, sigma=0.0, rate=0.0)
+    wd, ws, hd = B.weights_to_device(w, s.dtype), B.alloc_workspace(cfg), B.to_device(h, s.dtype)
+    out = torch.full_like(hd, 3.0)
+    B.slicemoe_forward(cfg, hd, wd, out, ws)
+    torch.cuda.synchronize()
+    _, n_tie = routing_agreement(B.workspace_views(cfg, ws)["topk_idx"].cpu().numpy(), ref["idx"], ref["logits"])
+    assert n_tie == 0, "this case was chosen to have no near-tie; pick another token count"
+    err = np.abs(out.cpu().numpy() - ref["h_out"]).max() / rms(ref["h_out"])
+    print(f"\n[{name}] h' {err:.1e}")
+    assert err <= TOL_F32
