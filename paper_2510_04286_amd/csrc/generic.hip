@@ -3,22 +3,26 @@
 #include "mfma.h"
 #include "output_role.h"
 #include "wavefront.h"
+#include <type_traits>
 
 namespace slicemoe {
 
 constexpr int kRB = 8;          // slices per block of the router
 constexpr int kGenThreads = 256;
 constexpr int kW2LdsBytes = 40 * 1024;   // Wr2 goes to LDS up to this size (fp32)
+constexpr int kW2Rows = 1, kW2Columns = 2;   // ... a row of it per hidden unit, or a column per expert in quads (Hr a multiple of 4)
 
 // Router of paper Section 3.1: g = ReLU(x Wr1 + br1) Wr2 + br2, softmax over E, top-k on the fp32 logits with ties to the
 // lower expert index.  Every pre-activation and logit is one chain of fused multiply-adds in ascending input order (which
 // experts win, and which hidden units are active, depends on no split of the sums), so the chains are what bounds it: one
 // thread per hidden unit with eight slices side by side; one thread per logit, fed from LDS; 32 lanes per slice for the
 // softmax and the selection.  2048 slices, ds = 64, Hr = 256, E = 8: 15.3 -> 11.5 us (logits from memory, softmax
-// by one thread per slice before).
+// by one thread per slice before).  A logit's chain reads four hidden units of the slice and of its expert per LDS access (kW2Columns: Wr2
+// by columns) where there was one, and the softmax and the selection go only as far across the lanes as there are experts: forward
+// of 2048 slices 29.9 -> 29.1 us, of 16 384 72.8 -> 70.1, of 65 536 with E = 16 140 -> 131.
 // HIST: leaves the block's chunk of the dispatch histogram behind.  An instance of its own: with a test of the table's address instead, the
 // large batches that have no use for it took 5% longer (the router alone, E = 8, k = 2, 131 072 slices: 142 us against 133).
-template <typename T, bool W2LDS, bool DROP, bool HIST>
+template <typename T, int W2LDS /* 0, kW2Rows or kW2Columns */, bool DROP, bool HIST>
 __global__ __launch_bounds__(kGenThreads) void route_generic_kernel(
     const T *__restrict__ x, long long Ns, int ds, int Hr, int E, int k,
     const T *__restrict__ Wr1, const T *__restrict__ br1, const T *__restrict__ Wr2, const T *__restrict__ br2,
@@ -27,11 +31,13 @@ __global__ __launch_bounds__(kGenThreads) void route_generic_kernel(
 {
     __shared__ int counts[HIST ? 64 : 1];   // selections of this block per expert
     extern __shared__ __align__(16) float smem[];
-    const int dsp = (ds + 3) & ~3, ust = Hr + 1;   // row strides: whole quads of features; hidden units of neighbouring slices in different banks
+    constexpr bool QUADS = W2LDS == kW2Columns;
+    // row strides: whole quads of features; hidden units of neighbouring slices in different banks, in quads where Wr2's are
+    const int dsp = (ds + 3) & ~3, ust = QUADS ? Hr + 4 : Hr + 1, wst = Hr + 4;
     float *xs = smem;                 // [kRB][dsp]
     float *us = xs + kRB * dsp;       // [kRB][ust]
     float *gs = us + kRB * ust;       // [kRB][E]
-    float *w2s = gs + kRB * E;        // [Hr][E] (W2LDS only)
+    float *w2s = gs + kRB * E;        // [Hr][E], or [E][wst] (W2LDS only)
     const int tid = threadIdx.x;
     if (HIST && tid < 64) counts[tid] = 0;
     const long long n0 = (long long)blockIdx.x * kRB;
@@ -42,7 +48,11 @@ __global__ __launch_bounds__(kGenThreads) void route_generic_kernel(
         xs[i] = r < rows && c < ds ? Storage<T>::load(x + (n0 + r) * ds + c) : 0.f;
     }
     if (W2LDS)
-        for (int i = tid; i < Hr * E; i += kGenThreads) w2s[i] = Storage<T>::load(Wr2 + i);
+        for (int i = tid; i < Hr * E; i += kGenThreads) {
+            const float v = Storage<T>::load(Wr2 + i);
+            if (QUADS) w2s[i % E * wst + i / E] = v;
+            else w2s[i] = v;
+        }
     __syncthreads();
     for (int j = tid; j < Hr; j += kGenThreads) {
         float acc[kRB];
@@ -76,21 +86,33 @@ __global__ __launch_bounds__(kGenThreads) void route_generic_kernel(
     for (int t = tid; t < kRB * E; t += kGenThreads) {
         const int r = t / E, e = t - r * E;
         float acc = Storage<T>::load(br2 + e);
+        const float draw = noise != nullptr && r < rows ? noise[(n0 + r) * E + e] : 0.f;
+        if (QUADS) {   // four hidden units of the slice and of the expert per load
+#pragma unroll 8
+            for (int j = 0; j < Hr; j += 4) {
+                const float4 u = *(const float4 *)(us + r * ust + j), w = *(const float4 *)(w2s + e * wst + j);
+                acc = fmaf(u.x, w.x, acc);
+                acc = fmaf(u.y, w.y, acc);
+                acc = fmaf(u.z, w.z, acc);
+                acc = fmaf(u.w, w.w, acc);
+            }
+        } else
 #pragma unroll 8
         for (int j = 0; j < Hr; ++j) acc = fmaf(us[r * ust + j], W2LDS ? w2s[j * E + e] : Storage<T>::load(Wr2 + (size_t)j * E + e), acc);
         // training-time logit noise (Section 5): before the selection and the softmax
-        if (noise != nullptr && r < rows) acc = fmaf(sigma, noise[(n0 + r) * E + e], acc);
+        if (noise != nullptr && r < rows) acc = fmaf(sigma, draw, acc);
         gs[t] = acc;
     }
     __syncthreads();
     // 32 lanes per slice, experts l and l + 32
     const int r = tid >> 5, l = tid & 31;
     static_assert(kGenThreads == 32 * kRB, "32 lanes per slice");
+    const int far = E > 16 ? 16 : E > 8 ? 8 : 4;   // the furthest lane that has an expert is less than twice as far
     float v0 = l < E ? gs[r * E + l] : -INFINITY, v1 = l + 32 < E ? gs[r * E + l + 32] : -INFINITY;
     float m = fmaxf(v0, v1);
-    for (int o = 16; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+    for (int o = far; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
     float den = (l < E ? expf((v0 - m) * inv_tau) : 0.f) + (l + 32 < E ? expf((v1 - m) * inv_tau) : 0.f);   // softmax of g / tau (Appendix B)
-    for (int o = 16; o > 0; o >>= 1) den += __shfl_xor(den, o);
+    for (int o = far; o > 0; o >>= 1) den += __shfl_xor(den, o);
     const long long n = n0 + r;
     for (int j = 0; j < k; ++j) {
         float bv = v0;
@@ -99,7 +121,7 @@ __global__ __launch_bounds__(kGenThreads) void route_generic_kernel(
             bv = v1;
             best = l + 32;
         }
-        for (int o = 16; o > 0; o >>= 1) {
+        for (int o = far; o > 0; o >>= 1) {
             const float ov = __shfl_xor(bv, o);
             const int oe = __shfl_xor(best, o);
             if (ov > bv || (ov == bv && oe < best)) {
@@ -370,16 +392,24 @@ static void run_route_generic(const slicemoe_config &c, const void *h, const sli
     const int ds = c.d / c.S;
     const int blocks = (int)((Ns + kRB - 1) / kRB);
     const float *noise = v.sigma > 0.f ? v.noise : nullptr;
-    const size_t smem = sizeof(float) * (size_t)kRB * (((ds + 3) & ~3) + c.Hr + 1 + c.E), w2 = sizeof(float) * (size_t)c.Hr * c.E;
-    const bool w2lds = w2 <= kW2LdsBytes && smem + w2 <= 64 * 1024 - (hist != nullptr ? 256 : 0);   // (256 bytes: the counts)
+    const size_t rest = (size_t)kRB * (((ds + 3) & ~3) + c.E);                       // floats: slices and logits
+    const size_t rows = rest + (size_t)kRB * (c.Hr + 1) + (size_t)c.Hr * c.E;        // with the hidden units and Wr2, in either layout
+    const size_t quads = rest + (size_t)kRB * (c.Hr + 4) + (size_t)(c.Hr + 4) * c.E;
+    const size_t limit = (64 * 1024 - (hist != nullptr ? 256 : 0)) / sizeof(float);   // (256 bytes: the counts)
+    const bool small = sizeof(float) * (size_t)c.Hr * c.E <= kW2LdsBytes;
+    const int place = small && c.Hr % 4 == 0 && quads <= limit ? kW2Columns : small && rows <= limit ? kW2Rows : 0;
+    const size_t smem = sizeof(float) * (place == kW2Columns ? quads : place == kW2Rows ? rows : rest + (size_t)kRB * (c.Hr + 1));
     const bool drop = v.rate > 0.f;
-    auto kern = hist != nullptr ? (w2lds ? (drop ? route_generic_kernel<T, true, true, true> : route_generic_kernel<T, true, false, true>)
-                                         : (drop ? route_generic_kernel<T, false, true, true> : route_generic_kernel<T, false, false, true>))
-                                : (w2lds ? (drop ? route_generic_kernel<T, true, true, false> : route_generic_kernel<T, true, false, false>)
-                                         : (drop ? route_generic_kernel<T, false, true, false> : route_generic_kernel<T, false, false, false>));
-    kern<<<blocks, kGenThreads, smem + (w2lds ? w2 : 0), s>>>((const T *)h, Ns, ds, c.Hr, c.E, c.k, (const T *)w.Wr1, (const T *)w.br1,
-                                                              (const T *)w.Wr2, (const T *)w.br2, noise, v.sigma, v.inv_tau,
-                                                              v.drop_u, v.rate, idx, p, hist, hist_stride);
+    auto pick = [&](auto placed) {
+        constexpr int W = decltype(placed)::value;
+        return hist != nullptr ? (drop ? route_generic_kernel<T, W, true, true> : route_generic_kernel<T, W, false, true>)
+                               : (drop ? route_generic_kernel<T, W, true, false> : route_generic_kernel<T, W, false, false>);
+    };
+    auto kern = place == kW2Columns ? pick(std::integral_constant<int, kW2Columns>())
+                : place == kW2Rows  ? pick(std::integral_constant<int, kW2Rows>())
+                                    : pick(std::integral_constant<int, 0>());
+    kern<<<blocks, kGenThreads, smem, s>>>((const T *)h, Ns, ds, c.Hr, c.E, c.k, (const T *)w.Wr1, (const T *)w.br1, (const T *)w.Wr2,
+                                           (const T *)w.br2, noise, v.sigma, v.inv_tau, v.drop_u, v.rate, idx, p, hist, hist_stride);
 }
 
 // A block's slices are a chunk of the dispatch histogram, in batches whose table is small enough for the scatter blocks to sum it: up to
