@@ -182,10 +182,11 @@ BackwardPlan backward_plan(const slicemoe_config &c)
 }
 
 // ---- A stream of the library's own, beside the caller's, for experts whose weight gradients are a kernel of their own (more
-// hidden tiles than a block, or a width above 64).  That kernel and the reduction after it depend on nothing that the rest of
-// the backward produces, and nothing but the caller depends on them, so they run on this stream while the row gradients and
+// hidden tiles than a block at width 64, the widths above 96, and 96 where the one pass is slower).  That kernel and the
+// reduction after it depend on nothing that the rest of the backward produces, and nothing but the caller depends on
+// them, so they run on this stream while the row gradients and
 // the router's kernels run on the caller's: the two chains fill each other's launch gaps and tails.  Whole backward, one
-// stream / two: width 96, He 384: T = 1024 130 / 105 us, T = 8191 278 / 250; width 128, He 512: T = 1024 349 / 283,
+// stream / two: width 96, He 384: T = 1024 130 / 105 us; width 128, He 512: T = 1024 349 / 283,
 // T = 16384 2538 / 2483; width 192, He 768: T = 1000 325 / 248, T = 4096 730 / 487; width 64, He 288: T = 16384 692 / 694.
 // One stream and two events per device, made at the first such backward on
 // that device and kept until the process ends; default priority, no implicit synchronisation with the null stream.
