@@ -317,7 +317,7 @@ __global__ __launch_bounds__(WAVES * 64, MINWAVES) void bwd_expert_kernel(
                         for (int c = 0; c < 4; ++c) z[c] = fmaf(pv[c], u[rt][c], bias);
                         twice_gelu4(z, act, slope);
 #pragma unroll
-                        for (int c = 0; c < 4; ++c) dz[c] = fmaf(da[rt][c], slope[c], da[rt][c]);   // twice dL/dz
+                        for (int c = 0; c < 4; ++c) dz[c] = da[rt][c] * slope[c];   // twice dL/dz
 #pragma unroll
                         for (int c = 0; c < 4; ++c) pd[c] = pv[c] * dz[c];
                         split_terms<TERMS>(act, a1, 2 * rt);

@@ -292,7 +292,7 @@ __global__ __launch_bounds__(kBmTileWaves<DS> * 64) void bwd_rows_streamed_mfma_
                     twice_gelu4(z, act, slope);
 #pragma unroll
                     for (int c = 0; c < 4; ++c) {
-                        const float dz = fmaf(da[4 * qq + c], slope[c], da[4 * qq + c]);   // twice dL/dz
+                        const float dz = da[4 * qq + c] * slope[c];   // twice dL/dz
                         dps[4 * (qq & 1) + c] = fmaf(dz, u[4 * qq + c], dps[4 * (qq & 1) + c]);
                         pdz[c] = half_p * dz;
                     }

@@ -377,7 +377,7 @@ __global__ __launch_bounds__(WAVES * 64, MINWAVES) void bwd_weights_kernel(
                         if (half == 1 && o1 < o2) second_load(0, o1);
                         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                        for (int c = 0; c < 4; ++c) dz[c] = fmaf(da[4 * q + c], slope[c], da[4 * q + c]);   // twice dL/dz
+                        for (int c = 0; c < 4; ++c) dz[c] = da[4 * q + c] * slope[c];   // twice dL/dz
 #pragma unroll
                         for (int c = 0; c < 4; ++c) pd[c] = pv[c] * dz[c];
                         split_terms<TERMS>(act, a1[half], 2 * qd);

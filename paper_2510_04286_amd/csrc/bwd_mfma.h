@@ -1,6 +1,7 @@
 // Shared pieces of the matrix-core backward kernels: fragment packing from a strided (possibly transposed) source,
-// the normal CDF and density, bf16 pair conversions.  See mfma.h for the operand layouts.
+// the activation and its derivative, bf16 pair conversions.  See mfma.h for the operand layouts.
 #pragma once
+#include "gelu_grad.h"
 #include "mfma.h"
 #include "wavefront.h"
 
@@ -156,19 +157,23 @@ hipError_t launch_backward_weights(const slicemoe_config &c, const BwdPacked &L,
                                    const int32_t *offsets, const int32_t *perm, const char *packed, size_t slot_floats, float *part,
                                    float *dxrow, float *dpk, hipStream_t s);
 
-// GELU and its derivative of four values: act = 2 z Phi(z) and slope with gelu'(z) = (1 + slope) / 2 (the factors of two, exact,
-// are taken out of the finished sums).  With x = |z|, e = exp(-x^2 / 2), t = 1 / (1 + 0.3 x): erf(x / sqrt 2) = 1 - e + x e N(t), where
-// N(t) = (1 - 2 Phi(-x) / e) / x is a quintic in t fitted to the least largest error (8e-9 of Phi; tighter below x = 1).  Both 1 - e and x e N(t)
-// vanish with x, so nothing cancels for small arguments: in fp32 the activation and the derivative are within 4.9e-8 of 64-bit
-// arithmetic (relative 2-norm, z normal with standard deviation 0.1 to 2.5), erff and expf give 4.0e-8, Abramowitz & Stegun 7.1.26
-// 5.9e-8 to 1.7e-7, for the same number of instructions as the last.
+// Twice GELU and twice its derivative of four values (the factors of two, exact, are taken out of the finished sums).  With x = |z|,
+// e = exp(-x^2 / 2), t = 1 / (1 + 0.3 x) and the quintic N(t) of gelu_grad.h: q = 2 Phi(-x) = e - x e N, and r = q - 2 x phi(x) is twice the
+// derivative at -x.  Then 2 z Phi(z) = (z + x) - x q, and the derivative is r below zero and 2 - r above: q and r keep a precision of their
+// own, where z (1 + erf) below zero has that of one.  Relative 2-norm of the error against 64-bit arithmetic, activation / derivative
+// (fp32, half a unit of error in the hardware's exponential):
+//                        this                                  1 + erf, same N          erff and expf            A & S 7.1.26
+//   z ~ N(0, 0.1 .. 2.5) 2.4e-8 .. 4.7e-8 / 3.6e-8 .. 5.1e-8   2.9e-8 .. 4.4e-8 / 4.9e-8   3.3e-8 .. 4.0e-8 / 4.0e-8  5.9e-8 .. 1.5e-7 / 1.7e-7
+//   z ~ N(-2, 0.3)       1.8e-7 / 1.3e-7                       4.9e-7 / 2.7e-7          3.3e-7 / 1.3e-7          1.7e-6 / 6.7e-7
+//   z ~ N(-5, 0.3)       5.4e-5 / 2.9e-6                       6.7e-3 / 5.5e-4          4.7e-3 / 2.2e-4          7.3e-4 / 3.9e-5
+// It takes two vector instructions more per element than 1 + erf (fused kernel's training step 529 -> 537 us), as many transcendental ones as the last.
 // Four side by side: a vector instruction that needs the result of the one before waits 8.3 cycles for it.
 __device__ __forceinline__ void twice_gelu4(const float (&z)[4], float (&act)[4], float (&slope)[4])
 {
-    float e[4], t[4], n[4], xe[4], g[4];
+    float e[4], t[4], n[4], q[4], xe[4], r[4];
 #define SLICEMOE_EACH for (int i = 0; i < 4; ++i)
 #pragma unroll
-    SLICEMOE_EACH t[i] = fmaf(0.3f, fabsf(z[i]), 1.f);
+    SLICEMOE_EACH t[i] = fmaf(kGeluGradP, fabsf(z[i]), 1.f);
 #pragma unroll
     SLICEMOE_EACH e[i] = z[i] * -0.72134752044448170f;   // exp(-z^2 / 2) = 2^(-z^2 log2(e) / 2)
 #pragma unroll
@@ -176,27 +181,23 @@ __device__ __forceinline__ void twice_gelu4(const float (&z)[4], float (&act)[4]
 #pragma unroll
     SLICEMOE_EACH e[i] = __builtin_amdgcn_exp2f(e[i] * z[i]);
 #pragma unroll
-    SLICEMOE_EACH n[i] = fmaf(-0.10319274309844689f, t[i], 0.38039573281868677f);
+    SLICEMOE_EACH n[i] = fmaf(kGeluGradN[0], t[i], kGeluGradN[1]);
 #pragma unroll
-    SLICEMOE_EACH n[i] = fmaf(n[i], t[i], -0.10600495306095319f);
+    for (int c = 2; c < 6; ++c)
 #pragma unroll
-    SLICEMOE_EACH n[i] = fmaf(n[i], t[i], 0.35579557363786846f);
-#pragma unroll
-    SLICEMOE_EACH n[i] = fmaf(n[i], t[i], 0.26746098326673917f);
-#pragma unroll
-    SLICEMOE_EACH n[i] = fmaf(n[i], t[i], 0.003429828810374159f);
+        SLICEMOE_EACH n[i] = fmaf(n[i], t[i], kGeluGradN[c]);
 #pragma unroll
     SLICEMOE_EACH xe[i] = e[i] * fabsf(z[i]);
 #pragma unroll
-    SLICEMOE_EACH g[i] = 1.f - e[i];
+    SLICEMOE_EACH act[i] = z[i] + fabsf(z[i]);
 #pragma unroll
-    SLICEMOE_EACH g[i] = fmaf(xe[i], n[i], g[i]);                                // erf(x / sqrt 2)
+    SLICEMOE_EACH q[i] = fmaf(-xe[i], n[i], e[i]);
 #pragma unroll
-    SLICEMOE_EACH slope[i] = fmaf(0.79788456080286536f, xe[i], g[i]);            // + 2 x phi(x)
+    SLICEMOE_EACH act[i] = fmaf(-fabsf(z[i]), q[i], act[i]);
 #pragma unroll
-    SLICEMOE_EACH act[i] = fmaf(fabsf(z[i]), g[i], z[i]);
+    SLICEMOE_EACH r[i] = fmaf(-0.79788456080286536f, xe[i], q[i]);
 #pragma unroll
-    SLICEMOE_EACH slope[i] = __builtin_copysignf(slope[i], z[i]);
+    SLICEMOE_EACH slope[i] = z[i] < 0.f ? r[i] : 2.f - r[i];
 #undef SLICEMOE_EACH
 }
 
