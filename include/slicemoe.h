@@ -292,7 +292,8 @@ slicemoe_status slicemoe_forward_train(const slicemoe_config *cfg, const void *h
  *   grads       out      one fp32 DEVICE array per weight tensor, logical layout, overwritten.  Partial sums are
  *                        added in a fixed order: same inputs, bit-identical weight gradients and dL/dh, on every
  *                        path (no floating-point atomics anywhere in the backward).
- *   workspace            >= slicemoe_backward_workspace_bytes(cfg), 256-byte aligned
+ *   workspace            >= slicemoe_backward_workspace_bytes(cfg), 256-byte aligned; the size never falls as T grows, so one made
+ *                        for a layer's largest batch takes its smaller ones
  *   stream               the call's place in this stream orders it against the caller's other work, as for every entry
  *                        point.  Experts that one pass of the matrix cores takes whole (d/S <= 64 and He <= 256) and the fp32
  *                        kernels stay on `stream`.  For the other experts on the matrix-core path the weight gradients (one

@@ -167,13 +167,15 @@ BackwardPlan backward_plan(const slicemoe_config &c)
     BackwardPlan p;
     const size_t Ns = (size_t)c.T * c.S, Na = Ns * c.k;
     const size_t ds = (size_t)(c.d / c.S);
-    p.expert_slots = backward_mfma_shape(c) ? backward_weights_slots(c) : backward_generic_expert_slots(c);
+    p.expert_slots = backward_mfma_shape(c) ? backward_weights_plan(c).slots : backward_generic_expert_slots(c);
+    const size_t expert_reserve = (size_t)(backward_mfma_shape(c) ? backward_weights_slots_bound(c) : p.expert_slots);
+    const size_t router_reserve = (size_t)(backward_router_mfma_shape(c) ? backward_router_mfma_slots_bound(c) : backward_generic_router_slots_bound(c));
     p.router_slots = backward_router_mfma_shape(c) ? backward_router_mfma_slots(c) : backward_generic_router_slots(c);
     size_t at = 0;
     p.dxrow = at;  at = align_up(at + Na * ds * sizeof(float), 256);
     p.dpk = at;    at = align_up(at + Na * sizeof(float), 256);
-    p.expert_part = at;  at = align_up(at + (size_t)p.expert_slots * expert_slot_floats((int)ds, c.He) * sizeof(float), 256);
-    p.router_part = at;  at = align_up(at + (size_t)p.router_slots * router_slot_floats((int)ds, c.Hr, c.E) * sizeof(float), 256);
+    p.expert_part = at;  at = align_up(at + expert_reserve * expert_slot_floats((int)ds, c.He) * sizeof(float), 256);
+    p.router_part = at;  at = align_up(at + router_reserve * router_slot_floats((int)ds, c.Hr, c.E) * sizeof(float), 256);
     p.packed = at;  at = align_up(at + backward_mfma_packed_bytes(c), 256);
     p.router_scratch = at;  at = align_up(at + backward_router_mfma_scratch_bytes(c), 256);
     p.cap = at;  at = align_up(at + (size_t)c.E * cap_blocks((long long)Na) * sizeof(unsigned long long), 256);

@@ -426,6 +426,8 @@ bool backward_onepass(const slicemoe_config &c)
     return passes == 1 || (passes <= 4 && units <= cus) || units >= cus * (passes <= 2 ? 10 : 4 * passes);
 }
 
+bool backward_onepass_by_batch(const slicemoe_config &c) { return c.d / c.S == 96 && expert_passes(c.He, expert_waves(96)) > 1; }
+
 BackwardWeightsPlan backward_expert_plan(const slicemoe_config &c)
 {
     BackwardWeightsPlan W;

@@ -695,12 +695,14 @@ BackwardWeightsPlan backward_generic_plan(const slicemoe_config &c)
 
 long long backward_generic_expert_slots(const slicemoe_config &c) { return backward_generic_plan(c).slots; }
 
+static int generic_router_blocks(const slicemoe_config &c)   // at the most, of one chunk of columns
+{
+    const int ds = c.d / c.S, blocks = num_compute_units() / ((ds + kGrFeat - 1) / kGrFeat);
+    return blocks < 1 ? 1 : blocks;
+}
 static int generic_router_units_per_block(const slicemoe_config &c)
 {
-    const long long units = ((long long)c.T * c.S + kGbRows - 1) / kGbRows;
-    const int ds = c.d / c.S, nch = (ds + kGrFeat - 1) / kGrFeat;
-    long long blocks = num_compute_units() / nch;
-    if (blocks < 1) blocks = 1;
+    const long long units = ((long long)c.T * c.S + kGbRows - 1) / kGbRows, blocks = generic_router_blocks(c);
     const long long per = (units + blocks - 1) / blocks;
     return per < 1 ? 1 : (int)per;
 }
@@ -709,6 +711,12 @@ long long backward_generic_router_slots(const slicemoe_config &c)
 {
     const long long units = ((long long)c.T * c.S + kGbRows - 1) / kGbRows, per = generic_router_units_per_block(c);
     return (units + per - 1) / per;
+}
+
+long long backward_generic_router_slots_bound(const slicemoe_config &c)
+{
+    const long long units = ((long long)c.T * c.S + kGbRows - 1) / kGbRows, most = generic_router_blocks(c);
+    return units < most ? units : most;
 }
 
 template <typename T> static bool quad_aligned(const void *p, int stride) { return stride % 4 == 0 && (uintptr_t)p % (4 * sizeof(T)) == 0; }

@@ -25,7 +25,8 @@ static BwdPacked bwd_packed_layout(const slicemoe_config &c)
 {
     BwdPacked L;
     const int ds = c.d / c.S, He = c.He;
-    const bool onepass = backward_onepass(c), fused = backward_weights_plan(c).fused;
+    // (w1c has its place for every batch of a layer if it has for some: the size never falls as the batch grows)
+    const bool onepass = backward_onepass(c) && !backward_onepass_by_batch(c), fused = !backward_onepass_by_batch(c) && backward_weights_plan(c).fused;
     const size_t dsK = (size_t)(ds + 15) / 16 * 16, dsN = (size_t)(ds + 31) / 32 * 32;
     L.w1f = 0;
     L.w2r = dsK * He * 2;

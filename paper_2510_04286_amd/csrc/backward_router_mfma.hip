@@ -977,17 +977,24 @@ size_t backward_router_mfma_scratch_bytes(const slicemoe_config &c)
 
 // Units of 32 slices per block of the weights kernel: one block per CU, at least two units each (a block leaves a slot of
 // partial sums behind, as large as the router's weights).
+constexpr int kRbLeastUnits = 2;
 static int router_units_per_block(const slicemoe_config &c)
 {
     const long long units = ((long long)c.T * c.S + kRbUnit - 1) / kRbUnit;
     const long long per = (units + num_compute_units() - 1) / num_compute_units();
-    return per < 2 ? 2 : (int)per;
+    return per < kRbLeastUnits ? kRbLeastUnits : (int)per;
 }
 
 long long backward_router_mfma_slots(const slicemoe_config &c)
 {
     const long long units = ((long long)c.T * c.S + kRbUnit - 1) / kRbUnit, per = router_units_per_block(c);
     return (units + per - 1) / per;
+}
+
+long long backward_router_mfma_slots_bound(const slicemoe_config &c)
+{
+    const long long units = ((long long)c.T * c.S + kRbUnit - 1) / kRbUnit, most = (units + kRbLeastUnits - 1) / kRbLeastUnits;
+    return most < num_compute_units() ? most : num_compute_units();
 }
 
 template <int DS, int ET>

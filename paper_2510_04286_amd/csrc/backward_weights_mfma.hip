@@ -493,9 +493,8 @@ static WeightsConfig weights_config(int ds, int He)
     return {4, 1, false};
 }
 
-BackwardWeightsPlan backward_weights_plan(const slicemoe_config &c)
+static BackwardWeightsPlan weights_kernel_plan(const slicemoe_config &c)
 {
-    if (backward_onepass(c)) return backward_expert_plan(c);
     BackwardWeightsPlan W;
     const WeightsConfig C = weights_config(c.d / c.S, c.He);
     const int HT = c.He / 32;
@@ -512,7 +511,17 @@ BackwardWeightsPlan backward_weights_plan(const slicemoe_config &c)
     return W;
 }
 
-long long backward_weights_slots(const slicemoe_config &c) { return backward_weights_plan(c).slots; }
+BackwardWeightsPlan backward_weights_plan(const slicemoe_config &c)
+{
+    return backward_onepass(c) ? backward_expert_plan(c) : weights_kernel_plan(c);
+}
+
+long long backward_weights_slots_bound(const slicemoe_config &c)
+{
+    if (!backward_onepass_by_batch(c)) return backward_weights_plan(c).slots;
+    const long long a = weights_kernel_plan(c).slots, b = backward_expert_plan(c).slots;
+    return a > b ? a : b;
+}
 
 template <int DS, int WAVES, int NBUF, bool WLDS, bool FUSE, int TERMS, int MINWAVES>
 static hipError_t run_weights(const slicemoe_config &c, const BackwardWeightsPlan &W, const BwdPacked &L, const void *h, const void *d_out,

@@ -148,6 +148,7 @@ struct BackwardWeightsPlan {
 BackwardWeightsPlan backward_weights_plan(const slicemoe_config &c);
 // The same of the one-pass kernel of 16-wide hidden tiles (backward_expert_mfma.hip) and the shapes it takes.
 bool backward_onepass(const slicemoe_config &c);
+bool backward_onepass_by_batch(const slicemoe_config &c);   // whether another number of tokens may be another choice
 BackwardWeightsPlan backward_expert_plan(const slicemoe_config &c);
 hipError_t launch_backward_expert_onepass(const slicemoe_config &c, const BwdPacked &L, const void *h, const void *d_out, const float *pk,
                                           const int32_t *offsets, const int32_t *perm, const char *packed, size_t slot_floats,

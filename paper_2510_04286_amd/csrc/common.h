@@ -157,7 +157,7 @@ hipError_t launch_route_mfma(const slicemoe_config &c, const void *h, const void
 // Backward pass (backward.hip): weight gradients into g, dL/dh into d_h.  backward_plan: layout of its scratch (row
 // gradients, dL/dp, slots of partial weight gradients); backward_lds_bytes: the measure that bounds the shapes it takes.
 struct BackwardPlan {
-    long long expert_slots, router_slots;   // slots of partial weight gradients
+    long long expert_slots, router_slots;   // slots of partial weight gradients that the call uses
     size_t dxrow, dpk, expert_part, router_part, packed, router_scratch, cap, total;   // byte offsets into the workspace, total size
 };
 BackwardPlan backward_plan(const slicemoe_config &c);
@@ -184,7 +184,11 @@ hipError_t launch_backward_expert_mfma(const slicemoe_config &c, const void *h, 
                                        const float *pk, const int32_t *offsets, const int32_t *perm, void *packed,
                                        size_t slot_floats, float *dxrow, float *dpk, float *part, hipStream_t s,
                                        const SideStream *side = nullptr);
-long long backward_weights_slots(const slicemoe_config &c);   // its slots of partial weight gradients
+// Slots of partial weight gradients to reserve: at least what the call uses, and never fewer for more tokens, so that a workspace made for
+// the largest batch of a layer takes its smaller ones, however those are split and whichever kernels they run on.
+long long backward_weights_slots_bound(const slicemoe_config &c);
+long long backward_router_mfma_slots_bound(const slicemoe_config &c);
+long long backward_generic_router_slots_bound(const slicemoe_config &c);
 // The fp32 backward of every other shape (backward_generic.hip): same outputs.
 long long backward_generic_expert_slots(const slicemoe_config &c);
 long long backward_generic_router_slots(const slicemoe_config &c);
