@@ -24,7 +24,10 @@ def shape(ds, He, E, k, T, S=4, cf=0.0):
 
 CASES = {
     "w24_1_pass_full": shape(24, 128, 4, 2, 65),      # eight tiles of 16 on eight wavefronts
-    "w24_2_passes": shape(24, 160, 3, 3, 41),         # ten: six and four
+    "w24_16_wavefronts": shape(24, 160, 3, 3, 41),    # ten tiles on sixteen
+    "w24_16_wavefronts_full": shape(24, 256, 5, 2, 70),
+    "w24_2_passes": shape(24, 288, 4, 2, 53),         # eighteen: ten and eight
+    "w24_5_passes": shape(24, 1056, 2, 1, 90),        # sixty-six: fourteen four times, ten
     "w24_one_row": shape(24, 32, 1, 1, 1, S=1),
     "w24_k8": shape(24, 96, 9, 8, 30),
     "w48_1_pass_full": shape(48, 192, 5, 2, 100),     # twelve tiles on twelve wavefronts
