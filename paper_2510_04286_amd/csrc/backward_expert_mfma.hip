@@ -94,8 +94,10 @@ __global__ __launch_bounds__(WAVES * 64, MINWAVES) void bwd_expert_kernel(
     int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int HT = He / 16;
-    // blocks of one XCD (consecutive ids go to the eight in turn) take consecutive shares: an expert's weights in few L2s
-    const int vb = blocks % 8 == 0 ? (int)(blockIdx.x % 8) * (blocks / 8) + (int)(blockIdx.x / 8) : (int)blockIdx.x;
+    // Blocks of one XCD (consecutive ids go to the eight in turn) take consecutive shares: an expert's weights in few L2s.  Not where two blocks fit a
+    // compute unit: a batch of hardly more units than blocks has two units in half of the shares and none in the others, and the busy ones would crowd
+    // half of the XCDs (width 24, He 96, 400 and 480 units: backward 49.9 and 51.2 us, 47.1 and 48.2 without).
+    const int vb = WAVES > 8 && blocks % 8 == 0 ? (int)(blockIdx.x % 8) * (blocks / 8) + (int)(blockIdx.x / 8) : (int)blockIdx.x;
 
     const int off_lo = offsets[min(lane, E)], off_hi = offsets[min(lane + 1, E)];
     const RowAxis A = row_axis(off_hi - off_lo, kUnit, 1, blocks, lane);
@@ -415,7 +417,7 @@ static int expert_pass_tiles(int He, int waves)
 }
 
 // Widths 24 and 48: always.  Backward of 32 to 8192 units, He 192 .. 3072, 4 and 16 experts, against the two kernels (one below He 288): width 48
-// 1.06 to 1.76 times their speed, width 24 0.99 to 1.8, He 96 .. 128 1.03 to 1.1 but for 480 to 512 units (0.96).  Width 96: where
+// 1.06 to 1.76 times their speed, width 24 0.99 to 1.8.  Width 96: where
 // one pass does (He <= 192: 1.09 to 1.23), where every block has at most one unit, or where it has so many that starting the
 // passes one after the other is little beside them -- the two kernels' groups of hidden tiles run side by side.  Backward in us, the two kernels / this one,
 // 16 experts: He 384, units per block 1 93.5 / 85.4, 2 94.7 / 102.5, 6 132.3 / 140.8, 9 168.9 / 166.2, 16 241.6 / 211.2; He 768 (four

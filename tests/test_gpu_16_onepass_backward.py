@@ -28,6 +28,7 @@ CASES = {
     "w24_16_wavefronts_full": shape(24, 256, 5, 2, 70),
     "w24_2_passes": shape(24, 288, 4, 2, 53),         # eighteen: ten and eight
     "w24_5_passes": shape(24, 1056, 2, 1, 90),        # sixty-six: fourteen four times, ten
+    "w24_half_of_the_shares": shape(24, 96, 6, 2, 240, S=32),   # 480 units and six experts on 480 blocks: shares of two
     "w24_one_row": shape(24, 32, 1, 1, 1, S=1),
     "w24_k8": shape(24, 96, 9, 8, 30),
     "w48_1_pass_full": shape(48, 192, 5, 2, 100),     # twelve tiles on twelve wavefronts
