@@ -29,11 +29,12 @@
 // TERMS: bf16 terms of the activation and of p dz, backward_terms(DS).
 #include "bwd_mfma.h"
 #include "lds_rows.h"
+#include "onepass_split.h"
 #include "wavefront.h"
 
 namespace slicemoe {
 
-constexpr int kUnit = 32;   // stacked rows a block works on at a time
+constexpr int kUnit = kOnepassUnit;
 
 __device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
 
@@ -402,37 +403,12 @@ __global__ __launch_bounds__(WAVES * 64, MINWAVES) void bwd_expert_kernel(
 }
 
 // ------------------------------------------------------------------------------------------------------ host
-// Wavefronts per block, blocks per CU: 12 wavefronts of 168 registers, three per SIMD; at width 24 two blocks of 8, of 128 registers, or
-// one of 16 where the hidden units are more than 128: a pass takes 256 of them (He 160 .. 256 in one pass instead of two).  Backward in us, 8
-// wavefronts / 16, 16 experts: He 192, 512 units 61.8 / 55.2, 4096 units 121 / 107; He 256, 128 units 48.9 / 47.6, 8192 units 201 / 197; He
-// 768, 512 units 103 / 86, 8192 units 434 / 419; He 1536, 32 units 113 / 96.
-static int expert_waves(int ds, int He) { return ds != 24 ? 12 : He <= 128 ? 8 : 16; }
-
-// Passes over the rows: as many as the hidden tiles of 16 need, the tiles spread evenly (an even number in each pass).
-static int expert_passes(int He, int waves) { return (He / 16 + waves - 1) / waves; }
-static int expert_pass_tiles(int He, int waves)
-{
-    const int passes = expert_passes(He, waves);
-    return (He / 32 + passes - 1) / passes * 2;
-}
-
-// Widths 24 and 48: always.  Backward of 32 to 8192 units, He 192 .. 3072, 4 and 16 experts, against the two kernels (one below He 288): width 48
-// 1.06 to 1.76 times their speed, width 24 0.99 to 1.8.  Width 96: where
-// one pass does (He <= 192: 1.09 to 1.23), where every block has at most one unit, or where it has so many that starting the
-// passes one after the other is little beside them -- the two kernels' groups of hidden tiles run side by side.  Backward in us, the two kernels / this one,
-// 16 experts: He 384, units per block 1 93.5 / 85.4, 2 94.7 / 102.5, 6 132.3 / 140.8, 9 168.9 / 166.2, 16 241.6 / 211.2; He 768 (four
-// passes) 1 114.7 / 108.3, 4 130.4 / 145.1, 12 290.8 / 293.6, 23 563.5 / 486.9; He 1536 (eight) 6 300 / 453, 32 1208 / 1178.
 bool backward_onepass(const slicemoe_config &c)
 {
-    const int ds = c.d / c.S;
-    if (ds == 24 || ds == 48) return true;
-    if (ds != 96) return false;
-    const long long units = ((long long)c.T * c.S * c.k + kUnit - 1) / kUnit, cus = num_compute_units();
-    const int passes = expert_passes(c.He, expert_waves(ds, c.He));
-    return passes == 1 || (passes <= 4 && units <= cus) || units >= cus * (passes <= 2 ? 10 : 4 * passes);
+    return onepass_chosen(c.d / c.S, c.He, ((long long)c.T * c.S * c.k + kUnit - 1) / kUnit, num_compute_units());
 }
 
-bool backward_onepass_by_batch(const slicemoe_config &c) { return c.d / c.S == 96 && expert_passes(c.He, expert_waves(96, c.He)) > 1; }
+bool backward_onepass_by_batch(const slicemoe_config &c) { return onepass_depends_on_batch(c.d / c.S, c.He); }
 
 BackwardWeightsPlan backward_expert_plan(const slicemoe_config &c)
 {
@@ -442,7 +418,7 @@ BackwardWeightsPlan backward_expert_plan(const slicemoe_config &c)
     W.step = kUnit;
     W.overhead = 1;
     W.groups = 1;
-    long long blocks = (long long)num_compute_units() * (expert_waves(c.d / c.S, c.He) == 8 ? 2 : 1);
+    long long blocks = (long long)num_compute_units() * onepass_blocks_per_cu(c.d / c.S, c.He);
     if (blocks > most) blocks = most;
     W.blocks = blocks < 1 ? 1 : (int)blocks;
     W.slots = (long long)W.blocks + c.E;
@@ -456,13 +432,13 @@ static hipError_t run_expert(const slicemoe_config &c, const BwdPacked &L, const
 {
     constexpr int TERMS = backward_terms(DS);
     constexpr size_t lds = ExpertTile<DS, WAVES, TERMS>::lds;
-    if (expert_waves(DS, c.He) != WAVES) return hipErrorInvalidValue;
+    if (onepass_waves(DS, c.He) != WAVES) return hipErrorInvalidValue;
     const BackwardWeightsPlan W = backward_expert_plan(c);
     auto kern = bwd_expert_kernel<DS, WAVES, TERMS, MINWAVES>;
     const hipError_t e = grant_dynamic_lds((const void *)kern, lds);
     if (e != hipSuccess) return e;
     kern<<<(unsigned)W.blocks, WAVES * 64, lds, s>>>((const bf16_t *)h, (const bf16_t *)d_out, pk, offsets, perm, packed, L.stride, L.w2r,
-                                                     L.b1, c.He, c.E, c.k, W.blocks, expert_pass_tiles(c.He, WAVES), slot_floats, part,
+                                                     L.b1, c.He, c.E, c.k, W.blocks, onepass_pass_tiles(DS, c.He), slot_floats, part,
                                                      dxrow, dpk);
     return hipGetLastError();
 }
@@ -472,7 +448,7 @@ hipError_t launch_backward_expert_onepass(const slicemoe_config &c, const BwdPac
                                           float *part, float *dxrow, float *dpk, hipStream_t s)
 {
     const int ds = c.d / c.S;
-    return ds == 24 && expert_waves(ds, c.He) == 8 ? run_expert<24, 8, 4>(c, L, h, d_out, pk, offsets, perm, packed, slot_floats, part, dxrow, dpk, s)
+    return ds == 24 && onepass_waves(ds, c.He) == 8 ? run_expert<24, 8, 4>(c, L, h, d_out, pk, offsets, perm, packed, slot_floats, part, dxrow, dpk, s)
          : ds == 24 ? run_expert<24, 16, 4>(c, L, h, d_out, pk, offsets, perm, packed, slot_floats, part, dxrow, dpk, s)
          : ds == 48 ? run_expert<48, 12, 3>(c, L, h, d_out, pk, offsets, perm, packed, slot_floats, part, dxrow, dpk, s)
          : ds == 96 ? run_expert<96, 12, 3>(c, L, h, d_out, pk, offsets, perm, packed, slot_floats, part, dxrow, dpk, s)

@@ -10,8 +10,10 @@ last place, 2^-7 relative, plus the same share of the RMS."""
 import numpy as np
 import pytest
 
+import oracle
 from paper_2510_04286_amd import workload as wl
 from tests.common import make_inputs, rms
+from tests.test_onepass_split import split
 
 pytestmark = pytest.mark.gpu
 
@@ -75,3 +77,56 @@ def test_one_pass_backward_equals_the_fp32_kernels(name):
     assert excess <= 1.0
     assert max(err[n] for n in ("W1", "b1", "W2", "b2")) <= bar, err
     assert max(err.values()) <= 5e-4, err
+
+
+TRAIN = dict(tau=0.8, sigma=0.1, rate=0.2)
+EDGES = {   # (shape, whether the one pass takes it at 256 compute units)
+    "w24_16_wavefronts": (shape(24, 224, 5, 2, 60), True),
+    "w48_capacity": (shape(48, 288, 6, 2, 80, cf=0.7), True),
+    "w96_2_passes_256_units": (shape(96, 224, 7, 1, 8192, S=1), True),
+    "w96_2_passes_257_units": (shape(96, 224, 7, 1, 8193, S=1), False),
+    "w96_2_passes_2559_units": (shape(96, 224, 5, 2, 40944, S=1), False),
+    "w96_2_passes_2560_units": (shape(96, 224, 5, 2, 40945, S=1), True),
+    "w96_3_passes_192_units": (shape(96, 416, 4, 1, 6144, S=1), True),
+    "w96_3_passes_193_units": (shape(96, 416, 4, 1, 6145, S=1), False),
+    "w96_4_passes_192_units": (shape(96, 608, 3, 3, 512, S=4, cf=1.0), True),
+    "w96_5_passes": (shape(96, 800, 3, 2, 100, S=1), False),   # (k = 2: with one assignment the dropout makes every probability one)
+}
+
+
+@pytest.mark.parametrize("name", list(EDGES))
+def test_both_sides_of_the_choice_against_64_bits(name):
+    """Noise, dropout and the capacity loss, on the routing and the probabilities that the forward left behind.  The bars of the test above; of the router's
+    gradients only the small cases are compared, a larger one has hidden units so close to zero that the two sides gate them differently."""
+    import torch
+    from paper_2510_04286_amd import binding as B
+    case, onepass = EDGES[name]
+    s, h, w = make_inputs(case)
+    units, cus = (s.Na + 31) // 32, torch.cuda.get_device_properties(0).multi_processor_count
+    assert cus != 256 or split().chosen(s.ds, s.He, units, cus) == onepass
+    cfg = B.config_of(s)
+    assert B.slicemoe_backward_uses_mfma(cfg) == 1
+    noise, drop_u = wl.make_router_draws(s)
+    dout, alpha = wl.make_dout(s), 0.3 * s.Ns
+    train = dict(temperature=TRAIN["tau"], noise_std=TRAIN["sigma"], dropout_rate=TRAIN["rate"], noise=torch.from_numpy(noise).to("cuda:0"),
+                 drop_u=torch.from_numpy(drop_u).to("cuda:0"))
+    hd, ws = B.to_device(h, s.dtype), B.alloc_workspace(cfg)
+    wd = B.pack(cfg, B.weights_to_device(w, s.dtype))
+    B.slicemoe_forward_train(cfg, hd, wd, torch.empty_like(hd), ws, **train)
+    grads, d_h = B.alloc_weight_grads(cfg), torch.empty_like(hd)
+    bws = torch.full((B.slicemoe_backward_workspace_bytes(cfg),), 0xFF, dtype=torch.uint8, device="cuda:0")   # NaNs: nothing is read unwritten
+    B.slicemoe_backward(cfg, hd, wd, ws, B.to_device(dout, s.dtype), d_h, grads, bws, train=dict(train, capacity_alpha=alpha))
+    torch.cuda.synchronize()
+    v = {n: t.cpu().numpy() for n, t in B.workspace_views(cfg, ws).items() if n in ("topk_idx", "topk_p", "inv")}
+    capg = oracle.capacity_surrogate(v["topk_idx"], v["topk_p"].astype(np.float64), s.E, alpha)["grad"]
+    ref = oracle.backward(h, s.S, s.k, w, dout, v["topk_idx"], v["inv"], noise=noise, drop_u=drop_u, capg=capg, **TRAIN)
+    small = s.Ns <= 1000
+    bar = 2e-4 if s.ds == 96 else 5e-5
+    err = {n: np.abs(grads[n].cpu().numpy() - ref[n]).max() / rms(ref[n]) for n in (NAMES if small else ("W1", "b1", "W2", "b2"))}
+    print(f"\n[{name}] {units} units; " + " ".join(f"{n} {e:.1e}" for n, e in err.items()))
+    assert max(err[n] for n in ("W1", "b1", "W2", "b2")) <= bar, err
+    assert max(err.values()) <= 5e-4, err
+    if small:
+        got = d_h.float().cpu().numpy().astype(np.float64)
+        excess = (np.abs(got - ref["d_h"]) / (2.0 ** -7 * np.abs(ref["d_h"]) + 2e-4 * rms(ref["d_h"]))).max()
+        assert excess <= 1.0

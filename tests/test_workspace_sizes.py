@@ -1,6 +1,6 @@
 """A workspace made for the largest batch of a layer takes every smaller one: its size never falls as the number of tokens grows, also
 where another batch is split differently (the router's backward: a unit of 32 slices more per block is fewer blocks) or runs on other kernels (the expert
-backward at slice width 96: one pass up to 256 units of 32 rows and again from 10 or 4 x passes units per compute unit, two kernels between).  Questions to the library that need no device (it then counts 256 compute units)."""
+backward at slice width 96: one pass in small batches and again in large ones, two kernels between).  Questions to the library that need no device (it then counts 256 compute units)."""
 import pytest
 
 from paper_2510_04286_amd import binding as B
@@ -15,7 +15,7 @@ def test_the_backward_workspace_never_shrinks(layer):
     dtype = layer[4] if len(layer) > 4 else "bf16"
     S = 4
     per = S * k
-    edges = [u * 32 // per for u in (1, E, 128, 255, 256, 257, 512, 513, 256 * 8, 256 * 10, 256 * 12, 256 * 16, 256 * 32)]
+    edges = [u * 32 // per for u in (1, E, 128, 192, 193, 255, 256, 257, 512, 513, 256 * 8, 256 * 10, 256 * 12, 256 * 16, 256 * 32)]
     tokens = sorted({t for e in edges for t in range(max(1, e - 3), e + 4)} | set(range(1, 12000, 37)))
     sizes = []
     for t in tokens:
