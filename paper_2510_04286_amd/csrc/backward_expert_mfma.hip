@@ -80,7 +80,7 @@ template <int DS, int WAVES, int TERMS, int MINWAVES>
 __global__ __launch_bounds__(WAVES * 64, MINWAVES) void bwd_expert_kernel(
     const bf16_t *__restrict__ x, const bf16_t *__restrict__ dout, const float *__restrict__ pk,
     const int32_t *__restrict__ offsets, const int32_t *__restrict__ perm, const char *__restrict__ packed,
-    size_t e_stride, size_t off_w2r, size_t off_b1, int He, int E, int k, int blocks, int pass_tiles,
+    size_t e_stride, size_t off_w2r, size_t off_b1, int He, int E, int k, int blocks, int overhead, int pass_tiles,
     size_t slot_floats, float *__restrict__ part, float *__restrict__ dxrow, float *__restrict__ dpk)
 {
     typedef ExpertTile<DS, WAVES, TERMS> G;
@@ -101,7 +101,7 @@ __global__ __launch_bounds__(WAVES * 64, MINWAVES) void bwd_expert_kernel(
     const int vb = WAVES > 8 && blocks % 8 == 0 ? (int)(blockIdx.x % 8) * (blocks / 8) + (int)(blockIdx.x / 8) : (int)blockIdx.x;
 
     const int off_lo = offsets[min(lane, E)], off_hi = offsets[min(lane + 1, E)];
-    const RowAxis A = row_axis(off_hi - off_lo, kUnit, 1, blocks, lane);
+    const RowAxis A = row_axis(off_hi - off_lo, kUnit, overhead, blocks, lane);
     const int c0 = vb * A.share, c1 = c0 + A.share;
 
     // ---- the piece this thread moves
@@ -129,7 +129,7 @@ __global__ __launch_bounds__(WAVES * 64, MINWAVES) void bwd_expert_kernel(
     for (int e = 0; e < E; ++e) {
         const int first = __builtin_amdgcn_readlane(A.first, e), steps = __builtin_amdgcn_readlane(A.steps, e);
         if (first >= c1) break;
-        const int s_lo = max(0, c0 - first - 1), s_hi = min(steps, c1 - first - 1);
+        const int s_lo = max(0, c0 - first - overhead), s_hi = min(steps, c1 - first - overhead);
         if (s_hi <= s_lo) continue;
         const int row0 = __builtin_amdgcn_readlane(off_lo, e) + s_lo * kUnit;   // rows below count from here
         const int nrows = min(__builtin_amdgcn_readlane(off_hi, e) - row0, (s_hi - s_lo) * kUnit);
@@ -410,19 +410,35 @@ bool backward_onepass(const slicemoe_config &c)
 
 bool backward_onepass_by_batch(const slicemoe_config &c) { return onepass_depends_on_batch(c.d / c.S, c.He); }
 
+// Blocks there are units for, at the most: an expert's rows begin one.
+static long long expert_blocks_bound(const slicemoe_config &c, long long units)
+{
+    const long long cap = (long long)num_compute_units() * onepass_blocks_per_cu(c.d / c.S, c.He), most = units + c.E - 1;
+    return most < 1 ? 1 : most < cap ? most : cap;
+}
+
+// Up to two units per expert every unit has a block of its own (no position for an expert's beginning: it would make the share of a block that has
+// experts of one unit each the number of experts over the number of whole units).  Beyond, a block has at least a beginning and a unit, or two
+// units: fewer slots of partial sums, whose traffic is more than the second unit costs.  Backward in us, with the position / without:
+//   2 E units and fewer   width 96, He 384: 1 token (S 8), 16 experts 134 / 56, 64 tokens (32 units) 69.9 / 66.5; He 768, 64 experts, 4 tokens 404 / 121, 128 units 156 / 151
+//                         width 48, He 192, 16 experts: 2 units 81 / 42, 32 units 48.0 / 46.6; width 24, He 96: 2 units 60 / 37, 32 units 42.6 / 41.6
+//   more, 16 experts      256 units: width 96, He 192 64.7 / 65.0, He 768 117 / 123; width 48, He 192 53.2 / 55.1; 4096 units: width 96, He 384 216 / 225
 BackwardWeightsPlan backward_expert_plan(const slicemoe_config &c)
 {
     BackwardWeightsPlan W;
-    const long long Na = (long long)c.T * c.S * c.k, most = (Na + kUnit - 1) / kUnit;
+    const long long units = ((long long)c.T * c.S * c.k + kUnit - 1) / kUnit, most = expert_blocks_bound(c, units);
+    const bool few = units <= 2 * c.E;
     W.fused = true;
     W.step = kUnit;
-    W.overhead = 1;
+    W.overhead = few ? 0 : 1;
     W.groups = 1;
-    long long blocks = (long long)num_compute_units() * onepass_blocks_per_cu(c.d / c.S, c.He);
-    if (blocks > most) blocks = most;
-    W.blocks = blocks < 1 ? 1 : (int)blocks;
+    W.blocks = (int)(few || units > most ? most : units);
     W.slots = (long long)W.blocks + c.E;
     return W;
+}
+long long backward_expert_slots_bound(const slicemoe_config &c)
+{
+    return expert_blocks_bound(c, ((long long)c.T * c.S * c.k + kUnit - 1) / kUnit) + c.E;
 }
 
 template <int DS, int WAVES, int MINWAVES>
@@ -438,7 +454,7 @@ static hipError_t run_expert(const slicemoe_config &c, const BwdPacked &L, const
     const hipError_t e = grant_dynamic_lds((const void *)kern, lds);
     if (e != hipSuccess) return e;
     kern<<<(unsigned)W.blocks, WAVES * 64, lds, s>>>((const bf16_t *)h, (const bf16_t *)d_out, pk, offsets, perm, packed, L.stride, L.w2r,
-                                                     L.b1, c.He, c.E, c.k, W.blocks, onepass_pass_tiles(DS, c.He), slot_floats, part,
+                                                     L.b1, c.He, c.E, c.k, W.blocks, W.overhead, onepass_pass_tiles(DS, c.He), slot_floats, part,
                                                      dxrow, dpk);
     return hipGetLastError();
 }

@@ -518,8 +518,8 @@ BackwardWeightsPlan backward_weights_plan(const slicemoe_config &c)
 
 long long backward_weights_slots_bound(const slicemoe_config &c)
 {
-    if (!backward_onepass_by_batch(c)) return backward_weights_plan(c).slots;
-    const long long a = weights_kernel_plan(c).slots, b = backward_expert_plan(c).slots;
+    const bool by_batch = backward_onepass_by_batch(c);
+    const long long a = by_batch || !backward_onepass(c) ? weights_kernel_plan(c).slots : 0, b = by_batch || backward_onepass(c) ? backward_expert_slots_bound(c) : 0;
     return a > b ? a : b;
 }
 

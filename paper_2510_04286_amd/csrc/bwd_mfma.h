@@ -150,6 +150,7 @@ BackwardWeightsPlan backward_weights_plan(const slicemoe_config &c);
 bool backward_onepass(const slicemoe_config &c);
 bool backward_onepass_by_batch(const slicemoe_config &c);   // whether another number of tokens may be another choice
 BackwardWeightsPlan backward_expert_plan(const slicemoe_config &c);
+long long backward_expert_slots_bound(const slicemoe_config &c);   // at least its slots, never fewer for more tokens
 hipError_t launch_backward_expert_onepass(const slicemoe_config &c, const BwdPacked &L, const void *h, const void *d_out, const float *pk,
                                           const int32_t *offsets, const int32_t *perm, const char *packed, size_t slot_floats,
                                           float *part, float *dxrow, float *dpk, hipStream_t s);

@@ -83,6 +83,13 @@ TRAIN = dict(tau=0.8, sigma=0.1, rate=0.2)
 EDGES = {   # (shape, whether the one pass takes it at 256 compute units)
     "w24_16_wavefronts": (shape(24, 224, 5, 2, 60), True),
     "w48_capacity": (shape(48, 288, 6, 2, 80, cf=0.7), True),
+    # two units per expert and fewer: a block for every unit; one unit more
+    "w24_8_units": (shape(24, 96, 4, 2, 128, S=1), True),
+    "w24_9_units": (shape(24, 96, 4, 2, 129, S=1), True),
+    "w48_64_experts_few_rows": (shape(48, 224, 64, 2, 33, S=2), True),
+    "w96_64_experts_a_row_each": (shape(96, 384, 64, 2, 9, S=4), True),
+    "w96_8_units": (shape(96, 224, 4, 2, 128, S=1), True),
+    "w96_9_units": (shape(96, 224, 4, 2, 129, S=1), True),
     "w96_2_passes_256_units": (shape(96, 224, 7, 1, 8192, S=1), True),
     "w96_2_passes_257_units": (shape(96, 224, 7, 1, 8193, S=1), False),
     "w96_2_passes_2559_units": (shape(96, 224, 5, 2, 40944, S=1), False),

@@ -15,7 +15,7 @@ def test_the_backward_workspace_never_shrinks(layer):
     dtype = layer[4] if len(layer) > 4 else "bf16"
     S = 4
     per = S * k
-    edges = [u * 32 // per for u in (1, E, 128, 192, 193, 255, 256, 257, 512, 513, 256 * 8, 256 * 10, 256 * 12, 256 * 16, 256 * 32)]
+    edges = [u * 32 // per for u in (1, E, 2 * E, 2 * E + 1, 128, 192, 193, 255, 256, 257, 512, 513, 256 * 8, 256 * 10, 256 * 12, 256 * 16, 256 * 32)]
     tokens = sorted({t for e in edges for t in range(max(1, e - 3), e + 4)} | set(range(1, 12000, 37)))
     sizes = []
     for t in tokens:
