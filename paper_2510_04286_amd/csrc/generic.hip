@@ -107,12 +107,17 @@ __global__ __launch_bounds__(kGenThreads) void route_generic_kernel(
     // 32 lanes per slice, experts l and l + 32
     const int r = tid >> 5, l = tid & 31;
     static_assert(kGenThreads == 32 * kRB, "32 lanes per slice");
-    const int far = E > 16 ? 16 : E > 8 ? 8 : 4;   // the furthest lane that has an expert is less than twice as far
+    // the furthest lane that has an expert is less than twice as far (tests in unrolled loops: a loop from `far` down costs 64 experts 1 us)
+    const int far = E > 16 ? 16 : E > 8 ? 8 : 4;
     float v0 = l < E ? gs[r * E + l] : -INFINITY, v1 = l + 32 < E ? gs[r * E + l + 32] : -INFINITY;
     float m = fmaxf(v0, v1);
-    for (int o = far; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+#pragma unroll
+    for (int o = 16; o > 0; o >>= 1)
+        if (o <= far) m = fmaxf(m, __shfl_xor(m, o));
     float den = (l < E ? expf((v0 - m) * inv_tau) : 0.f) + (l + 32 < E ? expf((v1 - m) * inv_tau) : 0.f);   // softmax of g / tau (Appendix B)
-    for (int o = far; o > 0; o >>= 1) den += __shfl_xor(den, o);
+#pragma unroll
+    for (int o = 16; o > 0; o >>= 1)
+        if (o <= far) den += __shfl_xor(den, o);
     const long long n = n0 + r;
     for (int j = 0; j < k; ++j) {
         float bv = v0;
@@ -121,7 +126,9 @@ __global__ __launch_bounds__(kGenThreads) void route_generic_kernel(
             bv = v1;
             best = l + 32;
         }
-        for (int o = far; o > 0; o >>= 1) {
+#pragma unroll
+        for (int o = 16; o > 0; o >>= 1) {
+            if (o > far) continue;
             const float ov = __shfl_xor(bv, o);
             const int oe = __shfl_xor(best, o);
             if (ov > bv || (ov == bv && oe < best)) {
