@@ -49,7 +49,7 @@ constexpr int kUnit = 32;   // stacked rows a block works on at a time
 
 // Geometry of one instantiation.
 template <int DS, int WAVES, int NBUF, bool WLDS, bool FUSE, int TERMS> struct WeightsTile {
-    static constexpr int KS = SliceTiles<DS>::KS, OT = SliceTiles<DS>::OT, FT = (DS + 15) / 16;
+    static constexpr int KS = SliceTiles<DS>::KS, OT = SliceTiles<DS>::OT, FT = DS / 16;
     static constexpr int THREADS = WAVES * 64;
     static constexpr int NBW = WAVES < 2 * OT ? WAVES : 2 * OT, TB = (2 * OT + NBW - 1) / NBW;   // wavefronts that add up db2, their shares
     static constexpr size_t rows_bytes = (size_t)2 * kUnit * LdsRows<DS>::STRIDE;                // x and dy of one unit
@@ -73,8 +73,9 @@ __global__ __launch_bounds__(WAVES * 64, MINWAVES) void bwd_weights_kernel(
     typedef WeightsTile<DS, WAVES, NBUF, WLDS, FUSE, TERMS> G;
     typedef LdsRows<DS> LR;
     constexpr int KS = G::KS, OT = G::OT, THREADS = G::THREADS, P = LR::P, PW = LR::PW;
-    constexpr int NX = (2 * kUnit * P + THREADS - 1) / THREADS;   // 16-byte pieces (of x, then of dy) a thread moves per unit
+    constexpr int NX = 2 * kUnit * P / THREADS;   // 16-byte pieces (of x, then of dy) a thread moves per unit
     static_assert(!FUSE || NBUF == 2, "the fused kernel has one barrier per unit");
+    static_assert(DS % 32 == 0 && NX * THREADS == 2 * kUnit * P, "whole tiles of features, a thread for every piece");
     extern __shared__ __align__(16) char lds[];
 
     const int tid = threadIdx.x, lane = tid & 63, jj = lane & 31, g = lane >> 5;
@@ -98,7 +99,7 @@ __global__ __launch_bounds__(WAVES * 64, MINWAVES) void bwd_weights_kernel(
 #pragma unroll
     for (int i = 0; i < NX; ++i) {
         const int q = tid + i * THREADS, half = q >= kUnit * P ? 1 : 0, r = q - half * kUnit * P;
-        mrow[i] = min(r / P, kUnit - 1);
+        mrow[i] = r / P;
         mcol[i] = 8 * (r % P);
         msrc[i] = (half ? dout : x) + mcol[i];
         mdst[i] = half * kUnit * LR::STRIDE + LR::offset(mrow[i], r % P);
@@ -204,8 +205,7 @@ __global__ __launch_bounds__(WAVES * 64, MINWAVES) void bwd_weights_kernel(
 #pragma unroll
             for (int i = 0; i < NX; ++i) {
                 const int q = tid + i * THREADS;
-                if (NX * THREADS == 2 * kUnit * P || q < 2 * kUnit * P)
-                    *(uint4 *)(lds + buf * G::rows_bytes + mdst[i]) = q < kUnit * P || r0 + mrow[i] < nrows ? mv[i] : make_uint4(0, 0, 0, 0);
+                *(uint4 *)(lds + buf * G::rows_bytes + mdst[i]) = q < kUnit * P || r0 + mrow[i] < nrows ? mv[i] : make_uint4(0, 0, 0, 0);
             }
             if (tid < kUnit) {
                 ao = ao_load;
@@ -269,7 +269,7 @@ __global__ __launch_bounds__(WAVES * 64, MINWAVES) void bwd_weights_kernel(
 #pragma unroll
             for (int i = 0; i < NT; ++i) {
                 const int tile = wave + i * WAVES, row = r0 + 16 * (tile & 1) + jo, col = 16 * (tile >> 1) + 4 * go;
-                if ((tile >> 1) < G::FT && (DS % 16 == 0 || col < DS) && row < nrows)   // (bytes: a segment's dL/dx is below 4 GB)
+                if ((tile >> 1) < G::FT && row < nrows)   // (bytes: a segment's dL/dx is below 4 GB)
                     *(f32x4 *)((char *)dxs + (unsigned)(row * (4 * DS) + 4 * col)) = 0.5f * dx[i];
             }
             if (tid < kUnit && r0 + tid < nrows) {
@@ -451,8 +451,8 @@ __global__ __launch_bounds__(WAVES * 64, MINWAVES) void bwd_weights_kernel(
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
                     const int f = 32 * ot + acc_feature(i, go);
-                    if (DS % 32 == 0 || f < DS) pW1[(size_t)f * he + 32 * ht + jo] = 0.5f * aW1[ot][i];
-                    if (DS % 32 == 0 || 32 * ot + jo < DS) pW2[(size_t)(32 * ht + acc_feature(i, go)) * DS + 32 * ot + jo] = 0.5f * aW2[ot][i];
+                    pW1[(size_t)f * he + 32 * ht + jo] = 0.5f * aW1[ot][i];
+                    pW2[(size_t)(32 * ht + acc_feature(i, go)) * DS + 32 * ot + jo] = 0.5f * aW2[ot][i];
                 }
             ab1 += __shfl_xor(ab1, 32);   // the two lane groups hold different rows of the same hidden unit
             if (go == 0) pb1[32 * ht + jo] = 0.5f * ab1;
