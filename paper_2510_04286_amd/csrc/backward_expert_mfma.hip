@@ -221,7 +221,7 @@ __global__ __launch_bounds__(WAVES * 64, MINWAVES) void bwd_expert_kernel(
 
             // ---- dL/dx of the unit before
             const int dft = wave >> 1, drt = wave & 1;
-            const int dx_col = 4 * (16 * dft + 4 * G4);   // bytes (a segment's dL/dx is below 4 GB: a block's share of less than 2^31 rows)
+            const int dx_col = 4 * (16 * dft + 4 * G4);   // bytes (unsigned offsets: a segment's dL/dx is below 4 GB, a block's share of the rows that fit the card)
             f32x4 dx, dx_before;
             // (Every load here is waited for on every path of the same unit: one left over would be waited for where its registers
             // are written next, behind the gather of the next unit, whose latency would then show.)
@@ -229,7 +229,7 @@ __global__ __launch_bounds__(WAVES * 64, MINWAVES) void bwd_expert_kernel(
                 dx = dx_before = f32x4{0.f, 0.f, 0.f, 0.f};
                 if (again && has_dx) {
                     const int col = DS % 16 == 0 ? dx_col : min(dx_col, 4 * DS - 16);
-                    dx_before = *(const f32x4 *)((const char *)dxs + (unsigned)(max(min(r0 + 16 * drt + c16, nrows - 1), 0) * (4 * DS) + col));
+                    dx_before = *(const f32x4 *)((const char *)dxs + (unsigned)max(min(r0 + 16 * drt + c16, nrows - 1), 0) * (4u * DS) + (unsigned)col);
                 }
                 if (again && keeper) dp_before = dpk[r0 < 0 ? 0 : ((const int *)(lds + G::off_id))[buf * kUnit + (lane & (kUnit - 1))]];
             };
@@ -258,7 +258,7 @@ __global__ __launch_bounds__(WAVES * 64, MINWAVES) void bwd_expert_kernel(
                 dx = (dx_before + dx) * scale;
                 const int row = r0 + 16 * drt + c16;
                 if (has_dx && (DS % 16 == 0 || dx_col < 4 * DS) && (unsigned)row < (unsigned)nrows)
-                    *(f32x4 *)((char *)dxs + (unsigned)(row * (4 * DS) + dx_col)) = dx;
+                    *(f32x4 *)((char *)dxs + ((unsigned)row * (4u * DS) + (unsigned)dx_col)) = dx;
                 if (keeper) {
                     const float *dps = (const float *)(lds + G::off_dp) + buf * WAVES * kUnit + (lane & (kUnit - 1));
                     float v[WAVES], t = dp_before;

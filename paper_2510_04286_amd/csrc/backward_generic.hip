@@ -95,7 +95,8 @@ __global__ __launch_bounds__(kGbThreads) void bwd_expert_generic_kernel(
     // LDS bases of a lane: what is added to them in the loops is known to the compiler and takes no register
     const float *xs_b = xs + jj * XST + g, *gs_b = gs + jj * XST + 4 * g, *xs_r = xs + 4 * g * XST + jj, *gs_r = gs + 4 * g * XST + jj, *ps_r = ps + wave * kGbRows + 4 * g;
     float *pz_w = pz + (wave * 32 + jj) * kGbT + 4 * g, *red_w = red + (wave * kGbRows + 4 * g) * kGbT + jj;
-    // Values kb + 8 q + 4 g .. of a row of n, zero past it: `row` elements from the uniform p, so that an address is one register.
+    // Values kb + 8 q + 4 g .. of a row of n, zero past it: `row` elements from the uniform p, so that an address is one register.  The rows of a
+    // tile count from p, which has the tile's own 64-bit offset: 31 rows are below 4 GB (He up to 34 million fp32 values).
     auto quads_of = [&](const T *p, unsigned row, int kb, int n, bool vec, float (&b)[16]) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -132,7 +133,8 @@ __global__ __launch_bounds__(kGbThreads) void bwd_expert_generic_kernel(
             float ab1 = 0.f, ab2 = 0.f;
             // operands of 32 of a chunk's features: column hid of W1, row hid of W2 (K-step s of quad q: features kb + 8 q + 4 g + s)
             auto first_layer = [&](int c0, int nf, int kb, float (&bu)[16], float (&bd)[16]) {
-                unsigned col = (unsigned)(g * He + hidc), row = (unsigned)(hidc * ds);
+                const int tile = min(h0 + wave * 32, He - 1);   // (uniform)
+                unsigned col = (unsigned)(g * He + hidc), row = (unsigned)(min(jj, He - 1 - tile) * ds);
                 asm volatile("" : "+v"(col), "+v"(row));   // opaque: addresses are not kept in registers from one unit to the next
 #pragma unroll
                 for (int s = 0; s < 16; ++s) {
@@ -140,7 +142,7 @@ __global__ __launch_bounds__(kGbThreads) void bwd_expert_generic_kernel(
                     if (AHEAD) bu[s] = Storage<T>::load(at);
                     else bu[s] = kb + 2 * s + g < nf ? Storage<T>::load(at) : 0.f;
                 }
-                quads_of(w2 + c0, row, kb, nf, vec_ds, bd);
+                quads_of(w2 + (size_t)tile * ds + c0, row, kb, nf, vec_ds, bd);
             };
             int assigned = perm[row0 + min(jj, nrows - 1)];   // of row jj of the unit, in every wavefront
             for (int r0 = 0; r0 < nrows; r0 += kGbRows) {
@@ -191,8 +193,9 @@ __global__ __launch_bounds__(kGbThreads) void bwd_expert_generic_kernel(
                 __builtin_amdgcn_sched_barrier(0);
                 float bx[AHEAD ? OTC : 1][16];   // of dL/dx, requested ahead of the activations
                 const int dx_t = wave % OTC, dx_k0 = wave / OTC * (kGbHidden / PARTS), dx_k1 = min(dx_k0 + kGbHidden / PARTS, He - h0);
-                const T *wf = w1 + (size_t)own_c0 * He + h0;
-                unsigned dx_row = (unsigned)(min(32 * dx_t + jj, own_n - 1) * He);
+                const int dx_tile = min(32 * dx_t, own_n - 1);
+                const T *wf = w1 + (size_t)(own_c0 + dx_tile) * He + h0;
+                unsigned dx_row = (unsigned)min(jj, own_n - 1 - dx_tile) * (unsigned)He;
                 asm volatile("" : "+v"(dx_row));
                 if (AHEAD) {
 #pragma unroll

@@ -270,7 +270,7 @@ __global__ __launch_bounds__(WAVES * 64, MINWAVES) void bwd_weights_kernel(
             for (int i = 0; i < NT; ++i) {
                 const int tile = wave + i * WAVES, row = r0 + 16 * (tile & 1) + jo, col = 16 * (tile >> 1) + 4 * go;
                 if ((tile >> 1) < G::FT && row < nrows)   // (bytes: a segment's dL/dx is below 4 GB)
-                    *(f32x4 *)((char *)dxs + (unsigned)(row * (4 * DS) + 4 * col)) = 0.5f * dx[i];
+                    *(f32x4 *)((char *)dxs + ((unsigned)row * (4u * DS) + 4u * (unsigned)col)) = 0.5f * dx[i];
             }
             if (tid < kUnit && r0 + tid < nrows) {
                 const float *dps = (const float *)(lds + G::off_dp) + buf * WAVES * kUnit + tid;
