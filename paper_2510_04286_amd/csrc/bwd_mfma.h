@@ -160,19 +160,20 @@ hipError_t launch_backward_weights(const slicemoe_config &c, const BwdPacked &L,
                                    float *dxrow, float *dpk, hipStream_t s);
 
 // Twice GELU and twice its derivative of four values (the factors of two, exact, are taken out of the finished sums).  With x = |z|,
-// e = exp(-x^2 / 2), t = 1 / (1 + 0.3 x) and the quintic N(t) of gelu_grad.h: q = 2 Phi(-x) = e - x e N, and r = q - 2 x phi(x) is twice the
-// derivative at -x.  Then 2 z Phi(z) = (z + x) - x q, and the derivative is r below zero and 2 - r above: q and r keep a precision of their
-// own, where z (1 + erf) below zero has that of one.  Relative 2-norm of the error against 64-bit arithmetic, activation / derivative
+// e = exp(-x^2 / 2), t = 1 / (1 + 0.3 x) and the quintic N(t) of gelu_grad.h: q = 2 Phi(-x) = e - x e N, 2 z Phi(z) = (z + x) - x q, and with
+// p = 2 Phi(z), which is q below zero and 2 - q above, twice the derivative is p + 2 z phi(z).  q keeps a precision of its own, where
+// z (1 + erf) below zero has that of one.  Relative 2-norm of the error against 64-bit arithmetic, activation / derivative
 // (fp32, half a unit of error in the hardware's exponential):
 //                        this                                  1 + erf, same N          erff and expf            A & S 7.1.26
-//   z ~ N(0, 0.1 .. 2.5) 2.4e-8 .. 4.7e-8 / 3.6e-8 .. 5.1e-8   2.9e-8 .. 4.4e-8 / 4.9e-8   3.3e-8 .. 4.0e-8 / 4.0e-8  5.9e-8 .. 1.5e-7 / 1.7e-7
+//   z ~ N(0, 0.1 .. 2.5) 2.4e-8 .. 4.7e-8 / 4.0e-8 .. 5.5e-8   2.9e-8 .. 4.4e-8 / 4.9e-8   3.3e-8 .. 4.0e-8 / 4.0e-8  5.9e-8 .. 1.5e-7 / 1.7e-7
 //   z ~ N(-2, 0.3)       1.8e-7 / 1.3e-7                       4.9e-7 / 2.7e-7          3.3e-7 / 1.3e-7          1.7e-6 / 6.7e-7
 //   z ~ N(-5, 0.3)       5.4e-5 / 2.9e-6                       6.7e-3 / 5.5e-4          4.7e-3 / 2.2e-4          7.3e-4 / 3.9e-5
-// It takes two vector instructions more per element than 1 + erf (fused kernel's training step 529 -> 537 us), as many transcendental ones as the last.
+// The step from q to 2 - q is a product with infinity, clamped to 0 .. 1 (no number for z = 0, which the clamp makes 0: p = 1 either way): a comparison and a
+// selection write and wait for a mask (backward of 32 768 tokens at width 96 660 us with them, 650 without; width 128 2377, 2349).
 // Four side by side: a vector instruction that needs the result of the one before waits 8.3 cycles for it.
 __device__ __forceinline__ void twice_gelu4(const float (&z)[4], float (&act)[4], float (&slope)[4])
 {
-    float e[4], t[4], n[4], q[4], xe[4], r[4];
+    float e[4], t[4], n[4], q[4], ze[4], above[4];
 #define SLICEMOE_EACH for (int i = 0; i < 4; ++i)
 #pragma unroll
     SLICEMOE_EACH t[i] = fmaf(kGeluGradP, fabsf(z[i]), 1.f);
@@ -189,17 +190,19 @@ __device__ __forceinline__ void twice_gelu4(const float (&z)[4], float (&act)[4]
 #pragma unroll
         SLICEMOE_EACH n[i] = fmaf(n[i], t[i], kGeluGradN[c]);
 #pragma unroll
-    SLICEMOE_EACH xe[i] = e[i] * fabsf(z[i]);
+    SLICEMOE_EACH ze[i] = e[i] * z[i];
+#pragma unroll
+    SLICEMOE_EACH above[i] = __builtin_amdgcn_fmed3f(z[i] * __builtin_inff(), 0.f, 1.f);   // 1 above zero, 0 below
+#pragma unroll
+    SLICEMOE_EACH q[i] = fmaf(-fabsf(ze[i]), n[i], e[i]);
 #pragma unroll
     SLICEMOE_EACH act[i] = z[i] + fabsf(z[i]);
 #pragma unroll
-    SLICEMOE_EACH q[i] = fmaf(-xe[i], n[i], e[i]);
-#pragma unroll
     SLICEMOE_EACH act[i] = fmaf(-fabsf(z[i]), q[i], act[i]);
 #pragma unroll
-    SLICEMOE_EACH r[i] = fmaf(-0.79788456080286536f, xe[i], q[i]);
+    SLICEMOE_EACH q[i] = fabsf(fmaf(2.f, above[i], -q[i]));   // p
 #pragma unroll
-    SLICEMOE_EACH slope[i] = z[i] < 0.f ? r[i] : 2.f - r[i];
+    SLICEMOE_EACH slope[i] = fmaf(0.79788456080286536f, ze[i], q[i]);
 #undef SLICEMOE_EACH
 }
 
