@@ -13,7 +13,7 @@
 // sum over the wavefronts.
 //
 // Work split.  A wavefront owns SIXTEEN hidden units (v_mfma_f32_16x16x32_bf16 throughout), so that the sums of its weight gradients
-// take ds / 2 registers and three wavefronts fit a SIMD (168 registers each): a wavefront alone issues an instruction every 5 to 6
+// take ds / 2 registers and three wavefronts fit a SIMD (168 registers each; four of 128 at width 24): a wavefront alone issues an instruction every 5 to 6
 // cycles, two and more get through one every 2.6 (fp32 multiply-add) to 4.6 (conversions, shifts).  Experts with more hidden
 // units than a block has wavefronts for go through the same rows again, pass after pass: dL/dx and dL/dp of the passes before are
 // read back by the thread that wrote them and added to.
@@ -24,7 +24,8 @@
 // the unit that issued it, and the opaque copies of the address bases.
 //
 // Measured, alone on the chip: 65 536 rows, width 48, He 192: 72 us of a kernel with 32 hidden units per wavefront, erff and expf -> 37;
-// 131 056 rows, width 96, He 384: 107 + 96 us of two kernels (row gradients, weight gradients) -> 141.
+// 131 056 rows, width 96, He 384: 107 + 96 us of two kernels (row gradients, weight gradients) -> 141 (4% more with the present form of the
+// activation, which has one instruction per element more than the one it was measured with: twice_gelu4).
 //
 // TERMS: bf16 terms of the activation and of p dz, backward_terms(DS).
 #include "bwd_mfma.h"

@@ -282,7 +282,8 @@ __global__ __launch_bounds__(kGbThreads) void bwd_expert_generic_kernel(
 // operands are requested, without conditions, before the phase in front of it -- the softmax's and the logits' with the slices, the
 // expert path's rows and dL/dh's weights before the weight gradients -- and dL/dh leaves as one quad per thread.  A unit of 32
 // slices is a chain of eight phases with a barrier between them, and half of its time was the latency of their loads: 4000
-// slices, ds = 64, E = 8: 39 -> 26 us; 16 384 slices (a step's backward): 156 -> 137.
+// slices, ds = 64, E = 8: 39 -> 26 us; 16 384 slices (a step's backward): 156 -> 137.  (It takes all 256 registers and spills 12, of which nine are
+// reloaded in every unit; the instance without AHEAD spills none and is the slower one all the same.)
 constexpr int kGrFeat = 64;   // features at a time, and columns of a block
 struct GenericRouterLds {   // floats
     static constexpr size_t xT = 0, w = xT + (size_t)kGrFeat * 36, us = w + (size_t)kGrFeat * kGbHidden;   // us: [32][257] u, then [256][33] dL/du

@@ -122,7 +122,7 @@ __device__ __forceinline__ void capacity_derivatives(const CapLoss &C, int E, in
     capg[tid] = S > 0.0 ? (float)(ldexp((double)C.alpha, C.bits) * (2.0 * E / (S * S)) * (c - Q / S)) : 0.f;
 }
 
-// Append what the expert part and the router part need (four and seven jobs); `packed` and `scratch` are their regions.
+// Append what the expert part and the router part need (three or four jobs, and seven); `packed` and `scratch` are their regions.
 void backward_expert_pack_jobs(const slicemoe_config &c, const slicemoe_weights &w, void *packed, BwdPackJobs &jobs);
 void backward_router_pack_jobs(const slicemoe_config &c, const slicemoe_weights &w, void *scratch, BwdPackJobs &jobs);
 
@@ -132,7 +132,7 @@ void backward_router_pack_jobs(const slicemoe_config &c, const slicemoe_weights 
 //   w1c  [HT][2][OT][64]   W1 with the hidden units as contraction slots in accumulator order:
 //                          lane (i, g), slot m: W1[32ot + i][32ht + chain_feature(s, g, m)]
 //   w1d  [FT][HT][64]      the same for 16-feature tiles: lane (i, g) of 16 x 4, slot m: W1[16ft + i][32ht + 8g + m]
-//                          (only one of w1c and w1d is there: w1d when the fused kernel runs)
+//                          (one of w1c and w1d is there: w1d when the fused kernel runs; neither where only the one-pass kernel does)
 //   b1   [He] fp32
 struct BwdPacked {
     size_t w1f, w2r, w1c, w1d, b1, stride;

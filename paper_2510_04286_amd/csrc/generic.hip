@@ -291,7 +291,7 @@ __global__ __launch_bounds__(kF32Threads) void ffn_generic_kernel(
 // all be requested ahead: the first product's weights with the rows, the second's before the activations, the output's bias with
 // those.  Every wavefront reads the unit's indexes itself, so that there is no barrier between an index and its row.
 // 8000 rows, ds = 64, He = 256: 18 -> 13 us; 32 768 rows (a forward pass): 108 -> 73 us, two blocks per compute unit instead of one
-// (128 registers, 144 before); ds = 32, He = 128, 131 072 rows: 289 -> 140.
+// (128 registers, 144 before; at ds = 64 that bound spills 8 to 10, four of them reloaded per 256 hidden units); ds = 32, He = 128, 131 072 rows: 289 -> 140.
 template <typename T, typename YT, int OT>
 __global__ __launch_bounds__(kF32Threads, 4) void ffn_generic_ahead_kernel(
     const T *__restrict__ x, const float *__restrict__ pk, const int32_t *__restrict__ offsets,
