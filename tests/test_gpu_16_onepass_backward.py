@@ -1,7 +1,8 @@
 """The one-pass expert backward (slice widths 24, 48 and 96) where its split can go wrong: hidden tiles that fill a pass of the block's
 wavefronts exactly, leave some idle, or need several passes (dL/dx and dL/dp of the passes before are read back and added to),
 one row, a ragged last unit, several units per block, every k, a capacity limit, an expert that takes all rows.  Against the fp32
-kernels, which every shape has (SLICEMOE_FLAG_FORCE_GENERIC), on the same routing.
+kernels, which every shape has (SLICEMOE_FLAG_FORCE_GENERIC), on the same routing; and on both sides of every line of the choice between this
+kernel and the two others at width 96 (csrc/onepass_split.h says which side a case is on) and of the two ways to split the units, against 64 bits.
 
 Bars.  Both sides sum in fp32; the operands of the one-pass kernel's second products have 24 significant bits at 24 and 48, 16 at 96 (two
 bf16 terms), so a summand differs by at most 2^-17 of itself at 96 and by fp32 rounding at the others, and a gradient, a sum

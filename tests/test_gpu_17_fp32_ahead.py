@@ -76,7 +76,8 @@ FORWARD = {   # the expert kernel that requests ahead: 32 and 64 columns, hidden
     "w64_three_tiles": shape(50, 3, 2, ds=64, He=96),
     "w64_two_groups": shape(50, 3, 2, ds=64, He=288),
     "w64_one_row": shape(1, 2, 1, S=1, ds=64, He=256),
-    # the router's second layer in LDS: columns in quads; rows, since columns would be 636 bytes too many; rows of an odd width
+    # the router's second layer in LDS: columns in quads; rows, since columns would be 720 bytes too many (464 without the
+    # histogram's counts); rows of an odd width
     "router_columns": shape(9, 39, 3, ds=492, Hr=128),
     "router_rows_fit_columns_do_not": shape(9, 39, 3, ds=496, Hr=256),
     "router_rows": shape(9, 17, 3, ds=20, Hr=129),

@@ -6,8 +6,8 @@ cases (no near-tie among them), because a weight gradient sums over every slice;
 treats the few near-ties it has.
 Bars, derived from the arithmetic (the forward's tolerance is stated for h' only).  Two kinds of kernels: fp32
 throughout (exact GELU) and, for bf16 storage at slice widths 24, 48, 64, 96, 128 and 192, bf16 matrix-core (fp32
-pre-activations and derivative, erf to 1.5e-7; p dL/dz and the activation enter the second matrix instructions as two-term
-bf16 splits with 16 significant bits against exact bf16 data, three terms and erff at 24, 48 and 192).  Both are of fp32
+pre-activations, activation and derivative; p dL/dz and the activation enter the second matrix instructions as two-term
+bf16 splits with 16 significant bits against exact bf16 data, three terms at 24, 48 and 192).  Both are of fp32
 grade and share the bars:
 dL/dh is computed in fp32 and rounded once to the storage type, so per element |err| <= 2^-8 |ref| + 2e-4 RMS for
 bf16 storage (half a unit in the last place of 8 significant bits is at most 2^-8 relative; the RMS term covers the
