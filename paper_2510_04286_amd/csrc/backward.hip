@@ -167,17 +167,19 @@ BackwardPlan backward_plan(const slicemoe_config &c)
     BackwardPlan p;
     const size_t Ns = (size_t)c.T * c.S, Na = Ns * c.k;
     const size_t ds = (size_t)(c.d / c.S);
-    p.expert_slots = backward_mfma_shape(c) ? backward_weights_plan(c).slots : backward_generic_expert_slots(c);
-    const size_t expert_reserve = (size_t)(backward_mfma_shape(c) ? backward_weights_slots_bound(c) : p.expert_slots);
-    const size_t router_reserve = (size_t)(backward_router_mfma_shape(c) ? backward_router_mfma_slots_bound(c) : backward_generic_router_slots_bound(c));
-    p.router_slots = backward_router_mfma_shape(c) ? backward_router_mfma_slots(c) : backward_generic_router_slots(c);
+    p.expert_mfma = backward_mfma_shape(c);
+    p.router_mfma = backward_router_mfma_shape(c);
+    const BackwardWeightsPlan W = p.expert_mfma ? backward_weights_plan(c) : backward_generic_plan(c);
+    p.expert_slots = W.slots;
+    p.router_slots = p.router_mfma ? backward_router_mfma_slots(c) : backward_generic_router_slots(c);
+    const size_t router_reserve = (size_t)(p.router_mfma ? backward_router_mfma_slots_bound(c) : backward_generic_router_slots_bound(c));
     size_t at = 0;
     p.dxrow = at;  at = align_up(at + Na * ds * sizeof(float), 256);
     p.dpk = at;    at = align_up(at + Na * sizeof(float), 256);
-    p.expert_part = at;  at = align_up(at + expert_reserve * expert_slot_floats((int)ds, c.He) * sizeof(float), 256);
+    p.expert_part = at;  at = align_up(at + (size_t)W.reserve * expert_slot_floats((int)ds, c.He) * sizeof(float), 256);
     p.router_part = at;  at = align_up(at + router_reserve * router_slot_floats((int)ds, c.Hr, c.E) * sizeof(float), 256);
-    p.packed = at;  at = align_up(at + backward_mfma_packed_bytes(c), 256);
-    p.router_scratch = at;  at = align_up(at + backward_router_mfma_scratch_bytes(c), 256);
+    p.packed = at;  at = align_up(at + (p.expert_mfma ? backward_mfma_packed_bytes(c) : 0), 256);
+    p.router_scratch = at;  at = align_up(at + (p.router_mfma ? backward_router_mfma_scratch_bytes(c) : 0), 256);
     p.cap = at;  at = align_up(at + (size_t)c.E * cap_blocks((long long)Na) * sizeof(unsigned long long), 256);
     p.total = at + 256;
     return p;
@@ -253,6 +255,7 @@ hipError_t launch_backward(const slicemoe_config &c, const void *h, const slicem
         return zero_fill(g.b2, (size_t)c.E * ds, s);
     }
     const BackwardPlan P = backward_plan(c);
+    const BackwardWeightsPlan W = P.expert_mfma ? backward_weights_plan(c) : backward_generic_plan(c);
     char *ws = (char *)workspace;
     RouteVariant v = v_in;
     float *dxrow = (float *)(ws + P.dxrow), *dpk = (float *)(ws + P.dpk);
@@ -262,8 +265,8 @@ hipError_t launch_backward(const slicemoe_config &c, const void *h, const slicem
     // CU beside the weight gradients), whatever it moves.
     BwdPackJobs jobs;
     jobs.count = 0;
-    if (backward_mfma_shape(c)) backward_expert_pack_jobs(c, w, ws + P.packed, jobs);
-    if (backward_router_mfma_shape(c)) backward_router_pack_jobs(c, w, ws + P.router_scratch, jobs);
+    if (P.expert_mfma) backward_expert_pack_jobs(c, W, w, ws + P.packed, jobs);
+    if (P.router_mfma) backward_router_pack_jobs(c, w, ws + P.router_scratch, jobs);
     CapSums cap = {0, idx, pk, Na, c.E, ldexpf(1.f, capacity_fraction_bits(Na)), (unsigned long long *)(ws + P.cap)};
     if (v.cap_alpha != 0.f) {
         cap.blocks = cap_blocks(Na);
@@ -281,13 +284,13 @@ hipError_t launch_backward(const slicemoe_config &c, const void *h, const slicem
     // Where one kernel gives dL/dx and the weight gradients only their reduction could run beside the router's kernels,
     // and it takes more from the first of them than it hides (d=1024 S=16 E=32 T=16384: 13 us + 45 us in turn, 67 us
     // together, and 6 us for the fork; the whole backward 469 us on one stream, 482 us on two).
-    if (backward_mfma_shape(c) && ((c.flags & SLICEMOE_FLAG_SINGLE_STREAM) || backward_weights_plan(c).fused)) {
-        e = launch_backward_expert_mfma(c, h, d_out, pk, offsets, perm, ws + P.packed, eslot, dxrow, dpk, epart, s);
+    if (P.expert_mfma && ((c.flags & SLICEMOE_FLAG_SINGLE_STREAM) || W.fused)) {
+        e = launch_backward_expert_mfma(c, W, h, d_out, pk, offsets, perm, ws + P.packed, eslot, dxrow, dpk, epart, s);
         if (e != hipSuccess) return e;
-    } else if (backward_mfma_shape(c)) {
+    } else if (P.expert_mfma) {
         side_lock.lock();
         if ((e = side_stream(&side)) != hipSuccess) return e;
-        e = launch_backward_expert_mfma(c, h, d_out, pk, offsets, perm, ws + P.packed, eslot, dxrow, dpk, epart, s, &side);
+        e = launch_backward_expert_mfma(c, W, h, d_out, pk, offsets, perm, ws + P.packed, eslot, dxrow, dpk, epart, s, &side);
         joiner.side = &side;   // from here on the side stream holds work of this call: joined on every way out
         joiner.s = s;
         se = side.stream;
@@ -297,13 +300,12 @@ hipError_t launch_backward(const slicemoe_config &c, const void *h, const slicem
         if (e != hipSuccess) return e;
     }
     const size_t rslot = router_slot_floats(ds, c.Hr, c.E);
-    const BackwardWeightsPlan W = backward_mfma_shape(c) ? backward_weights_plan(c) : backward_generic_plan(c);
     const ReduceArgs sums = {epart, offsets, W.step, W.overhead, W.blocks, eslot, rpart, (int)P.router_slots, rslot, 0, ds, c.He, c.Hr, c.E, g};
     // the experts' slots: at once, on the stream that fills them, or together with the router's (see kReduceApartBytes)
     const bool apart = se != s || ((size_t)P.expert_slots * eslot + (size_t)P.router_slots * rslot) * sizeof(float) > kReduceApartBytes;
     if (apart && (e = launch_reduce(sums, true, false, se)) != hipSuccess) return e;
 
-    if (backward_router_mfma_shape(c)) {
+    if (P.router_mfma) {
         e = launch_backward_router_mfma(c, h, v, drop_u, rate, idx, inv, dpk, dxrow, d_h, ws + P.router_scratch,
                                         rslot, rpart, s);
         if (e != hipSuccess) return e;

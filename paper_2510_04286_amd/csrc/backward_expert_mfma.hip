@@ -404,13 +404,6 @@ __global__ __launch_bounds__(WAVES * 64, MINWAVES) void bwd_expert_kernel(
 }
 
 // ------------------------------------------------------------------------------------------------------ host
-bool backward_onepass(const slicemoe_config &c)
-{
-    return onepass_chosen(c.d / c.S, c.He, ((long long)c.T * c.S * c.k + kUnit - 1) / kUnit, num_compute_units());
-}
-
-bool backward_onepass_by_batch(const slicemoe_config &c) { return onepass_depends_on_batch(c.d / c.S, c.He); }
-
 // Blocks there are units for, at the most: an expert's rows begin one.
 static long long expert_blocks_bound(const slicemoe_config &c, long long units)
 {
@@ -429,28 +422,24 @@ BackwardWeightsPlan backward_expert_plan(const slicemoe_config &c)
     BackwardWeightsPlan W;
     const long long units = ((long long)c.T * c.S * c.k + kUnit - 1) / kUnit, most = expert_blocks_bound(c, units);
     const bool few = units <= 2 * c.E;
-    W.fused = true;
+    W.onepass = W.fused = true;
     W.step = kUnit;
     W.overhead = few ? 0 : 1;
     W.groups = 1;
     W.blocks = (int)(few || units > most ? most : units);
     W.slots = (long long)W.blocks + c.E;
+    W.reserve = most + c.E;
     return W;
-}
-long long backward_expert_slots_bound(const slicemoe_config &c)
-{
-    return expert_blocks_bound(c, ((long long)c.T * c.S * c.k + kUnit - 1) / kUnit) + c.E;
 }
 
 template <int DS, int WAVES, int MINWAVES>
-static hipError_t run_expert(const slicemoe_config &c, const BwdPacked &L, const void *h, const void *d_out, const float *pk,
+static hipError_t run_expert(const slicemoe_config &c, const BackwardWeightsPlan &W, const BwdPacked &L, const void *h, const void *d_out, const float *pk,
                              const int32_t *offsets, const int32_t *perm, const char *packed, size_t slot_floats, float *part,
                              float *dxrow, float *dpk, hipStream_t s)
 {
     constexpr int TERMS = backward_terms(DS);
     constexpr size_t lds = ExpertTile<DS, WAVES, TERMS>::lds;
     if (onepass_waves(DS, c.He) != WAVES) return hipErrorInvalidValue;
-    const BackwardWeightsPlan W = backward_expert_plan(c);
     auto kern = bwd_expert_kernel<DS, WAVES, TERMS, MINWAVES>;
     const hipError_t e = grant_dynamic_lds((const void *)kern, lds);
     if (e != hipSuccess) return e;
@@ -460,15 +449,15 @@ static hipError_t run_expert(const slicemoe_config &c, const BwdPacked &L, const
     return hipGetLastError();
 }
 
-hipError_t launch_backward_expert_onepass(const slicemoe_config &c, const BwdPacked &L, const void *h, const void *d_out, const float *pk,
-                                          const int32_t *offsets, const int32_t *perm, const char *packed, size_t slot_floats,
+hipError_t launch_backward_expert_onepass(const slicemoe_config &c, const BackwardWeightsPlan &W, const BwdPacked &L, const void *h, const void *d_out,
+                                          const float *pk, const int32_t *offsets, const int32_t *perm, const char *packed, size_t slot_floats,
                                           float *part, float *dxrow, float *dpk, hipStream_t s)
 {
     const int ds = c.d / c.S;
-    return ds == 24 && onepass_waves(ds, c.He) == 8 ? run_expert<24, 8, 4>(c, L, h, d_out, pk, offsets, perm, packed, slot_floats, part, dxrow, dpk, s)
-         : ds == 24 ? run_expert<24, 16, 4>(c, L, h, d_out, pk, offsets, perm, packed, slot_floats, part, dxrow, dpk, s)
-         : ds == 48 ? run_expert<48, 12, 3>(c, L, h, d_out, pk, offsets, perm, packed, slot_floats, part, dxrow, dpk, s)
-         : ds == 96 ? run_expert<96, 12, 3>(c, L, h, d_out, pk, offsets, perm, packed, slot_floats, part, dxrow, dpk, s)
+    return ds == 24 && onepass_waves(ds, c.He) == 8 ? run_expert<24, 8, 4>(c, W, L, h, d_out, pk, offsets, perm, packed, slot_floats, part, dxrow, dpk, s)
+         : ds == 24 ? run_expert<24, 16, 4>(c, W, L, h, d_out, pk, offsets, perm, packed, slot_floats, part, dxrow, dpk, s)
+         : ds == 48 ? run_expert<48, 12, 3>(c, W, L, h, d_out, pk, offsets, perm, packed, slot_floats, part, dxrow, dpk, s)
+         : ds == 96 ? run_expert<96, 12, 3>(c, W, L, h, d_out, pk, offsets, perm, packed, slot_floats, part, dxrow, dpk, s)
                     : hipErrorInvalidValue;
 }
 

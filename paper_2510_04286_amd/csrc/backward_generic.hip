@@ -682,6 +682,7 @@ BackwardWeightsPlan backward_generic_plan(const slicemoe_config &c)
     BackwardWeightsPlan W;
     const long long Na = (long long)c.T * c.S * c.k;
     const int ds = c.d / c.S, cc = 32 * generic_col_tiles(ds);
+    W.onepass = false;
     W.fused = true;
     W.groups = 1;
     W.step = kGbRows;
@@ -693,11 +694,9 @@ BackwardWeightsPlan backward_generic_plan(const slicemoe_config &c)
     const long long most = (Na + kGbRows - 1) / kGbRows + c.E - 1;   // units: an expert's rows begin one
     if (blocks > most) blocks = most;
     W.blocks = blocks < 1 ? 1 : (int)blocks;
-    W.slots = (long long)W.blocks + c.E;
+    W.slots = W.reserve = (long long)W.blocks + c.E;
     return W;
 }
-
-long long backward_generic_expert_slots(const slicemoe_config &c) { return backward_generic_plan(c).slots; }
 
 static int generic_router_blocks(const slicemoe_config &c)   // at the most, of one chunk of columns
 {

@@ -18,6 +18,7 @@
 // bits) at widths 24, 48 and 192 (backward_terms), which are as close to 64-bit arithmetic as the fp32 kernels.  The kernels are
 // bound by vector instructions, not by the matrix pipe, so a further term costs little.
 #include "bwd_mfma.h"
+#include "onepass_split.h"
 
 namespace slicemoe {
 
@@ -26,7 +27,7 @@ static BwdPacked bwd_packed_layout(const slicemoe_config &c)
     BwdPacked L;
     const int ds = c.d / c.S, He = c.He;
     // (w1c has its place for every batch of a layer if it has for some: the size never falls as the batch grows)
-    const bool onepass = backward_onepass(c) && !backward_onepass_by_batch(c), fused = !backward_onepass_by_batch(c) && backward_weights_plan(c).fused;
+    const bool onepass = onepass_in_every_batch(ds, He), fused = weights_fused(ds, He);
     const size_t dsK = (size_t)(ds + 15) / 16 * 16, dsN = (size_t)(ds + 31) / 32 * 32;
     L.w1f = 0;
     L.w2r = dsK * He * 2;
@@ -361,7 +362,7 @@ bool backward_mfma_shape(const slicemoe_config &c)
 
 size_t backward_mfma_packed_bytes(const slicemoe_config &c)
 {
-    return backward_mfma_shape(c) ? bwd_packed_layout(c).stride * (size_t)c.E : 0;
+    return bwd_packed_layout(c).stride * (size_t)c.E;
 }
 
 template <int DS>
@@ -382,42 +383,39 @@ static hipError_t run_rows_mfma(const slicemoe_config &c, const BwdPacked &L, co
     return hipGetLastError();
 }
 
-void backward_expert_pack_jobs(const slicemoe_config &c, const slicemoe_weights &w, void *packed, BwdPackJobs &jobs)
+void backward_expert_pack_jobs(const slicemoe_config &c, const BackwardWeightsPlan &W, const slicemoe_weights &w, void *packed, BwdPackJobs &jobs)
 {
     const int He = c.He, E = c.E, ds = c.d / c.S, dsK = (ds + 15) / 16 * 16, dsN = (ds + 31) / 32 * 32;
     const BwdPacked L = bwd_packed_layout(c);
     char *pb = (char *)packed;
     const size_t wstride = (size_t)ds * He;
-    const bool onepass = backward_onepass(c);
     BwdPackJob *J = jobs.job + jobs.count;
-    jobs.count += onepass ? 3 : 4;
+    jobs.count += W.onepass ? 3 : 4;
     // w1f: the [ds, He] matrix W1 itself; w2r: the [ds, He] matrix M[c][hidden] = W2[hidden][c]
     J[0] = bwd_pack_job(kPackLayer1, w.W1, dsK, ds, He, He, (size_t)He, 1, wstride, pb + L.w1f, L.stride, E);
     J[1] = bwd_pack_job(kPackLayer1, w.W2, dsK, ds, He, He, 1, (size_t)ds, wstride, pb + L.w2r, L.stride, E);
     J[2] = bwd_pack_job(kPackBias, w.b1, He, He, He, He, 0, 0, (size_t)He, pb + L.b1, L.stride, E);
-    if (onepass) return;
+    if (W.onepass) return;
     // w1d: W1 in 16-feature tiles.  w1c: the [He, ds] matrix M[hidden][c] = W1[c][hidden], contraction over the hidden units
     // in accumulator order
-    if (backward_weights_plan(c).fused)
+    if (W.fused)
         J[3] = bwd_pack_job(kPackTile16, w.W1, dsK, ds, He, He, (size_t)He, 1, wstride, pb + L.w1d, L.stride, E);
     else J[3] = bwd_pack_job(kPackChain, w.W1, He, He, dsN, ds, 1, (size_t)He, wstride, pb + L.w1c, L.stride, E);
 }
 
 // Runs the kernels on the backward copies of the expert weights in `packed` (backward_expert_pack_jobs, launched on s before).
-// part holds backward_weights_plan(c).slots slots of slot_floats floats.  When the weight gradients come from a kernel of
+// part holds W.slots slots of slot_floats floats, W = backward_weights_plan(c).  When the weight gradients come from a kernel of
 // their own it runs on the side stream (if there is one), from the moment the repacked weights are there.
-hipError_t launch_backward_expert_mfma(const slicemoe_config &c, const void *h, const void *d_out,
+hipError_t launch_backward_expert_mfma(const slicemoe_config &c, const BackwardWeightsPlan &W, const void *h, const void *d_out,
                                        const float *pk, const int32_t *offsets, const int32_t *perm, void *packed,
                                        size_t slot_floats, float *dxrow, float *dpk, float *part, hipStream_t s,
                                        const SideStream *side)
 {
-    if (!backward_mfma_shape(c)) return hipErrorInvalidValue;
     const int ds = c.d / c.S;
-    const BackwardWeightsPlan W = backward_weights_plan(c);
     const BwdPacked L = bwd_packed_layout(c);
     const char *pb = (const char *)packed;
     hipError_t e;
-    if (backward_onepass(c)) return launch_backward_expert_onepass(c, L, h, d_out, pk, offsets, perm, pb, slot_floats, part, dxrow, dpk, s);
+    if (W.onepass) return launch_backward_expert_onepass(c, W, L, h, d_out, pk, offsets, perm, pb, slot_floats, part, dxrow, dpk, s);
     if (!W.fused) {
         if (side != nullptr) {
             if ((e = hipEventRecord(side->fork, s)) != hipSuccess) return e;
@@ -429,7 +427,7 @@ hipError_t launch_backward_expert_mfma(const slicemoe_config &c, const void *h, 
                       : run_rows_mfma<192>(c, L, h, d_out, pk, offsets, perm, pb, dxrow, dpk, s);
         if (e != hipSuccess) return e;
     }
-    return launch_backward_weights(c, L, h, d_out, pk, offsets, perm, pb, slot_floats, part, dxrow, dpk,
+    return launch_backward_weights(c, W, L, h, d_out, pk, offsets, perm, pb, slot_floats, part, dxrow, dpk,
                                    !W.fused && side != nullptr ? side->stream : s);
 }
 

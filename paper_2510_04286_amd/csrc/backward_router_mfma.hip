@@ -972,7 +972,7 @@ static RouterBwdScratch router_bwd_scratch(const slicemoe_config &c)
 
 size_t backward_router_mfma_scratch_bytes(const slicemoe_config &c)
 {
-    return backward_router_mfma_shape(c) ? router_bwd_scratch(c).total : 0;
+    return router_bwd_scratch(c).total;
 }
 
 // Units of 32 slices per block of the weights kernel: one block per CU, at least two units each (a block leaves a slot of

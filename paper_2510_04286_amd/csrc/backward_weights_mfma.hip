@@ -28,11 +28,12 @@
 // activation, the latter without prefetch and with transposes on the matrix pipe) -> 254 us (236 at the least); the partial sums of
 // the weight gradients fall from 140 MB in 1056 slots to 38 MB in 288 (their reduction 29-35 -> 12 us).  Unfused, alone on the
 // chip, at width 128, He = 512: 2.78 -> 1.09 ms for 1 048 576 rows; width 96, He = 384: 228 -> 98 us for 131 056 rows.  (Widths 24
-// and 48, and 96 where backward_onepass says so: backward_expert_mfma.hip.)
+// and 48, and 96 where onepass_chosen says so: backward_expert_mfma.hip.)
 //
 // TERMS: bf16 terms of the activation and of p dz, backward_terms(DS).
 #include "bwd_mfma.h"
 #include "lds_rows.h"
+#include "onepass_split.h"
 #include "wavefront.h"
 
 namespace slicemoe {
@@ -45,7 +46,7 @@ __device__ __forceinline__ int pdz_offset(int hidden, int quad)
     return hidden * 64 + ((quad ^ sw) << 3);
 }
 
-constexpr int kUnit = 32;   // stacked rows a block works on at a time
+constexpr int kUnit = kOnepassUnit;   // stacked rows a block works on at a time, as in the one-pass kernel
 
 // Geometry of one instantiation.
 template <int DS, int WAVES, int NBUF, bool WLDS, bool FUSE, int TERMS> struct WeightsTile {
@@ -479,18 +480,13 @@ __global__ __launch_bounds__(WAVES * 64, MINWAVES) void bwd_weights_kernel(
 //   192           192 accumulators: one wavefront per SIMD
 struct WeightsConfig {
     int waves, per_cu;
-    bool fused;
 };
 static WeightsConfig weights_config(int ds, int He)
 {
-    const int HT = He / 32;
-    if (ds == 64) {
-        if (HT <= 4) return {4, 1, true};
-        return {8, 1, HT <= 8};
-    }
-    if (ds == 96) return {4, 2, false};
-    if (ds == 128) return {8, 1, false};
-    return {4, 1, false};
+    if (ds == 64) return {He <= 128 ? 4 : 8, 1};
+    if (ds == 96) return {4, 2};
+    if (ds == 128) return {8, 1};
+    return {4, 1};
 }
 
 static BackwardWeightsPlan weights_kernel_plan(const slicemoe_config &c)
@@ -499,7 +495,8 @@ static BackwardWeightsPlan weights_kernel_plan(const slicemoe_config &c)
     const WeightsConfig C = weights_config(c.d / c.S, c.He);
     const int HT = c.He / 32;
     const long long Na = (long long)c.T * c.S * c.k;
-    W.fused = C.fused;
+    W.onepass = false;
+    W.fused = weights_fused(c.d / c.S, c.He);
     W.step = kUnit;
     W.overhead = 1;
     W.groups = (HT + C.waves - 1) / C.waves;
@@ -507,20 +504,18 @@ static BackwardWeightsPlan weights_kernel_plan(const slicemoe_config &c)
     const long long most = (Na + kUnit - 1) / kUnit;
     if (blocks > most) blocks = most;
     W.blocks = blocks < 1 ? 1 : (int)blocks;
-    W.slots = (long long)W.blocks + c.E;
+    W.slots = W.reserve = (long long)W.blocks + c.E;
     return W;
 }
 
 BackwardWeightsPlan backward_weights_plan(const slicemoe_config &c)
 {
-    return backward_onepass(c) ? backward_expert_plan(c) : weights_kernel_plan(c);
-}
-
-long long backward_weights_slots_bound(const slicemoe_config &c)
-{
-    const bool by_batch = backward_onepass_by_batch(c);
-    const long long a = by_batch || !backward_onepass(c) ? weights_kernel_plan(c).slots : 0, b = by_batch || backward_onepass(c) ? backward_expert_slots_bound(c) : 0;
-    return a > b ? a : b;
+    const int ds = c.d / c.S;
+    if (!onepass_depends_on_batch(ds, c.He)) return onepass_in_every_batch(ds, c.He) ? backward_expert_plan(c) : weights_kernel_plan(c);
+    const long long units = ((long long)c.T * c.S * c.k + kUnit - 1) / kUnit;
+    BackwardWeightsPlan one = backward_expert_plan(c), two = weights_kernel_plan(c);
+    one.reserve = two.reserve = one.reserve > two.reserve ? one.reserve : two.reserve;
+    return onepass_chosen(ds, c.He, units, num_compute_units()) ? one : two;
 }
 
 template <int DS, int WAVES, int NBUF, bool WLDS, bool FUSE, int TERMS, int MINWAVES>
@@ -539,11 +534,10 @@ static hipError_t run_weights(const slicemoe_config &c, const BackwardWeightsPla
     return hipGetLastError();
 }
 
-hipError_t launch_backward_weights(const slicemoe_config &c, const BwdPacked &L, const void *h, const void *d_out, const float *pk,
+hipError_t launch_backward_weights(const slicemoe_config &c, const BackwardWeightsPlan &W, const BwdPacked &L, const void *h, const void *d_out, const float *pk,
                                    const int32_t *offsets, const int32_t *perm, const char *packed, size_t slot_floats, float *part,
                                    float *dxrow, float *dpk, hipStream_t s)
 {
-    const BackwardWeightsPlan W = backward_weights_plan(c);
     const int ds = c.d / c.S, waves = weights_config(ds, c.He).waves;
 #define SLICEMOE_WEIGHTS(DS, WAVES, NBUF, WLDS, FUSE, MINW)                                                                        \
     if (ds == DS && waves == WAVES && W.fused == FUSE)                                                                              \

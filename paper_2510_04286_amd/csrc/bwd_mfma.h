@@ -123,7 +123,7 @@ __device__ __forceinline__ void capacity_derivatives(const CapLoss &C, int E, in
 }
 
 // Append what the expert part and the router part need (three or four jobs, and seven); `packed` and `scratch` are their regions.
-void backward_expert_pack_jobs(const slicemoe_config &c, const slicemoe_weights &w, void *packed, BwdPackJobs &jobs);
+void backward_expert_pack_jobs(const slicemoe_config &c, const BackwardWeightsPlan &W, const slicemoe_weights &w, void *packed, BwdPackJobs &jobs);
 void backward_router_pack_jobs(const slicemoe_config &c, const slicemoe_weights &w, void *scratch, BwdPackJobs &jobs);
 
 // Backward copies of one expert's weights in fragment order (bytes from the start of the expert's block).
@@ -140,22 +140,21 @@ struct BwdPacked {
 // Matrix-core expert weight gradients (backward_weights_mfma.hip): the split of the rows and the launches.  fused: the
 // kernel also writes dL/dx and dL/dp of the rows.
 struct BackwardWeightsPlan {
-    bool fused;
+    bool onepass, fused;   // onepass: bwd_expert_kernel (then fused too)
     int step, groups, blocks;
-    int overhead;      // of an expert, on the axis of the work split: 0 or 1
-    long long slots;   // of partial weight gradients
+    int overhead;          // of an expert, on the axis of the work split: 0 or 1
+    // Slots of partial weight gradients: those that this batch uses, and those to reserve -- at least as many, and never fewer for more
+    // tokens, so that a workspace made for a layer's largest batch takes its smaller ones, whichever kernels those run on.
+    long long slots, reserve;
 };
+constexpr bool weights_fused(int ds, int He) { return ds == 64 && He <= 256; }
 BackwardWeightsPlan backward_weights_plan(const slicemoe_config &c);
-// The same of the one-pass kernel of 16-wide hidden tiles (backward_expert_mfma.hip) and the shapes it takes.
-bool backward_onepass(const slicemoe_config &c);
-bool backward_onepass_by_batch(const slicemoe_config &c);   // whether another number of tokens may be another choice
-BackwardWeightsPlan backward_expert_plan(const slicemoe_config &c);
-long long backward_expert_slots_bound(const slicemoe_config &c);   // at least its slots, never fewer for more tokens
-hipError_t launch_backward_expert_onepass(const slicemoe_config &c, const BwdPacked &L, const void *h, const void *d_out, const float *pk,
-                                          const int32_t *offsets, const int32_t *perm, const char *packed, size_t slot_floats,
+BackwardWeightsPlan backward_expert_plan(const slicemoe_config &c);   // of the one-pass kernel (backward_expert_mfma.hip)
+hipError_t launch_backward_expert_onepass(const slicemoe_config &c, const BackwardWeightsPlan &W, const BwdPacked &L, const void *h, const void *d_out,
+                                          const float *pk, const int32_t *offsets, const int32_t *perm, const char *packed, size_t slot_floats,
                                           float *part, float *dxrow, float *dpk, hipStream_t s);
 BackwardWeightsPlan backward_generic_plan(const slicemoe_config &c);   // of the fp32 expert kernel (backward_generic.hip)
-hipError_t launch_backward_weights(const slicemoe_config &c, const BwdPacked &L, const void *h, const void *d_out, const float *pk,
+hipError_t launch_backward_weights(const slicemoe_config &c, const BackwardWeightsPlan &W, const BwdPacked &L, const void *h, const void *d_out, const float *pk,
                                    const int32_t *offsets, const int32_t *perm, const char *packed, size_t slot_floats, float *part,
                                    float *dxrow, float *dpk, hipStream_t s);
 

@@ -157,6 +157,7 @@ hipError_t launch_route_mfma(const slicemoe_config &c, const void *h, const void
 // Backward pass (backward.hip): weight gradients into g, dL/dh into d_h.  backward_plan: layout of its scratch (row
 // gradients, dL/dp, slots of partial weight gradients); backward_lds_bytes: the measure that bounds the shapes it takes.
 struct BackwardPlan {
+    bool expert_mfma, router_mfma;          // which kernels run
     long long expert_slots, router_slots;   // slots of partial weight gradients that the call uses
     size_t dxrow, dpk, expert_part, router_part, packed, router_scratch, cap, total;   // byte offsets into the workspace, total size
 };
@@ -164,11 +165,11 @@ BackwardPlan backward_plan(const slicemoe_config &c);
 // Matrix-core expert backward (backward_mfma.hip): shapes it takes, bytes of its repacked weights, and the launch
 // (row gradients, dL/dp, and slots of partial weight gradients).
 bool backward_mfma_shape(const slicemoe_config &c);
-size_t backward_mfma_packed_bytes(const slicemoe_config &c);
+size_t backward_mfma_packed_bytes(const slicemoe_config &c);   // (of a shape they take)
 // Matrix-core router backward (backward_router_mfma.hip): shapes it takes, bytes of its scratch (repacked router and
 // the dL/dg tables), and the launch (dL/dh and backward_router_mfma_slots slots of partial weight gradients).
 bool backward_router_mfma_shape(const slicemoe_config &c);
-size_t backward_router_mfma_scratch_bytes(const slicemoe_config &c);
+size_t backward_router_mfma_scratch_bytes(const slicemoe_config &c);   // (of a shape they take)
 hipError_t launch_backward_router_mfma(const slicemoe_config &c, const void *h,
                                        const RouteVariant &v, const float *drop_u, float rate, const int32_t *idx,
                                        const int32_t *inv, const float *dpk, const float *dxrow, void *d_h, void *scratch,
@@ -180,17 +181,15 @@ struct SideStream {
     hipStream_t stream;
     hipEvent_t fork, join;
 };
-hipError_t launch_backward_expert_mfma(const slicemoe_config &c, const void *h, const void *d_out,
+struct BackwardWeightsPlan;   // bwd_mfma.h
+hipError_t launch_backward_expert_mfma(const slicemoe_config &c, const BackwardWeightsPlan &W, const void *h, const void *d_out,
                                        const float *pk, const int32_t *offsets, const int32_t *perm, void *packed,
                                        size_t slot_floats, float *dxrow, float *dpk, float *part, hipStream_t s,
                                        const SideStream *side = nullptr);
-// Slots of partial weight gradients to reserve: at least what the call uses, and never fewer for more tokens, so that a workspace made for
-// the largest batch of a layer takes its smaller ones, however those are split and whichever kernels they run on.
-long long backward_weights_slots_bound(const slicemoe_config &c);
+// The router's slots to reserve: at least what the call uses, and never fewer for more tokens (a unit more per block is fewer blocks).
 long long backward_router_mfma_slots_bound(const slicemoe_config &c);
 long long backward_generic_router_slots_bound(const slicemoe_config &c);
 // The fp32 backward of every other shape (backward_generic.hip): same outputs.
-long long backward_generic_expert_slots(const slicemoe_config &c);
 long long backward_generic_router_slots(const slicemoe_config &c);
 hipError_t launch_backward_expert_generic(const slicemoe_config &c, const void *h, const slicemoe_weights &w, const void *d_out,
                                           const float *pk, const int32_t *offsets, const int32_t *perm, size_t slot_floats, float *dxrow,

@@ -29,13 +29,13 @@ constexpr int onepass_pass_tiles(int ds, int He) { return (He / 32 + onepass_pas
 //   He  768 (4)          128 units 110.4 / 102.3, 192 units 108.4 / 109.9, 256 units 107.6 / 117.8, 3000 units 286 / 287, 4096 units 383 / 381
 //           4 experts    128 units 106.9 / 94.3, 192 units 107.6 / 101.4, 256 units 108.0 / 108.9
 //   He 1536 (8)          1536 units 300 / 453, 8192 units 1208 / 1178
+constexpr bool onepass_in_every_batch(int ds, int He) { return ds == 24 || ds == 48 || (ds == 96 && onepass_passes(ds, He) == 1); }
 constexpr bool onepass_depends_on_batch(int ds, int He) { return ds == 96 && onepass_passes(ds, He) > 1; }
 constexpr bool onepass_chosen(int ds, int He, long long units, long long cus)
 {
     const int passes = onepass_passes(ds, He);
-    if (ds == 24 || ds == 48) return true;
-    if (ds != 96) return false;
-    return passes == 1 || (passes == 2 ? units <= cus || units >= 10 * cus : (passes <= 4 && 4 * units <= 3 * cus) || units >= 4 * passes * cus);
+    if (!onepass_depends_on_batch(ds, He)) return onepass_in_every_batch(ds, He);
+    return passes == 2 ? units <= cus || units >= 10 * cus : (passes <= 4 && 4 * units <= 3 * cus) || units >= 4 * passes * cus;
 }
 
 }  // namespace slicemoe
