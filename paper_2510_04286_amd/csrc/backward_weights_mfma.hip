@@ -515,7 +515,7 @@ BackwardWeightsPlan backward_weights_plan(const slicemoe_config &c)
     const long long units = ((long long)c.T * c.S * c.k + kUnit - 1) / kUnit;
     BackwardWeightsPlan one = backward_expert_plan(c), two = weights_kernel_plan(c);
     one.reserve = two.reserve = one.reserve > two.reserve ? one.reserve : two.reserve;
-    return onepass_chosen(ds, c.He, units, num_compute_units()) ? one : two;
+    return onepass_chosen(ds, c.He, c.E, units, num_compute_units()) ? one : two;
 }
 
 template <int DS, int WAVES, int NBUF, bool WLDS, bool FUSE, int TERMS, int MINWAVES>

@@ -20,22 +20,32 @@ constexpr int onepass_pass_tiles(int ds, int He) { return (He / 32 + onepass_pas
 
 // Widths 24 and 48: always.  Backward of 32 to 8192 units, He 192 .. 3072, 4 and 16 experts, against the two kernels (one below He 288):
 // width 48 1.06 to 1.76 times their speed, width 24 0.99 to 1.8.
-// Width 96, for units of 32 rows: where one pass does (He <= 192: 1.09 to 1.5); in small batches, up to a unit per CU where there are two passes
-// and up to three quarters of that where there are three or four (a block has two units, a position of the split goes to each expert's
-// beginning); and where a block has so many that starting the passes one after the other is little beside them -- the two kernels' groups of
-// hidden tiles run side by side.  Backward in us, two kernels / this one, 256 CUs, 16 experts unless stated:
+// Width 96, for units of 32 rows: where one pass does (He <= 192: 1.09 to 1.5); in batches of up to a unit per CU where there are two to four
+// passes -- with four only up to three quarters of that, where the row gradients' kernel is at its best: at most 32 experts (its tiles of 256 rows
+// are mostly full) and hidden tiles that it streams by three and more (rows_chunk, a divisor of their number); and where a block has so many units
+// that starting the passes one after the other is little beside them -- the two kernels' groups of hidden tiles run side by side.
+// Backward in us, two kernels / this one, 256 CUs, 16 experts unless stated:
 //   He  384 (2 passes)   128 units 82.2 / 73.2, 256 units 89.7 / 84.4, 512 units 89.6 / 97.5, 2048 units 157.1 / 157.0, 3000 units 187 / 174
-//   He  480 (3)          128 units 88.6 / 85.5, 192 units 89.0 / 90.6, 256 units 88.4 / 96.1, 2600 units 203 / 213, 4096 units 283 / 265
-//   He  768 (4)          128 units 110.4 / 102.3, 192 units 108.4 / 109.9, 256 units 107.6 / 117.8, 3000 units 286 / 287, 4096 units 383 / 381
-//           4 experts    128 units 106.9 / 94.3, 192 units 107.6 / 101.4, 256 units 108.0 / 108.9
+//   He  416 (3)          256 units 110.1 / 90.9; 4 experts 108.9 / 85.8, 64 143.5 / 128.4
+//   He  480, 576         192 units 89.0 / 90.6 and 94.5 / 93.1, 256 units 88.4 / 96.1 and 96.7 / 100.8; He 576, 4 experts 94.4 / 94.6, 48 139.2 / 128.9;
+//                        2600 units 203 / 213, 4096 units 283 / 265
+//   He  672, 768 (4)     128 units 102.6 / 98.2 and 110.4 / 102.3, 192 units 101.4 / 103.4 and 108.1 / 107.3, 256 units 101.8 / 112.2 and 107.3 / 117.5;
+//                        256 units, 4 experts 98.9 / 104.2 and 107.4 / 109.6, 48 149.2 / 142.4 and 153.0 / 149.6; 3000 units 286 / 287, 4096 units 383 / 381
 //   He 1536 (8)          1536 units 300 / 453, 8192 units 1208 / 1178
+constexpr int rows_chunk(int He)   // hidden tiles that the row gradients' kernel streams at a time at width 96: 18 KB each in 140 KB
+{
+    for (int c = 7; c > 1; --c)
+        if (He / 32 % c == 0) return c;
+    return 1;
+}
 constexpr bool onepass_in_every_batch(int ds, int He) { return ds == 24 || ds == 48 || (ds == 96 && onepass_passes(ds, He) == 1); }
 constexpr bool onepass_depends_on_batch(int ds, int He) { return ds == 96 && onepass_passes(ds, He) > 1; }
-constexpr bool onepass_chosen(int ds, int He, long long units, long long cus)
+constexpr bool onepass_chosen(int ds, int He, int E, long long units, long long cus)
 {
-    const int passes = onepass_passes(ds, He);
     if (!onepass_depends_on_batch(ds, He)) return onepass_in_every_batch(ds, He);
-    return passes == 2 ? units <= cus || units >= 10 * cus : (passes <= 4 && 4 * units <= 3 * cus) || units >= 4 * passes * cus;
+    const int passes = onepass_passes(ds, He);
+    const bool early = passes == 4 && E <= 32 && rows_chunk(He) >= 3;
+    return (passes <= 4 && units <= (early ? 3 * cus / 4 : cus)) || units >= cus * (passes <= 2 ? 10 : 4 * passes);
 }
 
 }  // namespace slicemoe

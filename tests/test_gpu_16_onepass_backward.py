@@ -95,9 +95,11 @@ EDGES = {   # (shape, whether the one pass takes it at 256 compute units)
     "w96_2_passes_257_units": (shape(96, 224, 7, 1, 8193, S=1), False),
     "w96_2_passes_2559_units": (shape(96, 224, 5, 2, 40944, S=1), False),
     "w96_2_passes_2560_units": (shape(96, 224, 5, 2, 40945, S=1), True),
-    "w96_3_passes_192_units": (shape(96, 416, 4, 1, 6144, S=1), True),
-    "w96_3_passes_193_units": (shape(96, 416, 4, 1, 6145, S=1), False),
-    "w96_4_passes_192_units": (shape(96, 608, 3, 3, 512, S=4, cf=1.0), True),
+    "w96_3_passes_256_units": (shape(96, 416, 4, 1, 8192, S=1), True),
+    "w96_3_passes_257_units": (shape(96, 416, 4, 1, 8193, S=1), False),
+    "w96_4_passes_192_units": (shape(96, 672, 3, 3, 512, S=4, cf=1.0), True),
+    "w96_4_passes_193_units": (shape(96, 672, 3, 1, 6145, S=1), False),
+    "w96_4_passes_prime_193_units": (shape(96, 608, 3, 1, 6145, S=1), True),
     "w96_5_passes": (shape(96, 800, 3, 2, 100, S=1), False),   # (k = 2: with one assignment the dropout makes every probability one)
 }
 
@@ -111,7 +113,7 @@ def test_both_sides_of_the_choice_against_64_bits(name):
     case, onepass = EDGES[name]
     s, h, w = make_inputs(case)
     units, cus = (s.Na + 31) // 32, torch.cuda.get_device_properties(0).multi_processor_count
-    assert cus != 256 or split().chosen(s.ds, s.He, units, cus) == onepass
+    assert cus != 256 or split().chosen(s.ds, s.He, s.E, units, cus) == onepass
     cfg = B.config_of(s)
     assert B.slicemoe_backward_uses_mfma(cfg) == 1
     noise, drop_u = wl.make_router_draws(s)
