@@ -98,7 +98,9 @@ EDGES = {   # (shape, whether the one pass takes it at 256 compute units)
     "w96_3_passes_256_units": (shape(96, 416, 4, 1, 8192, S=1), True),
     "w96_3_passes_257_units": (shape(96, 416, 4, 1, 8193, S=1), False),
     "w96_4_passes_192_units": (shape(96, 672, 3, 3, 512, S=4, cf=1.0), True),
-    "w96_4_passes_193_units": (shape(96, 672, 3, 1, 6145, S=1), False),
+    "w96_4_passes_224_units": (shape(96, 672, 3, 1, 7168, S=1), True),
+    "w96_4_passes_225_units": (shape(96, 672, 3, 1, 7169, S=1), False),
+    "w96_4_passes_16_experts_193_units": (shape(96, 672, 16, 1, 6145, S=1), False),
     "w96_4_passes_prime_193_units": (shape(96, 608, 3, 1, 6145, S=1), True),
     "w96_5_passes": (shape(96, 800, 3, 2, 100, S=1), False),   # (k = 2: with one assignment the dropout makes every probability one)
 }

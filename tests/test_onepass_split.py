@@ -41,12 +41,12 @@ def test_every_hidden_tile_is_in_one_pass(ds):
 
 
 @pytest.mark.parametrize("He,E,small,large", [(192, 16, None, None), (224, 16, 256, 2560), (384, 64, 256, 2560), (416, 16, 256, 3072), (576, 16, 256, 3072),
-                                              (608, 16, 256, 4096), (672, 16, 192, 4096), (768, 16, 192, 4096), (768, 32, 192, 4096), (768, 33, 256, 4096),
+                                              (608, 16, 256, 4096), (672, 16, 192, 4096), (672, 15, 224, 4096), (768, 16, 192, 4096), (768, 32, 192, 4096), (768, 33, 256, 4096),
                                               (704, 16, 256, 4096), (800, 16, 0, 5120), (1536, 16, 0, 8192)])
 def test_the_choice_at_width_96(He, E, small, large):
     """At 256 compute units: one pass up to `small` units of 32 rows and from `large` on, the two kernels between."""
     s = split()
-    for units in (1, 100, 191, 192, 193, 255, 256, 257, 1000, 2559, 2560, 3071, 3072, 4095, 4096, 5119, 5120, 8191, 8192, 100000):
+    for units in (1, 100, 191, 192, 193, 223, 224, 225, 255, 256, 257, 1000, 2559, 2560, 3071, 3072, 4095, 4096, 5119, 5120, 8191, 8192, 100000):
         assert s.chosen(96, He, E, units, 256) == (1 if small is None or units <= small or units >= large else 0), units
 
 
